@@ -170,3 +170,64 @@ def tolerance(case):
     neighbour) and 7e-3 for a single value (one bf16 step); fp32 outputs 6e-7 and 4e-5 (the weight gradient's
     derivative factor next to its pole).  Thresholds, scales and row pointers come out the same."""
     return {"rel": 3e-4, "max": 0.03} if case["dtype"] == "bf16" else {"rel": 2.5e-6, "max": 2e-4}
+
+
+# The layer once more, from its definition and in plain torch: what decides a code, a threshold or a residual
+# entry in fp32 (as the layer defines it), the products and everything behind them in fp64.
+
+def _codes(x, dim):
+    """E2M1 values (fp64) and fp32 scales of x [..] under one scale 6 / absmax along dim; midpoints go up."""
+    top = x.abs().amax(dim=dim, keepdim=True)
+    gamma = (6.0 / top.double()).float()   # the correctly rounded quotient: a code on a midpoint hangs on its last bit
+    gamma = torch.where((top > 0) & torch.isfinite(gamma), gamma, torch.ones_like(gamma))
+    pos = [0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0]
+    grid = torch.tensor([-v for v in pos[:0:-1]] + pos, device=x.device)
+    mid = (grid[1:] + grid[:-1]) / 2
+    return grid.double()[torch.bucketize(x * gamma, mid, right=True)], gamma
+
+
+def exact(case, seed):
+    s = prepare(dict(case, run="step", cached=False), seed)
+    A, W, dY = s["A"].float(), s["W"].float(), s["dY"].float()
+    M, K = A.shape
+    out = {}
+    qW, gW = _codes(W, 0)
+    rest = None
+    if case["alpha"] < 1.0:
+        token = case["scope"] == "token"
+        flat = (A if token else A.reshape(1, -1)).sort(dim=1).values
+        k = math.floor((1.0 - case["alpha"]) * flat.shape[1])
+        lo, hi = flat[:, k:k + 1], flat[:, flat.shape[1] - 1 - k:flat.shape[1] - k]
+        del flat
+        Ac = torch.minimum(torch.maximum(A, lo), hi)
+        rest = A - Ac
+        per_row = (rest != 0).sum(dim=1)
+        row_ptr = torch.zeros(M + 1, dtype=torch.int64, device=A.device)
+        torch.cumsum(per_row, 0, out=row_ptr[1:])
+        rest = rest.double()
+    else:
+        Ac = A
+    if case["run"] != "backward":
+        qA, gA = _codes(Ac, 1)
+        Y = (qA @ qW) / (gA.double() * gW.double())
+        if rest is not None:
+            Y += rest @ W.double()
+        out.update(Y=Y, gamma_W=gW.reshape(-1))
+        if rest is not None:
+            out.update(thresholds=torch.cat([lo, hi], dim=1).reshape(s["ctx"].thresholds.shape), row_ptr=row_ptr,
+                       nnz=row_ptr[-1:].reshape(s["ctx"].nnz.shape))
+    if case["run"] != "forward":
+        qY, gY = _codes(dY, 1)
+        qR, gR = _codes(W, 1)
+        out["dA"] = (qY @ qR.t()) / (gY.double() * gR.reshape(1, -1).double())
+        qC, gC = _codes(Ac, 0)
+        qD, gD = _codes(dY, 0)
+        dW = (qC.t() @ qD) / (gC.reshape(-1, 1).double() * gD.double())
+        if rest is not None:
+            dW += rest.t() @ dY.double()
+        a = (W * gW).abs()
+        left = torch.where(a >= 4, 4.0, torch.where(a >= 2, a.floor(), (2 * a).floor() / 2)).double()
+        width = torch.where(a >= 4, 2.0, torch.where(a >= 2, 1.0, 0.5)).double()
+        t = (2.0 * (a.double() - left) / width - 1.0).abs()
+        out["dW"] = dW * torch.clamp(t ** (1.0 / DGE_K - 1.0) / DGE_K, max=DGE_CAP)
+    return out
