@@ -53,7 +53,6 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
                              hipStream_t s);
-int64_t fp4_spmm_long_list_cap(int64_t capacity);
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                              float* gamma, hipStream_t s);
 int fp8_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes_t,
@@ -64,10 +63,10 @@ int fp4_launch_gemm_mixed(const uint8_t* L, const float* gl, const uint8_t* Rt, 
 int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q);
 int fp4_launch_order_rows(const int64_t* row_ptr, int64_t rows, int64_t nidx, int64_t capacity,
                           const int32_t* u_idx, const float* u_val, int32_t* idx, float* val, hipStream_t s);
-int64_t fp4_spmm_scratch_words(int64_t list_cap, int64_t Q, int64_t N);
+int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16);
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    int64_t list_cap, hipStream_t s);
+                    hipStream_t s);
 
 namespace {
 
@@ -135,7 +134,7 @@ FwdWs carve_fwd(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   // the workspace query does not know alpha, so it provides for alpha >= 0.9
   w.occ = carve_occ(c, M, provisioned_entries(M, K));
   w.R = dt == FP4_BF16 ? c.take<float>((size_t)(M * N)) : nullptr;
-  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(fp4_spmm_long_list_cap(provisioned_entries(M, K)), K, N));
+  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16));
   w.tg = c.take<uint32_t>((size_t)fp4_tensor_gamma_scratch_words());
   return w;
 }
@@ -149,7 +148,7 @@ FwdWs carve_fwd_mixed(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) 
   w.amax = c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(K, N));
   w.occ = carve_occ(c, M, provisioned_entries(M, K));
   w.R = dt == FP4_BF16 ? c.take<float>((size_t)(M * N)) : nullptr;
-  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(fp4_spmm_long_list_cap(provisioned_entries(M, K)), K, N));
+  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16));
   w.tg = nullptr;
   return w;
 }
@@ -169,7 +168,7 @@ struct WgradWs {
   int64_t* t_ptr; int32_t* t_idx; float* t_val; int32_t* u_idx; float* u_val; int32_t* t_scratch;
   int32_t* sp_scratch;
 };
-WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N) {
+WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   WgradWs w;
   w.qAt = c.take<uint8_t>((size_t)(K * M / 2));
   w.gAk = c.take<float>((size_t)K);
@@ -183,7 +182,7 @@ WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N) {
   w.u_idx = c.take<int32_t>((size_t)cap);
   w.u_val = c.take<float>((size_t)cap);
   w.t_scratch = c.take<int32_t>((size_t)fp4_csr_transpose_scratch_words(M, K));
-  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(fp4_spmm_long_list_cap(cap), M, N));
+  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(K, M, N, dt == FP4_BF16));
   return w;
 }
 
@@ -219,15 +218,15 @@ extern "C" size_t fp4_workspace_bytes(int op, int64_t M, int64_t K, int64_t N, f
     case FP4_OP_OCC: carve_occ(c, M, provisioned_entries(M, K)); break;
     case FP4_OP_FWD: carve_fwd(c, M, K, N, dt); break;
     case FP4_OP_DGRAD: carve_dgrad(c, M, K, N); break;
-    case FP4_OP_WGRAD: carve_wgrad(c, M, K, N); break;
+    case FP4_OP_WGRAD: carve_wgrad(c, M, K, N, dt); break;
     case FP4_OP_PREPARE: c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(K, N)); break;
     case FP4_OP_FWD_MIXED: carve_fwd_mixed(c, M, K, N, dt); break;
     case FP4_OP_BWD:
       carve_dgrad(c, M, K, N);
-      carve_wgrad(c, M, K, N);
+      carve_wgrad(c, M, K, N, dt);
       c.take<uint16_t>((size_t)fp4_dual_axis_part_elems(M, N));
       break;
-    case FP4_OP_SPMM: c.take<int32_t>((size_t)fp4_spmm_scratch_words(M + 2, K, N)); break;   // long-row list: at most M rows
+    case FP4_OP_SPMM: c.take<int32_t>((size_t)fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16)); break;
     default: return 0;
   }
   return c.off + 256;
@@ -405,8 +404,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
     if (rc) return rc;
     // Delta_A W with the unquantized W, fp32; lands where the GEMM epilogue picks it up
     float* R = bf16 ? w.R : reinterpret_cast<float*>(Y);
-    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch,
-                         fp4_spmm_long_list_cap(provisioned_entries(M, K)), s);
+    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, s);
     if (rc) return rc;
     addend = R;
   } else {
@@ -509,8 +507,7 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
     }
     if (rc) return rc;
     float* R = bf16 ? w.R : reinterpret_cast<float*>(Y);
-    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch,
-                         fp4_spmm_long_list_cap(provisioned_entries(M, K)), s);
+    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, s);
     if (rc) return rc;
     addend = R;
   } else {
@@ -588,7 +585,7 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
   hipStream_t s = (hipStream_t)stream;
   const int bf16 = dt == FP4_BF16;
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
-  WgradWs w = carve_wgrad(c, M, K, N);
+  WgradWs w = carve_wgrad(c, M, K, N, dt);
   if (saved->scope != FP4_OCC_TENSOR && saved->scope != FP4_OCC_TOKEN) return FP4_ERR_DTYPE;
   const int token = occ && saved->scope == FP4_OCC_TOKEN;   // thresholds: one pair per token
   // as the forward pass: entries beyond what the workspaces provide for cannot exist
@@ -603,8 +600,7 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
-    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch,
-                         fp4_spmm_long_list_cap(provisioned_entries(M, K)), s);
+    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, s);
     if (rc) return rc;
     addend = dW;
   }
@@ -631,7 +627,7 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   const int bf16 = dt == FP4_BF16;
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
   DgradWs d = carve_dgrad(c, M, K, N);
-  WgradWs w = carve_wgrad(c, M, K, N);
+  WgradWs w = carve_wgrad(c, M, K, N, dt);
   uint16_t* part = c.take<uint16_t>((size_t)fp4_dual_axis_part_elems(M, N));
   // dY: per token (codes for the activation gradient) and, in the same read, per-block column maxima
   int rc = fp4_launch_quantize_rows_colmax(dY, bf16, M, N, N, d.qdY, d.gdY, part, s);
@@ -662,8 +658,7 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
-    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch,
-                         fp4_spmm_long_list_cap(provisioned_entries(M, K)), s);
+    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, s);
     if (rc) return rc;
     addend = dW;
   }
@@ -681,7 +676,7 @@ extern "C" int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx,
   if (!aligned16(D) || !aligned16(R)) return FP4_ERR_ARG;
   if (!workspace || workspace_bytes < fp4_workspace_bytes(FP4_OP_SPMM, P, Q, N, dt)) return FP4_ERR_WORKSPACE;
   int32_t* scratch = reinterpret_cast<int32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
-  // no entry limit besides row_ptr itself; the long-row list is sized by P
-  return fp4_launch_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt == FP4_BF16, N, R, scratch, P + 2,
+  // no entry limit besides row_ptr itself
+  return fp4_launch_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt == FP4_BF16, N, R, scratch,
                          (hipStream_t)stream);
 }

@@ -13,7 +13,7 @@
 //     so a D element is fetched from L2 once per 1024 output rows;
 //   * a thread walks its row's entries (ascending columns) slab by slab: per non-zero 64 FMAs
 //     against one LDS row.
-// Rows much longer than the rest (the outlier channels of the transposed residual) would
+// Rows much longer than the rest (the outlier channels of the transposed residual, spmm_long_limit) would
 // stall their workgroup; they are left out of the tiled kernel and handled by a kernel that
 // spreads one row's entries over a workgroup and reduces.
 #include "fp4_common.h"
@@ -39,7 +39,6 @@ constexpr int SP_WPR = SP_KS / 64;    // waves whose 64 x 64 tiles fit the slab 
 static_assert(SP_KS % SP_RPP == 0, "whole staging passes");
 constexpr int SP_LD = SP_COLS;   // LDS row (floats), unpadded: see the lane swizzle in the kernel
 constexpr int SP_XM = 15;        // lane bits that rotate the order in which a thread reads a D row
-constexpr int LONG_ROW = 2048;  // entries above which a row goes to the long-row kernel
 
 template <class DT>
 FP4_D void load8g(const void* base, int64_t off, int valid, float (&v)[8]) {
@@ -85,11 +84,12 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
   // Entry positions are kept as 32-bit offsets from the workgroup's first entry (a workgroup's
   // rows hold fewer than 2^31 entries: the launcher bounds Q); the base stays in scalar registers.
   const int64_t ebase = row_ptr[min((int64_t)blockIdx.x * SP_ROWS, P)];
+  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
   uint32_t cur = 0, end = 0;
   if (row < P) {
     const int64_t b = row_ptr[row];
     int64_t e = max(min(row_ptr[row + 1], capacity), b);
-    if (e - b > LONG_ROW) e = b;   // long rows belong to the long-row kernels
+    if (e - b > long_limit) e = b;   // long rows belong to the long-row kernels
     cur = (uint32_t)(b - ebase);
     end = (uint32_t)(e - ebase);
   }
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
   // more so that the stores run along rows: 16 lanes x 16 B per row, four rows per instruction.
   // A wave's 64 x 64 tile takes 16 KiB, so the workgroup stores in two rounds of eight waves.
   bool skip = row >= P;   // rows outside the matrix, and long rows (other kernels write those)
-  if (!skip) skip = min(row_ptr[row + 1], capacity) - row_ptr[row] > LONG_ROW;
+  if (!skip) skip = min(row_ptr[row + 1], capacity) - row_ptr[row] > spmm_long_limit(row_ptr, P, Q, capacity);
   s_skip[tid] = skip ? 1 : 0;
   __syncthreads();   // everyone is done with the last slab
   const int lane = tid & 63, wave = tid >> 6;
@@ -268,22 +268,23 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
 }
 
 // ---- long rows -------------------------------------------------------------------------------
-// Rows above LONG_ROW entries, listed in ascending order by one workgroup (ballot + scan), so the
+// Long rows, listed in ascending order by one workgroup (ballot + scan), so the
 // split between the two long-row kernels below does not depend on timing.
-__global__ __launch_bounds__(1024) void find_long_rows_kernel(const int64_t* row_ptr, int64_t P, int64_t capacity,
+__global__ __launch_bounds__(1024) void find_long_rows_kernel(const int64_t* row_ptr, int64_t P, int64_t Q, int64_t capacity,
                                                               int32_t* list, int32_t* count, int32_t list_cap) {
   // 16 x 1024 rows per turn: all their row_ptr loads in flight at once, then one scan over the
   // 16 x 16 (round, wave) counts instead of a barrier-separated step per 1024 rows
   __shared__ int s_cnt[16 * 16];   // [round][wave] counts, then their exclusive prefix in that order
   __shared__ int s_base;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
   if (tid == 0) s_base = 0;
   for (int64_t r0 = 0; r0 < P; r0 += 16 * 1024) {
     uint32_t flags = 0;
 #pragma unroll
     for (int it = 0; it < 16; ++it) {
       const int64_t row = r0 + it * 1024 + tid;
-      const bool is_long = row < P && min(row_ptr[row + 1], capacity) - row_ptr[row] > LONG_ROW;
+      const bool is_long = row < P && min(row_ptr[row + 1], capacity) - row_ptr[row] > long_limit;
       flags |= (is_long ? 1u : 0u) << it;
     }
 #pragma unroll
@@ -844,34 +845,45 @@ __global__ __launch_bounds__(256) void csr_bitmap_sort_kernel(const int64_t* seg
 // ---- launchers ---------------------------------------------------------------------------------
 int fp4_trace_open(int kind, hipStream_t stream);
 void fp4_trace_close(int slot, hipStream_t stream);
-int64_t fp4_spmm_long_list_cap(int64_t capacity) { return capacity / LONG_ROW + 2; }
-
-// int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[list_cap], then
-// the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N].
-int64_t fp4_spmm_scratch_words(int64_t list_cap, int64_t Q, int64_t N) {
+int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q);
+int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
+                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, hipStream_t s);
+// int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
+// the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
+static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
+static int64_t spmm_long_words(int64_t P, int64_t Q, int64_t N) {
   const int64_t slices = (Q + LD_SLICE - 1) / LD_SLICE;
-  return 64 + ((list_cap + 63) / 64) * 64 + slices * LD_CAP * N;
+  return spmm_list_words(P) + (slices * LD_CAP * N + 63) / 64 * 64;
+}
+int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16) {
+  return spmm_long_words(P, Q, N) + (bf16 ? (fp4_spmm_mfma_scratch_bytes(P, Q) + 3) / 4 : 0);
 }
 
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    int64_t list_cap64, hipStream_t s) {
+                    hipStream_t s) {
   if (P == 0 || N == 0) return FP4_OK;
   if (Q >= ((int64_t)1 << 21)) return FP4_ERR_SHAPE;   // 32-bit entry offsets inside a workgroup's 1024 rows
-  const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
-  const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);
+  int rc = 1;
   if (bf16)
-    hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
-  else
-    hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
-  fp4_trace_close(trace_slot, s);
-  if (Q > LONG_ROW && capacity > LONG_ROW) {   // otherwise no row can be long
+    rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), s);
+  if (rc != 0 && rc != 1) return rc;
+  if (rc == 1) {
+    const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
+    const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);
+    if (bf16)
+      hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+    else
+      hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+    fp4_trace_close(trace_slot, s);
+  }
+  if (Q > 64 && capacity > 64) {   // otherwise no row can be long
     int32_t* count = scratch;
     int32_t* list = scratch + 64;
-    const int32_t list_cap = (int32_t)std::min<int64_t>(list_cap64, P);
-    float* part = reinterpret_cast<float*>(scratch + 64 + ((list_cap64 + 63) / 64) * 64);
+    const int32_t list_cap = (int32_t)P;
+    float* part = reinterpret_cast<float*>(scratch + spmm_list_words(P));
     const int slices = (int)((Q + LD_SLICE - 1) / LD_SLICE);
-    hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, capacity, list, count, list_cap);
+    hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count, list_cap);
     const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices, LD_CAP / LD_LB);
     if (bf16)
       hipLaunchKernelGGL((spmm_long_dense_kernel<BF16>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,

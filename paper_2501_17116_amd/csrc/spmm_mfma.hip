@@ -1,0 +1,412 @@
+// The residual product R[P x N] = S D (Sec. 3.2) for bf16 D on the matrix cores.
+//
+// S has about 2 % scattered entries.  Sixteen rows of it together touch about 28 % of the columns, so a
+// group of 16 rows is packed into "slots": one slot per column that any of the 16 rows has an entry in,
+// holding that column's 16 values (zero where a row has none) in bf16.  32 slots make one step of
+// v_mfma_f32_16x16x32_bf16: A = the 16 x 32 packed values, B = the 32 rows of D that the slots name,
+// gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three, and its
+// column takes as many slots: products are exact, sums are fp32, nothing is rounded to 16 bits.
+//
+// A lane owns 8 adjacent columns of D, so a gathered row arrives as one 16-byte LDS read per lane,
+// 256 contiguous bytes per quarter wave: free of bank conflicts whatever rows the slots name.  The matrix
+// core wants eight k values of one column per lane; v_perm_b32 turns eight rows x eight columns around.
+//
+// D passes through LDS as a ring of chunks (SM_KC rows x SM_NT columns, direct-to-LDS loads two chunks
+// ahead).  A slot may be multiplied in any phase in which its chunk is resident, and the packing decides
+// how many steps a group runs in each phase (a prefix of its slots, S[phase]): the steps stay full and the
+// waves of a workgroup in step with each other although the entries of a chunk are few and random.
+//
+// Bound: the matrix core (16 cycles an instruction), the LDS reads and the vector instructions (32 v_perm_b32 and 8
+// addresses a step) each leave room for about twice what is reached.  Residual of a 16384 x 4096 -> 12288 layer (2 %,
+// 1.3 M entries), packing included: 926 us, 35 TFLOP/s of useful products; plain fp32 FMAs fed from LDS (spmm.hip):
+// 1454 us.  6 %: 1487 against 2854 us; 0.2 %: 551 against 589 us.
+#include "fp4_common.h"
+#include "fp4_measure.h"
+
+#include <algorithm>
+#include <type_traits>
+
+int fp4_trace_open(int kind, hipStream_t stream);
+void fp4_trace_close(int slot, hipStream_t stream);
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int SM_KC = 128;       // rows of D per chunk
+constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): three to multiply from, two on their way
+constexpr int SM_AHEAD = 2;
+constexpr int SM_SLACK = SM_RING - SM_AHEAD - 1;   // phases a chunk stays after the one it arrives in
+constexpr int SM_NT = 128;       // columns of R per workgroup
+constexpr int SM_ROWB = SM_NT * 2;
+constexpr int SM_CHUNKB = SM_KC * SM_ROWB;
+constexpr int SM_STRIP = 8;      // column blocks that an XCD works on side by side
+constexpr int PK_TPR = 16;       // packing threads per row
+constexpr int64_t SM_MAXQ = 24576;   // the packing keeps a nibble per column and group in LDS, within 64 KiB
+static_assert(SM_ROWB == 256, "a quarter wave covers a row of a chunk with 16 bytes a lane");
+
+// steps a group of 16 rows has room for: every column once, and a quarter more for values of several terms
+inline int64_t sm_cap(int64_t Q) { return (Q + 31) / 32 + (Q + 127) / 128 + 3; }
+inline int64_t sm_phases(int64_t Q) { return (Q + SM_KC - 1) / SM_KC; }
+
+// v as the exact sum of up to three bf16 numbers (nearest first); returns how many
+FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const uint32_t u = f2u(v);
+    uint32_t h = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+    if ((h & 0x7f80u) == 0x7f80u) h = u >> 16;   // no rounding up to infinity
+    if ((u & 0x7f800000u) == 0x7f800000u) h = (u >> 16) | ((u & 0x7fffffu) != 0u ? 1u : 0u);
+    t[i] = i == 0 || (v != 0.0f) ? h : 0u;
+    if (i == 0 || v != 0.0f) n = i + 1;
+    const float r = v - u2f(h << 16);
+    v = (u & 0x7f800000u) == 0x7f800000u ? 0.0f : r;
+  }
+  return n;
+}
+
+// One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
+// steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the general
+// path (more slots than there is room for, or columns that repeat inside a row).
+template <int G>
+__global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
+                                                               const int32_t* __restrict__ col_idx,
+                                                               const float* __restrict__ val, int64_t capacity, int64_t P,
+                                                               int Q, int cap, int phases, uint8_t* __restrict__ a_buf,
+                                                               uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
+                                                               int32_t* __restrict__ steps) {
+  constexpr int ROWS = 16 * G, THREADS = ROWS * PK_TPR;
+  extern __shared__ uint32_t pk_lds[];
+  const int words = phases * (SM_KC / 8);
+  uint32_t* const nib = pk_lds;                                                // [G][words] a nibble per column: as many bits as slots
+  int32_t* const start = reinterpret_cast<int32_t*>(nib + G * words);       // [G][phases] slot count, then first slot
+  int32_t* const ends = start + G * phases;                                 // [phases] the groups' furthest end of a chunk's slots
+  uint16_t* const pre = reinterpret_cast<uint16_t*>(ends + phases);            // [G][words] slots of the chunk before this word
+  __shared__ int64_t s_b[ROWS];
+  __shared__ int s_n[ROWS];
+  __shared__ int s_bad, s_total[G], s_steps;
+  const int tid = threadIdx.x;
+  const int64_t bundle = blockIdx.x;
+  for (int i = tid; i < G * words; i += THREADS) nib[i] = 0;
+  if (tid < ROWS) {
+    const int64_t row = bundle * ROWS + tid;
+    int64_t b = 0, n = 0;
+    if (row < P) {
+      b = row_ptr[row];
+      n = max(min(row_ptr[row + 1], capacity), b) - b;
+      if (n > spmm_long_limit(row_ptr, P, Q, capacity)) n = 0;   // the long-row kernels' business
+    }
+    s_b[tid] = b;
+    s_n[tid] = (int)n;
+  }
+  if (tid == 0) s_bad = 0;
+  if (tid < G) s_total[tid] = 0;
+  __syncthreads();
+  const int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
+  const int grp = br / 16, r = br % 16;
+  const int n = s_n[br];
+  const int32_t* const cp = col_idx + s_b[br];
+  const float* const vp = val + s_b[br];
+  for (int i = rt; i < n; i += PK_TPR) {
+    const int c = cp[i];
+    uint32_t t[3];
+    const int nt = bf16_terms(vp[i], t);
+    if ((uint32_t)c >= (uint32_t)Q || (i > 0 && cp[i - 1] >= c)) { s_bad = 1; continue; }
+    atomicOr(&nib[grp * words + (c >> 3)], ((1u << nt) - 1u) << (4 * (c & 7)));
+  }
+  __syncthreads();
+  for (int i = tid; i < G * phases; i += THREADS) {
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < SM_KC / 8; ++w) {
+      pre[i * (SM_KC / 8) + w] = (uint16_t)sum;
+      sum += __popc(nib[i * (SM_KC / 8) + w]);
+    }
+    start[i] = sum;
+    atomicAdd(&s_total[i / phases], sum);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    // S follows an even pace, between what must be done (chunk c - SM_SLACK leaves) and what fills whole steps
+    int total = 0, e[G], S = 0;
+    for (int j = 0; j < G; ++j) { total = max(total, (s_total[j] + 31) / 32); e[j] = 0; }
+    int32_t* const sc = sched + bundle * phases;
+    for (int c = 0; c < phases; ++c) {
+      int least = 0x7fffffff, most = 0;
+      for (int j = 0; j < G; ++j) {
+        const int st = max(e[j], 32 * S);
+        e[j] = st + start[j * phases + c];
+        start[j * phases + c] = st;
+        least = min(least, e[j]);
+        most = max(most, e[j]);
+      }
+      ends[c] = most;
+      const int lo = max(S, c >= SM_SLACK ? (ends[c - SM_SLACK] + 31) / 32 : 0);
+      const int pace = (int)(((int64_t)total * (c + 1) + phases - 1) / phases);
+      S = c == phases - 1 ? max(lo, (most + 31) / 32) : max(min(pace, least / 32), lo);
+      sc[c] = S;
+    }
+    const bool ok = !s_bad && S <= cap;
+    if (!ok)
+      for (int c = 0; c < phases; ++c) sc[c] = 0;
+    s_steps = ok ? S : 0;
+    steps[bundle] = ok ? S : -1;
+  }
+  __syncthreads();
+  const int T = s_steps;
+  if (T == 0) return;
+  uint8_t* const ag = a_buf + (bundle * G + grp) * (int64_t)(cap + 1) * 1024;
+  uint8_t* const og = o_buf + (bundle * G + grp) * (int64_t)(cap + 1) * 64;
+  const u32x4 z = {0u, 0u, 0u, 0u};
+  const int gt = tid % (16 * PK_TPR);   // thread of the group
+  for (int i = gt; i < T * 64; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(ag + (int64_t)i * 16) = z;
+  for (int i = gt; i < T * 4; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(og + (int64_t)i * 16) = z;
+  __syncthreads();   // the zeros are written (a workgroup's stores reach L2 in order) before the values
+  for (int i = rt; i < n; i += PK_TPR) {
+    const int c = cp[i];
+    uint32_t t[3];
+    const int nt = bf16_terms(vp[i], t);
+    const int chunk = c / SM_KC, w = grp * words + (c >> 3);
+    const int pos = start[grp * phases + chunk] + pre[w] + __popc(nib[w] & ((1u << (4 * (c & 7))) - 1u));
+    const uint16_t at = (uint16_t)((chunk % SM_RING) * SM_KC + c % SM_KC);
+    for (int k = 0; k < nt; ++k) {
+      const int p = pos + k;
+      *reinterpret_cast<uint16_t*>(ag + (int64_t)(p >> 5) * 1024 + (((p >> 3) & 3) * 16 + r) * 16 + (p & 7) * 2) = (uint16_t)t[k];
+      *reinterpret_cast<uint16_t*>(og + (int64_t)p * 2) = at;
+    }
+  }
+}
+
+// The general path for one group of 16 rows and the workgroup's columns: plain fp32 sums over the rows' entries.
+FP4_D void sm_general(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
+                      int64_t Q, const uint16_t* D, int64_t N, int64_t row0, int64_t n0, int lane, float* R) {
+  const int64_t col = n0 + lane * 2;   // N is a multiple of 8
+  if (col >= N) return;
+  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
+  for (int64_t row = row0; row < min(row0 + 16, P); ++row) {
+    const int64_t b = row_ptr[row], e = max(min(row_ptr[row + 1], capacity), b);
+    if (e - b > long_limit) continue;
+    float s0 = 0.0f, s1 = 0.0f;
+    for (int64_t i = b; i < e; i += 8) {   // eight rows of D in flight
+      uint32_t d[8];
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int64_t c = i + k < e ? col_idx[i + k] : -1;
+        const bool ok = c >= 0 && c < Q;
+        v[k] = ok ? val[i + k] : 0.0f;
+        d[k] = ok ? *reinterpret_cast<const uint32_t*>(D + c * N + col) : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        s0 = fmaf(v[k], u2f(d[k] << 16), s0);
+        s1 = fmaf(v[k], u2f(d[k] & 0xffff0000u), s1);
+      }
+    }
+    R[row * N + col] = s0;
+    R[row * N + col + 1] = s1;
+  }
+}
+
+// WV waves multiply, G groups of 16 rows each; one more stages D.
+template <int G, int WV>
+__global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t* __restrict__ a_buf, const uint8_t* __restrict__ o_buf,
+                                                            const int32_t* __restrict__ sched, const int32_t* __restrict__ steps,
+                                                            int cap, int phases, int row_blocks, int col_blocks,
+                                                            const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                            const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q,
+                                                            const uint16_t* __restrict__ D, int64_t N, float* __restrict__ R) {
+  __shared__ __attribute__((aligned(16))) uint8_t ring[SM_RING * SM_CHUNKB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Workgroup i runs on XCD i % 8; each XCD takes a contiguous run of tiles, ordered so that the workgroups
+  // it runs at a time form four row blocks x eight column blocks and share D and the packed rows in its L2.
+  const int total = row_blocks * col_blocks, per_xcd = (total + 7) / 8;
+  const int id = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
+  const int strip = id / (SM_STRIP * row_blocks);
+  const int width = min(SM_STRIP, col_blocks - SM_STRIP * strip);
+  const int in_strip = id - SM_STRIP * strip * row_blocks;
+  const int64_t n0 = (int64_t)(SM_STRIP * strip + in_strip % width) * SM_NT;
+  const int rb = in_strip / width;
+  const int64_t bundles = (P + 16 * G - 1) / (16 * G);
+
+  if (wave == WV) {
+    // The staging wave.  Its loads are its own business: a wave's loads return in order, so in a multiplying wave
+    // every operand load would wait for the chunk requested before it.  One instruction fills 4 rows of a chunk;
+    // rows past Q and columns past N read zero (offset out of range).
+    constexpr int LD = SM_KC / 4;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(D) + n0, 0, (int)(uint32_t)((Q * N - n0) * 2), 0x00020000);
+    const bool in_n = n0 + (lane & 15) * 8 < N;
+    const uint32_t rowb = (uint32_t)(N * 2);
+    const uint32_t voff = (uint32_t)(lane >> 4) * rowb + (uint32_t)(lane & 15) * 16u;
+    auto stage = [&](int c) {
+      uint8_t* const slot = ring + (c % SM_RING) * SM_CHUNKB;
+      const int rows = in_n ? (int)min((int64_t)SM_KC, Q - (int64_t)c * SM_KC) - (lane >> 4) : 0;
+      uint32_t off = voff + (uint32_t)(c * SM_KC) * rowb;
+#pragma unroll
+      for (int j = 0; j < LD; ++j) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(slot + j * 4 * SM_ROWB), 16,
+                                                 4 * j < rows ? off : 0xf0000000u, 0, 0, 0);
+        off += 4 * rowb;
+      }
+    };
+#pragma unroll 1
+    for (int c = 0; c < SM_AHEAD; ++c) stage(c);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((SM_AHEAD - 1) * LD) : "memory");
+    __builtin_amdgcn_s_barrier();
+#pragma unroll 1
+    for (int p = 0; p < phases; ++p) {
+      stage(p + SM_AHEAD);   // past the end: zeros into a chunk nobody reads any more
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((SM_AHEAD - 1) * LD) : "memory");   // chunk p + 1 is there
+      __builtin_amdgcn_s_barrier();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may land in LDS after the workgroup has given it back
+    return;
+  }
+
+  f32x4 acc[G][8];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[g][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // The packed steps are read through scalar descriptors (a wave's groups lie one after another): the lane part
+  // of an address is one register, whatever the group.
+  const int64_t bundle = (int64_t)rb * WV + wave;
+  const bool live = bundle < bundles;
+  const int64_t bl = live ? bundle : 0;
+  const uint32_t a_stride = (uint32_t)(cap + 1) * 1024u, o_stride = (uint32_t)(cap + 1) * 64u;
+  const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a_buf) + bl * G * (int64_t)a_stride, 0, (int)(a_stride * (uint32_t)G), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_o = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(o_buf) + bl * G * (int64_t)o_stride, 0, (int)(o_stride * (uint32_t)G), 0x00020000);
+  const int32_t* const sp = sched + bl * phases;
+  const uint32_t a_lane = (uint32_t)lane * 16u, o_lane = (uint32_t)(lane >> 4) * 16u;
+  u32x4 a[G], o[G];
+  auto fetch = [&](int g, uint32_t step) {
+    a[g] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, a_lane, (uint32_t)g * a_stride + step * 1024u, 0);
+    o[g] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_o, o_lane, (uint32_t)g * o_stride + step * 64u, 0);
+  };
+#pragma unroll
+  for (int g = 0; g < G; ++g) fetch(g, 0);
+  const uint32_t lbase = (uint32_t)(lane & 15) * 16u;
+  __builtin_amdgcn_s_barrier();
+
+  uint32_t done = 0;
+  auto round = [&]() {
+    ++done;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      u32x4 d[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // row * 256 + the lane's bytes, in one instruction
+        const uint32_t at = __builtin_amdgcn_perm(o[g][e >> 1], lbase, (e & 1) ? 0x0c070600u : 0x0c050400u);
+        d[e] = *reinterpret_cast<const u32x4*>(ring + at);
+      }
+      const bf16x8 av = __builtin_bit_cast(bf16x8, a[g]);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        u32x4 lo, hi;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          lo[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x05040100u);
+          hi[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x07060302u);
+        }
+        acc[g][2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, lo), acc[g][2 * w], 0, 0, 0);
+        acc[g][2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, hi), acc[g][2 * w + 1], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(g, done);   // the group's next step, into the registers this one is done with
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  uint32_t upto = live ? (uint32_t)sp[0] : 0u;
+  for (int p = 0; p < phases; ++p) {
+    const uint32_t upto_next = live ? (uint32_t)sp[min(p + 1, phases - 1)] : 0u;
+    while (done < upto) round();
+    upto = upto_next;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the chunk that goes next are done
+    __builtin_amdgcn_s_barrier();
+  }
+
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int64_t row0 = (bundle * G + g) * 16;
+    if (row0 >= P) break;
+    // A zero value times an infinite or NaN element of D would reach the other rows of the group; and a group
+    // that was not packed has no sums at all: both take the general path.
+    float nf = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nf = fmaf(acc[g][j][i], 0.0f, nf);
+    if (steps[bundle] < 0 || __ballot(nf != 0.0f) != 0ull) {
+      sm_general(row_ptr, col_idx, val, capacity, P, Q, D, N, row0, n0, lane, R);
+      continue;
+    }
+    const int64_t col = n0 + (lane & 15) * 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t row = row0 + (lane >> 4) * 4 + i;
+      if (row < P && col < N) {
+        float* const dst = R + row * N + col;
+        *reinterpret_cast<f32x4*>(dst) = f32x4{acc[g][0][i], acc[g][1][i], acc[g][2][i], acc[g][3][i]};
+        *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[g][4][i], acc[g][5][i], acc[g][6][i], acc[g][7][i]};
+      }
+    }
+  }
+}
+
+}  // namespace
+
+// bytes of scratch the packed form of a P x Q matrix takes (0: this path does not take the matrix)
+int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
+  if (Q > SM_MAXQ || Q <= 0) return 0;
+  const int64_t groups = (P + 15) / 16 + 2;   // whole bundles of up to three
+  return groups * ((sm_cap(Q) + 1) * (1024 + 64) + (sm_phases(Q) + 1) * 4) + 1024;
+}
+
+// Returns 1 when the product is left to the fp32 kernel.
+int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
+                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, hipStream_t s) {
+  if (Q > SM_MAXQ || Q <= 0 || (uint64_t)(Q + 4 * SM_KC) * (uint64_t)N * 2 > 0xe0000000ull) return 1;   // 32-bit offsets into D
+  const int cap = (int)sm_cap(Q), phases = (int)sm_phases(Q);
+  const int col_blocks = (int)((N + SM_NT - 1) / SM_NT);
+  auto blocks = [&](int g, int wv) { return (P + 16 * g * wv - 1) / (16 * g * wv); };
+  auto launch = [&](auto g_c, auto wv_c) {
+    constexpr int G = decltype(g_c)::value, WV = decltype(wv_c)::value;
+    const int64_t bundles = (P + 16 * G - 1) / (16 * G);
+    uint8_t* const a_buf = reinterpret_cast<uint8_t*>(scratch);
+    uint8_t* const o_buf = a_buf + bundles * G * (int64_t)(cap + 1) * 1024;
+    int32_t* const sched = reinterpret_cast<int32_t*>(o_buf + bundles * G * (int64_t)(cap + 1) * 64);
+    int32_t* const steps = sched + bundles * phases;
+    const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)(G + 1) * phases * 4;
+    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles), dim3(16 * G * PK_TPR), lds, s, row_ptr, col_idx, val,
+                       capacity, P, (int)Q, cap, phases, a_buf, o_buf, sched, steps);
+    const int row_blocks = (int)blocks(G, WV);
+    const int per_xcd = (row_blocks * col_blocks + 7) / 8;
+    const int slot = fp4_trace_open(FP4_TRACE_SPMM, s);
+    hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
+                       steps, cap, phases, row_blocks, col_blocks, row_ptr, col_idx, val, capacity, P, Q,
+                       reinterpret_cast<const uint16_t*>(D), N, R);
+    fp4_trace_close(slot, s);
+  };
+  // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
+  // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows
+  // 2.3 us a phase, 176 rows 1.2, 112 rows 1.0; 16384 x 4096 -> 12288: 926 / 1355 / 1737 us, 1056 x 1376 -> 2080: 59 /
+  // 37 / 35 us, 512 x 8192 -> 8192: 147 / 99 / 136 us.
+  auto cost = [&](int g, int wv) { return (blocks(g, wv) * col_blocks + 255) / 256 * (300 + 16 * g * wv); };
+  const int64_t big = cost(3, 11), mid = cost(1, 11), small = cost(1, 7);
+  using I1 = std::integral_constant<int, 1>;
+  using I3 = std::integral_constant<int, 3>;
+  using I7 = std::integral_constant<int, 7>;
+  using I11 = std::integral_constant<int, 11>;
+  if (big <= mid && big <= small) launch(I3{}, I11{});
+  else if (mid <= small) launch(I1{}, I11{});
+  else launch(I1{}, I7{});
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}

@@ -1,0 +1,117 @@
+"""The bf16 residual product on the matrix cores (csrc/spmm_mfma.hip) where its packing and tiling can go wrong:
+row and column counts around its tiles, chunk edges, values of one to three bf16 terms, rows it leaves to the
+long-row kernels, bundles it leaves to the general path, non-finite elements.
+
+Bound: n products summed in fp32 in any order, each exact before the sum, differ from the exact sum by at most
+n * 2^-24 * sum |v d| to first order; 2^-23 leaves room for the higher orders and the matrix core's own adder.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _csr(S):
+    nz = S != 0
+    row_ptr = torch.zeros(S.shape[0] + 1, dtype=torch.int64)
+    torch.cumsum(nz.sum(1), 0, out=row_ptr[1:])
+    idx = nz.nonzero()
+    return row_ptr.cuda(), idx[:, 1].int().contiguous().cuda(), S[nz].contiguous().cuda()
+
+
+def _check(S, D, rows=None):
+    from paper_2501_17116_amd import binding as b
+    R = torch.full((S.shape[0], D.shape[1]), float("nan"), device="cuda")
+    b.fp4_residual_spmm(*_csr(S), S.shape[1], D.cuda(), R=R)
+    got = R.cpu().double()
+    ref = S.double() @ D.double()
+    mag = S.double().abs() @ D.double().abs()
+    n = (S != 0).sum(1, keepdim=True).double() + 1
+    sel = slice(None) if rows is None else rows
+    assert torch.all((got - ref).abs()[sel] <= (n * 2.0 ** -23 * mag + 1e-38)[sel])
+    return R
+
+
+def _draw(P, Q, N, density, terms, seed):
+    g = torch.Generator().manual_seed(seed)
+    S = torch.randn(P, Q, generator=g) * (torch.rand(P, Q, generator=g) < density)
+    if terms == 1:
+        S = S.bfloat16().float()
+    elif terms == 2:
+        S = S.bfloat16().float() - (S != 0) * 0.7109375 * 2.0 ** -7
+    return S, (torch.randn(Q, N, generator=g) * 0.02).bfloat16()
+
+
+@pytest.mark.parametrize("P,Q,N,density,terms", [
+    (1, 32, 8, 0.5, 1), (16, 128, 128, 0.02, 1), (17, 129, 136, 0.05, 3), (112, 127, 120, 0.1, 2),
+    (113, 256, 264, 0.02, 3), (176, 640, 128, 0.3, 1), (177, 641, 248, 0.3, 2), (528, 1376, 2080, 0.06, 2),
+    (529, 768, 4104, 0.02, 1), (1057, 96, 16392, 0.02, 1), (4096, 2100, 1032, 0.002, 2), (64, 4096, 512, 0.02, 1),
+])
+def test_against_fp64(P, Q, N, density, terms):
+    _check(*_draw(P, Q, N, density, terms, P + Q + N))
+
+
+@pytest.mark.parametrize("density", [0.0, 1.0])
+def test_empty_and_full(density):
+    _check(*_draw(200, 700, 136, density, 3 if density else 1, 5))   # full with three terms: more slots than there is room for
+
+
+def test_long_rows_and_dense_columns():
+    S, D = _draw(300, 4096, 264, 0.01, 2, 9)
+    S[7] = torch.randn(4096)              # left to the long-row kernels
+    S[40, :2048] = torch.randn(2048).bfloat16().float()   # just not
+    S[:, 1000] = torch.randn(300)
+    S[:, 1001] = torch.randn(300) * 50
+    _check(S, D)
+
+
+def test_extreme_magnitudes():
+    S, D = _draw(50, 300, 72, 0.1, 1, 11)
+    S *= torch.exp2(torch.randint(-100, 60, S.shape, generator=torch.Generator().manual_seed(1)).float())
+    _check(S, D)
+
+
+def test_non_finite_elements_stay_in_their_rows():
+    from paper_2501_17116_amd import binding as b
+    S, D = _draw(64, 400, 136, 0.05, 1, 13)
+    S[:, 100] = 0
+    S[:, 200] = 0
+    S[5, 100], S[33, 200] = 1.5, -2.0
+    D[100, 10], D[200, 100] = float("inf"), float("nan")
+    D[300] = 0
+    S[20, 300] = float("inf")             # inf * 0
+    R = torch.empty(64, 136, device="cuda")
+    b.fp4_residual_spmm(*_csr(S), 400, D.cuda(), R=R)
+    got = R.cpu()
+    assert got[5, 10] == float("inf") and torch.isnan(got[33, 100]) and torch.isnan(got[20]).all()
+    bad = torch.zeros(64, 136, dtype=torch.bool)
+    bad[5, 10] = bad[33, 100] = True
+    bad[20] = True
+    assert torch.isfinite(got[~bad]).all()
+    clean = S.clone(); clean[20] = 0
+    Dc = D.clone(); Dc[100, 10] = 0; Dc[200, 100] = 0
+    ref, mag = clean.double() @ Dc.double(), clean.double().abs() @ Dc.double().abs()
+    n = (S != 0).sum(1, keepdim=True).double() + 1
+    assert torch.all((((got.double() - ref).abs() <= n * 2.0 ** -23 * mag + 1e-38) | bad))
+
+
+def test_repeated_columns_are_summed():
+    from paper_2501_17116_amd import binding as b
+    D = torch.randn(64, 16).bfloat16()
+    rp = torch.tensor([0, 3, 5]).cuda()
+    ci = torch.tensor([4, 4, 9, 0, 63], dtype=torch.int32).cuda()
+    v = torch.tensor([1.0, 2.0, -1.0, 0.5, 4.0]).cuda()
+    R = b.fp4_residual_spmm(rp, ci, v, 64, D.cuda()).cpu()
+    Df = D.float()
+    assert np.allclose(R[0], 3 * Df[4] - Df[9], rtol=1e-6, atol=1e-6) and np.allclose(R[1], 0.5 * Df[0] + 4 * Df[63], rtol=1e-6, atol=1e-6)
+
+
+def test_same_bits_every_time():
+    from paper_2501_17116_amd import binding as b
+    S, D = _draw(700, 1300, 520, 0.03, 2, 17)
+    c = _csr(S)
+    Dd = D.cuda()
+    first = b.fp4_residual_spmm(*c, 1300, Dd).clone()
+    for _ in range(3):
+        assert torch.equal(b.fp4_residual_spmm(*c, 1300, Dd), first)
