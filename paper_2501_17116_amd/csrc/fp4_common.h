@@ -98,16 +98,6 @@ FP4_D float dge_factor(float w, float gamma, float pw, float inv_k, float cap) {
   const float e = pw == 0.0f ? 1.0f : __builtin_amdgcn_exp2f(pw * __builtin_amdgcn_logf(t));
   return fminf(inv_k * e, cap);
 }
-
-// Rows of the residual (or its transpose) with more entries than this are "long": outlier channels, nearly
-// dense among rows that are nearly empty.  The kernels that walk many rows side by side leave them out (one
-// such row holds up its whole workgroup), others multiply them.  A quarter of the columns, at most 2048, but
-// always four times the mean row.  Measured against 2048 entries whatever the width (steps with one to ten dense
-// channels): fp32 2048^3 1379 -> 429 us, fp32 256 x 512 x 512 337 -> 256 us, bf16 1056 x 1376 x 2080 836 -> 403 us.
-FP4_D int64_t spmm_long_limit(const int64_t* row_ptr, int64_t P, int64_t Q, int64_t capacity) {
-  const float mean = (float)min(row_ptr[P], capacity) / (float)P;
-  return max(min(max(Q / 4, (int64_t)64), (int64_t)2048), (int64_t)(4.0f * mean));
-}
 #endif  // __HIPCC__
 
 // Nearest E4M3 code (OCP FP8: bias 7, largest magnitude 448 = 0x7e, subnormal quantum 2^-9) of a

@@ -18,6 +18,7 @@
 // spreads one row's entries over a workgroup and reduces.
 #include "fp4_common.h"
 #include "fp4_measure.h"
+#include "spmm_long.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -268,57 +269,11 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
 }
 
 // ---- long rows -------------------------------------------------------------------------------
-// Long rows, listed in ascending order by one workgroup (ballot + scan), so the
-// split between the two long-row kernels below does not depend on timing.
+// The list of long rows (spmm_long.h) as a launch of its own, for the fp32 kernel; the matrix-core path has one
+// workgroup of its packing kernel make it.
 __global__ __launch_bounds__(1024) void find_long_rows_kernel(const int64_t* row_ptr, int64_t P, int64_t Q, int64_t capacity,
-                                                              int32_t* list, int32_t* count, int32_t list_cap) {
-  // 16 x 1024 rows per turn: all their row_ptr loads in flight at once, then one scan over the
-  // 16 x 16 (round, wave) counts instead of a barrier-separated step per 1024 rows
-  __shared__ int s_cnt[16 * 16];   // [round][wave] counts, then their exclusive prefix in that order
-  __shared__ int s_base;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
-  if (tid == 0) s_base = 0;
-  for (int64_t r0 = 0; r0 < P; r0 += 16 * 1024) {
-    uint32_t flags = 0;
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int64_t row = r0 + it * 1024 + tid;
-      const bool is_long = row < P && min(row_ptr[row + 1], capacity) - row_ptr[row] > long_limit;
-      flags |= (is_long ? 1u : 0u) << it;
-    }
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const unsigned long long m = __ballot((flags >> it) & 1u);
-      if (lane == 0) s_cnt[it * 16 + wave] = __popcll(m);
-    }
-    __syncthreads();   // counts complete (and s_base of the turn before)
-    if (wave == 0) {   // exclusive prefix over the 256 counts, four per lane
-      int c[4], sum = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { c[j] = s_cnt[lane * 4 + j]; sum += c[j]; }
-      int incl = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-      }
-      int run = s_base + incl - sum;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { s_cnt[lane * 4 + j] = run; run += c[j]; }
-      if (lane == 63) s_base = run;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const bool is_long = (flags >> it) & 1u;
-      const unsigned long long m = __ballot(is_long);
-      const int pos = s_cnt[it * 16 + wave] + __popcll(m & ((1ull << lane) - 1ull));
-      if (is_long && pos < list_cap) list[pos] = (int32_t)(r0 + it * 1024 + tid);
-    }
-    __syncthreads();   // s_cnt is rewritten in the next turn
-  }
-  if (tid == 0) *count = s_base;
+                                                              int32_t* list, int32_t* count) {
+  find_long_rows<1024>(row_ptr, P, Q, capacity, list, count);
 }
 
 // The first LD_CAP long rows (outlier channels of the transposed residual: nearly dense) are
@@ -494,11 +449,10 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   else long_dense_body<DT, LD_LB>(V, D, m0, rows_here, N, nl, pout);
 }
 
-__global__ __launch_bounds__(256) void spmm_long_reduce_kernel(const int32_t* list, const int32_t* count,
-                                                               const float* part, int slices, int64_t N, float* R) {
-  const int n_long = min(*count, LD_CAP);
+// Adds the slices' partial sums of the dense path's rows (blockIdx.y < LD_CAP), 256 columns a workgroup.
+FP4_D void long_reduce(const int32_t* list, int n_long, const float* part, int slices, int64_t N, float* R) {
   const int li = blockIdx.y;
-  if (li >= n_long) return;
+  if (li >= min(n_long, LD_CAP)) return;
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (n >= N) return;
   float sum = 0.0f;
@@ -506,47 +460,55 @@ __global__ __launch_bounds__(256) void spmm_long_reduce_kernel(const int32_t* li
   R[(int64_t)list[li] * N + n] = sum;
 }
 
-// Long rows beyond the dense path's share (list positions >= first), one at a time: one
-// workgroup per (long row, 32 columns): 4 column groups of 8 x 64 entry lanes; entry lane l
-// takes entries l, l+64, ...; the 64 partial sums are added in a fixed order.
+// The rest of the long rows in one launch: the dense path's rows are added up, and rows beyond its share (list
+// positions from LD_CAP on) are multiplied one at a time: one workgroup per (long row, 32 columns), LR_ROWS rows at
+// a time, 4 column groups of 8 x 64 entry lanes; entry lane l takes entries l, l+64, ...; the 64 partial sums are
+// added in a fixed order.
+constexpr int LR_ROWS = 8;
 template <class DT>
 __global__ __launch_bounds__(256) void spmm_long_rows_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                              const float* val, int64_t capacity,
                                                              const int32_t* list, const int32_t* count,
-                                                             int32_t list_cap, int32_t first, const void* D,
+                                                             const float* partial, int slices, const void* D,
                                                              int64_t N, float* R) {
   __shared__ float part[64][4][8];
-  const int n_long = min(*count, list_cap);
+  const int n_long = *count;
+  if (blockIdx.y < LD_CAP) {
+    long_reduce(list, n_long, partial, slices, N, R);
+    return;
+  }
   const int cg = threadIdx.x & 3, el = threadIdx.x >> 2;
-  const int64_t col = (int64_t)blockIdx.y * 32 + cg * 8;
-  const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
-  for (int li = first + blockIdx.x; li < n_long; li += gridDim.x) {
+  for (int li = blockIdx.y; li < n_long; li += LR_ROWS) {
     const int64_t row = list[li];
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
     const int64_t b = row_ptr[row], en = min(row_ptr[row + 1], capacity);
-    if (valid > 0) {
-      for (int64_t i = b + el; i < en; i += 64) {
-        const int32_t c = col_idx[i];
-        const float s = val[i];
-        float d[8];
-        load8g<DT>(D, (int64_t)c * N + col, valid, d);
+    for (int64_t n0 = (int64_t)blockIdx.x * 256; n0 < min((int64_t)(blockIdx.x + 1) * 256, N); n0 += 32) {
+      const int64_t col = n0 + cg * 8;
+      const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
+      float acc[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = fmaf(s, d[e], acc[e]);
+      for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+      if (valid > 0) {
+        for (int64_t i = b + el; i < en; i += 64) {
+          const int32_t c = col_idx[i];
+          const float s = val[i];
+          float d[8];
+          load8g<DT>(D, (int64_t)c * N + col, valid, d);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] = fmaf(s, d[e], acc[e]);
+        }
       }
-    }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[el][cg][e] = acc[e];
-    __syncthreads();
-    if (threadIdx.x < 32) {
-      const int g = threadIdx.x >> 3, e = threadIdx.x & 7;
-      float sum = 0.0f;
-      for (int l = 0; l < 64; ++l) sum += part[l][g][e];
-      const int64_t c1 = (int64_t)blockIdx.y * 32 + g * 8 + e;
-      if (c1 < N) R[row * N + c1] = sum;
+      for (int e = 0; e < 8; ++e) part[el][cg][e] = acc[e];
+      __syncthreads();
+      if (threadIdx.x < 32) {
+        const int g = threadIdx.x >> 3, e = threadIdx.x & 7;
+        float sum = 0.0f;
+        for (int l = 0; l < 64; ++l) sum += part[l][g][e];
+        const int64_t c1 = n0 + g * 8 + e;
+        if (c1 < N) R[row * N + c1] = sum;
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -847,7 +809,8 @@ int fp4_trace_open(int kind, hipStream_t stream);
 void fp4_trace_close(int slot, hipStream_t stream);
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q);
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
-                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, hipStream_t s);
+                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
+                         hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
 // the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
@@ -864,9 +827,12 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
                     hipStream_t s) {
   if (P == 0 || N == 0) return FP4_OK;
   if (Q >= ((int64_t)1 << 21)) return FP4_ERR_SHAPE;   // 32-bit entry offsets inside a workgroup's 1024 rows
+  const bool may_be_long = Q > 64 && capacity > 64;   // otherwise no row can be
+  int32_t* const count = scratch;
+  int32_t* const list = scratch + 64;
   int rc = 1;
   if (bf16)
-    rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), s);
+    rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, s);
   if (rc != 0 && rc != 1) return rc;
   if (rc == 1) {
     const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
@@ -876,31 +842,24 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
     else
       hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
     fp4_trace_close(trace_slot, s);
+    if (may_be_long)
+      hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count);
   }
-  if (Q > 64 && capacity > 64) {   // otherwise no row can be long
-    int32_t* count = scratch;
-    int32_t* list = scratch + 64;
-    const int32_t list_cap = (int32_t)P;
+  if (may_be_long) {
     float* part = reinterpret_cast<float*>(scratch + spmm_list_words(P));
     const int slices = (int)((Q + LD_SLICE - 1) / LD_SLICE);
-    hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count, list_cap);
     const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices, LD_CAP / LD_LB);
-    if (bf16)
+    const dim3 rgrid((unsigned)((N + 255) / 256), LD_CAP + LR_ROWS);
+    if (bf16) {
       hipLaunchKernelGGL((spmm_long_dense_kernel<BF16>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
                          count, D, Q, N, part);
-    else
+      hipLaunchKernelGGL((spmm_long_rows_kernel<BF16>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
+                         part, slices, D, N, R);
+    } else {
       hipLaunchKernelGGL((spmm_long_dense_kernel<F32>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
                          count, D, Q, N, part);
-    hipLaunchKernelGGL(spmm_long_reduce_kernel, dim3((unsigned)((N + 255) / 256), LD_CAP), dim3(256), 0, s, list, count,
-                       part, slices, N, R);
-    if (list_cap > LD_CAP) {
-      const dim3 lgrid((unsigned)std::min<int32_t>(list_cap - LD_CAP, 8), (unsigned)((N + 31) / 32));
-      if (bf16)
-        hipLaunchKernelGGL((spmm_long_rows_kernel<BF16>), lgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list,
-                           count, list_cap, LD_CAP, D, N, R);
-      else
-        hipLaunchKernelGGL((spmm_long_rows_kernel<F32>), lgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list,
-                           count, list_cap, LD_CAP, D, N, R);
+      hipLaunchKernelGGL((spmm_long_rows_kernel<F32>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
+                         part, slices, D, N, R);
     }
   }
   FP4_CHECK_LAUNCH();

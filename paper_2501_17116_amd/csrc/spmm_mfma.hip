@@ -22,6 +22,7 @@
 // 1454 us.  6 %: 1487 against 2854 us; 0.2 %: 551 against 589 us.
 #include "fp4_common.h"
 #include "fp4_measure.h"
+#include "spmm_long.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -75,19 +76,22 @@ __global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
                                                                int Q, int cap, int phases, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
-                                                               int32_t* __restrict__ steps) {
+                                                               int32_t* __restrict__ steps, int32_t* list, int32_t* count) {
   constexpr int ROWS = 16 * G, THREADS = ROWS * PK_TPR;
   extern __shared__ uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
   uint32_t* const nib = pk_lds;                                                // [G][words] a nibble per column: as many bits as slots
   int32_t* const start = reinterpret_cast<int32_t*>(nib + G * words);       // [G][phases] slot count, then first slot
-  int32_t* const ends = start + G * phases;                                 // [phases] the groups' furthest end of a chunk's slots
-  uint16_t* const pre = reinterpret_cast<uint16_t*>(ends + phases);            // [G][words] slots of the chunk before this word
+  uint16_t* const pre = reinterpret_cast<uint16_t*>(start + G * phases);   // [G][words] slots of the chunk before this word
   __shared__ int64_t s_b[ROWS];
   __shared__ int s_n[ROWS];
   __shared__ int s_bad, s_total[G], s_steps;
   const int tid = threadIdx.x;
-  const int64_t bundle = blockIdx.x;
+  if (blockIdx.x == 0) {   // the first workgroup lists the long rows
+    find_long_rows<THREADS>(row_ptr, P, Q, capacity, list, count);
+    return;
+  }
+  const int64_t bundle = blockIdx.x - 1;
   for (int i = tid; i < G * words; i += THREADS) nib[i] = 0;
   if (tid < ROWS) {
     const int64_t row = bundle * ROWS + tid;
@@ -108,12 +112,24 @@ __global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_
   const int n = s_n[br];
   const int32_t* const cp = col_idx + s_b[br];
   const float* const vp = val + s_b[br];
-  for (int i = rt; i < n; i += PK_TPR) {
-    const int c = cp[i];
-    uint32_t t[3];
-    const int nt = bf16_terms(vp[i], t);
-    if ((uint32_t)c >= (uint32_t)Q || (i > 0 && cp[i - 1] >= c)) { s_bad = 1; continue; }
-    atomicOr(&nib[grp * words + (c >> 3)], ((1u << nt) - 1u) << (4 * (c & 7)));
+  for (int i0 = rt; i0 < n; i0 += 4 * PK_TPR) {   // four entries a thread in flight
+    int c[4], before[4];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + u * PK_TPR, n - 1);
+      c[u] = cp[i];
+      v[u] = vp[i];
+      before[u] = i > 0 ? cp[i - 1] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      uint32_t t[3];
+      const int nt = bf16_terms(v[u], t);
+      if (i0 + u * PK_TPR >= n) continue;
+      if ((uint32_t)c[u] >= (uint32_t)Q || before[u] >= c[u]) { s_bad = 1; continue; }
+      atomicOr(&nib[grp * words + (c[u] >> 3)], ((1u << nt) - 1u) << (4 * (c[u] & 7)));
+    }
   }
   __syncthreads();
   for (int i = tid; i < G * phases; i += THREADS) {
@@ -127,31 +143,55 @@ __global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_
     atomicAdd(&s_total[i / phases], sum);
   }
   __syncthreads();
-  if (tid == 0) {
-    // S follows an even pace, between what must be done (chunk c - SM_SLACK leaves) and what fills whole steps
-    int total = 0, e[G], S = 0;
+  if (tid < 64) {
+    // S follows an even pace, between what must be done (chunk c - SM_SLACK leaves) and what fills whole steps.  One
+    // wave: a lane holds the counts of every 64th chunk, the recurrence runs on scalars.
+    int total = 0, e[G], ends[SM_SLACK + 1], S = 0, quot, rem, pace = 0, left = 0;
     for (int j = 0; j < G; ++j) { total = max(total, (s_total[j] + 31) / 32); e[j] = 0; }
+    total = __builtin_amdgcn_readfirstlane(total);
+    quot = total / phases;
+    rem = total % phases;
+#pragma unroll
+    for (int i = 0; i <= SM_SLACK; ++i) ends[i] = 0;
     int32_t* const sc = sched + bundle * phases;
-    for (int c = 0; c < phases; ++c) {
-      int least = 0x7fffffff, most = 0;
-      for (int j = 0; j < G; ++j) {
-        const int st = max(e[j], 32 * S);
-        e[j] = st + start[j * phases + c];
-        start[j * phases + c] = st;
-        least = min(least, e[j]);
-        most = max(most, e[j]);
+    for (int c0 = 0; c0 < phases; c0 += 64) {
+      int cnt[G], first[G], mine = 0;
+#pragma unroll
+      for (int j = 0; j < G; ++j) { cnt[j] = c0 + tid < phases ? start[j * phases + c0 + tid] : 0; first[j] = 0; }
+      const int here = min(64, phases - c0);
+      for (int i = 0; i < here; ++i) {
+        int least = 0x7fffffff, most = 0;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+          const int st = max(e[j], 32 * S);
+          first[j] = tid == i ? st : first[j];
+          e[j] = st + __builtin_amdgcn_readlane(cnt[j], i);
+          least = min(least, e[j]);
+          most = max(most, e[j]);
+        }
+#pragma unroll
+        for (int k = 0; k < SM_SLACK; ++k) ends[k] = ends[k + 1];
+        ends[SM_SLACK] = most;
+        pace += quot;   // ceil(total * (c + 1) / phases)
+        left += rem;
+        if (left >= phases) { left -= phases; ++pace; }
+        const int lo = max(S, (ends[0] + 31) / 32);
+        S = c0 + i == phases - 1 ? max(lo, (most + 31) / 32) : max(min(pace + (left > 0 ? 1 : 0), least / 32), lo);
+        mine = tid == i ? S : mine;
       }
-      ends[c] = most;
-      const int lo = max(S, c >= SM_SLACK ? (ends[c - SM_SLACK] + 31) / 32 : 0);
-      const int pace = (int)(((int64_t)total * (c + 1) + phases - 1) / phases);
-      S = c == phases - 1 ? max(lo, (most + 31) / 32) : max(min(pace, least / 32), lo);
-      sc[c] = S;
+      if (tid < here) {
+        sc[c0 + tid] = mine;
+#pragma unroll
+        for (int j = 0; j < G; ++j) start[j * phases + c0 + tid] = first[j];
+      }
     }
     const bool ok = !s_bad && S <= cap;
     if (!ok)
-      for (int c = 0; c < phases; ++c) sc[c] = 0;
-    s_steps = ok ? S : 0;
-    steps[bundle] = ok ? S : -1;
+      for (int c = tid; c < phases; c += 64) sc[c] = 0;
+    if (tid == 0) {
+      s_steps = ok ? S : 0;
+      steps[bundle] = ok ? S : -1;
+    }
   }
   __syncthreads();
   const int T = s_steps;
@@ -163,17 +203,29 @@ __global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_
   for (int i = gt; i < T * 64; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(ag + (int64_t)i * 16) = z;
   for (int i = gt; i < T * 4; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(og + (int64_t)i * 16) = z;
   __syncthreads();   // the zeros are written (a workgroup's stores reach L2 in order) before the values
-  for (int i = rt; i < n; i += PK_TPR) {
-    const int c = cp[i];
-    uint32_t t[3];
-    const int nt = bf16_terms(vp[i], t);
-    const int chunk = c / SM_KC, w = grp * words + (c >> 3);
-    const int pos = start[grp * phases + chunk] + pre[w] + __popc(nib[w] & ((1u << (4 * (c & 7))) - 1u));
-    const uint16_t at = (uint16_t)((chunk % SM_RING) * SM_KC + c % SM_KC);
-    for (int k = 0; k < nt; ++k) {
-      const int p = pos + k;
-      *reinterpret_cast<uint16_t*>(ag + (int64_t)(p >> 5) * 1024 + (((p >> 3) & 3) * 16 + r) * 16 + (p & 7) * 2) = (uint16_t)t[k];
-      *reinterpret_cast<uint16_t*>(og + (int64_t)p * 2) = at;
+  for (int i0 = rt; i0 < n; i0 += 4 * PK_TPR) {
+    int cc[4];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + u * PK_TPR, n - 1);
+      cc[u] = cp[i];
+      v[u] = vp[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i0 + u * PK_TPR >= n) continue;
+      const int c = cc[u];
+      uint32_t t[3];
+      const int nt = bf16_terms(v[u], t);
+      const int w = grp * words + (c >> 3);
+      const int pos = start[grp * phases + c / SM_KC] + pre[w] + __popc(nib[w] & ((1u << (4 * (c & 7))) - 1u));
+      const uint16_t at = (uint16_t)(c % (SM_RING * SM_KC));   // row of the ring
+      for (int k = 0; k < nt; ++k) {
+        const int p = pos + k;
+        *reinterpret_cast<uint16_t*>(ag + (int64_t)(p >> 5) * 1024 + (((p >> 3) & 3) * 16 + r) * 16 + (p & 7) * 2) = (uint16_t)t[k];
+        *reinterpret_cast<uint16_t*>(og + (int64_t)p * 2) = at;
+      }
     }
   }
 }
@@ -323,11 +375,17 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  uint32_t upto = live ? (uint32_t)sp[0] : 0u;
+  // The steps done at the end of each phase, 64 phases a register: a scalar load per phase would cost its latency
+  // in every one of them.
+  auto plan_at = [&](int p0) { return live ? sp[min(p0 + lane, phases - 1)] : 0; };
+  int plan = plan_at(0), plan_next = plan_at(64);
   for (int p = 0; p < phases; ++p) {
-    const uint32_t upto_next = live ? (uint32_t)sp[min(p + 1, phases - 1)] : 0u;
+    if (p > 0 && (p & 63) == 0) {
+      plan = plan_next;
+      plan_next = plan_at(p + 64);
+    }
+    const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane(plan, p & 63);
     while (done < upto) round();
-    upto = upto_next;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the chunk that goes next are done
     __builtin_amdgcn_s_barrier();
   }
@@ -347,15 +405,27 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
       sm_general(row_ptr, col_idx, val, capacity, P, Q, D, N, row0, n0, lane, R);
       continue;
     }
-    const int64_t col = n0 + (lane & 15) * 8;
+    // A lane holds 8 columns of 4 rows; four neighbours exchange 16-byte pieces so that each store instruction
+    // writes whole 64-byte runs: lane q of four stores piece q, then piece q + 4, of their 32 columns.
+    const int64_t col = n0 + (lane & 12) * 8 + (lane & 3) * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      f32x4 st[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          // quad_perm: every lane reads lane 0 0 1 1 (first half) or 2 2 3 3 of its four
+          const int even = h ? __builtin_amdgcn_mov_dpp((int)f2u(acc[g][k][i]), 0xfa, 0xf, 0xf, true)
+                             : __builtin_amdgcn_mov_dpp((int)f2u(acc[g][k][i]), 0x50, 0xf, 0xf, true);
+          const int odd = h ? __builtin_amdgcn_mov_dpp((int)f2u(acc[g][4 + k][i]), 0xfa, 0xf, 0xf, true)
+                            : __builtin_amdgcn_mov_dpp((int)f2u(acc[g][4 + k][i]), 0x50, 0xf, 0xf, true);
+          st[h][k] = u2f((uint32_t)((lane & 1) ? odd : even));
+        }
       const int64_t row = row0 + (lane >> 4) * 4 + i;
-      if (row < P && col < N) {
-        float* const dst = R + row * N + col;
-        *reinterpret_cast<f32x4*>(dst) = f32x4{acc[g][0][i], acc[g][1][i], acc[g][2][i], acc[g][3][i]};
-        *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[g][4][i], acc[g][5][i], acc[g][6][i], acc[g][7][i]};
-      }
+      float* const dst = R + row * N + col;
+      if (row < P && col < N) *reinterpret_cast<f32x4*>(dst) = st[0];
+      if (row < P && col + 16 < N) *reinterpret_cast<f32x4*>(dst + 16) = st[1];
     }
   }
 }
@@ -371,7 +441,8 @@ int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
 
 // Returns 1 when the product is left to the fp32 kernel.
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
-                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, hipStream_t s) {
+                         int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
+                         hipStream_t s) {
   if (Q > SM_MAXQ || Q <= 0 || (uint64_t)(Q + 4 * SM_KC) * (uint64_t)N * 2 > 0xe0000000ull) return 1;   // 32-bit offsets into D
   const int cap = (int)sm_cap(Q), phases = (int)sm_phases(Q);
   const int col_blocks = (int)((N + SM_NT - 1) / SM_NT);
@@ -383,9 +454,9 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     uint8_t* const o_buf = a_buf + bundles * G * (int64_t)(cap + 1) * 1024;
     int32_t* const sched = reinterpret_cast<int32_t*>(o_buf + bundles * G * (int64_t)(cap + 1) * 64);
     int32_t* const steps = sched + bundles * phases;
-    const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)(G + 1) * phases * 4;
-    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles), dim3(16 * G * PK_TPR), lds, s, row_ptr, col_idx, val,
-                       capacity, P, (int)Q, cap, phases, a_buf, o_buf, sched, steps);
+    const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)G * phases * 4;
+    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * PK_TPR), lds, s, row_ptr, col_idx, val,
+                       capacity, P, (int)Q, cap, phases, a_buf, o_buf, sched, steps, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
     const int slot = fp4_trace_open(FP4_TRACE_SPMM, s);
