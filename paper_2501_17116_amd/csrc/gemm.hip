@@ -580,6 +580,146 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
   }  // tiles
 }
 
+// The same product for outputs with too few 256 x 256 tiles to go round the chip: a workgroup of four waves takes
+// 64 x 64 outputs, a wave 32 x 32.  What bounds such a call is the chain of round trips of one tile, not a
+// rate, so operands go straight from memory to the matrix core's registers (a lane's 16 bytes of a row are its
+// fragment; a 128-byte line serves four steps out of L1), SG_IN steps ahead, and neither barrier nor staging stands
+// in between.  The output passes through LDS once so that it is read and written along rows.  Sums, scaling, addend
+// and factor are the same operations in the same order as in fp4_gemm_nt_kernel: the same bits.
+// 64 x 2048 x 2048: 10.9 us against 19.2; 512 x 512 x 256: 7.5 against 12.5 (fp32); 1056 x 2080 x 1376: 15 against 30.
+constexpr int SG_IN = 4;   // K steps (32 bytes a row) requested ahead: one 128-byte line of every row
+template <bool OUT_BF16, bool DGE, bool W_BF16>
+__global__ __launch_bounds__(256) void fp4_gemm_small_kernel(
+    const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,
+    const float* __restrict__ gr, const float* addend, void* outp, const void* __restrict__ Wp,
+    const float* __restrict__ gamma_w, GemmShape g) {
+  constexpr int T = 64, LD = T + 4;
+  __shared__ __attribute__((aligned(16))) float tile[T * LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int wp = (wave & 1) * 32, wq = (wave >> 1) * 32;
+  const int64_t P0 = (int64_t)(blockIdx.x % (unsigned)g.tiles_p) * T, Q0 = (int64_t)(blockIdx.x / (unsigned)g.tiles_p) * T;
+  // rows past the edge re-read the last row
+  const uint8_t* const rowL = Lp + min(P0 + wp + l32, g.P - 1) * g.Kb + lhi * 16;
+  const uint8_t* const rowR = Rp + min(Q0 + wq + l32, g.Q - 1) * g.Kb + lhi * 16;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  const int one = 127;
+  u32x4 a[2][SG_IN], b[2][SG_IN];
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  auto request = [&](int set, int64_t k0) {   // steps from byte k0 on; what lies past the row is zero
+#pragma unroll
+    for (int s = 0; s < SG_IN; ++s) {
+      const int64_t k = k0 + 32 * s;
+      const bool in = k + lhi * 16 < g.Kb;
+      a[set][s] = in ? *reinterpret_cast<const u32x4*>(rowR + k) : zero;
+      b[set][s] = in ? *reinterpret_cast<const u32x4*>(rowL + k) : zero;
+    }
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int s = 0; s < SG_IN; ++s) {
+      const u32x4 fa = a[set][s], fb = b[set][s];
+      const i32x8 va = {(int)fa.x, (int)fa.y, (int)fa.z, (int)fa.w, 0, 0, 0, 0};
+      const i32x8 vb = {(int)fb.x, (int)fb.y, (int)fb.z, (int)fb.w, 0, 0, 0, 0};
+      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, acc, 4, 4, 0, one, 0, one);
+    }
+  };
+  request(0, 0);
+  for (int64_t k0 = 0; k0 < g.Kb; k0 += 64 * SG_IN) {
+    request(1, k0 + 32 * SG_IN);
+    multiply(0);
+    if (k0 + 32 * SG_IN < g.Kb) {
+      request(0, k0 + 64 * SG_IN);
+      multiply(1);
+    }
+  }
+  const bool scaled = gl != nullptr;
+  const float il = scaled ? __builtin_amdgcn_rcpf(gl[min(P0 + wp + l32, g.P - 1)]) : 1.0f;
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const f32x4 y = {acc[g4 * 4] * il, acc[g4 * 4 + 1] * il, acc[g4 * 4 + 2] * il, acc[g4 * 4 + 3] * il};
+    *reinterpret_cast<f32x4*>(&tile[(wp + l32) * LD + wq + g4 * 8 + lhi * 4]) = y;
+  }
+  __syncthreads();
+  constexpr int UPR = T / 8, RPT = 256 / UPR;   // 8-column units a row, rows a pass
+  const int ql = (tid % UPR) * 8;
+  const int64_t q0 = Q0 + ql;
+  if (q0 >= g.Q) return;
+  const bool full = q0 + 7 < g.Q;
+  float ir[8], gw[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t q = min(q0 + e, g.Q - 1);
+    ir[e] = scaled ? __builtin_amdgcn_rcpf(gr[q]) : 1.0f;
+    gw[e] = DGE ? gamma_w[q] : 0.0f;
+  }
+  const float inv_k = DGE ? 1.0f / g.dge_k : 1.0f;
+  const float pw = inv_k - 1.0f;
+#pragma unroll 2
+  for (int pl = tid / UPR; pl < T; pl += RPT) {
+    const int64_t p = P0 + pl;
+    if (p >= g.P) break;
+    const f32x4 v0 = *reinterpret_cast<const f32x4*>(&tile[pl * LD + ql]), v1 = *reinterpret_cast<const f32x4*>(&tile[pl * LD + ql + 4]);
+    float y[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = __fmul_rn(y[e], ir[e]);
+    if (addend) {
+      const float* ad = addend + p * g.ldo + q0;
+      if (full) {
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(ad), a1 = *reinterpret_cast<const f32x4*>(ad + 4);
+        y[0] += a0.x; y[1] += a0.y; y[2] += a0.z; y[3] += a0.w;
+        y[4] += a1.x; y[5] += a1.y; y[6] += a1.z; y[7] += a1.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (q0 + e < g.Q) y[e] += ad[e];
+      }
+    }
+    if constexpr (DGE) {
+      float w[8];
+      const int64_t off = p * g.ldw + q0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = 0.0f;
+      if (W_BF16 && full) {
+        const u32x4 r = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(Wp) + off);
+        w[0] = u2f(r.x << 16); w[1] = u2f(r.x & 0xffff0000u);
+        w[2] = u2f(r.y << 16); w[3] = u2f(r.y & 0xffff0000u);
+        w[4] = u2f(r.z << 16); w[5] = u2f(r.z & 0xffff0000u);
+        w[6] = u2f(r.w << 16); w[7] = u2f(r.w & 0xffff0000u);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (q0 + e < g.Q)
+            w[e] = W_BF16 ? bf16_bits_to_f32(reinterpret_cast<const uint16_t*>(Wp)[off + e]) : reinterpret_cast<const float*>(Wp)[off + e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] *= dge_factor(w[e], gw[e], pw, inv_k, g.dge_cap);
+    }
+    if constexpr (OUT_BF16) {
+      uint16_t* o = reinterpret_cast<uint16_t*>(outp) + p * g.ldo + q0;
+      if (full) {
+        *reinterpret_cast<u32x4*>(o) = u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (q0 + e < g.Q) o[e] = (uint16_t)f32_to_bf16_bits(y[e]);
+      }
+    } else {
+      float* o = reinterpret_cast<float*>(outp) + p * g.ldo + q0;
+      if (full) {
+        *reinterpret_cast<f32x4*>(o) = f32x4{y[0], y[1], y[2], y[3]};
+        *reinterpret_cast<f32x4*>(o + 4) = f32x4{y[4], y[5], y[6], y[7]};
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (q0 + e < g.Q) o[e] = y[e];
+      }
+    }
+  }
+}
+
 __global__ void fp4_unpack_kernel(const uint8_t* codes, int64_t nbytes, uint8_t* out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nbytes) {
@@ -625,9 +765,19 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   const dim3 grid(std::min(((total + 7) / 8) * 8, (n_cu / 8) * 8)), block(NTHREADS);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
   const bool ragged = (g.Kb % BKB) != 0;
+  // Small tiles while each CU gets one of them (512 x 2048 x 2048: 11 against 18 us, 256 x 4096 x 16384: 62 against 77);
+  // with four per CU they lose (2048^3: 36 against 21).  A row of codes that ends inside a K step puts the big tiles
+  // on their slower path, so there the line lies at three per CU (1376 x 2080 x 1056, 726 tiles: 13 against 28 us).
+  const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64);
+  const bool small = small_tiles <= (ragged ? 3 : 1) * (int64_t)n_cu;
+  GemmShape gs = g;
+  gs.tiles_p = (int)((P + 63) / 64);
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
-    if (ragged)                                                                                           \
+    if (small)                                                                                            \
+      hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)small_tiles), dim3(256), 0, stream, L, Rt, gl, gr, \
+                         addend, out, W, gamma_w, gs);                                                    \
+    else if (ragged)                                                                                      \
       hipLaunchKernelGGL((fp4_gemm_nt_kernel<OB, DG, WB, true>), grid, block, 0, stream, L, Rt, gl, gr,   \
                          addend, out, W, gamma_w, g);                                                     \
     else                                                                                                  \
