@@ -174,7 +174,7 @@ WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   w.gAk = c.take<float>((size_t)K);
   w.qdYt = c.take<uint8_t>((size_t)(N * M / 2));
   w.gdYn = c.take<float>((size_t)N);
-  w.amax = c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(M, std::max(K, N)));
+  w.amax = c.take<uint32_t>((size_t)std::max(fp4_quantize_cols_scratch_words(M, K), fp4_quantize_cols_scratch_words(M, N)));
   const int64_t cap = provisioned_entries(M, K);
   w.t_ptr = c.take<int64_t>((size_t)(K + 1));
   w.t_idx = c.take<int32_t>((size_t)cap);

@@ -769,7 +769,8 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   // with four per CU they lose (2048^3: 36 against 21).  A row of codes that ends inside a K step puts the big tiles
   // on their slower path, so there the line lies at three per CU (1376 x 2080 x 1056, 726 tiles: 13 against 28 us).
   const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64);
-  const bool small = small_tiles <= (ragged ? 3 : 1) * (int64_t)n_cu;
+  // The factor with fp32 weights has no branch-free epilogue in the big tiles: four per CU (2048^3: 38 against 61 us).
+  const bool small = small_tiles <= (dge && !w_bf16 ? 4 : ragged ? 3 : 1) * (int64_t)n_cu;
   GemmShape gs = g;
   gs.tiles_p = (int)((P + 63) / 64);
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \

@@ -735,13 +735,19 @@ struct ColArgs {
   const void* x;
   uint8_t* codes_t;
   float* gamma;          // out [cols]
-  uint32_t* amax_bits;   // scratch [ceil(rows / CA_ROWS)][cols]: partial column maxima per row block
+  uint32_t* amax_bits;   // scratch [ceil(rows / row_block)][cols]: partial column maxima per row block
   const float* thr;      // clamp thresholds or null
   int64_t thr_stride;    // 0: one {lo, hi} pair for the tensor; 2: one pair per row, thr[2 r], thr[2 r + 1]
   int64_t rows, cols, ld;
+  int row_block;         // rows per workgroup in the absmax pass
 };
 
-constexpr int CA_ROWS = 128;  // rows per workgroup in the absmax pass
+// Rows per workgroup in the absmax pass: 128, fewer (32 at least) while that leaves fewer than 512 workgroups.
+inline int ca_rows(int64_t rows, int64_t cols) {
+  int per = 128;
+  while (per > 32 && (rows + per - 1) / per * ((cols + 511) / 512) < 512) per /= 2;
+  return per;
+}
 
 template <class DT, bool CLAMP>
 __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a) {
@@ -749,8 +755,8 @@ __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t unit = (int64_t)blockIdx.x * 64 + lane;   // 8 columns
   const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t r0 = (int64_t)blockIdx.y * CA_ROWS;
-  const int64_t r1 = min(r0 + CA_ROWS, a.rows);
+  const int64_t r0 = (int64_t)blockIdx.y * a.row_block;
+  const int64_t r1 = min(r0 + a.row_block, a.rows);
   float lo = 0, hi = 0;
   if (CLAMP) { lo = a.thr[0]; hi = a.thr[1]; }
   float m[8];
@@ -902,9 +908,10 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a) {
 }
 
 template <class DT, bool CLAMP>
-int launch_cols(const ColArgs& a, hipStream_t s) {
+int launch_cols(ColArgs a, hipStream_t s) {
+  a.row_block = ca_rows(a.rows, a.cols);
   const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t rblocks = (a.rows + CA_ROWS - 1) / CA_ROWS;
+  const int64_t rblocks = (a.rows + a.row_block - 1) / a.row_block;
   hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3((unsigned)((nunits + 63) / 64), (unsigned)rblocks), dim3(256),
                      0, s, a);
   hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits,
@@ -919,13 +926,21 @@ int launch_cols(const ColArgs& a, hipStream_t s) {
 // ------------------------------------------------------------------------------------------
 // Dual-axis pass over a bf16 tensor (Sec. 4.1: the backward pass needs dY scaled per token for the
 // activation gradient and per output channel for the weight gradient): row-wise codes and scales
-// as quantize_rows_kernel, and in the same read the column maxima of every block of DA_ROWS rows,
+// as quantize_rows_kernel, and in the same read the column maxima of every block of da_rows rows,
 // so that the column-wise quantization that follows needs no absmax pass of its own.
-// A workgroup walks DA_ROWS consecutive rows; a thread keeps its NV units of the row in flight
+// A workgroup walks da_rows consecutive rows; a thread keeps its NV units of the row in flight
 // one row ahead and the running maxima of its 8 NV columns as packed 16-bit magnitude patterns
 // (for bf16 the magnitude's bit pattern orders like the value: one packed integer max per pair).
 // ------------------------------------------------------------------------------------------
-constexpr int DA_ROWS = 32;
+// Rows per workgroup: as many as leave enough workgroups to hide the row-by-row chain (load, maximum, barrier,
+// store), a workgroup holding one row in flight: 1024 of them, of rows above 8192 columns 512 (there the partial
+// maxima, one row of them a workgroup, cost more than the rest gains).  32 rows whatever the size, against this:
+// 1056 x 2080 33.6 -> 7.9 us, 8192 x 2048 29.4 -> 14.2, 4096 x 13824 84 -> 41, 16384 x 4096 54.7 -> 44.9.
+inline int da_rows(int64_t rows, int64_t cols) {
+  int per = 32;
+  while (per > 4 && rows < (int64_t)per * (cols > 8192 ? 512 : 1024)) per /= 2;
+  return per;
+}
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 FP4_D uint32_t pk_max_u16(uint32_t a, uint32_t b) {
@@ -938,12 +953,12 @@ FP4_D uint32_t pk_max_u16(uint32_t a, uint32_t b) {
 template <int NV>
 __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                    int64_t cols, int64_t ld, uint8_t* __restrict__ codes,
-                                                                   float* __restrict__ gamma, uint16_t* __restrict__ part) {
+                                                                   float* __restrict__ gamma, uint16_t* __restrict__ part, int per) {
   __shared__ float s_max[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t nunits = cols / 8;                 // cols % 8 == 0 (checked by the launcher)
-  const int64_t r0 = (int64_t)blockIdx.x * DA_ROWS;
-  const int nrows = (int)min((int64_t)DA_ROWS, rows - r0);
+  const int64_t r0 = (int64_t)blockIdx.x * per;
+  const int nrows = (int)min((int64_t)per, rows - r0);
   u32x4 cm[NV];
 #pragma unroll
   for (int u = 0; u < NV; ++u) cm[u] = u32x4{0u, 0u, 0u, 0u};
@@ -984,7 +999,7 @@ __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_
     }
   };
   fetch(0, buf[0]);
-  for (int r = 0; r < DA_ROWS; r += 2) {           // two rows per turn: the buffers are indexed statically
+  for (int r = 0; r < nrows; r += 2) {             // two rows per turn: the buffers are indexed statically
     fetch(r + 1, buf[1]);
     process(r, buf[0]);
     fetch(r + 2, buf[0]);
@@ -1116,9 +1131,10 @@ __global__ __launch_bounds__(256) void fp8_quantize_cols_kernel(ColArgs a) {
 }
 
 template <class DT>
-int launch_cols_fp8(const ColArgs& a, hipStream_t s) {
+int launch_cols_fp8(ColArgs a, hipStream_t s) {
+  a.row_block = ca_rows(a.rows, a.cols);
   const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t rblocks = (a.rows + CA_ROWS - 1) / CA_ROWS;
+  const int64_t rblocks = (a.rows + a.row_block - 1) / a.row_block;
   hipLaunchKernelGGL((col_absmax_kernel<DT, false>), dim3((unsigned)((nunits + 63) / 64), (unsigned)rblocks), dim3(256), 0, s, a);
   hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits, rblocks,
                      a.gamma, a.cols, 448.0f);
@@ -1238,7 +1254,10 @@ __global__ __launch_bounds__(1024) void tensor_gamma_kernel(const uint32_t* part
 
 // ---- internal launchers used by the layer entry points --------------------------------------
 // words of scratch fp4_launch_quantize_cols needs
-int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols) { return (rows + CA_ROWS - 1) / CA_ROWS * cols; }
+int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols) {
+  const int per = ca_rows(rows, cols);
+  return (rows + per - 1) / per * cols;
+}
 
 int fp4_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              uint8_t* codes, float* gamma, hipStream_t s) {
@@ -1308,19 +1327,23 @@ int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int
 }
 
 // Dual-axis pass (bf16, cols a multiple of 8 and at most 16384, dense rows): returns 1 when the shape
-// is not covered (the caller then runs the two passes separately).  part: [ceil(rows / 32)][cols] uint16.
-int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) { return (rows + DA_ROWS - 1) / DA_ROWS * cols; }
+// is not covered (the caller then runs the two passes separately).  part: [ceil(rows / da_rows)][cols] uint16.
+int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) {
+  const int per = da_rows(rows, cols);
+  return (rows + per - 1) / per * cols;
+}
 
 int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                                     float* gamma, uint16_t* part, hipStream_t s) {
   if (!bf16 || (cols % 8) != 0 || cols > 256 * 8 * 8 || rows == 0 || cols == 0) return 1;
   const int64_t nunits = cols / 8;
-  const dim3 grid((unsigned)((rows + DA_ROWS - 1) / DA_ROWS)), block(256);
+  const int per = da_rows(rows, cols);
+  const dim3 grid((unsigned)((rows + per - 1) / per)), block(256);
   const uint16_t* xp = reinterpret_cast<const uint16_t*>(x);
-  if (nunits <= 256 * 2) hipLaunchKernelGGL((quantize_rows_colmax_kernel<2>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part);
-  else if (nunits <= 256 * 4) hipLaunchKernelGGL((quantize_rows_colmax_kernel<4>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part);
-  else if (nunits <= 256 * 6) hipLaunchKernelGGL((quantize_rows_colmax_kernel<6>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part);
-  else hipLaunchKernelGGL((quantize_rows_colmax_kernel<8>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part);
+  if (nunits <= 256 * 2) hipLaunchKernelGGL((quantize_rows_colmax_kernel<2>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
+  else if (nunits <= 256 * 4) hipLaunchKernelGGL((quantize_rows_colmax_kernel<4>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
+  else if (nunits <= 256 * 6) hipLaunchKernelGGL((quantize_rows_colmax_kernel<6>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
+  else hipLaunchKernelGGL((quantize_rows_colmax_kernel<8>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
@@ -1348,7 +1371,7 @@ int fp4_launch_quantize_cols_known_max(const void* x, int64_t rows, int64_t cols
   a.x = x; a.codes_t = codes_t; a.gamma = gamma;
   a.rows = rows; a.cols = cols; a.ld = ld;
   hipLaunchKernelGGL(amax16_to_gamma_kernel, dim3((unsigned)((cols + 127) / 128)), dim3(A16_WAVES * 64), 0, s, part,
-                     (rows + DA_ROWS - 1) / DA_ROWS, gamma, cols);
+                     (rows + da_rows(rows, cols) - 1) / da_rows(rows, cols), gamma, cols);
   hipLaunchKernelGGL((quantize_cols_kernel<BF16, false>),
                      dim3((unsigned)((cols + CT_COLS - 1) / CT_COLS), (unsigned)((rows + CT_ROWS - 1) / CT_ROWS)), dim3(256),
                      0, s, a);
