@@ -278,16 +278,24 @@ __global__ __launch_bounds__(1024) void find_long_rows_kernel(const int64_t* row
 
 // The first LD_CAP long rows (outlier channels of the transposed residual: nearly dense) are
 // multiplied as a small dense matrix so that D is streamed once per group of LD_LB of them instead
-// of once per row: a workgroup takes LD_SLICE rows of D x 512 columns x LD_LB long rows, scatters those
+// of once per row: a workgroup takes a slice of D's rows (ld_slice) x 512 columns x LD_LB long rows, scatters those
 // rows' values for its slice into an LDS table V[slice row][long row] (zero where a row has no
 // entry), and every lane keeps LD_LB x 8 accumulators for its 8 columns while the eight waves
 // split the slice's rows.  Partial sums per slice go to a scratch array and are added in slice
 // order by a second kernel, so the result does not depend on scheduling.
 constexpr int LD_LB = 8;         // long rows per workgroup pass (64 accumulators a lane: two workgroups share a CU)
-constexpr int LD_SLICE = 512;    // rows of D per workgroup
+constexpr int LD_SLICE = 512;    // most rows of D per workgroup
 constexpr int LD_CAP = 32;       // long rows the dense path takes; the rest go row by row
 constexpr int LD_COLS = 512;     // columns per workgroup (64 lanes x 8)
 constexpr int LD_WAVES = 8;      // waves per workgroup; they split the slice's rows
+// Rows of D per workgroup: 512, halved (to 64 at least) while that leaves fewer than 256 workgroups, whose stream of D
+// would then run on a part of the chip (512 against this: 1056 x 1376 x 2080 step, both products 35 -> 13 us; 2048^3 fp32
+// 44 -> 22).  Aiming at 512 workgroups gave nothing more and made the summing of the slices longer.
+inline int ld_slice(int64_t Q, int64_t N) {
+  int slice = LD_SLICE;
+  while (slice > 64 && (Q + slice - 1) / slice * ((N + LD_COLS - 1) / LD_COLS) < 256) slice /= 2;
+  return slice;
+}
 constexpr int LD_TABLE = LD_SLICE * LD_LB > LD_WAVES * 2 * LD_COLS ? LD_SLICE * LD_LB : LD_WAVES * 2 * LD_COLS;   // floats
 
 // Main loop and wave reduction of spmm_long_dense_kernel for NL accumulated long rows.
@@ -394,7 +402,7 @@ template <class DT>
 __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                               const float* val, int64_t capacity,
                                                               const int32_t* list, const int32_t* count,
-                                                              const void* D, int64_t Q, int64_t N, float* part) {
+                                                              const void* D, int64_t Q, int64_t N, int slice, float* part) {
   __shared__ __attribute__((aligned(16))) float V[LD_TABLE];   // 32 KiB, reused for the wave reduction
   __shared__ int64_t s_lo[LD_LB], s_en[LD_LB];
   const int n_long = min(*count, LD_CAP);
@@ -402,27 +410,38 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   if (g0 >= n_long) return;
   const int nl = min(LD_LB, n_long - g0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.y * LD_SLICE;
-  const int rows_here = (int)min((int64_t)LD_SLICE, Q - m0);
-  for (int i = tid; i < LD_SLICE * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
-  // where each long row's entries for this slice begin: one lane per long row searches
-  if (tid < nl) {
-    const int64_t row = list[g0 + tid];
+  const int64_t m0 = (int64_t)blockIdx.y * slice;
+  const int rows_here = (int)min((int64_t)slice, Q - m0);
+  const int shift = 31 - __builtin_clz(slice);   // a power of two
+  for (int i = tid; i < slice * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
+  // Where each long row's entries for this slice begin: a wave per long row, 64 probes a round (a bisection by one
+  // lane was a chain of fourteen round trips, a third of the workgroup's time).
+  static_assert(LD_LB <= LD_WAVES, "a wave per long row");
+  if (tid >> 6 < nl) {
+    const int64_t row = list[g0 + (tid >> 6)];
     int64_t lo = row_ptr[row];
     const int64_t en = min(row_ptr[row + 1], capacity);
     int64_t hi = en;
-    while (lo < hi) {   // first entry with column >= m0
-      const int64_t mid = (lo + hi) >> 1;
-      if (col_idx[mid] < m0) lo = mid + 1; else hi = mid;
+    while (lo < hi) {   // the first entry with column >= m0 lies in [lo, hi]
+      const int64_t step = (hi - lo + 63) / 64;
+      const int64_t at = lo + lane * step;
+      const int below = __popcll(__ballot(at < hi && col_idx[min(at, hi - 1)] < m0));   // columns ascend
+      if (below == 0) hi = lo;
+      else {
+        hi = min(hi, lo + below * step);
+        lo += (below - 1) * step + 1;
+      }
     }
-    s_lo[tid] = lo;
-    s_en[tid] = en;
+    if (lane == 0) {
+      s_lo[tid >> 6] = lo;
+      s_en[tid >> 6] = en;
+    }
   }
   __syncthreads();   // table zeroed, starts known
-  // All threads place the values: item j = (long row j / LD_SLICE, offset j % LD_SLICE from its start).
+  // All threads place the values: item j = (long row j / slice, offset j % slice from its start).
   // Columns ascend and are distinct inside a row, so the entries of this slice are among the first
-  // LD_SLICE from the start.  Four items a thread at a time, their loads issued together.
-  const int items = nl * LD_SLICE;
+  // `slice` from the start.  Four items a thread at a time, their loads issued together.
+  const int items = nl * slice;
   const int64_t m_end = m0 + rows_here;
   for (int j0 = tid; j0 < items; j0 += 4 * LD_WAVES * 64) {
     int32_t c[4];
@@ -430,8 +449,8 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = j0 + u * LD_WAVES * 64;
-      const int l = min(j / LD_SLICE, nl - 1);
-      const int64_t i = s_lo[l] + (j % LD_SLICE);
+      const int l = min(j >> shift, nl - 1);
+      const int64_t i = s_lo[l] + (j & (slice - 1));
       const bool ok = j < items && i < s_en[l];
       c[u] = ok ? col_idx[i] : 0x7fffffff;
       v[u] = ok ? val[i] : 0.0f;
@@ -439,7 +458,7 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = j0 + u * LD_WAVES * 64;
-      if (c[u] < m_end) V[(c[u] - m0) * LD_LB + min(j / LD_SLICE, nl - 1)] = v[u];
+      if (c[u] < m_end) V[(c[u] - m0) * LD_LB + min(j >> shift, nl - 1)] = v[u];
     }
   }
   __syncthreads();
@@ -456,7 +475,13 @@ FP4_D void long_reduce(const int32_t* list, int n_long, const float* part, int s
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (n >= N) return;
   float sum = 0.0f;
-  for (int sidx = 0; sidx < slices; ++sidx) sum += part[((int64_t)sidx * LD_CAP + li) * N + n];
+  for (int s0 = 0; s0 < slices; s0 += 8) {   // eight loads in flight, added in slice order
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = s0 + k < slices ? part[((int64_t)(s0 + k) * LD_CAP + li) * N + n] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) sum += v[k];
+  }
   R[(int64_t)list[li] * N + n] = sum;
 }
 
@@ -815,7 +840,8 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
 // the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
 static int64_t spmm_long_words(int64_t P, int64_t Q, int64_t N) {
-  const int64_t slices = (Q + LD_SLICE - 1) / LD_SLICE;
+  const int slice = ld_slice(Q, N);
+  const int64_t slices = (Q + slice - 1) / slice;
   return spmm_list_words(P) + (slices * LD_CAP * N + 63) / 64 * 64;
 }
 int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16) {
@@ -847,17 +873,18 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   }
   if (may_be_long) {
     float* part = reinterpret_cast<float*>(scratch + spmm_list_words(P));
-    const int slices = (int)((Q + LD_SLICE - 1) / LD_SLICE);
+    const int slice = ld_slice(Q, N);
+    const int slices = (int)((Q + slice - 1) / slice);
     const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices, LD_CAP / LD_LB);
     const dim3 rgrid((unsigned)((N + 255) / 256), LD_CAP + LR_ROWS);
     if (bf16) {
       hipLaunchKernelGGL((spmm_long_dense_kernel<BF16>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, part);
+                         count, D, Q, N, slice, part);
       hipLaunchKernelGGL((spmm_long_rows_kernel<BF16>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
                          part, slices, D, N, R);
     } else {
       hipLaunchKernelGGL((spmm_long_dense_kernel<F32>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, part);
+                         count, D, Q, N, slice, part);
       hipLaunchKernelGGL((spmm_long_rows_kernel<F32>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
                          part, slices, D, N, R);
     }
