@@ -403,13 +403,14 @@ def main():
                      "share_of_step": sum(gemm_ms) / ms_total if ms_total else None},
     }
     if spmm_ms:
-        # the kernel the step spends most of its time in: the residual product, plain fp32 FMAs on the
-        # vector ALUs (2 nnz N FLOP per launch), against the published fp32 vector peak
+        # the kernel the step spends most of its time in: the residual product (2 nnz N FLOP per launch; bf16 masters:
+        # packed slots on the matrix cores, bound by vector instructions; fp32: plain FMAs), against the published
+        # fp32 vector peak
         nnz = [int(L["ctx"].nnz.item()) for L in layers]
         spmm_flops = sum(2 * 2.0 * n * L["shape"].N for n, L in zip(nnz, layers))   # forward + weight gradient
         avg_spmm_ms = sum(spmm_ms) / len(spmm_ms)
         ach = spmm_flops / n_spmm / (avg_spmm_ms * 1e-3) / 1e12
-        out["roofline_residual"] = {"bound": "alu", "kernel": "spmm_tile_kernel", "achieved": ach,
+        out["roofline_residual"] = {"bound": "alu", "kernel": "spmm_mfma_kernel" if cfg.dtype == "bf16" else "spmm_tile_kernel", "achieved": ach,
                                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                                     "frac": ach / FP32_VECTOR_PEAK_TFLOPS, "traffic": None,
                                     "avg_launch_ms": avg_spmm_ms, "launches": len(spmm_ms),

@@ -42,7 +42,9 @@ constexpr int SM_NT = 128;       // columns of R per workgroup
 constexpr int SM_ROWB = SM_NT * 2;
 constexpr int SM_CHUNKB = SM_KC * SM_ROWB;
 constexpr int SM_STRIP = 8;      // column blocks that an XCD works on side by side
-constexpr int PK_TPR = 16;       // packing threads per row
+// Packing threads per row: what fills a workgroup.  A row's entries are two chains of loads, so more threads shorten
+// them (2048 rows of 164 entries, 16 / 32 / 64 threads a row: 20.1 / 17.8 / 16.7 us).
+constexpr int pk_tpr(int g) { return g == 1 ? 64 : 16; }
 constexpr int64_t SM_MAXQ = 24576;   // the packing keeps a nibble per column and group in LDS, within 64 KiB
 static_assert(SM_ROWB == 256, "a quarter wave covers a row of a chunk with 16 bytes a lane");
 
@@ -71,13 +73,13 @@ FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
 // steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the general
 // path (more slots than there is room for, or columns that repeat inside a row).
 template <int G>
-__global__ __launch_bounds__(16 * G * PK_TPR) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
+__global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx,
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
                                                                int Q, int cap, int phases, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
                                                                int32_t* __restrict__ steps, int32_t* list, int32_t* count) {
-  constexpr int ROWS = 16 * G, THREADS = ROWS * PK_TPR;
+  constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR;
   extern __shared__ uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
   uint32_t* const nib = pk_lds;                                                // [G][words] a nibble per column: as many bits as slots
@@ -455,7 +457,7 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     int32_t* const sched = reinterpret_cast<int32_t*>(o_buf + bundles * G * (int64_t)(cap + 1) * 64);
     int32_t* const steps = sched + bundles * phases;
     const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)G * phases * 4;
-    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * PK_TPR), lds, s, row_ptr, col_idx, val,
+    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * pk_tpr(G)), lds, s, row_ptr, col_idx, val,
                        capacity, P, (int)Q, cap, phases, a_buf, o_buf, sched, steps, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
