@@ -1,11 +1,13 @@
 // The high-precision sparse product of outlier compensation (Sec. 3.2):
 //   R[P x N] = S D,  S a P x Q CSR matrix with fp32 values (the clamped-away residual or its
 //   transpose), D [Q x N] dense in the master dtype, fp32 accumulation.
-// and the CSR transpose the weight-gradient pass needs (Delta_A^T dY).
+// and the CSR transpose the weight-gradient pass needs (Delta_A^T dY).  bf16 D goes to the matrix cores
+// (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D);
+// the tiled kernel here takes fp32 D and what lies beyond.
 //
 // S has density 2(1 - alpha) (about 2 %), scattered, plus a few nearly dense outlier channels.
 // At that density neither a dense matrix-core product (50x wasted work) nor a row gather
-// (every non-zero re-reads a row of D from L2) is acceptable, so the product is tiled the way
+// (every non-zero re-reads a row of D from L2) is acceptable, so the product of fp32 D is tiled the way
 // a dense GEMM is, with plain fp32 FMAs:
 //   * a workgroup of 1024 threads owns 1024 rows of R x 64 columns, one row per thread, the
 //     64 accumulators in registers;
