@@ -2,7 +2,7 @@
 //   R[P x N] = S D,  S a P x Q CSR matrix with fp32 values (the clamped-away residual or its
 //   transpose), D [Q x N] dense in the master dtype, fp32 accumulation.
 // and the CSR transpose the weight-gradient pass needs (Delta_A^T dY).  bf16 D goes to the matrix cores
-// (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D);
+// (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D, an eighth of S filled);
 // the tiled kernel here takes fp32 D and what lies beyond.
 //
 // S has density 2(1 - alpha) (about 2 %), scattered, plus a few nearly dense outlier channels.
@@ -858,8 +858,13 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   const bool may_be_long = Q > 64 && capacity > 64;   // otherwise no row can be
   int32_t* const count = scratch;
   int32_t* const list = scratch + 64;
+  // The packed product has room for every column of a group of 16 rows once and a quarter more.  Up to 2 entries in 16
+  // columns that holds with a margin whatever their values' tails (Student-t with three degrees of freedom, 10 %: 0.91 of
+  // the columns); at 20 % they would need 1.4 and the groups would fall to the general path one by one.  A capacity that
+  // says nothing (no limit) is taken for the usual few per cent.
+  const bool packs = capacity == INT64_MAX || capacity <= P * Q / 8;
   int rc = 1;
-  if (bf16)
+  if (bf16 && packs)
     rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, s);
   if (rc != 0 && rc != 1) return rc;
   if (rc == 1) {
