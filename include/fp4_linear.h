@@ -298,7 +298,8 @@ int fp4_dge_apply(const float* G, const void* W, fp4_dtype dt, const float* gamm
 
 /* R[P x N] (fp32, overwritten) = S D with S a P x Q CSR matrix (fp32 values) and D
  * [Q x N] dense of dtype dt: the high-precision sparse product of Sec. 3.2.  Column indices
- * must ascend inside a row.  Workspace: fp4_workspace_bytes(FP4_OP_SPMM, P, Q, N, dt). */
+ * must ascend inside a row; a column that occurs more than once counts with the sum of its
+ * values, whatever the row's length.  Workspace: fp4_workspace_bytes(FP4_OP_SPMM, P, Q, N, dt). */
 int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                       int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N,
                       float* R, void* workspace, size_t workspace_bytes, void* stream);

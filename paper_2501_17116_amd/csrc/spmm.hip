@@ -400,6 +400,58 @@ FP4_D void long_dense_body(float* V, const void* D, int64_t m0, int rows_here, i
   }
 }
 
+// Places the values of nl long rows for the D rows m0 .. m0 + rows_here - 1 into the zeroed table V[row][long row]; row
+// l's entries of the slice begin at s_lo[l], and *s_rep is 0 on entry.  Columns ascend inside a row.  Where they are
+// distinct, the entries of the slice are among the first `slice` from the start and every one has a word of its own:
+// item j = (long row j / slice, offset j % slice), four items a thread at a time, their loads issued together.  A row that
+// repeats a column is seen by an entry that equals the one before it (or by one more entry than there are columns): then
+// the first entry of each run writes the run's sum, in the entries' order.
+FP4_D void ld_place(float* V, const int32_t* col_idx, const float* val, const int64_t* s_lo, const int64_t* s_en,
+                    int* s_rep, int nl, int64_t m0, int rows_here, int slice) {
+  constexpr int THREADS = LD_WAVES * 64;
+  const int tid = threadIdx.x;
+  const int shift = 31 - __builtin_clz(slice);   // a power of two
+  const int items = nl * slice;
+  for (int j0 = tid; j0 < items; j0 += 4 * THREADS) {
+    int32_t c[4], before[4];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = j0 + u * THREADS;
+      const int l = min(j >> shift, nl - 1);
+      const int64_t i = s_lo[l] + (j & (slice - 1));
+      const bool ok = j < items && i < s_en[l];
+      c[u] = ok ? col_idx[i] : 0x7fffffff;
+      v[u] = ok ? val[i] : 0.0f;
+      before[u] = ok && i > s_lo[l] ? col_idx[i - 1] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t r = c[u] - m0;
+      if (r < 0 || r >= rows_here) continue;
+      if (before[u] == c[u]) *s_rep = 1;
+      else V[r * LD_LB + min((j0 + u * THREADS) >> shift, nl - 1)] = v[u];
+    }
+  }
+  if (tid < nl) {
+    const int64_t i = s_lo[tid] + slice;
+    if (i < s_en[tid] && col_idx[i] < m0 + rows_here) *s_rep = 1;
+  }
+  __syncthreads();
+  if (*s_rep == 0) return;
+  for (int l = 0; l < nl; ++l)
+    for (int64_t i = s_lo[l] + tid; i < s_en[l]; i += THREADS) {
+      const int32_t c = col_idx[i];
+      const int64_t r = c - m0;
+      if (r >= rows_here) break;
+      if (r < 0 || (i > s_lo[l] && col_idx[i - 1] == c)) continue;
+      float sum = val[i];
+      for (int64_t k = i + 1; k < s_en[l] && col_idx[k] == c; ++k) sum += val[k];
+      V[r * LD_LB + l] = sum;
+    }
+  __syncthreads();
+}
+
 template <class DT>
 __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                               const float* val, int64_t capacity,
@@ -407,6 +459,7 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
                                                               const void* D, int64_t Q, int64_t N, int slice, float* part) {
   __shared__ __attribute__((aligned(16))) float V[LD_TABLE];   // 32 KiB, reused for the wave reduction
   __shared__ int64_t s_lo[LD_LB], s_en[LD_LB];
+  __shared__ int s_rep;
   const int n_long = min(*count, LD_CAP);
   const int g0 = blockIdx.z * LD_LB;
   if (g0 >= n_long) return;
@@ -414,8 +467,8 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t m0 = (int64_t)blockIdx.y * slice;
   const int rows_here = (int)min((int64_t)slice, Q - m0);
-  const int shift = 31 - __builtin_clz(slice);   // a power of two
   for (int i = tid; i < slice * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
+  if (tid == 0) s_rep = 0;
   // Where each long row's entries for this slice begin: a wave per long row, 64 probes a round (a bisection by one
   // lane was a chain of fourteen round trips, a third of the workgroup's time).
   static_assert(LD_LB <= LD_WAVES, "a wave per long row");
@@ -440,30 +493,7 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
     }
   }
   __syncthreads();   // table zeroed, starts known
-  // All threads place the values: item j = (long row j / slice, offset j % slice from its start).
-  // Columns ascend and are distinct inside a row, so the entries of this slice are among the first
-  // `slice` from the start.  Four items a thread at a time, their loads issued together.
-  const int items = nl * slice;
-  const int64_t m_end = m0 + rows_here;
-  for (int j0 = tid; j0 < items; j0 += 4 * LD_WAVES * 64) {
-    int32_t c[4];
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u * LD_WAVES * 64;
-      const int l = min(j >> shift, nl - 1);
-      const int64_t i = s_lo[l] + (j & (slice - 1));
-      const bool ok = j < items && i < s_en[l];
-      c[u] = ok ? col_idx[i] : 0x7fffffff;
-      v[u] = ok ? val[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u * LD_WAVES * 64;
-      if (c[u] < m_end) V[(c[u] - m0) * LD_LB + min(j >> shift, nl - 1)] = v[u];
-    }
-  }
-  __syncthreads();
+  ld_place(V, col_idx, val, s_lo, s_en, &s_rep, nl, m0, rows_here, slice);
   float* const pout = part + (int64_t)blockIdx.y * LD_CAP * N + (int64_t)g0 * N;
   // accumulators only for as many long rows as there are (4 or 8): usually a handful
   if (nl <= 4) long_dense_body<DT, 4>(V, D, m0, rows_here, N, nl, pout);
@@ -855,7 +885,7 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
                     hipStream_t s) {
   if (P == 0 || N == 0) return FP4_OK;
   if (Q >= ((int64_t)1 << 21)) return FP4_ERR_SHAPE;   // 32-bit entry offsets inside a workgroup's 1024 rows
-  const bool may_be_long = Q > 64 && capacity > 64;   // otherwise no row can be
+  const bool may_be_long = Q > SPMM_LONG_MIN && capacity > SPMM_LONG_MIN;   // otherwise no row is
   int32_t* const count = scratch;
   int32_t* const list = scratch + 64;
   // The packed product has room for every column of a group of 16 rows once and a quarter more.  Up to 2 entries in 16

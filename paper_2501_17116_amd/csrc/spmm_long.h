@@ -7,9 +7,13 @@
 #if defined(__HIPCC__)
 // A row is long above a quarter of the columns, at most 2048 entries, but always above four times the mean row.  Measured against 2048 entries whatever the width (steps with one to ten dense
 // channels): fp32 2048^3 1379 -> 429 us, fp32 256 x 512 x 512 337 -> 256 us, bf16 1056 x 1376 x 2080 836 -> 403 us.
+// With 64 columns or fewer no row is long, also not one that repeats columns and so has more entries than that: the
+// long-row kernels are not launched then.
+constexpr int64_t SPMM_LONG_MIN = 64;
 FP4_D int64_t spmm_long_limit(const int64_t* row_ptr, int64_t P, int64_t Q, int64_t capacity) {
-  const float mean = (float)min(row_ptr[P], capacity) / (float)P;
-  return max(min(max(Q / 4, (int64_t)64), (int64_t)2048), (int64_t)(4.0f * mean));
+  if (Q <= SPMM_LONG_MIN) return INT64_MAX;
+  const float mean = (float)(min(row_ptr[P], capacity) - row_ptr[0]) / (float)P;
+  return max(min(max(Q / 4, SPMM_LONG_MIN), (int64_t)2048), (int64_t)(4.0f * mean));
 }
 
 // Rows in ascending order, by one workgroup of THREADS (ballot + scan), so the split between the long-row kernels

@@ -107,6 +107,38 @@ def test_repeated_columns_are_summed():
     assert np.allclose(R[0], 3 * Df[4] - Df[9], rtol=1e-6, atol=1e-6) and np.allclose(R[1], 0.5 * Df[0] + 4 * Df[63], rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Q", [32, 64, 65, 256, 700])
+def test_repeated_columns_in_rows_above_the_long_limit(Q, dtype):
+    """Rows of more entries than a row of distinct columns could have (Q <= 64: no row is long), and rows that count as
+    long (more than max(64, Q / 4) entries) with repeats inside a slice, on its edges and of a whole slice's columns."""
+    from paper_2501_17116_amd import binding as b
+    g = torch.Generator().manual_seed(Q)
+    rows = [torch.arange(0)] * 40
+    rows[3] = torch.arange(Q).repeat_interleave(3)                                   # every column three times
+    rows[17] = torch.cat([torch.arange(min(Q, 90)), torch.tensor([min(Q, 90) - 1])])   # one repeat, on the last column
+    rows[18] = torch.cat([torch.zeros(70, dtype=torch.long), torch.arange(Q)])
+    rows[30] = torch.randint(0, Q, (300,), generator=g).sort().values
+    rows[39] = torch.randint(0, Q, (5,), generator=g).sort().values
+    rp = torch.zeros(41, dtype=torch.int64)
+    torch.cumsum(torch.tensor([len(r) for r in rows]), 0, out=rp[1:])
+    ci = torch.cat(rows)
+    v = torch.randn(len(ci), generator=g)
+    D = torch.randn(Q, 264, generator=g).to(dtype)
+    S = torch.zeros(40, Q, dtype=torch.float64)
+    A = torch.zeros(40, Q, dtype=torch.float64)
+    at = (torch.repeat_interleave(torch.arange(40), rp.diff()), ci)
+    S.index_put_(at, v.double(), accumulate=True)
+    A.index_put_(at, v.double().abs(), accumulate=True)
+    args = (rp.cuda(), ci.int().cuda(), v.cuda(), Q, D.cuda())
+    R = torch.full((40, 264), float("nan"), device="cuda")
+    b.fp4_residual_spmm(*args, R=R)
+    # n products and up to as many sums of values, each rounded once: n * 2^-23 of the magnitudes, as above
+    bound = (rp.diff()[:, None] + 1) * 2.0 ** -23 * (A @ D.double().abs()) + 1e-38
+    assert torch.all((R.cpu().double() - S @ D.double()).abs() <= bound)
+    assert torch.equal(b.fp4_residual_spmm(*args), R)
+
+
 def test_same_bits_every_time():
     from paper_2501_17116_amd import binding as b
     S, D = _draw(700, 1300, 520, 0.03, 2, 17)
