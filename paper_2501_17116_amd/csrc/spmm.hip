@@ -500,27 +500,47 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   else long_dense_body<DT, LD_LB>(V, D, m0, rows_here, N, nl, pout);
 }
 
-// Adds the slices' partial sums of the dense path's rows (blockIdx.y < LD_CAP), 256 columns a workgroup.
-FP4_D void long_reduce(const int32_t* list, int n_long, const float* part, int slices, int64_t N, float* R) {
-  const int li = blockIdx.y;
-  if (li >= min(n_long, LD_CAP)) return;
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  float sum = 0.0f;
-  for (int s0 = 0; s0 < slices; s0 += 8) {   // eight loads in flight, added in slice order
-    float v[8];
+// One long row from its entries alone, for the 256 columns from n0 on: 32 columns at a time, 4 column groups of 8 x 64
+// entry lanes; entry lane l takes entries l, l + 64, ...; the 64 partial sums are added in a fixed order.
+template <class DT>
+FP4_D void long_row_entries(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t row,
+                            int64_t first, const void* D, int64_t N, float* R, float (&part)[64][4][8]) {
+  const int cg = threadIdx.x & 3, el = threadIdx.x >> 2;
+  const int64_t b = row_ptr[row], en = min(row_ptr[row + 1], capacity);
+  for (int64_t n0 = first; n0 < min(first + 256, N); n0 += 32) {
+    const int64_t col = n0 + cg * 8;
+    const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
+    float acc[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = s0 + k < slices ? part[((int64_t)(s0 + k) * LD_CAP + li) * N + n] : 0.0f;
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    if (valid > 0) {
+      for (int64_t i = b + el; i < en; i += 64) {
+        const int32_t c = col_idx[i];
+        const float s = val[i];
+        float d[8];
+        load8g<DT>(D, (int64_t)c * N + col, valid, d);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) sum += v[k];
+        for (int e = 0; e < 8; ++e) acc[e] = fmaf(s, d[e], acc[e]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[el][cg][e] = acc[e];
+    __syncthreads();
+    if (threadIdx.x < 32) {
+      const int g = threadIdx.x >> 3, e = threadIdx.x & 7;
+      float sum = 0.0f;
+      for (int l = 0; l < 64; ++l) sum += part[l][g][e];
+      const int64_t c1 = n0 + g * 8 + e;
+      if (c1 < N) R[row * N + c1] = sum;
+    }
+    __syncthreads();
   }
-  R[(int64_t)list[li] * N + n] = sum;
 }
 
-// The rest of the long rows in one launch: the dense path's rows are added up, and rows beyond its share (list
-// positions from LD_CAP on) are multiplied one at a time: one workgroup per (long row, 32 columns), LR_ROWS rows at
-// a time, 4 column groups of 8 x 64 entry lanes; entry lane l takes entries l, l+64, ...; the 64 partial sums are
-// added in a fixed order.
+// The rest of the long rows in one launch, 256 columns a workgroup.  The dense path's rows (blockIdx.y < LD_CAP): the
+// slices' partial sums are added up; where one comes out infinite or NaN the row's columns are summed from its entries
+// instead, since the table's zeros times an infinity of D in a column the row has no entry in are NaN.  Rows beyond
+// the dense path's share (list positions from LD_CAP on), LR_ROWS at a time, from their entries.
 constexpr int LR_ROWS = 8;
 template <class DT>
 __global__ __launch_bounds__(256) void spmm_long_rows_kernel(const int64_t* row_ptr, const int32_t* col_idx,
@@ -530,43 +550,28 @@ __global__ __launch_bounds__(256) void spmm_long_rows_kernel(const int64_t* row_
                                                              int64_t N, float* R) {
   __shared__ float part[64][4][8];
   const int n_long = *count;
-  if (blockIdx.y < LD_CAP) {
-    long_reduce(list, n_long, partial, slices, N, R);
+  const int64_t n0 = (int64_t)blockIdx.x * 256;
+  if (blockIdx.y >= LD_CAP) {
+    for (int li = blockIdx.y; li < n_long; li += LR_ROWS)
+      long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], n0, D, N, R, part);
     return;
   }
-  const int cg = threadIdx.x & 3, el = threadIdx.x >> 2;
-  for (int li = blockIdx.y; li < n_long; li += LR_ROWS) {
-    const int64_t row = list[li];
-    const int64_t b = row_ptr[row], en = min(row_ptr[row + 1], capacity);
-    for (int64_t n0 = (int64_t)blockIdx.x * 256; n0 < min((int64_t)(blockIdx.x + 1) * 256, N); n0 += 32) {
-      const int64_t col = n0 + cg * 8;
-      const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
-      float acc[8];
+  const int li = blockIdx.y;
+  if (li >= n_long) return;
+  const int64_t n = n0 + threadIdx.x;
+  float sum = 0.0f;
+  if (n < N) {
+    for (int s0 = 0; s0 < slices; s0 += 8) {   // eight loads in flight, added in slice order
+      float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-      if (valid > 0) {
-        for (int64_t i = b + el; i < en; i += 64) {
-          const int32_t c = col_idx[i];
-          const float s = val[i];
-          float d[8];
-          load8g<DT>(D, (int64_t)c * N + col, valid, d);
+      for (int k = 0; k < 8; ++k) v[k] = s0 + k < slices ? partial[((int64_t)(s0 + k) * LD_CAP + li) * N + n] : 0.0f;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[e] = fmaf(s, d[e], acc[e]);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) part[el][cg][e] = acc[e];
-      __syncthreads();
-      if (threadIdx.x < 32) {
-        const int g = threadIdx.x >> 3, e = threadIdx.x & 7;
-        float sum = 0.0f;
-        for (int l = 0; l < 64; ++l) sum += part[l][g][e];
-        const int64_t c1 = n0 + g * 8 + e;
-        if (c1 < N) R[row * N + c1] = sum;
-      }
-      __syncthreads();
+      for (int k = 0; k < 8; ++k) sum += v[k];
     }
+    R[(int64_t)list[li] * N + n] = sum;
   }
+  if (__syncthreads_or((f2u(sum) & 0x7f800000u) == 0x7f800000u))
+    long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], n0, D, N, R, part);
 }
 
 // ---- CSR transpose (P x Q -> Q x P) -----------------------------------------------------------

@@ -96,6 +96,31 @@ def test_non_finite_elements_stay_in_their_rows():
     assert torch.all((((got.double() - ref).abs() <= n * 2.0 ** -23 * mag + 1e-38) | bad))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_non_finite_elements_stay_out_of_long_rows_without_them(dtype):
+    """A long row that has no entry in an infinite element's row of D is finite; one that has, is infinite there only."""
+    from paper_2501_17116_amd import binding as b
+    S, D = _draw(200, 600, 520, 0.01, 1, 19)
+    g = torch.Generator().manual_seed(19)
+    long_rows = [3, 50, 51, 120]
+    for r in long_rows:
+        S[r] = torch.randn(600, generator=g)
+    S[:, 333] = 0
+    S[:, 90] = 0
+    S[50, 333], S[120, 90] = 2.0, -1.0
+    D = D.to(dtype)
+    D[333, 40], D[90, 400] = float("inf"), float("nan")
+    got = b.fp4_residual_spmm(*_csr(S), 600, D.cuda()).cpu()
+    bad = torch.zeros(200, 520, dtype=torch.bool)
+    bad[50, 40] = bad[120, 400] = True
+    assert got[50, 40] == float("inf") and torch.isnan(got[120, 400])
+    Df = D.double()
+    Df[333, 40] = Df[90, 400] = 0
+    ref, mag = S.double() @ Df, S.double().abs() @ Df.abs()
+    n = (S != 0).sum(1, keepdim=True).double() + 1
+    assert torch.all(((got.double() - ref).abs() <= n * 2.0 ** -23 * mag + 1e-38) | bad)
+
+
 def test_repeated_columns_are_summed():
     from paper_2501_17116_amd import binding as b
     D = torch.randn(64, 16).bfloat16()
