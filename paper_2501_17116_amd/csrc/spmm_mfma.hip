@@ -4,8 +4,9 @@
 // group of 16 rows is packed into "slots": one slot per column that any of the 16 rows has an entry in,
 // holding that column's 16 values (zero where a row has none) in bf16.  32 slots make one step of
 // v_mfma_f32_16x16x32_bf16: A = the 16 x 32 packed values, B = the 32 rows of D that the slots name,
-// gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three, and its
-// column takes as many slots: products are exact, sums are fp32, nothing is rounded to 16 bits.
+// gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three (down to 2^-110; rows with
+// smaller values of more bits take the general path), and its column takes as many slots: products are exact, sums are
+// fp32, nothing is rounded to 16 bits.
 //
 // A lane owns 8 adjacent columns of D, so a gathered row arrives as one 16-byte LDS read per lane,
 // 256 contiguous bytes per quarter wave: free of bank conflicts whatever rows the slots name.  The matrix
@@ -52,7 +53,8 @@ static_assert(SM_ROWB == 256, "a quarter wave covers a row of a chunk with 16 by
 inline int64_t sm_cap(int64_t Q) { return (Q + 31) / 32 + (Q + 127) / 128 + 3; }
 inline int64_t sm_phases(int64_t Q) { return (Q + SM_KC - 1) / SM_KC; }
 
-// v as the exact sum of up to three bf16 numbers (nearest first); returns how many
+// v as the exact sum of up to three bf16 numbers (nearest first); returns how many, 4 if three are not enough: below
+// 2^-110 the last of fp32's 24 bits can lie under the smallest bf16 number, 2^-133.
 FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
   int n = 0;
 #pragma unroll
@@ -66,12 +68,13 @@ FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
     const float r = v - u2f(h << 16);
     v = (u & 0x7f800000u) == 0x7f800000u ? 0.0f : r;
   }
-  return n;
+  return v != 0.0f ? 4 : n;
 }
 
 // One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
 // steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the general
-// path (more slots than there is room for, or columns that repeat inside a row).
+// path (more slots than there is room for, columns that repeat inside a row, or values that three bf16 terms do not
+// make up).
 template <int G>
 __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx,
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
       uint32_t t[3];
       const int nt = bf16_terms(v[u], t);
       if (i0 + u * PK_TPR >= n) continue;
-      if ((uint32_t)c[u] >= (uint32_t)Q || before[u] >= c[u]) { s_bad = 1; continue; }
+      if ((uint32_t)c[u] >= (uint32_t)Q || before[u] >= c[u] || nt > 3) { s_bad = 1; continue; }
       atomicOr(&nib[grp * words + (c[u] >> 3)], ((1u << nt) - 1u) << (4 * (c[u] & 7)));
     }
   }

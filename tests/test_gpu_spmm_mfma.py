@@ -72,6 +72,38 @@ def test_extreme_magnitudes():
     _check(S, D)
 
 
+@pytest.mark.parametrize("terms", [2, 3])
+@pytest.mark.parametrize("exp", [-149, -126, -118, -111, -104, 0, 120, 126])
+def test_split_of_extreme_values(terms, exp):
+    """Values around 2^exp, of every bit fp32 has there, against columns of D that bring the products to the middle of
+    the range: the sum of the bf16 terms has to be the value itself (below 2^-110 three of them are not enough)."""
+    from paper_2501_17116_amd import binding as b
+    S, D = _draw(64, 300, 72, 0.02, terms, 11 + terms)   # few enough slots for the packed path
+    S = (S.double() * 2.0 ** exp).clamp(-3.4e38, 3.4e38).float()
+    D = (D.double() * 2.0 ** max(-100, min(100, -exp))).bfloat16()
+    if exp > 100:
+        S[7, :40] = torch.tensor([3.4028234e38, -3.4028234e38, 3.3961776e38, 3.39e38]).repeat(10)
+    got = b.fp4_residual_spmm(*_csr(S), 300, D.cuda()).cpu().double()
+    ref, mag = S.double() @ D.double(), S.double().abs() @ D.double().abs()
+    n = (S != 0).sum(1, keepdim=True).double() + 1
+    # 2^-23 as above; results of subnormal size carry half a unit of 2^-149 per sum besides
+    assert torch.all((got - ref).abs() <= n * 2.0 ** -23 * mag + n * 2.0 ** -150)
+
+
+@pytest.mark.parametrize("exp_s,exp_d", [(-60, -70), (-100, -30), (0, -126), (0, -132), (-100, 0)])
+def test_tiny_products(exp_s, exp_d):
+    """Products and elements of D near and below the smallest normal numbers."""
+    from paper_2501_17116_amd import binding as b
+    S, D = _draw(64, 300, 72, 0.02, 2, 23)
+    S = (S.double() * 2.0 ** exp_s).float()
+    D = (D.double() * 2.0 ** exp_d).bfloat16()
+    got = b.fp4_residual_spmm(*_csr(S), 300, D.cuda()).cpu().double()
+    ref, mag = S.double() @ D.double(), S.double().abs() @ D.double().abs()
+    n = (S != 0).sum(1, keepdim=True).double() + 1
+    # up to three products an entry, each sum rounded to 2^-149 at the finest
+    assert torch.all((got - ref).abs() <= n * 2.0 ** -23 * mag + 3 * n * 2.0 ** -150)
+
+
 def test_non_finite_elements_stay_in_their_rows():
     from paper_2501_17116_amd import binding as b
     S, D = _draw(64, 400, 136, 0.05, 1, 13)
