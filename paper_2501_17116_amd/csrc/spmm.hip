@@ -2,8 +2,9 @@
 //   R[P x N] = S D,  S a P x Q CSR matrix with fp32 values (the clamped-away residual or its
 //   transpose), D [Q x N] dense in the master dtype, fp32 accumulation.
 // and the CSR transpose the weight-gradient pass needs (Delta_A^T dY).  bf16 D goes to the matrix cores
-// (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D, an eighth of S filled);
-// the tiled kernel here takes fp32 D and what lies beyond.
+// (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D) and
+// as the matrix's entries are worth packing, which its packing decides on the device; the tiled kernel here takes fp32 D
+// and the rest.
 //
 // S has density 2(1 - alpha) (about 2 %), scattered, plus a few nearly dense outlier channels.
 // At that density neither a dense matrix-core product (50x wasted work) nor a row gather
@@ -73,23 +74,18 @@ FP4_D void load8g(const void* base, int64_t off, int valid, float (&v)[8]) {
   }
 }
 
+// A workgroup's rows times the 64 columns of D from n0 on.  mine: whether the thread's row is this kernel's to write.
 template <class DT>
-__global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __restrict__ row_ptr,
-                                                            const int32_t* __restrict__ col_idx,
-                                                            const float* __restrict__ val, int64_t capacity,
-                                                            int64_t P, int64_t Q, const void* __restrict__ D,
-                                                            int64_t N, float* __restrict__ R) {
-  __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
-  __shared__ int s_skip[SP_ROWS];
-  const int tid = threadIdx.x;
+FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                           const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q, const void* __restrict__ D,
+                           int64_t N, float* __restrict__ R, int tid, bool mine, int64_t n0, float* slab, int* s_skip) {
   const int64_t row = (int64_t)blockIdx.x * SP_ROWS + tid;
-  const int64_t n0 = (int64_t)blockIdx.y * SP_COLS;
   // Entry positions are kept as 32-bit offsets from the workgroup's first entry (a workgroup's
   // rows hold fewer than 2^31 entries: the launcher bounds Q); the base stays in scalar registers.
   const int64_t ebase = row_ptr[min((int64_t)blockIdx.x * SP_ROWS, P)];
   const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
   uint32_t cur = 0, end = 0;
-  if (row < P) {
+  if (mine) {
     const int64_t b = row_ptr[row];
     int64_t e = max(min(row_ptr[row + 1], capacity), b);
     if (e - b > long_limit) e = b;   // long rows belong to the long-row kernels
@@ -239,7 +235,7 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
   // A lane's 64 sums belong to one row of R (lanes are N floats apart); they go through LDS once
   // more so that the stores run along rows: 16 lanes x 16 B per row, four rows per instruction.
   // A wave's 64 x 64 tile takes 16 KiB, so the workgroup stores in two rounds of eight waves.
-  bool skip = row >= P;   // rows outside the matrix, and long rows (other kernels write those)
+  bool skip = !mine;   // rows outside the matrix, and rows that other kernels write (long ones)
   if (!skip) skip = min(row_ptr[row + 1], capacity) - row_ptr[row] > spmm_long_limit(row_ptr, P, Q, capacity);
   s_skip[tid] = skip ? 1 : 0;
   __syncthreads();   // everyone is done with the last slab
@@ -267,6 +263,37 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
       }
     }
     __syncthreads();
+  }
+}
+
+// REST: only the rows that the packed product left (usually none: the workgroup leaves at once), and a workgroup takes every
+// gridDim.y-th column block of about 512 workgroups: an idle launch is over in 5 us (one workgroup a block: 13), a full one
+// takes as long as with one a block (16384 x 4096 -> 12288, 6 % of two-term values, the product: 256 workgroups 3406 us, 512
+// 3179, 1024 3151, one a block 3158).
+template <class DT, bool REST>
+__global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __restrict__ row_ptr,
+                                                            const int32_t* __restrict__ col_idx,
+                                                            const float* __restrict__ val, int64_t capacity,
+                                                            int64_t P, int64_t Q, const void* __restrict__ D,
+                                                            int64_t N, float* __restrict__ R, SpmmRest rest) {
+  __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
+  __shared__ int s_skip[SP_ROWS];
+  const int64_t row0 = (int64_t)blockIdx.x * SP_ROWS;
+  if constexpr (REST) {
+    auto is_mine = [&](int64_t row) {
+      if (row >= P) return false;
+      const int64_t bundle = row / rest.rows;
+      return rest.steps[bundle] < 0 || rest.steps[rest.bundles + bundle] != 0;
+    };
+    if (!__syncthreads_or(is_mine(row0 + threadIdx.x))) return;
+    for (int64_t n0 = (int64_t)blockIdx.y * SP_COLS; n0 < N; n0 += (int64_t)gridDim.y * SP_COLS) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each column block: kept across, they spill
+      spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, tid, is_mine(row0 + tid), n0, slab, s_skip);
+    }
+  } else {
+    spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, threadIdx.x, row0 + threadIdx.x < P,
+                        (int64_t)blockIdx.y * SP_COLS, slab, s_skip);
   }
 }
 
@@ -872,7 +899,7 @@ void fp4_trace_close(int slot, hipStream_t stream);
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q);
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
-                         hipStream_t s);
+                         SpmmRest& rest, hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
 // the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
@@ -893,22 +920,21 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   const bool may_be_long = Q > SPMM_LONG_MIN && capacity > SPMM_LONG_MIN;   // otherwise no row is
   int32_t* const count = scratch;
   int32_t* const list = scratch + 64;
-  // The packed product has room for every column of a group of 16 rows once and a quarter more.  Up to 2 entries in 16
-  // columns that holds with a margin whatever their values' tails (Student-t with three degrees of freedom, 10 %: 0.91 of
-  // the columns); at 20 % they would need 1.4 and the groups would fall to the general path one by one.  A capacity that
-  // says nothing (no limit) is taken for the usual few per cent.
-  const bool packs = capacity == INT64_MAX || capacity <= P * Q / 8;
+  const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
   int rc = 1;
-  if (bf16 && packs)
-    rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, s);
+  SpmmRest rest{nullptr, 0, 0};
+  if (bf16)
+    rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, rest, s);
   if (rc != 0 && rc != 1) return rc;
-  if (rc == 1) {
-    const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
+  if (rc == 0) {
+    const dim3 rgrid(grid.x, std::min(grid.y, std::max(1u, 512u / grid.x)));
+    hipLaunchKernelGGL((spmm_tile_kernel<BF16, true>), rgrid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
+  } else {
     const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);
     if (bf16)
-      hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+      hipLaunchKernelGGL((spmm_tile_kernel<BF16, false>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
     else
-      hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+      hipLaunchKernelGGL((spmm_tile_kernel<F32, false>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
     fp4_trace_close(trace_slot, s);
     if (may_be_long)
       hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count);

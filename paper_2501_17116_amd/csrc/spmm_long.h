@@ -4,6 +4,14 @@
 #pragma once
 #include "fp4_common.h"
 
+// What the packed product of spmm_mfma.hip leaves to the tiled kernel: bundle i has the rows from i * rows on, and is left
+// where steps[i] < 0 or steps[bundles + i] != 0.
+struct SpmmRest {
+  const int32_t* steps;
+  int64_t bundles;
+  int rows;
+};
+
 #if defined(__HIPCC__)
 // A row is long above a quarter of the columns, at most 2048 entries, but always above four times the mean row.  Measured against 2048 entries whatever the width (steps with one to ten dense
 // channels): fp32 2048^3 1379 -> 429 us, fp32 256 x 512 x 512 337 -> 256 us, bf16 1056 x 1376 x 2080 836 -> 403 us.

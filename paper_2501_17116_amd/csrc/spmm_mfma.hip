@@ -5,7 +5,7 @@
 // holding that column's 16 values (zero where a row has none) in bf16.  32 slots make one step of
 // v_mfma_f32_16x16x32_bf16: A = the 16 x 32 packed values, B = the 32 rows of D that the slots name,
 // gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three (down to 2^-110; rows with
-// smaller values of more bits take the general path), and its column takes as many slots: products are exact, sums are
+// smaller values of more bits are left to the tiled kernel), and its column takes as many slots: products are exact, sums are
 // fp32, nothing is rounded to 16 bits.
 //
 // A lane owns 8 adjacent columns of D, so a gathered row arrives as one 16-byte LDS read per lane,
@@ -49,6 +49,12 @@ constexpr int pk_tpr(int g) { return g == 1 ? 64 : 16; }
 constexpr int64_t SM_MAXQ = 24576;   // the packing keeps a nibble per column and group in LDS, within 64 KiB
 static_assert(SM_ROWB == 256, "a quarter wave covers a row of a chunk with 16 bytes a lane");
 
+// Slots a column up to which a matrix is packed, at a share d of entries.  The packed product takes a time that goes with
+// the slots, the tiled one's goes with the entries; they meet at 0.21 slots and 0.21 more per per cent of entries
+// (8192 x 4096 -> 11008: 1 % and 0.45 slots 548 against 523 us, 2 % and 0.55 640 / 712, 2 % and 0.83 879 / 712, 4 % and 0.96
+// 989 / 1097), at 0.10 in a smaller one (4096^3), where launches count.  A grid that does not fill the chip with the
+// tiled kernel's workgroups is packed as far as there is room, with a margin (512 x 4096 -> 4096, 2 %, 0.83: 86 / 90).
+constexpr float SM_ROOM_SLOTS = 1.15f, SM_EVEN_SLOTS = 0.14f, SM_EVEN_SHARE = 21.0f;
 // steps a group of 16 rows has room for: every column once, and a quarter more for values of several terms
 inline int64_t sm_cap(int64_t Q) { return (Q + 31) / 32 + (Q + 127) / 128 + 3; }
 inline int64_t sm_phases(int64_t Q) { return (Q + SM_KC - 1) / SM_KC; }
@@ -71,15 +77,33 @@ FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
   return v != 0.0f ? 4 : n;
 }
 
+// Whether a matrix is worth packing, from 256 rows spread over it (every workgroup looks at the same ones and comes to the
+// same answer, which depends on the matrix alone): the slots a column of a group needs on average, from the rows' entries
+// and the number of terms of one value of each.  rows[0..3]: rows that are not long, their entries, those of values
+// of two terms or more, of three.
+constexpr int PK_SAMPLE = 256;
+FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
+  const float cells = fmaxf((float)rows[0], 1.0f) * (float)Q;
+  float slots = 0.0f;
+#pragma unroll
+  for (int t = 1; t < 4; ++t) {
+    float none = fmaxf(1.0f - (float)rows[t] / cells, 0.0f);   // no row of 16 has one
+#pragma unroll
+    for (int k = 0; k < 4; ++k) none *= none;
+    slots += 1.0f - none;
+  }
+  return slots <= SM_ROOM_SLOTS && (small_grid || slots <= SM_EVEN_SLOTS + SM_EVEN_SHARE * (float)rows[1] / cells);
+}
+
 // One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
-// steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the general
-// path (more slots than there is room for, columns that repeat inside a row, or values that three bf16 terms do not
-// make up).
+// steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the tiled kernel (a
+// matrix that is not worth it, more slots than there is room for, columns that repeat inside a row, or values that three
+// bf16 terms do not make up); steps[bundles + bundle]: 0.
 template <int G>
 __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx,
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
-                                                               int Q, int cap, int phases, uint8_t* __restrict__ a_buf,
+                                                               int Q, int cap, int phases, bool small_grid, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
                                                                int32_t* __restrict__ steps, int32_t* list, int32_t* count) {
   constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR;
@@ -90,28 +114,59 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   uint16_t* const pre = reinterpret_cast<uint16_t*>(start + G * phases);   // [G][words] slots of the chunk before this word
   __shared__ int64_t s_b[ROWS];
   __shared__ int s_n[ROWS];
-  __shared__ int s_bad, s_total[G], s_steps;
+  __shared__ int s_bad, s_total[G], s_steps, s_sample[4][4];
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {   // the first workgroup lists the long rows
     find_long_rows<THREADS>(row_ptr, P, Q, capacity, list, count);
     return;
   }
-  const int64_t bundle = blockIdx.x - 1;
+  const int64_t bundle = blockIdx.x - 1, bundles = gridDim.x - 1;
+  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
+  // entries of a row; long ones are the long-row kernels' business
+  auto entries = [&](int64_t row, int64_t& b) -> int64_t {
+    b = row_ptr[row];
+    return max(min(row_ptr[row + 1], capacity), b) - b;
+  };
   for (int i = tid; i < G * words; i += THREADS) nib[i] = 0;
   if (tid < ROWS) {
     const int64_t row = bundle * ROWS + tid;
     int64_t b = 0, n = 0;
-    if (row < P) {
-      b = row_ptr[row];
-      n = max(min(row_ptr[row + 1], capacity), b) - b;
-      if (n > spmm_long_limit(row_ptr, P, Q, capacity)) n = 0;   // the long-row kernels' business
-    }
+    if (row < P) n = entries(row, b);
     s_b[tid] = b;
-    s_n[tid] = (int)n;
+    s_n[tid] = n > long_limit ? 0 : (int)n;
+  }
+  static_assert(THREADS >= 2 * PK_SAMPLE, "the last waves sample");
+  if (tid >= THREADS - PK_SAMPLE) {
+    int64_t b;
+    const int64_t n = entries((int64_t)(tid - (THREADS - PK_SAMPLE)) * P / PK_SAMPLE, b);
+    int c[4] = {n <= long_limit ? 1 : 0, n <= long_limit ? (int)min(n, (int64_t)Q) : 0, 0, 0};
+    if (c[1] > 0) {
+      uint32_t t[3];
+      const int nt = bf16_terms(val[b + n / 2], t);
+      c[2] = nt > 1 ? c[1] : 0;
+      c[3] = nt > 2 ? c[1] : 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] += __shfl_xor(c[k], o, 64);
+    if ((tid & 63) == 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s_sample[(THREADS - 1 - tid) >> 6][k] = c[k];
   }
   if (tid == 0) s_bad = 0;
   if (tid < G) s_total[tid] = 0;
   __syncthreads();
+  {
+    int rows[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rows[k] = s_sample[0][k] + s_sample[1][k] + s_sample[2][k] + s_sample[3][k];
+    if (tid == 0) steps[bundles + bundle] = 0;
+    if (!pk_worth(rows, Q, small_grid)) {
+      if (tid == 0) steps[bundle] = -1;
+      return;
+    }
+  }
   const int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
   const int grp = br / 16, r = br % 16;
   const int n = s_n[br];
@@ -235,44 +290,14 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   }
 }
 
-// The general path for one group of 16 rows and the workgroup's columns: plain fp32 sums over the rows' entries.
-FP4_D void sm_general(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
-                      int64_t Q, const uint16_t* D, int64_t N, int64_t row0, int64_t n0, int lane, float* R) {
-  const int64_t col = n0 + lane * 2;   // N is a multiple of 8
-  if (col >= N) return;
-  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
-  for (int64_t row = row0; row < min(row0 + 16, P); ++row) {
-    const int64_t b = row_ptr[row], e = max(min(row_ptr[row + 1], capacity), b);
-    if (e - b > long_limit) continue;
-    float s0 = 0.0f, s1 = 0.0f;
-    for (int64_t i = b; i < e; i += 8) {   // eight rows of D in flight
-      uint32_t d[8];
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int64_t c = i + k < e ? col_idx[i + k] : -1;
-        const bool ok = c >= 0 && c < Q;
-        v[k] = ok ? val[i + k] : 0.0f;
-        d[k] = ok ? *reinterpret_cast<const uint32_t*>(D + c * N + col) : 0u;
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        s0 = fmaf(v[k], u2f(d[k] << 16), s0);
-        s1 = fmaf(v[k], u2f(d[k] & 0xffff0000u), s1);
-      }
-    }
-    R[row * N + col] = s0;
-    R[row * N + col + 1] = s1;
-  }
-}
-
-// WV waves multiply, G groups of 16 rows each; one more stages D.
+// WV waves multiply, G groups of 16 rows each; one more stages D.  Bundles that are not packed are left out, and a
+// bundle with a non-finite sum is marked in steps[bundles + bundle]: a zero value times an infinite or NaN element of D
+// reaches the other rows of the group.  The tiled kernel writes the rows of both afterwards, from their entries.
 template <int G, int WV>
 __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t* __restrict__ a_buf, const uint8_t* __restrict__ o_buf,
                                                             const int32_t* __restrict__ sched, const int32_t* __restrict__ steps,
-                                                            int cap, int phases, int row_blocks, int col_blocks,
-                                                            const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                                                            const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q,
+                                                            int32_t* __restrict__ redo, int cap, int phases, int row_blocks,
+                                                            int col_blocks, int64_t P, int64_t Q,
                                                             const uint16_t* __restrict__ D, int64_t N, float* __restrict__ R) {
   __shared__ __attribute__((aligned(16))) uint8_t ring[SM_RING * SM_CHUNKB];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -288,6 +313,14 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
   const int64_t n0 = (int64_t)(SM_STRIP * strip + in_strip % width) * SM_NT;
   const int rb = in_strip / width;
   const int64_t bundles = (P + 16 * G - 1) / (16 * G);
+  // Nothing packed among the workgroup's bundles: every wave sees that alike (steps is written by the packing only) and
+  // leaves.  Scalar loads, so that the staging wave's chunks are on their way meanwhile.
+  auto nothing = [&]() {
+    int32_t most = -1;
+#pragma unroll
+    for (int w = 0; w < WV; ++w) most = max(most, steps[min((int64_t)rb * WV + w, bundles - 1)]);
+    return most < 0;
+  };
 
   if (wave == WV) {
     // The staging wave.  Its loads are its own business: a wave's loads return in order, so in a multiplying wave
@@ -312,6 +345,10 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
     };
 #pragma unroll 1
     for (int c = 0; c < SM_AHEAD; ++c) stage(c);
+    if (nothing()) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // as at the end
+      return;
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((SM_AHEAD - 1) * LD) : "memory");
     __builtin_amdgcn_s_barrier();
 #pragma unroll 1
@@ -324,6 +361,7 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
     return;
   }
 
+  if (nothing()) return;
   f32x4 acc[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -332,7 +370,7 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
   // The packed steps are read through scalar descriptors (a wave's groups lie one after another): the lane part
   // of an address is one register, whatever the group.
   const int64_t bundle = (int64_t)rb * WV + wave;
-  const bool live = bundle < bundles;
+  const bool live = bundle < bundles && steps[min(bundle, bundles - 1)] >= 0;
   const int64_t bl = live ? bundle : 0;
   const uint32_t a_stride = (uint32_t)(cap + 1) * 1024u, o_stride = (uint32_t)(cap + 1) * 64u;
   const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
@@ -395,19 +433,18 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
     __builtin_amdgcn_s_barrier();
   }
 
+  if (!live) return;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     const int64_t row0 = (bundle * G + g) * 16;
     if (row0 >= P) break;
-    // A zero value times an infinite or NaN element of D would reach the other rows of the group; and a group
-    // that was not packed has no sums at all: both take the general path.
     float nf = 0.0f;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) nf = fmaf(acc[g][j][i], 0.0f, nf);
-    if (steps[bundle] < 0 || __ballot(nf != 0.0f) != 0ull) {
-      sm_general(row_ptr, col_idx, val, capacity, P, Q, D, N, row0, n0, lane, R);
+    if (__ballot(nf != 0.0f) != 0ull) {
+      if (lane == 0) redo[bundle] = 1;
       continue;
     }
     // A lane holds 8 columns of 4 rows; four neighbours exchange 16-byte pieces so that each store instruction
@@ -441,16 +478,18 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
   if (Q > SM_MAXQ || Q <= 0) return 0;
   const int64_t groups = (P + 15) / 16 + 2;   // whole bundles of up to three
-  return groups * ((sm_cap(Q) + 1) * (1024 + 64) + (sm_phases(Q) + 1) * 4) + 1024;
+  return groups * ((sm_cap(Q) + 1) * (1024 + 64) + (sm_phases(Q) + 2) * 4) + 1024;
 }
 
-// Returns 1 when the product is left to the fp32 kernel.
+// Returns 1 when the product is left to the tiled kernel.  Otherwise that kernel has what remains: the rows of bundle i
+// (rest.rows of them) where rest.steps[i] < 0 or rest.steps[rest.bundles + i] != 0.
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
-                         hipStream_t s) {
+                         SpmmRest& rest, hipStream_t s) {
   if (Q > SM_MAXQ || Q <= 0 || (uint64_t)(Q + 4 * SM_KC) * (uint64_t)N * 2 > 0xe0000000ull) return 1;   // 32-bit offsets into D
   const int cap = (int)sm_cap(Q), phases = (int)sm_phases(Q);
   const int col_blocks = (int)((N + SM_NT - 1) / SM_NT);
+  const bool small_grid = (P + 1023) / 1024 * ((N + 63) / 64) < 256;   // workgroups of the tiled kernel
   auto blocks = [&](int g, int wv) { return (P + 16 * g * wv - 1) / (16 * g * wv); };
   auto launch = [&](auto g_c, auto wv_c) {
     constexpr int G = decltype(g_c)::value, WV = decltype(wv_c)::value;
@@ -461,14 +500,15 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     int32_t* const steps = sched + bundles * phases;
     const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)G * phases * 4;
     hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * pk_tpr(G)), lds, s, row_ptr, col_idx, val,
-                       capacity, P, (int)Q, cap, phases, a_buf, o_buf, sched, steps, list, count);
+                       capacity, P, (int)Q, cap, phases, small_grid, a_buf, o_buf, sched, steps, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
     const int slot = fp4_trace_open(FP4_TRACE_SPMM, s);
     hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
-                       steps, cap, phases, row_blocks, col_blocks, row_ptr, col_idx, val, capacity, P, Q,
-                       reinterpret_cast<const uint16_t*>(D), N, R);
+                       steps, steps + bundles, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
+                       N, R);
     fp4_trace_close(slot, s);
+    rest = SpmmRest{steps, bundles, 16 * G};
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
   // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows

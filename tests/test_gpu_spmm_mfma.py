@@ -52,9 +52,46 @@ def test_against_fp64(P, Q, N, density, terms):
     _check(*_draw(P, Q, N, density, terms, P + Q + N))
 
 
-@pytest.mark.parametrize("density", [0.0, 1.0])
-def test_empty_and_full(density):
-    _check(*_draw(200, 700, 136, density, 3 if density else 1, 5))   # full with three terms: more slots than there is room for
+@pytest.mark.parametrize("density,terms", [(0.0, 1), (1.0, 1), (1.0, 3)])
+def test_empty_and_full(density, terms):
+    _check(*_draw(200, 700, 136, density, terms, 5))
+
+
+@pytest.mark.parametrize("P,N", [(700, 520), (4500, 4104)])
+def test_bundles_without_room_beside_packed_ones(P, N):
+    """Groups whose three-term values take more slots than there is room for, in a matrix that is worth packing: the tiled
+    kernel writes their rows (one workgroup's, and in several), the packed product the others'."""
+    S, D = _draw(P, 1300, N, 0.01, 1, 29)
+    g = torch.Generator().manual_seed(29)
+    for r0 in (32, P - 20):
+        rows = slice(r0, min(r0 + 16, P))
+        n = S[rows].shape[0]
+        S[rows] = torch.randn(n, 1300, generator=g) * (torch.rand(n, 1300, generator=g) < 0.23)   # just not long
+    R = _check(S, D)
+    few = S.clone()
+    few[32:48] = 0
+    few[P - 20:P - 4] = 0
+    from paper_2501_17116_amd import binding as b
+    far = slice(96, P - 100)   # other bundles: the same bits whatever their neighbours hold
+    assert torch.equal(b.fp4_residual_spmm(*_csr(few), 1300, D.cuda())[far], R[far])
+
+
+@pytest.mark.parametrize("scope", [0, 1])
+def test_spare_capacity_changes_nothing(scope):
+    """Residual buffers larger than the clamp needs (as for alpha = 0.9): the same kernels, the same bits."""
+    from paper_2501_17116_amd import binding as b
+    torch.manual_seed(7)
+    M, K, N = 512, 768, 520 + 24
+    A = torch.randn(M, K, device="cuda")
+    A[:, 5] *= 30
+    A, W, dY = A.bfloat16(), (torch.randn(K, N, device="cuda") * 0.02).bfloat16(), (torch.randn(M, N, device="cuda") * 0.01).bfloat16()
+    out = []
+    for alpha in (0.99, 0.9):
+        ctx = b.FwdCtx(M, K, N, alpha, scope=scope)
+        Y, _ = b.fp4_linear_fwd(A, W, 0.99, ctx=ctx)
+        out.append((Y, *b.fp4_linear_bwd(dY, A, W, ctx, 5.0, 3.0), b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 5.0, 3.0)))
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
 
 
 def test_long_rows_and_dense_columns():
