@@ -1253,10 +1253,11 @@ __global__ __launch_bounds__(1024) void tensor_gamma_kernel(const uint32_t* part
 }
 
 // ---- internal launchers used by the layer entry points --------------------------------------
-// words of scratch fp4_launch_quantize_cols needs
+// words of scratch fp4_launch_quantize_cols needs, for this tensor and any smaller one (a caller sizes its workspace once,
+// for the largest): a block of fewer than 128 rows is only taken while twice its rows leave fewer than 512 workgroups of
+// 512 columns, so there are at most 1022 of them.
 int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols) {
-  const int per = ca_rows(rows, cols);
-  return (rows + per - 1) / per * cols;
+  return std::max((rows + 127) / 128 * cols, std::min<int64_t>((rows + 31) / 32 * cols, 1022 * 512));
 }
 
 int fp4_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
@@ -1328,9 +1329,11 @@ int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int
 
 // Dual-axis pass (bf16, cols a multiple of 8 and at most 16384, dense rows): returns 1 when the shape
 // is not covered (the caller then runs the two passes separately).  part: [ceil(rows / da_rows)][cols] uint16.
+// For this tensor and any smaller one: fewer than 32 rows a workgroup are only taken while twice as many leave fewer than
+// 1024 workgroups (above 8192 columns 512), so there are at most 2048 (1024) rows of partial maxima then.
 int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) {
-  const int per = da_rows(rows, cols);
-  return (rows + per - 1) / per * cols;
+  const int64_t most = (rows + 3) / 4, in = std::min<int64_t>(cols, 256 * 8 * 8);   // wider tensors are not covered
+  return std::max({(rows + 31) / 32 * in, std::min<int64_t>(most, 2048) * std::min<int64_t>(in, 8192), std::min<int64_t>(most, 1024) * in});
 }
 
 int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,

@@ -903,10 +903,11 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
 // the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
+// The partial sums' share, for this product and any smaller one: slices of fewer than 512 rows are only taken while twice as
+// many rows leave fewer than 256 workgroups of 512 columns, so there are at most 510 of them.
 static int64_t spmm_long_words(int64_t P, int64_t Q, int64_t N) {
-  const int slice = ld_slice(Q, N);
-  const int64_t slices = (Q + slice - 1) / slice;
-  return spmm_list_words(P) + (slices * LD_CAP * N + 63) / 64 * 64;
+  const int64_t most = std::max((Q + LD_SLICE - 1) / LD_SLICE * N, std::min<int64_t>((Q + 63) / 64 * N, 510 * LD_COLS));
+  return spmm_list_words(P) + (most * LD_CAP + 63) / 64 * 64;
 }
 int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16) {
   return spmm_long_words(P, Q, N) + (bf16 ? (fp4_spmm_mfma_scratch_bytes(P, Q) + 3) / 4 : 0);

@@ -474,9 +474,10 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
 
 }  // namespace
 
-// bytes of scratch the packed form of a P x Q matrix takes (0: this path does not take the matrix)
+// bytes of scratch the packed form of a P x Q matrix takes, and that of any smaller one: a matrix too wide for this path
+// counts as the widest that is not
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
-  if (Q > SM_MAXQ || Q <= 0) return 0;
+  Q = std::min(Q, SM_MAXQ);
   const int64_t groups = (P + 15) / 16 + 2;   // whole bundles of up to three
   return groups * ((sm_cap(Q) + 1) * (1024 + 64) + (sm_phases(Q) + 2) * 4) + 1024;
 }

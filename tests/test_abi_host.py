@@ -194,3 +194,25 @@ def test_library_fp8_rounding_equals_the_oracle_bit_for_bit(L):
               np.exp(rng.uniform(-25, 8, 2_000_000)) * rng.choice([-1, 1], 2_000_000)):
         x = x.astype(np.float32)
         assert np.array_equal(b.fp8_host_round_codes(x), o.q_e4m3(x))
+
+
+def test_a_smaller_problem_never_needs_a_larger_workspace(L):
+    """A buffer sized for the largest shape serves every smaller one, across the sizes at which a kernel changes its block,
+    slice or path."""
+    rng = np.random.default_rng(5)
+    edges = [64, 512, 1024, 2048, 4096, 7136, 8064, 8160, 8192, 8224, 11008, 12288, 16288, 16384, 24576, 24608, 32768]
+
+    def size():
+        return int(rng.choice(edges)) if rng.random() < 0.5 else 32 * int(np.exp(rng.uniform(np.log(1), np.log(1024))))
+
+    def bytes_of(op, s, dt):
+        return b.workspace_bytes(op, *s, dt)
+
+    for op in range(9):
+        for dt in (b.FP4_F32, b.FP4_BF16):
+            assert bytes_of(op, (8064, 2048, 2048), dt) <= bytes_of(op, (8192, 2048, 2048), dt)
+            assert bytes_of(op, (16288, 11008, 4096), dt) <= bytes_of(op, (16384, 11008, 12288), dt)
+            for _ in range(3000):
+                big = (size(), size(), size())
+                small = tuple(min(x, size()) if rng.random() < 0.6 else x for x in big)
+                assert bytes_of(op, small, dt) <= bytes_of(op, big, dt), (op, dt, small, big)
