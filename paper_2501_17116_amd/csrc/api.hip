@@ -108,11 +108,16 @@ struct OccTemps {
   int32_t* row_cnt;
   unsigned long long* total;
 };
-OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity) {
+// later: words of scratch whose use begins when the unordered entries are in their place; they share one block.
+OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity, int64_t later = 0, int32_t** later_out = nullptr) {
   OccTemps t;
   t.select = c.take<uint8_t>(fp4_select_scratch_bytes());
-  t.tmp_col = c.take<int32_t>((size_t)capacity);
-  t.tmp_val = c.take<float>((size_t)capacity);
+  Carver in = c;   // the entries' two arrays, or what comes later
+  t.tmp_col = in.take<int32_t>((size_t)capacity);
+  t.tmp_val = in.take<float>((size_t)capacity);
+  int32_t* const shared = c.take<int32_t>((size_t)later);
+  if (later_out) *later_out = shared;
+  c.off = std::max(c.off, in.off);
   t.row_start = c.take<int64_t>((size_t)rows);
   t.row_cnt = c.take<int32_t>((size_t)rows);
   t.total = c.take<unsigned long long>(1);
@@ -132,9 +137,8 @@ FwdWs carve_fwd(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   w.amax = c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(K, N));
   // sized for the densest residual the entry points accept (alpha > 0.5 -> fewer than M*K entries);
   // the workspace query does not know alpha, so it provides for alpha >= 0.9
-  w.occ = carve_occ(c, M, provisioned_entries(M, K));
+  w.occ = carve_occ(c, M, provisioned_entries(M, K), fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16), &w.sp_scratch);
   w.R = dt == FP4_BF16 ? c.take<float>((size_t)(M * N)) : nullptr;
-  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16));
   w.tg = c.take<uint32_t>((size_t)fp4_tensor_gamma_scratch_words());
   return w;
 }
@@ -146,9 +150,8 @@ FwdWs carve_fwd_mixed(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) 
   w.gA = c.take<float>((size_t)M);
   w.qWt = c.take<uint8_t>((size_t)(N * K));
   w.amax = c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(K, N));
-  w.occ = carve_occ(c, M, provisioned_entries(M, K));
+  w.occ = carve_occ(c, M, provisioned_entries(M, K), fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16), &w.sp_scratch);
   w.R = dt == FP4_BF16 ? c.take<float>((size_t)(M * N)) : nullptr;
-  w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(M, K, N, dt == FP4_BF16));
   w.tg = nullptr;
   return w;
 }
@@ -179,10 +182,13 @@ WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   w.t_ptr = c.take<int64_t>((size_t)(K + 1));
   w.t_idx = c.take<int32_t>((size_t)cap);
   w.t_val = c.take<float>((size_t)cap);
-  w.u_idx = c.take<int32_t>((size_t)cap);
-  w.u_val = c.take<float>((size_t)cap);
-  w.t_scratch = c.take<int32_t>((size_t)fp4_csr_transpose_scratch_words(M, K));
+  // the transposition is over when the product begins: its temporaries and the product's share one block
+  Carver in = c;
+  w.u_idx = in.take<int32_t>((size_t)cap);
+  w.u_val = in.take<float>((size_t)cap);
+  w.t_scratch = in.take<int32_t>((size_t)fp4_csr_transpose_scratch_words(M, K));
   w.sp_scratch = c.take<int32_t>((size_t)fp4_spmm_scratch_words(K, M, N, dt == FP4_BF16));
+  c.off = std::max(c.off, in.off);
   return w;
 }
 

@@ -216,3 +216,16 @@ def test_a_smaller_problem_never_needs_a_larger_workspace(L):
                 big = (size(), size(), size())
                 small = tuple(min(x, size()) if rng.random() < 0.6 else x for x in big)
                 assert bytes_of(op, small, dt) <= bytes_of(op, big, dt), (op, dt, small, big)
+
+
+def test_residual_temporaries_and_product_share_their_room(L):
+    """Forward and weight gradient hold either the unordered entries or the product's scratch at a time."""
+    MiB = 1 << 20
+    for M, K, N in ((16384, 11008, 4096), (16384, 4096, 12288), (4096, 5120, 13824)):
+        entries = 8 * b.occ_capacity(M, K, 0.9)
+        codes = (M + N) * K // 2
+        fwd = b.workspace_bytes(b.FP4_OP_FWD, M, K, N, b.FP4_BF16)
+        assert fwd <= codes + 4 * M * N + max(entries, b.workspace_bytes(b.FP4_OP_SPMM, M, K, N, b.FP4_BF16)) + 4 * MiB
+        wgrad = b.workspace_bytes(b.FP4_OP_WGRAD, M, K, N, b.FP4_BF16)
+        masks = 8 * ((M + 63) // 64) * K   # the transposition's counts and offsets
+        assert wgrad <= (K + N) * M // 2 + entries + max(entries + masks, b.workspace_bytes(b.FP4_OP_SPMM, K, M, N, b.FP4_BF16)) + 12 * MiB
