@@ -17,8 +17,7 @@
 //   * a thread walks its row's entries (ascending columns) slab by slab: per non-zero 64 FMAs
 //     against one LDS row.
 // Rows much longer than the rest (the outlier channels of the transposed residual, spmm_long_limit) would
-// stall their workgroup; they are left out of the tiled kernel and handled by a kernel that
-// spreads one row's entries over a workgroup and reduces.
+// stall their workgroup; they are left out of the tiled kernel and multiplied eight at a time as a dense matrix.
 #include "fp4_common.h"
 #include "fp4_measure.h"
 #include "spmm_long.h"
@@ -74,15 +73,15 @@ FP4_D void load8g(const void* base, int64_t off, int valid, float (&v)[8]) {
   }
 }
 
-// A workgroup's rows times the 64 columns of D from n0 on.  mine: whether the thread's row is this kernel's to write.
+// A block of SP_ROWS rows times the 64 columns of D from n0 on.  mine: whether the thread's row is to be written.
 template <class DT>
 FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                            const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q, const void* __restrict__ D,
-                           int64_t N, float* __restrict__ R, int tid, bool mine, int64_t n0, float* slab, int* s_skip) {
-  const int64_t row = (int64_t)blockIdx.x * SP_ROWS + tid;
+                           int64_t N, float* __restrict__ R, int64_t block, int tid, bool mine, int64_t n0, float* slab, int* s_skip) {
+  const int64_t row = block * SP_ROWS + tid;
   // Entry positions are kept as 32-bit offsets from the workgroup's first entry (a workgroup's
   // rows hold fewer than 2^31 entries: the launcher bounds Q); the base stays in scalar registers.
-  const int64_t ebase = row_ptr[min((int64_t)blockIdx.x * SP_ROWS, P)];
+  const int64_t ebase = row_ptr[min(block * SP_ROWS, P)];
   const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
   uint32_t cur = 0, end = 0;
   if (mine) {
@@ -257,7 +256,7 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
           const int r = 4 * ps + (lane >> 4);
           if (!s_skip[wave * 64 + r]) {
             const f32x4 t = *reinterpret_cast<const f32x4*>(&tile[r * SP_COLS + tc * 4]);
-            *reinterpret_cast<f32x4*>(R + ((int64_t)blockIdx.x * SP_ROWS + wave * 64 + r) * N + col) = t;
+            *reinterpret_cast<f32x4*>(R + (block * SP_ROWS + wave * 64 + r) * N + col) = t;
           }
         }
       }
@@ -266,35 +265,16 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
   }
 }
 
-// REST: only the rows that the packed product left (usually none: the workgroup leaves at once), and a workgroup takes every
-// gridDim.y-th column block of about 512 workgroups: an idle launch is over in 5 us (one workgroup a block: 13), a full one
-// takes as long as with one a block (16384 x 4096 -> 12288, 6 % of two-term values, the product: 256 workgroups 3406 us, 512
-// 3179, 1024 3151, one a block 3158).
-template <class DT, bool REST>
+template <class DT>
 __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col_idx,
                                                             const float* __restrict__ val, int64_t capacity,
                                                             int64_t P, int64_t Q, const void* __restrict__ D,
-                                                            int64_t N, float* __restrict__ R, SpmmRest rest) {
+                                                            int64_t N, float* __restrict__ R) {
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
   __shared__ int s_skip[SP_ROWS];
-  const int64_t row0 = (int64_t)blockIdx.x * SP_ROWS;
-  if constexpr (REST) {
-    auto is_mine = [&](int64_t row) {
-      if (row >= P) return false;
-      const int64_t bundle = row / rest.rows;
-      return rest.steps[bundle] < 0 || rest.steps[rest.bundles + bundle] != 0;
-    };
-    if (!__syncthreads_or(is_mine(row0 + threadIdx.x))) return;
-    for (int64_t n0 = (int64_t)blockIdx.y * SP_COLS; n0 < N; n0 += (int64_t)gridDim.y * SP_COLS) {
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each column block: kept across, they spill
-      spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, tid, is_mine(row0 + tid), n0, slab, s_skip);
-    }
-  } else {
-    spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, threadIdx.x, row0 + threadIdx.x < P,
-                        (int64_t)blockIdx.y * SP_COLS, slab, s_skip);
-  }
+  spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
+                      (int64_t)blockIdx.x * SP_ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS, slab, s_skip);
 }
 
 // ---- long rows -------------------------------------------------------------------------------
@@ -305,19 +285,18 @@ __global__ __launch_bounds__(1024) void find_long_rows_kernel(const int64_t* row
   find_long_rows<1024>(row_ptr, P, Q, capacity, list, count);
 }
 
-// The first LD_CAP long rows (outlier channels of the transposed residual: nearly dense) are
-// multiplied as a small dense matrix so that D is streamed once per group of LD_LB of them instead
-// of once per row: a workgroup takes a slice of D's rows (ld_slice) x 512 columns x LD_LB long rows, scatters those
-// rows' values for its slice into an LDS table V[slice row][long row] (zero where a row has no
-// entry), and every lane keeps LD_LB x 8 accumulators for its 8 columns while the eight waves
-// split the slice's rows.  Partial sums per slice go to a scratch array and are added in slice
+// Long rows (outlier channels of the transposed residual: nearly dense) are multiplied as a small dense matrix so that D is
+// streamed once per group of LD_LB of them instead of once per row: a workgroup takes a span of D's rows x 512 columns x
+// LD_LB long rows, scatters those rows' values for as many rows of the span as fit into an LDS table V[row][long row] (zero
+// where a row has no entry), and every lane keeps LD_LB x 8 accumulators for its 8 columns while the eight waves
+// split the table's rows.  Partial sums per span go to a scratch array and are added in span
 // order by a second kernel, so the result does not depend on scheduling.
 constexpr int LD_LB = 8;         // long rows per workgroup pass (64 accumulators a lane: two workgroups share a CU)
-constexpr int LD_SLICE = 512;    // most rows of D per workgroup
-constexpr int LD_CAP = 32;       // long rows the dense path takes; the rest go row by row
+constexpr int LD_SLICE = 512;    // most rows of D in the table, and in a slice
+constexpr int LD_CAP = 32;       // long rows up to which a span is one slice; sizes the partial sums' scratch
 constexpr int LD_COLS = 512;     // columns per workgroup (64 lanes x 8)
 constexpr int LD_WAVES = 8;      // waves per workgroup; they split the slice's rows
-// Rows of D per workgroup: 512, halved (to 64 at least) while that leaves fewer than 256 workgroups, whose stream of D
+// Rows of D per slice: 512, halved (to 64 at least) while that leaves fewer than 256 workgroups for a group of long rows, whose stream of D
 // would then run on a part of the chip (512 against this: 1056 x 1376 x 2080 step, both products 35 -> 13 us; 2048^3 fp32
 // 44 -> 22).  Aiming at 512 workgroups gave nothing more and made the summing of the slices longer.
 inline int ld_slice(int64_t Q, int64_t N) {
@@ -325,19 +304,23 @@ inline int ld_slice(int64_t Q, int64_t N) {
   while (slice > 64 && (Q + slice - 1) / slice * ((N + LD_COLS - 1) / LD_COLS) < 256) slice /= 2;
   return slice;
 }
+// Slices a span has with n_long long rows: as few as leave room for every row's sums of every span in the scratch, which has
+// LD_CAP rows' for every slice.  A single span goes straight to R and takes none.  4096 x 2048 -> 2048, 40 long rows of 0.4,
+// fp32: those beyond LD_CAP over the whole of D by four workgroups 148 us, row by row 117, this 68; 4096 x 4096 -> 4096, 256
+// of 0.5, bf16: row by row 3162, all in the tiled kernel 1509, this 230.
+FP4_D int ld_span(int n_long, int slices) {
+  int m = (n_long + LD_CAP - 1) / LD_CAP;
+  while (m < slices && (int64_t)((slices + m - 1) / m) * n_long > (int64_t)LD_CAP * slices) ++m;
+  return max(1, min(m, slices));
+}
 constexpr int LD_TABLE = LD_SLICE * LD_LB > LD_WAVES * 2 * LD_COLS ? LD_SLICE * LD_LB : LD_WAVES * 2 * LD_COLS;   // floats
 
-// Main loop and wave reduction of spmm_long_dense_kernel for NL accumulated long rows.
+// Main loop of spmm_long_dense_kernel for NL accumulated long rows: adds the slice's products to the wave's sums.
 template <class DT, int NL>
-FP4_D void long_dense_body(float* V, const void* D, int64_t m0, int rows_here, int64_t N, int nl, float* pout) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+FP4_D void long_dense_add(int tid, const float* V, const void* D, int64_t m0, int rows_here, int64_t N, float (&acc)[NL][8]) {
+  const int lane = tid & 63, wave = tid >> 6;
   const int64_t col = (int64_t)blockIdx.x * LD_COLS + lane * 8;
   const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
-  float acc[NL][8];
-#pragma unroll
-  for (int l = 0; l < NL; ++l)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[l][e] = 0.0f;
   constexpr int UN = NL <= 4 ? 6 : 4;   // rows in flight per wave
   auto fma_row = [&](int row, const float (&d)[8]) {
     const f32x4* vr = reinterpret_cast<const f32x4*>(&V[row * LD_LB]);
@@ -400,7 +383,12 @@ FP4_D void long_dense_body(float* V, const void* D, int64_t m0, int rows_here, i
       fma_row(r, d);
     }
   }
-  // add the waves' sums, two long rows at a time, in wave order
+}
+
+// Adds the waves' sums, two long rows at a time, in wave order, and hands out(long row, column, sum) the columns in range.
+template <int NL, class Out>
+FP4_D void long_dense_reduce(int tid, float* V, const float (&acc)[NL][8], int64_t N, int nl, Out out) {
+  const int lane = tid & 63, wave = tid >> 6;
   float* red = V;   // [LD_WAVES][2 rows][512 columns]
   static_assert(LD_WAVES * 2 * LD_COLS <= LD_TABLE, "reduction buffer fits the table");
 #pragma unroll
@@ -421,7 +409,7 @@ FP4_D void long_dense_body(float* V, const void* D, int64_t m0, int rows_here, i
         float sum = 0.0f;
 #pragma unroll
         for (int w = 0; w < LD_WAVES; ++w) sum += red[(w * 2 + ri) * LD_COLS + c];
-        pout[(int64_t)(q * 2 + ri) * N + gcol] = sum;
+        out(q * 2 + ri, gcol, sum);
       }
     }
   }
@@ -433,10 +421,9 @@ FP4_D void long_dense_body(float* V, const void* D, int64_t m0, int rows_here, i
 // item j = (long row j / slice, offset j % slice), four items a thread at a time, their loads issued together.  A row that
 // repeats a column is seen by an entry that equals the one before it (or by one more entry than there are columns): then
 // the first entry of each run writes the run's sum, in the entries' order.
-FP4_D void ld_place(float* V, const int32_t* col_idx, const float* val, const int64_t* s_lo, const int64_t* s_en,
+FP4_D void ld_place(int tid, float* V, const int32_t* col_idx, const float* val, const int64_t* s_lo, const int64_t* s_en,
                     int* s_rep, int nl, int64_t m0, int rows_here, int slice) {
   constexpr int THREADS = LD_WAVES * 64;
-  const int tid = threadIdx.x;
   const int shift = 31 - __builtin_clz(slice);   // a power of two
   const int items = nl * slice;
   for (int j0 = tid; j0 < items; j0 += 4 * THREADS) {
@@ -479,62 +466,95 @@ FP4_D void ld_place(float* V, const int32_t* col_idx, const float* val, const in
   __syncthreads();
 }
 
+// The sums of nl long rows, at most NL, over the rows of D in the table: to[l][column], added to what is there unless `set`.
+template <class DT, int NL>
+FP4_D void long_dense_turn(int tid, float* V, const void* D, int64_t m0, int rows_here, int64_t N, int nl, bool set, float* to,
+                            const int32_t* rows) {
+  float acc[NL][8];
+#pragma unroll
+  for (int l = 0; l < NL; ++l)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[l][e] = 0.0f;
+  long_dense_add<DT>(tid, V, D, m0, rows_here, N, acc);
+  long_dense_reduce(tid, V, acc, N, nl, [&](int l, int64_t col, float sum) {
+    float* const at = to + (rows ? (int64_t)rows[l] : (int64_t)l) * N + col;
+    *at = set ? sum : *at + sum;   // the thread that wrote it
+  });
+}
+
+// Items (group of eight long rows, span), as many per column block as there are; blockIdx.y takes every gridDim.y-th.  The
+// sums leave the registers after every turn of a span: kept across the next one's table they spill.
 template <class DT>
 __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                               const float* val, int64_t capacity,
                                                               const int32_t* list, const int32_t* count,
-                                                              const void* D, int64_t Q, int64_t N, int slice, float* part) {
+                                                              const void* D, int64_t Q, int64_t N, int slice, int slices,
+                                                              float* part, float* R) {
   __shared__ __attribute__((aligned(16))) float V[LD_TABLE];   // 32 KiB, reused for the wave reduction
   __shared__ int64_t s_lo[LD_LB], s_en[LD_LB];
   __shared__ int s_rep;
-  const int n_long = min(*count, LD_CAP);
-  const int g0 = blockIdx.z * LD_LB;
-  if (g0 >= n_long) return;
-  const int nl = min(LD_LB, n_long - g0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t m0 = (int64_t)blockIdx.y * slice;
-  const int rows_here = (int)min((int64_t)slice, Q - m0);
-  for (int i = tid; i < slice * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
-  if (tid == 0) s_rep = 0;
-  // Where each long row's entries for this slice begin: a wave per long row, 64 probes a round (a bisection by one
-  // lane was a chain of fourteen round trips, a third of the workgroup's time).
-  static_assert(LD_LB <= LD_WAVES, "a wave per long row");
-  if (tid >> 6 < nl) {
-    const int64_t row = list[g0 + (tid >> 6)];
-    int64_t lo = row_ptr[row];
-    const int64_t en = min(row_ptr[row + 1], capacity);
-    int64_t hi = en;
-    while (lo < hi) {   // the first entry with column >= m0 lies in [lo, hi]
-      const int64_t step = (hi - lo + 63) / 64;
-      const int64_t at = lo + lane * step;
-      const int below = __popcll(__ballot(at < hi && col_idx[min(at, hi - 1)] < m0));   // columns ascend
-      if (below == 0) hi = lo;
-      else {
-        hi = min(hi, lo + below * step);
-        lo += (below - 1) * step + 1;
+  const int n_long = *count;
+  const int groups = (n_long + LD_LB - 1) / LD_LB;
+  const int span = ld_span(n_long, slices), spans = (slices + span - 1) / span;
+  int rows_a_turn = slice;   // what of a span the table takes at a time: a power of two
+  while (2 * rows_a_turn <= min(LD_SLICE, span * slice)) rows_a_turn *= 2;
+  for (int item = blockIdx.y; item < groups * spans; item += gridDim.y) {
+    const int g0 = item % groups * LD_LB, nl = min(LD_LB, n_long - g0);
+    const int64_t first = (int64_t)(item / groups) * span * slice, last = min(first + (int64_t)span * slice, Q);
+#pragma unroll 1
+    for (int64_t m0 = first; m0 < last; m0 += rows_a_turn) {
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each turn: kept across, they spill
+      const int lane = tid & 63, wave = tid >> 6;
+      const int rows_here = (int)min((int64_t)rows_a_turn, last - m0);
+      __syncthreads();   // everyone is done with the table
+      for (int i = tid; i < rows_a_turn * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
+      if (tid == 0) s_rep = 0;
+      // A wave per long row finds where its entries for the turn begin, 64 probes a round (a bisection by one lane was a
+      // chain of fourteen round trips, a third of the workgroup's time), from the row's start or the turn before's.
+      static_assert(LD_LB <= LD_WAVES, "a wave per long row");
+      if (wave < nl) {
+        const int64_t row = list[g0 + wave];
+        int64_t lo = m0 == first ? row_ptr[row] : s_lo[wave];
+        const int64_t en = min(row_ptr[row + 1], capacity);
+        int64_t hi = en;
+        while (lo < hi) {   // the first entry with column >= m0 lies in [lo, hi]
+          const int64_t step = (hi - lo + 63) / 64;
+          const int64_t at = lo + lane * step;
+          const int below = __popcll(__ballot(at < hi && col_idx[min(at, hi - 1)] < m0));   // columns ascend
+          if (below == 0) hi = lo;
+          else {
+            hi = min(hi, lo + below * step);
+            lo += (below - 1) * step + 1;
+          }
+        }
+        if (lane == 0) {
+          s_lo[wave] = lo;
+          s_en[wave] = en;
+        }
       }
-    }
-    if (lane == 0) {
-      s_lo[tid >> 6] = lo;
-      s_en[tid >> 6] = en;
+      __syncthreads();   // table zeroed, starts known
+      ld_place(tid, V, col_idx, val, s_lo, s_en, &s_rep, nl, m0, rows_here, rows_a_turn);
+      float* const to = spans > 1 ? part + ((int64_t)(item / groups) * n_long + g0) * N : R;
+      const int32_t* const rows = spans > 1 ? nullptr : list + g0;
+      if (nl <= 4)   // sums only for as many long rows as there are (4 or 8): usually a handful
+        long_dense_turn<DT, 4>(tid, V, D, m0, rows_here, N, nl, m0 == first, to, rows);
+      else
+        long_dense_turn<DT, LD_LB>(tid, V, D, m0, rows_here, N, nl, m0 == first, to, rows);
     }
   }
-  __syncthreads();   // table zeroed, starts known
-  ld_place(V, col_idx, val, s_lo, s_en, &s_rep, nl, m0, rows_here, slice);
-  float* const pout = part + (int64_t)blockIdx.y * LD_CAP * N + (int64_t)g0 * N;
-  // accumulators only for as many long rows as there are (4 or 8): usually a handful
-  if (nl <= 4) long_dense_body<DT, 4>(V, D, m0, rows_here, N, nl, pout);
-  else long_dense_body<DT, LD_LB>(V, D, m0, rows_here, N, nl, pout);
 }
 
-// One long row from its entries alone, for the 256 columns from n0 on: 32 columns at a time, 4 column groups of 8 x 64
-// entry lanes; entry lane l takes entries l, l + 64, ...; the 64 partial sums are added in a fixed order.
+// One long row from its entries alone, 256 columns per 256 threads from `first` on: 32 columns at a time, 4 column groups of
+// 8 x 64 entry lanes; entry lane l takes entries l, l + 64, ...; the 64 partial sums are added in a fixed order.
 template <class DT>
 FP4_D void long_row_entries(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t row,
-                            int64_t first, const void* D, int64_t N, float* R, float (&part)[64][4][8]) {
-  const int cg = threadIdx.x & 3, el = threadIdx.x >> 2;
+                            int64_t first, const void* D, int64_t N, float* R, float* part) {
+  const int cg = threadIdx.x & 3, el = (threadIdx.x & 255) >> 2;
+  float* const mine = part + (threadIdx.x >> 8) * (64 * 32);   // [64][4][8]
   const int64_t b = row_ptr[row], en = min(row_ptr[row + 1], capacity);
-  for (int64_t n0 = first; n0 < min(first + 256, N); n0 += 32) {
+  for (int k = 0; k < 8; ++k) {
+    const int64_t n0 = first + (threadIdx.x >> 8) * 256 + k * 32;
     const int64_t col = n0 + cg * 8;
     const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
     float acc[8];
@@ -551,54 +571,93 @@ FP4_D void long_row_entries(const int64_t* row_ptr, const int32_t* col_idx, cons
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part[el][cg][e] = acc[e];
+    for (int e = 0; e < 8; ++e) mine[el * 32 + cg * 8 + e] = acc[e];
     __syncthreads();
-    if (threadIdx.x < 32) {
-      const int g = threadIdx.x >> 3, e = threadIdx.x & 7;
+    if ((threadIdx.x & 255) < 32) {
       float sum = 0.0f;
-      for (int l = 0; l < 64; ++l) sum += part[l][g][e];
-      const int64_t c1 = n0 + g * 8 + e;
+      for (int l = 0; l < 64; ++l) sum += mine[l * 32 + (threadIdx.x & 31)];
+      const int64_t c1 = n0 + (threadIdx.x & 31);
       if (c1 < N) R[row * N + c1] = sum;
     }
     __syncthreads();
   }
 }
 
-// The rest of the long rows in one launch, 256 columns a workgroup.  The dense path's rows (blockIdx.y < LD_CAP): the
-// slices' partial sums are added up; where one comes out infinite or NaN the row's columns are summed from its entries
-// instead, since the table's zeros times an infinity of D in a column the row has no entry in are NaN.  Rows beyond
-// the dense path's share (list positions from LD_CAP on), LR_ROWS at a time, from their entries.
-constexpr int LR_ROWS = 8;
+// What the dense path leaves to do, a column a thread from `first` on, every rows_apart-th long row from row0 on: the spans'
+// partial sums are added up, and where a row's sum is infinite or NaN the row's columns are summed from its
+// entries instead, since the table's zeros times an infinity of D in a column the row has no entry in are NaN.  part:
+// 64 x 32 floats per 256 threads.
 template <class DT>
-__global__ __launch_bounds__(256) void spmm_long_rows_kernel(const int64_t* row_ptr, const int32_t* col_idx,
-                                                             const float* val, int64_t capacity,
-                                                             const int32_t* list, const int32_t* count,
-                                                             const float* partial, int slices, const void* D,
-                                                             int64_t N, float* R) {
-  __shared__ float part[64][4][8];
-  const int n_long = *count;
-  const int64_t n0 = (int64_t)blockIdx.x * 256;
-  if (blockIdx.y >= LD_CAP) {
-    for (int li = blockIdx.y; li < n_long; li += LR_ROWS)
-      long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], n0, D, N, R, part);
+FP4_D void finish_long_rows(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
+                            const int32_t* list, int n_long, int row0, int rows_apart, const float* partial, int slices,
+                            int64_t first, const void* D, int64_t N, float* R, float* part) {
+  const int64_t n = first + threadIdx.x;
+  const int span = ld_span(n_long, slices), spans = (slices + span - 1) / span;
+  for (int li = row0; li < n_long; li += rows_apart) {
+    float* const r = R + (int64_t)list[li] * N;
+    float sum = 0.0f;
+    if (n < N) {
+      if (spans > 1) {
+        for (int s0 = 0; s0 < spans; s0 += 8) {   // eight loads in flight, added in span order
+          float v[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) v[k] = s0 + k < spans ? partial[((int64_t)(s0 + k) * n_long + li) * N + n] : 0.0f;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) sum += v[k];
+        }
+        r[n] = sum;
+      } else {
+        sum = r[n];
+      }
+    }
+    if (__syncthreads_or((f2u(sum) & 0x7f800000u) == 0x7f800000u))
+      long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], first, D, N, R, part);
+  }
+}
+
+constexpr int LF_ROWS = 16;   // long rows side by side
+template <class DT>
+__global__ __launch_bounds__(256) void spmm_finish_long_kernel(const int64_t* row_ptr, const int32_t* col_idx,
+                                                               const float* val, int64_t capacity, const int32_t* list,
+                                                               const int32_t* count, const float* partial, int slices,
+                                                               const void* D, int64_t N, float* R) {
+  __shared__ float part[64 * 32];
+  finish_long_rows<DT>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.y, LF_ROWS, partial, slices,
+                       (int64_t)blockIdx.x * 256, D, N, R, part);
+}
+
+// After the packed product and the dense path, one launch for what both leave.  The first long_blocks workgroups finish the
+// long rows; the other tiles.x * tiles.y take the rows that the packed product left (usually none: the workgroup leaves at
+// once), each every tiles.y-th column block.  About 512 of them: an idle launch is over in 5 us (one workgroup a block: 13),
+// a full one takes as long as with one a block (16384 x 4096 -> 12288, 6 % of two-term values, the product: 256 workgroups
+// 3406 us, 512 3179, 1024 3151, one a block 3158).
+__global__ __launch_bounds__(SP_ROWS) void spmm_rest_kernel(const int64_t* __restrict__ row_ptr,
+                                                            const int32_t* __restrict__ col_idx,
+                                                            const float* __restrict__ val, int64_t capacity,
+                                                            int64_t P, int64_t Q, const void* __restrict__ D,
+                                                            int64_t N, float* __restrict__ R, SpmmRest rest, dim3 tiles,
+                                                            unsigned long_blocks, const int32_t* list, const int32_t* count,
+                                                            const float* partial, int slices) {
+  __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
+  __shared__ int s_skip[SP_ROWS];
+  if (blockIdx.x < long_blocks) {
+    finish_long_rows<BF16>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.x % LF_ROWS, LF_ROWS, partial, slices,
+                           (int64_t)(blockIdx.x / LF_ROWS) * SP_ROWS, D, N, R, slab);
     return;
   }
-  const int li = blockIdx.y;
-  if (li >= n_long) return;
-  const int64_t n = n0 + threadIdx.x;
-  float sum = 0.0f;
-  if (n < N) {
-    for (int s0 = 0; s0 < slices; s0 += 8) {   // eight loads in flight, added in slice order
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = s0 + k < slices ? partial[((int64_t)(s0 + k) * LD_CAP + li) * N + n] : 0.0f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) sum += v[k];
-    }
-    R[(int64_t)list[li] * N + n] = sum;
+  const unsigned tile = blockIdx.x - long_blocks;
+  const int64_t block = tile % tiles.x, row0 = block * SP_ROWS;
+  auto is_mine = [&](int64_t row) {
+    if (row >= P) return false;
+    const int64_t bundle = row / rest.rows;
+    return rest.steps[bundle] < 0 || rest.steps[rest.bundles + bundle] != 0;
+  };
+  if (!__syncthreads_or(is_mine(row0 + threadIdx.x))) return;
+  for (int64_t n0 = (int64_t)(tile / tiles.x) * SP_COLS; n0 < N; n0 += (int64_t)tiles.y * SP_COLS) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each column block: kept across, they spill
+    spmm_tile_block<BF16>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, block, tid, is_mine(row0 + tid), n0, slab, s_skip);
   }
-  if (__syncthreads_or((f2u(sum) & 0x7f800000u) == 0x7f800000u))
-    long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], n0, D, N, R, part);
 }
 
 // ---- CSR transpose (P x Q -> Q x P) -----------------------------------------------------------
@@ -901,7 +960,7 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
                          SpmmRest& rest, hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
-// the fp32 partial sums of the dense long-row path, [slices][LD_CAP][N], then (bf16 D) the packed matrix.
+// the fp32 partial sums of the dense long-row path, [spans][long rows][N], at most LD_CAP x slices rows of N, then (bf16 D) the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
 // The partial sums' share, for this product and any smaller one: slices of fewer than 512 rows are only taken while twice as
 // many rows leave fewer than 256 workgroups of 512 columns, so there are at most 510 of them.
@@ -927,36 +986,42 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   if (bf16)
     rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, rest, s);
   if (rc != 0 && rc != 1) return rc;
-  if (rc == 0) {
-    const dim3 rgrid(grid.x, std::min(grid.y, std::max(1u, 512u / grid.x)));
-    hipLaunchKernelGGL((spmm_tile_kernel<BF16, true>), rgrid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
-  } else {
+  const bool packed = rc == 0;
+  if (!packed) {
     const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);
     if (bf16)
-      hipLaunchKernelGGL((spmm_tile_kernel<BF16, false>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
+      hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
     else
-      hipLaunchKernelGGL((spmm_tile_kernel<F32, false>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R, rest);
+      hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
     fp4_trace_close(trace_slot, s);
     if (may_be_long)
       hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count);
   }
+  float* const part = reinterpret_cast<float*>(scratch + spmm_list_words(P));
+  const int slice = ld_slice(Q, N);
+  const int slices = (int)((Q + slice - 1) / slice);
   if (may_be_long) {
-    float* part = reinterpret_cast<float*>(scratch + spmm_list_words(P));
-    const int slice = ld_slice(Q, N);
-    const int slices = (int)((Q + slice - 1) / slice);
-    const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices, LD_CAP / LD_LB);
-    const dim3 rgrid((unsigned)((N + 255) / 256), LD_CAP + LR_ROWS);
-    if (bf16) {
+    const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices * (LD_CAP / LD_LB));
+    if (bf16)
       hipLaunchKernelGGL((spmm_long_dense_kernel<BF16>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, slice, part);
-      hipLaunchKernelGGL((spmm_long_rows_kernel<BF16>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
-                         part, slices, D, N, R);
-    } else {
+                         count, D, Q, N, slice, slices, part, R);
+    else
       hipLaunchKernelGGL((spmm_long_dense_kernel<F32>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, slice, part);
-      hipLaunchKernelGGL((spmm_long_rows_kernel<F32>), rgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count,
-                         part, slices, D, N, R);
-    }
+                         count, D, Q, N, slice, slices, part, R);
+  }
+  if (packed) {
+    const dim3 tiles(grid.x, std::min(grid.y, std::max(1u, 512u / grid.x)));
+    const unsigned long_blocks = may_be_long ? LF_ROWS * (unsigned)((N + SP_ROWS - 1) / SP_ROWS) : 0;
+    hipLaunchKernelGGL(spmm_rest_kernel, dim3(tiles.x * tiles.y + long_blocks), dim3(SP_ROWS), 0, s, row_ptr, col_idx, val,
+                       capacity, P, Q, D, N, R, rest, tiles, long_blocks, list, count, part, slices);
+  } else if (may_be_long) {
+    const dim3 fgrid((unsigned)((N + 255) / 256), LF_ROWS);
+    if (bf16)
+      hipLaunchKernelGGL((spmm_finish_long_kernel<BF16>), fgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count, part,
+                         slices, D, N, R);
+    else
+      hipLaunchKernelGGL((spmm_finish_long_kernel<F32>), fgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count, part,
+                         slices, D, N, R);
   }
   FP4_CHECK_LAUNCH();
   return FP4_OK;

@@ -135,38 +135,20 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
     s_b[tid] = b;
     s_n[tid] = n > long_limit ? 0 : (int)n;
   }
+  // The sample: its value is on its way while the rows' entries are looked at.
   static_assert(THREADS >= 2 * PK_SAMPLE, "the last waves sample");
-  if (tid >= THREADS - PK_SAMPLE) {
+  const bool sampler = tid >= THREADS - PK_SAMPLE;
+  int sample_n = -1;
+  float sample_v = 0.0f;
+  if (sampler) {
     int64_t b;
     const int64_t n = entries((int64_t)(tid - (THREADS - PK_SAMPLE)) * P / PK_SAMPLE, b);
-    int c[4] = {n <= long_limit ? 1 : 0, n <= long_limit ? (int)min(n, (int64_t)Q) : 0, 0, 0};
-    if (c[1] > 0) {
-      uint32_t t[3];
-      const int nt = bf16_terms(val[b + n / 2], t);
-      c[2] = nt > 1 ? c[1] : 0;
-      c[3] = nt > 2 ? c[1] : 0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] += __shfl_xor(c[k], o, 64);
-    if ((tid & 63) == 0)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s_sample[(THREADS - 1 - tid) >> 6][k] = c[k];
+    if (n <= long_limit) sample_n = (int)min(n, (int64_t)Q);
+    if (sample_n > 0) sample_v = val[b + n / 2];
   }
   if (tid == 0) s_bad = 0;
   if (tid < G) s_total[tid] = 0;
   __syncthreads();
-  {
-    int rows[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) rows[k] = s_sample[0][k] + s_sample[1][k] + s_sample[2][k] + s_sample[3][k];
-    if (tid == 0) steps[bundles + bundle] = 0;
-    if (!pk_worth(rows, Q, small_grid)) {
-      if (tid == 0) steps[bundle] = -1;
-      return;
-    }
-  }
   const int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
   const int grp = br / 16, r = br % 16;
   const int n = s_n[br];
@@ -191,7 +173,31 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
       atomicOr(&nib[grp * words + (c[u] >> 3)], ((1u << nt) - 1u) << (4 * (c[u] & 7)));
     }
   }
+  if (sampler) {
+    uint32_t t[3];
+    const int nt = bf16_terms(sample_v, t);
+    int c[4] = {sample_n >= 0 ? 1 : 0, max(sample_n, 0), 0, 0};
+    c[2] = nt > 1 ? c[1] : 0;
+    c[3] = nt > 2 ? c[1] : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] += __shfl_xor(c[k], o, 64);
+    if ((tid & 63) == 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s_sample[(THREADS - 1 - tid) >> 6][k] = c[k];
+  }
   __syncthreads();
+  {
+    int rows[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rows[k] = s_sample[0][k] + s_sample[1][k] + s_sample[2][k] + s_sample[3][k];
+    if (tid == 0) steps[bundles + bundle] = 0;
+    if (!pk_worth(rows, Q, small_grid)) {
+      if (tid == 0) steps[bundle] = -1;
+      return;
+    }
+  }
   for (int i = tid; i < G * phases; i += THREADS) {
     int sum = 0;
 #pragma unroll

@@ -387,20 +387,25 @@ def test_residual_spmm_with_long_rows():
     assert_close(R, dense.numpy().astype(np.float64) @ D.numpy().astype(np.float64), "f32", "spmm long rows")
 
 
-@pytest.mark.parametrize("dtype,P,n_long", [("f32", 45, 40), ("bf16", 45, 40), ("bf16", 8, 7), ("f32", 14, 12)])
-def test_residual_spmm_many_long_rows(dtype, P, n_long):
-    # more long rows than the batched dense path accepts: the remainder goes row by row; two
-    # slices of D rows, the second ragged; short rows in between
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P,n_long,N", [(90, 7, 520), (140, 12, 264), (400, 32, 520), (400, 40, 520), (420, 47, 1032), (900, 100, 72),
+                                        (9000, 1400, 8)])
+def test_residual_spmm_many_long_rows(dtype, P, n_long, N):
+    # one ragged group of eight long rows, two, the 32 up to which a span of D's rows is one slice, and beyond: spans of two
+    # slices and more, ragged groups, so many rows that one span is left; the last slice ragged; short rows in between
     g = torch.Generator().manual_seed(23)
-    Q, N = 2600, 520
+    Q = 2600 if P < 5000 else 1100
+    long_rows = torch.randperm(P, generator=g)[:n_long]
+    mask = torch.rand(P, Q, generator=g) < 0.02
+    mask[long_rows] = torch.rand(n_long, Q, generator=g) < (0.9 if P < 5000 else 0.8)
     dense = torch.zeros(P, Q)
-    mask = torch.rand(P, Q, generator=g) < 0.9
-    mask[::9] = torch.rand((P + 8) // 9, Q, generator=g) < 0.02      # rows 0, 9, .. stay short
     dense[mask] = torch.randn(int(mask.sum()), generator=g)
     rows, cols = np.nonzero(dense.numpy())
     row_ptr = np.zeros(P + 1, np.int64)
     np.cumsum(np.bincount(rows, minlength=P), out=row_ptr[1:])
-    assert int((np.diff(row_ptr) > 2048).sum()) == n_long
+    # the kernels' rule: above a quarter of the columns (64 to 2048 entries) and four times the mean row
+    limit = max(min(max(Q // 4, 64), 2048), int(4 * row_ptr[-1] / P))
+    assert int((np.diff(row_ptr) > limit).sum()) == n_long
     vals = dense.numpy()[rows, cols].astype(np.float32)
     D = synth._finish(torch.randn(Q, N, generator=g), dtype)
     args = (torch.from_numpy(row_ptr).cuda(), torch.from_numpy(cols.astype(np.int32)).cuda(),

@@ -1,6 +1,6 @@
 """The bf16 residual product on the matrix cores (csrc/spmm_mfma.hip) where its packing and tiling can go wrong:
 row and column counts around its tiles, chunk edges, values of one to three bf16 terms, rows it leaves to the
-long-row kernels, bundles it leaves to the general path, non-finite elements.
+long-row kernels, bundles it leaves to the tiled kernel, non-finite elements.
 
 Bound: n products summed in fp32 in any order, each exact before the sum, differ from the exact sum by at most
 n * 2^-24 * sum |v d| to first order; 2^-23 leaves room for the higher orders and the matrix core's own adder.
@@ -166,23 +166,25 @@ def test_non_finite_elements_stay_in_their_rows():
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_non_finite_elements_stay_out_of_long_rows_without_them(dtype):
-    """A long row that has no entry in an infinite element's row of D is finite; one that has, is infinite there only."""
+@pytest.mark.parametrize("long_rows", [[3, 50, 51, 120], list(range(0, 190, 5))])
+def test_non_finite_elements_stay_out_of_long_rows_without_them(dtype, long_rows):
+    """A long row that has no entry in an infinite element's row of D is finite; one that has, is infinite there only.  Four
+    long rows, and more than the 32 up to which a span of D is one slice."""
     from paper_2501_17116_amd import binding as b
     S, D = _draw(200, 600, 520, 0.01, 1, 19)
     g = torch.Generator().manual_seed(19)
-    long_rows = [3, 50, 51, 120]
     for r in long_rows:
         S[r] = torch.randn(600, generator=g)
     S[:, 333] = 0
     S[:, 90] = 0
     S[50, 333], S[120, 90] = 2.0, -1.0
+    S[185, 333] = 3.0
     D = D.to(dtype)
     D[333, 40], D[90, 400] = float("inf"), float("nan")
     got = b.fp4_residual_spmm(*_csr(S), 600, D.cuda()).cpu()
     bad = torch.zeros(200, 520, dtype=torch.bool)
-    bad[50, 40] = bad[120, 400] = True
-    assert got[50, 40] == float("inf") and torch.isnan(got[120, 400])
+    bad[50, 40] = bad[120, 400] = bad[185, 40] = True
+    assert got[50, 40] == got[185, 40] == float("inf") and torch.isnan(got[120, 400])
     Df = D.double()
     Df[333, 40] = Df[90, 400] = 0
     ref, mag = S.double() @ Df, S.double().abs() @ Df.abs()
@@ -208,24 +210,26 @@ def test_repeated_columns_in_rows_above_the_long_limit(Q, dtype):
     long (more than max(64, Q / 4) entries) with repeats inside a slice, on its edges and of a whole slice's columns."""
     from paper_2501_17116_amd import binding as b
     g = torch.Generator().manual_seed(Q)
-    rows = [torch.arange(0)] * 40
+    rows = [torch.arange(0)] * 400
+    for r in range(50, 400, 9):   # more long rows (where there are any) than the 32 up to which a span is one slice
+        rows[r] = torch.randint(0, Q, (350,), generator=g).sort().values
     rows[3] = torch.arange(Q).repeat_interleave(3)                                   # every column three times
     rows[17] = torch.cat([torch.arange(min(Q, 90)), torch.tensor([min(Q, 90) - 1])])   # one repeat, on the last column
     rows[18] = torch.cat([torch.zeros(70, dtype=torch.long), torch.arange(Q)])
     rows[30] = torch.randint(0, Q, (300,), generator=g).sort().values
     rows[39] = torch.randint(0, Q, (5,), generator=g).sort().values
-    rp = torch.zeros(41, dtype=torch.int64)
+    rp = torch.zeros(401, dtype=torch.int64)
     torch.cumsum(torch.tensor([len(r) for r in rows]), 0, out=rp[1:])
     ci = torch.cat(rows)
     v = torch.randn(len(ci), generator=g)
     D = torch.randn(Q, 264, generator=g).to(dtype)
-    S = torch.zeros(40, Q, dtype=torch.float64)
-    A = torch.zeros(40, Q, dtype=torch.float64)
-    at = (torch.repeat_interleave(torch.arange(40), rp.diff()), ci)
+    S = torch.zeros(400, Q, dtype=torch.float64)
+    A = torch.zeros(400, Q, dtype=torch.float64)
+    at = (torch.repeat_interleave(torch.arange(400), rp.diff()), ci)
     S.index_put_(at, v.double(), accumulate=True)
     A.index_put_(at, v.double().abs(), accumulate=True)
     args = (rp.cuda(), ci.int().cuda(), v.cuda(), Q, D.cuda())
-    R = torch.full((40, 264), float("nan"), device="cuda")
+    R = torch.full((400, 264), float("nan"), device="cuda")
     b.fp4_residual_spmm(*args, R=R)
     # n products and up to as many sums of values, each rounded once: n * 2^-23 of the magnitudes, as above
     bound = (rp.diff()[:, None] + 1) * 2.0 ** -23 * (A @ D.double().abs()) + 1e-38
