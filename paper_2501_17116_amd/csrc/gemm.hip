@@ -769,8 +769,13 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   // with four per CU they lose (2048^3: 36 against 21).  A row of codes that ends inside a K step puts the big tiles
   // on their slower path, so there the line lies at three per CU (1376 x 2080 x 1056, 726 tiles: 13 against 28 us).
   const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64);
-  // The factor with fp32 weights has no branch-free epilogue in the big tiles: four per CU (2048^3: 38 against 61 us).
-  const bool small = small_tiles <= (dge && !w_bf16 ? 4 : ragged ? 3 : 1) * (int64_t)n_cu;
+  // The same, at longer contractions: 544 .. 16416, 256 to 768 tiles, 0.20 to 0.70 of the big tiles' time throughout.
+  // The factor with fp32 weights has no branch-free epilogue in the big tiles, about 60 us that the small ones save and
+  // lose again on the contraction: up to four per CU while tiles x contraction is at most that of 12288 codes per CU (weight
+  // gradient without the clamp, 2048 x 2048, contraction 2048 / 3072 / 4096 / 8192: 76 / 96 / 118 / 189 us against 94 / 106 /
+  // 110 / 141; 512 tiles, 6144: 101 against 119, 16384: 208 against 190).
+  const bool fp32_factor = dge && !w_bf16 && small_tiles <= 4 * (int64_t)n_cu && small_tiles * Kc <= 12288 * (int64_t)n_cu;
+  const bool small = fp32_factor || small_tiles <= (ragged ? 3 : 1) * (int64_t)n_cu;
   GemmShape gs = g;
   gs.tiles_p = (int)((P + 63) / 64);
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \

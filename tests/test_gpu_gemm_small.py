@@ -32,3 +32,18 @@ def test_small_tiles(P, Q, K):
         small = b.fp4_gemm(L.cuda(), gl.cuda(), R.cuda(), gr.cuda(), out_dtype=dt)
         big = b.fp4_gemm(Lb.cuda(), glb.cuda(), Rb.cuda(), grb.cuda(), out_dtype=dt)
         assert torch.equal(small, big[:P, :Q])
+
+
+@pytest.mark.parametrize("M,K,N", [(3072, 2048, 2048), (3104, 2048, 2048), (6144, 2048, 1024), (6176, 2048, 1024), (32, 64, 72)])
+def test_fp32_factor_on_both_sides_of_the_contraction_limit(M, K, N):
+    """The weight gradient with fp32 masters against its parts called one by one (the factor as a pass of its own): the
+    product is the same to the last bit, the factor one rounding of fp32 in either."""
+    from paper_2501_17116_amd import binding as b
+    torch.manual_seed(M + N)
+    A, W, dY = torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda") * 0.02, torch.randn(M, N, device="cuda")
+    _, ctx = b.fp4_linear_fwd(A, W, 1.0)
+    got = b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 5.0, 3.0)
+    qA, gA = b.fp4_quantize(A, b.FP4_AXIS_COL)
+    qY, gY = b.fp4_quantize(dY, b.FP4_AXIS_COL)
+    ref = b.fp4_dge_apply(b.fp4_gemm(qA, gA, qY, gY), W, ctx.gamma_W, 5.0, 3.0)
+    assert torch.all((got - ref).abs() <= 2.0 ** -22 * ref.abs())
