@@ -321,6 +321,26 @@ def ceilings(b, torch):
     return out
 
 
+# The launches of one residual product (those that find nothing to do leave at once)
+RESIDUAL_KERNELS = {"bf16": "spmm_pack_kernel + spmm_mfma_kernel + spmm_long_dense_kernel + spmm_rest_kernel",
+                    "f32": "spmm_tile_kernel + find_long_rows_kernel + spmm_long_dense_kernel + spmm_finish_long_kernel"}
+
+
+def gemm_kernels(cfg, layers, torch):
+    """Which of the FP4 GEMM's two kernels the step's products run on (the rule of fp4_launch_gemm)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    names = set()
+    for L in layers:
+        l = L["shape"]
+        for P, Q, Kc, factor in ((l.M, l.N, l.K, False), (l.M, l.K, l.N, False), (l.K, l.N, l.M, True)):
+            tiles = -(-P // 64) * -(-Q // 64)
+            small = tiles <= (3 if Kc // 2 % 128 else 1) * cus
+            if factor and cfg.dtype == "f32" and cfg.dge_k > 0:
+                small |= tiles <= 4 * cus and tiles * Kc <= 12288 * cus
+            names.add("fp4_gemm_small_kernel" if small else "fp4_gemm_nt_kernel")
+    return " + ".join(sorted(names))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -397,20 +417,20 @@ def main():
                                 cfg.layers[0].M, cfg.dtype, cfg.alpha, cfg.dge_k),
                    "gemm_flop_per_step": step_flops, "wall_ms_per_step": t_wall / args.steps * 1e3},
         # the contraction the metric names: the FP4 GEMM against the FP4 matrix-core peak
-        "roofline": {"bound": "mfma", "kernel": "fp4_gemm_nt_kernel", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": gemm_kernels(cfg, layers, torch), "achieved": achieved,
                      "peak": FP4_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP4_MFMA_PEAK_TFLOPS,
                      "traffic": None, "avg_launch_ms": avg_gemm_ms, "launches": len(gemm_ms),
                      "share_of_step": sum(gemm_ms) / ms_total if ms_total else None},
     }
     if spmm_ms:
-        # the kernel the step spends most of its time in: the residual product (2 nnz N FLOP per launch; bf16 masters:
-        # packed slots on the matrix cores, bound by vector instructions; fp32: plain FMAs), against the published
-        # fp32 vector peak
+        # the residual product, 2 nnz N FLOP each, all of its launches together.  bf16 masters multiply packed slots on the matrix
+        # cores, but what bounds them there is the vector instructions that bring rows of D into place, so both paths are
+        # read against the published fp32 vector peak (the rate the plain FMAs of fp32 masters have)
         nnz = [int(L["ctx"].nnz.item()) for L in layers]
         spmm_flops = sum(2 * 2.0 * n * L["shape"].N for n, L in zip(nnz, layers))   # forward + weight gradient
         avg_spmm_ms = sum(spmm_ms) / len(spmm_ms)
         ach = spmm_flops / n_spmm / (avg_spmm_ms * 1e-3) / 1e12
-        out["roofline_residual"] = {"bound": "alu", "kernel": "spmm_mfma_kernel" if cfg.dtype == "bf16" else "spmm_tile_kernel", "achieved": ach,
+        out["roofline_residual"] = {"bound": "alu", "kernel": RESIDUAL_KERNELS[cfg.dtype], "achieved": ach,
                                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                                     "frac": ach / FP32_VECTOR_PEAK_TFLOPS, "traffic": None,
                                     "avg_launch_ms": avg_spmm_ms, "launches": len(spmm_ms),

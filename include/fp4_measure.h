@@ -1,8 +1,8 @@
 /*
  * fp4_measure.h -- measurement and self-check helpers of libfp4mi.so, kept apart from the
  * product ABI (fp4_linear.h): the library's own rounding routine exposed for exhaustive
- * checks, ceilings of the part the rooflines are read against, and a per-launch timer of the
- * GEMM kernel.  Nothing here is on the hot path.  Status codes are fp4_status.
+ * checks, ceilings of the part the rooflines are read against, and a timer of the
+ * GEMM launches and residual products.  Nothing here is on the hot path.  Status codes are fp4_status.
  */
 #ifndef FP4_MEASURE_H
 #define FP4_MEASURE_H
@@ -42,9 +42,10 @@ int fp4_probe_mfma(const void* operand_bytes, int64_t nbytes, int workgroups, in
 int fp4_probe_copy(const void* src, void* dst, int64_t nbytes, void* stream);
 
 /* ---- measurement helper (host-side state, off by default; not thread-safe) ----
- * Between fp4_trace_begin(n) and fp4_trace_end() every launch of the FP4 GEMM kernel and of the
- * tiled sparse-product kernel, from any entry point, is bracketed by a pair of HIP events recorded
- * on the launch's own stream (at most n launches; later ones are not recorded).
+ * Between fp4_trace_begin(n) and fp4_trace_end() every FP4 GEMM launch and every residual product
+ * (all of its launches together: packing, multiplication, long rows), from any entry point, is
+ * bracketed by a pair of HIP events recorded on the call's own stream (at most n; later ones are
+ * not recorded).
  * fp4_trace_end waits for the recorded launches, writes their durations in milliseconds and their
  * kinds, in launch order, to ms_host / kind_host [0..capacity) (HOST memory) and returns the number
  * of launches recorded (>= 0) or a negative fp4_status. */

@@ -68,7 +68,7 @@ extern "C" int fp4_probe_copy(const void* src, void* dst, int64_t nbytes, void* 
   return FP4_OK;
 }
 
-// ---- per-launch timing of the two heavy kernels (off unless fp4_trace_begin was called) ---------
+// ---- timing of GEMM launches and residual products (off unless fp4_trace_begin was called) ---------
 #include <vector>
 namespace {
 struct LaunchTrace {

@@ -981,19 +981,21 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   int32_t* const count = scratch;
   int32_t* const list = scratch + 64;
   const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
+  const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);   // the whole product, as its entries are counted
   int rc = 1;
   SpmmRest rest{nullptr, 0, 0};
   if (bf16)
     rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, rest, s);
-  if (rc != 0 && rc != 1) return rc;
+  if (rc != 0 && rc != 1) {
+    fp4_trace_close(trace_slot, s);
+    return rc;
+  }
   const bool packed = rc == 0;
   if (!packed) {
-    const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);
     if (bf16)
       hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
     else
       hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
-    fp4_trace_close(trace_slot, s);
     if (may_be_long)
       hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count);
   }
@@ -1023,6 +1025,7 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
       hipLaunchKernelGGL((spmm_finish_long_kernel<F32>), fgrid, dim3(256), 0, s, row_ptr, col_idx, val, capacity, list, count, part,
                          slices, D, N, R);
   }
+  fp4_trace_close(trace_slot, s);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }

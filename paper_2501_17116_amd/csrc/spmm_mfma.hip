@@ -22,14 +22,10 @@
 // 1.3 M entries), packing included: 926 us, 35 TFLOP/s of useful products; plain fp32 FMAs fed from LDS (spmm.hip):
 // 1454 us.  6 %: 1487 against 2854 us; 0.2 %: 551 against 589 us.
 #include "fp4_common.h"
-#include "fp4_measure.h"
 #include "spmm_long.h"
 
 #include <algorithm>
 #include <type_traits>
-
-int fp4_trace_open(int kind, hipStream_t stream);
-void fp4_trace_close(int slot, hipStream_t stream);
 
 namespace {
 
@@ -510,11 +506,9 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                        capacity, P, (int)Q, cap, phases, small_grid, a_buf, o_buf, sched, steps, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
-    const int slot = fp4_trace_open(FP4_TRACE_SPMM, s);
     hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
                        steps, steps + bundles, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
                        N, R);
-    fp4_trace_close(slot, s);
     rest = SpmmRest{steps, bundles, 16 * G};
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
