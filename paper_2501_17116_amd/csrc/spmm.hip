@@ -74,7 +74,7 @@ FP4_D void load8g(const void* base, int64_t off, int valid, float (&v)[8]) {
 }
 
 // A block of SP_ROWS rows times the 64 columns of D from n0 on.  mine: whether the thread's row is to be written.
-template <class DT>
+template <class DT, bool EARLY>
 FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                            const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q, const void* __restrict__ D,
                            int64_t N, float* __restrict__ R, int64_t block, int tid, bool mine, int64_t n0, float* slab, int* s_skip) {
@@ -139,10 +139,10 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
   for (int j = 0; j < 8; ++j) xo[j] = (j ^ (swz & 7)) * 4;
   const int hi_off = (swz >> 3) * 32;
 
-  // bf16 D: a wave requests its share of the next slab as soon as its own rows are done with the
+  // EARLY (bf16 D): a wave requests its share of the next slab as soon as its own rows are done with the
   // current one (the registers of the read window are free then), so the round trip runs while
   // the slower waves finish instead of after the barrier.
-  constexpr bool EARLY = __is_same(DT, BF16);
+  static_assert(!EARLY || __is_same(DT, BF16), "raw bf16 units");
   [[maybe_unused]] u32x4 nxt[SP_KS / SP_RPP];
   [[maybe_unused]] auto fetch_next = [&](int64_t k0n) {
 #pragma unroll
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
                                                             int64_t N, float* __restrict__ R) {
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
   __shared__ int s_skip[SP_ROWS];
-  spmm_tile_block<DT>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
+  spmm_tile_block<DT, __is_same(DT, BF16)>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
                       (int64_t)blockIdx.x * SP_ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS, slab, s_skip);
 }
 
@@ -317,7 +317,7 @@ constexpr int LD_TABLE = LD_SLICE * LD_LB > LD_WAVES * 2 * LD_COLS ? LD_SLICE * 
 
 // Main loop of spmm_long_dense_kernel for NL accumulated long rows: adds the slice's products to the wave's sums.
 template <class DT, int NL>
-FP4_D void long_dense_add(int tid, const float* V, const void* D, int64_t m0, int rows_here, int64_t N, float (&acc)[NL][8]) {
+FP4_D void long_dense_add(int tid, const float* V, const void* D, int m0, int rows_here, int64_t N, float (&acc)[NL][8]) {
   const int lane = tid & 63, wave = tid >> 6;
   const int64_t col = (int64_t)blockIdx.x * LD_COLS + lane * 8;
   const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
@@ -340,7 +340,7 @@ FP4_D void long_dense_add(int tid, const float* V, const void* D, int64_t m0, in
       // Whole 16-byte units of bf16: the rows of the next turn are requested before the FMAs of this
       // one, as raw words (four registers a row), so a wave always has a turn's loads in flight.
       done = true;
-      const uint16_t* const base = reinterpret_cast<const uint16_t*>(D) + m0 * N + col;
+      const uint16_t* const base = reinterpret_cast<const uint16_t*>(D) + (int64_t)m0 * N + col;
       u32x4 cur[UN], nxt[UN];
       const u32x4 zero = {0u, 0u, 0u, 0u};
       auto request = [&](u32x4 (&dst)[UN], int r0) {
@@ -373,13 +373,13 @@ FP4_D void long_dense_add(int tid, const float* V, const void* D, int64_t m0, in
     for (; r + LD_WAVES * (UN - 1) < rows_here; r += LD_WAVES * UN) {
       float d[UN][8];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) load8g<DT>(D, (m0 + r + LD_WAVES * u) * N + col, valid, d[u]);
+      for (int u = 0; u < UN; ++u) load8g<DT>(D, (int64_t)(m0 + r + LD_WAVES * u) * N + col, valid, d[u]);
 #pragma unroll
       for (int u = 0; u < UN; ++u) fma_row(r + LD_WAVES * u, d[u]);
     }
     for (; r < rows_here; r += LD_WAVES) {
       float d[8];
-      load8g<DT>(D, (m0 + r) * N + col, valid, d);
+      load8g<DT>(D, (int64_t)(m0 + r) * N + col, valid, d);
       fma_row(r, d);
     }
   }
@@ -422,10 +422,12 @@ FP4_D void long_dense_reduce(int tid, float* V, const float (&acc)[NL][8], int64
 // repeats a column is seen by an entry that equals the one before it (or by one more entry than there are columns): then
 // the first entry of each run writes the run's sum, in the entries' order.
 FP4_D void ld_place(int tid, float* V, const int32_t* col_idx, const float* val, const int64_t* s_lo, const int64_t* s_en,
-                    int* s_rep, int nl, int64_t m0, int rows_here, int slice) {
+                    int* s_rep, int nl, int m0, int rows_here, int slice) {
   constexpr int THREADS = LD_WAVES * 64;
   const int shift = 31 - __builtin_clz(slice);   // a power of two
   const int items = nl * slice;
+  int32_t beyond = 0x7fffffff;   // the entry after as many as there are columns
+  if (tid < nl && s_lo[tid] + slice < s_en[tid]) beyond = col_idx[s_lo[tid] + slice];
   for (int j0 = tid; j0 < items; j0 += 4 * THREADS) {
     int32_t c[4], before[4];
     float v[4];
@@ -441,22 +443,19 @@ FP4_D void ld_place(int tid, float* V, const int32_t* col_idx, const float* val,
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int64_t r = c[u] - m0;
+      const int r = c[u] - m0;
       if (r < 0 || r >= rows_here) continue;
       if (before[u] == c[u]) *s_rep = 1;
       else V[r * LD_LB + min((j0 + u * THREADS) >> shift, nl - 1)] = v[u];
     }
   }
-  if (tid < nl) {
-    const int64_t i = s_lo[tid] + slice;
-    if (i < s_en[tid] && col_idx[i] < m0 + rows_here) *s_rep = 1;
-  }
+  if (beyond < m0 + rows_here) *s_rep = 1;
   __syncthreads();
   if (*s_rep == 0) return;
   for (int l = 0; l < nl; ++l)
     for (int64_t i = s_lo[l] + tid; i < s_en[l]; i += THREADS) {
       const int32_t c = col_idx[i];
-      const int64_t r = c - m0;
+      const int r = c - m0;
       if (r >= rows_here) break;
       if (r < 0 || (i > s_lo[l] && col_idx[i - 1] == c)) continue;
       float sum = val[i];
@@ -468,7 +467,7 @@ FP4_D void ld_place(int tid, float* V, const int32_t* col_idx, const float* val,
 
 // The sums of nl long rows, at most NL, over the rows of D in the table: to[l][column], added to what is there unless `set`.
 template <class DT, int NL>
-FP4_D void long_dense_turn(int tid, float* V, const void* D, int64_t m0, int rows_here, int64_t N, int nl, bool set, float* to,
+FP4_D void long_dense_turn(int tid, float* V, const void* D, int m0, int rows_here, int64_t N, int nl, bool set, float* to,
                             const int32_t* rows) {
   float acc[NL][8];
 #pragma unroll
@@ -488,7 +487,7 @@ template <class DT>
 __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                               const float* val, int64_t capacity,
                                                               const int32_t* list, const int32_t* count,
-                                                              const void* D, int64_t Q, int64_t N, int slice, int slices,
+                                                              const void* D, int Q, int64_t N, int slice, int slices,
                                                               float* part, float* R) {
   __shared__ __attribute__((aligned(16))) float V[LD_TABLE];   // 32 KiB, reused for the wave reduction
   __shared__ int64_t s_lo[LD_LB], s_en[LD_LB];
@@ -500,13 +499,13 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   while (2 * rows_a_turn <= min(LD_SLICE, span * slice)) rows_a_turn *= 2;
   for (int item = blockIdx.y; item < groups * spans; item += gridDim.y) {
     const int g0 = item % groups * LD_LB, nl = min(LD_LB, n_long - g0);
-    const int64_t first = (int64_t)(item / groups) * span * slice, last = min(first + (int64_t)span * slice, Q);
+    const int first = item / groups * span * slice, last = min(first + span * slice, Q);   // Q < 2^21
 #pragma unroll 1
-    for (int64_t m0 = first; m0 < last; m0 += rows_a_turn) {
+    for (int m0 = first; m0 < last; m0 += rows_a_turn) {
       int tid = threadIdx.x;
       asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each turn: kept across, they spill
       const int lane = tid & 63, wave = tid >> 6;
-      const int rows_here = (int)min((int64_t)rows_a_turn, last - m0);
+      const int rows_here = min(rows_a_turn, last - m0);
       __syncthreads();   // everyone is done with the table
       for (int i = tid; i < rows_a_turn * LD_LB; i += LD_WAVES * 64) V[i] = 0.0f;
       if (tid == 0) s_rep = 0;
@@ -545,23 +544,22 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   }
 }
 
-// One long row from its entries alone, 256 columns per 256 threads from `first` on: 32 columns at a time, 4 column groups of
-// 8 x 64 entry lanes; entry lane l takes entries l, l + 64, ...; the 64 partial sums are added in a fixed order.
-template <class DT>
+// The 256 columns from `first` on of one long row from its entries alone: 32 columns at a time, 4 column groups of 8 x
+// THREADS / 4 entry lanes; entry lane l takes every THREADS / 4-th entry from the l-th on; the lanes' sums are added in order.
+template <class DT, int THREADS>
 FP4_D void long_row_entries(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t row,
                             int64_t first, const void* D, int64_t N, float* R, float* part) {
-  const int cg = threadIdx.x & 3, el = (threadIdx.x & 255) >> 2;
-  float* const mine = part + (threadIdx.x >> 8) * (64 * 32);   // [64][4][8]
+  constexpr int LANES = THREADS / 4;
+  const int cg = threadIdx.x & 3, el = threadIdx.x >> 2;
   const int64_t b = row_ptr[row], en = min(row_ptr[row + 1], capacity);
-  for (int k = 0; k < 8; ++k) {
-    const int64_t n0 = first + (threadIdx.x >> 8) * 256 + k * 32;
+  for (int64_t n0 = first; n0 < min(first + 256, N); n0 += 32) {
     const int64_t col = n0 + cg * 8;
     const int valid = col < N ? (int)min((int64_t)8, N - col) : 0;
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
     if (valid > 0) {
-      for (int64_t i = b + el; i < en; i += 64) {
+      for (int64_t i = b + el; i < en; i += LANES) {
         const int32_t c = col_idx[i];
         const float s = val[i];
         float d[8];
@@ -571,58 +569,73 @@ FP4_D void long_row_entries(const int64_t* row_ptr, const int32_t* col_idx, cons
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) mine[el * 32 + cg * 8 + e] = acc[e];
+    for (int e = 0; e < 8; ++e) part[el * 32 + cg * 8 + e] = acc[e];
     __syncthreads();
-    if ((threadIdx.x & 255) < 32) {
+    if (threadIdx.x < 32) {
       float sum = 0.0f;
-      for (int l = 0; l < 64; ++l) sum += mine[l * 32 + (threadIdx.x & 31)];
-      const int64_t c1 = n0 + (threadIdx.x & 31);
+      for (int l = 0; l < LANES; ++l) sum += part[l * 32 + threadIdx.x];
+      const int64_t c1 = n0 + threadIdx.x;
       if (c1 < N) R[row * N + c1] = sum;
     }
     __syncthreads();
   }
 }
 
-// What the dense path leaves to do, a column a thread from `first` on, every rows_apart-th long row from row0 on: the spans'
-// partial sums are added up, and where a row's sum is infinite or NaN the row's columns are summed from its
-// entries instead, since the table's zeros times an infinity of D in a column the row has no entry in are NaN.  part:
-// 64 x 32 floats per 256 threads.
-template <class DT>
+// What the dense path leaves to do for the 256 columns from `first` on, every rows_apart-th long row from row0 on: the
+// spans' partial sums are added up (each 256 threads take every so many-th span, their sums are added in order), and where a
+// row's sum is infinite or NaN the row's columns are summed from its entries instead, since the table's zeros times an
+// infinity of D in a column the row has no entry in are NaN.  part: 8 THREADS floats.
+template <class DT, int THREADS>
 FP4_D void finish_long_rows(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                             const int32_t* list, int n_long, int row0, int rows_apart, const float* partial, int slices,
                             int64_t first, const void* D, int64_t N, float* R, float* part) {
-  const int64_t n = first + threadIdx.x;
+  constexpr int PARTS = THREADS / 256;
+  const int c = threadIdx.x & 255, q = threadIdx.x >> 8;
+  const int64_t n = first + c;
   const int span = ld_span(n_long, slices), spans = (slices + span - 1) / span;
   for (int li = row0; li < n_long; li += rows_apart) {
     float* const r = R + (int64_t)list[li] * N;
     float sum = 0.0f;
     if (n < N) {
       if (spans > 1) {
-        for (int s0 = 0; s0 < spans; s0 += 8) {   // eight loads in flight, added in span order
+        const int64_t step = (int64_t)PARTS * n_long * N;
+        const float* p = partial + ((int64_t)q * n_long + li) * N + n;
+        for (int s0 = q; s0 < spans; s0 += 8 * PARTS) {   // eight loads in flight, added in span order
           float v[8];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) v[k] = s0 + k < spans ? partial[((int64_t)(s0 + k) * n_long + li) * N + n] : 0.0f;
+          for (int k = 0; k < 8; ++k) {
+            v[k] = s0 + k * PARTS < spans ? *p : 0.0f;
+            p += step;
+          }
 #pragma unroll
           for (int k = 0; k < 8; ++k) sum += v[k];
         }
-        r[n] = sum;
-      } else {
+      } else if (q == 0) {
         sum = r[n];
       }
     }
-    if (__syncthreads_or((f2u(sum) & 0x7f800000u) == 0x7f800000u))
-      long_row_entries<DT>(row_ptr, col_idx, val, capacity, list[li], first, D, N, R, part);
+    if constexpr (PARTS > 1) {
+      part[threadIdx.x] = sum;
+      __syncthreads();
+      if (q == 0) {
+#pragma unroll
+        for (int k = 1; k < PARTS; ++k) sum += part[k * 256 + c];
+      }
+    }
+    if (n < N && q == 0 && spans > 1) r[n] = sum;
+    if (__syncthreads_or(q == 0 && (f2u(sum) & 0x7f800000u) == 0x7f800000u))
+      long_row_entries<DT, THREADS>(row_ptr, col_idx, val, capacity, list[li], first, D, N, R, part);
   }
 }
 
-constexpr int LF_ROWS = 16;   // long rows side by side
+constexpr int LF_ROWS = 8;   // long rows side by side
 template <class DT>
 __global__ __launch_bounds__(256) void spmm_finish_long_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                                const float* val, int64_t capacity, const int32_t* list,
                                                                const int32_t* count, const float* partial, int slices,
                                                                const void* D, int64_t N, float* R) {
-  __shared__ float part[64 * 32];
-  finish_long_rows<DT>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.y, LF_ROWS, partial, slices,
+  __shared__ float part[8 * 256];
+  finish_long_rows<DT, 256>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.y, LF_ROWS, partial, slices,
                        (int64_t)blockIdx.x * 256, D, N, R, part);
 }
 
@@ -641,22 +654,25 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_rest_kernel(const int64_t* __res
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
   __shared__ int s_skip[SP_ROWS];
   if (blockIdx.x < long_blocks) {
-    finish_long_rows<BF16>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.x % LF_ROWS, LF_ROWS, partial, slices,
-                           (int64_t)(blockIdx.x / LF_ROWS) * SP_ROWS, D, N, R, slab);
+    finish_long_rows<BF16, SP_ROWS>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.x % LF_ROWS, LF_ROWS, partial, slices,
+                                    (int64_t)(blockIdx.x / LF_ROWS) * 256, D, N, R, slab);
     return;
   }
+  __shared__ bool s_mine[SP_ROWS];
   const unsigned tile = blockIdx.x - long_blocks;
-  const int64_t block = tile % tiles.x, row0 = block * SP_ROWS;
-  auto is_mine = [&](int64_t row) {
-    if (row >= P) return false;
-    const int64_t bundle = row / rest.rows;
-    return rest.steps[bundle] < 0 || rest.steps[rest.bundles + bundle] != 0;
-  };
-  if (!__syncthreads_or(is_mine(row0 + threadIdx.x))) return;
+  const int64_t block = tile % tiles.x;
+  bool mine = false;
+  if (block * SP_ROWS + threadIdx.x < P) {
+    const uint32_t group = (uint32_t)((block * SP_ROWS + threadIdx.x) >> 4);   // P < 2^31: the list's rows have 32 bits
+    const uint32_t bundle = rest.groups == 3 ? group / 3u : group;
+    mine = rest.steps[bundle] < 0 || rest.redo[bundle] != 0;
+  }
+  s_mine[threadIdx.x] = mine;
+  if (!__syncthreads_or(mine)) return;
   for (int64_t n0 = (int64_t)(tile / tiles.x) * SP_COLS; n0 < N; n0 += (int64_t)tiles.y * SP_COLS) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));   // a lane's constants are formed again for each column block: kept across, they spill
-    spmm_tile_block<BF16>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, block, tid, is_mine(row0 + tid), n0, slab, s_skip);
+    spmm_tile_block<BF16, false>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, block, tid, s_mine[tid], n0, slab, s_skip);
   }
 }
 
@@ -983,7 +999,7 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
   const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);   // the whole product, as its entries are counted
   int rc = 1;
-  SpmmRest rest{nullptr, 0, 0};
+  SpmmRest rest{nullptr, nullptr, 0};
   if (bf16)
     rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, rest, s);
   if (rc != 0 && rc != 1) {
@@ -1003,17 +1019,19 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   const int slice = ld_slice(Q, N);
   const int slices = (int)((Q + slice - 1) / slice);
   if (may_be_long) {
-    const dim3 dgrid((unsigned)((N + LD_COLS - 1) / LD_COLS), (unsigned)slices * (LD_CAP / LD_LB));
+    // an item a workgroup for up to eight long rows, and two workgroups a CU for more; what finds no item leaves at once
+    const unsigned blocks = (unsigned)((N + LD_COLS - 1) / LD_COLS);
+    const dim3 dgrid(blocks, std::max((unsigned)slices, std::min((unsigned)slices * (LD_CAP / LD_LB), 512 / blocks)));
     if (bf16)
       hipLaunchKernelGGL((spmm_long_dense_kernel<BF16>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, slice, slices, part, R);
+                         count, D, (int)Q, N, slice, slices, part, R);
     else
       hipLaunchKernelGGL((spmm_long_dense_kernel<F32>), dgrid, dim3(LD_WAVES * 64), 0, s, row_ptr, col_idx, val, capacity, list,
-                         count, D, Q, N, slice, slices, part, R);
+                         count, D, (int)Q, N, slice, slices, part, R);
   }
   if (packed) {
     const dim3 tiles(grid.x, std::min(grid.y, std::max(1u, 512u / grid.x)));
-    const unsigned long_blocks = may_be_long ? LF_ROWS * (unsigned)((N + SP_ROWS - 1) / SP_ROWS) : 0;
+    const unsigned long_blocks = may_be_long ? LF_ROWS * (unsigned)((N + 255) / 256) : 0;
     hipLaunchKernelGGL(spmm_rest_kernel, dim3(tiles.x * tiles.y + long_blocks), dim3(SP_ROWS), 0, s, row_ptr, col_idx, val,
                        capacity, P, Q, D, N, R, rest, tiles, long_blocks, list, count, part, slices);
   } else if (may_be_long) {

@@ -4,12 +4,12 @@
 #pragma once
 #include "fp4_common.h"
 
-// What the packed product of spmm_mfma.hip leaves to the tiled kernel: bundle i has the rows from i * rows on, and is left
-// where steps[i] < 0 or steps[bundles + i] != 0.
+// What the packed product of spmm_mfma.hip leaves to the tiled kernel: bundle i has 16 * groups rows, and is left
+// where steps[i] < 0 or redo[i] != 0.
 struct SpmmRest {
   const int32_t* steps;
-  int64_t bundles;
-  int rows;
+  const int32_t* redo;
+  int groups;   // 1 or 3
 };
 
 #if defined(__HIPCC__)

@@ -31,6 +31,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+constexpr int SM_STEPS_PAD = 12;   // step counts read past the last bundle (11 waves)
 constexpr int SM_KC = 128;       // rows of D per chunk
 constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): three to multiply from, two on their way
 constexpr int SM_AHEAD = 2;
@@ -73,11 +74,10 @@ FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
   return v != 0.0f ? 4 : n;
 }
 
-// Whether a matrix is worth packing, from 256 rows spread over it (every workgroup looks at the same ones and comes to the
+// Whether a matrix is worth packing, from 64 rows spread over it (every workgroup looks at the same ones and comes to the
 // same answer, which depends on the matrix alone): the slots a column of a group needs on average, from the rows' entries
 // and the number of terms of one value of each.  rows[0..3]: rows that are not long, their entries, those of values
 // of two terms or more, of three.
-constexpr int PK_SAMPLE = 256;
 FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
   const float cells = fmaxf((float)rows[0], 1.0f) * (float)Q;
   float slots = 0.0f;
@@ -94,14 +94,14 @@ FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
 // One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
 // steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the tiled kernel (a
 // matrix that is not worth it, more slots than there is room for, columns that repeat inside a row, or values that three
-// bf16 terms do not make up); steps[bundles + bundle]: 0.
+// bf16 terms do not make up); redo[bundle]: 0.
 template <int G>
 __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx,
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
                                                                int Q, int cap, int phases, bool small_grid, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
-                                                               int32_t* __restrict__ steps, int32_t* list, int32_t* count) {
+                                                               int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list, int32_t* count) {
   constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR;
   extern __shared__ uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
@@ -110,52 +110,48 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   uint16_t* const pre = reinterpret_cast<uint16_t*>(start + G * phases);   // [G][words] slots of the chunk before this word
   __shared__ int64_t s_b[ROWS];
   __shared__ int s_n[ROWS];
-  __shared__ int s_bad, s_total[G], s_steps, s_sample[4][4];
+  __shared__ int s_bad, s_total[G], s_steps, s_sample[4];
   const int tid = threadIdx.x;
   if (blockIdx.x == 0) {   // the first workgroup lists the long rows
     find_long_rows<THREADS>(row_ptr, P, Q, capacity, list, count);
     return;
   }
   const int64_t bundle = blockIdx.x - 1, bundles = gridDim.x - 1;
-  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
-  // entries of a row; long ones are the long-row kernels' business
   auto entries = [&](int64_t row, int64_t& b) -> int64_t {
     b = row_ptr[row];
     return max(min(row_ptr[row + 1], capacity), b) - b;
   };
-  for (int i = tid; i < G * words; i += THREADS) nib[i] = 0;
-  if (tid < ROWS) {
-    const int64_t row = bundle * ROWS + tid;
-    int64_t b = 0, n = 0;
+  // A row a thread, and in the last wave the sample's rows, all requests before the limit's.
+  const bool sampler = tid >= THREADS - 64;
+  static_assert(THREADS >= ROWS + 64, "a wave for the sample");
+  int64_t b = 0, n = 0;
+  if (tid < ROWS || sampler) {
+    const int64_t row = sampler ? (int64_t)(tid & 63) * P / 64 : bundle * ROWS + tid;
     if (row < P) n = entries(row, b);
+  }
+  for (int i = tid; i < G * words; i += THREADS) nib[i] = 0;
+  const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
+  const bool is_long = n > long_limit;   // the long-row kernels' business
+  if (tid < ROWS) {
     s_b[tid] = b;
-    s_n[tid] = n > long_limit ? 0 : (int)n;
+    s_n[tid] = is_long ? 0 : (int)n;
   }
-  // The sample: its value is on its way while the rows' entries are looked at.
-  static_assert(THREADS >= 2 * PK_SAMPLE, "the last waves sample");
-  const bool sampler = tid >= THREADS - PK_SAMPLE;
-  int sample_n = -1;
-  float sample_v = 0.0f;
-  if (sampler) {
-    int64_t b;
-    const int64_t n = entries((int64_t)(tid - (THREADS - PK_SAMPLE)) * P / PK_SAMPLE, b);
-    if (n <= long_limit) sample_n = (int)min(n, (int64_t)Q);
-    if (sample_n > 0) sample_v = val[b + n / 2];
-  }
+  float sample_v = 0.0f;   // on its way while the rows' entries are looked at
+  if (sampler && n > 0 && !is_long) sample_v = val[b + n / 2];
   if (tid == 0) s_bad = 0;
   if (tid < G) s_total[tid] = 0;
   __syncthreads();
   const int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
   const int grp = br / 16, r = br % 16;
-  const int n = s_n[br];
+  const int n_mine = s_n[br];
   const int32_t* const cp = col_idx + s_b[br];
   const float* const vp = val + s_b[br];
-  for (int i0 = rt; i0 < n; i0 += 4 * PK_TPR) {   // four entries a thread in flight
+  for (int i0 = rt; i0 < n_mine; i0 += 4 * PK_TPR) {   // four entries a thread in flight
     int c[4], before[4];
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = min(i0 + u * PK_TPR, n - 1);
+      const int i = min(i0 + u * PK_TPR, n_mine - 1);
       c[u] = cp[i];
       v[u] = vp[i];
       before[u] = i > 0 ? cp[i - 1] : -1;
@@ -164,7 +160,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
     for (int u = 0; u < 4; ++u) {
       uint32_t t[3];
       const int nt = bf16_terms(v[u], t);
-      if (i0 + u * PK_TPR >= n) continue;
+      if (i0 + u * PK_TPR >= n_mine) continue;
       if ((uint32_t)c[u] >= (uint32_t)Q || before[u] >= c[u] || nt > 3) { s_bad = 1; continue; }
       atomicOr(&nib[grp * words + (c[u] >> 3)], ((1u << nt) - 1u) << (4 * (c[u] & 7)));
     }
@@ -172,7 +168,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   if (sampler) {
     uint32_t t[3];
     const int nt = bf16_terms(sample_v, t);
-    int c[4] = {sample_n >= 0 ? 1 : 0, max(sample_n, 0), 0, 0};
+    int c[4] = {is_long ? 0 : 1, is_long ? 0 : (int)min(n, (int64_t)Q), 0, 0};
     c[2] = nt > 1 ? c[1] : 0;
     c[3] = nt > 2 ? c[1] : 0;
 #pragma unroll
@@ -181,18 +177,16 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
       for (int k = 0; k < 4; ++k) c[k] += __shfl_xor(c[k], o, 64);
     if ((tid & 63) == 0)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) s_sample[(THREADS - 1 - tid) >> 6][k] = c[k];
+      for (int k = 0; k < 4; ++k) s_sample[k] = c[k];
   }
   __syncthreads();
-  {
-    int rows[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) rows[k] = s_sample[0][k] + s_sample[1][k] + s_sample[2][k] + s_sample[3][k];
-    if (tid == 0) steps[bundles + bundle] = 0;
-    if (!pk_worth(rows, Q, small_grid)) {
-      if (tid == 0) steps[bundle] = -1;
-      return;
-    }
+  if (tid < 32) {   // nothing to do again yet, and nothing packed past the last bundle
+    if (tid == 0) redo[bundle] = 0;
+    else if (bundle == bundles - 1 && tid < SM_STEPS_PAD) steps[bundles + tid - 1] = -1;
+  }
+  if (!pk_worth(s_sample, Q, small_grid)) {
+    if (tid == 0) steps[bundle] = -1;
+    return;
   }
   for (int i = tid; i < G * phases; i += THREADS) {
     int sum = 0;
@@ -265,18 +259,18 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   for (int i = gt; i < T * 64; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(ag + (int64_t)i * 16) = z;
   for (int i = gt; i < T * 4; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(og + (int64_t)i * 16) = z;
   __syncthreads();   // the zeros are written (a workgroup's stores reach L2 in order) before the values
-  for (int i0 = rt; i0 < n; i0 += 4 * PK_TPR) {
+  for (int i0 = rt; i0 < n_mine; i0 += 4 * PK_TPR) {
     int cc[4];
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = min(i0 + u * PK_TPR, n - 1);
+      const int i = min(i0 + u * PK_TPR, n_mine - 1);
       cc[u] = cp[i];
       v[u] = vp[i];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (i0 + u * PK_TPR >= n) continue;
+      if (i0 + u * PK_TPR >= n_mine) continue;
       const int c = cc[u];
       uint32_t t[3];
       const int nt = bf16_terms(v[u], t);
@@ -293,7 +287,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
 }
 
 // WV waves multiply, G groups of 16 rows each; one more stages D.  Bundles that are not packed are left out, and a
-// bundle with a non-finite sum is marked in steps[bundles + bundle]: a zero value times an infinite or NaN element of D
+// bundle with a non-finite sum is marked in redo: a zero value times an infinite or NaN element of D
 // reaches the other rows of the group.  The tiled kernel writes the rows of both afterwards, from their entries.
 template <int G, int WV>
 __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t* __restrict__ a_buf, const uint8_t* __restrict__ o_buf,
@@ -316,11 +310,11 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
   const int rb = in_strip / width;
   const int64_t bundles = (P + 16 * G - 1) / (16 * G);
   // Nothing packed among the workgroup's bundles: every wave sees that alike (steps is written by the packing only) and
-  // leaves.  Scalar loads, so that the staging wave's chunks are on their way meanwhile.
+  // leaves.  Scalar loads, behind the first requests.
   auto nothing = [&]() {
     int32_t most = -1;
 #pragma unroll
-    for (int w = 0; w < WV; ++w) most = max(most, steps[min((int64_t)rb * WV + w, bundles - 1)]);
+    for (int w = 0; w < WV; ++w) most = max(most, steps[(int64_t)rb * WV + w]);   // -1 past the last bundle
     return most < 0;
   };
 
@@ -363,7 +357,6 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
     return;
   }
 
-  if (nothing()) return;
   f32x4 acc[G][8];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -372,8 +365,7 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
   // The packed steps are read through scalar descriptors (a wave's groups lie one after another): the lane part
   // of an address is one register, whatever the group.
   const int64_t bundle = (int64_t)rb * WV + wave;
-  const bool live = bundle < bundles && steps[min(bundle, bundles - 1)] >= 0;
-  const int64_t bl = live ? bundle : 0;
+  const int64_t bl = min(bundle, bundles - 1);
   const uint32_t a_stride = (uint32_t)(cap + 1) * 1024u, o_stride = (uint32_t)(cap + 1) * 64u;
   const __amdgpu_buffer_rsrc_t rsrc_a = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(a_buf) + bl * G * (int64_t)a_stride, 0, (int)(a_stride * (uint32_t)G), 0x00020000);
@@ -389,6 +381,8 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
 #pragma unroll
   for (int g = 0; g < G; ++g) fetch(g, 0);
   const uint32_t lbase = (uint32_t)(lane & 15) * 16u;
+  const bool live = steps[bundle] >= 0;
+  if (nothing()) return;
   __builtin_amdgcn_s_barrier();
 
   uint32_t done = 0;
@@ -485,7 +479,7 @@ int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
 }
 
 // Returns 1 when the product is left to the tiled kernel.  Otherwise that kernel has what remains: the rows of bundle i
-// (rest.rows of them) where rest.steps[i] < 0 or rest.steps[rest.bundles + i] != 0.
+// (16 rest.groups of them) where rest.steps[i] < 0 or rest.redo[i] != 0.
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
                          SpmmRest& rest, hipStream_t s) {
@@ -501,15 +495,17 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     uint8_t* const o_buf = a_buf + bundles * G * (int64_t)(cap + 1) * 1024;
     int32_t* const sched = reinterpret_cast<int32_t*>(o_buf + bundles * G * (int64_t)(cap + 1) * 64);
     int32_t* const steps = sched + bundles * phases;
+    int32_t* const redo = steps + bundles + SM_STEPS_PAD;
     const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)G * phases * 4;
     hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * pk_tpr(G)), lds, s, row_ptr, col_idx, val,
-                       capacity, P, (int)Q, cap, phases, small_grid, a_buf, o_buf, sched, steps, list, count);
+                       capacity, P, (int)Q, cap, phases, small_grid, a_buf, o_buf, sched, steps, redo, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
     hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
-                       steps, steps + bundles, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
+                       steps, redo, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
                        N, R);
-    rest = SpmmRest{steps, bundles, 16 * G};
+    rest = SpmmRest{steps, redo, G};
+    static_assert(G == 1 || G == 3, "the rest's bundles");
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
   // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows
