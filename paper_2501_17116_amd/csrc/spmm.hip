@@ -498,8 +498,9 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   int rows_a_turn = slice;   // what of a span the table takes at a time: a power of two
   while (2 * rows_a_turn <= min(LD_SLICE, span * slice)) rows_a_turn *= 2;
   for (int item = blockIdx.y; item < groups * spans; item += gridDim.y) {
-    const int g0 = item % groups * LD_LB, nl = min(LD_LB, n_long - g0);
-    const int first = item / groups * span * slice, last = min(first + span * slice, Q);   // Q < 2^21
+    const int group = item / spans, at = item - group * spans;   // its span
+    const int g0 = group * LD_LB, nl = min(LD_LB, n_long - g0);
+    const int first = at * span * slice, last = min(first + span * slice, Q);   // Q < 2^21
 #pragma unroll 1
     for (int m0 = first; m0 < last; m0 += rows_a_turn) {
       int tid = threadIdx.x;
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
       }
       __syncthreads();   // table zeroed, starts known
       ld_place(tid, V, col_idx, val, s_lo, s_en, &s_rep, nl, m0, rows_here, rows_a_turn);
-      float* const to = spans > 1 ? part + ((int64_t)(item / groups) * n_long + g0) * N : R;
+      float* const to = spans > 1 ? part + ((int64_t)at * n_long + g0) * N : R;
       const int32_t* const rows = spans > 1 ? nullptr : list + g0;
       if (nl <= 4)   // sums only for as many long rows as there are (4 or 8): usually a handful
         long_dense_turn<DT, 4>(tid, V, D, m0, rows_here, N, nl, m0 == first, to, rows);
@@ -628,7 +629,7 @@ FP4_D void finish_long_rows(const int64_t* row_ptr, const int32_t* col_idx, cons
   }
 }
 
-constexpr int LF_ROWS = 8;   // long rows side by side
+constexpr int LF_ROWS = 32;   // long rows side by side
 template <class DT>
 __global__ __launch_bounds__(256) void spmm_finish_long_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                                const float* val, int64_t capacity, const int32_t* list,
@@ -641,9 +642,9 @@ __global__ __launch_bounds__(256) void spmm_finish_long_kernel(const int64_t* ro
 
 // After the packed product and the dense path, one launch for what both leave.  The first long_blocks workgroups finish the
 // long rows; the other tiles.x * tiles.y take the rows that the packed product left (usually none: the workgroup leaves at
-// once), each every tiles.y-th column block.  About 512 of them: an idle launch is over in 5 us (one workgroup a block: 13),
-// a full one takes as long as with one a block (16384 x 4096 -> 12288, 6 % of two-term values, the product: 256 workgroups
-// 3406 us, 512 3179, 1024 3151, one a block 3158).
+// once), each every tiles.y-th column block.  512 of them, two rounds of one a CU: an idle launch is over in 5 us (one
+// workgroup a block: 13), a full one takes about as long as with one a block (16384 x 4096 -> 12288, 6 % of two-term values,
+// the product: 256 workgroups 3406 us, 384 4107, 512 3179, 1024 3151, one a block 3158; the tiled kernel alone 2890).
 __global__ __launch_bounds__(SP_ROWS) void spmm_rest_kernel(const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col_idx,
                                                             const float* __restrict__ val, int64_t capacity,
@@ -654,8 +655,9 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_rest_kernel(const int64_t* __res
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
   __shared__ int s_skip[SP_ROWS];
   if (blockIdx.x < long_blocks) {
-    finish_long_rows<BF16, SP_ROWS>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.x % LF_ROWS, LF_ROWS, partial, slices,
-                                    (int64_t)(blockIdx.x / LF_ROWS) * 256, D, N, R, slab);
+    const unsigned blocks = (unsigned)((N + 255) / 256), apart = long_blocks / blocks;
+    finish_long_rows<BF16, SP_ROWS>(row_ptr, col_idx, val, capacity, list, *count, blockIdx.x / blocks, apart, partial, slices,
+                                    (int64_t)(blockIdx.x % blocks) * 256, D, N, R, slab);
     return;
   }
   __shared__ bool s_mine[SP_ROWS];
@@ -1031,7 +1033,9 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   }
   if (packed) {
     const dim3 tiles(grid.x, std::min(grid.y, std::max(1u, 512u / grid.x)));
-    const unsigned long_blocks = may_be_long ? LF_ROWS * (unsigned)((N + 255) / 256) : 0;
+    // up to eight long rows side by side, fewer where their column blocks are many: one workgroup fits a CU
+    const unsigned blocks = (unsigned)((N + 255) / 256);
+    const unsigned long_blocks = may_be_long ? blocks * std::max(1u, std::min(8u, 128u / blocks)) : 0;
     hipLaunchKernelGGL(spmm_rest_kernel, dim3(tiles.x * tiles.y + long_blocks), dim3(SP_ROWS), 0, s, row_ptr, col_idx, val,
                        capacity, P, Q, D, N, R, rest, tiles, long_blocks, list, count, part, slices);
   } else if (may_be_long) {
