@@ -79,16 +79,16 @@ FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
 // and the number of terms of one value of each.  rows[0..3]: rows that are not long, their entries, those of values
 // of two terms or more, of three.
 FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
-  const float cells = fmaxf((float)rows[0], 1.0f) * (float)Q;
+  const float a_cell = __builtin_amdgcn_rcpf(fmaxf((float)rows[0], 1.0f) * (float)Q);
   float slots = 0.0f;
 #pragma unroll
   for (int t = 1; t < 4; ++t) {
-    float none = fmaxf(1.0f - (float)rows[t] / cells, 0.0f);   // no row of 16 has one
+    float none = fmaxf(1.0f - (float)rows[t] * a_cell, 0.0f);   // no row of 16 has one
 #pragma unroll
     for (int k = 0; k < 4; ++k) none *= none;
     slots += 1.0f - none;
   }
-  return slots <= SM_ROOM_SLOTS && (small_grid || slots <= SM_EVEN_SLOTS + SM_EVEN_SHARE * (float)rows[1] / cells);
+  return slots <= SM_ROOM_SLOTS && (small_grid || slots <= SM_EVEN_SLOTS + SM_EVEN_SHARE * (float)rows[1] * a_cell);
 }
 
 // One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
@@ -165,28 +165,21 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
       atomicOr(&nib[grp * words + (c[u] >> 3)], ((1u << nt) - 1u) << (4 * (c[u] & 7)));
     }
   }
+  __syncthreads();
   if (sampler) {
     uint32_t t[3];
     const int nt = bf16_terms(sample_v, t);
-    int c[4] = {is_long ? 0 : 1, is_long ? 0 : (int)min(n, (int64_t)Q), 0, 0};
-    c[2] = nt > 1 ? c[1] : 0;
-    c[3] = nt > 2 ? c[1] : 0;
+    const uint64_t mine = is_long ? 0 : (uint64_t)min(n, (int64_t)Q);   // 21 bits hold the sum of 64
+    uint64_t sum = mine | (nt > 1 ? mine << 21 : 0) | (nt > 2 ? mine << 42 : 0);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] += __shfl_xor(c[k], o, 64);
-    if ((tid & 63) == 0)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s_sample[k] = c[k];
-  }
-  __syncthreads();
-  if (tid < 32) {   // nothing to do again yet, and nothing packed past the last bundle
-    if (tid == 0) redo[bundle] = 0;
-    else if (bundle == bundles - 1 && tid < SM_STEPS_PAD) steps[bundles + tid - 1] = -1;
-  }
-  if (!pk_worth(s_sample, Q, small_grid)) {
-    if (tid == 0) steps[bundle] = -1;
-    return;
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const int rows = __popcll(__ballot(!is_long));
+    if ((tid & 63) == 0) {
+      s_sample[0] = rows;
+      s_sample[1] = (int)(sum & 0x1fffff);
+      s_sample[2] = (int)(sum >> 21 & 0x1fffff);
+      s_sample[3] = (int)(sum >> 42);
+    }
   }
   for (int i = tid; i < G * phases; i += THREADS) {
     int sum = 0;
@@ -241,12 +234,14 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
         for (int j = 0; j < G; ++j) start[j * phases + c0 + tid] = first[j];
       }
     }
-    const bool ok = !s_bad && S <= cap;
+    const bool ok = !s_bad && S <= cap && pk_worth(s_sample, Q, small_grid);
     if (!ok)
       for (int c = tid; c < phases; c += 64) sc[c] = 0;
+    if (bundle == bundles - 1 && tid < SM_STEPS_PAD) steps[bundles + tid] = -1;   // nothing packed past the last bundle
     if (tid == 0) {
       s_steps = ok ? S : 0;
       steps[bundle] = ok ? S : -1;
+      redo[bundle] = 0;
     }
   }
   __syncthreads();

@@ -47,6 +47,7 @@ def _draw(P, Q, N, density, terms, seed):
     (1, 32, 8, 0.5, 1), (16, 128, 128, 0.02, 1), (17, 129, 136, 0.05, 3), (112, 127, 120, 0.1, 2),
     (113, 256, 264, 0.02, 3), (176, 640, 128, 0.3, 1), (177, 641, 248, 0.3, 2), (528, 1376, 2080, 0.06, 2),
     (529, 768, 4104, 0.02, 1), (1057, 96, 16392, 0.02, 1), (4096, 2100, 1032, 0.002, 2), (64, 4096, 512, 0.02, 1),
+    (40, 24576, 72, 0.002, 2), (40, 24608, 72, 0.002, 2),   # the widest that is packed, and the next
 ])
 def test_against_fp64(P, Q, N, density, terms):
     _check(*_draw(P, Q, N, density, terms, P + Q + N))
