@@ -309,6 +309,7 @@ inline int ld_slice(int64_t Q, int64_t N) {
 // fp32: those beyond LD_CAP over the whole of D by four workgroups 148 us, row by row 117, this 68; 4096 x 4096 -> 4096, 256
 // of 0.5, bf16: row by row 3162, all in the tiled kernel 1509, this 230.
 FP4_D int ld_span(int n_long, int slices) {
+  if (n_long <= LD_CAP) return 1;
   int m = (n_long + LD_CAP - 1) / LD_CAP;
   while (m < slices && (int64_t)((slices + m - 1) / m) * n_long > (int64_t)LD_CAP * slices) ++m;
   return max(1, min(m, slices));
@@ -493,12 +494,13 @@ __global__ __launch_bounds__(LD_WAVES * 64, 4) void spmm_long_dense_kernel(const
   __shared__ int64_t s_lo[LD_LB], s_en[LD_LB];
   __shared__ int s_rep;
   const int n_long = *count;
+  if (n_long == 0) return;
   const int groups = (n_long + LD_LB - 1) / LD_LB;
-  const int span = ld_span(n_long, slices), spans = (slices + span - 1) / span;
+  const int span = ld_span(n_long, slices), spans = span == 1 ? slices : (slices + span - 1) / span;
   int rows_a_turn = slice;   // what of a span the table takes at a time: a power of two
   while (2 * rows_a_turn <= min(LD_SLICE, span * slice)) rows_a_turn *= 2;
   for (int item = blockIdx.y; item < groups * spans; item += gridDim.y) {
-    const int group = item / spans, at = item - group * spans;   // its span
+    const int group = item < spans ? 0 : item / spans, at = item - group * spans;   // its span
     const int g0 = group * LD_LB, nl = min(LD_LB, n_long - g0);
     const int first = at * span * slice, last = min(first + span * slice, Q);   // Q < 2^21
 #pragma unroll 1
@@ -593,7 +595,8 @@ FP4_D void finish_long_rows(const int64_t* row_ptr, const int32_t* col_idx, cons
   constexpr int PARTS = THREADS / 256;
   const int c = threadIdx.x & 255, q = threadIdx.x >> 8;
   const int64_t n = first + c;
-  const int span = ld_span(n_long, slices), spans = (slices + span - 1) / span;
+  if (row0 >= n_long) return;
+  const int span = ld_span(n_long, slices), spans = span == 1 ? slices : (slices + span - 1) / span;
   for (int li = row0; li < n_long; li += rows_apart) {
     float* const r = R + (int64_t)list[li] * N;
     float sum = 0.0f;

@@ -19,8 +19,8 @@
 //
 // Bound: the matrix core (16 cycles an instruction), the LDS reads and the vector instructions (32 v_perm_b32 and 8
 // addresses a step) each leave room for about twice what is reached.  Residual of a 16384 x 4096 -> 12288 layer (2 %,
-// 1.3 M entries), packing included: 926 us, 35 TFLOP/s of useful products; plain fp32 FMAs fed from LDS (spmm.hip):
-// 1454 us.  6 %: 1487 against 2854 us; 0.2 %: 551 against 589 us.
+// 1.3 M entries), packing included: 857 us, 38 TFLOP/s of useful products; plain fp32 FMAs fed from LDS (spmm.hip):
+// 1423 us.  6 %: 1486 against 2961 us; 0.2 %: 524 against 609 us.
 #include "fp4_common.h"
 #include "spmm_long.h"
 
@@ -504,8 +504,8 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
   // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows
-  // 2.3 us a phase, 176 rows 1.2, 112 rows 1.0; 16384 x 4096 -> 12288: 926 / 1355 / 1737 us, 1056 x 1376 -> 2080: 59 /
-  // 37 / 35 us, 512 x 8192 -> 8192: 147 / 99 / 136 us.
+  // 2.3 us a phase, 176 rows 1.2, 112 rows 1.0; products 16384 x 4096 -> 12288: 852 / 1405 / 1831 us, 1056 x 1376 -> 2080:
+  // 40 / 29 / 28, 512 x 8192 -> 8192: 140 / 88 / 126.
   auto cost = [&](int g, int wv) { return (blocks(g, wv) * col_blocks + 255) / 256 * (300 + 16 * g * wv); };
   const int64_t big = cost(3, 11), mid = cost(1, 11), small = cost(1, 7);
   using I1 = std::integral_constant<int, 1>;
