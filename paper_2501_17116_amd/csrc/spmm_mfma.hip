@@ -167,10 +167,11 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   }
   __syncthreads();
   if (sampler) {
-    uint32_t t[3];
-    const int nt = bf16_terms(sample_v, t);
+    // more than one term: bits below bf16's; more than two: so has what the nearest bf16 number leaves
+    const uint32_t u = f2u(sample_v);
+    const float left = sample_v - u2f((u + 0x8000u) & 0xffff0000u);
     const uint64_t mine = is_long ? 0 : (uint64_t)min(n, (int64_t)Q);   // 21 bits hold the sum of 64
-    uint64_t sum = mine | (nt > 1 ? mine << 21 : 0) | (nt > 2 ? mine << 42 : 0);
+    uint64_t sum = mine | ((u & 0xffffu) ? mine << 21 : 0) | ((f2u(left) & 0xffffu) ? mine << 42 : 0);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     const int rows = __popcll(__ballot(!is_long));
