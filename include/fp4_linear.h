@@ -118,7 +118,8 @@ typedef struct {
 
 const char* fp4_status_string(int status);
 
-/* Bytes of device workspace an operation needs for the given problem. 0 for a bad op. */
+/* Bytes of device workspace an operation needs for the given problem. 0 for a bad op.  Never less
+ * for a larger problem: a buffer for the largest shape serves every smaller one. */
 size_t fp4_workspace_bytes(int op, int64_t M, int64_t K, int64_t N, fp4_dtype dt);
 
 /* Entries the residual buffers must hold: 2*floor((1-alpha)*rows*cols) (Sec. 3.2; the

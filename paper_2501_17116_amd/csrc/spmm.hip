@@ -274,7 +274,8 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __res
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
   __shared__ int s_skip[SP_ROWS];
   spmm_tile_block<DT, __is_same(DT, BF16)>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
-                      (int64_t)blockIdx.x * SP_ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS, slab, s_skip);
+                                           (int64_t)blockIdx.x * SP_ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS,
+                                           slab, s_skip);
 }
 
 // ---- long rows -------------------------------------------------------------------------------
@@ -296,9 +297,9 @@ constexpr int LD_SLICE = 512;    // most rows of D in the table, and in a slice
 constexpr int LD_CAP = 32;       // long rows up to which a span is one slice; sizes the partial sums' scratch
 constexpr int LD_COLS = 512;     // columns per workgroup (64 lanes x 8)
 constexpr int LD_WAVES = 8;      // waves per workgroup; they split the slice's rows
-// Rows of D per slice: 512, halved (to 64 at least) while that leaves fewer than 256 workgroups for a group of long rows, whose stream of D
-// would then run on a part of the chip (512 against this: 1056 x 1376 x 2080 step, both products 35 -> 13 us; 2048^3 fp32
-// 44 -> 22).  Aiming at 512 workgroups gave nothing more and made the summing of the slices longer.
+// Rows of D per slice: 512, halved (to 64 at least) while that leaves fewer than 256 workgroups for a group of long rows,
+// whose stream of D would then run on a part of the chip (512 against this: 1056 x 1376 x 2080 step, both products 35 -> 13
+// us; 2048^3 fp32 44 -> 22).  Aiming at 512 workgroups gave nothing more and made the summing of the slices longer.
 inline int ld_slice(int64_t Q, int64_t N) {
   int slice = LD_SLICE;
   while (slice > 64 && (Q + slice - 1) / slice * ((N + LD_COLS - 1) / LD_COLS) < 256) slice /= 2;
@@ -981,7 +982,8 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
                          SpmmRest& rest, hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
-// the fp32 partial sums of the dense long-row path, [spans][long rows][N], at most LD_CAP x slices rows of N, then (bf16 D) the packed matrix.
+// the fp32 partial sums of the dense long-row path, [spans][long rows][N], at most LD_CAP x slices rows of N, then (bf16 D)
+// the packed matrix.
 static int64_t spmm_list_words(int64_t P) { return 64 + (P + 63) / 64 * 64; }
 // The partial sums' share, for this product and any smaller one: slices of fewer than 512 rows are only taken while twice as
 // many rows leave fewer than 256 workgroups of 512 columns, so there are at most 510 of them.

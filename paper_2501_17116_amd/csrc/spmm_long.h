@@ -13,8 +13,9 @@ struct SpmmRest {
 };
 
 #if defined(__HIPCC__)
-// A row is long above a quarter of the columns, at most 2048 entries, but always above four times the mean row.  Measured against 2048 entries whatever the width (steps with one to ten dense
-// channels): fp32 2048^3 1379 -> 429 us, fp32 256 x 512 x 512 337 -> 256 us, bf16 1056 x 1376 x 2080 836 -> 403 us.
+// A row is long above a quarter of the columns, at most 2048 entries, but always above four times the mean row.  Measured
+// against 2048 entries whatever the width (steps with one to ten dense channels): fp32 2048^3 1379 -> 429 us, fp32 256 x 512
+// x 512 337 -> 256 us, bf16 1056 x 1376 x 2080 836 -> 403 us.
 // With 64 columns or fewer no row is long, also not one that repeats columns and so has more entries than that: the
 // long-row kernels are not launched then.
 constexpr int64_t SPMM_LONG_MIN = 64;

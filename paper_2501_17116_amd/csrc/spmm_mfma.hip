@@ -101,7 +101,8 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
                                                                int Q, int cap, int phases, bool small_grid, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
-                                                               int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list, int32_t* count) {
+                                                               int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list,
+                                                               int32_t* count) {
   constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR;
   extern __shared__ uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
