@@ -3,8 +3,10 @@
 // CSR.  (The clamp itself is fused into the quantization pass; the transpose for the weight
 // gradient and the sparse x dense product live with the sparse kernels.)
 #include "fp4_common.h"
+#include "last_block.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -16,11 +18,19 @@ constexpr int SEL_BINS = 2048;  // 11-bit digits
 constexpr int SEL_THREADS = 1024;   // per workgroup: the 64 KiB of LDS tables allow two workgroups per CU,
                                     // so their size decides how many loads a CU has in flight
 
+constexpr int SEL_PASSES = 3;   // digits, at most
+
+// A digit pass: a workgroup for every 8192 elements up to 256 of them, for every 65536 up to 512 (64 x 2048 bf16, one for
+// every 8192 / 65536: 8.5 / 9.2 us with the bins picked / without; 1056 x 1376 7.1 / 10.2; 8192 x 2048, 512 / 256: 18.1 /
+// 15.6, each adds its bins to the same words).  Up to 64 of them the last one picks the bins: a launch of 4 us less; with
+// more the arrivals cost more than that (8192 x 2048: 22.9 us against 15.6 + 4.9).
+constexpr int SEL_PICK_HERE = 64;
+
 // Selection state kept in the workspace between passes.
 struct SelState {
   unsigned long long rank[2];  // remaining 0-based rank of the lo / hi order statistic
   uint32_t prefix[2];          // key bits fixed so far (right-aligned)
-  uint32_t pad[2];
+  uint32_t arrived[SEL_PASSES];   // workgroups done with a pass
 };
 
 __global__ void sel_init_kernel(SelState* st, unsigned long long* hist, unsigned long long k,
@@ -32,6 +42,7 @@ __global__ void sel_init_kernel(SelState* st, unsigned long long* hist, unsigned
     st->rank[1] = n - 1 - k;
     st->prefix[0] = st->prefix[1] = 0;
     if (total) *total = 0;
+    for (int a = 0; a < SEL_PASSES; ++a) st->arrived[a] = 0;
   }
 }
 
@@ -45,10 +56,79 @@ FP4_D uint32_t key_of(uint32_t raw) {   // raw: bf16 bits (low 16) or fp32 bits
   else return f32_order_key(raw);
 }
 
-template <class DT>
+// Pick, for each of the two targets, the bin that holds its rank; extend the prefix, reduce
+// the rank, clear the histograms.  After the last pass the prefix is the full key: decode it.
+// One workgroup: the one that finishes its part of the histogram last, or a launch of its own.
+FP4_D void sel_pick(SelState* st, unsigned long long* hist, int bits, int first, int last, int key_bits, float* thresholds) {
+  constexpr int PER = SEL_BINS / SEL_THREADS;   // bins a thread owns when all SEL_BINS are in use
+  __shared__ unsigned long long s_w[SEL_THREADS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = 1 << bits;
+  const int per = (nb + SEL_THREADS - 1) / SEL_THREADS;
+  // both targets' bins and ranks are requested before either scan starts
+  unsigned long long vv[2][PER], rr[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const unsigned long long* hsrc = hist + (first ? 0 : s * SEL_BINS);
+    rr[s] = st->rank[s];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int b = tid * per + j;
+      vv[s][j] = (j < per && b < nb) ? load_device(hsrc + b) : 0;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    unsigned long long (&v)[PER] = vv[s];
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) sum += v[j];
+    // inclusive prefix of the threads' sums: the thread whose range [excl, incl) holds the rank
+    // owns the bin (the last thread, should the rank lie beyond the total)
+    unsigned long long incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += s_w[w];
+    const unsigned long long r = rr[s];
+    const unsigned long long excl = incl - sum;
+    if ((excl <= r && r < incl) || (tid == SEL_THREADS - 1 && r >= incl)) {
+      unsigned long long cum = excl;
+      int j = 0;
+      const int jend = min(per, nb - tid * per);   // bins of this thread that exist (may be <= 0)
+#pragma unroll
+      for (int q = 0; q < PER - 1; ++q)
+        if (j == q && q < jend - 1 && cum + v[q] <= r) { cum += v[q]; ++j; }
+      const int b = min(tid * per + j, nb - 1);
+      const uint32_t key = (st->prefix[s] << bits) | (uint32_t)b;
+      st->rank[s] = r - cum;
+      st->prefix[s] = key;
+      if (last) {
+        if (key_bits == 16) {
+          // 16-bit keys are the top half of the fp32 key of a bf16 value; undo the map on
+          // 16 bits so the low half of the fp32 pattern stays zero
+          const uint32_t h = (key & 0x8000u) ? (key & 0x7fffu) : (~key & 0xffffu);
+          thresholds[s] = u2f(h << 16);
+        } else {
+          thresholds[s] = u2f(f32_from_order_key(key));
+        }
+      }
+    }
+    __syncthreads();
+  }
+  for (int i = tid; i < 2 * SEL_BINS; i += SEL_THREADS) hist[i] = 0;
+}
+
+// PICK: the workgroup that is done last picks the bins.
+template <class DT, bool FIRST, bool PICK>
 __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, int64_t rows, int64_t cols,
-                                                       int64_t ld, int shift, int bits, int first,
-                                                       const SelState* st, unsigned long long* hist) {
+                                                       int64_t ld, int shift, int bits, int pass, int last, int key_bits,
+                                                       SelState* st, unsigned long long* hist, float* thresholds) {
+  constexpr bool first = FIRST;
   __shared__ uint32_t h[8 * SEL_BINS];   // first pass: 8 replicas; later: 4 replicas x 2 targets
   for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
   __syncthreads();
@@ -114,74 +194,14 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, in
       if (v) atomicAdd(&hist[i], (unsigned long long)v);
     }
   }
+  if constexpr (PICK) {
+    if (last_workgroup(&st->arrived[pass], gridDim.x)) sel_pick(st, hist, bits, first, last, key_bits, thresholds);
+  }
 }
 
-// Pick, for each of the two targets, the bin that holds its rank; extend the prefix, reduce
-// the rank, clear the histograms.  After the last pass the prefix is the full key: decode it.
-__global__ __launch_bounds__(256) void sel_pick_kernel(SelState* st, unsigned long long* hist, int bits,
-                                                       int first, int last, int key_bits,
-                                                       float* thresholds) {
-  constexpr int PER = SEL_BINS / 256;   // bins a thread owns when all SEL_BINS are in use
-  __shared__ unsigned long long s_w[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nb = 1 << bits;
-  const int per = (nb + 255) / 256;
-  // both targets' bins and ranks are requested before either scan starts
-  unsigned long long vv[2][PER], rr[2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const unsigned long long* hsrc = hist + (first ? 0 : s * SEL_BINS);
-    rr[s] = st->rank[s];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int b = tid * per + j;
-      vv[s][j] = (j < per && b < nb) ? hsrc[b] : 0;
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    unsigned long long (&v)[PER] = vv[s];
-    unsigned long long sum = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) sum += v[j];
-    // inclusive prefix of the threads' sums: the thread whose range [excl, incl) holds the rank
-    // owns the bin (the last thread, should the rank lie beyond the total)
-    unsigned long long incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
-    }
-    if (lane == 63) s_w[wave] = incl;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) incl += s_w[w];
-    const unsigned long long r = rr[s];
-    const unsigned long long excl = incl - sum;
-    if ((excl <= r && r < incl) || (tid == 255 && r >= incl)) {
-      unsigned long long cum = excl;
-      int j = 0;
-      const int jend = min(per, nb - tid * per);   // bins of this thread that exist (may be <= 0)
-#pragma unroll
-      for (int q = 0; q < PER - 1; ++q)
-        if (j == q && q < jend - 1 && cum + v[q] <= r) { cum += v[q]; ++j; }
-      const int b = min(tid * per + j, nb - 1);
-      st->rank[s] = r - cum;
-      st->prefix[s] = (st->prefix[s] << bits) | (uint32_t)b;
-      if (last) {
-        uint32_t key = st->prefix[s];
-        if (key_bits == 16) {
-          // 16-bit keys are the top half of the fp32 key of a bf16 value; undo the map on
-          // 16 bits so the low half of the fp32 pattern stays zero
-          const uint32_t h = (key & 0x8000u) ? (key & 0x7fffu) : (~key & 0xffffu);
-          thresholds[s] = u2f(h << 16);
-        } else {
-          thresholds[s] = u2f(f32_from_order_key(key));
-        }
-      }
-    }
-    __syncthreads();
-  }
-  for (int i = tid; i < 2 * SEL_BINS; i += 256) hist[i] = 0;
+__global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, unsigned long long* hist, int bits, int first, int last,
+                                                               int key_bits, float* thresholds) {
+  sel_pick(st, hist, bits, first, last, key_bits, thresholds);
 }
 
 // ---- CSR finalisation ---------------------------------------------------------------------
@@ -278,18 +298,24 @@ int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, i
   if (bf16) { digits[0] = 11; digits[1] = 5; nd = 2; }
   else { digits[0] = 11; digits[1] = 11; digits[2] = 10; nd = 3; }
   int shift = key_bits;
-  const unsigned grid =
-      (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + SEL_THREADS * 64 - 1) / (SEL_THREADS * 64), 512));
+  const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
+  const bool pick_here = grid <= SEL_PICK_HERE;
   for (int p = 0; p < nd; ++p) {
     shift -= digits[p];
-    if (bf16)
-      hipLaunchKernelGGL((sel_hist_kernel<BF16>), dim3(grid), dim3(SEL_THREADS), 0, s, x, rows, cols, ld, shift,
-                         digits[p], p == 0, st, hist);
-    else
-      hipLaunchKernelGGL((sel_hist_kernel<F32>), dim3(grid), dim3(SEL_THREADS), 0, s, x, rows, cols, ld, shift,
-                         digits[p], p == 0, st, hist);
-    hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(256), 0, s, st, hist, digits[p], p == 0, p == nd - 1,
-                       key_bits, thresholds);
+    auto launch = [&](auto dt, auto first, auto pick) {
+      hipLaunchKernelGGL((sel_hist_kernel<decltype(dt), decltype(first)::value, decltype(pick)::value>), dim3(grid), dim3(SEL_THREADS), 0, s, x, rows, cols, ld,
+                         shift, digits[p], p, p == nd - 1, key_bits, st, hist, thresholds);
+    };
+    auto pass = [&](auto dt, auto first) {
+      if (pick_here) launch(dt, first, std::true_type{});
+      else launch(dt, first, std::false_type{});
+    };
+    if (p == 0) { if (bf16) pass(BF16{}, std::true_type{}); else pass(F32{}, std::true_type{}); }
+    else { if (bf16) pass(BF16{}, std::false_type{}); else pass(F32{}, std::false_type{}); }
+    if (!pick_here)
+      hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(SEL_THREADS), 0, s, st, hist, digits[p], p == 0, p == nd - 1, key_bits,
+                         thresholds);
   }
   FP4_CHECK_LAUNCH();
   return FP4_OK;
