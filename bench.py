@@ -327,17 +327,19 @@ RESIDUAL_KERNELS = {"bf16": "spmm_pack_kernel + spmm_mfma_kernel + spmm_long_den
 
 
 def gemm_kernels(cfg, layers, torch):
-    """Which of the FP4 GEMM's two kernels the step's products run on (the rule of fp4_launch_gemm)."""
+    """Which of the FP4 GEMM's kernels the step's products run on (the rule of fp4_launch_gemm)."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     names = set()
     for L in layers:
         l = L["shape"]
-        for P, Q, Kc, factor in ((l.M, l.N, l.K, False), (l.M, l.K, l.N, False), (l.K, l.N, l.M, True)):
-            tiles = -(-P // 64) * -(-Q // 64)
-            small = tiles <= (3 if Kc // 2 % 128 else 1) * cus
-            if factor and cfg.dtype == "f32" and cfg.dge_k > 0:
-                small |= tiles <= 4 * cus and tiles * Kc <= 12288 * cus
-            names.add("fp4_gemm_small_kernel" if small else "fp4_gemm_nt_kernel")
+        for P, Q, Kc, factor in ((l.M, l.N, l.K, False), (l.M, l.K, l.N, False), (l.K, l.N, l.M, cfg.dge_k > 0)):
+            small, mid = -(-P // 64) * -(-Q // 64), -(-P // 128) * -(-Q // 128)
+            if (small <= 3 * cus and small * Kc <= 3072 * cus) if factor else (small <= 2 * cus and Kc <= 1024):
+                names.add("fp4_gemm_small_kernel")
+            elif mid <= ((1 if cfg.dtype == "bf16" else 3) if factor else 2) * cus:
+                names.add("fp4_gemm_mid_kernel")
+            else:
+                names.add("fp4_gemm_nt_kernel")
     return " + ".join(sorted(names))
 
 

@@ -44,6 +44,8 @@ constexpr int STAGE_BYTES = 2 * TILE_BYTES;
 constexpr int EPI_BASE = STAGE_BYTES;
 constexpr int SMEM_BYTES = 2 * STAGE_BYTES > EPI_BASE + EPI_BYTES ? 2 * STAGE_BYTES : EPI_BASE + EPI_BYTES;
 static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
+// Past the end of any tile's descriptor while its rows take no more than this (contractions to 31 M codes).
+constexpr uint32_t OUT_OF_RANGE = 0xf0000000u;
 
 // LDS layout of an operand stage: row r occupies bytes [128 r, 128 r + 128); its 16-byte
 // chunk c sits in slot c ^ ((r >> 1) & 7).  Sixteen consecutive rows reading the same logical
@@ -136,8 +138,8 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
     Q0 = (int64_t)tq * BN;
     tileL = uniform_ptr(Lp + P0 * g.Kb);
     tileR = uniform_ptr(Rp + Q0 * g.Kb);
-    // buffer descriptors over the tile's rows: loads past the end of the matrix return zero
-    const uint64_t bytesL = (uint64_t)(g.P - P0) * (uint64_t)g.Kb, bytesR = (uint64_t)(g.Q - Q0) * (uint64_t)g.Kb;
+    // buffer descriptors over the tile's rows: loads past their end return zero
+    const uint64_t bytesL = (uint64_t)min(g.P - P0, (int64_t)BM) * (uint64_t)g.Kb, bytesR = (uint64_t)min(g.Q - Q0, (int64_t)BN) * (uint64_t)g.Kb;
     rsrcL = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(tileL), 0,
         __builtin_amdgcn_readfirstlane((int)(bytesL > 0xffffffffull ? 0xffffffffu : (uint32_t)bytesL)), 0x00020000);
@@ -161,41 +163,30 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
       goffR[j] = (uint32_t)(rq * g.Kb + chunk * 16);
     }
   };
-  const int lds_lane = (wave * NLD) * 1024 + lane * 16;
   const int KT = (int)((g.Kb + BKB - 1) / BKB);
 
   f32x16 acc[QI][4];
 
-  // Fast path: global -> LDS without passing through registers.  Ragged K (K step overhanging
-  // the row): through registers, blanking the overhang.
+  // global -> LDS without passing through registers.  Where the last K step overhangs the row (KRAGGED), the chunks
+  // behind the row's end take an offset past the descriptor's end and arrive as zeros.  Through registers, with the overhang
+  // blanked, such a contraction took twice the time (8192 x 2048, 5504 codes: 100 us, now 51).
+  const uint32_t ragged_row = (uint32_t)g.Kb;
   auto load_tile = [&](int kt, int buf, int jb, int je) {
-    const uint8_t* bL = tileL + (int64_t)kt * BKB;
-    const uint8_t* bR = tileR + (int64_t)kt * BKB;
-    if constexpr (!KRAGGED) {
+    [[maybe_unused]] const uint32_t room = ragged_row - (uint32_t)(kt * BKB);   // bytes of the row from this step on
+    [[maybe_unused]] const int ln = lane;
 #pragma unroll
-      for (int j = jb; j < je; ++j) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rsrcL, (__attribute__((address_space(3))) void*)(sL + buf * STAGE_BYTES + (wave * NLD + j) * 1024), 16,
-            goffL[j], kt * BKB, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rsrcR, (__attribute__((address_space(3))) void*)(sR + buf * STAGE_BYTES + (wave * NLD + j) * 1024), 16,
-            goffR[j], kt * BKB, 0, 0);
+    for (int j = jb; j < je; ++j) {
+      uint32_t ol = goffL[j], orr = goffR[j];
+      if constexpr (KRAGGED) {
+        const int row = 8 * (wave * NLD + j) + (ln >> 3);
+        const bool in = (uint32_t)(((ln & 7) ^ ((row >> 1) & 7)) * 16) < room;
+        ol = in ? ol : OUT_OF_RANGE;
+        orr = in ? orr : OUT_OF_RANGE;
       }
-    } else {
-#pragma unroll
-      for (int j = jb; j < je; ++j) {
-        const int row = 8 * (wave * NLD + j) + (lane >> 3);
-        const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-        const bool ok = (int64_t)kt * BKB + chunk * 16 < g.Kb;
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        u32x4 a = z, b = z;
-        if (ok) {
-          a = *reinterpret_cast<const u32x4*>(bL + goffL[j]);
-          b = *reinterpret_cast<const u32x4*>(bR + goffR[j]);
-        }
-        *reinterpret_cast<u32x4*>(sL + buf * STAGE_BYTES + lds_lane + j * 1024) = a;
-        *reinterpret_cast<u32x4*>(sR + buf * STAGE_BYTES + lds_lane + j * 1024) = b;
-      }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrcL, (__attribute__((address_space(3))) void*)(sL + buf * STAGE_BYTES + (wave * NLD + j) * 1024), 16, ol, kt * BKB, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrcR, (__attribute__((address_space(3))) void*)(sR + buf * STAGE_BYTES + (wave * NLD + j) * 1024), 16, orr, kt * BKB, 0, 0);
     }
   };
 
@@ -254,9 +245,7 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
   load_tile(min(1, KT - 1), 1, 0, NLD);
-  if constexpr (KRAGGED) {
-    __builtin_amdgcn_s_waitcnt(0);
-  } else {
+  {
     // all but the 2 NLD loads just issued: stage 0 and, before it in issue order, whatever the
     // previous epilogue left in flight
     constexpr int n = 2 * NLD;
@@ -580,83 +569,102 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
   }  // tiles
 }
 
-// The same product for outputs with too few 256 x 256 tiles to go round the chip: a workgroup of four waves takes
-// 64 x 64 outputs, a wave 32 x 32.  What bounds such a call is the chain of round trips of one tile, not a
-// rate, so operands go straight from memory to the matrix core's registers (a lane's 16 bytes of a row are its
-// fragment; a 128-byte line serves four steps out of L1), SG_IN steps ahead, and neither barrier nor staging stands
-// in between.  The output passes through LDS once so that it is read and written along rows.  Sums, scaling, addend
-// and factor are the same operations in the same order as in fp4_gemm_nt_kernel: the same bits.
-// 64 x 2048 x 2048: 10.9 us against 19.2; 512 x 512 x 256: 7.5 against 12.5 (fp32); 1056 x 2080 x 1376: 15 against 30.
-constexpr int SG_IN = 4;   // K steps (32 bytes a row) requested ahead: one 128-byte line of every row
-template <bool OUT_BF16, bool DGE, bool W_BF16>
-__global__ __launch_bounds__(256) void fp4_gemm_small_kernel(
-    const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,
-    const float* __restrict__ gr, const float* addend, void* outp, const void* __restrict__ Wp,
-    const float* __restrict__ gamma_w, GemmShape g) {
-  constexpr int T = 64, LD = T + 4;
-  __shared__ __attribute__((aligned(16))) float tile[T * LD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int wp = (wave & 1) * 32, wq = (wave >> 1) * 32;
-  const int64_t P0 = (int64_t)(blockIdx.x % (unsigned)g.tiles_p) * T, Q0 = (int64_t)(blockIdx.x / (unsigned)g.tiles_p) * T;
-  // rows past the edge re-read the last row
-  const uint8_t* const rowL = Lp + min(P0 + wp + l32, g.P - 1) * g.Kb + lhi * 16;
-  const uint8_t* const rowR = Rp + min(Q0 + wq + l32, g.Q - 1) * g.Kb + lhi * 16;
-  f32x16 acc;
+// The scales of a thread's eight columns of a T x T tile, requested ahead of the main loop: fetched one by one behind it they were
+// a chain of memory round trips.
+template <int T, bool DGE>
+FP4_D void column_scales(int64_t Q0, const float* gr, const float* gamma_w, const GemmShape& g, float (&ir)[8], float (&gw)[8]) {
+  const int64_t q0 = Q0 + (int)(threadIdx.x % (T / 8)) * 8;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  const int one = 127;
-  u32x4 a[2][SG_IN], b[2][SG_IN];
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  auto request = [&](int set, int64_t k0) {   // steps from byte k0 on; what lies past the row is zero
-#pragma unroll
-    for (int s = 0; s < SG_IN; ++s) {
-      const int64_t k = k0 + 32 * s;
-      const bool in = k + lhi * 16 < g.Kb;
-      a[set][s] = in ? *reinterpret_cast<const u32x4*>(rowR + k) : zero;
-      b[set][s] = in ? *reinterpret_cast<const u32x4*>(rowL + k) : zero;
-    }
-  };
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int s = 0; s < SG_IN; ++s) {
-      const u32x4 fa = a[set][s], fb = b[set][s];
-      const i32x8 va = {(int)fa.x, (int)fa.y, (int)fa.z, (int)fa.w, 0, 0, 0, 0};
-      const i32x8 vb = {(int)fb.x, (int)fb.y, (int)fb.z, (int)fb.w, 0, 0, 0, 0};
-      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, acc, 4, 4, 0, one, 0, one);
-    }
-  };
-  request(0, 0);
-  for (int64_t k0 = 0; k0 < g.Kb; k0 += 64 * SG_IN) {
-    request(1, k0 + 32 * SG_IN);
-    multiply(0);
-    if (k0 + 32 * SG_IN < g.Kb) {
-      request(0, k0 + 64 * SG_IN);
-      multiply(1);
-    }
+  for (int e = 0; e < 8; ++e) {
+    ir[e] = 1.0f;
+    gw[e] = 0.0f;
   }
-  const bool scaled = gl != nullptr;
-  const float il = scaled ? __builtin_amdgcn_rcpf(gl[min(P0 + wp + l32, g.P - 1)]) : 1.0f;
+  if (gr != nullptr) {
 #pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
-    const f32x4 y = {acc[g4 * 4] * il, acc[g4 * 4 + 1] * il, acc[g4 * 4 + 2] * il, acc[g4 * 4 + 3] * il};
-    *reinterpret_cast<f32x4*>(&tile[(wp + l32) * LD + wq + g4 * 8 + lhi * 4]) = y;
+    for (int e = 0; e < 8; ++e) ir[e] = gr[min(q0 + e, g.Q - 1)];
   }
-  __syncthreads();
+  if constexpr (DGE) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) gw[e] = gamma_w[min(q0 + e, g.Q - 1)];
+  }
+}
+// What is left of a T x T tile of sums that lie in LDS scaled by 1/gamma_l: 1/gamma_r, addend, factor, conversion, stores
+// along rows.  The same operations in the same order as in fp4_gemm_nt_kernel.  256 threads.
+template <int T, bool OUT_BF16, bool DGE, bool W_BF16>
+FP4_D void finish_tile(const float* tile, int64_t P0, int64_t Q0, const float (&ir)[8], const float (&gw)[8], const float* addend,
+                       void* outp, const void* Wp, const GemmShape& g) {
+  constexpr int LD = T + 4;
+  const int tid = threadIdx.x;
   constexpr int UPR = T / 8, RPT = 256 / UPR;   // 8-column units a row, rows a pass
   const int ql = (tid % UPR) * 8;
   const int64_t q0 = Q0 + ql;
   if (q0 >= g.Q) return;
   const bool full = q0 + 7 < g.Q;
-  float ir[8], gw[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int64_t q = min(q0 + e, g.Q - 1);
-    ir[e] = scaled ? __builtin_amdgcn_rcpf(gr[q]) : 1.0f;
-    gw[e] = DGE ? gamma_w[q] : 0.0f;
-  }
   const float inv_k = DGE ? 1.0f / g.dge_k : 1.0f;
   const float pw = inv_k - 1.0f;
+  if (full && P0 + T <= g.P) {   // no edge in this thread's part: what it reads is requested four passes at a time
+    constexpr int NP = T / RPT, B = NP < 4 ? NP : 4;
+#pragma unroll 1
+    for (int b = 0; b < NP; b += B) {
+      const int pl0 = tid / UPR + b * RPT;
+      f32x4 ad[B][2];
+      u32x4 w[B][2];
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        ad[i][0] = ad[i][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        w[i][0] = w[i][1] = u32x4{0u, 0u, 0u, 0u};
+      }
+      if (addend) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          const float* a = addend + (P0 + pl0 + i * RPT) * g.ldo + q0;
+          ad[i][0] = *reinterpret_cast<const f32x4*>(a);
+          ad[i][1] = *reinterpret_cast<const f32x4*>(a + 4);
+        }
+      }
+      if constexpr (DGE) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          const int64_t off = (P0 + pl0 + i * RPT) * g.ldw + q0;
+          if constexpr (W_BF16) {
+            w[i][0] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(Wp) + off);
+          } else {
+            w[i][0] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const float*>(Wp) + off);
+            w[i][1] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const float*>(Wp) + off + 4);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        const int pl = pl0 + i * RPT;
+        const f32x4 v0 = *reinterpret_cast<const f32x4*>(&tile[pl * LD + ql]), v1 = *reinterpret_cast<const f32x4*>(&tile[pl * LD + ql + 4]);
+        float y[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = __fmul_rn(y[e], ir[e]);
+        if (addend) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) y[e] += ad[i][e >> 2][e & 3];
+        }
+        if constexpr (DGE) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t u = W_BF16 ? ((e & 1) ? w[i][0][e >> 1] & 0xffff0000u : w[i][0][e >> 1] << 16) : w[i][e >> 2][e & 3];
+            y[e] *= dge_factor(u2f(u), gw[e], pw, inv_k, g.dge_cap);
+          }
+        }
+        const int64_t off = (P0 + pl) * g.ldo + q0;
+        if constexpr (OUT_BF16) {
+          *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(outp) + off) =
+              u32x4{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]), pack_bf16x2(y[6], y[7])};
+        } else {
+          float* o = reinterpret_cast<float*>(outp) + off;
+          *reinterpret_cast<f32x4*>(o) = f32x4{y[0], y[1], y[2], y[3]};
+          *reinterpret_cast<f32x4*>(o + 4) = f32x4{y[4], y[5], y[6], y[7]};
+        }
+      }
+    }
+    return;
+  }
 #pragma unroll 2
   for (int pl = tid / UPR; pl < T; pl += RPT) {
     const int64_t p = P0 + pl;
@@ -720,6 +728,200 @@ __global__ __launch_bounds__(256) void fp4_gemm_small_kernel(
   }
 }
 
+// The same product for outputs with too few 256 x 256 tiles to go round the chip: a workgroup of four waves takes
+// 64 x 64 outputs, a wave 32 x 32.  What bounds such a call is the chain of round trips of one tile, not a
+// rate, so operands go straight from memory to the matrix core's registers (a lane's 16 bytes of a row are its
+// fragment; a 128-byte line serves four steps out of L1), SG_IN steps ahead, and neither barrier nor staging stands
+// in between.  The output passes through LDS once so that it is read and written along rows.  Sums, scaling, addend
+// and factor are the same operations in the same order as in fp4_gemm_nt_kernel: the same bits.
+// 512 x 512 x 256: 4.5 us, 6.3 with 128 x 128 tiles, 10.3 with 256 x 256; 1024 x 2048 x 288: 5.5 / 7.3 / 11.9.
+constexpr int SG_IN = 4;   // K steps (32 bytes a row) requested ahead: one 128-byte line of every row
+template <bool OUT_BF16, bool DGE, bool W_BF16>
+__global__ __launch_bounds__(256) void fp4_gemm_small_kernel(
+    const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,
+    const float* __restrict__ gr, const float* addend, void* outp, const void* __restrict__ Wp,
+    const float* __restrict__ gamma_w, GemmShape g) {
+  constexpr int T = 64, LD = T + 4;
+  __shared__ __attribute__((aligned(16))) float tile[T * LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int wp = (wave & 1) * 32, wq = (wave >> 1) * 32;
+  const int64_t P0 = (int64_t)(blockIdx.x % (unsigned)g.tiles_p) * T, Q0 = (int64_t)(blockIdx.x / (unsigned)g.tiles_p) * T;
+  // rows past the edge re-read the last row
+  const uint8_t* const rowL = Lp + min(P0 + wp + l32, g.P - 1) * g.Kb + lhi * 16;
+  const uint8_t* const rowR = Rp + min(Q0 + wq + l32, g.Q - 1) * g.Kb + lhi * 16;
+  float ir[8], gw[8], il = 1.0f;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  const int one = 127;
+  u32x4 a[2][SG_IN], b[2][SG_IN];
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  auto request = [&](int set, int64_t k0) {   // steps from byte k0 on; what lies past the row is zero
+#pragma unroll
+    for (int s = 0; s < SG_IN; ++s) {
+      const int64_t k = k0 + 32 * s;
+      const bool in = k + lhi * 16 < g.Kb;
+      a[set][s] = in ? *reinterpret_cast<const u32x4*>(rowR + k) : zero;
+      b[set][s] = in ? *reinterpret_cast<const u32x4*>(rowL + k) : zero;
+    }
+  };
+  auto multiply = [&](int set) {
+#pragma unroll
+    for (int s = 0; s < SG_IN; ++s) {
+      const u32x4 fa = a[set][s], fb = b[set][s];
+      const i32x8 va = {(int)fa.x, (int)fa.y, (int)fa.z, (int)fa.w, 0, 0, 0, 0};
+      const i32x8 vb = {(int)fb.x, (int)fb.y, (int)fb.z, (int)fb.w, 0, 0, 0, 0};
+      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, vb, acc, 4, 4, 0, one, 0, one);
+    }
+  };
+  request(0, 0);
+  column_scales<T, DGE>(Q0, gr, gamma_w, g, ir, gw);
+  if (gl != nullptr) il = gl[min(P0 + wp + l32, g.P - 1)];
+  for (int64_t k0 = 0; k0 < g.Kb; k0 += 64 * SG_IN) {
+    request(1, k0 + 32 * SG_IN);
+    multiply(0);
+    if (k0 + 32 * SG_IN < g.Kb) {
+      request(0, k0 + 64 * SG_IN);
+      multiply(1);
+    }
+  }
+  il = __builtin_amdgcn_rcpf(il);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ir[e] = __builtin_amdgcn_rcpf(ir[e]);
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    const f32x4 y = {acc[g4 * 4] * il, acc[g4 * 4 + 1] * il, acc[g4 * 4 + 2] * il, acc[g4 * 4 + 3] * il};
+    *reinterpret_cast<f32x4*>(&tile[(wp + l32) * LD + wq + g4 * 8 + lhi * 4]) = y;
+  }
+  __syncthreads();
+  finish_tile<T, OUT_BF16, DGE, W_BF16>(tile, P0, Q0, ir, gw, addend, outp, Wp, g);
+}
+
+// The same for outputs in between: 128 x 128 a workgroup of four waves, a wave 64 x 64, one workgroup per CU.  A K step's
+// products are over in a fifth of a microsecond, far less than a load takes, so operands go through a ring of four LDS
+// stages with three on their way (the layout of fp4_gemm_nt_kernel's); one barrier a step.  A step takes 0.6 us, with 64
+// workgroups as with 256: the 32 KiB it brings into a CU bound it (reading a step's fragments while the one before is
+// multiplied changed nothing).  Sums, scaling and the rest as above: the same bits.
+// 2048 x 2048 x 8192: 25.6 us, 46.9 with 256 x 256 tiles, 119 with 64 x 64; 2048^3 11.2 / 18.9 / 34.7; 1056 x 2080 x 1376
+// 9.7 / 17.0 / 12.4; weight gradient with fp32 masters, 2048 x 2048 x 8192, quantizers included: 93 / 140 / 186.
+constexpr int MG_T = 128, MG_RING = 4;
+constexpr int MG_OP = MG_T * BKB, MG_STAGE = 2 * MG_OP, MG_LD = MG_T * 8 / 256;   // bytes of an operand, of a stage; 16-byte chunks a thread
+template <bool OUT_BF16, bool DGE, bool W_BF16>
+__global__ __launch_bounds__(256) void fp4_gemm_mid_kernel(
+    const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,
+    const float* __restrict__ gr, const float* addend, void* outp, const void* __restrict__ Wp,
+    const float* __restrict__ gamma_w, GemmShape g) {
+  constexpr int T = MG_T, LD = T + 4;
+  static_assert(MG_RING * MG_STAGE >= T * LD * 4, "the sums lie over the ring");
+  __shared__ __attribute__((aligned(16))) uint8_t smem[MG_RING * MG_STAGE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int wp = (wave & 1) * 64, wq = (wave >> 1) * 64;
+  // each XCD a contiguous run of tiles, eight tile-rows side by side
+  const int total = g.tiles_p * g.tiles_q, per_xcd = (total + 7) / 8;
+  const int id = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
+  const int in_group = GROUP_P * g.tiles_q, first_p = id / in_group * GROUP_P;
+  const int gsz = min(g.tiles_p - first_p, GROUP_P);
+  const int64_t P0 = (int64_t)(first_p + id % in_group % gsz) * T, Q0 = (int64_t)(id % in_group / gsz) * T;
+  const __amdgpu_buffer_rsrc_t rsrcL = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(Lp) + P0 * g.Kb, 0, (int)(uint32_t)(min(g.P - P0, (int64_t)T) * g.Kb), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrcR = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(Rp) + Q0 * g.Kb, 0, (int)(uint32_t)(min(g.Q - Q0, (int64_t)T) * g.Kb), 0x00020000);
+  const uint32_t Kb = (uint32_t)g.Kb;
+  uint32_t offL[MG_LD], offR[MG_LD], at[MG_LD];   // a lane's chunk: from the tile's first row, and inside a step
+#pragma unroll
+  for (int j = 0; j < MG_LD; ++j) {
+    const int row = 8 * (wave * MG_LD + j) + (lane >> 3);
+    at[j] = (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    offL[j] = (uint32_t)min((int64_t)row, g.P - 1 - P0) * Kb + at[j];   // rows past the edge re-read the last row
+    offR[j] = (uint32_t)min((int64_t)row, g.Q - 1 - Q0) * Kb + at[j];
+  }
+  auto request = [&](int kt) {   // what lies past the row, and steps past the last, arrive as zeros
+    uint8_t* const st = smem + (kt & (MG_RING - 1)) * MG_STAGE + wave * MG_LD * 1024;
+    const uint32_t k = (uint32_t)(kt * BKB);
+#pragma unroll
+    for (int j = 0; j < MG_LD; ++j) {
+      const bool in = k + at[j] < Kb;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcL, (__attribute__((address_space(3))) void*)(st + j * 1024), 16,
+                                               in ? offL[j] + k : OUT_OF_RANGE, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcR, (__attribute__((address_space(3))) void*)(st + MG_OP + j * 1024), 16,
+                                               in ? offR[j] + k : OUT_OF_RANGE, 0, 0, 0);
+    }
+  };
+  float ir[8], gw[8], il[2] = {1.0f, 1.0f};
+  const int KT = (int)((g.Kb + BKB - 1) / BKB);
+  const int key = (l32 >> 1) & 7;
+  f32x16 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i >> 1][i & 1][v] = 0.0f;
+  const int one = 0x7f7f7f7f;
+#pragma unroll
+  for (int kt = 0; kt < MG_RING - 1; ++kt) request(kt);
+  column_scales<T, DGE>(Q0, gr, gamma_w, g, ir, gw);
+  if (gl != nullptr) {
+#pragma unroll
+    for (int pj = 0; pj < 2; ++pj) il[pj] = gl[min(P0 + wp + pj * 32 + l32, g.P - 1)];
+  }
+  for (int kt = 0; kt < KT; ++kt) {
+    asm volatile("" ::: "memory");
+    // this wave's share of step kt is there, and it is done reading step kt - 1; behind the barrier that holds for all
+    constexpr int left = (MG_RING - 2) * 2 * MG_LD;
+    __builtin_amdgcn_s_waitcnt(0x0070 | (left & 15) | ((left >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    request(kt + MG_RING - 1);
+    const uint8_t* const sL = smem + (kt & (MG_RING - 1)) * MG_STAGE + (wp + l32) * BKB;
+    const uint8_t* const sR = smem + (kt & (MG_RING - 1)) * MG_STAGE + MG_OP + (wq + l32) * BKB;
+    u32x4 fl[4][2], fr[4][2];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int slot = ((2 * ks + lhi) ^ key) * 16;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        fr[ks][j] = *reinterpret_cast<const u32x4*>(sR + slot + j * 32 * BKB);
+        fl[ks][j] = *reinterpret_cast<const u32x4*>(sL + slot + j * 32 * BKB);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // all sixteen requested before the first product
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int qi = 0; qi < 2; ++qi) {
+        const i32x8 a = {(int)fr[ks][qi].x, (int)fr[ks][qi].y, (int)fr[ks][qi].z, (int)fr[ks][qi].w, 0, 0, 0, 0};
+#pragma unroll
+        for (int pj = 0; pj < 2; ++pj) {
+          const i32x8 b = {(int)fl[ks][pj].x, (int)fl[ks][pj].y, (int)fl[ks][pj].z, (int)fl[ks][pj].w, 0, 0, 0, 0};
+          acc[qi][pj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[qi][pj], 4, 4, 0, one, 0, one);
+        }
+      }
+  }
+  __builtin_amdgcn_s_waitcnt(0);   // no load may land over the sums
+  __syncthreads();
+  float* const tile = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ir[e] = __builtin_amdgcn_rcpf(ir[e]);
+#pragma unroll
+  for (int pj = 0; pj < 2; ++pj) {
+    const int p = wp + pj * 32 + l32;
+    const float i1 = __builtin_amdgcn_rcpf(il[pj]);
+#pragma unroll
+    for (int qi = 0; qi < 2; ++qi)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x16& c = acc[qi][pj];
+        *reinterpret_cast<f32x4*>(&tile[p * LD + wq + qi * 32 + g4 * 8 + lhi * 4]) =
+            f32x4{c[g4 * 4] * i1, c[g4 * 4 + 1] * i1, c[g4 * 4 + 2] * i1, c[g4 * 4 + 3] * i1};
+      }
+  }
+  __syncthreads();
+  finish_tile<T, OUT_BF16, DGE, W_BF16>(tile, P0, Q0, ir, gw, addend, outp, Wp, g);
+}
+
 __global__ void fp4_unpack_kernel(const uint8_t* codes, int64_t nbytes, uint8_t* out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nbytes) {
@@ -765,24 +967,33 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   const dim3 grid(std::min(((total + 7) / 8) * 8, (n_cu / 8) * 8)), block(NTHREADS);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
   const bool ragged = (g.Kb % BKB) != 0;
-  // Small tiles while each CU gets one of them (512 x 2048 x 2048: 11 against 18 us, 256 x 4096 x 16384: 62 against 77);
-  // with four per CU they lose (2048^3: 36 against 21).  A row of codes that ends inside a K step puts the big tiles
-  // on their slower path, so there the line lies at three per CU (1376 x 2080 x 1056, 726 tiles: 13 against 28 us).
-  const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64);
-  // The same, at longer contractions: 544 .. 16416, 256 to 768 tiles, 0.20 to 0.70 of the big tiles' time throughout.
-  // The factor with fp32 weights has no branch-free epilogue in the big tiles, about 60 us that the small ones save and
-  // lose again on the contraction: up to four per CU while tiles x contraction is at most that of 12288 codes per CU (weight
-  // gradient without the clamp, 2048 x 2048, contraction 2048 / 3072 / 4096 / 8192: 76 / 96 / 118 / 189 us against 94 / 106 /
-  // 110 / 141; 512 tiles, 6144: 101 against 119, 16384: 208 against 190).
-  const bool fp32_factor = dge && !w_bf16 && small_tiles <= 4 * (int64_t)n_cu && small_tiles * Kc <= 12288 * (int64_t)n_cu;
-  const bool small = fp32_factor || small_tiles <= (ragged ? 3 : 1) * (int64_t)n_cu;
-  GemmShape gs = g;
+  // What bounds a call with few tiles is one tile's chain of steps, so the smaller tile wins while there is no more than a
+  // round or two of it.  Measured as 64 / 128 / 256 tiles, in us:
+  //  64, up to 1024 codes and two tiles per CU: 512 x 2048, 512 codes 5.6 / 7.1 / 11.5; 512 x 1024, 1024 7.2 / 7.8 / 13.3;
+  //   past that line 512 x 2048, 2048 10.7 / 9.5 / 17.5; 2048 x 2048, 256 9.7 / 7.6 / 11.4.
+  //  64 with the factor, which asks for many threads: tiles x contraction up to 3072 codes per CU (the whole weight gradient
+  //   without the clamp, fp32, 1024 x 1024, 2048 codes: 42 / 45 / 78; 1376 x 2080, 1056: 45 / 47 / 77; 2048 x 2048, 2048: 72 / 51 / 84).
+  //  128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend 40 / 22.6 / 24.8 and 237 / 54 / 58; past it
+  //   2816 x 3072, 4096 140 / 48 / 38.  With the factor one (2048 x 4096 x 4096 bf16 172 / 87 / 86), and with fp32 masters, for which
+  //   the big tiles have no branch-free epilogue, three (2048 x 5504, 2048 codes 138 / 88 / 93; 4096 x 4096, 2048 180 / 107 / 99).
+  const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64), mid_tiles = ((P + MG_T - 1) / MG_T) * ((Q + MG_T - 1) / MG_T);
+  const bool few = dge ? small_tiles <= 3 * (int64_t)n_cu && small_tiles * Kc <= 3072 * (int64_t)n_cu
+                       : small_tiles <= 2 * (int64_t)n_cu && Kc <= 1024;
+  // rows too long for the offsets of the larger tiles' descriptors
+  const bool small = few || g.Kb * (ragged ? BM : 1) > (int64_t)OUT_OF_RANGE;
+  const bool mid = mid_tiles <= (dge ? (w_bf16 ? 1 : 3) : 2) * (int64_t)n_cu && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE;
+  GemmShape gs = g, gm = g;
   gs.tiles_p = (int)((P + 63) / 64);
+  gm.tiles_p = (int)((P + MG_T - 1) / MG_T);
+  gm.tiles_q = (int)((Q + MG_T - 1) / MG_T);
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
     if (small)                                                                                            \
       hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)small_tiles), dim3(256), 0, stream, L, Rt, gl, gr, \
                          addend, out, W, gamma_w, gs);                                                    \
+    else if (mid)                                                                                         \
+      hipLaunchKernelGGL((fp4_gemm_mid_kernel<OB, DG, WB>), dim3((unsigned)((gm.tiles_p * gm.tiles_q + 7) / 8 * 8)), dim3(256), 0, \
+                         stream, L, Rt, gl, gr, addend, out, W, gamma_w, gm);                             \
     else if (ragged)                                                                                      \
       hipLaunchKernelGGL((fp4_gemm_nt_kernel<OB, DG, WB, true>), grid, block, 0, stream, L, Rt, gl, gr,   \
                          addend, out, W, gamma_w, g);                                                     \

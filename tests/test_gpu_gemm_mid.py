@@ -1,0 +1,48 @@
+"""The FP4 GEMM's 128 x 128 tiles at the edges of tiles, ring and dispatch, and its 256 x 256 tiles on contractions that end
+inside a K step: against the exact integer product (raw accumulators; every sum is a multiple of 1/4 below 2^22)
+and, scaled, against the definition's fp32 operations on it, to the last bit."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+GRID = torch.tensor([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6])
+
+
+def _values(codes):
+    return GRID[torch.stack([codes & 15, codes >> 4], -1).reshape(codes.shape[0], -1).long()]
+
+
+@pytest.mark.parametrize("P,Q,K", [(1, 8, 1056), (127, 136, 1280), (128, 128, 1312), (129, 1000, 2048), (2048, 2048, 32),
+                                   (2049, 2056, 288), (2176, 3840, 1024), (4096, 2048, 544),      # 128 x 128; 512 of them
+                                   (4096, 2056, 544), (2816, 3080, 32), (2816, 3072, 288), (4352, 4104, 992)])   # 256 x 256
+def test_products(P, Q, K):
+    from paper_2501_17116_amd import binding as b
+    g = torch.Generator().manual_seed(P + Q + K)
+    L = torch.randint(0, 256, (P, K // 2), generator=g, dtype=torch.uint8)
+    R = torch.randint(0, 256, (Q, K // 2), generator=g, dtype=torch.uint8)
+    raw = b.fp4_gemm(L.cuda(), None, R.cuda(), None)
+    exact = _values(L) @ _values(R).t()   # exact in fp32: no partial sum needs more than 24 bits
+    assert torch.equal(raw.cpu(), exact)
+    # powers of two: reciprocals and products without rounding, whatever the order
+    gl, gr = torch.exp2(torch.randint(-3, 4, (P,), generator=g).float()), torch.exp2(torch.randint(-3, 4, (Q,), generator=g).float())
+    addend = torch.randn(P, Q, generator=g)
+    scaled = exact / gl[:, None] / gr
+    assert torch.equal(b.fp4_gemm(L.cuda(), gl.cuda(), R.cuda(), gr.cuda(), out_dtype=torch.bfloat16).cpu(), scaled.bfloat16())
+    assert torch.equal(b.fp4_gemm(L.cuda(), gl.cuda(), R.cuda(), gr.cuda(), addend=addend.cuda()).cpu(), scaled + addend)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,K,N", [(96, 1280, 1288), (1056, 1376, 2080), (2080, 1056, 2056), (2048, 2048, 2048), (1056, 3104, 3080)])
+def test_weight_gradient_with_the_factor(M, K, N, dtype):
+    """Against its parts called one by one (the factor as a pass of its own): the same product to the last bit, the factor one
+    rounding of fp32 in either."""
+    from paper_2501_17116_amd import binding as b
+    torch.manual_seed(M + N)
+    A, W, dY = (t.to(dtype) for t in (torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda") * 0.02, torch.randn(M, N, device="cuda")))
+    _, ctx = b.fp4_linear_fwd(A, W, 1.0)
+    got = b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 5.0, 3.0)
+    qA, gA = b.fp4_quantize(A, b.FP4_AXIS_COL)
+    qY, gY = b.fp4_quantize(dY, b.FP4_AXIS_COL)
+    ref = b.fp4_dge_apply(b.fp4_gemm(qA, gA, qY, gY), W, ctx.gamma_W, 5.0, 3.0)
+    assert torch.all((got - ref).abs() <= 2.0 ** -22 * ref.abs())
