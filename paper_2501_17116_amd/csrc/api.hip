@@ -46,6 +46,9 @@ int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols);
 size_t fp4_select_scratch_bytes();
 int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k,
                           float* thresholds, void* scratch, unsigned long long* total, hipStream_t s);
+int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
+                                     void* scratch, unsigned long long* total, void* rows_scratch, int64_t rows_scratch_words,
+                                     int32_t* row_cnt, hipStream_t s);
 int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s);
 int fp4_launch_csr_gather(const int32_t* tmp_col, const float* tmp_val, int64_t rows, int64_t capacity,
                           const int64_t* row_ptr, int32_t* col_idx, float* val, hipStream_t s);
@@ -122,6 +125,16 @@ OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity, int64_t later = 0,
   t.row_cnt = c.take<int32_t>((size_t)rows);
   t.total = c.take<unsigned long long>(1);
   return t;
+}
+
+// The per-tensor thresholds, then how many elements of each row they clamp; the entries' temporaries are free until then.
+int thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds, const OccTemps& t,
+                          hipStream_t s) {
+  int rc = fp4_launch_thresholds_and_counts(x, bf16, rows, cols, ld, k, thresholds, t.select, t.total, t.tmp_col,
+                                            provisioned_entries(rows, cols), t.row_cnt, s);
+  if (rc != 1) return rc;
+  rc = fp4_launch_thresholds(x, bf16, rows, cols, ld, k, thresholds, t.select, t.total, s);
+  return rc ? rc : fp4_launch_occ_count(x, bf16, rows, cols, ld, thresholds, t.row_cnt, s);
 }
 
 struct FwdWs {
@@ -305,9 +318,7 @@ extern "C" int occ_clamp_residual(const void* x, fp4_dtype dt, int64_t rows, int
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
   OccTemps t = carve_occ(c, rows, provisioned_entries(rows, cols));
   capacity = std::min(capacity, provisioned_entries(rows, cols));  // never beyond the temporaries
-  int rc = fp4_launch_thresholds(x, dt == FP4_BF16, rows, cols, ld, k, thresholds, t.select, t.total, s);
-  if (rc) return rc;
-  rc = fp4_launch_occ_count(x, dt == FP4_BF16, rows, cols, ld, thresholds, t.row_cnt, s);
+  int rc = thresholds_and_counts(x, dt == FP4_BF16, rows, cols, ld, k, thresholds, t, s);
   if (rc) return rc;
   rc = fp4_launch_scan_rows(t.row_cnt, rows, row_ptr, nnz, s);
   if (rc) return rc;
@@ -386,9 +397,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
       rc = occ_token_chain(A, bf16, M, K, K, k_row, saved->thresholds, w.qA, w.gA, nullptr, saved->row_ptr,
                            saved->col_idx, saved->val, cap, saved->nnz, w.occ, s);
     } else {
-      rc = fp4_launch_thresholds(A, bf16, M, K, K, k, saved->thresholds, w.occ.select, w.occ.total, s);
-      if (rc) return rc;
-      rc = fp4_launch_occ_count(A, bf16, M, K, K, saved->thresholds, w.occ.row_cnt, s);
+      rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s);
       if (rc) return rc;
       rc = fp4_launch_scan_rows(w.occ.row_cnt, M, saved->row_ptr, saved->nnz, s);
       if (rc) return rc;
@@ -500,8 +509,7 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
     if (rc) return rc;
   } else if (occ) {
     const int64_t cap = std::min(saved->capacity, provisioned_entries(M, K));
-    rc = fp4_launch_thresholds(A, bf16, M, K, K, k, saved->thresholds, w.occ.select, w.occ.total, s);
-    if (!rc) rc = fp4_launch_occ_count(A, bf16, M, K, K, saved->thresholds, w.occ.row_cnt, s);
+    rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s);
     if (!rc) rc = fp4_launch_scan_rows(w.occ.row_cnt, M, saved->row_ptr, saved->nnz, s);
     if (rc) return rc;
     rc = fp4_launch_occ_rows(A, bf16, M, K, K, saved->thresholds, w.qA, w.gA, nullptr, saved->col_idx, saved->val,

@@ -31,6 +31,8 @@ struct SelState {
   unsigned long long rank[2];  // remaining 0-based rank of the lo / hi order statistic
   uint32_t prefix[2];          // key bits fixed so far (right-aligned)
   uint32_t arrived[SEL_PASSES];   // workgroups done with a pass
+  // windows (below): thresholds and row counts came out of one pass; a NaN was met; the thresholds' bins
+  uint32_t done, nan, bin[2];
 };
 
 __global__ void sel_init_kernel(SelState* st, unsigned long long* hist, unsigned long long k,
@@ -43,6 +45,7 @@ __global__ void sel_init_kernel(SelState* st, unsigned long long* hist, unsigned
     st->prefix[0] = st->prefix[1] = 0;
     if (total) *total = 0;
     for (int a = 0; a < SEL_PASSES; ++a) st->arrived[a] = 0;
+    st->done = st->nan = 0;
   }
 }
 
@@ -129,6 +132,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, in
                                                        int64_t ld, int shift, int bits, int pass, int last, int key_bits,
                                                        SelState* st, unsigned long long* hist, float* thresholds) {
   constexpr bool first = FIRST;
+  if (st->done) return;
   __shared__ uint32_t h[8 * SEL_BINS];   // first pass: 8 replicas; later: 4 replicas x 2 targets
   for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
   __syncthreads();
@@ -201,7 +205,174 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, in
 
 __global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, unsigned long long* hist, int bits, int first, int last,
                                                                int key_bits, float* thresholds) {
+  if (st->done) return;
   sel_pick(st, hist, bits, first, last, key_bits, thresholds);
+}
+
+// ---- Large bf16 tensors: thresholds and the rows' outlier counts out of one pass ------------------------------------------
+// A sample says where the thresholds are, to within a few of the 2048 leading 11-bit digits; the pass over all elements then
+// needs bins only for the keys around them (three digits, 96 keys a threshold), counts what lies outside, and keeps every
+// row's bins: with the thresholds known, a row's outliers are a sum over those.  Where a threshold turns out not to lie in
+// its window (or the windows meet, a NaN is about, a threshold is a zero, whose two keys are one value), `done` stays 0 and
+// the passes of the general path, launched behind, do their work; otherwise they leave at once.
+// Bound by the one read and, about as long, by vector instructions (nine an element).  16384 x 11008, in us: init 4.5, sample 6.4,
+// picks 5.0 + 5.9, the pass 96.9, the general path's two launches 9, rows 4.8, together 133; digit passes, picks and the count of
+// the rows after them 249.  16384 x 4096: 74 against 107.  Below 2^25 elements the launches cost what the pass saves (8192 x
+// 2048: digit passes, picks and count 43, of which this would leave 40).
+constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STRIDE = 200;   // bins; a wave's table; a row's in memory
+constexpr int SAMPLE_BLOCKS = 128, SAMPLE_VECS = 2 * SEL_THREADS;   // 16-byte vectors a workgroup
+
+__global__ __launch_bounds__(SEL_THREADS) void sel_sample_kernel(const u32x4* x, int64_t nvec, unsigned long long* hist) {
+  __shared__ uint32_t h[8 * SEL_BINS];
+  for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
+  __syncthreads();
+  uint32_t* const hrep = &h[(threadIdx.x & 7) * SEL_BINS];
+  const int64_t at = (int64_t)blockIdx.x * (nvec - SAMPLE_VECS) / (SAMPLE_BLOCKS - 1) + threadIdx.x;
+  const u32x4 r[2] = {x[at], x[at + SEL_THREADS]};
+#pragma unroll
+  for (int v = 0; v < 2; ++v)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      atomicAdd(&hrep[key_of<BF16>(r[v][e] & 0xffffu) >> 5], 1u);
+      atomicAdd(&hrep[key_of<BF16>(r[v][e] >> 16) >> 5], 1u);
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += h[q * SEL_BINS + i];
+    if (v) atomicAdd(&hist[i], (unsigned long long)v);
+  }
+}
+
+// First keys of the windows, from the digits that the sample's order statistics have.
+FP4_D uint32_t win_first(const SelState* st, int s) { return (uint32_t)min(max((int)st->prefix[s] - 1, 0), SEL_BINS - 3) * 32u; }
+
+// A wave per row.  Bin 0: below the lower window, 1 .. 96 in it, 97 between the two (not kept), 98 .. 193 in the upper one,
+// 194 above.
+__global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int64_t rows, int64_t cols, SelState* st, unsigned long long* hist,
+                                                         uint16_t* row_bins) {
+  __shared__ uint32_t tab[16][WIN_LDS];
+  __shared__ uint32_t total[WIN_LDS];
+  const uint32_t w0 = win_first(st, 0), w1 = win_first(st, 1);
+  if (w0 + WIN_KEYS > w1) return;   // pick_windows sees the same
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t* const t = tab[wave];
+#pragma unroll
+  for (int j = 0; j < WIN_LDS / 64; ++j) t[lane + 64 * j] = 0;
+  if (threadIdx.x < WIN_LDS) total[threadIdx.x] = 0;
+  __syncthreads();
+  typedef short s16x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  uint32_t sum[WIN_LDS / 64] = {};
+  u16x2 top = {0, 0};   // largest magnitude
+  const uint16_t lo1 = (uint16_t)max((int)w0 - 1, 0), hi1 = (uint16_t)(w1 - 1), most = WIN_KEYS + 1;
+  const uint16_t none = w0 == 0 ? 1 : 0;   // no key lies below a window that begins at 0
+  const u16x2 lo = {lo1, lo1}, hi = {hi1, hi1}, lim_lo = {(uint16_t)(most - none), (uint16_t)(most - none)}, lim_hi = {most, most}, one = {none, none};
+  auto visit = [&](uint32_t bin) {
+    if (bin != WIN_KEYS + 1) atomicAdd(&t[bin], 1u);
+  };
+  auto visit_vec = [&](const u32x4& r) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {   // two elements at a time: keys as key_of, then how far they are into either window
+      const uint32_t p = r[e];
+      const s16x2 sign = __builtin_bit_cast(s16x2, p) >> (short)15;
+      const u16x2 key = __builtin_bit_cast(u16x2, p ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u));
+      top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, p & 0x7fff7fffu));
+      const u16x2 bin = __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, lo), lim_lo) + one +
+                        __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, hi), lim_hi);
+      visit(bin.x);
+      visit(bin.y);
+    }
+  };
+  const int nvec = (int)(cols / 8);
+  for (int64_t row = (int64_t)blockIdx.x * 16 + wave; row < rows; row += (int64_t)gridDim.x * 16) {
+    const u32x4* const xr = reinterpret_cast<const u32x4*>(x + row * cols);
+    int i = lane;
+    for (; i + 3 * 64 < nvec; i += 4 * 64) {
+      const u32x4 r0 = xr[i], r1 = xr[i + 64], r2 = xr[i + 128], r3 = xr[i + 192];
+      visit_vec(r0); visit_vec(r1); visit_vec(r2); visit_vec(r3);
+    }
+    for (; i < nvec; i += 64) visit_vec(xr[i]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the table is this wave's own
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < WIN_LDS / 64; ++j) {
+      const uint32_t v = t[lane + 64 * j];
+      t[lane + 64 * j] = 0;
+      sum[j] += v;
+      if (lane + 64 * j < WIN_BINS) row_bins[row * WIN_STRIDE + lane + 64 * j] = (uint16_t)v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int j = 0; j < WIN_LDS / 64; ++j)
+    if (sum[j]) atomicAdd(&total[lane + 64 * j], sum[j]);
+  if (max(top.x, top.y) > 0x7f80) st->nan = 1;
+  __syncthreads();
+  if (threadIdx.x < WIN_BINS && total[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)total[threadIdx.x]);
+}
+
+// The thresholds from the bins' totals, or the state that the general path starts from.
+__global__ __launch_bounds__(256) void win_pick_kernel(SelState* st, unsigned long long* hist, unsigned long long k, unsigned long long n,
+                                                       float* thresholds) {
+  __shared__ unsigned long long h[WIN_BINS];
+  __shared__ uint32_t key[2], bin[2];
+  const int tid = threadIdx.x;
+  const uint32_t w0 = win_first(st, 0), w1 = win_first(st, 1);
+  if (tid < WIN_BINS) h[tid] = hist[tid];
+  if (tid < 2) bin[tid] = 0;
+  __syncthreads();
+  // thread 1 + j looks at the lower window's bin 1 + j and the upper one's 98 + j
+  if (tid >= 1 && tid <= WIN_KEYS && w0 + WIN_KEYS <= w1) {
+    unsigned long long below = 0, above = 0;
+    for (int b = 0; b < tid; ++b) below += h[b];
+    if (below <= k && k < below + h[tid]) { bin[0] = tid; key[0] = w0 + tid - 1; }
+    const int u = tid + WIN_KEYS + 1;
+    for (int b = u + 1; b < WIN_BINS; ++b) above += h[b];
+    if (above <= k && k < above + h[u]) { bin[1] = u; key[1] = w1 + tid - 1; }   // the (k + 1)-th from the top
+  }
+  __syncthreads();
+  if (tid == 0) {
+    // a zero's keys are 0x7fff and 0x8000
+    const bool ok = bin[0] && bin[1] && !st->nan && key[0] != 0x7fffu && key[0] != 0x8000u && key[1] != 0x7fffu && key[1] != 0x8000u;
+    if (ok)
+      for (int s = 0; s < 2; ++s) thresholds[s] = u2f(((key[s] & 0x8000u) ? (key[s] & 0x7fffu) : (~key[s] & 0xffffu)) << 16);
+    st->done = ok;
+    st->bin[0] = bin[0];
+    st->bin[1] = bin[1];
+    st->rank[0] = k;
+    st->rank[1] = n - 1 - k;
+    st->prefix[0] = st->prefix[1] = 0;
+  }
+  if (tid < WIN_BINS) hist[tid] = 0;
+}
+
+// Outliers of each row: from its bins, or, where the windows were missed, from its elements.  A wave per row.
+__global__ __launch_bounds__(256) void win_rows_kernel(const uint16_t* x, int64_t rows, int64_t cols, const SelState* st, const uint16_t* row_bins,
+                                                       const float* thr, int32_t* row_cnt) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  int cnt = 0;
+  if (st->done) {
+    const int b0 = (int)st->bin[0], b1 = (int)st->bin[1];
+#pragma unroll
+    for (int j = 0; j < WIN_LDS / 64; ++j) {
+      const int b = lane + 64 * j;
+      if (b < b0 || (b > b1 && b < WIN_BINS)) cnt += row_bins[row * WIN_STRIDE + b];
+    }
+  } else {
+    const float lo = thr[0], hi = thr[1];
+    for (int64_t i = lane; i < cols; i += 64) {
+      const float v = u2f((uint32_t)x[row * cols + i] << 16);
+      cnt += ((v < lo) | (v > hi)) ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+  if (lane == 0) row_cnt[row] = cnt;
 }
 
 // ---- CSR finalisation ---------------------------------------------------------------------
@@ -282,16 +453,11 @@ size_t fp4_select_scratch_bytes() {
   return align_up(sizeof(SelState), 256) + align_up(2 * SEL_BINS * sizeof(unsigned long long), 256);
 }
 
-// Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1].
-// Also zeroes *total (the residual entry counter) when given.
-int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k,
-                          float* thresholds, void* scratch, unsigned long long* total, hipStream_t s) {
-  SelState* st = reinterpret_cast<SelState*>(scratch);
-  unsigned long long* hist =
-      reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
+namespace {
+// The digit passes, from the state that sel_init_kernel (or win_pick_kernel) left.
+void launch_digits(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, float* thresholds, SelState* st, unsigned long long* hist,
+                   bool seldom, hipStream_t s) {
   const int64_t n = rows * cols;
-  hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist,
-                     (unsigned long long)k, (unsigned long long)n, total);
   const int key_bits = bf16 ? 16 : 32;
   int digits[3];
   int nd;
@@ -300,7 +466,7 @@ int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, i
   int shift = key_bits;
   const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
-  const bool pick_here = grid <= SEL_PICK_HERE;
+  const bool pick_here = seldom || grid <= SEL_PICK_HERE;   // launches that mostly leave at once: as few as there can be
   for (int p = 0; p < nd; ++p) {
     shift -= digits[p];
     auto launch = [&](auto dt, auto first, auto pick) {
@@ -317,6 +483,48 @@ int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, i
       hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(SEL_THREADS), 0, s, st, hist, digits[p], p == 0, p == nd - 1, key_bits,
                          thresholds);
   }
+}
+}  // namespace
+
+// Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1].
+// Also zeroes *total (the residual entry counter) when given.
+int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k,
+                          float* thresholds, void* scratch, unsigned long long* total, hipStream_t s) {
+  SelState* st = reinterpret_cast<SelState*>(scratch);
+  unsigned long long* hist =
+      reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
+  const int64_t n = rows * cols;
+  hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist,
+                     (unsigned long long)k, (unsigned long long)n, total);
+  launch_digits(x, bf16, rows, cols, ld, thresholds, st, hist, false, s);
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}
+
+// Thresholds and outlier counts of rows in one pass; 1 where that is not the better way (the caller then does one after the other).
+// rows_scratch: words that are free until the rows' entries are emitted.
+int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
+                                     void* scratch, unsigned long long* total, void* rows_scratch, int64_t rows_scratch_words,
+                                     int32_t* row_cnt, hipStream_t s) {
+  const int64_t n = rows * cols;
+  if (!bf16 || ld != cols || cols % 8 != 0 || cols > 65535 || n < ((int64_t)1 << 25) || n >= ((int64_t)1 << 32) ||
+      rows * WIN_STRIDE > 2 * rows_scratch_words)
+    return 1;
+  SelState* st = reinterpret_cast<SelState*>(scratch);
+  unsigned long long* hist =
+      reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
+  // the sample's ranks first
+  const int64_t ns = (int64_t)SAMPLE_BLOCKS * SAMPLE_VECS * 8;
+  const unsigned long long ks = (unsigned long long)((double)k / (double)n * (double)ns);
+  hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist, ks, (unsigned long long)ns, total);
+  hipLaunchKernelGGL(sel_sample_kernel, dim3(SAMPLE_BLOCKS), dim3(SEL_THREADS), 0, s, reinterpret_cast<const u32x4*>(x), n / 8, hist);
+  hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(SEL_THREADS), 0, s, st, hist, 11, 1, 0, 16, thresholds);
+  uint16_t* const bins = reinterpret_cast<uint16_t*>(rows_scratch);
+  const uint16_t* const xp = reinterpret_cast<const uint16_t*>(x);
+  hipLaunchKernelGGL(win_count_kernel, dim3((unsigned)std::min<int64_t>((rows + 15) / 16, 512)), dim3(1024), 0, s, xp, rows, cols, st, hist, bins);
+  hipLaunchKernelGGL(win_pick_kernel, dim3(1), dim3(256), 0, s, st, hist, (unsigned long long)k, (unsigned long long)n, thresholds);
+  launch_digits(x, bf16, rows, cols, ld, thresholds, st, hist, true, s);
+  hipLaunchKernelGGL(win_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, xp, rows, cols, st, bins, thresholds, row_cnt);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
