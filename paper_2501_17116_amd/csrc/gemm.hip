@@ -56,6 +56,7 @@ struct GemmShape {
   int64_t P, Q, Kb, ldo, ldw;
   float dge_k, dge_cap;
   int tiles_p, tiles_q;
+  int stagger;   // how much later than the one before each quarter of the workgroups begins, in 512 cycles
 };
 
 template <class F, int... I>
@@ -108,6 +109,7 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
   const int run_end = min(total, (xcd + 1) * per_xcd);
   int lid = xcd * per_xcd + wg_in_xcd;
   if (lid >= run_end) return;
+  for (int i = g.stagger * ((wg_in_xcd >> 3) & 3); i > 0; --i) __builtin_amdgcn_s_sleep(8);
 
   // Per-tile state.  The scalars (tile origin, base pointers, buffer descriptors) of the tile whose
   // operands are being fetched; they move on to the next tile as soon as this tile's main loop is
@@ -982,6 +984,13 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   // rows too long for the offsets of the larger tiles' descriptors
   const bool small = few || g.Kb * (ragged ? BM : 1) > (int64_t)OUT_OF_RANGE;
   const bool mid = mid_tiles <= (dge ? (w_bf16 ? 1 : 3) : 2) * (int64_t)n_cu && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE;
+  // Workgroups that start together come to their epilogues together: memory is idle while all multiply and the bound while all
+  // add, convert and store.  Four quarters 3.4 us apart overlap the two where an epilogue moves much (addend, fp32
+  // output) and a workgroup has enough tiles to make up for it, or those that have one less can be the late ones
+  // (16384 x 12288 x 4096 with addend 603 -> 561 us, 16384 x 4096 x 2048 151 -> 137, 5120 x 13824 x 4096 fp32 258 -> 246, 4096 x
+  // 11008 x 4096 131 -> 127; three full rounds 410 -> 415, bf16 without addend 353 -> 359).
+  const int wgs = (int)grid.x;
+  g.stagger = (addend || !out_bf16) && (total > 3 * wgs || (total > 2 * wgs && 8 * (int64_t)total <= 23 * (int64_t)wgs)) ? 15 : 0;
   GemmShape gs = g, gm = g;
   gs.tiles_p = (int)((P + 63) / 64);
   gm.tiles_p = (int)((P + MG_T - 1) / MG_T);
