@@ -340,6 +340,9 @@ def gemm_kernels(cfg, layers, torch):
                 names.add("fp4_gemm_mid_kernel")
             else:
                 names.add("fp4_gemm_nt_kernel")
+                big = -(-P // 256) * -(-Q // 256)
+                if big > cus and 4 * (big % cus) <= cus and big % cus:   # the last round in quarters
+                    names.add("fp4_gemm_mid_kernel")
     return " + ".join(sorted(names))
 
 

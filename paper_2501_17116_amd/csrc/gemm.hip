@@ -56,8 +56,19 @@ struct GemmShape {
   int64_t P, Q, Kb, ldo, ldw;
   float dge_k, dge_cap;
   int tiles_p, tiles_q;
+  int first, count;   // 256 x 256 tiles of this launch, in the order of tile_at
   int stagger;   // how much later than the one before each quarter of the workgroups begins, in 512 cycles
 };
+
+// Tile id of the order in which they are taken: eight tile-rows side by side.
+FP4_D void tile_at(const GemmShape& g, int id, int& tp, int& tq) {
+  const int in_group = GROUP_P * g.tiles_q;
+  const int group = id / in_group;
+  const int first_p = group * GROUP_P;
+  const int gsz = min(g.tiles_p - first_p, GROUP_P);
+  tp = first_p + (id % in_group) % gsz;
+  tq = (id % in_group) / gsz;
+}
 
 template <class F, int... I>
 FP4_D void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -102,7 +113,7 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
   // Persistent workgroups: the grid is at most one workgroup per CU and each walks a strided
   // share of its XCD's run of tiles, so a tile's stores drain while the next tile computes and
   // no workgroup relaunch sits between tiles.
-  const int total = g.tiles_p * g.tiles_q;
+  const int total = g.count;
   const int per_xcd = (total + 7) / 8;
   const int xcd = (int)(blockIdx.x % 8);
   const int wg_in_xcd = (int)(blockIdx.x / 8), wgs_per_xcd = (int)(gridDim.x / 8);
@@ -130,12 +141,8 @@ __global__ __launch_bounds__(NTHREADS) void fp4_gemm_nt_kernel(
     return (const uint8_t*)(((uint64_t)hi << 32) | lo);
   };
   auto tile_scalars = [&](int id) {
-    const int in_group = GROUP_P * g.tiles_q;
-    const int group = id / in_group;
-    const int first_p = group * GROUP_P;
-    const int gsz = min(g.tiles_p - first_p, GROUP_P);
-    const int tp = first_p + (id % in_group) % gsz;
-    const int tq = (id % in_group) / gsz;
+    int tp, tq;
+    tile_at(g, id, tp, tq);
     P0 = (int64_t)tp * BM;
     Q0 = (int64_t)tq * BN;
     tileL = uniform_ptr(Lp + P0 * g.Kb);
@@ -821,13 +828,20 @@ __global__ __launch_bounds__(256) void fp4_gemm_mid_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
   const int wp = (wave & 1) * 64, wq = (wave >> 1) * 64;
-  // each XCD a contiguous run of tiles, eight tile-rows side by side
-  const int total = g.tiles_p * g.tiles_q, per_xcd = (total + 7) / 8;
+  // each XCD a contiguous run of tiles: of the whole output, or (first > 0) the quarters of the 256 x 256 tiles from `first` on
+  const int total = g.count, per_xcd = (total + 7) / 8;
   const int id = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
-  const int in_group = GROUP_P * g.tiles_q, first_p = id / in_group * GROUP_P;
-  const int gsz = min(g.tiles_p - first_p, GROUP_P);
-  const int64_t P0 = (int64_t)(first_p + id % in_group % gsz) * T, Q0 = (int64_t)(id % in_group / gsz) * T;
+  int tp, tq;
+  if (g.first > 0) {
+    tile_at(g, g.first + (id >> 2), tp, tq);
+    tp = 2 * tp + (id & 1);
+    tq = 2 * tq + (id >> 1 & 1);
+  } else {
+    tile_at(g, id, tp, tq);
+  }
+  const int64_t P0 = (int64_t)tp * T, Q0 = (int64_t)tq * T;
+  if (P0 >= g.P || Q0 >= g.Q) return;   // a quarter behind the edge
   const __amdgpu_buffer_rsrc_t rsrcL = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(Lp) + P0 * g.Kb, 0, (int)(uint32_t)(min(g.P - P0, (int64_t)T) * g.Kb), 0x00020000);
   const __amdgpu_buffer_rsrc_t rsrcR = __builtin_amdgcn_make_buffer_rsrc(
@@ -964,9 +978,8 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   g.tiles_p = (int)((P + BM - 1) / BM);
   g.tiles_q = (int)((Q + BN - 1) / BN);
   const bool dge = W != nullptr && dge_k > 0.0f;
-  const int total = g.tiles_p * g.tiles_q;
+  int total = g.tiles_p * g.tiles_q;
   const int n_cu = compute_units_of_current_device();
-  const dim3 grid(std::min(((total + 7) / 8) * 8, (n_cu / 8) * 8)), block(NTHREADS);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
   const bool ragged = (g.Kb % BKB) != 0;
   // What bounds a call with few tiles is one tile's chain of steps, so the smaller tile wins while there is no more than a
@@ -984,31 +997,49 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   // rows too long for the offsets of the larger tiles' descriptors
   const bool small = few || g.Kb * (ragged ? BM : 1) > (int64_t)OUT_OF_RANGE;
   const bool mid = mid_tiles <= (dge ? (w_bf16 ? 1 : 3) : 2) * (int64_t)n_cu && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE;
+  // A last round of 256 x 256 tiles that no more than a quarter of the CUs have is cut into 128 x 128 ones, which go round the
+  // chip once: 320 tiles, 13824 codes 166 -> 143 us (with fp32 addend 183 -> 160), 2048 codes 41 -> 38 (59 -> 54); 289, 512
+  // codes 25.5 -> 23.6; 1080, 4096 codes 162 -> 153.  Two rounds of them take as long as the one they replace, or longer (352
+  // tiles, 512 / 4096 / 13824 codes 26 / 62 / 166 -> 29 / 66 / 173).
+  const int wgs = (n_cu / 8) * 8;
+  int rest = 0;
+  if (!small && !mid && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE && total > wgs && 4 * (total % wgs) <= wgs) rest = total % wgs;
+  total -= rest;
+  g.first = 0;
+  g.count = total;
+  const dim3 grid(std::min((total + 7) / 8 * 8, wgs)), block(NTHREADS);
   // Workgroups that start together come to their epilogues together: memory is idle while all multiply and the bound while all
   // add, convert and store.  Four quarters 3.4 us apart overlap the two where an epilogue moves much (addend, fp32
   // output) and a workgroup has enough tiles to make up for it, or those that have one less can be the late ones
   // (16384 x 12288 x 4096 with addend 603 -> 561 us, 16384 x 4096 x 2048 151 -> 137, 5120 x 13824 x 4096 fp32 258 -> 246, 4096 x
   // 11008 x 4096 131 -> 127; three full rounds 410 -> 415, bf16 without addend 353 -> 359).
-  const int wgs = (int)grid.x;
   g.stagger = (addend || !out_bf16) && (total > 3 * wgs || (total > 2 * wgs && 8 * (int64_t)total <= 23 * (int64_t)wgs)) ? 15 : 0;
   GemmShape gs = g, gm = g;
   gs.tiles_p = (int)((P + 63) / 64);
   gm.tiles_p = (int)((P + MG_T - 1) / MG_T);
   gm.tiles_q = (int)((Q + MG_T - 1) / MG_T);
+  gm.count = gm.tiles_p * gm.tiles_q;
+  if (rest) {   // the order of the 256 x 256 tiles
+    gm = g;
+    gm.first = total;
+    gm.count = 4 * rest;
+  }
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
     if (small)                                                                                            \
       hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)small_tiles), dim3(256), 0, stream, L, Rt, gl, gr, \
                          addend, out, W, gamma_w, gs);                                                    \
     else if (mid)                                                                                         \
-      hipLaunchKernelGGL((fp4_gemm_mid_kernel<OB, DG, WB>), dim3((unsigned)((gm.tiles_p * gm.tiles_q + 7) / 8 * 8)), dim3(256), 0, \
-                         stream, L, Rt, gl, gr, addend, out, W, gamma_w, gm);                             \
+      ;                                                                                                   \
     else if (ragged)                                                                                      \
       hipLaunchKernelGGL((fp4_gemm_nt_kernel<OB, DG, WB, true>), grid, block, 0, stream, L, Rt, gl, gr,   \
                          addend, out, W, gamma_w, g);                                                     \
     else                                                                                                  \
       hipLaunchKernelGGL((fp4_gemm_nt_kernel<OB, DG, WB, false>), grid, block, 0, stream, L, Rt, gl, gr,  \
                          addend, out, W, gamma_w, g);                                                     \
+    if (!small && (mid || rest))                                                                          \
+      hipLaunchKernelGGL((fp4_gemm_mid_kernel<OB, DG, WB>), dim3((unsigned)((gm.count + 7) / 8 * 8)), dim3(256), 0, stream, L, Rt, \
+                         gl, gr, addend, out, W, gamma_w, gm);                                            \
   } while (0)
   if (dge) {
     if (w_bf16) FP4_GEMM_LAUNCH(false, true, true);

@@ -15,25 +15,26 @@ def _values(codes):
 
 @pytest.mark.parametrize("P,Q,K", [(1, 8, 1056), (127, 136, 1280), (128, 128, 1312), (129, 1000, 2048), (2048, 2048, 32),
                                    (2049, 2056, 288), (2176, 3840, 1024), (4096, 2048, 544),      # 128 x 128; 512 of them
-                                   (4096, 2056, 544), (2816, 3080, 32), (2816, 3072, 288), (4352, 4104, 992)])   # 256 x 256
+                                   (4096, 2056, 544), (2816, 3080, 32), (2816, 3072, 288), (4352, 4096, 992),   # 256 x 256
+                                   (4104, 4104, 32), (4224, 4232, 544), (4352, 4352, 1024), (5120, 4096, 160)])   # and a last round in quarters
 def test_products(P, Q, K):
     from paper_2501_17116_amd import binding as b
     g = torch.Generator().manual_seed(P + Q + K)
     L = torch.randint(0, 256, (P, K // 2), generator=g, dtype=torch.uint8)
     R = torch.randint(0, 256, (Q, K // 2), generator=g, dtype=torch.uint8)
-    raw = b.fp4_gemm(L.cuda(), None, R.cuda(), None)
-    exact = _values(L) @ _values(R).t()   # exact in fp32: no partial sum needs more than 24 bits
-    assert torch.equal(raw.cpu(), exact)
+    exact = _values(L).cuda() @ _values(R).cuda().t()   # exact in fp32: no partial sum needs more than 24 bits
+    L, R = L.cuda(), R.cuda()
+    assert torch.equal(b.fp4_gemm(L, None, R, None), exact)
     # powers of two: reciprocals and products without rounding, whatever the order
-    gl, gr = torch.exp2(torch.randint(-3, 4, (P,), generator=g).float()), torch.exp2(torch.randint(-3, 4, (Q,), generator=g).float())
-    addend = torch.randn(P, Q, generator=g)
+    gl, gr = (torch.exp2(torch.randint(-3, 4, (n,), generator=g).float()).cuda() for n in (P, Q))
+    addend = torch.randn(P, Q, generator=g).cuda()
     scaled = exact / gl[:, None] / gr
-    assert torch.equal(b.fp4_gemm(L.cuda(), gl.cuda(), R.cuda(), gr.cuda(), out_dtype=torch.bfloat16).cpu(), scaled.bfloat16())
-    assert torch.equal(b.fp4_gemm(L.cuda(), gl.cuda(), R.cuda(), gr.cuda(), addend=addend.cuda()).cpu(), scaled + addend)
+    assert torch.equal(b.fp4_gemm(L, gl, R, gr, out_dtype=torch.bfloat16), scaled.bfloat16())
+    assert torch.equal(b.fp4_gemm(L, gl, R, gr, addend=addend), scaled + addend)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("M,K,N", [(96, 1280, 1288), (1056, 1376, 2080), (2080, 1056, 2056), (2048, 2048, 2048), (1056, 3104, 3080)])
+@pytest.mark.parametrize("M,K,N", [(96, 1280, 1288), (1056, 1376, 2080), (2080, 1056, 2056), (2048, 2048, 2048), (1056, 3104, 3080), (544, 4128, 4112)])
 def test_weight_gradient_with_the_factor(M, K, N, dtype):
     """Against its parts called one by one (the factor as a pass of its own): the same product to the last bit, the factor one
     rounding of fp32 in either."""
