@@ -31,15 +31,13 @@ struct BF16 {};
 struct F32 {};
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int SP_ROWS = 1024;   // output rows per workgroup = threads
+constexpr int SP_ROWS = 1024;   // output rows per workgroup = threads, where there are rows enough
 constexpr int SP_COLS = 64;     // output columns per workgroup
 constexpr int SP_KS = 512;      // rows of D per LDS slab
-constexpr int SP_RIF = 4;       // LDS chunk reads a lane has in flight before the FMAs that use them:
-                                // more do not fit the 128 VGPRs of a 1024-thread workgroup, and a smaller
-                                // workgroup with more registers loses more through occupancy
-constexpr int SP_RPP = SP_ROWS / 8;   // rows of D staged per pass (8 threads per row)
+// LDS chunk reads a lane has in flight before the FMAs that use them: more do not fit the 128 VGPRs of a 1024-thread
+// workgroup, and on a full chip a smaller workgroup with more registers loses more through occupancy
+constexpr int sp_rif(int rows) { return rows >= 1024 ? 4 : 8; }
 constexpr int SP_WPR = SP_KS / 64;    // waves whose 64 x 64 tiles fit the slab at once
-static_assert(SP_KS % SP_RPP == 0, "whole staging passes");
 constexpr int SP_LD = SP_COLS;   // LDS row (floats), unpadded: see the lane swizzle in the kernel
 constexpr int SP_XM = 15;        // lane bits that rotate the order in which a thread reads a D row
 
@@ -73,15 +71,17 @@ FP4_D void load8g(const void* base, int64_t off, int valid, float (&v)[8]) {
   }
 }
 
-// A block of SP_ROWS rows times the 64 columns of D from n0 on.  mine: whether the thread's row is to be written.
-template <class DT, bool EARLY>
+// A block of ROWS rows times the 64 columns of D from n0 on.  mine: whether the thread's row is to be written.
+template <class DT, bool EARLY, int ROWS = SP_ROWS>
 FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                            const float* __restrict__ val, int64_t capacity, int64_t P, int64_t Q, const void* __restrict__ D,
                            int64_t N, float* __restrict__ R, int64_t block, int tid, bool mine, int64_t n0, float* slab, int* s_skip) {
-  const int64_t row = block * SP_ROWS + tid;
+  constexpr int RPP = ROWS / 8, RIF = sp_rif(ROWS);   // rows of D staged per pass (8 threads per row)
+  static_assert(SP_KS % RPP == 0, "whole staging passes");
+  const int64_t row = block * ROWS + tid;
   // Entry positions are kept as 32-bit offsets from the workgroup's first entry (a workgroup's
   // rows hold fewer than 2^31 entries: the launcher bounds Q); the base stays in scalar registers.
-  const int64_t ebase = row_ptr[min(block * SP_ROWS, P)];
+  const int64_t ebase = row_ptr[min(block * ROWS, P)];
   const int64_t long_limit = spmm_long_limit(row_ptr, P, Q, capacity);
   uint32_t cur = 0, end = 0;
   if (mine) {
@@ -97,7 +97,7 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
 #pragma unroll
   for (int j = 0; j < SP_COLS; ++j) acc[j] = 0.0f;
 
-  // staging map: 8 threads cover the 64 columns of a D row, 128 rows per pass, 4 passes
+  // staging map: 8 threads cover the 64 columns of a D row, RPP rows per pass
   const int s_unit = tid & 7, s_row = tid >> 3;
   const int64_t s_col = n0 + s_unit * 8;
   const int s_valid = s_col < N ? (int)min((int64_t)8, N - s_col) : 0;
@@ -139,29 +139,41 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
   for (int j = 0; j < 8; ++j) xo[j] = (j ^ (swz & 7)) * 4;
   const int hi_off = (swz >> 3) * 32;
 
-  // EARLY (bf16 D): a wave requests its share of the next slab as soon as its own rows are done with the
-  // current one (the registers of the read window are free then), so the round trip runs while
+  // EARLY (bf16 D, and workgroups with registers to spare): a wave requests its share of the next slab as soon as its own rows
+  // are done with the current one (bf16: the registers of the read window are free then), so the round trip runs while
   // the slower waves finish instead of after the barrier.
-  static_assert(!EARLY || __is_same(DT, BF16), "raw bf16 units");
-  [[maybe_unused]] u32x4 nxt[SP_KS / SP_RPP];
+  constexpr int UNIT = __is_same(DT, BF16) ? 1 : 2;   // 16-byte loads of eight elements
+  static_assert(!EARLY || UNIT == 1 || ROWS < SP_ROWS, "registers");
+  [[maybe_unused]] u32x4 nxt[SP_KS / RPP][UNIT];
   [[maybe_unused]] auto fetch_next = [&](int64_t k0n) {
 #pragma unroll
-    for (int ps = 0; ps < SP_KS / SP_RPP; ++ps) {
-      const int64_t r = k0n + ps * SP_RPP + s_row;
-      nxt[ps] = u32x4{0u, 0u, 0u, 0u};
-      if (r < Q && s_valid >= 8) nxt[ps] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(D) + r * N + s_col);
+    for (int ps = 0; ps < SP_KS / RPP; ++ps) {
+      const int64_t r = k0n + ps * RPP + s_row;
+      if constexpr (UNIT == 1) {
+        nxt[ps][0] = u32x4{0u, 0u, 0u, 0u};
+        if (r < Q && s_valid >= 8) nxt[ps][0] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(D) + r * N + s_col);
+      } else {   // no branch: what stands in for rows past Q no entry names, and columns past N are not stored
+        const u32x4* const at = reinterpret_cast<const u32x4*>(reinterpret_cast<const float*>(D) + min(r, Q - 1) * N + (s_valid >= 8 ? s_col : 0));
+        nxt[ps][0] = at[0];
+        nxt[ps][UNIT - 1] = at[1];
+      }
     }
   };
-  if constexpr (EARLY) fetch_next(0);
+  if constexpr (EARLY) {
+    if (Q > 0) fetch_next(0);
+  }
 
   for (int64_t k0 = 0; k0 < Q; k0 += SP_KS) {
     __syncthreads();
 #pragma unroll
-    for (int ps = 0; ps < SP_KS / SP_RPP; ++ps) {
-      const int r = ps * SP_RPP + s_row;
+    for (int ps = 0; ps < SP_KS / RPP; ++ps) {
+      const int r = ps * RPP + s_row;
       f32x4 a, b;
-      if constexpr (EARLY) {
-        const u32x4 u = nxt[ps];
+      if constexpr (EARLY && UNIT == 2) {
+        a = __builtin_bit_cast(f32x4, nxt[ps][0]);
+        b = __builtin_bit_cast(f32x4, nxt[ps][UNIT - 1]);
+      } else if constexpr (EARLY) {
+        const u32x4 u = nxt[ps][0];
         a = f32x4{u2f(u.x << 16), u2f(u.x & 0xffff0000u), u2f(u.y << 16), u2f(u.y & 0xffff0000u)};
         b = f32x4{u2f(u.z << 16), u2f(u.z & 0xffff0000u), u2f(u.w << 16), u2f(u.w & 0xffff0000u)};
       } else {
@@ -192,24 +204,24 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
         ++cur;
         const float v = vq[i];
         const float* dr = &slab[(cq[i] - (int32_t)k0) * SP_LD];
-        // A window of SP_RIF chunk reads stays in flight: chunk g's FMAs are followed by the read
-        // of chunk g + SP_RIF into the registers they freed, in exactly this order.
+        // A window of RIF chunk reads stays in flight: chunk g's FMAs are followed by the read
+        // of chunk g + RIF into the registers they freed, in exactly this order.
         static_assert(SP_XM == 15 && SP_COLS == 64, "one chunk per swizzle constant");
         auto chunk = [&](int g) {
           return *reinterpret_cast<const f32x4*>(dr + ((g & 8) ? 32 - hi_off : hi_off) + xo[g & 7]);
         };
-        f32x4 d4[SP_RIF];
+        f32x4 d4[RIF];
 #pragma unroll
-        for (int q = 0; q < SP_RIF; ++q) d4[q] = chunk(q);
+        for (int q = 0; q < RIF; ++q) d4[q] = chunk(q);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < 16; ++g) {
-          const f32x4 d = d4[g % SP_RIF];
+          const f32x4 d = d4[g % RIF];
           acc[4 * g + 0] = fmaf(v, d.x, acc[4 * g + 0]);
           acc[4 * g + 1] = fmaf(v, d.y, acc[4 * g + 1]);
           acc[4 * g + 2] = fmaf(v, d.z, acc[4 * g + 2]);
           acc[4 * g + 3] = fmaf(v, d.w, acc[4 * g + 3]);
-          if (g + SP_RIF < 16) d4[g % SP_RIF] = chunk(g + SP_RIF);
+          if (g + RIF < 16) d4[g % RIF] = chunk(g + RIF);
           __builtin_amdgcn_sched_barrier(0);
         }
         // the sums are final here: the optimizer may not sink a step's FMAs into the block where
@@ -241,7 +253,7 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
   const int lane = tid & 63, wave = tid >> 6;
   float* const tile = slab + (wave % SP_WPR) * (64 * SP_COLS);
 #pragma unroll 1
-  for (int round = 0; round < (SP_ROWS / 64 + SP_WPR - 1) / SP_WPR; ++round) {
+  for (int round = 0; round < (ROWS / 64 + SP_WPR - 1) / SP_WPR; ++round) {
     if (wave / SP_WPR == round) {
 #pragma unroll
       for (int j = 0; j < SP_COLS; j += 4)
@@ -256,7 +268,7 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
           const int r = 4 * ps + (lane >> 4);
           if (!s_skip[wave * 64 + r]) {
             const f32x4 t = *reinterpret_cast<const f32x4*>(&tile[r * SP_COLS + tc * 4]);
-            *reinterpret_cast<f32x4*>(R + (block * SP_ROWS + wave * 64 + r) * N + col) = t;
+            *reinterpret_cast<f32x4*>(R + (block * ROWS + wave * 64 + r) * N + col) = t;
           }
         }
       }
@@ -265,17 +277,17 @@ FP4_D void spmm_tile_block(const int64_t* __restrict__ row_ptr, const int32_t* _
   }
 }
 
-template <class DT>
-__global__ __launch_bounds__(SP_ROWS) void spmm_tile_kernel(const int64_t* __restrict__ row_ptr,
-                                                            const int32_t* __restrict__ col_idx,
-                                                            const float* __restrict__ val, int64_t capacity,
-                                                            int64_t P, int64_t Q, const void* __restrict__ D,
-                                                            int64_t N, float* __restrict__ R) {
+template <class DT, int ROWS = SP_ROWS>
+__global__ __launch_bounds__(ROWS) void spmm_tile_kernel(const int64_t* __restrict__ row_ptr,
+                                                         const int32_t* __restrict__ col_idx,
+                                                         const float* __restrict__ val, int64_t capacity,
+                                                         int64_t P, int64_t Q, const void* __restrict__ D,
+                                                         int64_t N, float* __restrict__ R) {
   __shared__ __attribute__((aligned(16))) float slab[SP_KS * SP_LD];
-  __shared__ int s_skip[SP_ROWS];
-  spmm_tile_block<DT, __is_same(DT, BF16)>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
-                                           (int64_t)blockIdx.x * SP_ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS,
-                                           slab, s_skip);
+  __shared__ int s_skip[ROWS];
+  spmm_tile_block<DT, __is_same(DT, BF16) || (ROWS < SP_ROWS), ROWS>(row_ptr, col_idx, val, capacity, P, Q, D, N, R, blockIdx.x, threadIdx.x,
+                                                 (int64_t)blockIdx.x * ROWS + threadIdx.x < P, (int64_t)blockIdx.y * SP_COLS,
+                                                 slab, s_skip);
 }
 
 // ---- long rows -------------------------------------------------------------------------------
@@ -1023,8 +1035,17 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   if (!packed) {
     if (bf16)
       hipLaunchKernelGGL((spmm_tile_kernel<BF16>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
-    else
-      hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+    else {
+      // Half as many rows a workgroup while those go round the chip once: the slab is staged as often as there are workgroups,
+      // but a CU's gathers go twice as fast (1024 / 512 / 256 rows, with the long rows' launches, at 2 %: 2048^3 72 / 56 / 58 us,
+      // 2500 x 2048 -> 3000 76 / 66 / 99, 1024^3 43 / 32 / 32; beyond one round 3072^3 104 / 142 / 184).
+      const int64_t half = (P + SP_ROWS / 2 - 1) / (SP_ROWS / 2);
+      if (half * grid.y <= 256)
+        hipLaunchKernelGGL((spmm_tile_kernel<F32, SP_ROWS / 2>), dim3((unsigned)half, grid.y), dim3(SP_ROWS / 2), 0, s, row_ptr, col_idx, val,
+                           capacity, P, Q, D, N, R);
+      else
+        hipLaunchKernelGGL((spmm_tile_kernel<F32>), grid, dim3(SP_ROWS), 0, s, row_ptr, col_idx, val, capacity, P, Q, D, N, R);
+    }
     if (may_be_long)
       hipLaunchKernelGGL(find_long_rows_kernel, dim3(1), dim3(1024), 0, s, row_ptr, P, Q, capacity, list, count);
   }
