@@ -126,6 +126,14 @@ FP4_D void store8(void* base, int64_t off, int valid, const float (&v)[8]) {
 // sign than x the sign of the zero may differ, which no code, scale or residual entry depends on.
 // x lies outside [lo, hi] exactly when the result differs from x.
 FP4_D float clamp3(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+// Whether x clamped to c is an entry of the residual: exactly where the pass that counts the entries says so (x < lo or x > hi).
+// One that was not counted has no slot, so a NaN must not be one (c != x would hold), and a threshold that is a
+// NaN, which the count finds nothing beyond, has to stand for an infinity.  One compare either way.
+FP4_D bool is_outlier(float c, float x) { return __builtin_islessgreater(c, x); }
+FP4_D void nan_thresholds_to_inf(float& lo, float& hi) {
+  lo = lo == lo ? lo : -INFINITY;
+  hi = hi == hi ? hi : INFINITY;
+}
 
 FP4_D float wave_max(float v) {
 #pragma unroll
@@ -369,7 +377,11 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
   const int64_t xoff = row * a.ld;
 
   float lo = 0.0f, hi = 0.0f;
-  if (OCC && !TOKEN) { lo = a.thr[0]; hi = a.thr[1]; }
+  if (OCC && !TOKEN) {
+    lo = a.thr[0];
+    hi = a.thr[1];
+    nan_thresholds_to_inf(lo, hi);
+  }
   auto valid_of = [&](int64_t unit) -> int {
     if (!(row_ok && unit < nunits)) return 0;
     if constexpr (FULL) return 8;
@@ -403,6 +415,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
       select_row_thresholds<DT, TPR, NV>(cache, row_ok, t, a.cols, nunits, a.tail_k,
                                          s_hist + (TPR == 256 ? 0 : wave * TS_ROW), s_sel, lo, hi);
       if (row_ok && t == 0) { a.thr_out[2 * row] = lo; a.thr_out[2 * row + 1] = hi; }
+      nan_thresholds_to_inf(lo, hi);
     }
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
@@ -419,7 +432,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
         for (int e = 0; e < 8; ++e) {
           const float x = v[e];
           const float c = clamp3(x, lo, hi);
-          cu += c != x ? 1 : 0;
+          cu += is_outlier(c, x) ? 1 : 0;
           um = fmaxf(um, fabsf(c));
         }
         if (valid == 0) { cu = 0; um = 0.0f; }
@@ -435,7 +448,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
           float x = v[e];
           if (OCC) {
             const float c = clamp3(x, lo, hi);
-            cu += (c != x && e < valid) ? 1 : 0;
+            cu += (is_outlier(c, x) && e < valid) ? 1 : 0;
             x = e < valid ? c : 0.0f;
           }
           amax = fmaxf(amax, fabsf(x));
@@ -455,7 +468,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
         float x = v[e];
         if (OCC) {
           const float c = clamp3(x, lo, hi);
-          cnt += (c != x && e < valid) ? 1 : 0;
+          cnt += (is_outlier(c, x) && e < valid) ? 1 : 0;
           x = e < valid ? c : 0.0f;
         }
         amax = fmaxf(amax, fabsf(x));
@@ -594,7 +607,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
         const float x = v[e];
         x0[e] = x;
         const float c = clamp3(x, lo, hi);
-        om |= (c != x && (FULL || e < valid)) ? (1u << e) : 0u;   // finish() is not entered for an absent unit
+        om |= (is_outlier(c, x) && (FULL || e < valid)) ? (1u << e) : 0u;   // finish() is not entered for an absent unit
         v[e] = c;
       }
       while (om) {
