@@ -327,22 +327,19 @@ RESIDUAL_KERNELS = {"bf16": "spmm_pack_kernel + spmm_mfma_kernel + spmm_long_den
 
 
 def gemm_kernels(cfg, layers, torch):
-    """Which of the FP4 GEMM's kernels the step's products run on (the rule of fp4_launch_gemm)."""
+    """Which of the FP4 GEMM's kernels the step's products run on."""
+    from paper_2501_17116_amd import binding as b
     cus = torch.cuda.get_device_properties(0).multi_processor_count
+    bf16, clamp = cfg.dtype == "bf16", cfg.alpha < 1.0
     names = set()
     for L in layers:
         l = L["shape"]
-        for P, Q, Kc, factor in ((l.M, l.N, l.K, False), (l.M, l.K, l.N, False), (l.K, l.N, l.M, cfg.dge_k > 0)):
-            small, mid = -(-P // 64) * -(-Q // 64), -(-P // 128) * -(-Q // 128)
-            if (small <= 3 * cus and small * Kc <= 3072 * cus) if factor else (small <= 2 * cus and Kc <= 1024):
-                names.add("fp4_gemm_small_kernel")
-            elif mid <= ((1 if cfg.dtype == "bf16" else 3) if factor else 2) * cus:
+        for P, Q, Kc, factor, addend, out_bf16 in ((l.M, l.N, l.K, False, clamp, bf16), (l.M, l.K, l.N, False, False, bf16),
+                                                   (l.K, l.N, l.M, cfg.dge_k > 0, clamp, False)):
+            tile, last_round = b.fp4_gemm_tiling(P, Q, Kc, factor, bf16, addend, out_bf16, cus)
+            names.add({64: "fp4_gemm_small_kernel", 128: "fp4_gemm_mid_kernel", 256: "fp4_gemm_nt_kernel"}[tile])
+            if last_round:
                 names.add("fp4_gemm_mid_kernel")
-            else:
-                names.add("fp4_gemm_nt_kernel")
-                big = -(-P // 256) * -(-Q // 256)
-                if big > cus and 4 * (big % cus) <= cus and big % cus:   # the last round in quarters
-                    names.add("fp4_gemm_mid_kernel")
     return " + ".join(sorted(names))
 
 

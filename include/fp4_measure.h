@@ -30,6 +30,13 @@ int fp8_host_round_codes(const float* x_host, int64_t n, uint8_t* codes_host);
 int fp4_device_round_codes(const float* x, int64_t n, uint8_t* codes, void* stream);
 int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 
+/* Output tiles the FP4 GEMM [P x Q], contraction Kc, is cut into on a device with that many compute units, by the rule its launches
+ * follow (host arithmetic, no GPU): 64, 128 or 256 rows and columns; with 256, *last_round (may be NULL) is the number of
+ * tiles of the last round that are cut into 128 x 128 ones, otherwise 0.  factor: the weight gradient's derivative factor
+ * with weights in bf16 (w_bf16) or fp32; addend: whether there is one; out_bf16: the output's type. */
+int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
+                    int* last_round);
+
 /* ---- ceilings measured on the part (for reading the rooflines; not part of the method) ----
  * fp4_probe_mfma: `workgroups` workgroups of 8 waves each run `iters` iterations of 8 FP4
  *   32x32x64 MFMAs per wave with operands taken from operand_bytes (device, >= 16 bytes): an

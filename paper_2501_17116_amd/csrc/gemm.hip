@@ -13,6 +13,7 @@
 // is a multiple of 1/4 and bounded by 36, so the fp32 accumulator is exact for any contraction
 // length below 2^22/36 and does not depend on summation order.
 #include "fp4_common.h"
+#include "gemm_tiling.h"
 #include "fp4_measure.h"
 
 #include <algorithm>
@@ -44,8 +45,8 @@ constexpr int STAGE_BYTES = 2 * TILE_BYTES;
 constexpr int EPI_BASE = STAGE_BYTES;
 constexpr int SMEM_BYTES = 2 * STAGE_BYTES > EPI_BASE + EPI_BYTES ? 2 * STAGE_BYTES : EPI_BASE + EPI_BYTES;
 static_assert(SMEM_BYTES <= 160 * 1024, "LDS budget");
-// Past the end of any tile's descriptor while its rows take no more than this (contractions to 31 M codes).
-constexpr uint32_t OUT_OF_RANGE = 0xf0000000u;
+constexpr uint32_t OUT_OF_RANGE = GEMM_OUT_OF_RANGE;   // where a descriptor has nothing: arrives as zeros
+static_assert(BKB == GEMM_K_STEP && BM == 256 && BN == 256, "as gemm_tiling has them");
 
 // LDS layout of an operand stage: row r occupies bytes [128 r, 128 r + 128); its 16-byte
 // chunk c sits in slot c ^ ((r >> 1) & 7).  Sixteen consecutive rows reading the same logical
@@ -978,56 +979,29 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   g.tiles_p = (int)((P + BM - 1) / BM);
   g.tiles_q = (int)((Q + BN - 1) / BN);
   const bool dge = W != nullptr && dge_k > 0.0f;
-  int total = g.tiles_p * g.tiles_q;
   const int n_cu = compute_units_of_current_device();
+  const GemmTiling t = gemm_tiling(P, Q, Kc, dge, w_bf16 != 0, addend != nullptr, out_bf16 != 0, n_cu);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
-  const bool ragged = (g.Kb % BKB) != 0;
-  // What bounds a call with few tiles is one tile's chain of steps, so the smaller tile wins while there is no more than a
-  // round or two of it.  Measured as 64 / 128 / 256 tiles, in us:
-  //  64, up to 1024 codes and two tiles per CU: 512 x 2048, 512 codes 5.6 / 7.1 / 11.5; 512 x 1024, 1024 7.2 / 7.8 / 13.3;
-  //   past that line 512 x 2048, 2048 10.7 / 9.5 / 17.5; 2048 x 2048, 256 9.7 / 7.6 / 11.4.
-  //  64 with the factor, which asks for many threads: tiles x contraction up to 3072 codes per CU (the whole weight gradient
-  //   without the clamp, fp32, 1024 x 1024, 2048 codes: 42 / 45 / 78; 1376 x 2080, 1056: 45 / 47 / 77; 2048 x 2048, 2048: 72 / 51 / 84).
-  //  128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend 40 / 22.6 / 24.8 and 237 / 54 / 58; past it
-  //   2816 x 3072, 4096 140 / 48 / 38.  With the factor one (2048 x 4096 x 4096 bf16 172 / 87 / 86), and with fp32 masters, for which
-  //   the big tiles have no branch-free epilogue, three (2048 x 5504, 2048 codes 138 / 88 / 93; 4096 x 4096, 2048 180 / 107 / 99).
-  const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64), mid_tiles = ((P + MG_T - 1) / MG_T) * ((Q + MG_T - 1) / MG_T);
-  const bool few = dge ? small_tiles <= 3 * (int64_t)n_cu && small_tiles * Kc <= 3072 * (int64_t)n_cu
-                       : small_tiles <= 2 * (int64_t)n_cu && Kc <= 1024;
-  // rows too long for the offsets of the larger tiles' descriptors
-  const bool small = few || g.Kb * (ragged ? BM : 1) > (int64_t)OUT_OF_RANGE;
-  const bool mid = mid_tiles <= (dge ? (w_bf16 ? 1 : 3) : 2) * (int64_t)n_cu && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE;
-  // A last round of 256 x 256 tiles that no more than a quarter of the CUs have is cut into 128 x 128 ones, which go round the
-  // chip once: 320 tiles, 13824 codes 166 -> 143 us (with fp32 addend 183 -> 160), 2048 codes 41 -> 38 (59 -> 54); 289, 512
-  // codes 25.5 -> 23.6; 1080, 4096 codes 162 -> 153.  Two rounds of them take as long as the one they replace, or longer (352
-  // tiles, 512 / 4096 / 13824 codes 26 / 62 / 166 -> 29 / 66 / 173).
-  const int wgs = (n_cu / 8) * 8;
-  int rest = 0;
-  if (!small && !mid && g.Kb * MG_T <= (int64_t)OUT_OF_RANGE && total > wgs && 4 * (total % wgs) <= wgs) rest = total % wgs;
-  total -= rest;
+  const bool ragged = (g.Kb % BKB) != 0, small = t.tile == 64, mid = t.tile == 128;
+  const int total = g.tiles_p * g.tiles_q - t.rest;
   g.first = 0;
   g.count = total;
-  const dim3 grid(std::min((total + 7) / 8 * 8, wgs)), block(NTHREADS);
-  // Workgroups that start together come to their epilogues together: memory is idle while all multiply and the bound while all
-  // add, convert and store.  Four quarters 3.4 us apart overlap the two where an epilogue moves much (addend, fp32
-  // output) and a workgroup has enough tiles to make up for it, or those that have one less can be the late ones
-  // (16384 x 12288 x 4096 with addend 603 -> 561 us, 16384 x 4096 x 2048 151 -> 137, 5120 x 13824 x 4096 fp32 258 -> 246, 4096 x
-  // 11008 x 4096 131 -> 127; three full rounds 410 -> 415, bf16 without addend 353 -> 359).
-  g.stagger = (addend || !out_bf16) && (total > 3 * wgs || (total > 2 * wgs && 8 * (int64_t)total <= 23 * (int64_t)wgs)) ? 15 : 0;
+  g.stagger = t.stagger;
+  const dim3 grid(std::min((total + 7) / 8 * 8, (n_cu / 8) * 8)), block(NTHREADS);
   GemmShape gs = g, gm = g;
   gs.tiles_p = (int)((P + 63) / 64);
   gm.tiles_p = (int)((P + MG_T - 1) / MG_T);
   gm.tiles_q = (int)((Q + MG_T - 1) / MG_T);
   gm.count = gm.tiles_p * gm.tiles_q;
-  if (rest) {   // the order of the 256 x 256 tiles
+  if (t.rest) {   // the order of the 256 x 256 tiles
     gm = g;
     gm.first = total;
-    gm.count = 4 * rest;
+    gm.count = 4 * t.rest;
   }
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
     if (small)                                                                                            \
-      hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)small_tiles), dim3(256), 0, stream, L, Rt, gl, gr, \
+      hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)(((P + 63) / 64) * ((Q + 63) / 64))), dim3(256), 0, stream, L, Rt, gl, gr, \
                          addend, out, W, gamma_w, gs);                                                    \
     else if (mid)                                                                                         \
       ;                                                                                                   \
@@ -1037,7 +1011,7 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
     else                                                                                                  \
       hipLaunchKernelGGL((fp4_gemm_nt_kernel<OB, DG, WB, false>), grid, block, 0, stream, L, Rt, gl, gr,  \
                          addend, out, W, gamma_w, g);                                                     \
-    if (!small && (mid || rest))                                                                          \
+    if (!small && (mid || t.rest))                                                                        \
       hipLaunchKernelGGL((fp4_gemm_mid_kernel<OB, DG, WB>), dim3((unsigned)((gm.count + 7) / 8 * 8)), dim3(256), 0, stream, L, Rt, \
                          gl, gr, addend, out, W, gamma_w, gm);                                            \
   } while (0)
@@ -1070,6 +1044,14 @@ extern "C" int fp4_gemm(const uint8_t* codes_l, const float* gamma_l, const uint
   return fp4_launch_gemm(codes_l, gamma_l, codes_rt, gamma_r, P, Q, Kc, addend, out,
                          out_dt == FP4_BF16, ldo, nullptr, 0, 0, nullptr, 0.0f, 0.0f,
                          (hipStream_t)stream);
+}
+
+extern "C" int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
+                               int* last_round) {
+  if (P <= 0 || Q <= 0 || Kc < 0 || (Kc % 32) != 0 || compute_units < 8) return FP4_ERR_SHAPE;
+  const GemmTiling t = gemm_tiling(P, Q, Kc, factor != 0, w_bf16 != 0, addend != 0, out_bf16 != 0, compute_units);
+  if (last_round) *last_round = t.rest;
+  return t.tile;
 }
 
 extern "C" int fp4_unpack(const uint8_t* codes, int64_t rows, int64_t cols, uint8_t* one_per_byte,
