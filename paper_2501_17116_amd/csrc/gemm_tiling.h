@@ -32,7 +32,8 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
   // The larger tiles address their rows by 32-bit offsets into a descriptor; rows too long for that go to the next smaller
   // one, and the 64 x 64 ones have 64-bit addresses.
   const bool fits_big = Kb * 256 <= (int64_t)GEMM_OUT_OF_RANGE, fits_mid = Kb * 128 <= (int64_t)GEMM_OUT_OF_RANGE;
-  if (few || !fits_mid) {
+  // An empty contraction has no K step to request, which the staged tilings do ahead: the operands may be null.
+  if (few || !fits_mid || Kb == 0) {
     t.tile = 64;
     return t;
   }

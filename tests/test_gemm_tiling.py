@@ -16,3 +16,9 @@ def test_rows_stay_within_the_offsets(row_bytes):
             tile, last_round = b.fp4_gemm_tiling(P, Q, 2 * row_bytes, factor, w_bf16, addend, out_bf16)
             assert tile == 64 or row_bytes * tile <= LIMIT, (P, Q, tile)
             assert last_round == 0 or tile == 256
+
+
+@pytest.mark.parametrize("P,Q", [(1, 8), (4096, 4096), (40000, 40000)])
+def test_an_empty_contraction_runs_where_nothing_is_requested_ahead(P, Q):
+    for factor, w_bf16, addend, out_bf16 in itertools.product((0, 1), repeat=4):
+        assert b.fp4_gemm_tiling(P, Q, 0, factor, w_bf16, addend, out_bf16) == (64, 0)

@@ -47,3 +47,13 @@ def test_fp32_factor_on_both_sides_of_the_contraction_limit(M, K, N):
     qY, gY = b.fp4_quantize(dY, b.FP4_AXIS_COL)
     ref = b.fp4_dge_apply(b.fp4_gemm(qA, gA, qY, gY), W, ctx.gamma_W, 5.0, 3.0)
     assert torch.all((got - ref).abs() <= 2.0 ** -22 * ref.abs())
+
+
+@pytest.mark.parametrize("P,Q", [(65, 72), (4096, 4104)])
+def test_an_empty_contraction(P, Q):
+    """No codes at all, and no operands: the addend alone."""
+    from paper_2501_17116_amd import binding as b
+    addend = torch.randn(P, Q, device="cuda")
+    out = torch.full((P, Q), float("nan"), device="cuda")
+    assert b.lib().fp4_gemm(None, None, None, None, P, Q, 0, b._ptr(addend), b._ptr(out), b.FP4_F32, Q, b._stream()) == 0
+    assert torch.equal(out, addend)
