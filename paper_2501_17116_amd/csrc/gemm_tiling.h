@@ -14,21 +14,52 @@ struct GemmTiling {
 constexpr uint32_t GEMM_OUT_OF_RANGE = 0xf0000000u;
 constexpr int GEMM_K_STEP = 128;   // bytes of a row that one stage of the staged tilings holds
 
+// Whether the 64 x 64 tiles, whose operands go straight to registers, beat the 128 x 128 ones, whose go through a ring in LDS.  What
+// bounds a call with few tiles is one tile's chain of steps: theirs is shorter to start and slower a step, so the line is a
+// length of the contraction, and it moves with
+//  - whether a row of codes is whole 128-byte lines.  Where it is, all rows of a tile come to the end of a line in the same step
+//    and their next lines are waited for together; where it is not, a few do in every step;
+//  - the rounds of tiles that a CU takes (the smaller tile is the first to need a second one);
+//  - the factor, which asks for many threads.
+// In us as 64 / 128 tiles, bf16 out with fp32 addend or fp32 out, one round: rows of whole lines, 1024 codes (64 x 2048) 6.9 / 7.0,
+// 2048 9.7 / 8.8; others, 1056 (64 x 2048) 5.1 / 7.7, 4640 (512 x 512) 0.85 of the 128 tiles' time, 6176 1.00.  Two rounds, whole
+// lines, 256 / 512 codes 0.91 / 1.13, others 1056 / 1312 0.92 / 1.00; three rounds, others, 416 / 544 0.96 / 1.01.  With the factor, one
+// round, whole lines, 3072 / 4096 codes 0.95 / 1.04, others 8224 / 10272 0.92 / 1.06; two rounds, 768 / 1024 0.98 / 1.05 and 2080 / 2592
+// 0.85 / 1.04; three, 256 / 512 0.90 / 1.06 and 1056 / 1312 0.92 / 1.00, with fp32 weights 1312 / 1568 0.86 / 1.0 and, four rounds,
+// 384 0.62, 800 1.02.
+inline bool gemm_small_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, bool w_bf16, int n_cu) {
+  const int64_t tp = (P + 63) / 64, tq = (Q + 63) / 64, tiles = tp * tq, rounds = (tiles + n_cu - 1) / n_cu, Kb = Kc / 2;
+  if (rounds > 4) return false;
+  const int r = (int)std::max<int64_t>(rounds, 1) - 1;
+  if (Kb % GEMM_K_STEP == 0) {
+    static constexpr int plain[4] = {1280, 256, 0, 0}, with_factor[4] = {3072, 768, 256, 0};
+    return Kc <= (factor ? with_factor : plain)[r];
+  }
+  static constexpr int plain[4] = {6144, 1088, 448, 0}, with_factor[4] = {8448, 2336, 1184, 0}, with_f32_factor[4] = {8448, 2336, 1376, 640};
+  int limit = (factor ? (w_bf16 ? with_factor : with_f32_factor) : plain)[r];
+  if (P <= 32 && !factor && r == 0) limit *= 2;   // half of a 64-row tile re-reads its last row (32 x 2976, 6368 codes 14.6 / 16.9)
+  if (Kc > limit) return false;
+  if (Kc <= 1024 || tp == 1 || tq == 1) return true;
+  // An operand row is read once for every tile that needs it, so the rows that an XCD's tiles need (they are dealt round, column by
+  // column) have to stay in its 4 MiB of L2: 320 x 3200, 2592 / 3616 codes, 3.0 / 4.3 MB: 0.92 / 1.13; 512 x 2048, 3104 / 4640, 3.3 / 4.9
+  // MB: 0.83 / 1.25.  With the factor 512 x 2048, 3616 / 5152, 3.8 / 5.4 MB: 0.90 / 1.09, and where a CU takes more than one
+  // round 512 x 4096, 1312 / 1824, 2.7 / 3.8 MB: 0.87 / 1.15.
+  int64_t stride = 8;
+  while (tp % stride) stride /= 2;   // of the tiles of a column, each XCD has every stride-th
+  const int64_t share = (tiles + 7) / 8, rows = 64 * (std::min(tq, share) + std::min(tp / stride, share));
+  return rows * Kb <= (!factor ? 15 << 18 : r == 0 ? 18 << 18 : 10 << 18);
+}
+
 inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, bool w_bf16, bool addend, bool out_bf16, int n_cu) {
   GemmTiling t = {256, 0, 0};
   const int64_t Kb = Kc / 2;
-  // What bounds a call with few tiles is one tile's chain of steps, so the smaller tile wins while there is no more than a
-  // round or two of it.  Measured as 64 / 128 / 256 tiles, in us:
-  //  64, up to 1024 codes and two tiles per CU: 512 x 2048, 512 codes 5.6 / 7.1 / 11.5; 512 x 1024, 1024 7.2 / 7.8 / 13.3;
-  //   past that line 512 x 2048, 2048 10.7 / 9.5 / 17.5; 2048 x 2048, 256 9.7 / 7.6 / 11.4.
-  //  64 with the factor, which asks for many threads: tiles x contraction up to 3072 codes per CU (the whole weight gradient
-  //   without the clamp, fp32, 1024 x 1024, 2048 codes: 42 / 45 / 78; 1376 x 2080, 1056: 45 / 47 / 77; 2048 x 2048, 2048: 72 / 51 / 84).
-  //  128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend 40 / 22.6 / 24.8 and 237 / 54 / 58; past it
-  //   2816 x 3072, 4096 140 / 48 / 38.  With the factor one (2048 x 4096 x 4096 bf16 172 / 87 / 86), and with fp32 masters, for which
-  //   the big tiles have no branch-free epilogue, three (2048 x 5504, 2048 codes 138 / 88 / 93; 4096 x 4096, 2048 180 / 107 / 99).
-  const int64_t small_tiles = ((P + 63) / 64) * ((Q + 63) / 64), mid_tiles = ((P + 127) / 128) * ((Q + 127) / 128);
-  const bool few = factor ? small_tiles <= 3 * (int64_t)n_cu && small_tiles * Kc <= 3072 * (int64_t)n_cu
-                          : small_tiles <= 2 * (int64_t)n_cu && Kc <= 1024;
+  const bool few = gemm_small_tiles_win(P, Q, Kc, factor, w_bf16, n_cu);
+  // 128 x 128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend, as 64 / 128 / 256 tiles in us: 40 / 22.6 / 24.8 and
+  // 237 / 54 / 58; past it 2816 x 3072, 4096 140 / 48 / 38.  With the factor one (2048 x 4096 x 4096 bf16 172 / 87 / 86).  With fp32
+  // masters, for which the big tiles have no branch-free epilogue, three with an addend (2016 x 4640, 1632 codes 128 / 256: 54 / 62;
+  // 2800 x 3456, 3328 63 / 67) and two without (2872 x 3376, 8448 88 / 76; 1248 x 7344, 5600 79 / 67).
+  const int64_t mid_tiles = ((P + 127) / 128) * ((Q + 127) / 128);
+  const int mid_per_cu = !factor ? 2 : w_bf16 ? 1 : addend ? 3 : 2;
   // The larger tiles address their rows by 32-bit offsets into a descriptor; rows too long for that go to the next smaller
   // one, and the 64 x 64 ones have 64-bit addresses.
   const bool fits_big = Kb * 256 <= (int64_t)GEMM_OUT_OF_RANGE, fits_mid = Kb * 128 <= (int64_t)GEMM_OUT_OF_RANGE;
@@ -37,7 +68,7 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
     t.tile = 64;
     return t;
   }
-  if (mid_tiles <= (factor ? (w_bf16 ? 1 : 3) : 2) * (int64_t)n_cu || !fits_big) {
+  if (mid_tiles <= mid_per_cu * (int64_t)n_cu || !fits_big) {
     t.tile = 128;
     return t;
   }

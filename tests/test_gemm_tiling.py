@@ -22,3 +22,28 @@ def test_rows_stay_within_the_offsets(row_bytes):
 def test_an_empty_contraction_runs_where_nothing_is_requested_ahead(P, Q):
     for factor, w_bf16, addend, out_bf16 in itertools.product((0, 1), repeat=4):
         assert b.fp4_gemm_tiling(P, Q, 0, factor, w_bf16, addend, out_bf16) == (64, 0)
+
+
+# (P, Q, Kc, factor, w_bf16, addend, tile): either side of the lines, and shapes that were measured far from them
+LINES = [
+    # rows of whole 128-byte lines: one round of 64 x 64 tiles, two, three
+    (512, 2048, 1280, 0, 0, 0, 64), (512, 2048, 1536, 0, 0, 0, 128), (520, 2048, 256, 0, 0, 0, 64), (520, 2048, 512, 0, 0, 0, 128),
+    (1032, 2048, 256, 0, 0, 0, 128), (512, 2048, 3072, 1, 1, 0, 64), (512, 2048, 3328, 1, 1, 0, 128), (520, 2048, 768, 1, 1, 1, 64),
+    (520, 2048, 1024, 1, 1, 1, 128), (1032, 2048, 256, 1, 0, 1, 64), (1032, 2048, 512, 1, 0, 1, 128),
+    # others
+    (192, 1216, 1216, 0, 0, 0, 64), (32, 704, 1056, 0, 0, 0, 64), (224, 1408, 1312, 0, 0, 1, 64), (512, 512, 6144 - 32, 0, 0, 0, 64),
+    (512, 512, 6176, 0, 0, 0, 128), (32, 512, 6176, 0, 0, 0, 64), (520, 2048, 1056, 0, 0, 0, 64), (520, 2048, 1120, 0, 0, 0, 128),
+    (1032, 2048, 416, 0, 0, 0, 64), (1032, 2048, 480, 0, 0, 0, 128), (1024, 832, 6016, 1, 1, 0, 64), (512, 512, 8416, 1, 1, 0, 64),
+    (512, 512, 8480, 1, 1, 0, 128), (520, 2048, 1312, 1, 1, 0, 64), (1280, 1280, 2400, 1, 1, 0, 128), (1032, 2048, 1184, 1, 1, 0, 64), (1032, 2048, 1248, 1, 1, 0, 128),
+    (1032, 2048, 1376, 1, 0, 0, 64), (672, 5496, 384, 1, 0, 0, 64), (672, 5496, 672, 1, 0, 0, 128),
+    # what an XCD's tiles need of the operands beyond its L2
+    (320, 3200, 2592, 0, 0, 0, 64), (320, 3200, 3616, 0, 0, 0, 128), (512, 2048, 3104, 0, 0, 0, 64), (512, 2048, 4640, 0, 0, 0, 128),
+    (512, 4096, 1312, 1, 1, 1, 128), (512, 4096, 1184, 1, 1, 1, 64),
+    # fp32 weights: two rounds of 128 x 128 tiles, three with an addend
+    (2872, 3376, 8448, 1, 0, 0, 256), (2872, 3376, 8448, 1, 0, 1, 128), (1024, 8160, 8448, 1, 0, 0, 128),
+]
+
+
+@pytest.mark.parametrize("P,Q,Kc,factor,w_bf16,addend,tile", LINES)
+def test_tiles(P, Q, Kc, factor, w_bf16, addend, tile):
+    assert b.fp4_gemm_tiling(P, Q, Kc, factor, w_bf16, addend, 0, 256)[0] == tile

@@ -57,3 +57,41 @@ def test_an_empty_contraction(P, Q):
     out = torch.full((P, Q), float("nan"), device="cuda")
     assert b.lib().fp4_gemm(None, None, None, None, P, Q, 0, b._ptr(addend), b._ptr(out), b.FP4_F32, Q, b._stream()) == 0
     assert torch.equal(out, addend)
+
+
+@pytest.mark.parametrize("P,Q,K,tile", [(512, 2048, 1280, 64), (512, 2048, 1536, 128), (520, 2048, 256, 64), (520, 2048, 512, 128),
+                                        (520, 2056, 1056, 64), (520, 2056, 1120, 128), (1032, 2056, 416, 64), (1032, 2056, 480, 128),
+                                        (512, 512, 6112, 64), (32, 520, 6176, 64), (40, 520, 6176, 128)])
+def test_either_side_of_the_lines_between_the_tilings(P, Q, K, tile):
+    """Under scales of any value: the rows of a problem that the 256 x 256 tiles take, to the last bit."""
+    from paper_2501_17116_amd import binding as b
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or b.fp4_gemm_tiling(P, Q, K)[0] == tile
+    g = torch.Generator(device="cuda").manual_seed(P + Q + K)
+    Pb, Qb = 4608, 4352   # 306 tiles
+    L = torch.randint(0, 256, (Pb, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    R = torch.randint(0, 256, (Qb, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    gl, gr = torch.rand(Pb, generator=g, device="cuda") + 0.5, torch.rand(Qb, generator=g, device="cuda") + 0.5
+    addend = torch.randn(Pb, Qb, generator=g, device="cuda")
+    for dt in (torch.float32, torch.bfloat16):
+        one = b.fp4_gemm(L[:P], gl[:P], R[:Q], gr[:Q], out_dtype=dt, addend=addend[:P, :Q].contiguous())
+        big = b.fp4_gemm(L, gl, R, gr, out_dtype=dt, addend=addend)
+        assert torch.equal(one, big[:P, :Q])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,K,N", [(3072, 512, 2048), (3328, 512, 2048), (768, 520, 2048), (1024, 520, 2048), (256, 1032, 2048), (512, 1032, 2048),
+                                   (6016, 1024, 832), (8480, 512, 512), (1312, 520, 2048), (2400, 1280, 1280), (1184, 1032, 2048),
+                                   (1376, 1032, 2048), (1408, 1032, 2048), (640, 672, 5496), (672, 672, 5496)])
+def test_factor_on_either_side_of_the_lines(M, K, N, dtype):
+    """The weight gradient against its parts called one by one: the product is the same to the last bit, the factor one
+    rounding of fp32 in either."""
+    from paper_2501_17116_amd import binding as b
+    torch.manual_seed(M + N)
+    A, W, dY = (t.to(dtype) for t in (torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda") * 0.02, torch.randn(M, N, device="cuda")))
+    _, ctx = b.fp4_linear_fwd(A[:, :K // 32 * 32].contiguous(), W[:K // 32 * 32].contiguous(), 1.0)
+    got = b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 5.0, 3.0)
+    qA, gA = b.fp4_quantize(A, b.FP4_AXIS_COL)
+    qY, gY = b.fp4_quantize(dY, b.FP4_AXIS_COL)
+    ref = b.fp4_dge_apply(b.fp4_gemm(qA, gA, qY, gY), W, ctx.gamma_W, 5.0, 3.0)
+    assert torch.all((got - ref).abs() <= 2.0 ** -22 * ref.abs())
