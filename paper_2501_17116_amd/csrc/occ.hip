@@ -213,22 +213,26 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, uns
 // A sample says where the thresholds are, to within a few of the 2048 leading 11-bit digits; the pass over all elements then
 // needs bins only for the keys around them (three digits, 96 keys a threshold), counts what lies outside, and keeps every
 // row's bins: with the thresholds known, a row's outliers are a sum over those.  Where a threshold turns out not to lie in
-// its window (or the windows meet, a NaN is about, a threshold is a zero, whose two keys are one value), `done` stays 0 and
-// the passes of the general path, launched behind, do their work; otherwise they leave at once.
+// its window, or a NaN is about, `done` stays 0 and the passes of the general path, launched behind, do their work; otherwise
+// they leave at once.
 // Bound by the one read and, about as long, by vector instructions (nine an element).  16384 x 11008, in us: init 4.5, sample 6.4,
 // picks 5.0 + 5.9, the pass 96.9, the general path's two launches 9, rows 4.8, together 133; digit passes, picks and the count of
 // the rows after them 249.  16384 x 4096: 74 against 107.  Below 2^25 elements the launches cost what the pass saves (8192 x
 // 2048: digit passes, picks and count 43, of which this would leave 40).
 constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STRIDE = 200;   // bins; a wave's table; a row's in memory
-constexpr int SAMPLE_BLOCKS = 128, SAMPLE_VECS = 2 * SEL_THREADS;   // 16-byte vectors a workgroup
+constexpr uint32_t KEY_NEG_ZERO = 0x7fff, KEY_POS_ZERO = 0x8000;
+constexpr int SAMPLE_BLOCKS = 128, SAMPLE_RUNS = SAMPLE_BLOCKS * 2 * (SEL_THREADS / 64);   // runs of 64 16-byte vectors
 
+// 4096 runs of 512 elements, evenly spaced.  As many elements in 128 runs were a few hundred whole rows: of tensors with a hundred
+// large rows in thousands (first tokens of a sequence), or rows that differ in scale, it missed the windows of one in seven.
 __global__ __launch_bounds__(SEL_THREADS) void sel_sample_kernel(const u32x4* x, int64_t nvec, unsigned long long* hist) {
   __shared__ uint32_t h[8 * SEL_BINS];
   for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
   __syncthreads();
   uint32_t* const hrep = &h[(threadIdx.x & 7) * SEL_BINS];
-  const int64_t at = (int64_t)blockIdx.x * (nvec - SAMPLE_VECS) / (SAMPLE_BLOCKS - 1) + threadIdx.x;
-  const u32x4 r[2] = {x[at], x[at + SEL_THREADS]};
+  const int64_t run = (int64_t)blockIdx.x * (2 * SEL_THREADS / 64) + threadIdx.x / 64;
+  auto vec = [&](int64_t c) { return x[c * (nvec - 64) / (SAMPLE_RUNS - 1) + (threadIdx.x & 63)]; };
+  const u32x4 r[2] = {vec(run), vec(run + SEL_THREADS / 64)};
 #pragma unroll
   for (int v = 0; v < 2; ++v)
 #pragma unroll
@@ -245,98 +249,152 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_sample_kernel(const u32x4* x,
   }
 }
 
-// First keys of the windows, from the digits that the sample's order statistics have.
-FP4_D uint32_t win_first(const SelState* st, int s) { return (uint32_t)min(max((int)st->prefix[s] - 1, 0), SEL_BINS - 3) * 32u; }
+// First keys of the windows, from the digits that the sample's order statistics have.  Windows that would meet lie side by
+// side, and either threshold may be in either.  (The lowest digit is that of a negative NaN.)
+struct Windows {
+  uint32_t w0, w1;
+  FP4_D explicit Windows(const SelState* st) {
+    const int d0 = min(max((int)st->prefix[0] - 1, 1), SEL_BINS - 6);
+    w0 = (uint32_t)d0 * 32u;
+    w1 = (uint32_t)min(max((int)st->prefix[1] - 1, d0 + 3), SEL_BINS - 3) * 32u;
+  }
+  FP4_D bool side_by_side() const { return w0 + WIN_KEYS == w1; }
+  // Bin 0: below the lower window, 1 .. 96 in it, 97 between the two (not kept), 98 .. 193 in the upper one, 194 above.
+  FP4_D int bin(uint32_t key) const {
+    return (key < w0 ? 0 : (int)min(key - w0 + 1, WIN_KEYS + 1u)) + (key < w1 ? 0 : (int)min(key - w1 + 1, WIN_KEYS + 1u));
+  }
+  // The two keys of zero, which may be most of a tensor, are counted apart where either is in a window.
+  FP4_D bool zeros_apart() const {
+    const int a = bin(KEY_NEG_ZERO), b = bin(KEY_POS_ZERO);
+    return a % (WIN_KEYS + 1) != 0 || b % (WIN_KEYS + 1) != 0;
+  }
+};
 
-// A wave per row.  Bin 0: below the lower window, 1 .. 96 in it, 97 between the two (not kept), 98 .. 193 in the upper one,
-// 194 above.
+// A wave per row.
 __global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int64_t rows, int64_t cols, SelState* st, unsigned long long* hist,
                                                          uint16_t* row_bins) {
   __shared__ uint32_t tab[16][WIN_LDS];
-  __shared__ uint32_t total[WIN_LDS];
-  const uint32_t w0 = win_first(st, 0), w1 = win_first(st, 1);
-  if (w0 + WIN_KEYS > w1) return;   // pick_windows sees the same
+  __shared__ uint32_t total[WIN_LDS + 2];
+  const Windows win(st);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t* const t = tab[wave];
 #pragma unroll
   for (int j = 0; j < WIN_LDS / 64; ++j) t[lane + 64 * j] = 0;
-  if (threadIdx.x < WIN_LDS) total[threadIdx.x] = 0;
+  if (threadIdx.x < WIN_LDS + 2) total[threadIdx.x] = 0;
   __syncthreads();
   typedef short s16x2 __attribute__((ext_vector_type(2)));
   typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
   uint32_t sum[WIN_LDS / 64] = {};
   u16x2 top = {0, 0};   // largest magnitude
-  const uint16_t lo1 = (uint16_t)max((int)w0 - 1, 0), hi1 = (uint16_t)(w1 - 1), most = WIN_KEYS + 1;
-  const uint16_t none = w0 == 0 ? 1 : 0;   // no key lies below a window that begins at 0
-  const u16x2 lo = {lo1, lo1}, hi = {hi1, hi1}, lim_lo = {(uint16_t)(most - none), (uint16_t)(most - none)}, lim_hi = {most, most}, one = {none, none};
-  auto visit = [&](uint32_t bin) {
-    if (bin != WIN_KEYS + 1) atomicAdd(&t[bin], 1u);
-  };
-  auto visit_vec = [&](const u32x4& r) {
+  // Sums of 0 / 1 / 1 and of 0 / 1 / 2 for -0, +0 and the rest.  16 bits hold them: rows have 500 elements or more (row_bins has to fit
+  // the entries' room) and the tensor fewer than 2^32, so a half word meets at most 2^13 + 2^7 of them.
+  u16x2 nz1 = {0, 0}, nz2 = {0, 0};
+  const uint16_t lo1 = (uint16_t)(win.w0 - 1), hi1 = (uint16_t)(win.w1 - 1), most = WIN_KEYS + 1;
+  const u16x2 lo = {lo1, lo1}, hi = {hi1, hi1}, lim = {most, most};
+  auto all_rows = [&](auto zeros) {
+    constexpr bool ZEROS = decltype(zeros)::value;
+    auto visit = [&](uint32_t bin) {
+      if (bin != WIN_KEYS + 1 && (!ZEROS || bin < WIN_BINS)) atomicAdd(&t[bin], 1u);
+    };
+    auto visit_vec = [&](const u32x4& r) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {   // two elements at a time: keys as key_of, then how far they are into either window
-      const uint32_t p = r[e];
-      const s16x2 sign = __builtin_bit_cast(s16x2, p) >> (short)15;
-      const u16x2 key = __builtin_bit_cast(u16x2, p ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u));
-      top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, p & 0x7fff7fffu));
-      const u16x2 bin = __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, lo), lim_lo) + one +
-                        __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, hi), lim_hi);
-      visit(bin.x);
-      visit(bin.y);
+      for (int e = 0; e < 4; ++e) {   // two elements at a time: keys as key_of, then how far they are into either window
+        const uint32_t p = r[e];
+        const s16x2 sign = __builtin_bit_cast(s16x2, p) >> (short)15;
+        const u16x2 key = __builtin_bit_cast(u16x2, p ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u));
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, p & 0x7fff7fffu));
+        u16x2 bin = __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, lo), lim) +
+                    __builtin_elementwise_min(__builtin_elementwise_sub_sat(key, hi), lim);
+        if constexpr (ZEROS) {   // half of the elements on one word of a table: the atomics would wait for each other
+          const u16x2 d = key - (u16x2){KEY_NEG_ZERO, KEY_NEG_ZERO}, one = {1, 1}, two = {2, 2};
+          const u16x2 d2 = __builtin_elementwise_min(d, two);
+          nz1 += __builtin_elementwise_min(d, one);
+          nz2 += d2;
+          bin |= (d2 ^ two) << (u16x2){8, 8};   // past the bins
+        }
+        visit(bin.x);
+        visit(bin.y);
+        // a pair at a time, or the sums become trees and a CU has registers for one workgroup instead of two
+        if constexpr (ZEROS) asm volatile("" : "+v"(nz1), "+v"(nz2));
+      }
+    };
+    const int nvec = (int)(cols / 8);
+    for (int64_t row = (int64_t)blockIdx.x * 16 + wave; row < rows; row += (int64_t)gridDim.x * 16) {
+      const u32x4* const xr = reinterpret_cast<const u32x4*>(x + row * cols);
+      int i = lane;
+      for (; i + 3 * 64 < nvec; i += 4 * 64) {
+        const u32x4 r0 = xr[i], r1 = xr[i + 64], r2 = xr[i + 128], r3 = xr[i + 192];
+        visit_vec(r0); visit_vec(r1); visit_vec(r2); visit_vec(r3);
+      }
+      for (; i < nvec; i += 64) visit_vec(xr[i]);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the table is this wave's own
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < WIN_LDS / 64; ++j) {
+        const uint32_t v = t[lane + 64 * j];
+        t[lane + 64 * j] = 0;
+        sum[j] += v;
+        if (lane + 64 * j < WIN_BINS) row_bins[row * WIN_STRIDE + lane + 64 * j] = (uint16_t)v;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   };
-  const int nvec = (int)(cols / 8);
-  for (int64_t row = (int64_t)blockIdx.x * 16 + wave; row < rows; row += (int64_t)gridDim.x * 16) {
-    const u32x4* const xr = reinterpret_cast<const u32x4*>(x + row * cols);
-    int i = lane;
-    for (; i + 3 * 64 < nvec; i += 4 * 64) {
-      const u32x4 r0 = xr[i], r1 = xr[i + 64], r2 = xr[i + 128], r3 = xr[i + 192];
-      visit_vec(r0); visit_vec(r1); visit_vec(r2); visit_vec(r3);
-    }
-    for (; i < nvec; i += 64) visit_vec(xr[i]);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the table is this wave's own
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < WIN_LDS / 64; ++j) {
-      const uint32_t v = t[lane + 64 * j];
-      t[lane + 64 * j] = 0;
-      sum[j] += v;
-      if (lane + 64 * j < WIN_BINS) row_bins[row * WIN_STRIDE + lane + 64 * j] = (uint16_t)v;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
+  const bool zeros_apart = win.zeros_apart();
+  if (zeros_apart) all_rows(std::true_type{});
+  else all_rows(std::false_type{});
 #pragma unroll
   for (int j = 0; j < WIN_LDS / 64; ++j)
     if (sum[j]) atomicAdd(&total[lane + 64 * j], sum[j]);
+  if (zeros_apart) {
+    atomicAdd(&total[WIN_LDS], (uint32_t)nz1.x + nz1.y);
+    atomicAdd(&total[WIN_LDS + 1], (uint32_t)nz2.x + nz2.y);
+  }
   if (max(top.x, top.y) > 0x7f80) st->nan = 1;
   __syncthreads();
-  if (threadIdx.x < WIN_BINS && total[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)total[threadIdx.x]);
+  if (threadIdx.x < WIN_LDS + 2 && total[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)total[threadIdx.x]);
 }
 
 // The thresholds from the bins' totals, or the state that the general path starts from.
-__global__ __launch_bounds__(256) void win_pick_kernel(SelState* st, unsigned long long* hist, unsigned long long k, unsigned long long n,
-                                                       float* thresholds) {
-  __shared__ unsigned long long h[WIN_BINS];
+__global__ __launch_bounds__(WIN_LDS) void win_pick_kernel(SelState* st, unsigned long long* hist, unsigned long long k, unsigned long long n,
+                                                           float* thresholds) {
+  __shared__ unsigned long long s_w[WIN_LDS / 64];
   __shared__ uint32_t key[2], bin[2];
-  const int tid = threadIdx.x;
-  const uint32_t w0 = win_first(st, 0), w1 = win_first(st, 1);
-  if (tid < WIN_BINS) h[tid] = hist[tid];
-  if (tid < 2) bin[tid] = 0;
-  __syncthreads();
-  // thread 1 + j looks at the lower window's bin 1 + j and the upper one's 98 + j
-  if (tid >= 1 && tid <= WIN_KEYS && w0 + WIN_KEYS <= w1) {
-    unsigned long long below = 0, above = 0;
-    for (int b = 0; b < tid; ++b) below += h[b];
-    if (below <= k && k < below + h[tid]) { bin[0] = tid; key[0] = w0 + tid - 1; }
-    const int u = tid + WIN_KEYS + 1;
-    for (int b = u + 1; b < WIN_BINS; ++b) above += h[b];
-    if (above <= k && k < above + h[u]) { bin[1] = u; key[1] = w1 + tid - 1; }   // the (k + 1)-th from the top
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const Windows win(st);
+  const bool zeros_apart = win.zeros_apart();
+  unsigned long long v = tid < WIN_BINS ? hist[tid] : 0, neg = 0, pos = 0;
+  if (zeros_apart) {   // the sums of win_count_kernel, undone
+    const unsigned long long nz1 = hist[WIN_LDS], nz2 = hist[WIN_LDS + 1];
+    neg = n - nz1;
+    pos = 2 * nz1 - nz2;
+    if (tid == win.bin(KEY_NEG_ZERO)) v += neg;
+    if (tid == win.bin(KEY_POS_ZERO)) v += pos;
   }
+  if (tid == WIN_KEYS + 1) v = 0;
+  if (tid < 2) bin[tid] = 0;
+  unsigned long long incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) s_w[wave] = incl;
+  __syncthreads();
+  unsigned long long total = 0;   // without what lies between the windows
+  for (int w = 0; w < WIN_LDS / 64; ++w) {
+    if (w < wave) incl += s_w[w];
+    total += s_w[w];
+  }
+  const unsigned long long below = incl - v, above = total - incl;
+  const bool lower = tid >= 1 && tid <= WIN_KEYS, upper = tid >= WIN_KEYS + 2 && tid < WIN_BINS - 1, both = win.side_by_side();
+  const uint32_t mine = lower ? win.w0 + tid - 1 : win.w1 + tid - (WIN_KEYS + 2);
+  if ((lower || (upper && both)) && below <= k && k < incl) { bin[0] = tid; key[0] = mine; }
+  if ((upper || (lower && both)) && above <= k && k < above + v) { bin[1] = tid; key[1] = mine; }   // the (k + 1)-th from the top
   __syncthreads();
   if (tid == 0) {
-    // a zero's keys are 0x7fff and 0x8000
-    const bool ok = bin[0] && bin[1] && !st->nan && key[0] != 0x7fffu && key[0] != 0x8000u && key[1] != 0x7fffu && key[1] != 0x8000u;
+    // Rows' bins leave zeros out where they are counted apart: right while they are no outliers.
+    const bool ok = bin[0] && bin[1] && !st->nan && !(neg + pos && (key[0] > KEY_POS_ZERO || key[1] < KEY_NEG_ZERO));
     if (ok)
       for (int s = 0; s < 2; ++s) thresholds[s] = u2f(((key[s] & 0x8000u) ? (key[s] & 0x7fffu) : (~key[s] & 0xffffu)) << 16);
     st->done = ok;
@@ -346,7 +404,8 @@ __global__ __launch_bounds__(256) void win_pick_kernel(SelState* st, unsigned lo
     st->rank[1] = n - 1 - k;
     st->prefix[0] = st->prefix[1] = 0;
   }
-  if (tid < WIN_BINS) hist[tid] = 0;
+  hist[tid] = 0;
+  if (tid < 2) hist[WIN_LDS + tid] = 0;
 }
 
 // Outliers of each row: from its bins, or, where the windows were missed, from its elements.  A wave per row.
@@ -365,9 +424,14 @@ __global__ __launch_bounds__(256) void win_rows_kernel(const uint16_t* x, int64_
     }
   } else {
     const float lo = thr[0], hi = thr[1];
-    for (int64_t i = lane; i < cols; i += 64) {
-      const float v = u2f((uint32_t)x[row * cols + i] << 16);
-      cnt += ((v < lo) | (v > hi)) ? 1 : 0;
+    const u32x4* const xr = reinterpret_cast<const u32x4*>(x + row * cols);
+    for (int64_t i = lane; i < cols / 8; i += 64) {
+      const u32x4 r = xr[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = u2f(r[e] << 16), b = u2f(r[e] & 0xffff0000u);
+        cnt += (((a < lo) | (a > hi)) ? 1 : 0) + (((b < lo) | (b > hi)) ? 1 : 0);
+      }
     }
   }
 #pragma unroll
@@ -514,7 +578,7 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
   unsigned long long* hist =
       reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
   // the sample's ranks first
-  const int64_t ns = (int64_t)SAMPLE_BLOCKS * SAMPLE_VECS * 8;
+  const int64_t ns = (int64_t)SAMPLE_RUNS * 64 * 8;
   const unsigned long long ks = (unsigned long long)((double)k / (double)n * (double)ns);
   hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist, ks, (unsigned long long)ns, total);
   hipLaunchKernelGGL(sel_sample_kernel, dim3(SAMPLE_BLOCKS), dim3(SEL_THREADS), 0, s, reinterpret_cast<const u32x4*>(x), n / 8, hist);
