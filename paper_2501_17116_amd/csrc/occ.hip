@@ -126,13 +126,16 @@ FP4_D void sel_pick(SelState* st, unsigned long long* hist, int bits, int first,
   for (int i = tid; i < 2 * SEL_BINS; i += SEL_THREADS) hist[i] = 0;
 }
 
-// PICK: the workgroup that is done last picks the bins.
-template <class DT, bool FIRST, bool PICK>
+// PICK: the workgroup that is done last picks the bins.  BEHIND: launched behind the one pass of large tensors (below), which may
+// have left nothing to do; elsewhere nothing is asked before the first element is requested.
+template <class DT, bool FIRST, bool PICK, bool BEHIND>
 __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, int64_t rows, int64_t cols,
                                                        int64_t ld, int shift, int bits, int pass, int last, int key_bits,
                                                        SelState* st, unsigned long long* hist, float* thresholds) {
   constexpr bool first = FIRST;
-  if (st->done) return;
+  if constexpr (BEHIND) {
+    if (st->done) return;
+  }
   __shared__ uint32_t h[8 * SEL_BINS];   // first pass: 8 replicas; later: 4 replicas x 2 targets
   for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
   __syncthreads();
@@ -205,7 +208,6 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, in
 
 __global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, unsigned long long* hist, int bits, int first, int last,
                                                                int key_bits, float* thresholds) {
-  if (st->done) return;
   sel_pick(st, hist, bits, first, last, key_bits, thresholds);
 }
 
@@ -518,9 +520,9 @@ size_t fp4_select_scratch_bytes() {
 }
 
 namespace {
-// The digit passes, from the state that sel_init_kernel (or win_pick_kernel) left.
+// The digit passes, from the state that sel_init_kernel left, or (behind) win_pick_kernel.
 void launch_digits(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, float* thresholds, SelState* st, unsigned long long* hist,
-                   bool seldom, hipStream_t s) {
+                   bool behind, hipStream_t s) {
   const int64_t n = rows * cols;
   const int key_bits = bf16 ? 16 : 32;
   int digits[3];
@@ -530,16 +532,19 @@ void launch_digits(const void* x, int bf16, int64_t rows, int64_t cols, int64_t 
   int shift = key_bits;
   const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
-  const bool pick_here = seldom || grid <= SEL_PICK_HERE;   // launches that mostly leave at once: as few as there can be
+  const bool pick_here = behind || grid <= SEL_PICK_HERE;   // launches that mostly leave at once: as few as there can be
   for (int p = 0; p < nd; ++p) {
     shift -= digits[p];
-    auto launch = [&](auto dt, auto first, auto pick) {
-      hipLaunchKernelGGL((sel_hist_kernel<decltype(dt), decltype(first)::value, decltype(pick)::value>), dim3(grid), dim3(SEL_THREADS), 0, s, x, rows, cols, ld,
-                         shift, digits[p], p, p == nd - 1, key_bits, st, hist, thresholds);
+    auto launch = [&](auto dt, auto first, auto pick, auto after) {
+      hipLaunchKernelGGL((sel_hist_kernel<decltype(dt), decltype(first)::value, decltype(pick)::value, decltype(after)::value>), dim3(grid),
+                         dim3(SEL_THREADS), 0, s, x, rows, cols, ld, shift, digits[p], p, p == nd - 1, key_bits, st, hist, thresholds);
     };
     auto pass = [&](auto dt, auto first) {
-      if (pick_here) launch(dt, first, std::true_type{});
-      else launch(dt, first, std::false_type{});
+      if constexpr (__is_same(decltype(dt), BF16)) {
+        if (behind) return launch(dt, first, std::true_type{}, std::true_type{});
+      }
+      if (pick_here) launch(dt, first, std::true_type{}, std::false_type{});
+      else launch(dt, first, std::false_type{}, std::false_type{});
     };
     if (p == 0) { if (bf16) pass(BF16{}, std::true_type{}); else pass(F32{}, std::true_type{}); }
     else { if (bf16) pass(BF16{}, std::false_type{}); else pass(F32{}, std::false_type{}); }
