@@ -31,11 +31,12 @@ int fp4_device_round_codes(const float* x, int64_t n, uint8_t* codes, void* stre
 int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 
 /* Output tiles the FP4 GEMM [P x Q], contraction Kc, is cut into on a device with that many compute units, by the rule its launches
- * follow (host arithmetic, no GPU): 64, 128 or 256 rows and columns; with 256, *last_round (may be NULL) is the number of
- * tiles of the last round that are cut into 128 x 128 ones, otherwise 0.  factor: the weight gradient's derivative factor
+ * follow (host arithmetic, no GPU): 64, 128 or 256 rows and columns.  With 256, *last_round is the number of tiles of the
+ * last round that are cut into 128 x 128 ones and *stagger how much later than the one before each quarter of the workgroups
+ * begins, in 512 cycles; otherwise 0 (either may be NULL).  factor: the weight gradient's derivative factor
  * with weights in bf16 (w_bf16) or fp32; addend: whether there is one; out_bf16: the output's type. */
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
-                    int* last_round);
+                    int* last_round, int* stagger);
 
 /* ---- ceilings measured on the part (for reading the rooflines; not part of the method) ----
  * fp4_probe_mfma: `workgroups` workgroups of 8 waves each run `iters` iterations of 8 FP4

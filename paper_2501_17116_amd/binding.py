@@ -98,7 +98,7 @@ def lib() -> C.CDLL:
         L.fp4_probe_mfma.restype = i32
         L.fp4_probe_copy.argtypes = [vp, vp, i64, vp]
         L.fp4_probe_copy.restype = i32
-        L.fp4_gemm_tiling.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32, vp]
+        L.fp4_gemm_tiling.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32, vp, vp]
         L.fp4_gemm_tiling.restype = i32
         L.fp4_trace_begin.argtypes = [i32]
         L.fp4_trace_begin.restype = i32
@@ -560,14 +560,15 @@ FP4_TRACE_GEMM, FP4_TRACE_SPMM = 0, 1
 
 
 def fp4_gemm_tiling(P: int, Q: int, Kc: int, factor: bool = False, w_bf16: bool = False, addend: bool = False,
-                    out_bf16: bool = False, compute_units: int = 256) -> Tuple[int, int]:
-    """Tile size of the FP4 GEMM and how many tiles of a last round are cut smaller (host arithmetic, no GPU)."""
-    last_round = C.c_int(0)
+                    out_bf16: bool = False, compute_units: int = 256) -> Tuple[int, int, int]:
+    """Tile size of the FP4 GEMM, how many tiles of a last round are cut smaller, and the delay between quarters of the
+    workgroups (host arithmetic, no GPU)."""
+    last_round, stagger = C.c_int(0), C.c_int(0)
     tile = lib().fp4_gemm_tiling(P, Q, Kc, int(factor), int(w_bf16), int(addend), int(out_bf16), compute_units,
-                                 C.byref(last_round))
+                                 C.byref(last_round), C.byref(stagger))
     if tile < 0:
         _check(tile, "fp4_gemm_tiling")
-    return tile, last_round.value
+    return tile, last_round.value, stagger.value
 
 
 def fp4_trace_begin(max_launches: int) -> None:

@@ -1047,10 +1047,11 @@ extern "C" int fp4_gemm(const uint8_t* codes_l, const float* gamma_l, const uint
 }
 
 extern "C" int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
-                               int* last_round) {
+                               int* last_round, int* stagger) {
   if (P <= 0 || Q <= 0 || Kc < 0 || (Kc % 32) != 0 || compute_units < 8) return FP4_ERR_SHAPE;
   const GemmTiling t = gemm_tiling(P, Q, Kc, factor != 0, w_bf16 != 0, addend != 0, out_bf16 != 0, compute_units);
   if (last_round) *last_round = t.rest;
+  if (stagger) *stagger = t.stagger;
   return t.tile;
 }
 

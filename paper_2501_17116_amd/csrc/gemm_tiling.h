@@ -83,8 +83,14 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
   // add, convert and store.  Four quarters 3.4 us apart overlap the two where an epilogue moves much (addend, fp32
   // output) and a workgroup has enough tiles to make up for it, or those that have one less can be the late ones
   // (16384 x 12288 x 4096 with addend 603 -> 561 us, 16384 x 4096 x 2048 151 -> 137, 5120 x 13824 x 4096 fp32 258 -> 246, 4096 x
-  // 11008 x 4096 131 -> 127; three full rounds 410 -> 415, bf16 without addend 353 -> 359).
+  // 11008 x 4096 131 -> 127; three full rounds 410 -> 415, bf16 without addend 353 -> 359).  It stays off where it lost: fp32
+  // outputs in whole rounds with nothing behind them (1024 tiles, 256 / 512 / 1024 codes 66 -> 71, 74 -> 80, 89 -> 94; 1536, 2048 codes
+  // with addend 262 -> 270; with 64 cut tiles behind, 1024 codes, 101 -> 85), the factor with fp32 weights (736 tiles, 256 codes 142 -> 148, else within 2 %), and at short contractions nearly three rounds (736
+  // tiles, 256: bf16 with addend 62 -> 63, factor 94 -> 98, 1024: factor 107 -> 109) and the factor without addend (1088, 256: 141 -> 146).
   const int64_t full = total - t.rest;
-  t.stagger = (addend || !out_bf16) && (full > 3 * wgs || (full > 2 * wgs && 8 * full <= 23 * (int64_t)wgs)) ? 15 : 0;
+  const bool whole = full % wgs == 0 && t.rest == 0, short_k = Kc < 1024;
+  const bool rounds = full > 3 * wgs || (full > 2 * wgs && 8 * full <= (Kc < (factor ? 2048 : 1024) ? 21 : 23) * (int64_t)wgs);
+  const bool gains = factor ? w_bf16 && (addend || !short_k) : out_bf16 ? addend : !whole;
+  t.stagger = rounds && gains ? 15 : 0;
   return t;
 }

@@ -13,7 +13,7 @@ def test_rows_stay_within_the_offsets(row_bytes):
     """Whatever the output's size and type, a staged tile's rows can be addressed."""
     for P, Q in itertools.product((64, 256, 4096, 40000), (64, 2048, 40000)):
         for factor, w_bf16, addend, out_bf16 in itertools.product((0, 1), repeat=4):
-            tile, last_round = b.fp4_gemm_tiling(P, Q, 2 * row_bytes, factor, w_bf16, addend, out_bf16)
+            tile, last_round, _ = b.fp4_gemm_tiling(P, Q, 2 * row_bytes, factor, w_bf16, addend, out_bf16)
             assert tile == 64 or row_bytes * tile <= LIMIT, (P, Q, tile)
             assert last_round == 0 or tile == 256
 
@@ -21,7 +21,7 @@ def test_rows_stay_within_the_offsets(row_bytes):
 @pytest.mark.parametrize("P,Q", [(1, 8), (4096, 4096), (40000, 40000)])
 def test_an_empty_contraction_runs_where_nothing_is_requested_ahead(P, Q):
     for factor, w_bf16, addend, out_bf16 in itertools.product((0, 1), repeat=4):
-        assert b.fp4_gemm_tiling(P, Q, 0, factor, w_bf16, addend, out_bf16) == (64, 0)
+        assert b.fp4_gemm_tiling(P, Q, 0, factor, w_bf16, addend, out_bf16) == (64, 0, 0)
 
 
 # (P, Q, Kc, factor, w_bf16, addend, tile): either side of the lines, and shapes that were measured far from them
@@ -47,3 +47,19 @@ LINES = [
 @pytest.mark.parametrize("P,Q,Kc,factor,w_bf16,addend,tile", LINES)
 def test_tiles(P, Q, Kc, factor, w_bf16, addend, tile):
     assert b.fp4_gemm_tiling(P, Q, Kc, factor, w_bf16, addend, 0, 256)[0] == tile
+
+
+# (P, Q, Kc, factor, w_bf16, addend, out_bf16, whether the workgroups begin in quarters)
+STAGGER = [
+    (8192, 4864, 2048, 0, 0, 1, 1, True), (8192, 4864, 2048, 0, 0, 0, 1, False), (8192, 4864, 2048, 0, 0, 0, 0, True),   # 2.4 rounds
+    (16384, 4096, 1024, 0, 0, 0, 0, False), (16384, 6144, 2048, 0, 0, 1, 0, False), (16384, 4096, 1024, 0, 0, 1, 1, True),   # whole rounds
+    (16384, 4352, 1024, 0, 0, 0, 0, True),                                                                              # and cut tiles behind
+    (8192, 5888, 256, 0, 0, 1, 1, False), (8192, 5888, 2048, 0, 0, 1, 1, True), (8192, 6144, 2048, 0, 0, 1, 1, False),   # nearly three rounds, three
+    (8192, 5888, 4096, 1, 0, 1, 0, False), (16384, 4352, 256, 1, 1, 0, 0, False), (16384, 4352, 2048, 1, 1, 0, 0, True),     # the factor
+    (8192, 2048, 4096, 0, 0, 1, 1, False),                                                                               # 128 x 128 tiles
+]
+
+
+@pytest.mark.parametrize("P,Q,Kc,factor,w_bf16,addend,out_bf16,on", STAGGER)
+def test_late_workgroups(P, Q, Kc, factor, w_bf16, addend, out_bf16, on):
+    assert (b.fp4_gemm_tiling(P, Q, Kc, factor, w_bf16, addend, out_bf16)[2] > 0) == on
