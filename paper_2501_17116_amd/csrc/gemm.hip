@@ -948,9 +948,11 @@ __global__ void fp4_unpack_kernel(const uint8_t* codes, int64_t nbytes, uint8_t*
   }
 }
 
-// Compute units of the device the launch goes to (one persistent workgroup each).  Looked up once
+}  // namespace
+
+// Compute units of the device the launch goes to (here one persistent workgroup each).  Looked up once
 // per device; concurrent first calls write the same value.
-int compute_units_of_current_device() {
+int fp4_compute_units_of_current_device() {
   static int cached[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
@@ -961,8 +963,6 @@ int compute_units_of_current_device() {
   }
   return n;
 }
-
-}  // namespace
 
 // Internal launcher shared by fp4_gemm and the layer entry points.
 int fp4_trace_open(int kind, hipStream_t stream);
@@ -979,7 +979,7 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   g.tiles_p = (int)((P + BM - 1) / BM);
   g.tiles_q = (int)((Q + BN - 1) / BN);
   const bool dge = W != nullptr && dge_k > 0.0f;
-  const int n_cu = compute_units_of_current_device();
+  const int n_cu = fp4_compute_units_of_current_device();
   const GemmTiling t = gemm_tiling(P, Q, Kc, dge, w_bf16 != 0, addend != nullptr, out_bf16 != 0, n_cu);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
   const bool ragged = (g.Kb % BKB) != 0, small = t.tile == 64, mid = t.tile == 128;

@@ -10,10 +10,10 @@
 // At that density neither a dense matrix-core product (50x wasted work) nor a row gather
 // (every non-zero re-reads a row of D from L2) is acceptable, so the product of fp32 D is tiled the way
 // a dense GEMM is, with plain fp32 FMAs:
-//   * a workgroup of 1024 threads owns 1024 rows of R x 64 columns, one row per thread, the
-//     64 accumulators in registers;
+//   * a workgroup of 1024 threads (512 where those go round the chip once) owns as many rows of R x 64 columns, one row per
+//     thread, the 64 accumulators in registers;
 //   * D is staged through LDS in slabs of 512 rows x 64 columns, widened to fp32 once per slab,
-//     so a D element is fetched from L2 once per 1024 output rows;
+//     so a D element is fetched from L2 once per 1024 (512) output rows;
 //   * a thread walks its row's entries (ascending columns) slab by slab: per non-zero 64 FMAs
 //     against one LDS row.
 // Rows much longer than the rest (the outlier channels of the transposed residual, spmm_long_limit) would
@@ -993,6 +993,7 @@ __global__ __launch_bounds__(256) void csr_bitmap_sort_kernel(const int64_t* seg
 }  // namespace
 
 // ---- launchers ---------------------------------------------------------------------------------
+int fp4_compute_units_of_current_device();
 int fp4_trace_open(int kind, hipStream_t stream);
 void fp4_trace_close(int slot, hipStream_t stream);
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q);
@@ -1040,7 +1041,7 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
       // but a CU's gathers go twice as fast (1024 / 512 / 256 rows, with the long rows' launches, at 2 %: 2048^3 72 / 56 / 58 us,
       // 2500 x 2048 -> 3000 76 / 66 / 99, 1024^3 43 / 32 / 32; beyond one round 3072^3 104 / 142 / 184).
       const int64_t half = (P + SP_ROWS / 2 - 1) / (SP_ROWS / 2);
-      if (half * grid.y <= 256)
+      if (half * grid.y <= fp4_compute_units_of_current_device())
         hipLaunchKernelGGL((spmm_tile_kernel<F32, SP_ROWS / 2>), dim3((unsigned)half, grid.y), dim3(SP_ROWS / 2), 0, s, row_ptr, col_idx, val,
                            capacity, P, Q, D, N, R);
       else
