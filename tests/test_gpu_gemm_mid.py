@@ -33,6 +33,32 @@ def test_products(P, Q, K):
     assert torch.equal(b.fp4_gemm(L, gl, R, gr, addend=addend), scaled + addend)
 
 
+@pytest.mark.parametrize("P,Q,K", [(33, 8, 1536), (127, 136, 1792), (128, 128, 6176), (129, 264, 6208), (127, 392, 6304), (1, 8, 12320)])
+def test_edges_of_a_tile(P, Q, K):
+    """Contractions long enough for 128 x 128 tiles however few there are."""
+    from paper_2501_17116_amd import binding as b
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert b.fp4_gemm_tiling(P, Q, K)[0] == 128
+    test_products(P, Q, K)
+
+
+@pytest.mark.parametrize("P,Q,K", [(4352, 4352, 544), (4104, 4360, 1024), (4224, 4360, 288), (2056, 8456, 96)])
+def test_a_last_round_in_quarters_gives_the_same_bits(P, Q, K):
+    """Under scales of any value: the rows of a problem twice as high, whose 256 x 256 tiles are all left whole."""
+    from paper_2501_17116_amd import binding as b
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert b.fp4_gemm_tiling(P, Q, K)[:2] > (256, 0) and b.fp4_gemm_tiling(2 * P, Q, K)[:2] == (256, 0)
+    g = torch.Generator(device="cuda").manual_seed(P + Q + K)
+    L = torch.randint(0, 256, (2 * P, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    R = torch.randint(0, 256, (Q, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    gl, gr = torch.rand(2 * P, generator=g, device="cuda") + 0.5, torch.rand(Q, generator=g, device="cuda") + 0.5
+    addend = torch.randn(2 * P, Q, generator=g, device="cuda")
+    for dt in (torch.float32, torch.bfloat16):
+        for ad in (None, addend):
+            cut = b.fp4_gemm(L[:P], gl[:P], R, gr, out_dtype=dt, addend=None if ad is None else ad[:P])
+            assert torch.equal(cut, b.fp4_gemm(L, gl, R, gr, out_dtype=dt, addend=ad)[:P])
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("M,K,N", [(96, 1280, 1288), (1056, 1376, 2080), (2080, 1056, 2056), (2048, 2048, 2048), (1056, 3104, 3080), (544, 4128, 4112)])
 def test_weight_gradient_with_the_factor(M, K, N, dtype):

@@ -1,6 +1,6 @@
-"""The FP4 GEMM's small-tile kernel at the edges of its tiles and of the rule that selects it: against the exact
-integer product (raw accumulators) and, scaled, bit for bit against a problem large enough for the 256 x 256 tiles that
-holds the same rows and columns."""
+"""The FP4 GEMM's small-tile kernel at the edges of its tiles, and products on either side of the lines between it and the
+128 x 128 tiles: against the exact integer product (raw accumulators) and, scaled, bit for bit against a problem large enough
+for the 256 x 256 tiles that holds the same rows and columns."""
 import pytest
 import torch
 
@@ -35,9 +35,10 @@ def test_small_tiles(P, Q, K):
 
 
 @pytest.mark.parametrize("M,K,N", [(3072, 2048, 2048), (3104, 2048, 2048), (6144, 2048, 1024), (6176, 2048, 1024), (32, 64, 72)])
-def test_fp32_factor_on_both_sides_of_the_contraction_limit(M, K, N):
-    """The weight gradient with fp32 masters against its parts called one by one (the factor as a pass of its own): the
-    product is the same to the last bit, the factor one rounding of fp32 in either."""
+def test_fp32_factor(M, K, N):
+    """The weight gradient with fp32 masters, on 128 x 128 tiles in rounds and part rounds and on one of 64 x 64, against its
+    parts called one by one (the factor as a pass of its own): the product is the same to the last bit, the factor one
+    rounding of fp32 in either."""
     from paper_2501_17116_amd import binding as b
     torch.manual_seed(M + N)
     A, W, dY = torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda") * 0.02, torch.randn(M, N, device="cuda")
@@ -81,7 +82,7 @@ def test_either_side_of_the_lines_between_the_tilings(P, Q, K, tile):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("M,K,N", [(3072, 512, 2048), (3328, 512, 2048), (768, 520, 2048), (1024, 520, 2048), (256, 1032, 2048), (512, 1032, 2048),
-                                   (6016, 1024, 832), (8480, 512, 512), (1312, 520, 2048), (2400, 1280, 1280), (1184, 1032, 2048),
+                                   (6016, 1024, 832), (8480, 512, 512), (8480, 264, 136), (3328, 136, 264), (1312, 520, 2048), (2400, 1280, 1280), (1184, 1032, 2048),
                                    (1376, 1032, 2048), (1408, 1032, 2048), (640, 672, 5496), (672, 672, 5496)])
 def test_factor_on_either_side_of_the_lines(M, K, N, dtype):
     """The weight gradient against its parts called one by one: the product is the same to the last bit, the factor one
