@@ -217,9 +217,10 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, uns
 // row's bins: with the thresholds known, a row's outliers are a sum over those.  Where a threshold turns out not to lie in
 // its window, or a NaN is about, `done` stays 0 and the passes of the general path, launched behind, do their work; otherwise
 // they leave at once.
-// Bound by the one read and, about as long, by vector instructions (nine an element).  16384 x 11008, in us: init 4.5, sample 6.4,
-// picks 5.0 + 5.9, the pass 96.9, the general path's two launches 9, rows 4.8, together 133; digit passes, picks and the count of
-// the rows after them 249.  16384 x 4096: 74 against 107.  Below 2^25 elements the launches cost what the pass saves (8192 x
+// Bound by the one read and, about as long, by vector instructions (nine an element, twelve where zeros are counted apart).
+// 16384 x 11008, in us: init 4.6, sample 6.6, picks 4.8 + 4.7, the pass 94.7, the general path's two launches 9, rows 4.9, together
+// 130; digit passes, picks and the count of the rows after them 249.  16384 x 4096: 71 against 107.  With scan and emission: half
+// zeros, 16384 x 11008, 250 against 540; a miss 419 against 353.  Below 2^25 elements the launches cost what the pass saves (8192 x
 // 2048: digit passes, picks and count 43, of which this would leave 40).
 constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STRIDE = 200;   // bins; a wave's table; a row's in memory
 constexpr uint32_t KEY_NEG_ZERO = 0x7fff, KEY_POS_ZERO = 0x8000;
