@@ -226,8 +226,8 @@ constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STR
 constexpr uint32_t KEY_NEG_ZERO = 0x7fff, KEY_POS_ZERO = 0x8000;
 constexpr int SAMPLE_BLOCKS = 128, SAMPLE_RUNS = SAMPLE_BLOCKS * 2 * (SEL_THREADS / 64);   // runs of 64 16-byte vectors
 
-// 4096 runs of 512 elements, evenly spaced.  As many elements in 128 runs were a few hundred whole rows: of tensors with a hundred
-// large rows in thousands (first tokens of a sequence), or rows that differ in scale, it missed the windows of one in seven.
+// 4096 runs of 512 elements, evenly spaced.  As many elements in 128 runs were a few hundred whole rows: of 216 tensors and alphas
+// (large rows or channels, first tokens 1000 times as large, rows or channels that differ in scale) the windows missed 20, now 1.
 __global__ __launch_bounds__(SEL_THREADS) void sel_sample_kernel(const u32x4* x, int64_t nvec, unsigned long long* hist) {
   __shared__ uint32_t h[8 * SEL_BINS];
   for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
