@@ -38,6 +38,11 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
+/* fp4_residual_spmm by the kernels that large products take, whatever the size: same arguments, workspace and result (sums in
+ * another order). */
+int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t P, int64_t Q, const void* D,
+                              fp4_dtype dt, int64_t N, float* R, void* workspace, size_t workspace_bytes, void* stream);
+
 /* ---- ceilings measured on the part (for reading the rooflines; not part of the method) ----
  * fp4_probe_mfma: `workgroups` workgroups of 8 waves each run `iters` iterations of 8 FP4
  *   32x32x64 MFMAs per wave with operands taken from operand_bytes (device, >= 16 bytes): an

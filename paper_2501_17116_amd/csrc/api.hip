@@ -3,6 +3,7 @@
 // memory or synchronizes; every buffer is the caller's, every kernel goes to the caller's stream,
 // and the library keeps no state between calls.
 #include "fp4_common.h"
+#include "fp4_measure.h"
 
 #include <algorithm>
 #include <cmath>
@@ -69,7 +70,7 @@ int fp4_launch_order_rows(const int64_t* row_ptr, int64_t rows, int64_t nidx, in
 int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16);
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    hipStream_t s);
+                    hipStream_t s, bool general = false);
 
 namespace {
 
@@ -680,9 +681,9 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
                          dge_cap, s);
 }
 
-extern "C" int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
-                                 int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
-                                 void* workspace, size_t workspace_bytes, void* stream) {
+namespace {
+int residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t P, int64_t Q, const void* D, fp4_dtype dt,
+                  int64_t N, float* R, void* workspace, size_t workspace_bytes, void* stream, bool general) {
   if (!dtype_ok(dt)) return FP4_ERR_DTYPE;
   if (P < 0 || Q < 0 || N < 0 || (N % 8) != 0) return FP4_ERR_SHAPE;
   if (P == 0 || N == 0) return FP4_OK;
@@ -692,5 +693,18 @@ extern "C" int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx,
   int32_t* scratch = reinterpret_cast<int32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
   // no entry limit besides row_ptr itself
   return fp4_launch_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt == FP4_BF16, N, R, scratch,
-                         (hipStream_t)stream);
+                         (hipStream_t)stream, general);
+}
+}  // namespace
+
+extern "C" int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
+                                 int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
+                                 void* workspace, size_t workspace_bytes, void* stream) {
+  return residual_spmm(row_ptr, col_idx, val, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, false);
+}
+
+extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
+                                         int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
+                                         void* workspace, size_t workspace_bytes, void* stream) {
+  return residual_spmm(row_ptr, col_idx, val, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, true);
 }

@@ -4,10 +4,10 @@
 // and the CSR transpose the weight-gradient pass needs (Delta_A^T dY).  bf16 D goes to the matrix cores
 // (spmm_mfma.hip) as far as that path's 32-bit offsets and packing tables reach (24576 columns of S, 3.5 GiB of D) and
 // as the matrix's entries are worth packing, which its packing decides on the device; the tiled kernel here takes fp32 D
-// and the rest.
+// and the rest.  Small products of either type are one launch that gathers rows of D from L2 (spmm_gather.hip).
 //
 // S has density 2(1 - alpha) (about 2 %), scattered, plus a few nearly dense outlier channels.
-// At that density neither a dense matrix-core product (50x wasted work) nor a row gather
+// At that density and a large size neither a dense matrix-core product (50x wasted work) nor a row gather
 // (every non-zero re-reads a row of D from L2) is acceptable, so the product of fp32 D is tiled the way
 // a dense GEMM is, with plain fp32 FMAs:
 //   * a workgroup of 1024 threads (512 where those go round the chip once) owns as many rows of R x 64 columns, one row per
@@ -1000,6 +1000,8 @@ int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q);
 int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P,
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
                          SpmmRest& rest, hipStream_t s);
+int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
+                           const void* D, int bf16, int64_t N, float* R, hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
 // the fp32 partial sums of the dense long-row path, [spans][long rows][N], at most LD_CAP x slices rows of N, then (bf16 D)
 // the packed matrix.
@@ -1014,9 +1016,10 @@ int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16) {
   return spmm_long_words(P, Q, N) + (bf16 ? (fp4_spmm_mfma_scratch_bytes(P, Q) + 3) / 4 : 0);
 }
 
+// general: by the kernels that large products take, whatever the size
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    hipStream_t s) {
+                    hipStream_t s, bool general) {
   if (P == 0 || N == 0) return FP4_OK;
   if (Q >= ((int64_t)1 << 21)) return FP4_ERR_SHAPE;   // 32-bit entry offsets inside a workgroup's 1024 rows
   const bool may_be_long = Q > SPMM_LONG_MIN && capacity > SPMM_LONG_MIN;   // otherwise no row is
@@ -1024,7 +1027,11 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   int32_t* const list = scratch + 64;
   const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
   const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);   // the whole product, as its entries are counted
-  int rc = 1;
+  int rc = general ? 1 : fp4_launch_spmm_gather(row_ptr, col_idx, val, capacity, P, Q, D, bf16, N, R, s);
+  if (rc != 1) {
+    fp4_trace_close(trace_slot, s);
+    return rc;
+  }
   SpmmRest rest{nullptr, nullptr, 0};
   if (bf16)
     rc = fp4_launch_spmm_mfma(row_ptr, col_idx, val, capacity, P, Q, D, N, R, scratch + spmm_long_words(P, Q, N), list, count, rest, s);

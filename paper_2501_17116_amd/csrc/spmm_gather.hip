@@ -1,0 +1,188 @@
+// The residual product R[P x N] = S D of a small layer: one launch, no packing, no staging, no list of long rows.
+//
+// The packed and the tiled kernels (spmm_mfma.hip, spmm.hip) are four launches, and what they stage, plan and list pays where a
+// row of D is used again and again.  In a small product the launches are most of it and D fits the L2s: here every entry
+// gathers its piece of D from L2, GA_AHEAD requests of 1 KiB on their way a wave, and plain FMAs add it up.
+#include "fp4_common.h"
+#include "spmm_long.h"
+
+#include <type_traits>
+
+namespace {
+
+struct BF16 {};
+struct F32 {};
+
+constexpr int GA_AHEAD = 8;
+
+// LANES lanes have an entry's piece of D, 16 bytes each; a request of a wave brings the pieces of 64 / LANES entries.  A
+// workgroup has ROWS rows of a strip of columns, WAVES / ROWS waves a row; rows of more than the limit are shared by all its
+// waves.  The waves of a row take a contiguous part of its entries each, and the parts are added in that order.
+template <class DT, int LANES, int WAVES, int ROWS>
+__global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
+                                                                 const float* __restrict__ val, int64_t capacity, int64_t P, int row_blocks,
+                                                                 int items, int Q, const uint8_t* __restrict__ D, int64_t N,
+                                                                 float* __restrict__ R) {
+  static_assert(WAVES % ROWS == 0 && ROWS < 64, "whole waves a row, a lane a row");
+  constexpr int ES = __is_same(DT, BF16) ? 2 : 4, PER = 16 / ES, COLS = LANES * PER, SIDE = 64 / LANES, SHARE = WAVES / ROWS;
+  __shared__ __attribute__((aligned(16))) float sums[WAVES][SIDE][COLS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Workgroup i runs on XCD i % 8, and each XCD takes a contiguous run of items, rows inside columns: its L2 then holds the
+  // one strip of D that its workgroups gather from.
+  const int per_xcd = (items + 7) / 8;
+  const int item = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per_xcd || item >= items) return;
+  const int64_t row0 = (int64_t)(item % row_blocks) * ROWS;
+  const int64_t n0 = (int64_t)(item / row_blocks) * COLS;
+  const int side = lane / LANES, l = lane % LANES;
+  // What an entry past the last or a column past N would ask for lies past the descriptor's end and arrives as zero: no branch between
+  // the requests, which would each wait for the one before.
+  constexpr uint32_t NOWHERE = 0xf0000000u;
+  const uint32_t rowb = (uint32_t)(N * ES);
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(D), 0, (int)((uint32_t)Q * rowb), 0x00020000);
+  const bool in_n = n0 + l * PER < N;   // N is a multiple of 8
+  const uint32_t at = in_n ? (uint32_t)(n0 + l * PER) * ES : NOWHERE;
+  // This wave's sums over the entries [b, e), left in its part of `sums`.  Each turn's 64 entries are added up by themselves: an
+  // outlier channel's row in one chain is further off than the sums it replaces.
+  auto gather = [&](int64_t b, int64_t e) {
+    float sum[PER] = {};
+    for (int64_t i0 = b; i0 < e; i0 += 64) {
+      const int here = (int)min(e - i0, (int64_t)64);
+      int c = -1;   // of no entry; other columns that D has not are left out like it
+      float v = 0.0f;
+      if (lane < here) {
+        c = col_idx[i0 + lane];
+        v = val[i0 + lane];
+      }
+      const bool is = (uint32_t)c < (uint32_t)Q;
+      const uint32_t off = is ? (uint32_t)c * rowb : NOWHERE;
+      if (!is) v = 0.0f;
+      float acc[PER] = {};
+      for (int j = 0; j < here; j += GA_AHEAD * SIDE) {
+        u32x4 p[GA_AHEAD];
+#pragma unroll
+        for (int u = 0; u < GA_AHEAD; ++u) {
+          if constexpr (SIDE == 1) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)off, j + u);
+            p[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at | (o == NOWHERE ? NOWHERE : 0u), o == NOWHERE ? 0u : o, 0);
+          } else {
+            const uint32_t o = (uint32_t)__shfl((int)off, j + u * SIDE + side, 64);
+            p[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, o == NOWHERE || !in_n ? NOWHERE : at + o, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < GA_AHEAD; ++u) {
+          float vu;
+          if constexpr (SIDE == 1) vu = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(v), j + u));
+          else vu = __shfl(v, j + u * SIDE + side, 64);
+#pragma unroll
+          for (int k = 0; k < PER; ++k) {
+            float d;
+            if constexpr (ES == 2) d = u2f((k & 1) ? p[u][k >> 1] & 0xffff0000u : p[u][k >> 1] << 16);
+            else d = u2f(p[u][k]);
+            acc[k] = fmaf(vu, d, acc[k]);
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < PER; ++k) sum[k] += acc[k];
+    }
+#pragma unroll
+    for (int h = 0; h < PER / 4; ++h)
+      *reinterpret_cast<f32x4*>(&sums[wave][side][l * PER + 4 * h]) = f32x4{sum[4 * h], sum[4 * h + 1], sum[4 * h + 2], sum[4 * h + 3]};
+  };
+  // The rows' ends, a lane each; every wave has them all, so all come to the same answer without a word.
+  const int64_t rp = min(row_ptr[min(row0 + min(lane, ROWS), P)], capacity);
+  const int64_t next = __shfl_down(rp, 1, 64);
+  const int n_lane = lane < ROWS ? (int)max(next - rp, (int64_t)0) : 0;
+  const int64_t limit = max((int64_t)64, 4 * (min(row_ptr[P], capacity) - row_ptr[0]) / P);
+  const uint64_t long_rows = __ballot(n_lane > limit);
+  auto part = [&](int r, int i, int of) {   // the i-th part of row r's entries
+    const int64_t first = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(rp >> 32), r) << 32 |
+                                    (uint32_t)__builtin_amdgcn_readlane((int)rp, r));
+    const int64_t n = __builtin_amdgcn_readlane(n_lane, r);
+    gather(first + n * i / of, first + n * (i + 1) / of);
+  };
+  for (uint64_t m = long_rows; m != 0; m &= m - 1) {
+    const int r = __builtin_ctzll(m);
+    part(r, wave, WAVES);
+    __syncthreads();
+    for (int t = tid; t < COLS; t += WAVES * 64) {
+      float s = 0.0f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w)
+#pragma unroll
+        for (int h = 0; h < SIDE; ++h) s += sums[w][h][t];
+      if (n0 + t < N) R[(row0 + r) * N + n0 + t] = s;
+    }
+    __syncthreads();   // the sums are read
+  }
+  const int mine = wave / SHARE;
+  const bool shared_row = (long_rows >> mine) & 1;
+  if (!shared_row) part(mine, wave % SHARE, SHARE);
+  if constexpr (SHARE == 1) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the sums are this wave's own
+    __builtin_amdgcn_wave_barrier();
+    if (shared_row || row0 + mine >= P) return;
+#pragma unroll
+    for (int t = lane * 4; t < COLS; t += 256) {
+      f32x4 s = *reinterpret_cast<const f32x4*>(&sums[wave][0][t]);
+#pragma unroll
+      for (int h = 1; h < SIDE; ++h) s += *reinterpret_cast<const f32x4*>(&sums[wave][h][t]);
+      if (n0 + t < N) *reinterpret_cast<f32x4*>(R + (row0 + mine) * N + n0 + t) = s;
+    }
+  } else {
+    __syncthreads();
+#pragma unroll
+    for (int t = tid * 4; t < ROWS * COLS; t += WAVES * 256) {
+      const int r = t / COLS, c = t % COLS;
+      f32x4 s = *reinterpret_cast<const f32x4*>(&sums[r * SHARE][0][c]);
+#pragma unroll
+      for (int h = 1; h < SHARE * SIDE; ++h) s += *reinterpret_cast<const f32x4*>(&sums[r * SHARE + h / SIDE][h % SIDE][c]);
+      if (!((long_rows >> r) & 1) && row0 + r < P && n0 + c < N) *reinterpret_cast<f32x4*>(R + (row0 + r) * N + n0 + c) = s;
+    }
+  }
+}
+
+}  // namespace
+
+// Returns 1 where the packed or the tiled kernel is the better one.
+//
+// The gathers move entries x N x the size of an element through the L2s, at about 20 TB/s while a strip of D stays in one (2048^3,
+// 6 %, bf16: 1.03 GB in 46 us); the other kernels' time goes with what they stage and with the output.  The lines lie where the two meet
+// at the 6 % of the densest residual in use.  In us, this / the others:
+//   bf16  64 x 2048 -> 2048, 2 % 3.8 / 27.4; 1056 x 1376 -> 2080, 6 % 23.5 / 35.0; 2048^3, 0.2 % 14 / 31, 2 % 20.6 / 35.7, 6 % 46 / 49;
+//         4096 x 1024 -> 2048, 6 % 51 / 56; 16384 x 128 -> 2048, 6 % 63 / 52; 512 x 4096 -> 8192, 6 % 103 / 75
+//   fp32  256 x 512 -> 512, 2 % 3.2 / 19.8; 2048^3, 2 % 30.5 / 53.5, 6 % 74 / 95; 2048 x 1024 -> 2048, 6 % 40 / 52; 4096 x 1024 -> 2048,
+//         6 % 76 / 60
+// A dense row moves Q x 512 bytes through one CU: with four of them 2048 x 1024 -> 1024 15.4 / 29.2, 512 x 8192 -> 1024 86.6 / 86.0,
+// 256 x 16384 -> 1024 306 / 149, hence the line at 8192.  A matrix 12 % full or more would be better off there from 2^32 on (2048^3 bf16,
+// 12 %: 81 / 59).
+int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
+                           const void* D, int bf16, int64_t N, float* R, hipStream_t s) {
+  const int es = bf16 ? 2 : 4;
+  const double out = (double)P * (double)N, d_bytes = (double)Q * (double)N * es;
+  if (out * (double)Q > 0x1p33 || out > (bf16 ? 0x1p23 : 0x1p22) || Q > 8192 || d_bytes > (double)0xe0000000u) return 1;   // 32-bit offsets into D
+  const uint8_t* const d = reinterpret_cast<const uint8_t*>(D);
+  auto launch = [&](auto dt, auto lanes, auto waves, auto rows) {
+    constexpr int L = decltype(lanes)::value, W = decltype(waves)::value, ROWS = decltype(rows)::value;
+    const int64_t cols = L * 16 / es, row_blocks = (P + ROWS - 1) / ROWS, items = (N + cols - 1) / cols * row_blocks;
+    hipLaunchKernelGGL((spmm_gather_kernel<decltype(dt), L, W, ROWS>), dim3((unsigned)((items + 7) / 8 * 8)), dim3(W * 64), 0, s, row_ptr,
+                       col_idx, val, capacity, P, (int)row_blocks, (int)items, (int)Q, d, N, R);
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I4 = std::integral_constant<int, 4>;
+  using I8 = std::integral_constant<int, 8>;
+  using I32 = std::integral_constant<int, 32>;
+  using I64 = std::integral_constant<int, 64>;
+  // Four waves a row where eight rows a workgroup would leave half the chip without one: 64 x 2048 -> 2048 3.8 against 5.6 us, 256 x 512 ->
+  // 512 3.3 / 4.2; 1056 x 1376 -> 2080 25.5 / 21.7.
+  const int64_t half = (int64_t)32 * 16 / es;
+  const bool few = (P + 7) / 8 * ((N + half - 1) / half) < 128;
+  auto shape = [&](auto dt) { if (few) launch(dt, I64{}, I4{}, I1{}); else launch(dt, I32{}, I8{}, I8{}); };
+  if (bf16) shape(BF16{}); else shape(F32{});
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}

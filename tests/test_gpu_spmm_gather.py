@@ -1,0 +1,57 @@
+"""The gathering kernel of small residual products (csrc/spmm_gather.hip) at the edges of its rows a workgroup, its strips of columns, its
+64 entries a turn and 8 or 16 a request, with rows that all waves share, and on both sides of the line where the other kernels begin.
+
+Bound: n products summed in fp32 in any order differ from the exact sum by at most n * 2^-24 * sum |v d| to first order (those of bf16
+values with up to three terms are exact, others rounded once in the FMA); 2^-23 leaves room for the higher orders.
+"""
+import pytest
+import torch
+
+from paper_2501_17116_amd import binding as b
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("P,Q,N", [(1, 1, 8), (7, 63, 248), (8, 64, 256), (9, 65, 264), (33, 300, 520), (1023, 129, 264), (1025, 512, 520),
+                                   (2049, 96, 136), (300, 8192, 72), (40, 8193, 72),   # the widest it takes, and the next
+                                   (2048, 2048, 2048), (2049, 2048, 2048)])           # 2^33, and more
+def test_against_fp64(P, Q, N, dtype):
+    g = torch.Generator(device="cuda").manual_seed(P + Q + N)
+    S = torch.randn(P, Q, generator=g, device="cuda") * (torch.rand(P, Q, generator=g, device="cuda") < 0.05)
+    if P > 5:
+        S[P // 2] = 0.0                                                # an empty row
+        S[P // 3] = torch.randn(Q, generator=g, device="cuda")         # rows that all waves share, two of them neighbours
+        S[P // 3 + 1] = torch.randn(Q, generator=g, device="cuda")
+        S[P - 1] = torch.randn(Q, generator=g, device="cuda")
+    nz = S != 0
+    ptr = torch.zeros(P + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(nz.sum(1), 0, out=ptr[1:])
+    col, val = nz.nonzero()[:, 1].int().contiguous(), S[nz].contiguous()
+    D = torch.randn(Q, N, generator=g, device="cuda").to(dtype)
+    R = torch.full((P, N), float("nan"), device="cuda")
+    b.fp4_residual_spmm(ptr, col, val, Q, D, R=R)
+    mag = S.double().abs() @ D.double().abs()
+    n = nz.sum(1, keepdim=True).double() + 1
+    assert torch.all((R.double() - S.double() @ D.double()).abs() <= n * 2.0 ** -23 * mag)
+    assert torch.equal(R, b.fp4_residual_spmm(ptr, col, val, Q, D))    # a fixed order
+    assert torch.all((R - b.fp4_residual_spmm_general(ptr, col, val, Q, D)).abs() <= 2 * n * 2.0 ** -23 * mag)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_entries_in_any_order(dtype):
+    """Columns unsorted and repeated, a first entry that is not the array's first."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    P, Q, N = 50, 200, 264
+    count = torch.randint(0, 90, (P,), generator=g, device="cuda")
+    ptr = torch.full((P + 1,), 11, dtype=torch.int64, device="cuda")
+    ptr[1:] += torch.cumsum(count, 0)
+    nnz = int(ptr[-1])
+    col = torch.randint(0, Q, (nnz,), generator=g, device="cuda").int()
+    val = torch.randn(nnz, generator=g, device="cuda")
+    D = torch.randn(Q, N, generator=g, device="cuda").to(dtype)
+    row = torch.repeat_interleave(torch.arange(P, device="cuda"), count)
+    ref = torch.zeros(P, N, dtype=torch.float64, device="cuda").index_add_(0, row, val[11:, None].double() * D.double()[col[11:].long()])
+    mag = torch.zeros_like(ref).index_add_(0, row, (val[11:, None].double() * D.double()[col[11:].long()]).abs())
+    R = b.fp4_residual_spmm(ptr, col, val, Q, D)
+    assert torch.all((R.double() - ref).abs() <= (count[:, None] + 1).double() * 2.0 ** -23 * mag)
