@@ -866,13 +866,27 @@ __global__ __launch_bounds__(256) void csr_mask_scan_kernel(const uint8_t* cnt8,
   for (; bi < b1; ++bi) { ex[(int64_t)bi * Q + c] = run; run += cnt8[(int64_t)bi * Q + c]; }
 }
 
-template <int QMAX>
+// Where pass 3 takes the positions from.  FEW: from the counts of all row blocks, at most MB_FEW_BYTES of them, which every
+// workgroup adds up for itself.  SCAN: from pass 2's ex and totals, which every workgroup scans over the columns.  Either way
+// a column's position waits in LDS beside its mask, and the workgroup of the first row block writes t_ptr.  TABLE: masks of more
+// than 8192 columns leave no room for positions; t_ptr comes from a scan of its own.  Bound by round trips to memory, so by the
+// launches and by what a workgroup asks for one after another.
+// Whole transposition at 2 % (count, scan over blocks, scan over columns and fill as four launches / now): 256 x 512 12.3 / 8.2 us,
+// 1056 x 1376 at 6 % 28.7 / 19.3, 2048 x 2048 22.2 / 14.9, 8192 x 2048 25.0 / 19.3, 16384 x 4096 46.3 / 38.1.
+enum class MbFrom { FEW, SCAN, TABLE };
+constexpr int64_t MB_FEW_BYTES = 64 * 1024;
+
+template <int QMAX, MbFrom FROM>
 __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                             const float* val, int64_t rows, int64_t Q,
-                                                            int64_t capacity, const int64_t* t_ptr,
-                                                            const uint32_t* ex, int32_t* t_idx, float* t_val) {
+                                                            int64_t capacity, int64_t* t_ptr, const uint32_t* ex, const int32_t* cnt,
+                                                            const uint8_t* cnt8, int32_t* t_idx, float* t_val) {
+  constexpr bool TABLE = FROM == MbFrom::TABLE;
+  constexpr int PER = QMAX / MB_THREADS;   // consecutive columns a thread forms positions of: a multiple of 4
   __shared__ uint32_t mb_mask[2 * QMAX];
   __shared__ long long s_rp[MB_ROWS + 1];
+  __shared__ uint32_t s_pos[TABLE ? 1 : QMAX];   // fewer than 2^32 entries (the launcher's rule)
+  __shared__ uint32_t s_w[MB_THREADS / 64];
   // Each XCD takes a contiguous run of row blocks.  A block has one or two entries of a column, and its neighbours' lie beside
   // them: written from eight L2s they were partial lines of every one, from one L2 they are whole (16384 x 4096 at 2 %: 48.9
   // -> 29.3 us).
@@ -880,14 +894,61 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
   const int block = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if ((int)(blockIdx.x / 8) >= per_xcd || block >= nblocks) return;
   const int64_t r0 = (int64_t)block * MB_ROWS;
-  for (int i = threadIdx.x; i < 2 * Q; i += MB_THREADS) mb_mask[i] = 0;
+  const int c0 = (int)threadIdx.x * PER;
+  uint32_t before[PER] = {}, total[PER] = {}, sum = 0, incl = 0;   // a column's entries in earlier blocks, and all of them
   mb_load_rows(row_ptr, rows, capacity, r0, s_rp);
+  for (int i = threadIdx.x; i < 2 * Q; i += MB_THREADS) mb_mask[i] = 0;
+  if constexpr (!TABLE) {
+#pragma unroll
+    for (int j = 0; j < PER; j += 4) {   // Q is a multiple of 4
+      if (c0 + j >= Q) break;
+      if constexpr (FROM == MbFrom::FEW) {
+#pragma unroll 16
+        for (int b = 0; b < nblocks; ++b) {
+          const uint32_t four = *reinterpret_cast<const uint32_t*>(cnt8 + (int64_t)b * Q + c0 + j);
+          const uint32_t early = b < block ? four : 0;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            before[j + q] += (early >> (8 * q)) & 0xffu;
+            total[j + q] += (four >> (8 * q)) & 0xffu;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          before[j + q] = ex[(int64_t)block * Q + c0 + j + q];
+          total[j + q] = (uint32_t)cnt[c0 + j + q];
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) sum += total[j];
+    incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t up = __shfl_up(incl, o, 64);
+      if ((int)(threadIdx.x & 63) >= o) incl += up;
+    }
+    if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = incl;
+  }
   __syncthreads();
+  if constexpr (!TABLE) {
+    uint32_t at = incl - sum;
+    for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) at += s_w[w];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (c0 + j >= Q) break;
+      s_pos[c0 + j] = at + before[j];
+      at += total[j];
+      if (block == 0) t_ptr[c0 + j + 1] = at;
+    }
+    if (block == 0 && threadIdx.x == 0) t_ptr[0] = 0;
+  }
   const long long b = s_rp[0], e = s_rp[MB_ROWS];
   mb_build_masks(col_idx, s_rp, b, e, mb_mask);
   __syncthreads();
-  // Placement, four entries a thread at a time: every step of the chain column -> (segment start,
-  // block offset) -> store is a round trip to memory, so the four chains run side by side.
+  // Placement, four entries a thread at a time: the steps of the chain column -> position -> store that go to memory are round
+  // trips, so the four chains run side by side.
   const uint32_t* exb = ex + (int64_t)block * Q;
   for (long long i0 = b + threadIdx.x; i0 < e; i0 += 4 * MB_THREADS) {
     int32_t c[4];
@@ -900,7 +961,10 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
       v[u] = i < e ? val[i] : 0.0f;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pos[u] = c[u] >= 0 ? t_ptr[c[u]] + exb[c[u]] : capacity;
+    for (int u = 0; u < 4; ++u) {
+      if constexpr (TABLE) pos[u] = c[u] >= 0 ? t_ptr[c[u]] + exb[c[u]] : capacity;
+      else pos[u] = c[u] >= 0 ? (int64_t)s_pos[c[u]] : capacity;
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (c[u] < 0) continue;
@@ -1116,19 +1180,32 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
       hipLaunchKernelGGL((csr_mask_count_kernel<decltype(qmax)::value>), dim3(nblocks), dim3(MB_THREADS), 0, s, row_ptr, col_idx,
                          P, Q, capacity, cnt8);
     };
-    auto fill = [&](auto qmax) {
-      hipLaunchKernelGGL((csr_mask_fill_kernel<decltype(qmax)::value>), dim3((nblocks + 7) / 8 * 8), dim3(MB_THREADS), 0, s, row_ptr, col_idx,
-                         val, P, Q, capacity, t_ptr, ex, t_idx, t_val);
-    };
     using Q4 = std::integral_constant<int, 4096>;
     using Q8 = std::integral_constant<int, 8192>;
     using Q16 = std::integral_constant<int, MB_MAXQ>;
+    auto fill = [&](auto qmax, auto from) {
+      hipLaunchKernelGGL((csr_mask_fill_kernel<decltype(qmax)::value, decltype(from)::value>), dim3((nblocks + 7) / 8 * 8), dim3(MB_THREADS), 0,
+                         s, row_ptr, col_idx, val, P, Q, capacity, t_ptr, ex, cnt, cnt8, t_idx, t_val);
+    };
+    using Few = std::integral_constant<MbFrom, MbFrom::FEW>;
+    using Scan = std::integral_constant<MbFrom, MbFrom::SCAN>;
+    using Table = std::integral_constant<MbFrom, MbFrom::TABLE>;
     if (Q <= 4096) count(Q4{}); else if (Q <= 8192) count(Q8{}); else count(Q16{});
+    const bool positions = Q <= 8192 && Q % 4 == 0 && P * Q < ((int64_t)1 << 32);
+    if (positions && nblocks * Q <= MB_FEW_BYTES) {
+      if (Q <= 4096) fill(Q4{}, Few{}); else fill(Q8{}, Few{});
+      FP4_CHECK_LAUNCH();
+      return FP4_OK;
+    }
     hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0, s, cnt8, nblocks, Q, ex, cnt);
     FP4_CHECK_LAUNCH();
-    const int rc = fp4_launch_scan_rows(cnt, Q, t_ptr, nullptr, s);
-    if (rc) return rc;
-    if (Q <= 4096) fill(Q4{}); else if (Q <= 8192) fill(Q8{}); else fill(Q16{});
+    if (positions) {
+      if (Q <= 4096) fill(Q4{}, Scan{}); else fill(Q8{}, Scan{});
+    } else {
+      const int rc = fp4_launch_scan_rows(cnt, Q, t_ptr, nullptr, s);
+      if (rc) return rc;
+      if (Q <= 4096) fill(Q4{}, Table{}); else if (Q <= 8192) fill(Q8{}, Table{}); else fill(Q16{}, Table{});
+    }
     FP4_CHECK_LAUNCH();
     return FP4_OK;
   }
