@@ -38,8 +38,9 @@ int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t col
 int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols);
 int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                                     float* gamma, uint16_t* part, hipStream_t s);
-int fp4_launch_quantize_cols_known_max(const void* x, int64_t rows, int64_t cols, int64_t ld, const uint16_t* part,
-                                       uint8_t* codes_t, float* gamma, hipStream_t s);
+int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
+                                  uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, hipStream_t s);
 int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const int32_t* row_cnt, int64_t stride,
                             const int64_t* row_ptr, int64_t rows, int64_t capacity, int32_t* col_idx, float* val,
                             hipStream_t s);
@@ -191,7 +192,7 @@ WgradWs carve_wgrad(Carver& c, int64_t M, int64_t K, int64_t N, fp4_dtype dt) {
   w.gAk = c.take<float>((size_t)K);
   w.qdYt = c.take<uint8_t>((size_t)(N * M / 2));
   w.gdYn = c.take<float>((size_t)N);
-  w.amax = c.take<uint32_t>((size_t)std::max(fp4_quantize_cols_scratch_words(M, K), fp4_quantize_cols_scratch_words(M, N)));
+  w.amax = c.take<uint32_t>((size_t)fp4_quantize_cols_scratch_words(M, K + N));
   const int64_t cap = provisioned_entries(M, K);
   w.t_ptr = c.take<int64_t>((size_t)(K + 1));
   w.t_idx = c.take<int32_t>((size_t)cap);
@@ -610,8 +611,8 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
     rc = fp4_launch_csr_transpose(saved->row_ptr, saved->col_idx, saved->val, saved->nnz, M, K, cap,
                                   w.t_ptr, w.t_idx, w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
   // A_c per input channel (codes [K x M/2]); dY per output channel (codes [N x M/2])
-  if (!rc) rc = fp4_launch_quantize_cols(A, bf16, M, K, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, w.amax, s);
-  if (!rc) rc = fp4_launch_quantize_cols(dY, bf16, M, N, N, nullptr, 0, w.qdYt, w.gdYn, w.amax, s);
+  if (!rc) rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, dY, N, nullptr, w.qdYt,
+                                              w.gdYn, w.amax, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
@@ -666,10 +667,8 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
                                   w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
     if (rc) return rc;
   }
-  rc = fp4_launch_quantize_cols(A, bf16, M, K, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, w.amax, s);
-  if (rc) return rc;
-  if (dual) rc = fp4_launch_quantize_cols_known_max(dY, M, N, N, part, w.qdYt, w.gdYn, s);
-  else rc = fp4_launch_quantize_cols(dY, bf16, M, N, N, nullptr, 0, w.qdYt, w.gdYn, w.amax, s);
+  rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, dY, N, dual ? part : nullptr,
+                                     w.qdYt, w.gdYn, w.amax, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {

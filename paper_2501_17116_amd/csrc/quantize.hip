@@ -748,7 +748,10 @@ struct ColArgs {
   const void* x;
   uint8_t* codes_t;
   float* gamma;          // out [cols]
-  uint32_t* amax_bits;   // scratch [ceil(rows / row_block)][cols]: partial column maxima per row block
+  uint32_t* amax_bits;   // scratch [ceil(rows / row_block)][amax_ld]: partial column maxima per row block
+  int64_t amax_ld;
+  const uint16_t* part16;   // or, as the dual-axis pass leaves them, bf16 magnitude patterns [parts][cols]
+  int parts;             // rows of partial maxima that quantize_cols_kernel makes the scales of; 0: gamma holds them
   const float* thr;      // clamp thresholds or null
   int64_t thr_stride;    // 0: one {lo, hi} pair for the tensor; 2: one pair per row, thr[2 r], thr[2 r + 1]
   int64_t rows, cols, ld;
@@ -765,10 +768,9 @@ inline int ca_rows(int64_t rows, int64_t cols) {
 }
 
 template <class DT, bool CLAMP>
-__global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a) {
-  __shared__ float s_m[4][64][8];
+FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, float (&s_m)[4][64][8]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t unit = (int64_t)blockIdx.x * 64 + lane;   // 8 columns
+  const int64_t unit = (int64_t)strip * 64 + lane;   // 8 columns
   const int64_t nunits = (a.cols + 7) / 8;
   const int64_t r0 = (int64_t)blockIdx.y * a.row_block;
   const int64_t r1 = min(r0 + a.row_block, a.rows);
@@ -817,7 +819,7 @@ __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a) {
   // one row of partial maxima per row block (plain stores; a small fold follows): hundreds of
   // workgroups maxing the same words with device-wide atomics cost 10-18 us per tensor
   if (wave == 0 && valid > 0) {
-    uint32_t* const prow = a.amax_bits + (int64_t)blockIdx.y * a.cols;
+    uint32_t* const prow = a.amax_bits + (int64_t)blockIdx.y * a.amax_ld;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float mm = fmaxf(fmaxf(s_m[0][lane][e], s_m[1][lane][e]), fmaxf(s_m[2][lane][e], s_m[3][lane][e]));
@@ -826,9 +828,17 @@ __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a) {
   }
 }
 
+// Two tensors of as many rows a launch: the first strips_a strips are a's, the rest b's, which is never clamped.
+template <class DT, bool CLAMP>
+__global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a, ColArgs b, unsigned strips_a) {
+  __shared__ float s_m[4][64][8];
+  if (blockIdx.x < strips_a) col_absmax_strip<DT, CLAMP>(a, blockIdx.x, s_m);
+  else col_absmax_strip<DT, false>(b, blockIdx.x - strips_a, s_m);
+}
+
 // gamma[c] from the g partial rows of column maxima (bit patterns of non-negative floats order
 // like unsigned integers)
-__global__ __launch_bounds__(256) void amax_to_gamma_kernel(const uint32_t* part, int64_t g, float* gamma, int64_t n,
+__global__ __launch_bounds__(256) void amax_to_gamma_kernel(const uint32_t* part, int64_t ld, int64_t g, float* gamma, int64_t n,
                                                             float fmax) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= n) return;
@@ -838,9 +848,9 @@ __global__ __launch_bounds__(256) void amax_to_gamma_kernel(const uint32_t* part
   int64_t i = 0;
   for (; i + 15 < g; i += 16) {   // sixteen loads in flight
 #pragma unroll
-    for (int j = 0; j < 16; ++j) m[j] = max(m[j], part[(i + j) * n + c]);
+    for (int j = 0; j < 16; ++j) m[j] = max(m[j], part[(i + j) * ld + c]);
   }
-  for (; i < g; ++i) m[0] = max(m[0], part[i * n + c]);
+  for (; i < g; ++i) m[0] = max(m[0], part[i * ld + c]);
 #pragma unroll
   for (int j = 1; j < 16; ++j) m[0] = max(m[0], m[j]);
   gamma[c] = absmax_to_gamma_of(u2f(m[0]), fmax);
@@ -849,22 +859,98 @@ __global__ __launch_bounds__(256) void amax_to_gamma_kernel(const uint32_t* part
 constexpr int CT_ROWS = 256;
 constexpr int CT_COLS = 64;
 
+struct ColShared {
+  uint32_t w[CT_COLS][CT_ROWS / 8 + 1];   // [col][rowgroup]: the 8 codes of rows 8*rowgroup..+7 of one column; +1 word of padding
+  uint32_t m[4][CT_COLS];                 // column maxima that each wave found, as fp32 patterns
+  float g[CT_COLS];
+};
+
+FP4_D uint32_t pk_max_u16(uint32_t a, uint32_t b) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// The scales of a tile's columns from their partial maxima, 16 bytes a lane: every tile of a column does this again, beside its own
+// loads, where a launch in between took 3 to 5 us.  The tiles of the first row block leave the scales in memory.
+FP4_D void cols_fold(const ColArgs& a, int64_t c0, bool leave, ColShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  u32x4 m = {0u, 0u, 0u, 0u};
+  if (a.part16) {   // 8 lanes a row, 32 rows of partial maxima at a time
+    const int l = tid & 7;
+    if (c0 + l * 8 < a.cols) {
+      const uint16_t* const p = a.part16 + c0 + l * 8;
+#pragma unroll 8
+      for (int i = tid >> 3; i < a.parts; i += 32) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(p + (int64_t)i * a.cols);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m[q] = pk_max_u16(m[q], v[q]);
+      }
+    }
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) m[q] = pk_max_u16(m[q], (uint32_t)__shfl_xor((int)m[q], o, 64));
+    if (lane < 8)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        sh.m[wave][l * 8 + 2 * q] = m[q] << 16;
+        sh.m[wave][l * 8 + 2 * q + 1] = m[q] & 0xffff0000u;
+      }
+  } else {          // 16 lanes a row, 16 rows at a time
+    const int l = tid & 15;
+    if (c0 + l * 4 < a.cols) {
+      const uint32_t* const p = a.amax_bits + c0 + l * 4;
+#pragma unroll 8
+      for (int i = tid >> 4; i < a.parts; i += 16) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(p + (int64_t)i * a.amax_ld);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m[q] = max(m[q], v[q]);
+      }
+    }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) m[q] = max(m[q], (uint32_t)__shfl_xor((int)m[q], o, 64));
+    if (lane < 16)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sh.m[wave][l * 4 + q] = m[q];
+  }
+  __syncthreads();
+  if (tid < CT_COLS) {
+    const float g = absmax_to_gamma(u2f(max(max(sh.m[0][tid], sh.m[1][tid]), max(sh.m[2][tid], sh.m[3][tid]))));
+    sh.g[tid] = g;
+    if (leave && c0 + tid < a.cols) a.gamma[c0 + tid] = g;
+  }
+  __syncthreads();
+}
+
 template <class DT, bool CLAMP>
-__global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a) {
-  // s_w[col][rowgroup]: the 8 codes of rows 8*rowgroup..+7 of one column; +1 word of padding
-  __shared__ uint32_t s_w[CT_COLS][CT_ROWS / 8 + 1];
+FP4_D void quantize_cols_tile(const ColArgs& a, unsigned strip, ColShared& sh) {
   const int tid = threadIdx.x;
   const int chunk = tid & 7;      // 8 columns
   const int rg = tid >> 3;        // row group 0..31 (8 rows each)
-  const int64_t c0 = (int64_t)blockIdx.x * CT_COLS;
+  const int64_t c0 = (int64_t)strip * CT_COLS;
   const int64_t r0 = (int64_t)blockIdx.y * CT_ROWS;
   const int64_t col = c0 + chunk * 8;
   const int valid = col < a.cols ? (int)min((int64_t)8, a.cols - col) : 0;
   float lo = 0, hi = 0;
   if (CLAMP) { lo = a.thr[0]; hi = a.thr[1]; }
-  float g[8];
+  Raw8<DT> raw[8];   // requested before the scales are formed
 #pragma unroll
-  for (int e = 0; e < 8; ++e) g[e] = (e < valid) ? a.gamma[col + e] : 1.0f;
+  for (int i = 0; i < 8; ++i) {
+    const int64_t r = r0 + rg * 8 + i;
+    raw[i] = Raw8<DT>{};
+    if (valid > 0 && r < a.rows) load_raw8<DT>(a.x, r * a.ld + col, valid, raw[i]);
+  }
+  float g[8];
+  if (a.parts) {
+    cols_fold(a, c0, blockIdx.y == 0, sh);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = sh.g[chunk * 8 + e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = (e < valid) ? a.gamma[col + e] : 1.0f;
+  }
   uint32_t w[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) w[e] = 0;
@@ -872,13 +958,9 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a) {
   static_for4([&](auto ic) {
     constexpr int i = decltype(ic)::value * 2;
     float v0[8], v1[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { v0[e] = 0.0f; v1[e] = 0.0f; }
+    widen8<DT>(raw[i], v0);
+    widen8<DT>(raw[i + 1], v1);
     const int64_t r = r0 + rg * 8 + i;
-    if (valid > 0) {
-      if (r < a.rows) load8<DT>(a.x, r * a.ld + col, valid, v0);
-      if (r + 1 < a.rows) load8<DT>(a.x, (r + 1) * a.ld + col, valid, v1);
-    }
     float lo1 = lo, hi1 = hi;
     if (CLAMP && a.thr_stride) {   // per-row thresholds
       const int64_t ra = min(r, a.rows - 1), rb = min(r + 1, a.rows - 1);
@@ -900,7 +982,7 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) w[e] = q_e2m1_drop_zero_signs(w[e]);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) s_w[chunk * 8 + e][rg] = w[e];
+  for (int e = 0; e < 8; ++e) sh.w[chunk * 8 + e][rg] = w[e];
   __syncthreads();
   // write-out: 4 threads per column, 8 words (32 bytes, 64 rows) each
   const int oc = tid >> 2;
@@ -913,29 +995,40 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a) {
   uint8_t* dst = a.codes_t + ocol * row_bytes + b0;
   const int nbytes = (int)min((int64_t)32, row_bytes - b0);
   if (nbytes == 32 && (row_bytes % 16) == 0) {
-    u32x4 o0 = {s_w[oc][part * 8 + 0], s_w[oc][part * 8 + 1], s_w[oc][part * 8 + 2], s_w[oc][part * 8 + 3]};
-    u32x4 o1 = {s_w[oc][part * 8 + 4], s_w[oc][part * 8 + 5], s_w[oc][part * 8 + 6], s_w[oc][part * 8 + 7]};
+    u32x4 o0 = {sh.w[oc][part * 8 + 0], sh.w[oc][part * 8 + 1], sh.w[oc][part * 8 + 2], sh.w[oc][part * 8 + 3]};
+    u32x4 o1 = {sh.w[oc][part * 8 + 4], sh.w[oc][part * 8 + 5], sh.w[oc][part * 8 + 6], sh.w[oc][part * 8 + 7]};
     reinterpret_cast<u32x4*>(dst)[0] = o0;
     reinterpret_cast<u32x4*>(dst)[1] = o1;
   } else {
-    for (int b = 0; b < nbytes; ++b) dst[b] = (uint8_t)(s_w[oc][part * 8 + b / 4] >> (8 * (b & 3)));
+    for (int b = 0; b < nbytes; ++b) dst[b] = (uint8_t)(sh.w[oc][part * 8 + b / 4] >> (8 * (b & 3)));
   }
 }
 
+// Two tensors of as many rows a launch, as col_absmax_kernel.
 template <class DT, bool CLAMP>
-int launch_cols(ColArgs a, hipStream_t s) {
-  a.row_block = ca_rows(a.rows, a.cols);
-  const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t rblocks = (a.rows + a.row_block - 1) / a.row_block;
-  hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3((unsigned)((nunits + 63) / 64), (unsigned)rblocks), dim3(256),
-                     0, s, a);
-  hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits,
-                     rblocks, a.gamma, a.cols, 6.0f);
-  hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>),
-                     dim3((unsigned)((a.cols + CT_COLS - 1) / CT_COLS), (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS)),
-                     dim3(256), 0, s, a);
-  FP4_CHECK_LAUNCH();
-  return FP4_OK;
+__global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a, ColArgs b, unsigned strips_a) {
+  __shared__ ColShared sh;
+  if (blockIdx.x < strips_a) quantize_cols_tile<DT, CLAMP>(a, blockIdx.x, sh);
+  else quantize_cols_tile<DT, false>(b, blockIdx.x - strips_a, sh);
+}
+
+// The tiles fold the partial maxima themselves while all of them together read no more than 128 MiB for it, from L2.  Pass in us with
+// a launch for the scales before it / without, for both tensors of a weight gradient: 1056 x (1376 + 2080) 12.8 / 9.0 (3 and 6 MB), 8192 x
+// (2048 + 2048) 31.8 / 26.8 (34 and 134); with only the second's apart 4096 x (5120 + 13824) 49.4 / 58.5 (226 MB for that one), 16384 x
+// (4096 + 12288) 154.9 / 168.0 (805).
+inline bool fold_in_tiles(const ColArgs& a, int parts, int bytes) {
+  return (a.rows + CT_ROWS - 1) / CT_ROWS * a.cols * parts * bytes <= (int64_t)128 << 20;
+}
+
+inline unsigned ca_strips(int64_t cols) { return (unsigned)(((cols + 7) / 8 + 63) / 64); }
+inline unsigned ct_strips(int64_t cols) { return (unsigned)((cols + CT_COLS - 1) / CT_COLS); }
+
+// The scales, where the tiles don't form them themselves.
+void launch_amax_to_gamma(ColArgs& a, int parts, hipStream_t s) {
+  a.parts = 0;
+  if (fold_in_tiles(a, parts, 4) && a.cols % 4 == 0 && a.amax_ld % 4 == 0 && aligned16(a.amax_bits)) a.parts = parts;
+  else hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits, a.amax_ld,
+                          (int64_t)parts, a.gamma, a.cols, 6.0f);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -956,15 +1049,6 @@ inline int da_rows(int64_t rows, int64_t cols) {
   while (per > 4 && rows < (int64_t)per * (cols > 8192 ? 512 : 1024)) per /= 2;
   return per;
 }
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-FP4_D uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-  union { uint32_t u; u16x2 v; } x, y, r;
-  x.u = a; y.u = b;
-  r.v = __builtin_elementwise_max(x.v, y.v);
-  return r.u;
-}
-
 template <int NV>
 __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                    int64_t cols, int64_t ld, uint8_t* __restrict__ codes,
@@ -1061,6 +1145,35 @@ __global__ __launch_bounds__(A16_WAVES * 64) void amax16_to_gamma_kernel(const u
   }
 }
 
+void launch_amax16_to_gamma(ColArgs& a, hipStream_t s) {
+  if (fold_in_tiles(a, a.parts, 2)) return;
+  hipLaunchKernelGGL(amax16_to_gamma_kernel, dim3((unsigned)((a.cols + 127) / 128)), dim3(A16_WAVES * 64), 0, s, a.part16, (int64_t)a.parts,
+                     a.gamma, a.cols);
+  a.parts = 0;
+}
+
+// b.x null: a alone.  b.part16 set: b's maxima are known (b.parts rows of them).
+template <class DT, bool CLAMP>
+int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, hipStream_t s) {
+  const bool b_max = b.x && !b.part16;
+  const int64_t width = a.cols + (b_max ? b.cols : 0);
+  a.row_block = b.row_block = ca_rows(a.rows, width);
+  a.amax_bits = amax;
+  b.amax_bits = amax + a.cols;
+  a.amax_ld = b.amax_ld = width;
+  const int rblocks = (int)((a.rows + a.row_block - 1) / a.row_block);
+  hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3(ca_strips(a.cols) + (b_max ? ca_strips(b.cols) : 0), (unsigned)rblocks), dim3(256),
+                     0, s, a, b, ca_strips(a.cols));
+  launch_amax_to_gamma(a, rblocks, s);
+  if (b_max) launch_amax_to_gamma(b, rblocks, s);
+  else if (b.x) launch_amax16_to_gamma(b, s);
+  hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>),
+                     dim3(ct_strips(a.cols) + (b.x ? ct_strips(b.cols) : 0), (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS)), dim3(256), 0, s, a, b,
+                     ct_strips(a.cols));
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}
+
 // ------------------------------------------------------------------------------------------
 // FP8 (E4M3) vector-wise quantization for the mixed-format ablations (Sec. 4.3): same absmax
 // scaling with MAX = 448, one code per byte.  Not on the FP4 hot path: plain two-pass kernels.
@@ -1148,10 +1261,10 @@ __global__ __launch_bounds__(256) void fp8_quantize_cols_kernel(ColArgs a) {
 template <class DT>
 int launch_cols_fp8(ColArgs a, hipStream_t s) {
   a.row_block = ca_rows(a.rows, a.cols);
-  const int64_t nunits = (a.cols + 7) / 8;
+  a.amax_ld = a.cols;
   const int64_t rblocks = (a.rows + a.row_block - 1) / a.row_block;
-  hipLaunchKernelGGL((col_absmax_kernel<DT, false>), dim3((unsigned)((nunits + 63) / 64), (unsigned)rblocks), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits, rblocks,
+  hipLaunchKernelGGL((col_absmax_kernel<DT, false>), dim3(ca_strips(a.cols), (unsigned)rblocks), dim3(256), 0, s, a, a, ca_strips(a.cols));
+  hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits, a.cols, rblocks,
                      a.gamma, a.cols, 448.0f);
   hipLaunchKernelGGL((fp8_quantize_cols_kernel<DT>), dim3((unsigned)((a.cols + 63) / 64), (unsigned)((a.rows + 63) / 64)),
                      dim3(256), 0, s, a);
@@ -1373,26 +1486,9 @@ int fp4_launch_quantize_cols_given_gamma(const void* x, int bf16, int64_t rows, 
   ColArgs a = {};
   a.x = x; a.codes_t = codes_t; a.gamma = gamma;
   a.rows = rows; a.cols = cols; a.ld = ld;
-  const dim3 grid((unsigned)((cols + CT_COLS - 1) / CT_COLS), (unsigned)((rows + CT_ROWS - 1) / CT_ROWS));
-  if (bf16) hipLaunchKernelGGL((quantize_cols_kernel<BF16, false>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((quantize_cols_kernel<F32, false>), grid, dim3(256), 0, s, a);
-  FP4_CHECK_LAUNCH();
-  return FP4_OK;
-}
-
-// Column-wise quantization of a bf16 tensor whose column maxima per row block are already known
-// (from the dual-axis pass): scales, then the transposing pass; the tensor is read once.
-int fp4_launch_quantize_cols_known_max(const void* x, int64_t rows, int64_t cols, int64_t ld, const uint16_t* part,
-                                       uint8_t* codes_t, float* gamma, hipStream_t s) {
-  if (rows == 0 || cols == 0) return FP4_OK;
-  ColArgs a = {};
-  a.x = x; a.codes_t = codes_t; a.gamma = gamma;
-  a.rows = rows; a.cols = cols; a.ld = ld;
-  hipLaunchKernelGGL(amax16_to_gamma_kernel, dim3((unsigned)((cols + 127) / 128)), dim3(A16_WAVES * 64), 0, s, part,
-                     (rows + da_rows(rows, cols) - 1) / da_rows(rows, cols), gamma, cols);
-  hipLaunchKernelGGL((quantize_cols_kernel<BF16, false>),
-                     dim3((unsigned)((cols + CT_COLS - 1) / CT_COLS), (unsigned)((rows + CT_ROWS - 1) / CT_ROWS)), dim3(256),
-                     0, s, a);
+  const dim3 grid(ct_strips(cols), (unsigned)((rows + CT_ROWS - 1) / CT_ROWS));
+  if (bf16) hipLaunchKernelGGL((quantize_cols_kernel<BF16, false>), grid, dim3(256), 0, s, a, a, grid.x);
+  else hipLaunchKernelGGL((quantize_cols_kernel<F32, false>), grid, dim3(256), 0, s, a, a, grid.x);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
@@ -1426,11 +1522,28 @@ int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols
                              uint32_t* amax_scratch, hipStream_t s) {
   if (rows == 0 || cols == 0) return FP4_OK;
   ColArgs a = {};
-  a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.amax_bits = amax_scratch; a.thr = clamp_thr;
+  a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
   a.thr_stride = per_row_thr ? 2 : 0;
   a.rows = rows; a.cols = cols; a.ld = ld;
-  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, s) : launch_cols<F32, true>(a, s);
-  return bf16 ? launch_cols<BF16, false>(a, s) : launch_cols<F32, false>(a, s);
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, {}, amax_scratch, s) : launch_cols<F32, true>(a, {}, amax_scratch, s);
+  return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, s) : launch_cols<F32, false>(a, {}, amax_scratch, s);
+}
+
+// The weight gradient's operands, x [rows x cols] (clamped) and y [rows x cols_y], in as many launches as one of them takes.  part_y:
+// y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.
+int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
+                                  uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, hipStream_t s) {
+  if (rows == 0 || cols == 0 || cols_y == 0) return FP4_ERR_SHAPE;
+  ColArgs a = {}, b = {};
+  a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
+  a.thr_stride = per_row_thr ? 2 : 0;
+  a.rows = rows; a.cols = cols; a.ld = cols;
+  b.x = y; b.codes_t = codes_y; b.gamma = gamma_y; b.part16 = part_y;
+  b.rows = rows; b.cols = cols_y; b.ld = cols_y;
+  if (part_y) b.parts = (int)((rows + da_rows(rows, cols_y) - 1) / da_rows(rows, cols_y));
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, b, amax_scratch, s) : launch_cols<F32, true>(a, b, amax_scratch, s);
+  return bf16 ? launch_cols<BF16, false>(a, b, amax_scratch, s) : launch_cols<F32, false>(a, b, amax_scratch, s);
 }
 
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
