@@ -16,13 +16,13 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
                     float dge_cap, hipStream_t stream);
 int fp4_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              uint8_t* codes, float* gamma, hipStream_t s);
-int fp4_launch_occ_count(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thr,
-                         int32_t* row_cnt, hipStream_t s);
-int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thr,
-                        uint8_t* codes, float* gamma, void* x_clamped, int32_t* col_idx, float* val,
-                        int32_t* tmp_col, float* tmp_val, const int64_t* row_ptr, int64_t capacity, const float* gamma_in,
-                        hipStream_t s);
+int fp4_row_sum_shift(int64_t rows);
+int64_t fp4_row_sum_words(int64_t rows);
 int64_t fp4_tensor_gamma_scratch_words();
+int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thr,
+                        uint8_t* codes, float* gamma, void* x_clamped, int32_t* col_idx, float* val, int32_t* tmp_col,
+                        float* tmp_val, int32_t* row_cnt, const int32_t* row_sum, int64_t* row_ptr, int64_t* nnz, int64_t capacity,
+                        const float* gamma_in, hipStream_t s);
 int fp4_launch_tensor_gamma(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thr,
                             uint32_t* scratch, float* scalar, float* bcast, int64_t n, hipStream_t s);
 int fp4_launch_quantize_rows_fixed(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* gamma_in,
@@ -31,7 +31,7 @@ int fp4_launch_quantize_cols_given_gamma(const void* x, int bf16, int64_t rows, 
                                          uint8_t* codes_t, float* gamma, hipStream_t s);
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
-                             uint32_t* amax_scratch, hipStream_t s);
+                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words);
 int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t tail_k,
                               float* thr_out, uint8_t* codes, float* gamma, void* x_clamped, int32_t* tmp_col,
                               float* tmp_val, int32_t* row_cnt, hipStream_t s);
@@ -46,11 +46,11 @@ int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const 
                             hipStream_t s);
 int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols);
 size_t fp4_select_scratch_bytes();
-int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k,
-                          float* thresholds, void* scratch, unsigned long long* total, hipStream_t s);
+int64_t fp4_select_clear_words();
+int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t n, hipStream_t s);
 int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
-                                     void* scratch, unsigned long long* total, void* rows_scratch, int64_t rows_scratch_words,
-                                     int32_t* row_cnt, hipStream_t s);
+                                     void* scratch, void* rows_scratch, int64_t rows_scratch_words, int32_t* row_cnt, int32_t* row_sum,
+                                     int shift, hipStream_t s);
 int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s);
 int fp4_launch_csr_gather(const int32_t* tmp_col, const float* tmp_val, int64_t rows, int64_t capacity,
                           const int64_t* row_ptr, int32_t* col_idx, float* val, hipStream_t s);
@@ -109,9 +109,7 @@ struct OccTemps {
   void* select;
   int32_t* tmp_col;
   float* tmp_val;
-  int64_t* row_start;
-  int32_t* row_cnt;
-  unsigned long long* total;
+  int32_t *row_cnt, *row_sum;
 };
 // later: words of scratch whose use begins when the unordered entries are in their place; they share one block.
 OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity, int64_t later = 0, int32_t** later_out = nullptr) {
@@ -123,20 +121,30 @@ OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity, int64_t later = 0,
   int32_t* const shared = c.take<int32_t>((size_t)later);
   if (later_out) *later_out = shared;
   c.off = std::max(c.off, in.off);
-  t.row_start = c.take<int64_t>((size_t)rows);
   t.row_cnt = c.take<int32_t>((size_t)rows);
-  t.total = c.take<unsigned long long>(1);
+  t.row_sum = c.take<int32_t>((size_t)fp4_row_sum_words(rows));
   return t;
 }
 
-// The per-tensor thresholds, then how many elements of each row they clamp; the entries' temporaries are free until then.
+// The per-tensor thresholds, then how many elements of each row they clamp; the entries' temporaries are free until then, t.select is
+// cleared.
 int thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds, const OccTemps& t,
                           hipStream_t s) {
-  int rc = fp4_launch_thresholds_and_counts(x, bf16, rows, cols, ld, k, thresholds, t.select, t.total, t.tmp_col,
-                                            provisioned_entries(rows, cols), t.row_cnt, s);
-  if (rc != 1) return rc;
-  rc = fp4_launch_thresholds(x, bf16, rows, cols, ld, k, thresholds, t.select, t.total, s);
-  return rc ? rc : fp4_launch_occ_count(x, bf16, rows, cols, ld, thresholds, t.row_cnt, s);
+  return fp4_launch_thresholds_and_counts(x, bf16, rows, cols, ld, k, thresholds, t.select, t.tmp_col, provisioned_entries(rows, cols),
+                                          t.row_cnt, t.row_sum, fp4_row_sum_shift(rows), s);
+}
+
+// Clamp, codes and the ordered residual, after thresholds_and_counts.
+int emit_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thresholds, uint8_t* codes, float* gamma,
+              void* x_clamped, int64_t* row_ptr, int32_t* col_idx, float* val, int64_t capacity, int64_t* nnz, const float* gamma_in,
+              const OccTemps& t, hipStream_t s) {
+  int rc = fp4_launch_occ_rows(x, bf16, rows, cols, ld, thresholds, codes, gamma, x_clamped, col_idx, val, t.tmp_col, t.tmp_val, t.row_cnt,
+                               t.row_sum, row_ptr, nnz, capacity, gamma_in, s);
+  if (rc == 1) {   // streamed rows: entries unordered in the temporaries
+    rc = fp4_launch_order_rows(row_ptr, rows, cols, capacity, t.tmp_col, t.tmp_val, col_idx, val, s);
+    if (rc == 1) rc = fp4_launch_csr_gather(t.tmp_col, t.tmp_val, rows, capacity, row_ptr, col_idx, val, s);
+  }
+  return rc;
 }
 
 struct FwdWs {
@@ -320,25 +328,13 @@ extern "C" int occ_clamp_residual(const void* x, fp4_dtype dt, int64_t rows, int
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
   OccTemps t = carve_occ(c, rows, provisioned_entries(rows, cols));
   capacity = std::min(capacity, provisioned_entries(rows, cols));  // never beyond the temporaries
-  int rc = thresholds_and_counts(x, dt == FP4_BF16, rows, cols, ld, k, thresholds, t, s);
+  int rc = fp4_launch_clear_select(t.select, nullptr, nullptr, 0, s);
+  if (!rc) rc = thresholds_and_counts(x, dt == FP4_BF16, rows, cols, ld, k, thresholds, t, s);
   if (rc) return rc;
-  rc = fp4_launch_scan_rows(t.row_cnt, rows, row_ptr, nnz, s);
-  if (rc) return rc;
-  rc = fp4_launch_occ_rows(x, dt == FP4_BF16, rows, cols, ld, thresholds, codes, gamma, x_clamped, col_idx, val,
-                           t.tmp_col, t.tmp_val, row_ptr, capacity, nullptr, s);
-  if (rc == 1) {   // streamed rows: entries unordered in the temporaries
-    rc = fp4_launch_order_rows(row_ptr, rows, cols, capacity, t.tmp_col, t.tmp_val, col_idx, val, s);
-    if (rc == 1) rc = fp4_launch_csr_gather(t.tmp_col, t.tmp_val, rows, capacity, row_ptr, col_idx, val, s);
-  }
-  return rc;
+  return emit_rows(x, dt == FP4_BF16, rows, cols, ld, thresholds, codes, gamma, x_clamped, row_ptr, col_idx, val, capacity, nnz, nullptr, t, s);
 }
 
 namespace {
-__global__ void copy_f32_kernel(const float* src, float* dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-
 bool cache_ok(const fp4_weight_cache* wq) {
   return wq && wq->qWt && wq->gamma_W && wq->qWk && wq->gamma_Wk && aligned16(wq->qWt) && aligned16(wq->qWk);
 }
@@ -376,20 +372,23 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
 
   // W per output channel -> codes [N x K/2], scales kept for the DGE term of the backward pass;
   // from the cache when the caller prepared one (W does not change between micro-batches)
+  // The first launch also clears what the search for the thresholds counts in.
   int rc = FP4_OK;
   const uint8_t* qWt = w.qWt;
+  void* const clear = occ && !token ? w.occ.select : nullptr;
+  if (wq || wgt_tensor) {
+    const bool copy = wq && saved->gamma_W != wq->gamma_W;
+    rc = fp4_launch_clear_select(clear, copy ? wq->gamma_W : nullptr, saved->gamma_W, copy ? N : 0, s);
+    if (rc) return rc;
+  }
   if (wq) {
     qWt = wq->qWt;
-    if (saved->gamma_W != wq->gamma_W) {
-      hipLaunchKernelGGL(copy_f32_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, wq->gamma_W, saved->gamma_W, N);
-      if (hipGetLastError() != hipSuccess) return FP4_ERR_HIP;
-    }
   } else if (wgt_tensor) {
     rc = fp4_launch_tensor_gamma(W, bf16, K, N, N, nullptr, w.tg, nullptr, saved->gamma_W, N, s);
     if (!rc) rc = fp4_launch_quantize_cols_given_gamma(W, bf16, K, N, N, w.qWt, saved->gamma_W, s);
     if (rc) return rc;
   } else {
-    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s);
+    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, clear, fp4_select_clear_words());
     if (rc) return rc;
   }
   const float* addend = nullptr;
@@ -401,8 +400,6 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
     } else {
       rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s);
       if (rc) return rc;
-      rc = fp4_launch_scan_rows(w.occ.row_cnt, M, saved->row_ptr, saved->nnz, s);
-      if (rc) return rc;
       const float* g_all = nullptr;   // tensor-wise activations: one scale, from the clamped tensor's absmax
       if (act_tensor) {
         rc = fp4_launch_tensor_gamma(A, bf16, M, K, K, saved->thresholds, w.tg, reinterpret_cast<float*>(w.tg + TG_SCALAR),
@@ -410,13 +407,8 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
         if (rc) return rc;
         g_all = reinterpret_cast<const float*>(w.tg + TG_SCALAR);
       }
-      rc = fp4_launch_occ_rows(A, bf16, M, K, K, saved->thresholds, w.qA, w.gA, nullptr, saved->col_idx, saved->val,
-                               w.occ.tmp_col, w.occ.tmp_val, saved->row_ptr, cap, g_all, s);
-      if (rc == 1) {   // streamed rows: entries unordered in the temporaries
-        rc = fp4_launch_order_rows(saved->row_ptr, M, K, cap, w.occ.tmp_col, w.occ.tmp_val, saved->col_idx, saved->val, s);
-        if (rc == 1)
-          rc = fp4_launch_csr_gather(w.occ.tmp_col, w.occ.tmp_val, M, cap, saved->row_ptr, saved->col_idx, saved->val, s);
-      }
+      rc = emit_rows(A, bf16, M, K, K, saved->thresholds, w.qA, w.gA, nullptr, saved->row_ptr, saved->col_idx, saved->val, cap, saved->nnz,
+                     g_all, w.occ, s);
     }
     if (rc) return rc;
     // Delta_A W with the unquantized W, fp32; lands where the GEMM epilogue picks it up
@@ -502,8 +494,12 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
   FwdWs w = carve_fwd_mixed(c, M, K, N, dt);
   int rc;
-  if (w8) rc = fp8_launch_quantize_cols(W, bf16, K, N, N, w.qWt, saved->gamma_W, w.amax, s);
-  else rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s);
+  if (w8) {
+    rc = occ ? fp4_launch_clear_select(w.occ.select, nullptr, nullptr, 0, s) : FP4_OK;
+    if (!rc) rc = fp8_launch_quantize_cols(W, bf16, K, N, N, w.qWt, saved->gamma_W, w.amax, s);
+  } else {
+    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, nullptr, 0);
+  }
   if (rc) return rc;
   const float* addend = nullptr;
   if (a8) {
@@ -512,15 +508,9 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
   } else if (occ) {
     const int64_t cap = std::min(saved->capacity, provisioned_entries(M, K));
     rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s);
-    if (!rc) rc = fp4_launch_scan_rows(w.occ.row_cnt, M, saved->row_ptr, saved->nnz, s);
-    if (rc) return rc;
-    rc = fp4_launch_occ_rows(A, bf16, M, K, K, saved->thresholds, w.qA, w.gA, nullptr, saved->col_idx, saved->val,
-                             w.occ.tmp_col, w.occ.tmp_val, saved->row_ptr, cap, nullptr, s);
-    if (rc == 1) {
-      rc = fp4_launch_order_rows(saved->row_ptr, M, K, cap, w.occ.tmp_col, w.occ.tmp_val, saved->col_idx, saved->val, s);
-      if (rc == 1)
-        rc = fp4_launch_csr_gather(w.occ.tmp_col, w.occ.tmp_val, M, cap, saved->row_ptr, saved->col_idx, saved->val, s);
-    }
+    if (!rc)
+      rc = emit_rows(A, bf16, M, K, K, saved->thresholds, w.qA, w.gA, nullptr, saved->row_ptr, saved->col_idx, saved->val, cap, saved->nnz,
+                     nullptr, w.occ, s);
     if (rc) return rc;
     float* R = bf16 ? w.R : reinterpret_cast<float*>(Y);
     rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, s);
@@ -558,7 +548,7 @@ extern "C" int fp4_prepare_weights(const void* W, fp4_dtype dt, int64_t K, int64
   hipStream_t s = (hipStream_t)stream;
   const int bf16 = dt == FP4_BF16;
   uint32_t* amax = reinterpret_cast<uint32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
-  int rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, wq->qWt, wq->gamma_W, amax, s);   // forward's operand
+  int rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, wq->qWt, wq->gamma_W, amax, s, nullptr, 0);   // forward's operand
   if (rc) return rc;
   return fp4_launch_quantize_rows(W, bf16, K, N, N, wq->qWk, wq->gamma_Wk, s);                   // dgrad's operand
 }

@@ -3,9 +3,9 @@
 // CSR.  (The clamp itself is fused into the quantization pass; the transpose for the weight
 // gradient and the sparse x dense product live with the sparse kernels.)
 #include "fp4_common.h"
-#include "last_block.h"
 
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 namespace {
@@ -18,211 +18,161 @@ constexpr int SEL_BINS = 2048;  // 11-bit digits
 constexpr int SEL_THREADS = 1024;   // per workgroup: the 64 KiB of LDS tables allow two workgroups per CU,
                                     // so their size decides how many loads a CU has in flight
 
-constexpr int SEL_PASSES = 3;   // digits, at most
-
 // A digit pass: a workgroup for every 8192 elements up to 256 of them, for every 65536 up to 512 (64 x 2048 bf16, one for
-// every 8192 / 65536: 8.5 / 9.2 us with the bins picked / without; 1056 x 1376 7.1 / 10.2; 8192 x 2048, 512 / 256: 18.1 /
-// 15.6, each adds its bins to the same words).  Up to 64 of them the last one picks the bins: a launch of 4 us less; with
-// more the arrivals cost more than that (8192 x 2048: 22.9 us against 15.6 + 4.9).
-constexpr int SEL_PICK_HERE = 64;
+// every 8192 / 65536: 8.5 / 9.2 us; 1056 x 1376 7.1 / 10.2; 8192 x 2048, 512 / 256: 18.1 / 15.6, each adds its bins to the same words).
+//
+// The bins that hold the two ranks are found by whoever needs them next: every workgroup of the next digit's pass, and of the
+// count behind the last, scans them again while its first elements are on their way: 2 to 3 us, where a launch of one workgroup took
+// 4.5 and its gap.  So each digit has bins of its own in memory, all cleared before the first.
+constexpr int SEL_AT[3] = {0, SEL_BINS, 3 * SEL_BINS};      // where a digit's bins begin (the first's are shared by both targets)
+constexpr int SEL_APART[3] = {0, SEL_BINS, SEL_BINS / 2};   // from one target's bins to the other's
+constexpr int SEL_WORDS = 4 * SEL_BINS;
+// bf16: 11 + 5 bits; fp32: 11 + 11 + 10
+template <class DT> constexpr int sel_digits() { return __is_same(DT, BF16) ? 2 : 3; }
+template <class DT> constexpr int sel_bits(int pass) { return pass == 0 ? 11 : __is_same(DT, BF16) ? 5 : pass == 1 ? 11 : 10; }
+template <class DT> constexpr int sel_shift(int pass) {   // bits below a digit
+  int at = __is_same(DT, BF16) ? 16 : 32;
+  for (int p = 0; p <= pass; ++p) at -= sel_bits<DT>(p);
+  return at;
+}
+
+struct Ranks { unsigned long long v[2]; };   // 0-based, of the lo / hi order statistic
 
 // Selection state kept in the workspace between passes.
 struct SelState {
-  unsigned long long rank[2];  // remaining 0-based rank of the lo / hi order statistic
-  uint32_t prefix[2];          // key bits fixed so far (right-aligned)
-  uint32_t arrived[SEL_PASSES];   // workgroups done with a pass
-  // windows (below): thresholds and row counts came out of one pass; a NaN was met; the thresholds' bins
-  uint32_t done, nan, bin[2];
+  unsigned long long rank[2];  // remaining ranks after the first digit
+  uint32_t prefix[2];          // key bits fixed by then (right-aligned)
+  // windows (below): their first keys; thresholds and row counts came out of one pass; a NaN was met; the thresholds' bins
+  uint32_t window[2], unused, done, nan, bin[2];
+  uint32_t prefix2[2];         // after the second digit
+  unsigned long long rank2[2];
 };
+static_assert(offsetof(SelState, done) == 9 * 4, "the tests read it there");
+constexpr int SEL_CLEAR = (256 + SEL_WORDS * 8) / 8;   // 8-byte words, state and bins, that are 0 when a selection begins
 
-__global__ void sel_init_kernel(SelState* st, unsigned long long* hist, unsigned long long k,
-                                unsigned long long n, unsigned long long* total) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 2 * SEL_BINS) hist[i] = 0;
-  if (i == 0) {
-    st->rank[0] = k;
-    st->rank[1] = n - 1 - k;
-    st->prefix[0] = st->prefix[1] = 0;
-    if (total) *total = 0;
-    for (int a = 0; a < SEL_PASSES; ++a) st->arrived[a] = 0;
-    st->done = st->nan = 0;
-  }
-}
-
-// One digit pass: histogram of key digit (key >> shift) & (2^bits - 1) over the elements whose
-// higher bits equal the prefix found so far (first pass: all elements, one shared histogram).
-// The workgroup histogram is replicated (by lane) to thin out same-address LDS atomics: real
-// tensors put most of their mass in a few dozen exponent bins.
 template <class DT>
 FP4_D uint32_t key_of(uint32_t raw) {   // raw: bf16 bits (low 16) or fp32 bits
   if constexpr (__is_same(DT, BF16)) return f32_order_key(raw << 16) >> 16;
   else return f32_order_key(raw);
 }
+template <class DT>
+FP4_D float value_of(uint32_t key) {
+  // 16-bit keys are the top half of the fp32 key of a bf16 value; undo the map on
+  // 16 bits so the low half of the fp32 pattern stays zero
+  if constexpr (__is_same(DT, BF16)) return u2f(((key & 0x8000u) ? (key & 0x7fffu) : (~key & 0xffffu)) << 16);
+  else return u2f(f32_from_order_key(key));
+}
 
-// Pick, for each of the two targets, the bin that holds its rank; extend the prefix, reduce
-// the rank, clear the histograms.  After the last pass the prefix is the full key: decode it.
-// One workgroup: the one that finishes its part of the histogram last, or a launch of its own.
-FP4_D void sel_pick(SelState* st, unsigned long long* hist, int bits, int first, int last, int key_bits, float* thresholds) {
-  constexpr int PER = SEL_BINS / SEL_THREADS;   // bins a thread owns when all SEL_BINS are in use
-  __shared__ unsigned long long s_w[SEL_THREADS / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nb = 1 << bits;
-  const int per = (nb + SEL_THREADS - 1) / SEL_THREADS;
-  // both targets' bins and ranks are requested before either scan starts
-  unsigned long long vv[2][PER], rr[2];
+template <class T>
+FP4_D T scan_lanes(T v, int width) {   // inclusive, over groups of `width` lanes
+  const int at = threadIdx.x & (width - 1);
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const unsigned long long* hsrc = hist + (first ? 0 : s * SEL_BINS);
-    rr[s] = st->rank[s];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int b = tid * per + j;
-      vv[s][j] = (j < per && b < nb) ? load_device(hsrc + b) : 0;
-    }
+  for (int o = 1; o < width; o <<= 1) {
+    const T up = __shfl_up(v, o, width);
+    if (at >= o) v += up;
   }
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    unsigned long long (&v)[PER] = vv[s];
-    unsigned long long sum = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) sum += v[j];
-    // inclusive prefix of the threads' sums: the thread whose range [excl, incl) holds the rank
-    // owns the bin (the last thread, should the rank lie beyond the total)
-    unsigned long long incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
+  return v;
+}
+
+// For each of the two targets the bin that holds its rank, of NB bins each (APART words from the other's, 0: they share one histogram),
+// and its rank in there.  By all THREADS of a workgroup; of 32 bins by one wave of it (every wave for itself: 8192 x 2048, the count
+// 22.1 us instead of 10.9; all that are under way ask one memory channel for the same two lines).
+template <int THREADS, int NB, int APART>
+FP4_D void find_bins(const unsigned long long* hist, const Ranks& ranks, uint32_t (&bin)[2], Ranks& left) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  if constexpr (NB == 32) {
+    __shared__ unsigned long long s_left[2];
+    __shared__ uint32_t s_bin[2];
+    if (tid < 64) {
+      const unsigned long long v = hist[(lane >> 5) * APART + (lane & 31)], incl = scan_lanes(v, 32), excl = incl - v;
+      const unsigned long long r = lane < 32 ? ranks.v[0] : ranks.v[1];
+      // the bin whose range [excl, incl) holds the rank (the last, should the rank lie beyond the total)
+      if ((excl <= r && r < incl) || ((lane & 31) == 31 && r >= incl)) { s_bin[lane >> 5] = (uint32_t)(lane & 31); s_left[lane >> 5] = r - excl; }
     }
-    if (lane == 63) s_w[wave] = incl;
     __syncthreads();
-    for (int w = 0; w < wave; ++w) incl += s_w[w];
-    const unsigned long long r = rr[s];
-    const unsigned long long excl = incl - sum;
-    if ((excl <= r && r < incl) || (tid == SEL_THREADS - 1 && r >= incl)) {
-      unsigned long long cum = excl;
-      int j = 0;
-      const int jend = min(per, nb - tid * per);   // bins of this thread that exist (may be <= 0)
 #pragma unroll
-      for (int q = 0; q < PER - 1; ++q)
-        if (j == q && q < jend - 1 && cum + v[q] <= r) { cum += v[q]; ++j; }
-      const int b = min(tid * per + j, nb - 1);
-      const uint32_t key = (st->prefix[s] << bits) | (uint32_t)b;
-      st->rank[s] = r - cum;
-      st->prefix[s] = key;
-      if (last) {
-        if (key_bits == 16) {
-          // 16-bit keys are the top half of the fp32 key of a bf16 value; undo the map on
-          // 16 bits so the low half of the fp32 pattern stays zero
-          const uint32_t h = (key & 0x8000u) ? (key & 0x7fffu) : (~key & 0xffffu);
-          thresholds[s] = u2f(h << 16);
-        } else {
-          thresholds[s] = u2f(f32_from_order_key(key));
-        }
+    for (int s = 0; s < 2; ++s) { bin[s] = s_bin[s]; left.v[s] = s_left[s]; }
+  } else {
+    constexpr int PER = NB / THREADS, WAVES = THREADS / 64, SETS = APART ? 2 : 1;
+    static_assert(PER >= 1 && NB % THREADS == 0, "a thread owns whole bins");
+    __shared__ unsigned long long s_w[SETS][WAVES], s_left[2];
+    __shared__ uint32_t s_bin[2];
+    unsigned long long v[SETS][PER], sum[SETS], incl[SETS];
+#pragma unroll
+    for (int q = 0; q < SETS; ++q)
+#pragma unroll
+      for (int j = 0; j < PER; ++j) v[q][j] = hist[q * APART + tid * PER + j];
+#pragma unroll
+    for (int q = 0; q < SETS; ++q) {
+      sum[q] = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) sum[q] += v[q][j];
+      incl[q] = scan_lanes(sum[q], 64);
+      if (lane == 63) s_w[q][tid >> 6] = incl[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SETS; ++q)
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {   // all of them requested at once
+        const unsigned long long ws = s_w[q][w];
+        if (w < (tid >> 6)) incl[q] += ws;
+      }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int q = SETS == 2 ? s : 0;
+      const unsigned long long r = ranks.v[s], excl = incl[q] - sum[q];
+      if ((excl <= r && r < incl[q]) || (tid == THREADS - 1 && r >= incl[q])) {
+        unsigned long long cum = excl;
+        int j = 0;
+#pragma unroll
+        for (int b = 0; b < PER - 1; ++b)
+          if (j == b && cum + v[q][b] <= r) { cum += v[q][b]; ++j; }
+        s_bin[s] = (uint32_t)(tid * PER + j);
+        s_left[s] = r - cum;
       }
     }
     __syncthreads();
-  }
-  for (int i = tid; i < 2 * SEL_BINS; i += SEL_THREADS) hist[i] = 0;
-}
-
-// PICK: the workgroup that is done last picks the bins.  BEHIND: launched behind the one pass of large tensors (below), which may
-// have left nothing to do; elsewhere nothing is asked before the first element is requested.
-template <class DT, bool FIRST, bool PICK, bool BEHIND>
-__global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, int64_t rows, int64_t cols,
-                                                       int64_t ld, int shift, int bits, int pass, int last, int key_bits,
-                                                       SelState* st, unsigned long long* hist, float* thresholds) {
-  constexpr bool first = FIRST;
-  if constexpr (BEHIND) {
-    if (st->done) return;
-  }
-  __shared__ uint32_t h[8 * SEL_BINS];   // first pass: 8 replicas; later: 4 replicas x 2 targets
-  for (int i = threadIdx.x; i < 8 * SEL_BINS; i += SEL_THREADS) h[i] = 0;
-  __syncthreads();
-  const uint32_t mask = (1u << bits) - 1u;
-  const uint32_t p0 = st->prefix[0], p1 = st->prefix[1];
-  const int hs = shift + bits;
-  const int lane = threadIdx.x & 63;
-  uint32_t* const hrep = first ? &h[(lane & 7) * SEL_BINS] : &h[(lane & 3) * 2 * SEL_BINS];
-  auto visit = [&](uint32_t raw) {
-    const uint32_t key = key_of<DT>(raw);
-    const uint32_t d = (key >> shift) & mask;
-    if (first) {
-      atomicAdd(&hrep[d], 1u);
-    } else {
-      const uint32_t hi_bits = hs >= 32 ? 0u : (key >> hs);
-      if (hi_bits == p0) atomicAdd(&hrep[d], 1u);
-      if (hi_bits == p1) atomicAdd(&hrep[SEL_BINS + d], 1u);
-    }
-  };
-  constexpr int EPV = __is_same(DT, BF16) ? 8 : 4;   // elements per 16-byte load
-  const bool flat = (ld == cols) && (cols % EPV) == 0;
-  if (flat) {
-    const int64_t nvec = rows * cols / EPV;
-    const u32x4* xv = reinterpret_cast<const u32x4*>(x);
-    auto visit_vec = [&](const u32x4& r) {
-      if constexpr (__is_same(DT, BF16)) {
-        visit(r.x & 0xffffu); visit(r.x >> 16); visit(r.y & 0xffffu); visit(r.y >> 16);
-        visit(r.z & 0xffffu); visit(r.z >> 16); visit(r.w & 0xffffu); visit(r.w >> 16);
-      } else {
-        visit(r.x); visit(r.y); visit(r.z); visit(r.w);
-      }
-    };
-    // four loads in flight per lane: with the LDS tables limiting a CU to two workgroups, one
-    // load at a time leaves the memory pipe mostly idle
-    const int64_t stride = (int64_t)gridDim.x * SEL_THREADS;
-    int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x;
-    for (; i + 3 * stride < nvec; i += 4 * stride) {
-      const u32x4 r0 = xv[i], r1 = xv[i + stride], r2 = xv[i + 2 * stride], r3 = xv[i + 3 * stride];
-      visit_vec(r0); visit_vec(r1); visit_vec(r2); visit_vec(r3);
-    }
-    for (; i < nvec; i += stride) visit_vec(xv[i]);
-  } else {
-    const int64_t n = rows * cols;
-    for (int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * SEL_THREADS) {
-      const int64_t r = i / cols, c = i - r * cols;
-      if constexpr (__is_same(DT, BF16)) visit(reinterpret_cast<const uint16_t*>(x)[r * ld + c]);
-      else visit(reinterpret_cast<const uint32_t*>(x)[r * ld + c]);
-    }
-  }
-  __syncthreads();
-  if (first) {
-    for (int i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) {
-      uint32_t v = 0;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) v += h[r * SEL_BINS + i];
-      if (v) atomicAdd(&hist[i], (unsigned long long)v);
-    }
-  } else {
-    for (int i = threadIdx.x; i < 2 * SEL_BINS; i += SEL_THREADS) {
-      uint32_t v = 0;
+    for (int s = 0; s < 2; ++s) { bin[s] = s_bin[s]; left.v[s] = s_left[s]; }
+  }
+}
+
+// What digit pass PASS - 1 found: the keys' leading bits, and the ranks that remain.  keep: left in memory for the passes after this.
+template <class DT, int PASS, int THREADS>
+FP4_D void find_digit(SelState* st, const unsigned long long* hist, const Ranks& ranks, bool keep, uint32_t (&prefix)[2]) {
+  constexpr int D = PASS - 1;
+  Ranks in = ranks, left;
+  if constexpr (D > 0)
+    for (int s = 0; s < 2; ++s) in.v[s] = D == 1 ? st->rank[s] : st->rank2[s];
+  uint32_t bin[2];
+  find_bins<THREADS, 1 << sel_bits<DT>(D), SEL_APART[D]>(hist + SEL_AT[D], in, bin, left);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v += h[r * 2 * SEL_BINS + i];
-      if (v) atomicAdd(&hist[i], (unsigned long long)v);
+  for (int s = 0; s < 2; ++s) {
+    prefix[s] = D == 0 ? bin[s] : ((D == 1 ? st->prefix[s] : st->prefix2[s]) << sel_bits<DT>(D)) | bin[s];
+    if (keep && threadIdx.x == 0) {
+      if (D == 0) { st->prefix[s] = prefix[s]; st->rank[s] = left.v[s]; }
+      else { st->prefix2[s] = prefix[s]; st->rank2[s] = left.v[s]; }
     }
   }
-  if constexpr (PICK) {
-    if (last_workgroup(&st->arrived[pass], gridDim.x)) sel_pick(st, hist, bits, first, last, key_bits, thresholds);
-  }
 }
 
-__global__ __launch_bounds__(SEL_THREADS) void sel_pick_kernel(SelState* st, unsigned long long* hist, int bits, int first, int last,
-                                                               int key_bits, float* thresholds) {
-  sel_pick(st, hist, bits, first, last, key_bits, thresholds);
-}
-
-// ---- Large bf16 tensors: thresholds and the rows' outlier counts out of one pass ------------------------------------------
-// A sample says where the thresholds are, to within a few of the 2048 leading 11-bit digits; the pass over all elements then
-// needs bins only for the keys around them (three digits, 96 keys a threshold), counts what lies outside, and keeps every
-// row's bins: with the thresholds known, a row's outliers are a sum over those.  Where a threshold turns out not to lie in
-// its window, or a NaN is about, `done` stays 0 and the passes of the general path, launched behind, do their work; otherwise
-// they leave at once.
+// ---- bf16 tensors: thresholds and the rows' outlier counts out of one pass -------------------------------------------------
+// The leading 11-bit digits of the thresholds, exactly (from a digit pass, up to 2^25 elements) or to within a few of 2048 (from a
+// sample), leave few keys; the pass over all elements then needs bins only for the keys around them (three digits, 96 keys a
+// threshold), counts what lies outside, and keeps every row's bins: with the thresholds known, a row's outliers are a sum over those.
+// Where a sampled threshold turns out not to lie in its window, or a NaN is about, `done` stays 0 and the passes of the general path,
+// launched behind, do their work; otherwise they leave at once.  Behind an exact digit the thresholds always come out of the bins, and
+// what can fail (a NaN, zeros that are outliers) is that the rows' bins tell the rows' counts: those are taken from the elements then.
 // Bound by the one read and, about as long, by vector instructions (nine an element, twelve where zeros are counted apart).
-// 16384 x 11008, in us: init 4.6, sample 6.6, picks 4.8 + 4.7, the pass 94.7, the general path's two launches 9, rows 4.9, together
-// 130; digit passes, picks and the count of the rows after them 249.  16384 x 4096: 71 against 107.  With scan and emission: half
-// zeros, 16384 x 11008, 250 against 540; a miss 419 against 353.  Below 2^25 elements the launches cost what the pass saves (8192 x
-// 2048: digit passes, picks and count 43, of which this would leave 40).
+// 16384 x 11008, in us: sample 6.6, the pass 97, the general path's two launches 10, rows 6, together 119 (130 with picks in launches of
+// their own, of 4.8 each); digit passes, picks and the count of the rows after them 249.  16384 x 4096: 65 against 107.  Half
+// zeros, 16384 x 11008, with scan and emission, 250 against 540; a miss 419 against 353.  8192 x 2048, behind a digit pass of 14 us: the
+// pass 19.5, rows 7.6, where a second digit pass and the count of the rows took 15 and 11 and two picks and the clearing 4.5 each; 1056 x
+// 1376 7.2 + 8.1 + 4.2 against 7.1 + 4.4 + 7.3 + 4.0 + 4.2 and 2.2.
 constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STRIDE = 200;   // bins; a wave's table; a row's in memory
+// in memory: the sample's bins and the windows', beside the digits'
+constexpr int SAMPLE_AT = SEL_AT[2], WIN_AT = SEL_AT[1] + 64;
 constexpr uint32_t KEY_NEG_ZERO = 0x7fff, KEY_POS_ZERO = 0x8000;
 constexpr int SAMPLE_BLOCKS = 128, SAMPLE_RUNS = SAMPLE_BLOCKS * 2 * (SEL_THREADS / 64);   // runs of 64 16-byte vectors
 
@@ -248,19 +198,20 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_sample_kernel(const u32x4* x,
     uint32_t v = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) v += h[q * SEL_BINS + i];
-    if (v) atomicAdd(&hist[i], (unsigned long long)v);
+    if (v) atomicAdd(&hist[SAMPLE_AT + i], (unsigned long long)v);
   }
 }
 
 // First keys of the windows, from the digits that the sample's order statistics have.  Windows that would meet lie side by
-// side, and either threshold may be in either.  (The lowest digit is that of a negative NaN.)
+// side, and either threshold may be in either.
 struct Windows {
   uint32_t w0, w1;
-  FP4_D explicit Windows(const SelState* st) {
-    const int d0 = min(max((int)st->prefix[0] - 1, 1), SEL_BINS - 6);
-    w0 = (uint32_t)d0 * 32u;
-    w1 = (uint32_t)min(max((int)st->prefix[1] - 1, d0 + 3), SEL_BINS - 3) * 32u;
+  FP4_D explicit Windows(const uint32_t (&digit)[2]) {
+    const int d0 = min(max((int)digit[0] - 1, 0), SEL_BINS - 6);
+    w0 = max((uint32_t)d0 * 32u, 1u);   // bin 0 is what lies below: key 0 alone, then
+    w1 = max((uint32_t)min(max((int)digit[1] - 1, d0 + 3), SEL_BINS - 3) * 32u, w0 + WIN_KEYS);
   }
+  FP4_D explicit Windows(const SelState* st) : w0(st->window[0]), w1(st->window[1]) {}
   FP4_D bool side_by_side() const { return w0 + WIN_KEYS == w1; }
   // Bin 0: below the lower window, 1 .. 96 in it, 97 between the two (not kept), 98 .. 193 in the upper one, 194 above.
   FP4_D int bin(uint32_t key) const {
@@ -274,11 +225,15 @@ struct Windows {
 };
 
 // A wave per row.
-__global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int64_t rows, int64_t cols, SelState* st, unsigned long long* hist,
-                                                         uint16_t* row_bins) {
+__global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int64_t rows, int64_t cols, Ranks sample, const unsigned long long* digits,
+                                                         SelState* st, unsigned long long* hist, uint16_t* row_bins) {
   __shared__ uint32_t tab[16][WIN_LDS];
   __shared__ uint32_t total[WIN_LDS + 2];
-  const Windows win(st);
+  uint32_t digit[2];
+  Ranks left;
+  find_bins<1024, SEL_BINS, 0>(digits, sample, digit, left);
+  const Windows win(digit);
+  if (blockIdx.x == 0 && threadIdx.x == 0) { st->window[0] = win.w0; st->window[1] = win.w1; }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t* const t = tab[wave];
 #pragma unroll
@@ -355,19 +310,21 @@ __global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int6
   }
   if (max(top.x, top.y) > 0x7f80) st->nan = 1;
   __syncthreads();
-  if (threadIdx.x < WIN_LDS + 2 && total[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)total[threadIdx.x]);
+  if (threadIdx.x < WIN_LDS + 2 && total[threadIdx.x]) atomicAdd(&hist[WIN_AT + threadIdx.x], (unsigned long long)total[threadIdx.x]);
 }
 
-// The thresholds from the bins' totals, or the state that the general path starts from.
-__global__ __launch_bounds__(WIN_LDS) void win_pick_kernel(SelState* st, unsigned long long* hist, unsigned long long k, unsigned long long n,
-                                                           float* thresholds) {
+// The thresholds' keys and bins from the bins' totals; false where rows' bins don't tell the rows' outliers, or the windows were missed.
+// By all threads of a workgroup of 256 or more.
+FP4_D bool find_windowed(const SelState* st, const unsigned long long* all_bins, const Ranks& ranks, unsigned long long n,
+                         uint32_t (&key_out)[2], uint32_t (&bin_out)[2]) {
+  const unsigned long long* const hist = all_bins + WIN_AT;
   __shared__ unsigned long long s_w[WIN_LDS / 64];
   __shared__ uint32_t key[2], bin[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const unsigned long long k = ranks.v[0];
   const Windows win(st);
-  const bool zeros_apart = win.zeros_apart();
   unsigned long long v = tid < WIN_BINS ? hist[tid] : 0, neg = 0, pos = 0;
-  if (zeros_apart) {   // the sums of win_count_kernel, undone
+  if (win.zeros_apart()) {   // the sums of win_count_kernel, undone
     const unsigned long long nz1 = hist[WIN_LDS], nz2 = hist[WIN_LDS + 1];
     neg = n - nz1;
     pos = 2 * nz1 - nz2;
@@ -375,14 +332,14 @@ __global__ __launch_bounds__(WIN_LDS) void win_pick_kernel(SelState* st, unsigne
     if (tid == win.bin(KEY_POS_ZERO)) v += pos;
   }
   if (tid == WIN_KEYS + 1) v = 0;
-  if (tid < 2) bin[tid] = 0;
+  if (tid < 2) bin[tid] = WIN_BINS;
   unsigned long long incl = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const unsigned long long up = __shfl_up(incl, o, 64);
     if (lane >= o) incl += up;
   }
-  if (lane == 63) s_w[wave] = incl;
+  if (lane == 63 && wave < WIN_LDS / 64) s_w[wave] = incl;
   __syncthreads();
   unsigned long long total = 0;   // without what lies between the windows
   for (int w = 0; w < WIN_LDS / 64; ++w) {
@@ -390,59 +347,289 @@ __global__ __launch_bounds__(WIN_LDS) void win_pick_kernel(SelState* st, unsigne
     total += s_w[w];
   }
   const unsigned long long below = incl - v, above = total - incl;
-  const bool lower = tid >= 1 && tid <= WIN_KEYS, upper = tid >= WIN_KEYS + 2 && tid < WIN_BINS - 1, both = win.side_by_side();
+  const bool lower = (tid >= 1 || win.w0 == 1) && tid <= WIN_KEYS, upper = tid >= WIN_KEYS + 2 && tid < WIN_BINS - 1, both = win.side_by_side();
   const uint32_t mine = lower ? win.w0 + tid - 1 : win.w1 + tid - (WIN_KEYS + 2);
   if ((lower || (upper && both)) && below <= k && k < incl) { bin[0] = tid; key[0] = mine; }
   if ((upper || (lower && both)) && above <= k && k < above + v) { bin[1] = tid; key[1] = mine; }   // the (k + 1)-th from the top
   __syncthreads();
-  if (tid == 0) {
-    // Rows' bins leave zeros out where they are counted apart: right while they are no outliers.
-    const bool ok = bin[0] && bin[1] && !st->nan && !(neg + pos && (key[0] > KEY_POS_ZERO || key[1] < KEY_NEG_ZERO));
-    if (ok)
-      for (int s = 0; s < 2; ++s) thresholds[s] = u2f(((key[s] & 0x8000u) ? (key[s] & 0x7fffu) : (~key[s] & 0xffffu)) << 16);
-    st->done = ok;
-    st->bin[0] = bin[0];
-    st->bin[1] = bin[1];
-    st->rank[0] = k;
-    st->rank[1] = n - 1 - k;
-    st->prefix[0] = st->prefix[1] = 0;
-  }
-  hist[tid] = 0;
-  if (tid < 2) hist[WIN_LDS + tid] = 0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) { key_out[q] = key[q]; bin_out[q] = bin[q]; }
+  // Rows' bins leave zeros out where they are counted apart: right while they are no outliers.
+  return bin_out[0] < WIN_BINS && bin_out[1] < WIN_BINS && !st->nan &&
+         !(neg + pos && (key_out[0] > KEY_POS_ZERO || key_out[1] < KEY_NEG_ZERO));
 }
 
-// Outliers of each row: from its bins, or, where the windows were missed, from its elements.  A wave per row.
-__global__ __launch_bounds__(256) void win_rows_kernel(const uint16_t* x, int64_t rows, int64_t cols, const SelState* st, const uint16_t* row_bins,
-                                                       const float* thr, int32_t* row_cnt) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  int cnt = 0;
-  if (st->done) {
-    const int b0 = (int)st->bin[0], b1 = (int)st->bin[1];
+// One digit pass: histogram of the key's digit over the elements whose higher bits equal the prefix found so far (first pass: all
+// elements, one shared histogram).
+// The workgroup histogram is replicated (by lane) to thin out same-address LDS atomics: real
+// tensors put most of their mass in a few dozen exponent bins.
+// BEHIND: launched behind the one pass of large tensors (below), which may have left nothing to do.
+template <class DT, int PASS, bool BEHIND>
+__global__ __launch_bounds__(SEL_THREADS) void sel_hist_kernel(const void* x, int64_t rows, int64_t cols, int64_t ld, Ranks ranks,
+                                                               SelState* st, unsigned long long* hist, float* thresholds) {
+  constexpr bool first = PASS == 0;
+  constexpr int BINS = 1 << sel_bits<DT>(PASS), SHIFT = sel_shift<DT>(PASS), HS = SHIFT + sel_bits<DT>(PASS);
+  constexpr int TABLE = first ? BINS : 2 * BINS, REPLICAS = first ? 8 : 4;
+  constexpr int EPV = __is_same(DT, BF16) ? 8 : 4;   // elements per 16-byte load
+  __shared__ uint32_t h[REPLICAS * TABLE];
+  const bool flat = (ld == cols) && (cols % EPV) == 0;
+  const int64_t nvec = flat ? rows * cols / EPV : 0, stride = (int64_t)gridDim.x * SEL_THREADS;
+  const u32x4* const xv = reinterpret_cast<const u32x4*>(x);
+  int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x;
+  // four loads in flight per lane, the first four before anything else: with the LDS tables limiting a CU to two workgroups, one
+  // load at a time leaves the memory pipe mostly idle
+  u32x4 r[4];
+  auto fetch = [&](int64_t at) {
 #pragma unroll
-    for (int j = 0; j < WIN_LDS / 64; ++j) {
-      const int b = lane + 64 * j;
-      if (b < b0 || (b > b1 && b < WIN_BINS)) cnt += row_bins[row * WIN_STRIDE + b];
+    for (int j = 0; j < 4; ++j)
+      if (at + j * stride < nvec) r[j] = xv[at + j * stride];
+  };
+  if constexpr (!BEHIND) fetch(i);
+  for (int b = threadIdx.x; b < REPLICAS * TABLE; b += SEL_THREADS) h[b] = 0;
+  uint32_t p[2] = {0, 0};
+  if constexpr (BEHIND) {
+    if constexpr (first) {
+      uint32_t key[2], bin[2];
+      const bool ok = find_windowed(st, hist, ranks, rows * cols, key, bin);
+      if (blockIdx.x == 0 && threadIdx.x < 2) {
+        if (ok) thresholds[threadIdx.x] = value_of<DT>(threadIdx.x ? key[1] : key[0]);
+        st->bin[threadIdx.x] = threadIdx.x ? bin[1] : bin[0];
+        st->done = ok;
+      }
+      if (ok) return;
+    } else if (st->done) {
+      return;
     }
-  } else {
-    const float lo = thr[0], hi = thr[1];
-    const u32x4* const xr = reinterpret_cast<const u32x4*>(x + row * cols);
-    for (int64_t i = lane; i < cols / 8; i += 64) {
-      const u32x4 r = xr[i];
+    fetch(i);
+  }
+  if constexpr (!first) find_digit<DT, PASS, SEL_THREADS>(st, hist, ranks, blockIdx.x == 0, p);
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  uint32_t* const hrep = &h[(lane & (REPLICAS - 1)) * TABLE];
+  auto visit = [&](uint32_t raw) {
+    const uint32_t key = key_of<DT>(raw);
+    const uint32_t d = (key >> SHIFT) & (BINS - 1);
+    if constexpr (first) {
+      atomicAdd(&hrep[d], 1u);
+    } else {
+      const uint32_t hi_bits = key >> HS;
+      if (hi_bits == p[0]) atomicAdd(&hrep[d], 1u);
+      if (hi_bits == p[1]) atomicAdd(&hrep[BINS + d], 1u);
+    }
+  };
+  if (flat) {
+    auto visit_vec = [&](const u32x4& v) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float a = u2f(r[e] << 16), b = u2f(r[e] & 0xffff0000u);
-        cnt += (((a < lo) | (a > hi)) ? 1 : 0) + (((b < lo) | (b > hi)) ? 1 : 0);
+        if constexpr (__is_same(DT, BF16)) { visit(v[e] & 0xffffu); visit(v[e] >> 16); }
+        else visit(v[e]);
       }
+    };
+    while (i < nvec) {
+      const u32x4 c[4] = {r[0], r[1], r[2], r[3]};
+      fetch(i + 4 * stride);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (i + j * stride < nvec) visit_vec(c[j]);
+      i += 4 * stride;
+    }
+  } else {
+    const int64_t n = rows * cols;
+    for (; i < n; i += stride) {
+      const int64_t row = i / cols, c = i - row * cols;
+      if constexpr (__is_same(DT, BF16)) visit(reinterpret_cast<const uint16_t*>(x)[row * ld + c]);
+      else visit(reinterpret_cast<const uint32_t*>(x)[row * ld + c]);
     }
   }
+  __syncthreads();
+  for (int b = threadIdx.x; b < TABLE; b += SEL_THREADS) {
+    uint32_t v = 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (lane == 0) row_cnt[row] = cnt;
+    for (int q = 0; q < REPLICAS; ++q) v += h[q * TABLE + b];
+    if (v) atomicAdd(&hist[SEL_AT[PASS] + (b < BINS ? b : SEL_APART[PASS] + b - BINS)], (unsigned long long)v);
+  }
+}
+
+// ---- Outliers of each row, and of each block of 4 << shift rows -----------------------------------------------------------
+// Eight elements of a row as loaded.
+template <class DT> struct Unit { u32x4 r[__is_same(DT, BF16) ? 1 : 2]; };
+template <class DT>
+FP4_D void load_unit(const void* x, int64_t off, int valid, Unit<DT>& u) {
+  constexpr int E = __is_same(DT, BF16) ? 2 : 4;   // bytes an element
+  const uint8_t* const p = reinterpret_cast<const uint8_t*>(x) + off * E;
+  if (valid >= 8) {
+#pragma unroll
+    for (int q = 0; q < E / 2; ++q) u.r[q] = reinterpret_cast<const u32x4*>(p)[q];
+  } else {
+    uint32_t w[2 * E] = {};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (e >= valid) continue;
+      if constexpr (E == 2) w[e / 2] |= (uint32_t)reinterpret_cast<const uint16_t*>(p)[e] << (16 * (e & 1));
+      else w[e] = reinterpret_cast<const uint32_t*>(p)[e];
+    }
+#pragma unroll
+    for (int q = 0; q < 2 * E; ++q) u.r[q / 4][q % 4] = w[q];
+  }
+}
+template <class DT>
+FP4_D int count_unit(const Unit<DT>& u, int valid, float lo, float hi) {
+  int cnt = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float v;
+    if constexpr (__is_same(DT, BF16)) v = u2f((e & 1) ? u.r[0][e / 2] & 0xffff0000u : u.r[0][e / 2] << 16);
+    else v = u2f(u.r[e / 4][e % 4]);
+    cnt += (e < valid && ((v < lo) | (v > hi))) ? 1 : 0;
+  }
+  return cnt;
+}
+
+struct RowCounts { int32_t *cnt, *sum; int shift; };   // sum[b]: of rows b * (4 << shift) ..
+
+FP4_D int wave_sum(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// A wave per row and four at a time; find(thr) gives the thresholds to all threads, while the first elements are on their way.
+template <class DT, class F>
+FP4_D void count_rows(const void* x, int64_t rows, int64_t cols, int64_t ld, const RowCounts& out, F&& find) {
+  __shared__ int s_sum[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = 1 << out.shift;
+  const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * per;
+  const int nrows = (int)min((int64_t)per, rows - row0);   // may be <= 0
+  const int64_t nunits = (cols + 7) / 8;
+  const int steps = (int)((nunits + 255) / 256);           // of four units a lane
+  auto valid_of = [&](int step, int q) {
+    const int64_t unit = (int64_t)step * 256 + q * 64 + lane;
+    return unit < nunits ? (int)min((int64_t)8, cols - unit * 8) : 0;
+  };
+  Unit<DT> u[4];
+  auto fetch = [&](int row, int step) {
+    if (row >= nrows) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load_unit<DT>(x, (row0 + row) * ld + ((int64_t)step * 256 + q * 64 + lane) * 8, valid_of(step, q), u[q]);
+  };
+  fetch(0, 0);
+  float thr[2];
+  find(thr);
+  int sum = 0;
+  for (int row = 0; row < nrows; ++row) {
+    int cnt = 0;
+    for (int step = 0; step < steps; ++step) {
+      const Unit<DT> c[4] = {u[0], u[1], u[2], u[3]};
+      if (step + 1 < steps) fetch(row, step + 1);
+      else fetch(row + 1, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cnt += count_unit<DT>(c[q], valid_of(step, q), thr[0], thr[1]);
+    }
+    cnt = wave_sum(cnt);
+    if (lane == 0) out.cnt[row0 + row] = cnt;
+    sum += cnt;
+  }
+  if (lane == 0) s_sum[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) out.sum[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+}
+
+// After the last digit pass: the thresholds, to memory as well, and the counts.
+template <class DT>
+FP4_D void find_thresholds(SelState* st, const unsigned long long* hist, const Ranks& ranks, float* thresholds, float (&thr)[2]) {
+  uint32_t key[2];
+  find_digit<DT, sel_digits<DT>(), 256>(st, hist, ranks, false, key);
+  thr[0] = value_of<DT>(key[0]);
+  thr[1] = value_of<DT>(key[1]);
+  if (blockIdx.x == 0 && threadIdx.x < 2) thresholds[threadIdx.x] = thr[threadIdx.x];
+}
+
+template <class DT>
+__global__ __launch_bounds__(256) void sel_count_kernel(const void* x, int64_t rows, int64_t cols, int64_t ld, Ranks ranks, SelState* st,
+                                                        const unsigned long long* hist, float* thresholds, RowCounts out) {
+  count_rows<DT>(x, rows, cols, ld, out, [&](float (&thr)[2]) { find_thresholds<DT>(st, hist, ranks, thresholds, thr); });
+}
+
+__global__ __launch_bounds__(256) void sel_clear_kernel(unsigned long long* clear, const float* src, float* dst, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (clear && i < SEL_CLEAR) clear[i] = 0;
+  if (i < n) dst[i] = src[i];
+}
+
+// Outliers of each row: from its bins, or, where these don't tell, from its elements.  EXACT: the windows hold the thresholds, which are
+// still to be found; otherwise the digit passes have run.
+template <bool EXACT>
+__global__ __launch_bounds__(256) void win_rows_kernel(const uint16_t* x, int64_t rows, int64_t cols, Ranks ranks, SelState* st,
+                                                       const unsigned long long* hist, const uint16_t* row_bins, float* thresholds, RowCounts out) {
+  uint32_t key[2] = {}, bin[2] = {st->bin[0], st->bin[1]};
+  const bool ok = EXACT ? find_windowed(st, hist, ranks, rows * cols, key, bin) : st->done != 0;
+  if (EXACT && blockIdx.x == 0 && threadIdx.x < 2) thresholds[threadIdx.x] = value_of<BF16>(threadIdx.x ? key[1] : key[0]);
+  if (!ok) {
+    count_rows<BF16>(x, rows, cols, cols, out, [&](float (&thr)[2]) {
+      if constexpr (EXACT) { thr[0] = value_of<BF16>(key[0]); thr[1] = value_of<BF16>(key[1]); }
+      else find_thresholds<BF16>(st, hist, ranks, thresholds, thr);
+    });
+    return;
+  }
+  __shared__ int s_sum[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = 1 << out.shift;
+  const int b0 = (int)bin[0], b1 = (int)bin[1];
+  const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * per;
+  int sum = 0;
+  for (int j = 0; j < per; ++j) {
+    const int64_t row = row0 + j;
+    int cnt = 0;
+    if (row < rows)
+#pragma unroll
+      for (int q = 0; q < WIN_LDS / 64; ++q) {
+        const int b = lane + 64 * q;
+        if (b < b0 || (b > b1 && b < WIN_BINS)) cnt += row_bins[row * WIN_STRIDE + b];
+      }
+    cnt = wave_sum(cnt);
+    if (lane == 0 && row < rows) out.cnt[row] = cnt;
+    sum += cnt;
+  }
+  if (lane == 0) s_sum[wave] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) out.sum[blockIdx.x] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
 }
 
 // ---- CSR finalisation ---------------------------------------------------------------------
+// ptr[0] = 0, ptr[i+1] = sum cnt[0..i]; optional copy of the total.  A workgroup for 1024 counts, which adds up those before them
+// for itself: up to 64 Ki counts, from L2, 16 bytes a thread at a time.  One workgroup for all of them wrote 16 strided runs a thread:
+// 8192 counts 6.6 -> 4.9 us, 16384 11.0 -> 5.1.
+constexpr int64_t SCAN_WIDE = 65536;
+__global__ __launch_bounds__(1024) void scan_counts_wide_kernel(const int32_t* cnt, int64_t n, int64_t* ptr, int64_t* total_out) {
+  __shared__ long long s_before[16], s_w[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t b0 = (int64_t)blockIdx.x * 1024, i = b0 + tid;
+  const long long mine = i < n ? cnt[i] : 0;
+  long long before = 0;
+#pragma unroll 4
+  for (int64_t j = (int64_t)tid * 4; j < b0; j += 4096) {   // b0 is a multiple of 4
+    const i32x4 t = *reinterpret_cast<const i32x4*>(cnt + j);
+    before += (long long)t.x + t.y + t.z + t.w;
+  }
+  long long incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+    before += __shfl_xor(before, o, 64);
+  }
+  if (lane == 63) { s_w[wave] = incl; s_before[wave] = before; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const long long t = s_w[w];
+    incl += s_before[w];
+    if (w < wave) incl += t;
+  }
+  if (i < n) ptr[i + 1] = incl;
+  if (i == 0) ptr[0] = 0;
+  if (i == n - 1 && total_out) *total_out = incl;
+}
+
 // ptr[0] = 0, ptr[i+1] = sum cnt[0..i]; optional copy of the total.  One workgroup; a thread
 // takes 16 consecutive counts, so one block scan covers 16384 of them.
 __global__ __launch_bounds__(1024) void scan_counts_kernel(const int32_t* cnt, int64_t n, int64_t* ptr,
@@ -516,91 +703,83 @@ __global__ __launch_bounds__(256) void csr_gather_kernel(const int32_t* tmp_col,
 }  // namespace
 
 // ---- internal launchers -----------------------------------------------------------------------
-size_t fp4_select_scratch_bytes() {
-  return align_up(sizeof(SelState), 256) + align_up(2 * SEL_BINS * sizeof(unsigned long long), 256);
-}
+size_t fp4_select_scratch_bytes() { return SEL_CLEAR * 8; }
+int64_t fp4_select_clear_words() { return SEL_CLEAR; }
 
-namespace {
-// The digit passes, from the state that sel_init_kernel left, or (behind) win_pick_kernel.
-void launch_digits(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, float* thresholds, SelState* st, unsigned long long* hist,
-                   bool behind, hipStream_t s) {
-  const int64_t n = rows * cols;
-  const int key_bits = bf16 ? 16 : 32;
-  int digits[3];
-  int nd;
-  if (bf16) { digits[0] = 11; digits[1] = 5; nd = 2; }
-  else { digits[0] = 11; digits[1] = 11; digits[2] = 10; nd = 3; }
-  int shift = key_bits;
-  const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
-  const bool pick_here = behind || grid <= SEL_PICK_HERE;   // launches that mostly leave at once: as few as there can be
-  for (int p = 0; p < nd; ++p) {
-    shift -= digits[p];
-    auto launch = [&](auto dt, auto first, auto pick, auto after) {
-      hipLaunchKernelGGL((sel_hist_kernel<decltype(dt), decltype(first)::value, decltype(pick)::value, decltype(after)::value>), dim3(grid),
-                         dim3(SEL_THREADS), 0, s, x, rows, cols, ld, shift, digits[p], p, p == nd - 1, key_bits, st, hist, thresholds);
-    };
-    auto pass = [&](auto dt, auto first) {
-      if constexpr (__is_same(decltype(dt), BF16)) {
-        if (behind) return launch(dt, first, std::true_type{}, std::true_type{});
-      }
-      if (pick_here) launch(dt, first, std::true_type{}, std::false_type{});
-      else launch(dt, first, std::false_type{}, std::false_type{});
-    };
-    if (p == 0) { if (bf16) pass(BF16{}, std::true_type{}); else pass(F32{}, std::true_type{}); }
-    else { if (bf16) pass(BF16{}, std::false_type{}); else pass(F32{}, std::false_type{}); }
-    if (!pick_here)
-      hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(SEL_THREADS), 0, s, st, hist, digits[p], p == 0, p == nd - 1, key_bits,
-                         thresholds);
-  }
-}
-}  // namespace
-
-// Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1].
-// Also zeroes *total (the residual entry counter) when given.
-int fp4_launch_thresholds(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k,
-                          float* thresholds, void* scratch, unsigned long long* total, hipStream_t s) {
-  SelState* st = reinterpret_cast<SelState*>(scratch);
-  unsigned long long* hist =
-      reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
-  const int64_t n = rows * cols;
-  hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist,
-                     (unsigned long long)k, (unsigned long long)n, total);
-  launch_digits(x, bf16, rows, cols, ld, thresholds, st, hist, false, s);
+// Clears a selection's scratch (null: none) and copies n floats: what a layer does ahead of its passes, in one launch.
+int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t n, hipStream_t s) {
+  const int64_t most = std::max<int64_t>(scratch ? SEL_CLEAR : 0, n);
+  if (most == 0) return FP4_OK;
+  hipLaunchKernelGGL(sel_clear_kernel, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, reinterpret_cast<unsigned long long*>(scratch),
+                     src, dst, n);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
 
-// Thresholds and outlier counts of rows in one pass; 1 where that is not the better way (the caller then does one after the other).
-// rows_scratch: words that are free until the rows' entries are emitted.
+// Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1], then the outliers of each row (row_cnt) and
+// of each block of 4 << shift rows (row_sum).  scratch: fp4_select_scratch_bytes(), cleared.  rows_scratch: words that are free until
+// the rows' entries are emitted.
 int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
-                                     void* scratch, unsigned long long* total, void* rows_scratch, int64_t rows_scratch_words,
-                                     int32_t* row_cnt, hipStream_t s) {
+                                     void* scratch, void* rows_scratch, int64_t rows_scratch_words, int32_t* row_cnt, int32_t* row_sum,
+                                     int shift, hipStream_t s) {
+  SelState* const st = reinterpret_cast<SelState*>(scratch);
+  unsigned long long* const hist = reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + 256);
   const int64_t n = rows * cols;
-  if (!bf16 || ld != cols || cols % 8 != 0 || cols > 65535 || n < ((int64_t)1 << 25) || n >= ((int64_t)1 << 32) ||
-      rows * WIN_STRIDE > 2 * rows_scratch_words)
-    return 1;
-  SelState* st = reinterpret_cast<SelState*>(scratch);
-  unsigned long long* hist =
-      reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(scratch) + align_up(sizeof(SelState), 256));
-  // the sample's ranks first
-  const int64_t ns = (int64_t)SAMPLE_RUNS * 64 * 8;
-  const unsigned long long ks = (unsigned long long)((double)k / (double)n * (double)ns);
-  hipLaunchKernelGGL(sel_init_kernel, dim3(2 * SEL_BINS / 256), dim3(256), 0, s, st, hist, ks, (unsigned long long)ns, total);
-  hipLaunchKernelGGL(sel_sample_kernel, dim3(SAMPLE_BLOCKS), dim3(SEL_THREADS), 0, s, reinterpret_cast<const u32x4*>(x), n / 8, hist);
-  hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(SEL_THREADS), 0, s, st, hist, 11, 1, 0, 16, thresholds);
-  uint16_t* const bins = reinterpret_cast<uint16_t*>(rows_scratch);
-  const uint16_t* const xp = reinterpret_cast<const uint16_t*>(x);
-  hipLaunchKernelGGL(win_count_kernel, dim3((unsigned)std::min<int64_t>((rows + 15) / 16, 512)), dim3(1024), 0, s, xp, rows, cols, st, hist, bins);
-  hipLaunchKernelGGL(win_pick_kernel, dim3(1), dim3(256), 0, s, st, hist, (unsigned long long)k, (unsigned long long)n, thresholds);
-  launch_digits(x, bf16, rows, cols, ld, thresholds, st, hist, true, s);
-  hipLaunchKernelGGL(win_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, xp, rows, cols, st, bins, thresholds, row_cnt);
+  const Ranks ranks = {{(unsigned long long)k, (unsigned long long)(n - 1 - k)}};
+  const RowCounts out = {row_cnt, row_sum, shift};
+  const unsigned count_grid = (unsigned)((rows + (4 << shift) - 1) / (4 << shift));
+  const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
+  auto digit = [&](auto dt, auto pass, auto behind) {
+    hipLaunchKernelGGL((sel_hist_kernel<decltype(dt), decltype(pass)::value, decltype(behind)::value>), dim3(grid), dim3(SEL_THREADS), 0, s, x,
+                       rows, cols, ld, ranks, st, hist, thresholds);
+  };
+  using First = std::integral_constant<int, 0>;
+  using Second = std::integral_constant<int, 1>;
+  using Third = std::integral_constant<int, 2>;
+  if (bf16 && ld == cols && cols % 8 == 0 && cols <= 65535 && n < ((int64_t)1 << 32) && rows * WIN_STRIDE <= 2 * rows_scratch_words) {
+    uint16_t* const bins = reinterpret_cast<uint16_t*>(rows_scratch);
+    const uint16_t* const xp = reinterpret_cast<const uint16_t*>(x);
+    auto window = [&](const Ranks& r, const unsigned long long* digits) {
+      hipLaunchKernelGGL(win_count_kernel, dim3((unsigned)std::min<int64_t>((rows + 15) / 16, 512)), dim3(1024), 0, s, xp, rows, cols, r, digits,
+                         st, hist, bins);
+    };
+    auto counts = [&](auto exact) {
+      hipLaunchKernelGGL((win_rows_kernel<decltype(exact)::value>), dim3(count_grid), dim3(256), 0, s, xp, rows, cols, ranks, st, hist, bins,
+                         thresholds, out);
+    };
+    if (n >= ((int64_t)1 << 25)) {
+      const int64_t ns = (int64_t)SAMPLE_RUNS * 64 * 8;
+      const unsigned long long ks = (unsigned long long)((double)k / (double)n * (double)ns);
+      hipLaunchKernelGGL(sel_sample_kernel, dim3(SAMPLE_BLOCKS), dim3(SEL_THREADS), 0, s, reinterpret_cast<const u32x4*>(x), n / 8, hist);
+      window({{ks, (unsigned long long)ns - 1 - ks}}, hist + SAMPLE_AT);   // the sample's ranks
+      digit(BF16{}, First{}, std::true_type{});
+      digit(BF16{}, Second{}, std::true_type{});
+      counts(std::false_type{});
+    } else {
+      digit(BF16{}, First{}, std::false_type{});
+      window(ranks, hist + SEL_AT[0]);
+      counts(std::true_type{});
+    }
+  } else if (bf16) {
+    digit(BF16{}, First{}, std::false_type{});
+    digit(BF16{}, Second{}, std::false_type{});
+    hipLaunchKernelGGL((sel_count_kernel<BF16>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+  } else {
+    digit(F32{}, First{}, std::false_type{});
+    digit(F32{}, Second{}, std::false_type{});
+    digit(F32{}, Third{}, std::false_type{});
+    hipLaunchKernelGGL((sel_count_kernel<F32>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+  }
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
 
 int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s) {
-  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, s, row_cnt, rows, row_ptr, nnz);
+  if (rows > 0 && rows <= SCAN_WIDE && aligned16(row_cnt))
+    hipLaunchKernelGGL(scan_counts_wide_kernel, dim3((unsigned)((rows + 1023) / 1024)), dim3(1024), 0, s, row_cnt, rows, row_ptr, nnz);
+  else
+    hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, s, row_cnt, rows, row_ptr, nnz);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }

@@ -175,6 +175,11 @@ struct RowArgs {
   int32_t* tmp_col;      // OCC: where the entries go (final arrays when the kernel emits them in order)
   float* tmp_val;
   const int64_t* row_ptr;  // OCC: [rows + 1] first entry slot of every row (counted beforehand)
+  // or, with row_sum, the row's entries in row_cnt and those of every 4 << sum_shift rows in row_sum, at most SUM_BLOCKS of these:
+  // the kernel adds up what comes before a row and leaves the first entry slots in ptr_out, their number in nnz_out
+  const int32_t* row_sum;
+  int sum_shift;
+  int64_t *ptr_out, *nnz_out;
   int64_t rows, cols, ld, capacity;
   // per-token thresholds (TOKEN variants): found inside the kernel, row by row
   float* thr_out;          // [rows][2] {lo, hi} of every row
@@ -184,6 +189,8 @@ struct RowArgs {
   // tensor-wise scaling (granularity ablation, Sec. 4.3): one scale, computed beforehand, for every row
   const float* gamma_in;   // null: each row's own absmax scale
 };
+
+constexpr int SUM_BLOCKS = 2048;   // two 16-byte loads a thread
 
 // ------------------------------------------------------------------------------------------
 // Per-token order statistics (Sec. 3.2 with the quantile taken over each token's channels):
@@ -354,7 +361,8 @@ FP4_D void select_row_thresholds(Raw8<DT> (&cache)[NV], bool row_ok, int t, int6
 // and the row's entry count to row_cnt (the caller compacts).
 // FULL: cols is a multiple of 8 (every unit is whole or absent), which spares the clamp its
 // per-element bounds tests -- with them the kernel is bound by vector instructions, not by memory.
-template <class DT, bool OCC, int TPR, int NV, bool TOKEN = false, bool FULL = false>
+// SUMS: the places of the entries come from row_cnt and row_sum instead of row_ptr.
+template <class DT, bool OCC, int TPR, int NV, bool TOKEN = false, bool FULL = false, bool SUMS = false>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
   constexpr int RPB = 256 / TPR;
   constexpr bool CACHED = NV > 0;
@@ -387,6 +395,23 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
     if constexpr (FULL) return 8;
     else return (int)min((int64_t)8, a.cols - unit * 8);
   };
+
+  static_assert(!SUMS || (OCC && CACHED && !TOKEN), "sums of entries counted beforehand");
+  __shared__ uint32_t s_before[4];
+  // requested before the row; two loads a thread in place of a launch (3.5 to 5 us) that scans the counts
+  u32x4 sums[2] = {};
+  int32_t sums_rest = 0, row_n[RPB] = {};
+  const int64_t wg_row = (int64_t)blockIdx.x * RPB;
+  if constexpr (SUMS) {
+    const int64_t blocks = wg_row >> (2 + a.sum_shift), first = blocks << (2 + a.sum_shift);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)   // the array is whole 16-byte words
+      if (q * 1024 + tid * 4 < blocks) sums[q] = *reinterpret_cast<const u32x4*>(a.row_sum + q * 1024 + tid * 4);
+    if (first + tid < wg_row) sums_rest = a.row_cnt[first + tid];
+#pragma unroll
+    for (int j = 0; j < RPB; ++j)
+      if (wg_row + j < a.rows) row_n[j] = a.row_cnt[wg_row + j];
+  }
 
   Raw8<DT> cache[CACHED ? NV : 1];
   float amax = 0.0f;
@@ -510,6 +535,29 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
     if constexpr (TOKEN) {
       base = row * a.stride_e;
       emit = row_ok;
+    } else if constexpr (SUMS) {
+      const int64_t blocks = wg_row >> (2 + a.sum_shift);
+      uint32_t before = (uint32_t)sums_rest;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (q * 1024 + tid * 4 + j < blocks) before += sums[q][j];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) before += (uint32_t)__shfl_xor((int)before, o, 64);
+      if (lane == 0) s_before[wave] = before;
+      __syncthreads();
+      base = (long long)s_before[0] + s_before[1] + s_before[2] + s_before[3];
+      int32_t mine = row_n[0];
+#pragma unroll
+      for (int j = 1; j < RPB; ++j)
+        if (wg_row + j <= row) { base += row_n[j - 1]; mine = row_n[j]; }
+      if (row_ok && t == 0) {
+        a.ptr_out[row + 1] = base + mine;
+        if (row == 0) a.ptr_out[0] = 0;
+        if (row == a.rows - 1) *a.nnz_out = base + mine;
+      }
+      emit = row_ok && base + mine <= a.capacity;
     } else {
       base = row_ok ? a.row_ptr[row] : 0;
       emit = row_ok && (a.row_ptr[row + 1] <= a.capacity);
@@ -649,28 +697,6 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
   }
 }
 
-// Entries each row will contribute to the residual: elements outside [lo, hi].  One wave per row.
-template <class DT>
-__global__ __launch_bounds__(256) void occ_count_rows_kernel(const void* x, int64_t rows, int64_t cols, int64_t ld,
-                                                             const float* thr, int32_t* row_cnt) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const float lo = thr[0], hi = thr[1];
-  const int64_t nunits = (cols + 7) / 8;
-  int cnt = 0;
-  for (int64_t u = lane; u < nunits; u += 64) {
-    const int valid = (int)min((int64_t)8, cols - u * 8);
-    float v[8];
-    load8<DT>(x, row * ld + u * 8, valid, v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) cnt += (e < valid && ((v[e] < lo) | (v[e] > hi))) ? 1 : 0;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (lane == 0) row_cnt[row] = cnt;
-}
-
 template <class DT, bool OCC>
 int launch_rows(const RowArgs& a, hipStream_t s) {
   const int64_t nunits = (a.cols + 7) / 8;
@@ -680,7 +706,8 @@ int launch_rows(const RowArgs& a, hipStream_t s) {
     constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
     if constexpr (OCC && NV > 0) {
       if ((a.cols % 8) == 0) {
-        hipLaunchKernelGGL((quantize_rows_kernel<DT, true, TPR, NV, false, true>), grid, b, 0, s, a);
+        if (a.row_sum) hipLaunchKernelGGL((quantize_rows_kernel<DT, true, TPR, NV, false, true, true>), grid, b, 0, s, a);
+        else hipLaunchKernelGGL((quantize_rows_kernel<DT, true, TPR, NV, false, true>), grid, b, 0, s, a);
         return;
       }
     }
@@ -756,6 +783,8 @@ struct ColArgs {
   int64_t thr_stride;    // 0: one {lo, hi} pair for the tensor; 2: one pair per row, thr[2 r], thr[2 r + 1]
   int64_t rows, cols, ld;
   int row_block;         // rows per workgroup in the absmax pass
+  unsigned long long* clear;   // words that the absmax pass sets to 0 for a launch behind it; null: none
+  int64_t clear_words;
 };
 
 // Rows per workgroup in the absmax pass: 128, fewer (32 at least) while that leaves fewer than 512 workgroups and a column at
@@ -832,6 +861,10 @@ FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, float (&s_m)[4][64
 template <class DT, bool CLAMP>
 __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a, ColArgs b, unsigned strips_a) {
   __shared__ float s_m[4][64][8];
+  if (a.clear)
+    for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < a.clear_words;
+         i += (int64_t)gridDim.x * gridDim.y * 256)
+      a.clear[i] = 0;
   if (blockIdx.x < strips_a) col_absmax_strip<DT, CLAMP>(a, blockIdx.x, s_m);
   else col_absmax_strip<DT, false>(b, blockIdx.x - strips_a, s_m);
 }
@@ -1425,32 +1458,44 @@ int fp4_launch_quantize_rows_fixed(const void* x, int bf16, int64_t rows, int64_
   return bf16 ? launch_rows<BF16, false>(a, s) : launch_rows<F32, false>(a, s);
 }
 
-int fp4_launch_occ_count(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, const float* thr,
-                         int32_t* row_cnt, hipStream_t s) {
-  if (rows == 0) return FP4_OK;
-  const dim3 grid((unsigned)((rows + 3) / 4));
-  if (bf16) hipLaunchKernelGGL((occ_count_rows_kernel<BF16>), grid, dim3(256), 0, s, x, rows, cols, ld, thr, row_cnt);
-  else hipLaunchKernelGGL((occ_count_rows_kernel<F32>), grid, dim3(256), 0, s, x, rows, cols, ld, thr, row_cnt);
-  FP4_CHECK_LAUNCH();
-  return FP4_OK;
+// The rows' entry counts in blocks of 4 << shift, so that there are at most SUM_BLOCKS of them, up to 65536 rows
+// (a wave of the count has 1 << shift rows one after another).
+int fp4_row_sum_shift(int64_t rows) {
+  int shift = 0;
+  while (shift < 3 && rows > ((int64_t)SUM_BLOCKS << (2 + shift))) ++shift;
+  return shift;
 }
+// int32 words for the sums: whole 16-byte words
+int64_t fp4_row_sum_words(int64_t rows) { return (rows + 15) / 16 * 4; }   // for shift 0, the most of them
 
-// Rows short enough to stay in registers between the passes (up to 16384 elements) leave their
-// entries in ascending column order straight in (col_idx, val) and the call returns 0; longer
+// Clamp, codes, entries in ascending column order and their places, from the rows' counts (row_cnt, row_sum).  Rows short enough to stay
+// in registers between the passes (up to 16384 elements) leave their entries straight in (col_idx, val) and the call returns 0; longer
 // rows are streamed, their entries go unordered to (tmp_col, tmp_val) and the call returns 1:
 // the caller then orders them into (col_idx, val).  Negative: fp4_status.
+int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s);
 int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                         const float* thr, uint8_t* codes, float* gamma, void* x_clamped,
-                        int32_t* col_idx, float* val, int32_t* tmp_col, float* tmp_val,
-                        const int64_t* row_ptr, int64_t capacity, const float* gamma_in, hipStream_t s) {
+                        int32_t* col_idx, float* val, int32_t* tmp_col, float* tmp_val, int32_t* row_cnt, const int32_t* row_sum,
+                        int64_t* row_ptr, int64_t* nnz, int64_t capacity, const float* gamma_in, hipStream_t s) {
   if (rows == 0 || cols == 0) return FP4_OK;
   const bool ordered = (cols + 7) / 8 <= 256 * 8;   // the variants launch_rows picks with a register cache
   RowArgs a = {};
   a.x = x; a.codes = codes; a.gamma = gamma; a.x_clamped = x_clamped; a.thr = thr; a.gamma_in = gamma_in;
   a.tmp_col = ordered ? col_idx : tmp_col;
   a.tmp_val = ordered ? val : tmp_val;
-  a.row_ptr = row_ptr;
   a.rows = rows; a.cols = cols; a.ld = ld; a.capacity = capacity;
+  a.sum_shift = fp4_row_sum_shift(rows);
+  // A workgroup that has one row (more than 4096 columns) pays for the sums what one with four does, about 0.7 us a round of them:
+  // 16384 x 11008 156 -> 171 us against a scan of 5.1; 8192 x 2048 18.0 -> 21.6 and 4.9, 1056 x
+  // 1376 7.6 -> 8.5 and 3.5, 16384 x 4096 61.6 -> 62.9 and 5.1, each with a gap between launches.
+  const bool cheap = cols <= 4096 || rows <= 2048;
+  if (ordered && cheap && cols % 8 == 0 && rows <= ((int64_t)SUM_BLOCKS << (2 + a.sum_shift)) && rows * cols < ((int64_t)1 << 32)) {
+    a.row_cnt = row_cnt; a.row_sum = row_sum; a.ptr_out = row_ptr; a.nnz_out = nnz;
+  } else {
+    const int rc = fp4_launch_scan_rows(row_cnt, rows, row_ptr, nnz, s);
+    if (rc) return rc;
+    a.row_ptr = row_ptr;
+  }
   const int rc = bf16 ? launch_rows<BF16, true>(a, s) : launch_rows<F32, true>(a, s);
   return rc ? rc : (ordered ? 0 : 1);
 }
@@ -1519,9 +1564,10 @@ int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const 
 
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
-                             uint32_t* amax_scratch, hipStream_t s) {
+                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words) {
   if (rows == 0 || cols == 0) return FP4_OK;
   ColArgs a = {};
+  a.clear = reinterpret_cast<unsigned long long*>(clear); a.clear_words = clear_words;
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
   a.thr_stride = per_row_thr ? 2 : 0;
   a.rows = rows; a.cols = cols; a.ld = ld;
@@ -1607,7 +1653,7 @@ extern "C" int fp4_quantize(const void* x, fp4_dtype dt, int64_t rows, int64_t c
     return fp4_launch_quantize_rows_fixed(x, dt == FP4_BF16, rows, cols, ld, gamma, codes, nullptr, (hipStream_t)stream);
   }
   return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma,
-                                  reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream);
+                                  reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream, nullptr, 0);
 }
 
 // ---- the entry point that allocates nothing -----------------------------------------------------
@@ -1652,7 +1698,7 @@ extern "C" int fp4_quantize_noalloc(const void* x, fp4_dtype dt, int64_t rows, i
   if (rc) return rc;
   // every word the scale kernel reads is written by the maxima kernel of the same call first, so
   // what an earlier call left behind is never seen and nothing has to be cleared
-  return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma, sp, (hipStream_t)stream);
+  return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma, sp, (hipStream_t)stream, nullptr, 0);
 }
 
 extern "C" int fp4_dge_apply(const float* G, const void* W, fp4_dtype dt, const float* gamma_W,
