@@ -91,7 +91,9 @@ FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
   return slots <= SM_ROOM_SLOTS && (small_grid || slots <= SM_EVEN_SLOTS + SM_EVEN_SHARE * (float)rows[1] * a_cell);
 }
 
-// One workgroup per bundle of G groups (the groups of one wave, which step together).  sched[bundle][phase]:
+// One workgroup per bundle of G groups (the groups of one wave, which step together), or G of them (split), which all count and
+// plan for the whole bundle and write one group each: fewer bundles than a third of the chip left the rest of it idle while each
+// wrote some hundred KiB (4096 rows of 328 entries 53.5 -> 46.0 us, 2048 of 164 27.1 -> 22.4).  sched[bundle][phase]:
 // steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the tiled kernel (a
 // matrix that is not worth it, more slots than there is room for, columns that repeat inside a row, or values that three
 // bf16 terms do not make up); redo[bundle]: 0.
@@ -99,7 +101,7 @@ template <int G>
 __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int64_t* __restrict__ row_ptr,
                                                                const int32_t* __restrict__ col_idx,
                                                                const float* __restrict__ val, int64_t capacity, int64_t P,
-                                                               int Q, int cap, int phases, bool small_grid, uint8_t* __restrict__ a_buf,
+                                                               int Q, int cap, int phases, bool small_grid, bool split, uint8_t* __restrict__ a_buf,
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
                                                                int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list,
                                                                int32_t* count) {
@@ -117,7 +119,9 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
     find_long_rows<THREADS>(row_ptr, P, Q, capacity, list, count);
     return;
   }
-  const int64_t bundle = blockIdx.x - 1, bundles = gridDim.x - 1;
+  const int64_t bundles = split ? (gridDim.x - 1) / G : gridDim.x - 1;
+  const int64_t bundle = split ? (blockIdx.x - 1) / G : blockIdx.x - 1;
+  const int part = (int)(blockIdx.x - 1 - bundle * G);   // split: the group to write
   auto entries = [&](int64_t row, int64_t& b) -> int64_t {
     b = row_ptr[row];
     return max(min(row_ptr[row + 1], capacity), b) - b;
@@ -142,11 +146,12 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   if (tid == 0) s_bad = 0;
   if (tid < G) s_total[tid] = 0;
   __syncthreads();
-  const int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
-  const int grp = br / 16, r = br % 16;
-  const int n_mine = s_n[br];
-  const int32_t* const cp = col_idx + s_b[br];
-  const float* const vp = val + s_b[br];
+  int tpr = PK_TPR;
+  int br = tid / PK_TPR, rt = tid % PK_TPR;   // row of the bundle, thread of the row
+  int grp = br / 16, r = br % 16;
+  int n_mine = s_n[br];
+  const int32_t* cp = col_idx + s_b[br];
+  const float* vp = val + s_b[br];
   for (int i0 = rt; i0 < n_mine; i0 += 4 * PK_TPR) {   // four entries a thread in flight
     int c[4], before[4];
     float v[4];
@@ -249,25 +254,35 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   __syncthreads();
   const int T = s_steps;
   if (T == 0) return;
+  int gt = tid % (16 * PK_TPR);   // thread of the group
+  if (split) {   // all of them to the one group
+    tpr = THREADS / 16;
+    grp = part;
+    r = tid / (THREADS / 16);
+    rt = tid % (THREADS / 16);
+    gt = tid;
+    n_mine = s_n[grp * 16 + r];
+    cp = col_idx + s_b[grp * 16 + r];
+    vp = val + s_b[grp * 16 + r];
+  }
   uint8_t* const ag = a_buf + (bundle * G + grp) * (int64_t)(cap + 1) * 1024;
   uint8_t* const og = o_buf + (bundle * G + grp) * (int64_t)(cap + 1) * 64;
   const u32x4 z = {0u, 0u, 0u, 0u};
-  const int gt = tid % (16 * PK_TPR);   // thread of the group
-  for (int i = gt; i < T * 64; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(ag + (int64_t)i * 16) = z;
-  for (int i = gt; i < T * 4; i += 16 * PK_TPR) *reinterpret_cast<u32x4*>(og + (int64_t)i * 16) = z;
+  for (int i = gt; i < T * 64; i += 16 * tpr) *reinterpret_cast<u32x4*>(ag + (int64_t)i * 16) = z;
+  for (int i = gt; i < T * 4; i += 16 * tpr) *reinterpret_cast<u32x4*>(og + (int64_t)i * 16) = z;
   __syncthreads();   // the zeros are written (a workgroup's stores reach L2 in order) before the values
-  for (int i0 = rt; i0 < n_mine; i0 += 4 * PK_TPR) {
+  for (int i0 = rt; i0 < n_mine; i0 += 4 * tpr) {
     int cc[4];
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = min(i0 + u * PK_TPR, n_mine - 1);
+      const int i = min(i0 + u * tpr, n_mine - 1);
       cc[u] = cp[i];
       v[u] = vp[i];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (i0 + u * PK_TPR >= n_mine) continue;
+      if (i0 + u * tpr >= n_mine) continue;
       const int c = cc[u];
       uint32_t t[3];
       const int nt = bf16_terms(v[u], t);
@@ -467,6 +482,8 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
 
 }  // namespace
 
+int fp4_compute_units_of_current_device();
+
 // bytes of scratch the packed form of a P x Q matrix takes, and that of any smaller one: a matrix too wide for this path
 // counts as the widest that is not
 int64_t fp4_spmm_mfma_scratch_bytes(int64_t P, int64_t Q) {
@@ -494,8 +511,9 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     int32_t* const steps = sched + bundles * phases;
     int32_t* const redo = steps + bundles + SM_STEPS_PAD;
     const size_t lds = (size_t)G * phases * (SM_KC / 8) * 6 + (size_t)G * phases * 4;
-    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)bundles + 1), dim3(16 * G * pk_tpr(G)), lds, s, row_ptr, col_idx, val,
-                       capacity, P, (int)Q, cap, phases, small_grid, a_buf, o_buf, sched, steps, redo, list, count);
+    const bool split = G > 1 && bundles * G <= 2 * fp4_compute_units_of_current_device();
+    hipLaunchKernelGGL((spmm_pack_kernel<G>), dim3((unsigned)(bundles * (split ? G : 1)) + 1), dim3(16 * G * pk_tpr(G)), lds, s, row_ptr, col_idx,
+                       val, capacity, P, (int)Q, cap, phases, small_grid, split, a_buf, o_buf, sched, steps, redo, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
     hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
