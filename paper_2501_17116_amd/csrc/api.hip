@@ -36,8 +36,10 @@ int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t col
                               float* thr_out, uint8_t* codes, float* gamma, void* x_clamped, int32_t* tmp_col,
                               float* tmp_val, int32_t* row_cnt, hipStream_t s);
 int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols);
-int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
-                                    float* gamma, uint16_t* part, hipStream_t s);
+int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes, float* gamma,
+                                    uint16_t* part, const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, hipStream_t s);
+int fp4_launch_quantize_rows_pair(const void* x, const void* y, int bf16, int64_t rows, int64_t rows_y, int64_t cols, uint8_t* codes,
+                                  float* gamma, uint8_t* codes_y, float* gamma_y, hipStream_t s);
 int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
                                   uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, hipStream_t s);
@@ -447,17 +449,12 @@ int dgrad_impl(const void* dY, const void* W, const fp4_weight_cache* wq, fp4_dt
   const int bf16 = dt == FP4_BF16;
   Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
   DgradWs w = carve_dgrad(c, M, K, N);
-  int rc = fp4_launch_quantize_rows(dY, bf16, M, N, N, w.qdY, w.gdY, s);   // per token
+  // dY per token, W per input channel
+  const int rc = wq ? fp4_launch_quantize_rows(dY, bf16, M, N, N, w.qdY, w.gdY, s)
+                    : fp4_launch_quantize_rows_pair(dY, W, bf16, M, K, N, w.qdY, w.gdY, w.qW, w.gWk, s);
   if (rc) return rc;
-  const uint8_t* qW = w.qW;
-  const float* gWk = w.gWk;
-  if (wq) {
-    qW = wq->qWk;
-    gWk = wq->gamma_Wk;
-  } else {
-    rc = fp4_launch_quantize_rows(W, bf16, K, N, N, w.qW, w.gWk, s);       // per input channel
-    if (rc) return rc;
-  }
+  const uint8_t* const qW = wq ? wq->qWk : w.qW;
+  const float* const gWk = wq ? wq->gamma_Wk : w.gWk;
   return fp4_launch_gemm(w.qdY, w.gdY, qW, gWk, M, K, N, nullptr, dA, bf16, K, nullptr, 0, 0, nullptr, 0.0f, 0.0f, s);
 }
 }  // namespace
@@ -635,19 +632,16 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   DgradWs d = carve_dgrad(c, M, K, N);
   WgradWs w = carve_wgrad(c, M, K, N, dt);
   uint16_t* part = c.take<uint16_t>((size_t)fp4_dual_axis_part_elems(M, N));
-  // dY: per token (codes for the activation gradient) and, in the same read, per-block column maxima
-  int rc = fp4_launch_quantize_rows_colmax(dY, bf16, M, N, N, d.qdY, d.gdY, part, s);
+  // dY: per token (codes for the activation gradient) and, in the same read, per-block column maxima; W per input channel beside it
+  int rc = fp4_launch_quantize_rows_colmax(dY, bf16, M, N, N, d.qdY, d.gdY, part, wq ? nullptr : W, K, d.qW, d.gWk, s);
   const bool dual = rc == 0;
-  if (rc == 1) rc = fp4_launch_quantize_rows(dY, bf16, M, N, N, d.qdY, d.gdY, s);
+  if (rc == 1)
+    rc = wq ? fp4_launch_quantize_rows(dY, bf16, M, N, N, d.qdY, d.gdY, s)
+            : fp4_launch_quantize_rows_pair(dY, W, bf16, M, K, N, d.qdY, d.gdY, d.qW, d.gWk, s);
   if (rc) return rc;
   // activation gradient
-  const uint8_t* qW = d.qW;
-  const float* gWk = d.gWk;
-  if (wq) { qW = wq->qWk; gWk = wq->gamma_Wk; }
-  else {
-    rc = fp4_launch_quantize_rows(W, bf16, K, N, N, d.qW, d.gWk, s);
-    if (rc) return rc;
-  }
+  const uint8_t* const qW = wq ? wq->qWk : d.qW;
+  const float* const gWk = wq ? wq->gamma_Wk : d.gWk;
   rc = fp4_launch_gemm(d.qdY, d.gdY, qW, gWk, M, K, N, nullptr, dA, bf16, K, nullptr, 0, 0, nullptr, 0.0f, 0.0f, s);
   if (rc) return rc;
   // weight gradient

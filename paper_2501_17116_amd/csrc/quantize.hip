@@ -188,6 +188,11 @@ struct RowArgs {
   int64_t stride_e;        // entry slots reserved per row (2 tail_k)
   // tensor-wise scaling (granularity ablation, Sec. 4.3): one scale, computed beforehand, for every row
   const float* gamma_in;   // null: each row's own absmax scale
+  // a second tensor with as many columns, whose rows follow (without the clamp only)
+  const void* x2;
+  uint8_t* codes2;
+  float* gamma2;
+  int64_t rows2;
 };
 
 constexpr int SUM_BLOCKS = 2048;   // two 16-byte loads a thread
@@ -378,8 +383,15 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
   const int t = tid % TPR;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int64_t row = (int64_t)blockIdx.x * RPB + tid / TPR;
-  const bool row_ok = row < a.rows;
+  int64_t row = (int64_t)blockIdx.x * RPB + tid / TPR;
+  bool row_ok = row < a.rows;
+  if constexpr (!OCC) {
+    if (!row_ok && row < a.rows + a.rows2) {   // the same for all threads of a row
+      row -= a.rows;
+      row_ok = true;
+      a.x = a.x2; a.codes = a.codes2; a.gamma = a.gamma2;
+    }
+  }
   const int64_t nunits = (a.cols + 7) / 8;
   const int nloop = CACHED ? NV : (int)((nunits + TPR - 1) / TPR);
   const int64_t xoff = row * a.ld;
@@ -700,7 +712,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
 template <class DT, bool OCC>
 int launch_rows(const RowArgs& a, hipStream_t s) {
   const int64_t nunits = (a.cols + 7) / 8;
-  const dim3 g4((unsigned)((a.rows + 3) / 4)), g1((unsigned)a.rows), b(256);
+  const int64_t rows = a.rows + a.rows2;
+  const dim3 g4((unsigned)((rows + 3) / 4)), g1((unsigned)rows), b(256);
   // the fused clamp has a variant for rows made of whole units
   auto go = [&](auto tpr, auto nv, dim3 grid) {
     constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
@@ -1082,14 +1095,26 @@ inline int da_rows(int64_t rows, int64_t cols) {
   while (per > 4 && rows < (int64_t)per * (cols > 8192 ? 512 : 1024)) per /= 2;
   return per;
 }
+// A second tensor with as many columns (y; the weights, whose codes the activation gradient needs) goes through the same launch by
+// rows only: the workgroups from `blocks` on have per_y rows of it each.  Apart / together in us: 1056 x 2080 and 1376 rows more 7.8 + 6.8 /
+// 9.9, 8192 x 2048 and 2048 14.9 + 5.5 / 15.0, 4096 x 11008 and 4096 34.7 + 34.1 / 57.7, 4096 x 13824 and 5120 40.9 + 46.1 / 75.5.
 template <int NV>
 __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                    int64_t cols, int64_t ld, uint8_t* __restrict__ codes,
-                                                                   float* __restrict__ gamma, uint16_t* __restrict__ part, int per) {
+                                                                   float* __restrict__ gamma, uint16_t* __restrict__ part, int per, unsigned blocks,
+                                                                   const uint16_t* __restrict__ y, int64_t rows_y, uint8_t* __restrict__ codes_y,
+                                                                   float* __restrict__ gamma_y, int per_y) {
   __shared__ float s_max[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t nunits = cols / 8;                 // cols % 8 == 0 (checked by the launcher)
-  const int64_t r0 = (int64_t)blockIdx.x * per;
+  const bool second = blockIdx.x >= blocks;
+  if (second) {
+    x = y; codes = codes_y; gamma = gamma_y;
+    rows = rows_y;
+    ld = cols;
+    per = per_y;
+  }
+  const int64_t r0 = (int64_t)(second ? blockIdx.x - blocks : blockIdx.x) * per;
   const int nrows = (int)min((int64_t)per, rows - r0);
   u32x4 cm[NV];
 #pragma unroll
@@ -1137,6 +1162,7 @@ __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_
     fetch(r + 2, buf[0]);
     process(r + 1, buf[1]);
   }
+  if (second) return;
   uint16_t* prow = part + (int64_t)blockIdx.x * cols;
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
@@ -1509,19 +1535,35 @@ int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) {
   return std::max({(rows + 31) / 32 * in, std::min<int64_t>(most, 2048) * std::min<int64_t>(in, 8192), std::min<int64_t>(most, 1024) * in});
 }
 
+// y (null: none): a second tensor [rows_y x cols], quantized by rows only.
 int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
-                                    float* gamma, uint16_t* part, hipStream_t s) {
+                                    float* gamma, uint16_t* part, const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y,
+                                    hipStream_t s) {
   if (!bf16 || (cols % 8) != 0 || cols > 256 * 8 * 8 || rows == 0 || cols == 0) return 1;
   const int64_t nunits = cols / 8;
-  const int per = da_rows(rows, cols);
-  const dim3 grid((unsigned)((rows + per - 1) / per)), block(256);
-  const uint16_t* xp = reinterpret_cast<const uint16_t*>(x);
-  if (nunits <= 256 * 2) hipLaunchKernelGGL((quantize_rows_colmax_kernel<2>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
-  else if (nunits <= 256 * 4) hipLaunchKernelGGL((quantize_rows_colmax_kernel<4>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
-  else if (nunits <= 256 * 6) hipLaunchKernelGGL((quantize_rows_colmax_kernel<6>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
-  else hipLaunchKernelGGL((quantize_rows_colmax_kernel<8>), grid, block, 0, s, xp, rows, cols, ld, codes, gamma, part, per);
+  const int per = da_rows(rows, cols), per_y = 4;   // nothing is folded over y's rows, so few are as good
+  const unsigned blocks = (unsigned)((rows + per - 1) / per), blocks_y = y ? (unsigned)((rows_y + per_y - 1) / per_y) : 0;
+  auto go = [&](auto nv) {
+    hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value>), dim3(blocks + blocks_y), dim3(256), 0, s,
+                       reinterpret_cast<const uint16_t*>(x), rows, cols, ld, codes, gamma, part, per, blocks,
+                       reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y);
+  };
+  if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{});
+  else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{});
+  else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{});
+  else go(std::integral_constant<int, 8>{});
   FP4_CHECK_LAUNCH();
   return FP4_OK;
+}
+
+// Two tensors with as many columns by rows, in one launch.
+int fp4_launch_quantize_rows_pair(const void* x, const void* y, int bf16, int64_t rows, int64_t rows_y, int64_t cols, uint8_t* codes,
+                                  float* gamma, uint8_t* codes_y, float* gamma_y, hipStream_t s) {
+  if (rows == 0 || rows_y == 0 || cols == 0) return FP4_ERR_SHAPE;
+  RowArgs a = {};
+  a.x = x; a.codes = codes; a.gamma = gamma; a.rows = rows; a.cols = cols; a.ld = cols;
+  a.x2 = y; a.codes2 = codes_y; a.gamma2 = gamma_y; a.rows2 = rows_y;
+  return bf16 ? launch_rows<BF16, false>(a, s) : launch_rows<F32, false>(a, s);
 }
 
 // The transposing column pass alone, with the scales already in gamma[cols] (tensor-wise scaling: all equal).
