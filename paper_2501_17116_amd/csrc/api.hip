@@ -36,13 +36,14 @@ int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t col
                               float* thr_out, uint8_t* codes, float* gamma, void* x_clamped, int32_t* tmp_col,
                               float* tmp_val, int32_t* row_cnt, hipStream_t s);
 int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols);
-int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes, float* gamma,
-                                    uint16_t* part, const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, hipStream_t s);
+int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64_t cols, uint8_t* codes, float* gamma, uint16_t* part16,
+                                    const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, const void* z, int64_t cols_z,
+                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, hipStream_t s);
 int fp4_launch_quantize_rows_pair(const void* x, const void* y, int bf16, int64_t rows, int64_t rows_y, int64_t cols, uint8_t* codes,
                                   float* gamma, uint8_t* codes_y, float* gamma_y, hipStream_t s);
 int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
-                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, hipStream_t s);
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, hipStream_t s);
 int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const int32_t* row_cnt, int64_t stride,
                             const int64_t* row_ptr, int64_t rows, int64_t capacity, int32_t* col_idx, float* val,
                             hipStream_t s);
@@ -599,7 +600,7 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
                                   w.t_ptr, w.t_idx, w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
   // A_c per input channel (codes [K x M/2]); dY per output channel (codes [N x M/2])
   if (!rc) rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, dY, N, nullptr, w.qdYt,
-                                              w.gdYn, w.amax, s);
+                                              w.gdYn, w.amax, false, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
@@ -632,12 +633,12 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   DgradWs d = carve_dgrad(c, M, K, N);
   WgradWs w = carve_wgrad(c, M, K, N, dt);
   uint16_t* part = c.take<uint16_t>((size_t)fp4_dual_axis_part_elems(M, N));
-  // dY: per token (codes for the activation gradient) and, in the same read, per-block column maxima; W per input channel beside it
-  int rc = fp4_launch_quantize_rows_colmax(dY, bf16, M, N, N, d.qdY, d.gdY, part, wq ? nullptr : W, K, d.qW, d.gWk, s);
-  const bool dual = rc == 0;
-  if (rc == 1)
-    rc = wq ? fp4_launch_quantize_rows(dY, bf16, M, N, N, d.qdY, d.gdY, s)
-            : fp4_launch_quantize_rows_pair(dY, W, bf16, M, K, N, d.qdY, d.gdY, d.qW, d.gWk, s);
+  // dY: per token (codes for the activation gradient) and, in the same read, per-block column maxima; W per input channel and A's column
+  // maxima (for the weight gradient) beside it
+  bool dual, known;
+  const float* const thr = occ ? saved->thresholds : nullptr;
+  int rc = fp4_launch_quantize_rows_absmax(dY, bf16, M, N, d.qdY, d.gdY, part, wq ? nullptr : W, K, d.qW, d.gWk, A, K, thr, token, w.amax,
+                                           &dual, &known, s);
   if (rc) return rc;
   // activation gradient
   const uint8_t* const qW = wq ? wq->qWk : d.qW;
@@ -651,8 +652,7 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
                                   w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
     if (rc) return rc;
   }
-  rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, dY, N, dual ? part : nullptr,
-                                     w.qdYt, w.gdYn, w.amax, s);
+  rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, thr, token, w.qAt, w.gAk, dY, N, dual ? part : nullptr, w.qdYt, w.gdYn, w.amax, known, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {

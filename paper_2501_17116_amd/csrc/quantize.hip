@@ -368,7 +368,7 @@ FP4_D void select_row_thresholds(Raw8<DT> (&cache)[NV], bool row_ok, int t, int6
 // per-element bounds tests -- with them the kernel is bound by vector instructions, not by memory.
 // SUMS: the places of the entries come from row_cnt and row_sum instead of row_ptr.
 template <class DT, bool OCC, int TPR, int NV, bool TOKEN = false, bool FULL = false, bool SUMS = false>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
+FP4_D void quantize_rows_block(RowArgs a) {
   constexpr int RPB = 256 / TPR;
   constexpr bool CACHED = NV > 0;
   static_assert(!TOKEN || (OCC && CACHED), "per-token thresholds need the row in registers");
@@ -709,14 +709,32 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
   }
 }
 
+template <class DT, bool OCC, int TPR, int NV, bool TOKEN = false, bool FULL = false, bool SUMS = false>
+__global__ __launch_bounds__(256) void quantize_rows_kernel(RowArgs a) {
+  quantize_rows_block<DT, OCC, TPR, NV, TOKEN, FULL, SUMS>(a);
+}
+
+// Threads a row and units of it a thread keeps: one wave per row while the row fits 64 lanes x 8 units, else the whole workgroup (0: none
+// kept, the row is streamed).
+template <class F>
+void rows_shape(int64_t cols, F&& go) {
+  using std::integral_constant;
+  const int64_t nunits = (cols + 7) / 8;
+  if (nunits <= 64 * 2) go(integral_constant<int, 64>{}, integral_constant<int, 2>{});
+  else if (nunits <= 64 * 4) go(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+  else if (nunits <= 64 * 8) go(integral_constant<int, 64>{}, integral_constant<int, 8>{});
+  else if (nunits <= 256 * 4) go(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+  else if (nunits <= 256 * 6) go(integral_constant<int, 256>{}, integral_constant<int, 6>{});
+  else if (nunits <= 256 * 8) go(integral_constant<int, 256>{}, integral_constant<int, 8>{});
+  else go(integral_constant<int, 256>{}, integral_constant<int, 0>{});
+}
+
 template <class DT, bool OCC>
 int launch_rows(const RowArgs& a, hipStream_t s) {
-  const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t rows = a.rows + a.rows2;
-  const dim3 g4((unsigned)((rows + 3) / 4)), g1((unsigned)rows), b(256);
   // the fused clamp has a variant for rows made of whole units
-  auto go = [&](auto tpr, auto nv, dim3 grid) {
+  rows_shape(a.cols, [&](auto tpr, auto nv) {
     constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
+    const dim3 grid((unsigned)((a.rows + a.rows2 + 256 / TPR - 1) / (256 / TPR))), b(256);
     if constexpr (OCC && NV > 0) {
       if ((a.cols % 8) == 0) {
         if (a.row_sum) hipLaunchKernelGGL((quantize_rows_kernel<DT, true, TPR, NV, false, true, true>), grid, b, 0, s, a);
@@ -725,16 +743,7 @@ int launch_rows(const RowArgs& a, hipStream_t s) {
       }
     }
     hipLaunchKernelGGL((quantize_rows_kernel<DT, OCC, TPR, NV>), grid, b, 0, s, a);
-  };
-  using std::integral_constant;
-  // one wave per row while the row fits 64 lanes x 8 units, else the whole workgroup
-  if (nunits <= 64 * 2) go(integral_constant<int, 64>{}, integral_constant<int, 2>{}, g4);
-  else if (nunits <= 64 * 4) go(integral_constant<int, 64>{}, integral_constant<int, 4>{}, g4);
-  else if (nunits <= 64 * 8) go(integral_constant<int, 64>{}, integral_constant<int, 8>{}, g4);
-  else if (nunits <= 256 * 4) go(integral_constant<int, 256>{}, integral_constant<int, 4>{}, g1);
-  else if (nunits <= 256 * 6) go(integral_constant<int, 256>{}, integral_constant<int, 6>{}, g1);
-  else if (nunits <= 256 * 8) go(integral_constant<int, 256>{}, integral_constant<int, 8>{}, g1);
-  else go(integral_constant<int, 256>{}, integral_constant<int, 0>{}, g1);
+  });
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
@@ -810,11 +819,11 @@ inline int ca_rows(int64_t rows, int64_t cols) {
 }
 
 template <class DT, bool CLAMP>
-FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, float (&s_m)[4][64][8]) {
+FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, unsigned row_block, float (&s_m)[4][64][8]) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t unit = (int64_t)strip * 64 + lane;   // 8 columns
   const int64_t nunits = (a.cols + 7) / 8;
-  const int64_t r0 = (int64_t)blockIdx.y * a.row_block;
+  const int64_t r0 = (int64_t)row_block * a.row_block;
   const int64_t r1 = min(r0 + a.row_block, a.rows);
   float lo = 0, hi = 0;
   if (CLAMP) { lo = a.thr[0]; hi = a.thr[1]; }
@@ -861,7 +870,7 @@ FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, float (&s_m)[4][64
   // one row of partial maxima per row block (plain stores; a small fold follows): hundreds of
   // workgroups maxing the same words with device-wide atomics cost 10-18 us per tensor
   if (wave == 0 && valid > 0) {
-    uint32_t* const prow = a.amax_bits + (int64_t)blockIdx.y * a.amax_ld;
+    uint32_t* const prow = a.amax_bits + (int64_t)row_block * a.amax_ld;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float mm = fmaxf(fmaxf(s_m[0][lane][e], s_m[1][lane][e]), fmaxf(s_m[2][lane][e], s_m[3][lane][e]));
@@ -878,8 +887,21 @@ __global__ __launch_bounds__(256) void col_absmax_kernel(ColArgs a, ColArgs b, u
     for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < a.clear_words;
          i += (int64_t)gridDim.x * gridDim.y * 256)
       a.clear[i] = 0;
-  if (blockIdx.x < strips_a) col_absmax_strip<DT, CLAMP>(a, blockIdx.x, s_m);
-  else col_absmax_strip<DT, false>(b, blockIdx.x - strips_a, s_m);
+  if (blockIdx.x < strips_a) col_absmax_strip<DT, CLAMP>(a, blockIdx.x, blockIdx.y, s_m);
+  else col_absmax_strip<DT, false>(b, blockIdx.x - strips_a, blockIdx.y, s_m);
+}
+
+// Workgroup i of those that do the absmax pass of two tensors (col_absmax_kernel) inside another launch.
+struct AbsmaxTail {
+  ColArgs a, b;
+  unsigned strips_a, strips;   // of a, of both
+};
+template <class DT, bool CLAMP>
+FP4_D void absmax_tail(const AbsmaxTail& t, unsigned i) {
+  __shared__ float s_m[4][64][8];
+  const unsigned strip = i % t.strips, row_block = i / t.strips;
+  if (strip < t.strips_a) col_absmax_strip<DT, CLAMP>(t.a, strip, row_block, s_m);
+  else col_absmax_strip<DT, false>(t.b, strip - t.strips_a, row_block, s_m);
 }
 
 // gamma[c] from the g partial rows of column maxima (bit patterns of non-negative floats order
@@ -1098,12 +1120,18 @@ inline int da_rows(int64_t rows, int64_t cols) {
 // A second tensor with as many columns (y; the weights, whose codes the activation gradient needs) goes through the same launch by
 // rows only: the workgroups from `blocks` on have per_y rows of it each.  Apart / together in us: 1056 x 2080 and 1376 rows more 7.8 + 6.8 /
 // 9.9, 8192 x 2048 and 2048 14.9 + 5.5 / 15.0, 4096 x 11008 and 4096 34.7 + 34.1 / 57.7, 4096 x 13824 and 5120 40.9 + 46.1 / 75.5.
-template <int NV>
+// The workgroups from `blocks_rows` on do the absmax pass of a tensor that is quantized by columns later (the weight gradient's A).
+template <int NV, bool CLAMP>
 __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                    int64_t cols, int64_t ld, uint8_t* __restrict__ codes,
                                                                    float* __restrict__ gamma, uint16_t* __restrict__ part, int per, unsigned blocks,
                                                                    const uint16_t* __restrict__ y, int64_t rows_y, uint8_t* __restrict__ codes_y,
-                                                                   float* __restrict__ gamma_y, int per_y) {
+                                                                   float* __restrict__ gamma_y, int per_y, unsigned blocks_rows,
+                                                                   AbsmaxTail tail) {
+  if (blockIdx.x >= blocks_rows) {
+    absmax_tail<BF16, CLAMP>(tail, blockIdx.x - blocks_rows);
+    return;
+  }
   __shared__ float s_max[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t nunits = cols / 8;                 // cols % 8 == 0 (checked by the launcher)
@@ -1211,24 +1239,49 @@ void launch_amax16_to_gamma(ColArgs& a, hipStream_t s) {
   a.parts = 0;
 }
 
-// b.x null: a alone.  b.part16 set: b's maxima are known (b.parts rows of them).
-template <class DT, bool CLAMP>
-int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, hipStream_t s) {
-  const bool b_max = b.x && !b.part16;
-  const int64_t width = a.cols + (b_max ? b.cols : 0);
+// Sizes and scratch of the absmax pass of a and, unless its maxima come as part16, b; returns the row blocks.
+unsigned absmax_layout(ColArgs& a, ColArgs& b, uint32_t* amax) {
+  const int64_t width = a.cols + (b.x && !b.part16 ? b.cols : 0);
   a.row_block = b.row_block = ca_rows(a.rows, width);
   a.amax_bits = amax;
   b.amax_bits = amax + a.cols;
   a.amax_ld = b.amax_ld = width;
-  const int rblocks = (int)((a.rows + a.row_block - 1) / a.row_block);
-  hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3(ca_strips(a.cols) + (b_max ? ca_strips(b.cols) : 0), (unsigned)rblocks), dim3(256),
-                     0, s, a, b, ca_strips(a.cols));
+  return (unsigned)((a.rows + a.row_block - 1) / a.row_block);
+}
+
+// b.x null: a alone.  b.part16 set: b's maxima are known (b.parts rows of them).  known: the absmax pass is done.
+template <class DT, bool CLAMP>
+int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, hipStream_t s) {
+  const bool b_max = b.x && !b.part16;
+  const int rblocks = (int)absmax_layout(a, b, amax);
+  if (!known)
+    hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3(ca_strips(a.cols) + (b_max ? ca_strips(b.cols) : 0), (unsigned)rblocks), dim3(256),
+                       0, s, a, b, ca_strips(a.cols));
   launch_amax_to_gamma(a, rblocks, s);
   if (b_max) launch_amax_to_gamma(b, rblocks, s);
   else if (b.x) launch_amax16_to_gamma(b, s);
   hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>),
                      dim3(ct_strips(a.cols) + (b.x ? ct_strips(b.cols) : 0), (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS)), dim3(256), 0, s, a, b,
                      ct_strips(a.cols));
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}
+
+// Rows by themselves, two tensors of them, and the absmax pass of tensors that are quantized by columns later.
+template <class DT, int TPR, int NV, bool CLAMP>
+__global__ __launch_bounds__(256) void quantize_rows_absmax_kernel(RowArgs a, unsigned blocks_rows, AbsmaxTail tail) {
+  if (blockIdx.x < blocks_rows) quantize_rows_block<DT, false, TPR, NV>(a);
+  else absmax_tail<DT, CLAMP>(tail, blockIdx.x - blocks_rows);
+}
+
+template <class DT>
+int launch_rows_absmax(const RowArgs& a, const AbsmaxTail& t, unsigned blocks_tail, hipStream_t s) {
+  rows_shape(a.cols, [&](auto tpr, auto nv) {
+    constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
+    const unsigned blocks = (unsigned)((a.rows + a.rows2 + 256 / TPR - 1) / (256 / TPR));
+    if (t.a.thr) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true>), dim3(blocks + blocks_tail), dim3(256), 0, s, a, blocks, t);
+    else hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, false>), dim3(blocks + blocks_tail), dim3(256), 0, s, a, blocks, t);
+  });
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
@@ -1535,23 +1588,51 @@ int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) {
   return std::max({(rows + 31) / 32 * in, std::min<int64_t>(most, 2048) * std::min<int64_t>(in, 8192), std::min<int64_t>(most, 1024) * in});
 }
 
-// y (null: none): a second tensor [rows_y x cols], quantized by rows only.
-int fp4_launch_quantize_rows_colmax(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
-                                    float* gamma, uint16_t* part, const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y,
-                                    hipStream_t s) {
-  if (!bf16 || (cols % 8) != 0 || cols > 256 * 8 * 8 || rows == 0 || cols == 0) return 1;
-  const int64_t nunits = cols / 8;
-  const int per = da_rows(rows, cols), per_y = 4;   // nothing is folded over y's rows, so few are as good
-  const unsigned blocks = (unsigned)((rows + per - 1) / per), blocks_y = y ? (unsigned)((rows_y + per_y - 1) / per_y) : 0;
-  auto go = [&](auto nv) {
-    hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value>), dim3(blocks + blocks_y), dim3(256), 0, s,
-                       reinterpret_cast<const uint16_t*>(x), rows, cols, ld, codes, gamma, part, per, blocks,
-                       reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y);
-  };
-  if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{});
-  else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{});
-  else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{});
-  else go(std::integral_constant<int, 8>{});
+// What the backward pass of a layer begins with, in one launch: dY [rows x cols] by rows (codes, gamma), W (y; null: none) [rows_y x cols]
+// by rows, and the column maxima that fp4_launch_quantize_cols_pair(known) goes on with: dY's as rows of part16 where the dual-axis
+// pass covers it (bf16, cols at most 16384: *dual), otherwise in amax_scratch, beside those of A (z) [rows x cols_z], clamped at clamp_thr; *known
+// tells whether they are there.
+int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64_t cols, uint8_t* codes, float* gamma, uint16_t* part16,
+                                    const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, const void* z, int64_t cols_z,
+                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, hipStream_t s) {
+  if (rows == 0 || cols == 0 || cols_z == 0 || cols % 8 != 0) return FP4_ERR_SHAPE;
+  *dual = bf16 && cols <= 256 * 8 * 8;
+  AbsmaxTail t = {};
+  t.a.x = z; t.a.thr = clamp_thr; t.a.thr_stride = per_row_thr ? 2 : 0;
+  t.a.rows = rows; t.a.cols = cols_z; t.a.ld = cols_z;
+  t.b.x = x; t.b.part16 = *dual ? part16 : nullptr;
+  t.b.rows = rows; t.b.cols = cols; t.b.ld = cols;
+  const unsigned row_blocks = absmax_layout(t.a, t.b, amax_scratch);
+  t.strips_a = ca_strips(cols_z);
+  t.strips = t.strips_a + (*dual ? 0 : ca_strips(cols));
+  // A second read of what the memory-side cache still holds is cheaper than one from memory: where A and dY are more than that, A's
+  // maxima are taken right before its codes.  In us, apart / together: 8192 x 2048 x 2048 step 424 / 416, 4096 x 4096 x 11008 1100 / 1093,
+  // 8192 x 4096 x 11008 backward (247 MB) 1069 / 1061, 16384 x 4096 x 4096 (268 MB) 644 / 642, 16384 x 4096 x 12288 (537 MB) 3604 / 3620.
+  *known = rows * (cols + cols_z) * (bf16 ? 2 : 4) <= (int64_t)288 << 20;
+  const unsigned blocks_tail = *known ? t.strips * row_blocks : 0;
+  if (*dual) {
+    const int64_t nunits = cols / 8;
+    const int per = da_rows(rows, cols), per_y = 4;   // nothing is folded over y's rows, so few are as good
+    const unsigned blocks = (unsigned)((rows + per - 1) / per), blocks_y = y ? (unsigned)((rows_y + per_y - 1) / per_y) : 0;
+    auto go = [&](auto nv, auto clamp) {
+      hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value, decltype(clamp)::value>), dim3(blocks + blocks_y + blocks_tail), dim3(256),
+                         0, s, reinterpret_cast<const uint16_t*>(x), rows, cols, cols, codes, gamma, part16, per, blocks,
+                         reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y, blocks + blocks_y, t);
+    };
+    auto width = [&](auto clamp) {
+      if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{}, clamp);
+      else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{}, clamp);
+      else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{}, clamp);
+      else go(std::integral_constant<int, 8>{}, clamp);
+    };
+    if (clamp_thr) width(std::true_type{}); else width(std::false_type{});
+  } else {
+    RowArgs a = {};
+    a.x = x; a.codes = codes; a.gamma = gamma; a.rows = rows; a.cols = cols; a.ld = cols;
+    if (y) { a.x2 = y; a.codes2 = codes_y; a.gamma2 = gamma_y; a.rows2 = rows_y; }
+    const int rc = bf16 ? launch_rows_absmax<BF16>(a, t, blocks_tail, s) : launch_rows_absmax<F32>(a, t, blocks_tail, s);
+    if (rc) return rc;
+  }
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
@@ -1613,15 +1694,16 @@ int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
   a.thr_stride = per_row_thr ? 2 : 0;
   a.rows = rows; a.cols = cols; a.ld = ld;
-  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, {}, amax_scratch, s) : launch_cols<F32, true>(a, {}, amax_scratch, s);
-  return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, s) : launch_cols<F32, false>(a, {}, amax_scratch, s);
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, {}, amax_scratch, false, s) : launch_cols<F32, true>(a, {}, amax_scratch, false, s);
+  return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, false, s) : launch_cols<F32, false>(a, {}, amax_scratch, false, s);
 }
 
 // The weight gradient's operands, x [rows x cols] (clamped) and y [rows x cols_y], in as many launches as one of them takes.  part_y:
-// y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.
+// y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.  known:
+// fp4_launch_quantize_rows_absmax has left the maxima in it.
 int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
-                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, hipStream_t s) {
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, hipStream_t s) {
   if (rows == 0 || cols == 0 || cols_y == 0) return FP4_ERR_SHAPE;
   ColArgs a = {}, b = {};
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
@@ -1630,8 +1712,8 @@ int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t
   b.x = y; b.codes_t = codes_y; b.gamma = gamma_y; b.part16 = part_y;
   b.rows = rows; b.cols = cols_y; b.ld = cols_y;
   if (part_y) b.parts = (int)((rows + da_rows(rows, cols_y) - 1) / da_rows(rows, cols_y));
-  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, b, amax_scratch, s) : launch_cols<F32, true>(a, b, amax_scratch, s);
-  return bf16 ? launch_cols<BF16, false>(a, b, amax_scratch, s) : launch_cols<F32, false>(a, b, amax_scratch, s);
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, b, amax_scratch, known, s) : launch_cols<F32, true>(a, b, amax_scratch, known, s);
+  return bf16 ? launch_cols<BF16, false>(a, b, amax_scratch, known, s) : launch_cols<F32, false>(a, b, amax_scratch, known, s);
 }
 
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
