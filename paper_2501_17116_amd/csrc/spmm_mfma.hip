@@ -33,9 +33,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int SM_STEPS_PAD = 12;   // step counts read past the last bundle (11 waves)
 constexpr int SM_KC = 128;       // rows of D per chunk
-constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): three to multiply from, two on their way
-constexpr int SM_AHEAD = 2;
-constexpr int SM_SLACK = SM_RING - SM_AHEAD - 1;   // phases a chunk stays after the one it arrives in
+constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): to multiply from, and on their way
+// Chunks on their way.  With one group a wave a phase has so little to multiply that it lasts as long as a chunk takes to come, so three
+// are, by two staging waves (a wave has 63 loads under way at most, a chunk is 32).
+constexpr int sm_ahead(int g) { return g == 1 ? 3 : 2; }
+constexpr int sm_stagers(int g) { return g == 1 ? 2 : 1; }
+constexpr int sm_slack(int g) { return SM_RING - sm_ahead(g) - 1; }   // phases a chunk stays after the one it arrives in
+constexpr int SM_DEEP = 3;       // steps of a single group requested ahead
 constexpr int SM_NT = 128;       // columns of R per workgroup
 constexpr int SM_ROWB = SM_NT * 2;
 constexpr int SM_CHUNKB = SM_KC * SM_ROWB;
@@ -105,7 +109,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
                                                                uint8_t* __restrict__ o_buf, int32_t* __restrict__ sched,
                                                                int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list,
                                                                int32_t* count) {
-  constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR;
+  constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR, SM_SLACK = sm_slack(G);
   extern __shared__ uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
   uint32_t* const nib = pk_lds;                                                // [G][words] a nibble per column: as many bits as slots
@@ -298,15 +302,16 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   }
 }
 
-// WV waves multiply, G groups of 16 rows each; one more stages D.  Bundles that are not packed are left out, and a
+// WV waves multiply, G groups of 16 rows each; one or two more stage D.  Bundles that are not packed are left out, and a
 // bundle with a non-finite sum is marked in redo: a zero value times an infinite or NaN element of D
 // reaches the other rows of the group.  The tiled kernel writes the rows of both afterwards, from their entries.
 template <int G, int WV>
-__global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t* __restrict__ a_buf, const uint8_t* __restrict__ o_buf,
+__global__ __launch_bounds__((WV + sm_stagers(G)) * 64) void spmm_mfma_kernel(const uint8_t* __restrict__ a_buf, const uint8_t* __restrict__ o_buf,
                                                             const int32_t* __restrict__ sched, const int32_t* __restrict__ steps,
                                                             int32_t* __restrict__ redo, int cap, int phases, int row_blocks,
                                                             int col_blocks, int64_t P, int64_t Q,
                                                             const uint16_t* __restrict__ D, int64_t N, float* __restrict__ R) {
+  constexpr int SM_AHEAD = sm_ahead(G), STAGERS = sm_stagers(G);
   __shared__ __attribute__((aligned(16))) uint8_t ring[SM_RING * SM_CHUNKB];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -330,19 +335,21 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
     return most < 0;
   };
 
-  if (wave == WV) {
-    // The staging wave.  Its loads are its own business: a wave's loads return in order, so in a multiplying wave
+  if (wave >= WV) {
+    // The staging waves.  Their loads are their own business: a wave's loads return in order, so in a multiplying wave
     // every operand load would wait for the chunk requested before it.  One instruction fills 4 rows of a chunk;
     // rows past Q and columns past N read zero (offset out of range).
-    constexpr int LD = SM_KC / 4;
+    constexpr int LD = SM_KC / 4 / STAGERS;
+    static_assert(SM_AHEAD * LD <= 64, "a load more than can be counted waits for one");
+    const int first = STAGERS == 1 ? 0 : (wave - WV) * LD;   // of the chunk's instructions
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(D) + n0, 0, (int)(uint32_t)((Q * N - n0) * 2), 0x00020000);
     const bool in_n = n0 + (lane & 15) * 8 < N;
     const uint32_t rowb = (uint32_t)(N * 2);
-    const uint32_t voff = (uint32_t)(lane >> 4) * rowb + (uint32_t)(lane & 15) * 16u;
+    const uint32_t voff = (uint32_t)(4 * first + (lane >> 4)) * rowb + (uint32_t)(lane & 15) * 16u;
     auto stage = [&](int c) {
-      uint8_t* const slot = ring + (c % SM_RING) * SM_CHUNKB;
-      const int rows = in_n ? (int)min((int64_t)SM_KC, Q - (int64_t)c * SM_KC) - (lane >> 4) : 0;
+      uint8_t* const slot = ring + (c % SM_RING) * SM_CHUNKB + first * 4 * SM_ROWB;
+      const int rows = in_n ? (int)min((int64_t)SM_KC, Q - (int64_t)c * SM_KC) - 4 * first - (lane >> 4) : 0;
       uint32_t off = voff + (uint32_t)(c * SM_KC) * rowb;
 #pragma unroll
       for (int j = 0; j < LD; ++j) {
@@ -385,45 +392,62 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
       const_cast<uint8_t*>(o_buf) + bl * G * (int64_t)o_stride, 0, (int)(o_stride * (uint32_t)G), 0x00020000);
   const int32_t* const sp = sched + bl * phases;
   const uint32_t a_lane = (uint32_t)lane * 16u, o_lane = (uint32_t)(lane >> 4) * 16u;
-  u32x4 a[G], o[G];
-  auto fetch = [&](int g, uint32_t step) {
-    a[g] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, a_lane, (uint32_t)g * a_stride + step * 1024u, 0);
-    o[g] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_o, o_lane, (uint32_t)g * o_stride + step * 64u, 0);
+  // Steps requested: the next one of each group; a single group's next SM_DEEP, which a phase or two have in all, or each would wait for
+  // a round trip to L2 (steps past the last lie past the descriptors' ends or are another bundle's room, and are not used).
+  constexpr int SETS = G == 1 ? SM_DEEP : G;
+  u32x4 a[SETS], o[SETS];
+  auto fetch = [&](int set, uint32_t step) {
+    const uint32_t g = G == 1 ? 0u : (uint32_t)set;
+    a[set] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_a, a_lane, g * a_stride + step * 1024u, 0);
+    o[set] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_o, o_lane, g * o_stride + step * 64u, 0);
   };
 #pragma unroll
-  for (int g = 0; g < G; ++g) fetch(g, 0);
+  for (int set = 0; set < SETS; ++set) fetch(set, G == 1 ? (uint32_t)set : 0u);
   const uint32_t lbase = (uint32_t)(lane & 15) * 16u;
   const bool live = steps[bundle] >= 0;
   if (nothing()) return;
   __builtin_amdgcn_s_barrier();
 
   uint32_t done = 0;
-  auto round = [&]() {
-    ++done;
+  auto multiply = [&](int set, int g) {   // a step of group g
+    u32x4 d[8];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      u32x4 d[8];
+    for (int e = 0; e < 8; ++e) {
+      // row * 256 + the lane's bytes, in one instruction
+      const uint32_t at = __builtin_amdgcn_perm(o[set][e >> 1], lbase, (e & 1) ? 0x0c070600u : 0x0c050400u);
+      d[e] = *reinterpret_cast<const u32x4*>(ring + at);
+    }
+    const bf16x8 av = __builtin_bit_cast(bf16x8, a[set]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // row * 256 + the lane's bytes, in one instruction
-        const uint32_t at = __builtin_amdgcn_perm(o[g][e >> 1], lbase, (e & 1) ? 0x0c070600u : 0x0c050400u);
-        d[e] = *reinterpret_cast<const u32x4*>(ring + at);
+    for (int w = 0; w < 4; ++w) {
+      u32x4 lo, hi;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x05040100u);
+        hi[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x07060302u);
       }
-      const bf16x8 av = __builtin_bit_cast(bf16x8, a[g]);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        u32x4 lo, hi;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          lo[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x05040100u);
-          hi[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x07060302u);
-        }
-        acc[g][2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, lo), acc[g][2 * w], 0, 0, 0);
-        acc[g][2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, hi), acc[g][2 * w + 1], 0, 0, 0);
+      acc[g][2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, lo), acc[g][2 * w], 0, 0, 0);
+      acc[g][2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, hi), acc[g][2 * w + 1], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(set, G == 1 ? done + SM_DEEP - 1 : done);   // into the registers this step is done with
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int turn = 0;   // a single group's: the set of its next step
+  auto rounds = [&](uint32_t upto) {
+    if constexpr (G == 1) {
+      static_assert(SM_DEEP == 3, "the turns below");
+      while (done < upto) {
+        if (turn == 0) { ++done; multiply(0, 0); turn = 1; if (done == upto) break; }
+        if (turn == 1) { ++done; multiply(1, 0); turn = 2; if (done == upto) break; }
+        ++done; multiply(2, 0); turn = 0;
       }
-      __builtin_amdgcn_sched_barrier(0);
-      fetch(g, done);   // the group's next step, into the registers this one is done with
-      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      while (done < upto) {
+        ++done;
+#pragma unroll
+        for (int g = 0; g < G; ++g) multiply(g, g);
+      }
     }
   };
   // The steps done at the end of each phase, 64 phases a register: a scalar load per phase would cost its latency
@@ -436,7 +460,7 @@ __global__ __launch_bounds__((WV + 1) * 64) void spmm_mfma_kernel(const uint8_t*
       plan_next = plan_at(p + 64);
     }
     const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane(plan, p & 63);
-    while (done < upto) round();
+    rounds(upto);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the chunk that goes next are done
     __builtin_amdgcn_s_barrier();
   }
@@ -516,7 +540,7 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                        val, capacity, P, (int)Q, cap, phases, small_grid, split, a_buf, o_buf, sched, steps, redo, list, count);
     const int row_blocks = (int)blocks(G, WV);
     const int per_xcd = (row_blocks * col_blocks + 7) / 8;
-    hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + 1) * 64), 0, s, a_buf, o_buf, sched,
+    hipLaunchKernelGGL((spmm_mfma_kernel<G, WV>), dim3((unsigned)(8 * per_xcd)), dim3((WV + sm_stagers(G)) * 64), 0, s, a_buf, o_buf, sched,
                        steps, redo, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
                        N, R);
     rest = SpmmRest{steps, redo, G};
@@ -524,8 +548,10 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
   // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows
-  // 2.3 us a phase, 176 rows 1.2, 112 rows 1.0; products 16384 x 4096 -> 12288: 852 / 1405 / 1831 us, 1056 x 1376 -> 2080:
-  // 40 / 29 / 28, 512 x 8192 -> 8192: 140 / 88 / 126.
+  // 2.3 us a phase, 176 rows 0.9 (1.05 with two chunks on their way and one step requested ahead); products, their packing and long rows
+  // included, 528 / 176 / 112 rows: 2048 x 8192 -> 2048 218 / 116 / 169 us, 3072 x 8192 -> 2048 223 / 194 / 172, 4096^3 133 / 157 / 210,
+  // 512 x 8192 -> 8192 214 / 110 / 158.  Two rounds of 176 rows against one of 528, between which this leaves the latter: at 2 % they are
+  // faster (4096 x 8192 -> 2048 200 / 227), at 0.2 % slower (110 / 96), and how full the matrix is is not known here.
   auto cost = [&](int g, int wv) { return (blocks(g, wv) * col_blocks + 255) / 256 * (300 + 16 * g * wv); };
   const int64_t big = cost(3, 11), mid = cost(1, 11), small = cost(1, 7);
   using I1 = std::integral_constant<int, 1>;
