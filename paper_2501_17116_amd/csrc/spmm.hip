@@ -763,7 +763,7 @@ __global__ __launch_bounds__(256) void csr_transpose_fill_kernel(const int64_t* 
 }
 
 // ---- transpose as a stable counting sort on the column (column range fits the LDS masks) ---------
-// The rows are cut into blocks of 64.  Inside a block, column c's entries are described by a 64-bit
+// The rows are cut into blocks of 64 (32, mb_rows).  Inside a block, column c's entries are described by a 64-bit
 // mask of the rows that hold one (built with LDS atomic ORs: the result does not depend on their
 // order).  Pass 1 writes the population count of every mask, cnt8[block][c].  Pass 2 scans those
 // counts over the blocks of each column (exclusive, ex[block][c]) and leaves the column totals.
@@ -771,22 +771,25 @@ __global__ __launch_bounds__(256) void csr_transpose_fill_kernel(const int64_t* 
 //   t_ptr[c] + ex[block][c] + popcount(mask[c] below bit r - r0),
 // i.e. behind every entry of the column from an earlier row: the transposed matrix comes out with
 // ascending indices inside every segment, without global atomics and without an ordering pass.
-constexpr int MB_ROWS = 64;          // rows per block = bits per mask
+// Rows per block = bits per mask: 64, above 8192 columns 32, whose masks leave the LDS room for the columns' positions.
+constexpr int mb_rows(int64_t Q) { return Q > 8192 ? 32 : 64; }
 constexpr int MB_THREADS = 1024;   // per workgroup in the two passes that walk entries: they are latency-bound
-constexpr int MB_MAXQ = 16384;       // columns whose masks (8 bytes each) fit 128 KiB of LDS
+constexpr int MB_MAXQ = 16384;       // columns whose masks and positions (4 bytes each) fit 128 KiB of LDS
 
-// first (entry offset, row) bookkeeping shared by pass 1 and pass 3: s_rp[0..64] = clipped row starts
+// first (entry offset, row) bookkeeping shared by pass 1 and pass 3: s_rp[0..MB_ROWS] = clipped row starts
+template <int MB_ROWS>
 FP4_D void mb_load_rows(const int64_t* row_ptr, int64_t rows, int64_t capacity, int64_t r0, long long* s_rp) {
   if (threadIdx.x <= MB_ROWS) {
     const int64_t r = min(r0 + (int64_t)threadIdx.x, rows);
     s_rp[threadIdx.x] = min(row_ptr[r], capacity);
   }
 }
-// row (0..63) of entry e of the block: the last i with s_rp[i] <= e
+// row of entry e of the block: the last i with s_rp[i] <= e
+template <int MB_ROWS>
 FP4_D int mb_row_of(const long long* s_rp, long long e) {
   int lo = 0, hi = MB_ROWS;   // invariant: s_rp[lo] <= e < s_rp[hi]
 #pragma unroll
-  for (int it = 0; it < 6; ++it) {
+  for (int it = 0; (1 << it) < MB_ROWS; ++it) {
     const int mid = (lo + hi) >> 1;
     if (s_rp[mid] <= e) lo = mid; else hi = mid;
   }
@@ -795,6 +798,7 @@ FP4_D int mb_row_of(const long long* s_rp, long long e) {
 
 // sets, for every entry e of the block's range [b, e_end), bit (row of e) of its column's mask; four
 // column loads a thread in flight
+template <int MB_ROWS>
 FP4_D void mb_build_masks(const int32_t* col_idx, const long long* s_rp, long long b, long long e_end, uint32_t* mb_mask) {
   for (long long i0 = b + threadIdx.x; i0 < e_end; i0 += 4 * MB_THREADS) {
     int32_t c[4];
@@ -806,8 +810,8 @@ FP4_D void mb_build_masks(const int32_t* col_idx, const long long* s_rp, long lo
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (c[u] < 0) continue;
-      const int r = mb_row_of(s_rp, i0 + (long long)u * MB_THREADS);
-      atomicOr(&mb_mask[2 * c[u] + (r >> 5)], 1u << (r & 31));
+      const int r = mb_row_of<MB_ROWS>(s_rp, i0 + (long long)u * MB_THREADS);
+      atomicOr(&mb_mask[MB_ROWS / 32 * c[u] + (r >> 5)], 1u << (r & 31));
     }
   }
 }
@@ -816,17 +820,18 @@ template <int QMAX>   // columns the LDS masks are laid out for (the launcher pi
 __global__ __launch_bounds__(MB_THREADS) void csr_mask_count_kernel(const int64_t* row_ptr, const int32_t* col_idx,
                                                              int64_t rows, int64_t Q, int64_t capacity,
                                                              uint8_t* cnt8) {
-  __shared__ uint32_t mb_mask[2 * QMAX];   // rows 0..31 of the block in word 2c, rows 32..63 in word 2c + 1
+  constexpr int MB_ROWS = mb_rows(QMAX), MW = MB_ROWS / 32;
+  __shared__ uint32_t mb_mask[MW * QMAX];   // rows 0..31 of the block in the first of a column's words
   __shared__ long long s_rp[MB_ROWS + 1];
   const int64_t r0 = (int64_t)blockIdx.x * MB_ROWS;
-  for (int i = threadIdx.x; i < 2 * Q; i += MB_THREADS) mb_mask[i] = 0;
-  mb_load_rows(row_ptr, rows, capacity, r0, s_rp);
+  for (int i = threadIdx.x; i < MW * Q; i += MB_THREADS) mb_mask[i] = 0;
+  mb_load_rows<MB_ROWS>(row_ptr, rows, capacity, r0, s_rp);
   __syncthreads();
   const long long b = s_rp[0], e = s_rp[MB_ROWS];
-  mb_build_masks(col_idx, s_rp, b, e, mb_mask);
+  mb_build_masks<MB_ROWS>(col_idx, s_rp, b, e, mb_mask);
   __syncthreads();
   uint8_t* out = cnt8 + (int64_t)blockIdx.x * Q;
-  for (int c = threadIdx.x; c < Q; c += MB_THREADS) out[c] = (uint8_t)(__popc(mb_mask[2 * c]) + __popc(mb_mask[2 * c + 1]));
+  for (int c = threadIdx.x; c < Q; c += MB_THREADS) out[c] = (uint8_t)(__popc(mb_mask[MW * c]) + (MW > 1 ? __popc(mb_mask[MW * c + MW - 1]) : 0));
 }
 
 // 64 columns per workgroup; the four waves split the blocks into quarters: sum, exchange, rescan.
@@ -868,11 +873,12 @@ __global__ __launch_bounds__(256) void csr_mask_scan_kernel(const uint8_t* cnt8,
 
 // Where pass 3 takes the positions from.  FEW: from the counts of all row blocks, at most MB_FEW_BYTES of them, which every
 // workgroup adds up for itself.  SCAN: from pass 2's ex and totals, which every workgroup scans over the columns.  Either way
-// a column's position waits in LDS beside its mask, and the workgroup of the first row block writes t_ptr.  TABLE: masks of more
-// than 8192 columns leave no room for positions; t_ptr comes from a scan of its own.  Bound by round trips to memory, so by the
+// a column's position waits in LDS beside its mask, and the workgroup of the first row block writes t_ptr.  TABLE: with 2^32
+// elements or more positions have no room in 32 bits; t_ptr comes from a scan of its own.  Bound by round trips to memory, so by the
 // launches and by what a workgroup asks for one after another.
 // Whole transposition at 2 % (count, scan over blocks, scan over columns and fill as four launches / now): 256 x 512 12.3 / 8.2 us,
-// 1056 x 1376 at 6 % 28.7 / 19.3, 2048 x 2048 22.2 / 14.9, 8192 x 2048 25.0 / 19.3, 16384 x 4096 46.3 / 38.1.
+// 1056 x 1376 at 6 % 28.7 / 19.3, 2048 x 2048 22.2 / 14.9, 8192 x 2048 25.0 / 19.3, 16384 x 4096 46.3 / 38.1,
+// 16384 x 11008 the fill alone (blocks of 64 rows, from a table / of 32) 156 / 98.
 enum class MbFrom { FEW, SCAN, TABLE };
 constexpr int64_t MB_FEW_BYTES = 64 * 1024;
 
@@ -882,8 +888,9 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
                                                             int64_t capacity, int64_t* t_ptr, const uint32_t* ex, const int32_t* cnt,
                                                             const uint8_t* cnt8, int32_t* t_idx, float* t_val) {
   constexpr bool TABLE = FROM == MbFrom::TABLE;
+  constexpr int MB_ROWS = mb_rows(QMAX), MW = MB_ROWS / 32;
   constexpr int PER = QMAX / MB_THREADS;   // consecutive columns a thread forms positions of: a multiple of 4
-  __shared__ uint32_t mb_mask[2 * QMAX];
+  __shared__ uint32_t mb_mask[MW * QMAX];
   __shared__ long long s_rp[MB_ROWS + 1];
   __shared__ uint32_t s_pos[TABLE ? 1 : QMAX];   // fewer than 2^32 entries (the launcher's rule)
   __shared__ uint32_t s_w[MB_THREADS / 64];
@@ -896,8 +903,8 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
   const int64_t r0 = (int64_t)block * MB_ROWS;
   const int c0 = (int)threadIdx.x * PER;
   uint32_t before[PER] = {}, total[PER] = {}, sum = 0, incl = 0;   // a column's entries in earlier blocks, and all of them
-  mb_load_rows(row_ptr, rows, capacity, r0, s_rp);
-  for (int i = threadIdx.x; i < 2 * Q; i += MB_THREADS) mb_mask[i] = 0;
+  mb_load_rows<MB_ROWS>(row_ptr, rows, capacity, r0, s_rp);
+  for (int i = threadIdx.x; i < MW * Q; i += MB_THREADS) mb_mask[i] = 0;
   if constexpr (!TABLE) {
 #pragma unroll
     for (int j = 0; j < PER; j += 4) {   // Q is a multiple of 4
@@ -945,7 +952,7 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
     if (block == 0 && threadIdx.x == 0) t_ptr[0] = 0;
   }
   const long long b = s_rp[0], e = s_rp[MB_ROWS];
-  mb_build_masks(col_idx, s_rp, b, e, mb_mask);
+  mb_build_masks<MB_ROWS>(col_idx, s_rp, b, e, mb_mask);
   __syncthreads();
   // Placement, four entries a thread at a time: the steps of the chain column -> position -> store that go to memory are round
   // trips, so the four chains run side by side.
@@ -968,8 +975,8 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (c[u] < 0) continue;
-      const int r = mb_row_of(s_rp, i0 + (long long)u * MB_THREADS);
-      const uint32_t lo = mb_mask[2 * c[u]], hi = mb_mask[2 * c[u] + 1];
+      const int r = mb_row_of<MB_ROWS>(s_rp, i0 + (long long)u * MB_THREADS);
+      const uint32_t lo = mb_mask[MW * c[u]], hi = mb_mask[MW * c[u] + MW - 1];
       const uint32_t below = r < 32 ? __popc(lo & ((1u << r) - 1u)) : __popc(lo) + __popc(hi & ((1u << (r - 32)) - 1u));
       const int64_t p = pos[u] + below;
       if (p < capacity) {
@@ -1162,7 +1169,7 @@ int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr,
 // cnt[Q], ex[blocks][Q] (uint32), cnt8[blocks][Q] (bytes).  Otherwise: cnt[Q], cursor[Q].
 int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
   if (Q > MB_MAXQ) return 2 * Q;
-  const int64_t blocks = (P + MB_ROWS - 1) / MB_ROWS;
+  const int64_t blocks = (P + mb_rows(Q) - 1) / mb_rows(Q);
   return Q + 64 + blocks * Q + (blocks * Q + 3) / 4 + 64;
 }
 
@@ -1173,7 +1180,7 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
                              hipStream_t s) {
   int32_t* cnt = scratch;
   if (Q <= MB_MAXQ) {
-    const int nblocks = (int)std::max<int64_t>(1, (P + MB_ROWS - 1) / MB_ROWS);
+    const int nblocks = (int)std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q));
     uint32_t* ex = reinterpret_cast<uint32_t*>(scratch + Q + 64);
     uint8_t* cnt8 = reinterpret_cast<uint8_t*>(ex + (int64_t)nblocks * Q);
     auto count = [&](auto qmax) {
@@ -1191,16 +1198,16 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
     using Scan = std::integral_constant<MbFrom, MbFrom::SCAN>;
     using Table = std::integral_constant<MbFrom, MbFrom::TABLE>;
     if (Q <= 4096) count(Q4{}); else if (Q <= 8192) count(Q8{}); else count(Q16{});
-    const bool positions = Q <= 8192 && Q % 4 == 0 && P * Q < ((int64_t)1 << 32);
+    const bool positions = Q % 4 == 0 && P * Q < ((int64_t)1 << 32);
     if (positions && nblocks * Q <= MB_FEW_BYTES) {
-      if (Q <= 4096) fill(Q4{}, Few{}); else fill(Q8{}, Few{});
+      if (Q <= 4096) fill(Q4{}, Few{}); else if (Q <= 8192) fill(Q8{}, Few{}); else fill(Q16{}, Few{});
       FP4_CHECK_LAUNCH();
       return FP4_OK;
     }
     hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0, s, cnt8, nblocks, Q, ex, cnt);
     FP4_CHECK_LAUNCH();
     if (positions) {
-      if (Q <= 4096) fill(Q4{}, Scan{}); else fill(Q8{}, Scan{});
+      if (Q <= 4096) fill(Q4{}, Scan{}); else if (Q <= 8192) fill(Q8{}, Scan{}); else fill(Q16{}, Scan{});
     } else {
       const int rc = fp4_launch_scan_rows(cnt, Q, t_ptr, nullptr, s);
       if (rc) return rc;

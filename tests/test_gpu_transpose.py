@@ -1,5 +1,5 @@
 """The residual's transpose inside the weight gradient, at the sizes where its positions come from another place: counts of
-all row blocks in the filling workgroup (up to 64 Ki of them), pass 2's scan beyond that, a table above 8192 columns."""
+all row blocks in the filling workgroup (up to 64 Ki of them), pass 2's scan beyond that, blocks of 32 rows above 8192 columns."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,7 @@ from paper_2501_17116_amd import binding as b
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K", [(32, 64), (96, 4128), (1024, 4096), (1056, 4096), (512, 8192), (544, 8192), (96, 8224)])
+@pytest.mark.parametrize("M,K", [(32, 64), (96, 4128), (1024, 4096), (1056, 4096), (512, 8192), (544, 8192), (96, 8224), (224, 8224), (256, 8224), (96, 16384)])
 def test_weight_gradient_of_a_residual(M, K):
     N, alpha, k, cap = 32, 0.97, 5.0, 3.0
     g = torch.Generator().manual_seed(M + K)
