@@ -1167,10 +1167,12 @@ int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr,
 
 // int32 words of scratch the transpose of a P x Q matrix needs.  Mask path (Q <= MB_MAXQ):
 // cnt[Q], ex[blocks][Q] (uint32), cnt8[blocks][Q] (bytes).  Otherwise: cnt[Q], cursor[Q].
+// A matrix too wide for the masks counts as the widest that is not, or a wider one would need less.
 int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
-  if (Q > MB_MAXQ) return 2 * Q;
+  const int64_t columns = 2 * Q;
+  Q = std::min<int64_t>(Q, MB_MAXQ);
   const int64_t blocks = (P + mb_rows(Q) - 1) / mb_rows(Q);
-  return Q + 64 + blocks * Q + (blocks * Q + 3) / 4 + 64;
+  return std::max(columns, Q + 64 + blocks * Q + (blocks * Q + 3) / 4 + 64);
 }
 
 // u_idx/u_val: unordered staging, capacity entries each (only the path for very wide matrices uses it)

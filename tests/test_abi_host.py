@@ -2,6 +2,7 @@
 arguments before launching anything, and its rounding routine (run on the host) agrees with
 the oracle bit for bit."""
 import ctypes as C
+import itertools
 import os
 import re
 
@@ -216,6 +217,19 @@ def test_a_smaller_problem_never_needs_a_larger_workspace(L):
                 big = (size(), size(), size())
                 small = tuple(min(x, size()) if rng.random() < 0.6 else x for x in big)
                 assert bytes_of(op, small, dt) <= bytes_of(op, big, dt), (op, dt, small, big)
+
+
+@pytest.mark.parametrize("op", range(9))
+def test_workspaces_grow_along_every_dimension(L, op):
+    """Each dimension by itself, in the smallest steps, past every size at which a path begins or ends; the other two at
+    sizes on either side of those."""
+    around = [v + d for v in (64, 512, 1024, 2048, 4096, 8192, 16384, 24576, 32768, 65536) for d in (-32, 0, 32)]
+    for dt in (b.FP4_F32, b.FP4_BF16):
+        for dim in range(3):
+            for other in itertools.product((32, 4096, 8224, 16384, 65536), repeat=2):
+                need = [b.workspace_bytes(op, *other[:dim], v, *other[dim:], dt) for v in around]
+                for v, less, more in zip(around[1:], need, need[1:]):
+                    assert less <= more, (dt, dim, other, v)
 
 
 def test_residual_temporaries_and_product_share_their_room(L):
