@@ -304,6 +304,12 @@ int fp4_dge_apply(const float* G, const void* W, fp4_dtype dt, const float* gamm
 int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                       int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N,
                       float* R, void* workspace, size_t workspace_bytes, void* stream);
+/* The same of a matrix that is known to have at most `capacity` entries (the room col_idx and val have; what row_ptr
+ * counts beyond that is left out): a small product is faster by another kernel the fewer entries there can be, and the
+ * call above has to reckon with a full matrix. */
+int fp4_residual_spmm_bounded(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
+                              int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N,
+                              float* R, void* workspace, size_t workspace_bytes, void* stream);
 
 #ifdef __cplusplus
 }

@@ -92,6 +92,9 @@ def lib() -> C.CDLL:
         L.fp4_dge_apply.argtypes = [vp, vp, i32, vp, i64, i64, f32, f32, vp, vp]
         L.fp4_residual_spmm.argtypes = [vp, vp, vp, i64, i64, vp, i32, i64, vp, vp, sz, vp]
         L.fp4_residual_spmm_general.argtypes = L.fp4_residual_spmm.argtypes
+        L.fp4_residual_spmm_bounded.argtypes = [vp, vp, vp, i64, i64, i64, vp, i32, i64, vp, vp, sz, vp]
+        L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64]
+        L.fp4_residual_spmm_gathers.restype = i32
         L.fp4_host_round_codes.argtypes = [vp, i64, vp]
         L.fp4_device_round_codes.argtypes = [vp, i64, vp, vp]
         L.fp4_device_round_sweep.argtypes = [vp, vp]
@@ -518,22 +521,27 @@ def fp4_dge_apply(G: torch.Tensor, W: torch.Tensor, gamma_W: torch.Tensor, dge_k
 
 def fp4_residual_spmm(row_ptr: torch.Tensor, col_idx: torch.Tensor, val: torch.Tensor, Q: int,
                       D: torch.Tensor, R: Optional[torch.Tensor] = None, ws: Optional[Workspace] = None) -> torch.Tensor:
-    return _residual_spmm("fp4_residual_spmm", row_ptr, col_idx, val, Q, D, R, ws)
+    return _residual_spmm("fp4_residual_spmm_bounded", (col_idx.numel(),), row_ptr, col_idx, val, Q, D, R, ws)
 
 
 def fp4_residual_spmm_general(row_ptr: torch.Tensor, col_idx: torch.Tensor, val: torch.Tensor, Q: int,
                               D: torch.Tensor, R: Optional[torch.Tensor] = None, ws: Optional[Workspace] = None) -> torch.Tensor:
-    return _residual_spmm("fp4_residual_spmm_general", row_ptr, col_idx, val, Q, D, R, ws)
+    return _residual_spmm("fp4_residual_spmm_general", (), row_ptr, col_idx, val, Q, D, R, ws)
 
 
-def _residual_spmm(name, row_ptr, col_idx, val, Q, D, R, ws):
+def fp4_residual_spmm_gathers(P: int, Q: int, N: int, dt: int, entries: int) -> bool:
+    """Whether a residual product is the gathering kernel's (host arithmetic, no GPU)."""
+    return bool(lib().fp4_residual_spmm_gathers(P, Q, N, dt, entries))
+
+
+def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
     _dev_check(row_ptr, col_idx, val, D, R)
     P = row_ptr.numel() - 1
     N = D.shape[1]
     if R is None:
         R = torch.empty((P, N), dtype=torch.float32, device=D.device)
     w = _ws(workspace_bytes(FP4_OP_SPMM, P, Q, N, _dt(D)), ws)
-    _check(getattr(lib(), name)(_ptr(row_ptr), _ptr(col_idx), _ptr(val), P, Q, _ptr(D), _dt(D), N,
+    _check(getattr(lib(), name)(_ptr(row_ptr), _ptr(col_idx), _ptr(val), *capacity, P, Q, _ptr(D), _dt(D), N,
                                 _ptr(R), _ptr(w), w.numel(), _stream()), name)
     return R
 

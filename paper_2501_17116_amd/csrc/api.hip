@@ -665,29 +665,35 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
 }
 
 namespace {
-int residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t P, int64_t Q, const void* D, fp4_dtype dt,
-                  int64_t N, float* R, void* workspace, size_t workspace_bytes, void* stream, bool general) {
+int residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q, const void* D,
+                  fp4_dtype dt, int64_t N, float* R, void* workspace, size_t workspace_bytes, void* stream, bool general) {
   if (!dtype_ok(dt)) return FP4_ERR_DTYPE;
   if (P < 0 || Q < 0 || N < 0 || (N % 8) != 0) return FP4_ERR_SHAPE;
+  if (capacity < 0) return FP4_ERR_ARG;
   if (P == 0 || N == 0) return FP4_OK;
   if (!row_ptr || !D || !R) return FP4_ERR_NULL;
   if (!aligned16(D) || !aligned16(R)) return FP4_ERR_ARG;
   if (!workspace || workspace_bytes < fp4_workspace_bytes(FP4_OP_SPMM, P, Q, N, dt)) return FP4_ERR_WORKSPACE;
   int32_t* scratch = reinterpret_cast<int32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
-  // no entry limit besides row_ptr itself
-  return fp4_launch_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt == FP4_BF16, N, R, scratch,
-                         (hipStream_t)stream, general);
+  return fp4_launch_spmm(row_ptr, col_idx, val, capacity, P, Q, D, dt == FP4_BF16, N, R, scratch, (hipStream_t)stream, general);
 }
 }  // namespace
 
 extern "C" int fp4_residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                                  int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
                                  void* workspace, size_t workspace_bytes, void* stream) {
-  return residual_spmm(row_ptr, col_idx, val, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, false);
+  // no entry limit besides row_ptr itself
+  return residual_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, false);
+}
+
+extern "C" int fp4_residual_spmm_bounded(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
+                                         int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
+                                         void* workspace, size_t workspace_bytes, void* stream) {
+  return residual_spmm(row_ptr, col_idx, val, capacity, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, false);
 }
 
 extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                                          int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
                                          void* workspace, size_t workspace_bytes, void* stream) {
-  return residual_spmm(row_ptr, col_idx, val, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, true);
+  return residual_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, true);
 }

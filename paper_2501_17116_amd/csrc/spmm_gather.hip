@@ -4,8 +4,10 @@
 // row of D is used again and again.  In a small product the launches are most of it and D fits the L2s: here every entry
 // gathers its piece of D from L2, GA_AHEAD requests of 1 KiB on their way a wave, and plain FMAs add it up.
 #include "fp4_common.h"
+#include "fp4_measure.h"
 #include "spmm_long.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -152,23 +154,38 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
 
 }  // namespace
 
-// Returns 1 where the packed or the tiled kernel is the better one.
+// Whether a product of `entries` entries, or at most so many, is gathered.
 //
-// The gathers move entries x N x the size of an element through the L2s, at about 20 TB/s while a strip of D stays in one (2048^3,
-// 6 %, bf16: 1.03 GB in 46 us); the other kernels' time goes with what they stage and with the output.  The lines lie where the two meet
-// at the 6 % of the densest residual in use.  In us, this / the others:
-//   bf16  64 x 2048 -> 2048, 2 % 3.8 / 27.4; 1056 x 1376 -> 2080, 6 % 23.5 / 35.0; 2048^3, 0.2 % 14 / 31, 2 % 20.6 / 35.7, 6 % 46 / 49;
-//         4096 x 1024 -> 2048, 6 % 51 / 56; 16384 x 128 -> 2048, 6 % 63 / 52; 512 x 4096 -> 8192, 6 % 103 / 75
-//   fp32  256 x 512 -> 512, 2 % 3.2 / 19.8; 2048^3, 2 % 30.5 / 53.5, 6 % 74 / 95; 2048 x 1024 -> 2048, 6 % 40 / 52; 4096 x 1024 -> 2048,
-//         6 % 76 / 60
-// A dense row moves Q x 512 bytes through one CU: with four of them 2048 x 1024 -> 1024 15.4 / 29.2, 512 x 8192 -> 1024 86.6 / 86.0,
-// 256 x 16384 -> 1024 306 / 149, hence the line at 8192.  A matrix 12 % full or more would be better off there from 2^32 on (2048^3 bf16,
-// 12 %: 81 / 59).
-int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
-                           const void* D, int bf16, int64_t N, float* R, hipStream_t s) {
+// The gathers move entries x N x the size of an element through the L2s, at 20 to 30 TB/s while a strip of D stays in one; the other kernels'
+// time goes with what they stage, Q x N, and with the output.  What they take besides goes with the entries too, but in the packed kernel
+// hardly (and a value of several terms may send its matrix to the tiled one: the lines are those of values that bf16 holds, at which it is
+// fastest).  So there is a number of entries up to which gathering is faster.  In us, this / the others, and the bytes where they meet:
+//   bf16  4096 x 512 -> 1024, 12 % 28 / 32, 20 % 38 / 35 (709 MB); 2048 x 1024 -> 1024, 12 % 27 / 34, 20 % 39 / 36 (762); 1056 x 1376 ->
+//         2080, 6 % 24 / 35, 12 % 40 / 40 (704); 2048 x 2048 -> 1024, 12 % 45 / 50, 20 % 72 / 54 (1171); 2048^3, 2 % 23 / 37, 6 % 48 / 50, 9 %
+//         67 / 56, 20 % 132 / 63 (1104); 1024 x 4096 -> 1024, 20 % 76 / 86 (2046); 512 x 8192 -> 1024, 20 % 109 / 153 (2918)
+//   fp32  4096 x 512 -> 1024, 20 % 63 / 67, 50 % 145 / 122 (2060); 2048^3, 12 % 144 / 148, 20 % 229 / 214 (4737); 1056 x 1376 -> 2080, 2048 x
+//         1024 -> 1024 and smaller outputs never, 100 % 418 / 491 and 277 / 367: there the tiled kernel has too few workgroups
+// Beyond 2^33, 2^23 outputs (fp32 2^22) or 8192 columns the others are faster at 6 %, the densest residual in use: bf16 16384 x 128 -> 2048
+// 63 / 52, 512 x 4096 -> 8192 103 / 75; fp32 4096 x 1024 -> 2048 76 / 60.  A dense row moves Q x 512 bytes through one CU: with four of them 2048 x
+// 1024 -> 1024 15.4 / 29.2, 512 x 8192 -> 1024 86.6 / 86.0, 256 x 16384 -> 1024 306 / 149.
+static bool gathers(int64_t P, int64_t Q, int64_t N, int bf16, int64_t entries) {
   const int es = bf16 ? 2 : 4;
   const double out = (double)P * (double)N, d_bytes = (double)Q * (double)N * es;
-  if (out * (double)Q > 0x1p33 || out > (bf16 ? 0x1p23 : 0x1p22) || Q > 8192 || d_bytes > (double)0xe0000000u) return 1;   // 32-bit offsets into D
+  if (out * (double)Q > 0x1p33 || out > (bf16 ? 0x1p23 : 0x1p22) || Q > 8192 || d_bytes > (double)0xe0000000u) return false;   // 32-bit offsets into D
+  const double moved = std::min((double)entries, (double)P * (double)Q) * (double)N * es;
+  if (bf16) return moved <= 0x1p28 + (double)Q * 0x1p18 + 64 * out;
+  return out <= 5 * 0x1p19 || moved <= 0x1p30 + 1.5 * (double)Q * 0x1p20;
+}
+
+extern "C" int fp4_residual_spmm_gathers(int64_t P, int64_t Q, int64_t N, fp4_dtype dt, int64_t entries) {
+  return gathers(P, Q, N, dt == FP4_BF16, entries);
+}
+
+// Returns 1 where the packed or the tiled kernel takes the product.  capacity: no more entries than that.
+int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
+                           const void* D, int bf16, int64_t N, float* R, hipStream_t s) {
+  if (!gathers(P, Q, N, bf16, capacity)) return 1;
+  const int es = bf16 ? 2 : 4;
   const uint8_t* const d = reinterpret_cast<const uint8_t*>(D);
   auto launch = [&](auto dt, auto lanes, auto waves, auto rows) {
     constexpr int L = decltype(lanes)::value, W = decltype(waves)::value, ROWS = decltype(rows)::value;
