@@ -35,7 +35,13 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
   const int per_xcd = (items + 7) / 8;
   const int item = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
   if ((int)(blockIdx.x / 8) >= per_xcd || item >= items) return;
-  const int64_t row0 = (int64_t)(item % row_blocks) * ROWS;
+  // Of every eight rows that lie side by side a workgroup has one, and not always the same: outlier channels are often neighbours, or as
+  // far apart as a head is wide, and rows that all waves share are taken one after another.  In us, bf16, 1 % and eight full rows side by
+  // side, eight rows in order a workgroup / now / the kernels of large products: 2048^3 112 / 25 / 43, 512 x 2048 -> 512 108 / 19 / 35,
+  // 1024^3 59 / 13 / 31, 4096 x 512 -> 1024 35 / 13 / 34; fp32 2048^3 85 / 32 / 56.  Without such rows up to 4 % slower (1056 x 1376 -> 2080, 6 %
+  // 24.0 / 25.0; 2048^3 22.2 / 22.5), because the entries' lines are several workgroups'.
+  const int rb = item % row_blocks;
+  auto row_of = [&](int r) { return (int64_t)(rb / 8) * (8 * ROWS) + 8 * r + ((rb + r) & 7); };   // P or more: none
   const int64_t n0 = (int64_t)(item / row_blocks) * COLS;
   const int side = lane / LANES, l = lane % LANES;
   // What an entry past the last or a column past N would ask for lies past the descriptor's end and arrives as zero: no branch between
@@ -97,8 +103,8 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
       *reinterpret_cast<f32x4*>(&sums[wave][side][l * PER + 4 * h]) = f32x4{sum[4 * h], sum[4 * h + 1], sum[4 * h + 2], sum[4 * h + 3]};
   };
   // The rows' ends, a lane each; every wave has them all, so all come to the same answer without a word.
-  const int64_t rp = min(row_ptr[min(row0 + min(lane, ROWS), P)], capacity);
-  const int64_t next = __shfl_down(rp, 1, 64);
+  const int64_t my_row = min(row_of(min(lane, ROWS - 1)), P);
+  const int64_t rp = min(row_ptr[my_row], capacity), next = min(row_ptr[min(my_row + 1, P)], capacity);
   const int n_lane = lane < ROWS ? (int)max(next - rp, (int64_t)0) : 0;
   const int64_t limit = max((int64_t)64, 4 * (min(row_ptr[P], capacity) - row_ptr[0]) / P);
   const uint64_t long_rows = __ballot(n_lane > limit);
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
         for (int h = 1; h < SIDE; ++h) q += sums[w][h][t] + sums[w + 1][h][t];
         s += q;
       }
-      if (n0 + t < N) R[(row0 + r) * N + n0 + t] = s;
+      if (n0 + t < N) R[row_of(r) * N + n0 + t] = s;
     }
     __syncthreads();   // the sums are read
   }
@@ -131,13 +137,13 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
   if constexpr (SHARE == 1) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the sums are this wave's own
     __builtin_amdgcn_wave_barrier();
-    if (shared_row || row0 + mine >= P) return;
+    if (shared_row || row_of(mine) >= P) return;
 #pragma unroll
     for (int t = lane * 4; t < COLS; t += 256) {
       f32x4 s = *reinterpret_cast<const f32x4*>(&sums[wave][0][t]);
 #pragma unroll
       for (int h = 1; h < SIDE; ++h) s += *reinterpret_cast<const f32x4*>(&sums[wave][h][t]);
-      if (n0 + t < N) *reinterpret_cast<f32x4*>(R + (row0 + mine) * N + n0 + t) = s;
+      if (n0 + t < N) *reinterpret_cast<f32x4*>(R + row_of(mine) * N + n0 + t) = s;
     }
   } else {
     __syncthreads();
@@ -147,7 +153,7 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
       f32x4 s = *reinterpret_cast<const f32x4*>(&sums[r * SHARE][0][c]);
 #pragma unroll
       for (int h = 1; h < SHARE * SIDE; ++h) s += *reinterpret_cast<const f32x4*>(&sums[r * SHARE + h / SIDE][h % SIDE][c]);
-      if (!((long_rows >> r) & 1) && row0 + r < P && n0 + c < N) *reinterpret_cast<f32x4*>(R + (row0 + r) * N + n0 + c) = s;
+      if (!((long_rows >> r) & 1) && row_of(r) < P && n0 + c < N) *reinterpret_cast<f32x4*>(R + row_of(r) * N + n0 + c) = s;
     }
   }
 }
@@ -166,43 +172,45 @@ __global__ __launch_bounds__(WAVES * 64, 8) void spmm_gather_kernel(const int64_
 //   fp32  4096 x 512 -> 1024, 20 % 63 / 67, 50 % 145 / 122 (2060); 2048^3, 12 % 144 / 148, 20 % 229 / 214 (4737); 1056 x 1376 -> 2080, 2048 x
 //         1024 -> 1024 and smaller outputs never, 100 % 418 / 491 and 277 / 367: there the tiled kernel has too few workgroups
 // Beyond 2^33, 2^23 outputs (fp32 2^22) or 8192 columns the others are faster at 6 %, the densest residual in use: bf16 16384 x 128 -> 2048
-// 63 / 52, 512 x 4096 -> 8192 103 / 75; fp32 4096 x 1024 -> 2048 76 / 60.  A dense row moves Q x 512 bytes through one CU: with four of them 2048 x
-// 1024 -> 1024 15.4 / 29.2, 512 x 8192 -> 1024 86.6 / 86.0, 256 x 16384 -> 1024 306 / 149.
-static bool gathers(int64_t P, int64_t Q, int64_t N, int bf16, int64_t entries) {
+// 63 / 52, 512 x 4096 -> 8192 103 / 75; fp32 4096 x 1024 -> 2048 76 / 60.  A dense row moves Q x 512 bytes through one CU, about 8.5 ns an entry, which
+// from 4096 to 8192 columns on is what the others take for everything: 1 % and none / one / four of them, bf16 512 x 4096 -> 1024 8, 32, 33 / 38,
+// 46, 46; 512 x 8192 -> 2048 15, 85, 83 / 61, 74, 74; 256 x 16384 -> 1024 306 / 149.  channels: the rows are (a weight gradient's transposed
+// residual), and outlier channels are what there is of such rows; tokens are seldom.
+static bool gathers(int64_t P, int64_t Q, int64_t N, int bf16, int64_t entries, bool channels) {
   const int es = bf16 ? 2 : 4;
   const double out = (double)P * (double)N, d_bytes = (double)Q * (double)N * es;
-  if (out * (double)Q > 0x1p33 || out > (bf16 ? 0x1p23 : 0x1p22) || Q > 8192 || d_bytes > (double)0xe0000000u) return false;   // 32-bit offsets into D
+  if (out * (double)Q > 0x1p33 || out > (bf16 ? 0x1p23 : 0x1p22) || Q > (channels ? 4096 : 8192) || d_bytes > (double)0xe0000000u) return false;   // 32-bit offsets into D
   const double moved = std::min((double)entries, (double)P * (double)Q) * (double)N * es;
   if (bf16) return moved <= 0x1p28 + (double)Q * 0x1p18 + 64 * out;
   return out <= 5 * 0x1p19 || moved <= 0x1p30 + 1.5 * (double)Q * 0x1p20;
 }
 
-extern "C" int fp4_residual_spmm_gathers(int64_t P, int64_t Q, int64_t N, fp4_dtype dt, int64_t entries) {
-  return gathers(P, Q, N, dt == FP4_BF16, entries);
+extern "C" int fp4_residual_spmm_gathers(int64_t P, int64_t Q, int64_t N, fp4_dtype dt, int64_t entries, int channels) {
+  return gathers(P, Q, N, dt == FP4_BF16, entries, channels != 0);
 }
 
 // Returns 1 where the packed or the tiled kernel takes the product.  capacity: no more entries than that.
 int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
-                           const void* D, int bf16, int64_t N, float* R, hipStream_t s) {
-  if (!gathers(P, Q, N, bf16, capacity)) return 1;
+                           const void* D, int bf16, int64_t N, float* R, bool channels, hipStream_t s) {
+  if (!gathers(P, Q, N, bf16, capacity, channels)) return 1;
   const int es = bf16 ? 2 : 4;
   const uint8_t* const d = reinterpret_cast<const uint8_t*>(D);
   auto launch = [&](auto dt, auto lanes, auto waves, auto rows) {
     constexpr int L = decltype(lanes)::value, W = decltype(waves)::value, ROWS = decltype(rows)::value;
-    const int64_t cols = L * 16 / es, row_blocks = (P + ROWS - 1) / ROWS, items = (N + cols - 1) / cols * row_blocks;
+    const int64_t cols = L * 16 / es, row_blocks = (P + 8 * ROWS - 1) / (8 * ROWS) * 8, items = (N + cols - 1) / cols * row_blocks;
     hipLaunchKernelGGL((spmm_gather_kernel<decltype(dt), L, W, ROWS>), dim3((unsigned)((items + 7) / 8 * 8)), dim3(W * 64), 0, s, row_ptr,
                        col_idx, val, capacity, P, (int)row_blocks, (int)items, (int)Q, d, N, R);
   };
   using I1 = std::integral_constant<int, 1>;
-  using I4 = std::integral_constant<int, 4>;
   using I8 = std::integral_constant<int, 8>;
   using I32 = std::integral_constant<int, 32>;
   using I64 = std::integral_constant<int, 64>;
-  // Four waves a row where eight rows a workgroup would leave half the chip without one: 64 x 2048 -> 2048 3.8 against 5.6 us, 256 x 512 ->
-  // 512 3.3 / 4.2; 1056 x 1376 -> 2080 25.5 / 21.7.
+  // Eight waves a row where eight rows a workgroup would leave half the chip without one (four: 64 x 2048 -> 2048 3.8 against 5.6 us, 256 x 512
+  // -> 512 3.3 / 4.2; 1056 x 1376 -> 2080 25.5 / 21.7).  Four of them are as fast but where rows are full or nearly: 64 x 8192 -> 2048 bf16, 6 %, four /
+  // eight 16.5 / 13.9, 1 % and one full row 156 / 91; 64 x 2048 -> 2048 36 / 27.
   const int64_t half = (int64_t)32 * 16 / es;
   const bool few = (P + 7) / 8 * ((N + half - 1) / half) < 128;
-  auto shape = [&](auto dt) { if (few) launch(dt, I64{}, I4{}, I1{}); else launch(dt, I32{}, I8{}, I8{}); };
+  auto shape = [&](auto dt) { if (few) launch(dt, I64{}, I8{}, I1{}); else launch(dt, I32{}, I8{}, I8{}); };
   if (bf16) shape(BF16{}); else shape(F32{});
   FP4_CHECK_LAUNCH();
   return FP4_OK;

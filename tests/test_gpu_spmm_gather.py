@@ -55,3 +55,40 @@ def test_entries_in_any_order(dtype):
     mag = torch.zeros_like(ref).index_add_(0, row, (val[11:, None].double() * D.double()[col[11:].long()]).abs())
     R = b.fp4_residual_spmm(ptr, col, val, Q, D)
     assert torch.all((R.double() - ref).abs() <= (count[:, None] + 1).double() * 2.0 ** -23 * mag)
+
+
+def _csr(mask, g):
+    ptr = torch.zeros(mask.shape[0] + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(mask.sum(1), 0, out=ptr[1:])
+    S = torch.randn(*mask.shape, generator=g, device="cuda").bfloat16().float()
+    return ptr, mask.nonzero()[:, 1].int().contiguous(), S[mask].contiguous()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("apart", [1, 8, 16, 64, 128])
+def test_full_rows_at_a_distance_cost_what_one_does(apart, dtype):
+    """Eight of them, side by side or a head's width apart, are eight workgroups' (side by side and taken one after another by one, they
+    cost 2.3 times as much as a single one)."""
+    P, Q, N = 2048, 2048, 1024
+    g = torch.Generator(device="cuda").manual_seed(1)
+    sparse = torch.rand(P, Q, generator=g, device="cuda") < 0.01
+    D = torch.randn(Q, N, generator=g, device="cuda").to(dtype)
+    R = torch.empty(P, N, device="cuda")
+    best = []
+    for rows in (1, 8):
+        mask = sparse.clone()
+        mask[[1024 - 4 * apart + i * apart for i in range(rows)]] = True
+        args = _csr(mask, g)
+        for _ in range(3):
+            b.fp4_residual_spmm(*args, Q, D, R=R)
+        times = []
+        for _ in range(12):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(8):
+                b.fp4_residual_spmm(*args, Q, D, R=R)
+            e[1].record()
+            e[1].synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        best.append(min(times))
+    assert best[1] < 2.0 * best[0], best
