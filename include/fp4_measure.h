@@ -38,6 +38,11 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
+/* Where the places of the entries come from in the transpose that a weight gradient takes of its residual [P x Q]: 1: counts of all row
+ * blocks, added up where they are needed, 2: a scan of them over the blocks, 3: as 2 and a scan over the columns, 0: otherwise
+ * (host arithmetic, no GPU). */
+int fp4_residual_transpose_positions(int64_t P, int64_t Q);
+
 /* Whether a residual product S [P x Q] D [Q x N] of at most so many entries is one launch that gathers rows of D (1) or goes to the
  * kernels of large products (0), by the rule the launches follow (host arithmetic, no GPU).  channels: S is the transposed residual
  * of a weight gradient. */

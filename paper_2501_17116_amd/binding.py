@@ -95,6 +95,8 @@ def lib() -> C.CDLL:
         L.fp4_residual_spmm_bounded.argtypes = [vp, vp, vp, i64, i64, i64, vp, i32, i64, vp, vp, sz, vp]
         L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64, i32]
         L.fp4_residual_spmm_gathers.restype = i32
+        L.fp4_residual_transpose_positions.argtypes = [i64, i64]
+        L.fp4_residual_transpose_positions.restype = i32
         L.fp4_host_round_codes.argtypes = [vp, i64, vp]
         L.fp4_device_round_codes.argtypes = [vp, i64, vp, vp]
         L.fp4_device_round_sweep.argtypes = [vp, vp]
@@ -544,6 +546,11 @@ def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
     _check(getattr(lib(), name)(_ptr(row_ptr), _ptr(col_idx), _ptr(val), *capacity, P, Q, _ptr(D), _dt(D), N,
                                 _ptr(R), _ptr(w), w.numel(), _stream()), name)
     return R
+
+
+def fp4_residual_transpose_positions(P: int, Q: int) -> int:
+    """Where the places of a transposed residual's entries come from (host arithmetic, no GPU)."""
+    return int(lib().fp4_residual_transpose_positions(P, Q))
 
 
 def fp4_host_round_codes(x_host):

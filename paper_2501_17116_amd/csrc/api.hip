@@ -61,6 +61,7 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
                              hipStream_t s);
+int fp4_csr_transpose_from(int64_t P, int64_t Q);
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                              float* gamma, hipStream_t s);
 int fp8_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes_t,
@@ -697,3 +698,5 @@ extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* 
                                          void* workspace, size_t workspace_bytes, void* stream) {
   return residual_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, true);
 }
+
+extern "C" int fp4_residual_transpose_positions(int64_t P, int64_t Q) { return fp4_csr_transpose_from(P, Q); }

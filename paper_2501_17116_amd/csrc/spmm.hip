@@ -871,16 +871,18 @@ __global__ __launch_bounds__(256) void csr_mask_scan_kernel(const uint8_t* cnt8,
   for (; bi < b1; ++bi) { ex[(int64_t)bi * Q + c] = run; run += cnt8[(int64_t)bi * Q + c]; }
 }
 
-// Where pass 3 takes the positions from.  FEW: from the counts of all row blocks, at most MB_FEW_BYTES of them, which every
-// workgroup adds up for itself.  SCAN: from pass 2's ex and totals, which every workgroup scans over the columns.  Either way
+// Where pass 3 takes the positions from.  FEW: from the counts of all row blocks, at most MB_FEW_BYTES of them in MB_FEW_BLOCKS, which
+// every workgroup adds up for itself, sixteen blocks at a time: as many rows of counts take as many round trips however few the
+// columns are (fill alone, FEW / as SCAN with its launch before it, us: 16384 x 128 15 / 10, 65536 x 64 123 / 22, 131072 x 32 477 / 38; whole
+// weight gradients with 64 blocks 53.6 / 53.9, with 128 51.5 / 50.5).  SCAN: from pass 2's ex and totals, which every workgroup scans over the columns.  Either way
 // a column's position waits in LDS beside its mask, and the workgroup of the first row block writes t_ptr.  TABLE: with 2^32
 // elements or more positions have no room in 32 bits; t_ptr comes from a scan of its own.  Bound by round trips to memory, so by the
 // launches and by what a workgroup asks for one after another.
 // Whole transposition at 2 % (count, scan over blocks, scan over columns and fill as four launches / now): 256 x 512 12.3 / 8.2 us,
 // 1056 x 1376 at 6 % 28.7 / 19.3, 2048 x 2048 22.2 / 14.9, 8192 x 2048 25.0 / 19.3, 16384 x 4096 46.3 / 38.1,
 // 16384 x 11008 the fill alone (blocks of 64 rows, from a table / of 32) 156 / 98.
-enum class MbFrom { FEW, SCAN, TABLE };
-constexpr int64_t MB_FEW_BYTES = 64 * 1024;
+enum class MbFrom { FEW = 1, SCAN, TABLE };
+constexpr int64_t MB_FEW_BYTES = 64 * 1024, MB_FEW_BLOCKS = 64;
 
 template <int QMAX, MbFrom FROM>
 __global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t* row_ptr, const int32_t* col_idx,
@@ -1176,13 +1178,22 @@ int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
 }
 
 // u_idx/u_val: unordered staging, capacity entries each (only the path for very wide matrices uses it)
+static int64_t mb_blocks(int64_t P, int64_t Q) { return std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q)); }
+static bool mb_positions(int64_t P, int64_t Q) { return Q % 4 == 0 && P * Q < ((int64_t)1 << 32); }
+int fp4_csr_transpose_from(int64_t P, int64_t Q) {
+  if (Q > MB_MAXQ) return 0;   // no masks
+  if (!mb_positions(P, Q)) return (int)MbFrom::TABLE;
+  const int64_t blocks = mb_blocks(P, Q);
+  return (int)(blocks <= MB_FEW_BLOCKS && blocks * Q <= MB_FEW_BYTES ? MbFrom::FEW : MbFrom::SCAN);
+}
 int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
                              hipStream_t s) {
   int32_t* cnt = scratch;
   if (Q <= MB_MAXQ) {
-    const int nblocks = (int)std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q));
+    const MbFrom source = (MbFrom)fp4_csr_transpose_from(P, Q);
+    const int nblocks = (int)mb_blocks(P, Q);
     uint32_t* ex = reinterpret_cast<uint32_t*>(scratch + Q + 64);
     uint8_t* cnt8 = reinterpret_cast<uint8_t*>(ex + (int64_t)nblocks * Q);
     auto count = [&](auto qmax) {
@@ -1200,15 +1211,14 @@ int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, con
     using Scan = std::integral_constant<MbFrom, MbFrom::SCAN>;
     using Table = std::integral_constant<MbFrom, MbFrom::TABLE>;
     if (Q <= 4096) count(Q4{}); else if (Q <= 8192) count(Q8{}); else count(Q16{});
-    const bool positions = Q % 4 == 0 && P * Q < ((int64_t)1 << 32);
-    if (positions && nblocks * Q <= MB_FEW_BYTES) {
+    if (source == MbFrom::FEW) {
       if (Q <= 4096) fill(Q4{}, Few{}); else if (Q <= 8192) fill(Q8{}, Few{}); else fill(Q16{}, Few{});
       FP4_CHECK_LAUNCH();
       return FP4_OK;
     }
     hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0, s, cnt8, nblocks, Q, ex, cnt);
     FP4_CHECK_LAUNCH();
-    if (positions) {
+    if (source == MbFrom::SCAN) {
       if (Q <= 4096) fill(Q4{}, Scan{}); else if (Q <= 8192) fill(Q8{}, Scan{}); else fill(Q16{}, Scan{});
     } else {
       const int rc = fp4_launch_scan_rows(cnt, Q, t_ptr, nullptr, s);
