@@ -38,10 +38,15 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
-/* Where the places of the entries come from in the transpose that a weight gradient takes of its residual [P x Q]: 1: counts of all row
- * blocks, added up where they are needed, 2: a scan of them over the blocks, 3: as 2 and a scan over the columns, 0: otherwise
- * (host arithmetic, no GPU). */
+/* The transpose that a weight gradient takes of its residual [P x Q]: CSR of [Q x P], indices ascending in every row.  positions: where
+ * the entries' places come from, 1: counts of all row blocks, added up where they are needed, 2: a scan of them over the blocks,
+ * 3: as 2 and a scan over the columns, or 0: as the sizes have it, which fp4_residual_transpose_positions tells (host arithmetic, no
+ * GPU; 0 where there are more than 16384 columns and none of these is used).  1 and 2 need Q % 4 == 0 and P Q < 2^32.  At most
+ * fp4_occ_capacity(P, Q, 0.9) entries.  Workspace: fp4_workspace_bytes(FP4_OP_WGRAD, P, Q, 32, FP4_F32). */
 int fp4_residual_transpose_positions(int64_t P, int64_t Q);
+int fp4_residual_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val, const int64_t* nnz, int64_t P, int64_t Q,
+                           int64_t capacity, int positions, int64_t* t_ptr, int32_t* t_idx, float* t_val, void* workspace,
+                           size_t workspace_bytes, void* stream);
 
 /* Whether a residual product S [P x Q] D [Q x N] of at most so many entries is one launch that gathers rows of D (1) or goes to the
  * kernels of large products (0), by the rule the launches follow (host arithmetic, no GPU).  channels: S is the transposed residual

@@ -97,6 +97,8 @@ def lib() -> C.CDLL:
         L.fp4_residual_spmm_gathers.restype = i32
         L.fp4_residual_transpose_positions.argtypes = [i64, i64]
         L.fp4_residual_transpose_positions.restype = i32
+        L.fp4_residual_transpose.argtypes = [vp, vp, vp, vp, i64, i64, i64, i32, vp, vp, vp, vp, sz, vp]
+        L.fp4_residual_transpose.restype = i32
         L.fp4_host_round_codes.argtypes = [vp, i64, vp]
         L.fp4_device_round_codes.argtypes = [vp, i64, vp, vp]
         L.fp4_device_round_sweep.argtypes = [vp, vp]
@@ -551,6 +553,19 @@ def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
 def fp4_residual_transpose_positions(P: int, Q: int) -> int:
     """Where the places of a transposed residual's entries come from (host arithmetic, no GPU)."""
     return int(lib().fp4_residual_transpose_positions(P, Q))
+
+
+def fp4_residual_transpose(row_ptr: torch.Tensor, col_idx: torch.Tensor, val: torch.Tensor, nnz: torch.Tensor, Q: int,
+                           positions: int = 0, ws: Optional[Workspace] = None) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
+    """CSR of the transpose as a weight gradient takes it; col_idx and val have room for what row_ptr counts."""
+    _dev_check(row_ptr, col_idx, val, nnz)
+    P = row_ptr.numel() - 1
+    t_ptr = torch.empty(Q + 1, dtype=torch.int64, device=val.device)
+    t_idx, t_val = torch.empty_like(col_idx), torch.empty_like(val)
+    w = _ws(workspace_bytes(FP4_OP_WGRAD, P, Q, 32, FP4_F32), ws)
+    _check(lib().fp4_residual_transpose(_ptr(row_ptr), _ptr(col_idx), _ptr(val), _ptr(nnz), P, Q, col_idx.numel(), positions, _ptr(t_ptr),
+                                        _ptr(t_idx), _ptr(t_val), _ptr(w), w.numel(), _stream()), "fp4_residual_transpose")
+    return t_ptr, t_idx, t_val
 
 
 def fp4_host_round_codes(x_host):

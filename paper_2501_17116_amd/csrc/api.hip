@@ -60,7 +60,7 @@ int fp4_launch_csr_gather(const int32_t* tmp_col, const float* tmp_val, int64_t 
 int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
-                             hipStream_t s);
+                             hipStream_t s, int from = 0);
 int fp4_csr_transpose_from(int64_t P, int64_t Q);
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
                              float* gamma, hipStream_t s);
@@ -700,3 +700,18 @@ extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* 
 }
 
 extern "C" int fp4_residual_transpose_positions(int64_t P, int64_t Q) { return fp4_csr_transpose_from(P, Q); }
+
+extern "C" int fp4_residual_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val, const int64_t* nnz, int64_t P, int64_t Q,
+                                      int64_t capacity, int positions, int64_t* t_ptr, int32_t* t_idx, float* t_val, void* workspace,
+                                      size_t workspace_bytes, void* stream) {
+  if (P <= 0 || Q <= 0) return FP4_ERR_SHAPE;
+  if (!row_ptr || !col_idx || !val || !nnz || !t_ptr || !t_idx || !t_val) return FP4_ERR_NULL;
+  if (positions < 0 || positions > 3 || (positions && fp4_csr_transpose_from(P, Q) == 0)) return FP4_ERR_ARG;
+  const int64_t provided = provisioned_entries(P, Q);
+  if (capacity < 0 || capacity > provided) return FP4_ERR_CAPACITY;
+  if (!workspace || workspace_bytes < fp4_workspace_bytes(FP4_OP_WGRAD, P, Q, 32, FP4_F32)) return FP4_ERR_WORKSPACE;
+  Carver c(reinterpret_cast<void*>(align_up((size_t)(uintptr_t)workspace, 256)));
+  const WgradWs w = carve_wgrad(c, P, Q, 32, FP4_F32);
+  return fp4_launch_csr_transpose(row_ptr, col_idx, val, nnz, P, Q, capacity, t_ptr, t_idx, t_val, w.u_idx, w.u_val, w.t_scratch,
+                                  (hipStream_t)stream, positions);
+}

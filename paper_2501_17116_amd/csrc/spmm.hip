@@ -1178,6 +1178,7 @@ int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
 }
 
 // u_idx/u_val: unordered staging, capacity entries each (only the path for very wide matrices uses it)
+// from: a MbFrom, or 0 for that of the sizes
 static int64_t mb_blocks(int64_t P, int64_t Q) { return std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q)); }
 static bool mb_positions(int64_t P, int64_t Q) { return Q % 4 == 0 && P * Q < ((int64_t)1 << 32); }
 int fp4_csr_transpose_from(int64_t P, int64_t Q) {
@@ -1189,10 +1190,11 @@ int fp4_csr_transpose_from(int64_t P, int64_t Q) {
 int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
-                             hipStream_t s) {
+                             hipStream_t s, int from) {
   int32_t* cnt = scratch;
   if (Q <= MB_MAXQ) {
-    const MbFrom source = (MbFrom)fp4_csr_transpose_from(P, Q);
+    const MbFrom source = (MbFrom)(from ? from : fp4_csr_transpose_from(P, Q));
+    if (source != MbFrom::TABLE && !mb_positions(P, Q)) return FP4_ERR_ARG;
     const int nblocks = (int)mb_blocks(P, Q);
     uint32_t* ex = reinterpret_cast<uint32_t*>(scratch + Q + 64);
     uint8_t* cnt8 = reinterpret_cast<uint8_t*>(ex + (int64_t)nblocks * Q);
