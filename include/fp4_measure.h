@@ -38,6 +38,11 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
+/* Which passes find the thresholds of a [rows x cols] tensor and count its rows' outliers (host arithmetic, no GPU). */
+#define FP4_SELECT_WINDOWS 1   /* one pass over the elements with bins for the keys around the thresholds, otherwise digit passes alone */
+#define FP4_SELECT_SAMPLE 2    /* the windows lie where a sample says, otherwise where a first digit pass does */
+int fp4_select_route(int64_t rows, int64_t cols, int64_t ld, fp4_dtype dt);
+
 /* The transpose that a weight gradient takes of its residual [P x Q]: CSR of [Q x P], indices ascending in every row.  positions: where
  * the entries' places come from, 1: counts of all row blocks, added up where they are needed, 2: a scan of them over the blocks,
  * 3: as 2 and a scan over the columns, or 0: as the sizes have it, which fp4_residual_transpose_positions tells (host arithmetic, no

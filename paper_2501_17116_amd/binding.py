@@ -95,6 +95,8 @@ def lib() -> C.CDLL:
         L.fp4_residual_spmm_bounded.argtypes = [vp, vp, vp, i64, i64, i64, vp, i32, i64, vp, vp, sz, vp]
         L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64, i32]
         L.fp4_residual_spmm_gathers.restype = i32
+        L.fp4_select_route.argtypes = [i64, i64, i64, i32]
+        L.fp4_select_route.restype = i32
         L.fp4_residual_transpose_positions.argtypes = [i64, i64]
         L.fp4_residual_transpose_positions.restype = i32
         L.fp4_residual_transpose.argtypes = [vp, vp, vp, vp, i64, i64, i64, i32, vp, vp, vp, vp, sz, vp]
@@ -548,6 +550,14 @@ def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
     _check(getattr(lib(), name)(_ptr(row_ptr), _ptr(col_idx), _ptr(val), *capacity, P, Q, _ptr(D), _dt(D), N,
                                 _ptr(R), _ptr(w), w.numel(), _stream()), name)
     return R
+
+
+FP4_SELECT_WINDOWS, FP4_SELECT_SAMPLE = 1, 2
+
+
+def fp4_select_route(rows: int, cols: int, dt: int, ld: Optional[int] = None) -> int:
+    """Which passes find a tensor's thresholds (host arithmetic, no GPU)."""
+    return int(lib().fp4_select_route(rows, cols, cols if ld is None else ld, dt))
 
 
 def fp4_residual_transpose_positions(P: int, Q: int) -> int:

@@ -50,6 +50,7 @@ int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const 
 int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols);
 size_t fp4_select_scratch_bytes();
 int64_t fp4_select_clear_words();
+int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t rows_scratch_words);
 int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t n, hipStream_t s);
 int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
                                      void* scratch, void* rows_scratch, int64_t rows_scratch_words, int32_t* row_cnt, int32_t* row_sum,
@@ -697,6 +698,10 @@ extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* 
                                          int64_t P, int64_t Q, const void* D, fp4_dtype dt, int64_t N, float* R,
                                          void* workspace, size_t workspace_bytes, void* stream) {
   return residual_spmm(row_ptr, col_idx, val, INT64_MAX, P, Q, D, dt, N, R, workspace, workspace_bytes, stream, true);
+}
+
+extern "C" int fp4_select_route(int64_t rows, int64_t cols, int64_t ld, fp4_dtype dt) {
+  return fp4_select_passes(dt == FP4_BF16, rows, cols, ld, provisioned_entries(rows, cols));
 }
 
 extern "C" int fp4_residual_transpose_positions(int64_t P, int64_t Q) { return fp4_csr_transpose_from(P, Q); }

@@ -3,6 +3,7 @@
 // CSR.  (The clamp itself is fused into the quantization pass; the transpose for the weight
 // gradient and the sparse x dense product live with the sparse kernels.)
 #include "fp4_common.h"
+#include "fp4_measure.h"
 
 #include <algorithm>
 #include <cstddef>
@@ -716,6 +717,25 @@ int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t
   return FP4_OK;
 }
 
+// Which passes find the thresholds: bits of fp4_select_route (fp4_measure.h).
+//
+// The pass with windows has a wave a row and sixteen rows a workgroup, so few long rows leave most of the chip without one, and where zeros are
+// counted apart (rectified tensors, whose lower threshold is zero) it takes half as long again; digit passes spread over the chip whatever
+// the shape.  Clamp alone in us, N(0, 1) and rectified, windows / digits, and what both took when the digits' bins were picked in launches of their
+// own: 64 x 2048 24 and 31 / 24 and 26, 31 and 34; 64 x 13824 42 and 59 / 39 and 41, 47 and 49; 256 x 8192 37 and 49 / 42 and 44, 47 and 49; 256 x
+// 13824 47 and 63 / 49 and 51, 54 and 56; 1024 x 28672 106 and 150 / 121 and 159, 125 and 160.  From 2^25 elements on the sample takes a digit pass's
+// place (16384 x 4096 above).
+constexpr int64_t WIN_COLS_PER_ROW = 32;
+int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t rows_scratch_words) {
+  const int64_t n = rows * cols;
+  int route = 0;
+  if (bf16 && ld == cols && cols % 8 == 0 && cols <= 65535 && n < ((int64_t)1 << 32) && rows * WIN_STRIDE <= 2 * rows_scratch_words) {
+    if (n >= ((int64_t)1 << 25)) route |= FP4_SELECT_SAMPLE | FP4_SELECT_WINDOWS;
+    else if (cols <= WIN_COLS_PER_ROW * rows) route |= FP4_SELECT_WINDOWS;
+  }
+  return route;
+}
+
 // Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1], then the outliers of each row (row_cnt) and
 // of each block of 4 << shift rows (row_sum).  scratch: fp4_select_scratch_bytes(), cleared.  rows_scratch: words that are free until
 // the rows' entries are emitted.
@@ -737,7 +757,8 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
   using First = std::integral_constant<int, 0>;
   using Second = std::integral_constant<int, 1>;
   using Third = std::integral_constant<int, 2>;
-  if (bf16 && ld == cols && cols % 8 == 0 && cols <= 65535 && n < ((int64_t)1 << 32) && rows * WIN_STRIDE <= 2 * rows_scratch_words) {
+  const int route = fp4_select_passes(bf16, rows, cols, ld, rows_scratch_words);
+  if (route & FP4_SELECT_WINDOWS) {
     uint16_t* const bins = reinterpret_cast<uint16_t*>(rows_scratch);
     const uint16_t* const xp = reinterpret_cast<const uint16_t*>(x);
     auto window = [&](const Ranks& r, const unsigned long long* digits) {
@@ -748,7 +769,7 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
       hipLaunchKernelGGL((win_rows_kernel<decltype(exact)::value>), dim3(count_grid), dim3(256), 0, s, xp, rows, cols, ranks, st, hist, bins,
                          thresholds, out);
     };
-    if (n >= ((int64_t)1 << 25)) {
+    if (route & FP4_SELECT_SAMPLE) {
       const int64_t ns = (int64_t)SAMPLE_RUNS * 64 * 8;
       const unsigned long long ks = (unsigned long long)((double)k / (double)n * (double)ns);
       hipLaunchKernelGGL(sel_sample_kernel, dim3(SAMPLE_BLOCKS), dim3(SEL_THREADS), 0, s, reinterpret_cast<const u32x4*>(x), n / 8, hist);

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("what", ["normal", "relu", "masked", "relu_neg", "sparse", "one value", "two values", "row scales"])
-@pytest.mark.parametrize("rows,cols,alpha", [(1, 504, 0.99), (64, 2048, 0.99), (1056, 1376, 0.97), (2049, 1032, 0.999)])
+@pytest.mark.parametrize("rows,cols,alpha", [(1, 504, 0.99), (16, 504, 0.99), (64, 2048, 0.99), (1056, 1376, 0.97), (2049, 1032, 0.999)])
 def test_windows_behind_an_exact_digit(rows, cols, alpha, what):
     g = torch.Generator(device="cuda").manual_seed(rows)
     x = _one_sided(what, rows, cols, alpha, g)

@@ -1,0 +1,26 @@
+"""Which passes find the clamp's thresholds (csrc/occ.hip), on the CPU."""
+import pytest
+
+from paper_2501_17116_amd import binding as b
+
+BF16, F32 = b.FP4_BF16, b.FP4_F32
+
+
+@pytest.mark.parametrize("rows,cols,windows", [
+    (64, 2048, True), (64, 2056, False), (1056, 1376, True), (2049, 1032, True), (8192, 2048, True), (1024, 28672, True), (512, 13824, True),
+    (256, 8192, True), (504, 504, True), (16, 504, True),
+    # few long rows: a wave a row would leave most of the chip idle
+    (1, 504, False), (1, 16384, False), (16, 16384, False), (32, 28672, False), (64, 13824, False), (128, 13824, False), (256, 13824, False),
+    (480, 65504, False),
+    # rows whose bins have no room, or that are not whole 16-byte words
+    (8192, 496, False), (8192, 64, False), (8192, 508, False),
+])
+def test_windows_behind_a_digit(rows, cols, windows):
+    assert b.fp4_select_route(rows, cols, BF16) & 3 == (b.FP4_SELECT_WINDOWS if windows else 0)
+    assert b.fp4_select_route(rows, cols, F32) & 3 == 0
+    assert b.fp4_select_route(rows, cols, BF16, ld=cols + 8) & 3 == 0
+
+
+@pytest.mark.parametrize("rows,cols", [(16384, 4096), (16384, 11008), (4096, 8192), (1024, 65504), (66600, 504)])
+def test_windows_behind_a_sample(rows, cols):
+    assert b.fp4_select_route(rows, cols, BF16) & 3 == b.FP4_SELECT_WINDOWS | b.FP4_SELECT_SAMPLE
