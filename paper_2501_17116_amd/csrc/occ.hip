@@ -24,7 +24,11 @@ constexpr int SEL_THREADS = 1024;   // per workgroup: the 64 KiB of LDS tables a
 //
 // The bins that hold the two ranks are found by whoever needs them next: every workgroup of the next digit's pass, and of the
 // count behind the last, scans them again while its first elements are on their way: 2 to 3 us, where a launch of one workgroup took
-// 4.5 and its gap.  So each digit has bins of its own in memory, all cleared before the first.
+// 4.5 and its gap.  So each digit has bins of its own in memory, all cleared before the first.  The count behind bf16's second digit
+// does so with up to SEL_FIND_BLOCKS workgroups only: its 64 bins lie in four lines, and a thousand workgroups that ask for them at once take
+// 20 us (clamp alone of 64 / 128 / 256 / 1024 / 8192 rows of 64, found by the count 20.6 / 22.9 / 25.2 / 34.1 / 43.7 us, in a launch of its own 21.0 /
+// 21.8 / 22.0 / 22.2 / 31.7).  fp32's 1024 bins a threshold lie in many: 1024 rows of 64 27.3 / 28.1, 8192 of 2048 94.3 / 93.1, 16384 of 2048 145.6 / 147.8.
+constexpr unsigned SEL_FIND_BLOCKS = 16;
 constexpr int SEL_AT[3] = {0, SEL_BINS, 3 * SEL_BINS};      // where a digit's bins begin (the first's are shared by both targets)
 constexpr int SEL_APART[3] = {0, SEL_BINS, SEL_BINS / 2};   // from one target's bins to the other's
 constexpr int SEL_WORDS = 4 * SEL_BINS;
@@ -545,10 +549,20 @@ FP4_D void find_thresholds(SelState* st, const unsigned long long* hist, const R
   if (blockIdx.x == 0 && threadIdx.x < 2) thresholds[threadIdx.x] = thr[threadIdx.x];
 }
 
-template <class DT>
+// FOUND: sel_pick_kernel has found the thresholds.
+template <class DT, bool FOUND>
 __global__ __launch_bounds__(256) void sel_count_kernel(const void* x, int64_t rows, int64_t cols, int64_t ld, Ranks ranks, SelState* st,
                                                         const unsigned long long* hist, float* thresholds, RowCounts out) {
-  count_rows<DT>(x, rows, cols, ld, out, [&](float (&thr)[2]) { find_thresholds<DT>(st, hist, ranks, thresholds, thr); });
+  count_rows<DT>(x, rows, cols, ld, out, [&](float (&thr)[2]) {
+    if constexpr (FOUND) { thr[0] = thresholds[0]; thr[1] = thresholds[1]; }
+    else find_thresholds<DT>(st, hist, ranks, thresholds, thr);
+  });
+}
+
+template <class DT>
+__global__ __launch_bounds__(256) void sel_pick_kernel(SelState* st, const unsigned long long* hist, Ranks ranks, float* thresholds) {
+  float thr[2];
+  find_thresholds<DT>(st, hist, ranks, thresholds, thr);
 }
 
 __global__ __launch_bounds__(256) void sel_clear_kernel(unsigned long long* clear, const float* src, float* dst, int64_t n) {
@@ -704,6 +718,7 @@ __global__ __launch_bounds__(256) void csr_gather_kernel(const int32_t* tmp_col,
 }  // namespace
 
 // ---- internal launchers -----------------------------------------------------------------------
+int fp4_row_sum_shift(int64_t rows);
 size_t fp4_select_scratch_bytes() { return SEL_CLEAR * 8; }
 int64_t fp4_select_clear_words() { return SEL_CLEAR; }
 
@@ -726,6 +741,7 @@ int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t
 // 13824 47 and 63 / 49 and 51, 54 and 56; 1024 x 28672 106 and 150 / 121 and 159, 125 and 160.  From 2^25 elements on the sample takes a digit pass's
 // place (16384 x 4096 above).
 constexpr int64_t WIN_COLS_PER_ROW = 32;
+static unsigned count_blocks(int64_t rows, int shift) { return (unsigned)((rows + (4 << shift) - 1) / (4 << shift)); }
 int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t rows_scratch_words) {
   const int64_t n = rows * cols;
   int route = 0;
@@ -733,6 +749,7 @@ int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t 
     if (n >= ((int64_t)1 << 25)) route |= FP4_SELECT_SAMPLE | FP4_SELECT_WINDOWS;
     else if (cols <= WIN_COLS_PER_ROW * rows) route |= FP4_SELECT_WINDOWS;
   }
+  if (bf16 && !route && count_blocks(rows, fp4_row_sum_shift(rows)) > SEL_FIND_BLOCKS) route |= FP4_SELECT_FOUND;
   return route;
 }
 
@@ -747,7 +764,7 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
   const int64_t n = rows * cols;
   const Ranks ranks = {{(unsigned long long)k, (unsigned long long)(n - 1 - k)}};
   const RowCounts out = {row_cnt, row_sum, shift};
-  const unsigned count_grid = (unsigned)((rows + (4 << shift) - 1) / (4 << shift));
+  const unsigned count_grid = count_blocks(rows, shift);
   const int64_t few = std::min<int64_t>((n + 8191) / 8192, 256), many = std::min<int64_t>((n + 65535) / 65536, 512);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::max(few, many));
   auto digit = [&](auto dt, auto pass, auto behind) {
@@ -785,12 +802,17 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
   } else if (bf16) {
     digit(BF16{}, First{}, std::false_type{});
     digit(BF16{}, Second{}, std::false_type{});
-    hipLaunchKernelGGL((sel_count_kernel<BF16>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    if (route & FP4_SELECT_FOUND) {
+      hipLaunchKernelGGL((sel_pick_kernel<BF16>), dim3(1), dim3(256), 0, s, st, hist, ranks, thresholds);
+      hipLaunchKernelGGL((sel_count_kernel<BF16, true>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    } else {
+      hipLaunchKernelGGL((sel_count_kernel<BF16, false>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    }
   } else {
     digit(F32{}, First{}, std::false_type{});
     digit(F32{}, Second{}, std::false_type{});
     digit(F32{}, Third{}, std::false_type{});
-    hipLaunchKernelGGL((sel_count_kernel<F32>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    hipLaunchKernelGGL((sel_count_kernel<F32, false>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
   }
   FP4_CHECK_LAUNCH();
   return FP4_OK;

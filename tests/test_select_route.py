@@ -24,3 +24,11 @@ def test_windows_behind_a_digit(rows, cols, windows):
 @pytest.mark.parametrize("rows,cols", [(16384, 4096), (16384, 11008), (4096, 8192), (1024, 65504), (66600, 504)])
 def test_windows_behind_a_sample(rows, cols):
     assert b.fp4_select_route(rows, cols, BF16) & 3 == b.FP4_SELECT_WINDOWS | b.FP4_SELECT_SAMPLE
+
+
+@pytest.mark.parametrize("rows,cols,found", [(64, 64, False), (65, 64, True), (64, 13824, False), (128, 13824, True), (4096, 64, True), (8192, 256, True),
+                                             (262144, 32, True), (8192, 2048, False), (16384, 4096, False)])
+def test_thresholds_in_a_launch_of_their_own(rows, cols, found):
+    """Where more than a few workgroups count the rows behind a bf16 tensor's second digit."""
+    assert bool(b.fp4_select_route(rows, cols, BF16) & b.FP4_SELECT_FOUND) == found
+    assert not b.fp4_select_route(rows, cols, F32) & b.FP4_SELECT_FOUND
