@@ -42,6 +42,7 @@ int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, in
 #define FP4_SELECT_WINDOWS 1   /* one pass over the elements with bins for the keys around the thresholds, otherwise digit passes alone */
 #define FP4_SELECT_SAMPLE 2    /* the windows lie where a sample says, otherwise where a first digit pass does */
 #define FP4_SELECT_FOUND 4     /* the thresholds are found in a launch of their own, otherwise by every workgroup that counts */
+#define FP4_SELECT_APART 8     /* rows are counted each by itself, without sums of blocks of them */
 int fp4_select_route(int64_t rows, int64_t cols, int64_t ld, fp4_dtype dt);
 
 /* The transpose that a weight gradient takes of its residual [P x Q]: CSR of [Q x P], indices ascending in every row.  positions: where

@@ -552,7 +552,7 @@ def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
     return R
 
 
-FP4_SELECT_WINDOWS, FP4_SELECT_SAMPLE, FP4_SELECT_FOUND = 1, 2, 4
+FP4_SELECT_WINDOWS, FP4_SELECT_SAMPLE, FP4_SELECT_FOUND, FP4_SELECT_APART = 1, 2, 4, 8
 
 
 def fp4_select_route(rows: int, cols: int, dt: int, ld: Optional[int] = None) -> int:

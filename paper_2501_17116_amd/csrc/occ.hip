@@ -511,11 +511,15 @@ FP4_D void count_rows(const void* x, int64_t rows, int64_t cols, int64_t ld, con
     const int64_t unit = (int64_t)step * 256 + q * 64 + lane;
     return unit < nunits ? (int)min((int64_t)8, cols - unit * 8) : 0;
   };
+  // whether a lane has anything of the wave's q-th units: a branch that all take, where a short row's three absent units of four cost
+  // as much as the one it has (clamp alone, 32768 x 64 bf16 71.5 -> 62.0 us, 65536 x 64 111 -> 93)
+  auto is_there = [&](int step, int q) { return (int64_t)step * 256 + q * 64 < nunits; };
   Unit<DT> u[4];
   auto fetch = [&](int row, int step) {
     if (row >= nrows) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) load_unit<DT>(x, (row0 + row) * ld + ((int64_t)step * 256 + q * 64 + lane) * 8, valid_of(step, q), u[q]);
+    for (int q = 0; q < 4; ++q)
+      if (is_there(step, q)) load_unit<DT>(x, (row0 + row) * ld + ((int64_t)step * 256 + q * 64 + lane) * 8, valid_of(step, q), u[q]);
   };
   fetch(0, 0);
   float thr[2];
@@ -528,7 +532,8 @@ FP4_D void count_rows(const void* x, int64_t rows, int64_t cols, int64_t ld, con
       if (step + 1 < steps) fetch(row, step + 1);
       else fetch(row + 1, 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) cnt += count_unit<DT>(c[q], valid_of(step, q), thr[0], thr[1]);
+      for (int q = 0; q < 4; ++q)
+        if (is_there(step, q)) cnt += count_unit<DT>(c[q], valid_of(step, q), thr[0], thr[1]);
     }
     cnt = wave_sum(cnt);
     if (lane == 0) out.cnt[row0 + row] = cnt;
@@ -557,6 +562,26 @@ __global__ __launch_bounds__(256) void sel_count_kernel(const void* x, int64_t r
     if constexpr (FOUND) { thr[0] = thresholds[0]; thr[1] = thresholds[1]; }
     else find_thresholds<DT>(st, hist, ranks, thresholds, thr);
   });
+}
+
+// More rows than have their sums taken: a wave a row, nothing more (131072 x 64 bf16 25 us, with eight rows
+// a wave and their sums, which nothing reads, 91).
+template <class DT>
+__global__ __launch_bounds__(256) void sel_count_apart_kernel(const void* x, int64_t rows, int64_t cols, int64_t ld, const float* thresholds,
+                                                              int32_t* row_cnt) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const float lo = thresholds[0], hi = thresholds[1];
+  int cnt = 0;
+  for (int64_t unit = lane; unit < (cols + 7) / 8; unit += 64) {
+    const int valid = (int)min((int64_t)8, cols - unit * 8);
+    Unit<DT> u;
+    load_unit<DT>(x, row * ld + unit * 8, valid, u);
+    cnt += count_unit<DT>(u, valid, lo, hi);
+  }
+  cnt = wave_sum(cnt);
+  if (lane == 0) row_cnt[row] = cnt;
 }
 
 template <class DT>
@@ -719,6 +744,7 @@ __global__ __launch_bounds__(256) void csr_gather_kernel(const int32_t* tmp_col,
 
 // ---- internal launchers -----------------------------------------------------------------------
 int fp4_row_sum_shift(int64_t rows);
+int64_t fp4_row_sum_most();
 size_t fp4_select_scratch_bytes() { return SEL_CLEAR * 8; }
 int64_t fp4_select_clear_words() { return SEL_CLEAR; }
 
@@ -749,12 +775,13 @@ int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t 
     if (n >= ((int64_t)1 << 25)) route |= FP4_SELECT_SAMPLE | FP4_SELECT_WINDOWS;
     else if (cols <= WIN_COLS_PER_ROW * rows) route |= FP4_SELECT_WINDOWS;
   }
+  if (!route && rows > fp4_row_sum_most()) route |= FP4_SELECT_FOUND | FP4_SELECT_APART;
   if (bf16 && !route && count_blocks(rows, fp4_row_sum_shift(rows)) > SEL_FIND_BLOCKS) route |= FP4_SELECT_FOUND;
   return route;
 }
 
 // Thresholds lo = v[k], hi = v[n-1-k] of the ascending-sorted tensor into thresholds[0..1], then the outliers of each row (row_cnt) and
-// of each block of 4 << shift rows (row_sum).  scratch: fp4_select_scratch_bytes(), cleared.  rows_scratch: words that are free until
+// of each block of 4 << shift rows (row_sum; up to fp4_row_sum_most() rows).  scratch: fp4_select_scratch_bytes(), cleared.  rows_scratch: words that are free until
 // the rows' entries are emitted.
 int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
                                      void* scratch, void* rows_scratch, int64_t rows_scratch_words, int32_t* row_cnt, int32_t* row_sum,
@@ -799,20 +826,27 @@ int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int6
       window(ranks, hist + SEL_AT[0]);
       counts(std::true_type{});
     }
-  } else if (bf16) {
-    digit(BF16{}, First{}, std::false_type{});
-    digit(BF16{}, Second{}, std::false_type{});
-    if (route & FP4_SELECT_FOUND) {
-      hipLaunchKernelGGL((sel_pick_kernel<BF16>), dim3(1), dim3(256), 0, s, st, hist, ranks, thresholds);
-      hipLaunchKernelGGL((sel_count_kernel<BF16, true>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
-    } else {
-      hipLaunchKernelGGL((sel_count_kernel<BF16, false>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
-    }
   } else {
-    digit(F32{}, First{}, std::false_type{});
-    digit(F32{}, Second{}, std::false_type{});
-    digit(F32{}, Third{}, std::false_type{});
-    hipLaunchKernelGGL((sel_count_kernel<F32, false>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    auto count = [&](auto dt) {
+      using DT = decltype(dt);
+      if (route & FP4_SELECT_FOUND) hipLaunchKernelGGL((sel_pick_kernel<DT>), dim3(1), dim3(256), 0, s, st, hist, ranks, thresholds);
+      if (route & FP4_SELECT_APART)
+        hipLaunchKernelGGL((sel_count_apart_kernel<DT>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, x, rows, cols, ld, thresholds, row_cnt);
+      else if (route & FP4_SELECT_FOUND)
+        hipLaunchKernelGGL((sel_count_kernel<DT, true>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+      else
+        hipLaunchKernelGGL((sel_count_kernel<DT, false>), dim3(count_grid), dim3(256), 0, s, x, rows, cols, ld, ranks, st, hist, thresholds, out);
+    };
+    if (bf16) {
+      digit(BF16{}, First{}, std::false_type{});
+      digit(BF16{}, Second{}, std::false_type{});
+      count(BF16{});
+    } else {
+      digit(F32{}, First{}, std::false_type{});
+      digit(F32{}, Second{}, std::false_type{});
+      digit(F32{}, Third{}, std::false_type{});
+      count(F32{});
+    }
   }
   FP4_CHECK_LAUNCH();
   return FP4_OK;

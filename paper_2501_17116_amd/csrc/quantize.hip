@@ -1569,6 +1569,7 @@ int fp4_row_sum_shift(int64_t rows) {
   while (shift < 3 && rows > ((int64_t)SUM_BLOCKS << (2 + shift))) ++shift;
   return shift;
 }
+int64_t fp4_row_sum_most() { return (int64_t)SUM_BLOCKS << 5; }
 // int32 words for the sums: whole 16-byte words
 int64_t fp4_row_sum_words(int64_t rows) { return (rows + 15) / 16 * 4; }   // for shift 0, the most of them
 
@@ -1593,7 +1594,7 @@ int fp4_launch_occ_rows(const void* x, int bf16, int64_t rows, int64_t cols, int
   // 16384 x 11008 156 -> 171 us against a scan of 5.1; 8192 x 2048 18.0 -> 21.6 and 4.9, 1056 x
   // 1376 7.6 -> 8.5 and 3.5, 16384 x 4096 61.6 -> 62.9 and 5.1, each with a gap between launches.
   const bool cheap = cols <= 4096 || rows <= 2048;
-  if (ordered && cheap && cols % 8 == 0 && rows <= ((int64_t)SUM_BLOCKS << (2 + a.sum_shift)) && rows * cols < ((int64_t)1 << 32)) {
+  if (ordered && cheap && cols % 8 == 0 && rows <= fp4_row_sum_most() && rows * cols < ((int64_t)1 << 32)) {
     a.row_cnt = row_cnt; a.row_sum = row_sum; a.ptr_out = row_ptr; a.nnz_out = nnz;
   } else {
     const int rc = fp4_launch_scan_rows(row_cnt, rows, row_ptr, nnz, s);

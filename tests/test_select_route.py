@@ -31,4 +31,14 @@ def test_windows_behind_a_sample(rows, cols):
 def test_thresholds_in_a_launch_of_their_own(rows, cols, found):
     """Where more than a few workgroups count the rows behind a bf16 tensor's second digit."""
     assert bool(b.fp4_select_route(rows, cols, BF16) & b.FP4_SELECT_FOUND) == found
-    assert not b.fp4_select_route(rows, cols, F32) & b.FP4_SELECT_FOUND
+    if rows <= 65536:
+        assert not b.fp4_select_route(rows, cols, F32) & b.FP4_SELECT_FOUND
+
+
+@pytest.mark.parametrize("dt", [BF16, F32])
+def test_rows_counted_by_themselves(dt):
+    """Where the emitting kernel has no use for sums of blocks of rows, the count does not take eight rows a wave for them."""
+    both = b.FP4_SELECT_FOUND | b.FP4_SELECT_APART
+    for rows, cols in ((65537, 64), (131072, 32), (262144, 256)):
+        assert b.fp4_select_route(rows, cols, dt) == both
+    assert not b.fp4_select_route(65536, 64, dt) & b.FP4_SELECT_APART
