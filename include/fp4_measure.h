@@ -38,6 +38,10 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
+/* Whether the tiles of one tensor's column-wise quantization form their scales themselves (1) or a launch before them does (0)
+ * (host arithmetic, no GPU). */
+int fp4_quantize_cols_folds(int64_t rows, int64_t cols);
+
 /* Which passes find the thresholds of a [rows x cols] tensor and count its rows' outliers (host arithmetic, no GPU). */
 #define FP4_SELECT_WINDOWS 1   /* one pass over the elements with bins for the keys around the thresholds, otherwise digit passes alone */
 #define FP4_SELECT_SAMPLE 2    /* the windows lie where a sample says, otherwise where a first digit pass does */

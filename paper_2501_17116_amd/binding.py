@@ -95,6 +95,8 @@ def lib() -> C.CDLL:
         L.fp4_residual_spmm_bounded.argtypes = [vp, vp, vp, i64, i64, i64, vp, i32, i64, vp, vp, sz, vp]
         L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64, i32]
         L.fp4_residual_spmm_gathers.restype = i32
+        L.fp4_quantize_cols_folds.argtypes = [i64, i64]
+        L.fp4_quantize_cols_folds.restype = i32
         L.fp4_select_route.argtypes = [i64, i64, i64, i32]
         L.fp4_select_route.restype = i32
         L.fp4_residual_transpose_positions.argtypes = [i64, i64]
@@ -550,6 +552,11 @@ def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):
     _check(getattr(lib(), name)(_ptr(row_ptr), _ptr(col_idx), _ptr(val), *capacity, P, Q, _ptr(D), _dt(D), N,
                                 _ptr(R), _ptr(w), w.numel(), _stream()), name)
     return R
+
+
+def fp4_quantize_cols_folds(rows: int, cols: int) -> bool:
+    """Whether the tiles of a tensor's column-wise quantization form their scales themselves (host arithmetic, no GPU)."""
+    return bool(lib().fp4_quantize_cols_folds(rows, cols))
 
 
 FP4_SELECT_WINDOWS, FP4_SELECT_SAMPLE, FP4_SELECT_FOUND, FP4_SELECT_APART = 1, 2, 4, 8

@@ -1084,17 +1084,25 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a, ColArgs b
 // a launch for the scales before it / without, for both tensors of a weight gradient: 1056 x (1376 + 2080) 12.8 / 9.0 (3 and 6 MB), 8192 x
 // (2048 + 2048) 31.8 / 26.8 (34 and 134); with only the second's apart 4096 x (5120 + 13824) 49.4 / 58.5 (226 MB for that one), 16384 x
 // (4096 + 12288) 154.9 / 168.0 (805).
-inline bool fold_in_tiles(const ColArgs& a, int parts, int bytes) {
-  return (a.rows + CT_ROWS - 1) / CT_ROWS * a.cols * parts * bytes <= (int64_t)128 << 20;
+//
+// A tensor by itself has one such launch, and its tiles, beyond six a CU, come after one another, each with a fold's round trips before its
+// codes: there the line lies, unless the columns are so few that the launch takes longer (a thread a column walks all partial maxima).  In us,
+// both passes, with the launch / folded: bf16 2048 x 2048 13 / 11, 8192 x 2048 (1024 tiles) 27 / 24, 12288 x 2048 (1536) 34 / 35, 8192 x 4096 (2048)
+// 38 / 39, 12288 x 4096 46 / 50, 8192 x 8192 57 / 64, 13824 x 5120 60 / 67, 10208 x 8256 69 / 86, but 32768 x 1024 (2048) 41 / 37; fp32
+// 6144 x 4096 (1536) 41 / 42, 8192 x 4096 49 / 52, 8192 x 8192 99 / 109, 8192 x 5504 63 / 70, 10208 x 8256 133 / 150, but 32768 x 1024 54 / 48.
+constexpr int64_t FOLD_ALONE_TILES = 1536, FOLD_ALONE_COLS = 1024;
+inline bool fold_in_tiles(int64_t rows, int64_t cols, int64_t parts, int bytes, bool alone) {
+  const int64_t tiles = (rows + CT_ROWS - 1) / CT_ROWS * ((cols + CT_COLS - 1) / CT_COLS);
+  return (!alone || tiles <= FOLD_ALONE_TILES || cols <= FOLD_ALONE_COLS) && (rows + CT_ROWS - 1) / CT_ROWS * cols * parts * bytes <= (int64_t)128 << 20;
 }
 
 inline unsigned ca_strips(int64_t cols) { return (unsigned)(((cols + 7) / 8 + 63) / 64); }
 inline unsigned ct_strips(int64_t cols) { return (unsigned)((cols + CT_COLS - 1) / CT_COLS); }
 
 // The scales, where the tiles don't form them themselves.
-void launch_amax_to_gamma(ColArgs& a, int parts, hipStream_t s) {
+void launch_amax_to_gamma(ColArgs& a, int parts, bool alone, hipStream_t s) {
   a.parts = 0;
-  if (fold_in_tiles(a, parts, 4) && a.cols % 4 == 0 && a.amax_ld % 4 == 0 && aligned16(a.amax_bits)) a.parts = parts;
+  if (fold_in_tiles(a.rows, a.cols, parts, 4, alone) && a.cols % 4 == 0 && a.amax_ld % 4 == 0 && aligned16(a.amax_bits)) a.parts = parts;
   else hipLaunchKernelGGL(amax_to_gamma_kernel, dim3((unsigned)((a.cols + 255) / 256)), dim3(256), 0, s, a.amax_bits, a.amax_ld,
                           (int64_t)parts, a.gamma, a.cols, 6.0f);
 }
@@ -1258,7 +1266,7 @@ __global__ __launch_bounds__(A16_WAVES * 64) void amax16_to_gamma_kernel(const u
 }
 
 void launch_amax16_to_gamma(ColArgs& a, hipStream_t s) {
-  if (fold_in_tiles(a, a.parts, 2)) return;
+  if (fold_in_tiles(a.rows, a.cols, a.parts, 2, false)) return;
   hipLaunchKernelGGL(amax16_to_gamma_kernel, dim3((unsigned)((a.cols + 127) / 128)), dim3(A16_WAVES * 64), 0, s, a.part16, (int64_t)a.parts,
                      a.gamma, a.cols);
   a.parts = 0;
@@ -1282,8 +1290,8 @@ int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, hipStream_t s)
   if (!known)
     hipLaunchKernelGGL((col_absmax_kernel<DT, CLAMP>), dim3(ca_strips(a.cols) + (b_max ? ca_strips(b.cols) : 0), (unsigned)rblocks), dim3(256),
                        0, s, a, b, ca_strips(a.cols));
-  launch_amax_to_gamma(a, rblocks, s);
-  if (b_max) launch_amax_to_gamma(b, rblocks, s);
+  launch_amax_to_gamma(a, rblocks, !b.x, s);
+  if (b_max) launch_amax_to_gamma(b, rblocks, false, s);
   else if (b.x) launch_amax16_to_gamma(b, s);
   hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>),
                      dim3(ct_strips(a.cols) + (b.x ? ct_strips(b.cols) : 0), (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS)), dim3(256), 0, s, a, b,
@@ -1523,6 +1531,11 @@ __global__ __launch_bounds__(1024) void tensor_gamma_kernel(const uint32_t* part
 // 512 columns, so there are at most 1022 of them.
 int64_t fp4_quantize_cols_scratch_words(int64_t rows, int64_t cols) {
   return std::max((rows + 127) / 128 * cols, std::min<int64_t>((rows + 31) / 32 * cols, 1022 * 512));
+}
+
+extern "C" int fp4_quantize_cols_folds(int64_t rows, int64_t cols) {
+  const int64_t per = ca_rows(rows, cols);
+  return fold_in_tiles(rows, cols, (rows + per - 1) / per, 4, true) && cols % 4 == 0;
 }
 
 int fp4_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
