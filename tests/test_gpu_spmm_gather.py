@@ -92,3 +92,33 @@ def test_full_rows_at_a_distance_cost_what_one_does(apart, dtype):
             times.append(e[0].elapsed_time(e[1]))
         best.append(min(times))
     assert best[1] < 2.0 * best[0], best
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("P,Q,N", [(40, 600, 136), (1030, 300, 520)])   # a row a workgroup, eight rows
+def test_infinities_and_nan_stay_with_their_entries(P, Q, N, dtype):
+    """Rows of D that are not finite reach the rows of S with an entry there, and no others: not those of the same workgroup or wave, not
+    rows that all waves share, and not through the zeros that fill a request up."""
+    g = torch.Generator(device="cuda").manual_seed(P)
+    mask = torch.rand(P, Q, generator=g, device="cuda") < 0.02
+    mask[P // 3] = True
+    mask[P // 3, 5:8] = False            # a long row without an entry in the rows that are not finite
+    mask[P // 2] = True
+    ptr, col, val = _csr(mask, g)
+    D = torch.randn(Q, N, generator=g, device="cuda")
+    D[5, ::3] = float("inf")
+    D[6, 1::3] = -float("inf")
+    D[7, 2::5] = float("nan")
+    D = D.to(dtype)
+    assert b.fp4_residual_spmm_gathers(P, Q, N, b.FP4_BF16 if dtype == torch.bfloat16 else b.FP4_F32, col.numel())
+    R = b.fp4_residual_spmm(ptr, col, val, Q, D)
+    row = torch.repeat_interleave(torch.arange(P, device="cuda"), ptr[1:] - ptr[:-1])
+    ref = torch.zeros(P, N, dtype=torch.float64, device="cuda").index_add_(0, row, val[:, None].double() * D.double()[col.long()])
+    mag = torch.zeros_like(ref).index_add_(0, row, (val[:, None].double() * D.double()[col.long()]).abs())
+    assert torch.equal(R.isnan(), ref.isnan())
+    infinite = ref.isinf()
+    assert torch.equal(R[infinite].double(), ref[infinite])
+    fine = ref.isfinite()
+    n = (ptr[1:] - ptr[:-1])[:, None].double() + 1
+    assert torch.all(((R.double() - ref).abs() <= n * 2.0 ** -23 * mag)[fine])
+    assert fine[P // 3].all() and not fine[P // 2].all()
