@@ -172,7 +172,7 @@ FP4_D void find_digit(SelState* st, const unsigned long long* hist, const Ranks&
 // Bound by the one read and, about as long, by vector instructions (nine an element, twelve where zeros are counted apart).
 // 16384 x 11008, in us: sample 6.6, the pass 97, the general path's two launches 10, rows 6, together 119 (130 with picks in launches of
 // their own, of 4.8 each); digit passes, picks and the count of the rows after them 249.  16384 x 4096: 65 against 107.  Half
-// zeros, 16384 x 11008, with scan and emission, 250 against 540; a miss 419 against 353.  8192 x 2048, behind a digit pass of 14 us: the
+// zeros, 16384 x 11008, with scan and emission, 250 against 540; a miss (a NaN), which took 466 with picks, now 367.  8192 x 2048, behind a digit pass of 14 us: the
 // pass 19.5, rows 7.6, where a second digit pass and the count of the rows took 15 and 11 and two picks and the clearing 4.5 each; 1056 x
 // 1376 7.2 + 8.1 + 4.2 against 7.1 + 4.4 + 7.3 + 4.0 + 4.2 and 2.2.
 constexpr int WIN_KEYS = 96, WIN_BINS = 2 * WIN_KEYS + 3, WIN_LDS = 256, WIN_STRIDE = 200;   // bins; a wave's table; a row's in memory
@@ -249,8 +249,9 @@ __global__ __launch_bounds__(1024) void win_count_kernel(const uint16_t* x, int6
   typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
   uint32_t sum[WIN_LDS / 64] = {};
   u16x2 top = {0, 0};   // largest magnitude
-  // Sums of 0 / 1 / 1 and of 0 / 1 / 2 for -0, +0 and the rest.  16 bits hold them: rows have 500 elements or more (row_bins has to fit
-  // the entries' room) and the tensor fewer than 2^32, so a half word meets at most 2^13 + 2^7 of them.
+  // Sums of 0 / 1 / 1 and of 0 / 1 / 2 for -0, +0 and the rest.  16 bits hold them: a half word meets 4 elements for every 512 begun of a row, in
+  // ceil(rows / 8192) rows, rows have 500 elements or more (row_bins has to fit the entries' room) and the tensor fewer than 2^32: at most
+  // 2^13 + 2^10 elements.
   u16x2 nz1 = {0, 0}, nz2 = {0, 0};
   const uint16_t lo1 = (uint16_t)(win.w0 - 1), hi1 = (uint16_t)(win.w1 - 1), most = WIN_KEYS + 1;
   const u16x2 lo = {lo1, lo1}, hi = {hi1, hi1}, lim = {most, most};

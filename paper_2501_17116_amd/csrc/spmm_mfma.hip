@@ -13,7 +13,7 @@
 // core wants eight k values of one column per lane; v_perm_b32 turns eight rows x eight columns around.
 //
 // D passes through LDS as a ring of chunks (SM_KC rows x SM_NT columns, direct-to-LDS loads two chunks
-// ahead).  A slot may be multiplied in any phase in which its chunk is resident, and the packing decides
+// ahead, three with one group a wave).  A slot may be multiplied in any phase in which its chunk is resident, and the packing decides
 // how many steps a group runs in each phase (a prefix of its slots, S[phase]): the steps stay full and the
 // waves of a workgroup in step with each other although the entries of a chunk are few and random.
 //
@@ -96,8 +96,8 @@ FP4_D bool pk_worth(const int (&rows)[4], int Q, bool small_grid) {
 }
 
 // One workgroup per bundle of G groups (the groups of one wave, which step together), or G of them (split), which all count and
-// plan for the whole bundle and write one group each: fewer bundles than a third of the chip left the rest of it idle while each
-// wrote some hundred KiB (4096 rows of 328 entries 53.5 -> 46.0 us, 2048 of 164 27.1 -> 22.4).  sched[bundle][phase]:
+// plan for the whole bundle and write one group each, up to two of these workgroups a CU: bundles of three groups that are fewer
+// than two thirds of the CUs left the rest idle while each wrote some hundred KiB (4096 rows of 328 entries 53.5 -> 46.0 us, 2048 of 164 27.1 -> 22.4).  sched[bundle][phase]:
 // steps done when the phase ends; steps[bundle]: steps in all, or -1 when the bundle is left to the tiled kernel (a
 // matrix that is not worth it, more slots than there is room for, columns that repeat inside a row, or values that three
 // bf16 terms do not make up); redo[bundle]: 0.
