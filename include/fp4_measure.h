@@ -60,9 +60,8 @@ int fp4_residual_transpose(const int64_t* row_ptr, const int32_t* col_idx, const
                            size_t workspace_bytes, void* stream);
 
 /* Whether a residual product S [P x Q] D [Q x N] of at most so many entries is one launch that gathers rows of D (1) or goes to the
- * kernels of large products (0), by the rule the launches follow (host arithmetic, no GPU).  channels: S is the transposed residual
- * of a weight gradient. */
-int fp4_residual_spmm_gathers(int64_t P, int64_t Q, int64_t N, fp4_dtype dt, int64_t entries, int channels);
+ * kernels of large products (0), by the rule the launches follow (host arithmetic, no GPU). */
+int fp4_residual_spmm_gathers(int64_t P, int64_t Q, int64_t N, fp4_dtype dt, int64_t entries);
 
 /* fp4_residual_spmm by the kernels that large products take, whatever the size: same arguments, workspace and result (sums in
  * another order). */

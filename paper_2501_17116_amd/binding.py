@@ -93,7 +93,7 @@ def lib() -> C.CDLL:
         L.fp4_residual_spmm.argtypes = [vp, vp, vp, i64, i64, vp, i32, i64, vp, vp, sz, vp]
         L.fp4_residual_spmm_general.argtypes = L.fp4_residual_spmm.argtypes
         L.fp4_residual_spmm_bounded.argtypes = [vp, vp, vp, i64, i64, i64, vp, i32, i64, vp, vp, sz, vp]
-        L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64, i32]
+        L.fp4_residual_spmm_gathers.argtypes = [i64, i64, i64, i32, i64]
         L.fp4_residual_spmm_gathers.restype = i32
         L.fp4_quantize_cols_folds.argtypes = [i64, i64]
         L.fp4_quantize_cols_folds.restype = i32
@@ -537,9 +537,9 @@ def fp4_residual_spmm_general(row_ptr: torch.Tensor, col_idx: torch.Tensor, val:
     return _residual_spmm("fp4_residual_spmm_general", (), row_ptr, col_idx, val, Q, D, R, ws)
 
 
-def fp4_residual_spmm_gathers(P: int, Q: int, N: int, dt: int, entries: int, channels: bool = False) -> bool:
+def fp4_residual_spmm_gathers(P: int, Q: int, N: int, dt: int, entries: int) -> bool:
     """Whether a residual product is the gathering kernel's (host arithmetic, no GPU)."""
-    return bool(lib().fp4_residual_spmm_gathers(P, Q, N, dt, entries, int(channels)))
+    return bool(lib().fp4_residual_spmm_gathers(P, Q, N, dt, entries))
 
 
 def _residual_spmm(name, capacity, row_ptr, col_idx, val, Q, D, R, ws):

@@ -76,7 +76,7 @@ int fp4_launch_order_rows(const int64_t* row_ptr, int64_t rows, int64_t nidx, in
 int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16);
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    bool channels, hipStream_t s, bool general = false);
+                    hipStream_t s, bool general = false);
 
 namespace {
 
@@ -418,7 +418,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
     if (rc) return rc;
     // Delta_A W with the unquantized W, fp32; lands where the GEMM epilogue picks it up
     float* R = bf16 ? w.R : reinterpret_cast<float*>(Y);
-    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, false, s);
+    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, s);
     if (rc) return rc;
     addend = R;
   } else {
@@ -513,7 +513,7 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
                      nullptr, w.occ, s);
     if (rc) return rc;
     float* R = bf16 ? w.R : reinterpret_cast<float*>(Y);
-    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, false, s);
+    rc = fp4_launch_spmm(saved->row_ptr, saved->col_idx, saved->val, cap, M, K, W, bf16, N, R, w.sp_scratch, s);
     if (rc) return rc;
     addend = R;
   } else {
@@ -606,7 +606,7 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
-    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, true, s);
+    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, s);
     if (rc) return rc;
     addend = dW;
   }
@@ -658,7 +658,7 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
-    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, true, s);
+    rc = fp4_launch_spmm(w.t_ptr, w.t_idx, w.t_val, cap, K, M, dY, bf16, N, dW, w.sp_scratch, s);
     if (rc) return rc;
     addend = dW;
   }
@@ -677,7 +677,7 @@ int residual_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* v
   if (!aligned16(D) || !aligned16(R)) return FP4_ERR_ARG;
   if (!workspace || workspace_bytes < fp4_workspace_bytes(FP4_OP_SPMM, P, Q, N, dt)) return FP4_ERR_WORKSPACE;
   int32_t* scratch = reinterpret_cast<int32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
-  return fp4_launch_spmm(row_ptr, col_idx, val, capacity, P, Q, D, dt == FP4_BF16, N, R, scratch, false, (hipStream_t)stream, general);
+  return fp4_launch_spmm(row_ptr, col_idx, val, capacity, P, Q, D, dt == FP4_BF16, N, R, scratch, (hipStream_t)stream, general);
 }
 }  // namespace
 

@@ -1074,7 +1074,7 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                          int64_t Q, const void* D, int64_t N, float* R, void* scratch, int32_t* list, int32_t* count,
                          SpmmRest& rest, hipStream_t s);
 int fp4_launch_spmm_gather(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity, int64_t P, int64_t Q,
-                           const void* D, int bf16, int64_t N, float* R, bool channels, hipStream_t s);
+                           const void* D, int bf16, int64_t N, float* R, hipStream_t s);
 // int32 words of scratch fp4_launch_spmm needs: count[64 (only [0] used)], list[P], then
 // the fp32 partial sums of the dense long-row path, [spans][long rows][N], at most LD_CAP x slices rows of N, then (bf16 D)
 // the packed matrix.
@@ -1089,10 +1089,10 @@ int64_t fp4_spmm_scratch_words(int64_t P, int64_t Q, int64_t N, int bf16) {
   return spmm_long_words(P, Q, N) + (bf16 ? (fp4_spmm_mfma_scratch_bytes(P, Q) + 3) / 4 : 0);
 }
 
-// channels: the rows are channels, not tokens.  general: by the kernels that large products take, whatever the size
+// general: by the kernels that large products take, whatever the size
 int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float* val, int64_t capacity,
                     int64_t P, int64_t Q, const void* D, int bf16, int64_t N, float* R, int32_t* scratch,
-                    bool channels, hipStream_t s, bool general) {
+                    hipStream_t s, bool general) {
   if (P == 0 || N == 0) return FP4_OK;
   if (Q >= ((int64_t)1 << 21)) return FP4_ERR_SHAPE;   // 32-bit entry offsets inside a workgroup's 1024 rows
   const bool may_be_long = Q > SPMM_LONG_MIN && capacity > SPMM_LONG_MIN;   // otherwise no row is
@@ -1100,7 +1100,7 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
   int32_t* const list = scratch + 64;
   const dim3 grid((unsigned)((P + SP_ROWS - 1) / SP_ROWS), (unsigned)((N + SP_COLS - 1) / SP_COLS));
   const int trace_slot = fp4_trace_open(FP4_TRACE_SPMM, s);   // the whole product, as its entries are counted
-  int rc = general ? 1 : fp4_launch_spmm_gather(row_ptr, col_idx, val, capacity, P, Q, D, bf16, N, R, channels, s);
+  int rc = general ? 1 : fp4_launch_spmm_gather(row_ptr, col_idx, val, capacity, P, Q, D, bf16, N, R, s);
   if (rc != 1) {
     fp4_trace_close(trace_slot, s);
     return rc;

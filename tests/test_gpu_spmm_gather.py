@@ -122,3 +122,57 @@ def test_infinities_and_nan_stay_with_their_entries(P, Q, N, dtype):
     n = (ptr[1:] - ptr[:-1])[:, None].double() + 1
     assert torch.all(((R.double() - ref).abs() <= n * 2.0 ** -23 * mag)[fine])
     assert fine[P // 3].all() and not fine[P // 2].all()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("P,Q,N,full", [(5, 4104, 8, [4]), (3, 4104, 72, [1]), (70, 4104, 136, [0, 1, 69]), (600, 4160, 520, [7, 8, 9, 400, 599]),
+                                        (1200, 6000, 72, list(range(0, 1200, 97))),
+                                        (64, 4608, 8192, [1, 3, 8, 9, 10, 30, 62, 63])])   # more full rows than there are workgroups for a strip
+def test_long_rows_of_more_than_4096_columns(P, Q, N, full, dtype):
+    """Rows that the first workgroups take, beside rows that a workgroup's waves share (between four times the mean and 256 entries) and others."""
+    g = torch.Generator(device="cuda").manual_seed(P + Q)
+    mask = torch.rand(P, Q, generator=g, device="cuda") < 4.0 / Q
+    mask[P // 2] = torch.rand(Q, generator=g, device="cuda") < 120.0 / Q
+    for r in full:
+        mask[r] = torch.rand(Q, generator=g, device="cuda") < (0.9 if r % 2 else 300.0 / Q)
+    ptr, col, val = _csr(mask, g)
+    D = torch.randn(Q, N, generator=g, device="cuda").to(dtype)
+    assert b.fp4_residual_spmm_gathers(P, Q, N, b.FP4_BF16 if dtype == torch.bfloat16 else b.FP4_F32, col.numel())
+    R = torch.full((P, N), float("nan"), device="cuda")
+    b.fp4_residual_spmm(ptr, col, val, Q, D, R=R)
+    row = torch.repeat_interleave(torch.arange(P, device="cuda"), ptr[1:] - ptr[:-1])
+    S = torch.zeros(P, Q, dtype=torch.float64, device="cuda")
+    S[row, col.long()] = val.double()
+    n = (ptr[1:] - ptr[:-1])[:, None].double() + 1
+    assert torch.all((R.double() - S @ D.double()).abs() <= n * 2.0 ** -23 * (S.abs() @ D.double().abs()))
+    assert torch.equal(R, b.fp4_residual_spmm(ptr, col, val, Q, D))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_a_full_row_of_8192_columns_is_not_waited_for(dtype):
+    """One among 1 %: a few workgroups that took it as it came, a wide strip each, made the product five to eight times as long."""
+    P, Q, N = 512, 8192, 512
+    g = torch.Generator(device="cuda").manual_seed(1)
+    mask = torch.rand(P, Q, generator=g, device="cuda") < 0.01
+    D = torch.randn(Q, N, generator=g, device="cuda").to(dtype)
+    R = torch.empty(P, N, device="cuda")
+    best = []
+    for full in (False, True):
+        mask[P // 3] |= full
+        args, ws = _csr(mask, g), b.Workspace()
+        graph = torch.cuda.CUDAGraph()
+        b.fp4_residual_spmm(*args, Q, D, R=R, ws=ws)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            for _ in range(8):
+                b.fp4_residual_spmm(*args, Q, D, R=R, ws=ws)
+        times = []
+        for _ in range(12):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            graph.replay()
+            e[1].record()
+            e[1].synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        best.append(min(times))
+    assert best[1] < 4.2 * best[0], best

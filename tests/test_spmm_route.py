@@ -35,11 +35,3 @@ def test_never_for_more_entries_only():
         assert took == sorted(took, reverse=True)
         if P * Q * N > 2 ** 33 or Q > 8192:
             assert not any(took)
-
-
-def test_long_rows_of_channels_are_not_gathered():
-    """The weight gradient's rows are channels, of which outlier channels hold nearly every token."""
-    for dt in (BF16, F32):
-        for M, want in ((4096, True), (4128, False), (8192, False)):
-            assert b.fp4_residual_spmm_gathers(512, M, 1024, dt, 512 * M // 50, channels=True) == want
-            assert b.fp4_residual_spmm_gathers(512, M, 1024, dt, 512 * M // 50)
