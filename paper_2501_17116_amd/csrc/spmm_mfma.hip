@@ -2,25 +2,30 @@
 //
 // S has about 2 % scattered entries.  Sixteen rows of it together touch about 28 % of the columns, so a
 // group of 16 rows is packed into "slots": one slot per column that any of the 16 rows has an entry in,
-// holding that column's 16 values (zero where a row has none) in bf16.  32 slots make one step of
-// v_mfma_f32_16x16x32_bf16: A = the 16 x 32 packed values, B = the 32 rows of D that the slots name,
-// gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three (down to 2^-110; rows with
-// smaller values of more bits are left to the tiled kernel), and its column takes as many slots: products are exact, sums are
-// fp32, nothing is rounded to 16 bits.
+// holding that column's 16 values (zero where a row has none) in bf16.  32 slots make one step: A = the 16 x 32 packed values, B = the
+// 32 rows of D that the slots name, gathered from LDS.  An fp32 value that is no bf16 number is the exact sum of two or three (down to
+// 2^-110; rows with smaller values of more bits are left to the tiled kernel), and its column takes as many slots: products are
+// exact, sums are fp32, nothing is rounded to 16 bits.
 //
-// A lane owns 8 adjacent columns of D, so a gathered row arrives as one 16-byte LDS read per lane,
-// 256 contiguous bytes per quarter wave: free of bank conflicts whatever rows the slots name.  The matrix
-// core wants eight k values of one column per lane; v_perm_b32 turns eight rows x eight columns around.
+// A lane owns 8 adjacent columns of D, so a gathered row arrives as one 16-byte LDS read per lane, 256 contiguous bytes per
+// quarter wave: free of bank conflicts whatever rows the slots name.  A register then holds two columns of one row, where the dense
+// matrix instruction wants two rows of one column: v_perm_b32 turned eight rows x eight columns around, 32 a step.  The 2:4 sparse
+// instruction (v_smfmac_f32_16x16x64_bf16) takes them as they came: of every four adjacent k values, here two columns of two rows, it
+// multiplies two, the first column's or the second's as its index says, so that the same registers serve for both columns, and the
+// eight registers of eight rows have only to be put side by side (26 v_mov_b32 a step; 12 v_swap_b32, or v_pk_mov_b32, take as long).
+// A step of a SIMD alone, three waves of three groups: 155 -> 122 ns.  The product with its packing, at 2 %, us: 16384 x 4096 -> 12288
+// 826 -> 813, 4096 x 16384 -> 12288 787 -> 764, 16384 x 11008 -> 4096 669 -> 652, 8192 x 4096 -> 11008 377 -> 360, 4096 x 8192 ->
+// 11008 397 -> 377 (1 to 2 % of it from not waiting for operands at each phase, at `plan`).
 //
 // D passes through LDS as a ring of chunks (SM_KC rows x SM_NT columns, direct-to-LDS loads two chunks
 // ahead, three with one group a wave).  A slot may be multiplied in any phase in which its chunk is resident, and the packing decides
 // how many steps a group runs in each phase (a prefix of its slots, S[phase]): the steps stay full and the
 // waves of a workgroup in step with each other although the entries of a chunk are few and random.
 //
-// Bound: the matrix core (16 cycles an instruction), the LDS reads and the vector instructions (32 v_perm_b32 and 8
-// addresses a step) each leave room for about twice what is reached.  Residual of a 16384 x 4096 -> 12288 layer (2 %,
-// 1.3 M entries), packing included: 857 us, 38 TFLOP/s of useful products; plain fp32 FMAs fed from LDS (spmm.hip):
-// 1423 us.  6 %: 1486 against 2961 us; 0.2 %: 524 against 609 us.
+// Bound: a SIMD's vector instructions (34 a step beside the matrix core's 8, which have 16 cycles each) and the return of its LDS reads, which
+// do not overlap: reads alone 62 ns a step, with the matrix core 84, with the moves 122; nine wave-steps of the fullest SIMD where there
+// are 8.25 on average; of 16384 x 4096 -> 12288's 813 us about 190 are what the sums' way to memory costs, mostly by making the loads wait.
+// The same with plain fp32 FMAs fed from LDS (spmm.hip): 1423 us; 6 %: 1400 against 2961 us; 0.2 %: 500 against 609 us.
 #include "fp4_common.h"
 #include "spmm_long.h"
 
@@ -30,6 +35,8 @@
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 
 constexpr int SM_STEPS_PAD = 12;   // step counts read past the last bundle (11 waves)
 constexpr int SM_KC = 128;       // rows of D per chunk
@@ -43,11 +50,15 @@ constexpr int SM_DEEP = 3;       // steps of a single group requested ahead
 constexpr int SM_NT = 128;       // columns of R per workgroup
 constexpr int SM_ROWB = SM_NT * 2;
 constexpr int SM_CHUNKB = SM_KC * SM_ROWB;
+// Which two of four adjacent k values the 2:4 sparse instruction multiplies, two bits a value: the first and the third (low half), or the
+// second and the fourth.
+constexpr int SM_FIRST_OF_TWO = (int)0xdddd8888;
 constexpr int SM_STRIP = 8;      // column blocks that an XCD works on side by side
 // Packing threads per row: what fills a workgroup.  A row's entries are two chains of loads, so more threads shorten
 // them (2048 rows of 164 entries, 16 / 32 / 64 threads a row: 20.1 / 17.8 / 16.7 us).
 constexpr int pk_tpr(int g) { return g == 1 ? 64 : 16; }
 constexpr int64_t SM_MAXQ = 24576;   // the packing keeps a nibble per column and group in LDS, within 64 KiB
+constexpr int SM_PLANS = (int)((SM_MAXQ + 64 * SM_KC - 1) / (64 * SM_KC));   // registers that hold a step count for every phase
 static_assert(SM_ROWB == 256, "a quarter wave covers a row of a chunk with 16 bytes a lane");
 
 // Slots a column up to which a matrix is packed, at a share d of entries.  The packed product takes a time that goes with
@@ -59,6 +70,13 @@ constexpr float SM_ROOM_SLOTS = 1.15f, SM_EVEN_SLOTS = 0.14f, SM_EVEN_SHARE = 21
 // steps a group of 16 rows has room for: every column once, and a quarter more for values of several terms
 inline int64_t sm_cap(int64_t Q) { return (Q + 31) / 32 + (Q + 127) / 128 + 3; }
 inline int64_t sm_phases(int64_t Q) { return (Q + SM_KC - 1) / SM_KC; }
+
+// Byte of a step's packed values at which row r's value of slot p stands.  A lane gathers the eight rows of D of slots 8 q .. 8 q + 7, q its
+// quarter of the wave; the instruction pairs the first four with values 4 (q & 1) .. of quarter q / 2, the others with those of quarter 2 + q / 2.
+FP4_D int sm_a_at(int p, int r) {
+  const int quarter = (p >> 1 & 2) | p >> 4, i = (p >> 1 & 4) | (p & 3);
+  return (quarter * 16 + r) * 16 + i * 2;
+}
 
 // v as the exact sum of up to three bf16 numbers (nearest first); returns how many, 4 if three are not enough: below
 // 2^-110 the last of fp32's 24 bits can lie under the smallest bf16 number, 2^-133.
@@ -295,7 +313,7 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
       const uint16_t at = (uint16_t)(c % (SM_RING * SM_KC));   // row of the ring
       for (int k = 0; k < nt; ++k) {
         const int p = pos + k;
-        *reinterpret_cast<uint16_t*>(ag + (int64_t)(p >> 5) * 1024 + (((p >> 3) & 3) * 16 + r) * 16 + (p & 7) * 2) = (uint16_t)t[k];
+        *reinterpret_cast<uint16_t*>(ag + (int64_t)(p >> 5) * 1024 + sm_a_at(p & 31, r)) = (uint16_t)t[k];
         *reinterpret_cast<uint16_t*>(og + (int64_t)p * 2) = at;
       }
     }
@@ -420,14 +438,12 @@ __global__ __launch_bounds__((WV + sm_stagers(G)) * 64) void spmm_mfma_kernel(co
     const bf16x8 av = __builtin_bit_cast(bf16x8, a[set]);
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      u32x4 lo, hi;
+      u32x8 two;   // columns 2 w and 2 w + 1 of the lane's eight rows, as they came
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x05040100u);
-        hi[e] = __builtin_amdgcn_perm(d[2 * e + 1][w], d[2 * e][w], 0x07060302u);
-      }
-      acc[g][2 * w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, lo), acc[g][2 * w], 0, 0, 0);
-      acc[g][2 * w + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, hi), acc[g][2 * w + 1], 0, 0, 0);
+      for (int e = 0; e < 8; ++e) two[e] = d[e][w];
+      const bf16x16 dv = __builtin_bit_cast(bf16x16, two);
+      acc[g][2 * w] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, dv, acc[g][2 * w], SM_FIRST_OF_TWO, 0, 0);
+      acc[g][2 * w + 1] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(av, dv, acc[g][2 * w + 1], SM_FIRST_OF_TWO, 0, 1);
     }
     __builtin_amdgcn_sched_barrier(0);
     fetch(set, G == 1 ? done + SM_DEEP - 1 : done);   // into the registers this step is done with
@@ -450,16 +466,18 @@ __global__ __launch_bounds__((WV + sm_stagers(G)) * 64) void spmm_mfma_kernel(co
       }
     }
   };
-  // The steps done at the end of each phase, 64 phases a register: a scalar load per phase would cost its latency
-  // in every one of them.
-  auto plan_at = [&](int p0) { return live ? sp[min(p0 + lane, phases - 1)] : 0; };
-  int plan = plan_at(0), plan_next = plan_at(64);
+  // The steps done at the end of each phase, 64 phases a register, all of them loaded and waited for here: a load inside the loop, of
+  // which there was one every 64 phases, made the compiler wait at every phase for whatever was under way, the next steps' operands above all.
+  int plan[SM_PLANS];
+#pragma unroll
+  for (int i = 0; i < SM_PLANS; ++i) plan[i] = live ? sp[min(64 * i + lane, phases - 1)] : 0;
+#pragma unroll
+  for (int i = 0; i < SM_PLANS; ++i) asm volatile("" : "+v"(plan[i]));
   for (int p = 0; p < phases; ++p) {
-    if (p > 0 && (p & 63) == 0) {
-      plan = plan_next;
-      plan_next = plan_at(p + 64);
-    }
-    const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane(plan, p & 63);
+    if (p > 0 && (p & 63) == 0)
+#pragma unroll
+      for (int i = 0; i + 1 < SM_PLANS; ++i) plan[i] = plan[i + 1];
+    const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane(plan[0], p & 63);
     rounds(upto);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the chunk that goes next are done
     __builtin_amdgcn_s_barrier();
