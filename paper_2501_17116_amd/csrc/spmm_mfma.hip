@@ -46,6 +46,7 @@ constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): to multiply fro
 constexpr int sm_ahead(int g) { return g == 1 ? 3 : 2; }
 constexpr int sm_stagers(int g) { return g == 1 ? 2 : 1; }
 constexpr int sm_slack(int g) { return SM_RING - sm_ahead(g) - 1; }   // phases a chunk stays after the one it arrives in
+constexpr int SM_PACE = 4;       // steps whose multiples bundles are paced by
 constexpr int SM_DEEP = 3;       // steps of a single group requested ahead
 constexpr int SM_NT = 128;       // columns of R per workgroup
 constexpr int SM_ROWB = SM_NT * 2;
@@ -222,11 +223,17 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   }
   __syncthreads();
   if (tid < 64) {
-    // S follows an even pace, between what must be done (chunk c - SM_SLACK leaves) and what fills whole steps.  One
-    // wave: a lane holds the counts of every 64th chunk, the recurrence runs on scalars.
-    int total = 0, e[G], ends[SM_SLACK + 1], S = 0, quot, rem, pace = 0, left = 0;
+    // S follows an even pace, between what must be done (chunk c - SM_SLACK leaves) and what fills whole steps, and takes no more steps in a
+    // phase than the pace does, unless it must: the waves of a workgroup wait for each other at every phase, so that one which makes up for a
+    // step it fell behind holds up all others.  The pace begins a phase late, when every bundle has the slots for it, and is that of the next
+    // multiple of four steps, so that most bundles have the same (16384 x 4096 -> 12288 at 2 % 811 -> 777 us; counted over the phases, the fullest SIMD of a
+    // workgroup has 6 % fewer steps).  Bundles of one group keep to their own pace, without a limit (2048 x 8192 -> 2048 90.6 us, 92.0 with).  One wave: a lane
+    // holds the counts of every 64th chunk, the recurrence runs on scalars.
+    constexpr bool EVEN = G > 1;
+    int total = 0, e[G], ends[SM_SLACK + 1], S = 0, quot, rem, pace = 0, more = 0, left = 0;
     for (int j = 0; j < G; ++j) { total = max(total, (s_total[j] + 31) / 32); e[j] = 0; }
     total = __builtin_amdgcn_readfirstlane(total);
+    if constexpr (EVEN) total = (total + SM_PACE) / SM_PACE * SM_PACE;
     quot = total / phases;
     rem = total % phases;
 #pragma unroll
@@ -250,11 +257,15 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
 #pragma unroll
         for (int k = 0; k < SM_SLACK; ++k) ends[k] = ends[k + 1];
         ends[SM_SLACK] = most;
-        pace += quot;   // ceil(total * (c + 1) / phases)
-        left += rem;
-        if (left >= phases) { left -= phases; ++pace; }
         const int lo = max(S, (ends[0] + 31) / 32);
-        S = c0 + i == phases - 1 ? max(lo, (most + 31) / 32) : max(min(pace + (left > 0 ? 1 : 0), least / 32), lo);
+        int next = pace;
+        if constexpr (EVEN) next = min(pace, S + more);
+        more = quot;   // pace: floor(total * c / phases) from here on
+        left += rem;
+        if (left >= phases) { left -= phases; ++more; }
+        pace += more;
+        if constexpr (!EVEN) next = pace + (left > 0 ? 1 : 0);
+        S = c0 + i == phases - 1 ? max(lo, (most + 31) / 32) : max(min(next, least / 32), lo);
         mine = tid == i ? S : mine;
       }
       if (tid < here) {
