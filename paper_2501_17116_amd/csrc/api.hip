@@ -4,6 +4,8 @@
 // and the library keeps no state between calls.
 #include "fp4_common.h"
 #include "fp4_measure.h"
+#include "csr_mask.h"
+#include "select.h"
 
 #include <algorithm>
 #include <cmath>
@@ -31,19 +33,22 @@ int fp4_launch_quantize_cols_given_gamma(const void* x, int bf16, int64_t rows, 
                                          uint8_t* codes_t, float* gamma, hipStream_t s);
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
-                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words);
+                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words, const SelFirst* first);
+bool fp4_select_first_beside(const SelFirst& f, int64_t rows, int64_t cols);
+bool fp4_select_begins_with_digits(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t rows_scratch_words);
 int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t tail_k,
                               float* thr_out, uint8_t* codes, float* gamma, void* x_clamped, int32_t* tmp_col,
                               float* tmp_val, int32_t* row_cnt, hipStream_t s);
 int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols);
 int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64_t cols, uint8_t* codes, float* gamma, uint16_t* part16,
                                     const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, const void* z, int64_t cols_z,
-                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, hipStream_t s);
+                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, MbArgs* m, hipStream_t s);
 int fp4_launch_quantize_rows_pair(const void* x, const void* y, int bf16, int64_t rows, int64_t rows_y, int64_t cols, uint8_t* codes,
                                   float* gamma, uint8_t* codes_y, float* gamma_y, hipStream_t s);
 int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
-                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, hipStream_t s);
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, const MbArgs* m, hipStream_t s);
+bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y);
 int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const int32_t* row_cnt, int64_t stride,
                             const int64_t* row_ptr, int64_t rows, int64_t capacity, int32_t* col_idx, float* val,
                             hipStream_t s);
@@ -54,7 +59,7 @@ int fp4_select_passes(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t 
 int fp4_launch_clear_select(void* scratch, const float* src, float* dst, int64_t n, hipStream_t s);
 int fp4_launch_thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds,
                                      void* scratch, void* rows_scratch, int64_t rows_scratch_words, int32_t* row_cnt, int32_t* row_sum,
-                                     int shift, hipStream_t s);
+                                     int shift, bool first_done, hipStream_t s);
 int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s);
 int fp4_launch_csr_gather(const int32_t* tmp_col, const float* tmp_val, int64_t rows, int64_t capacity,
                           const int64_t* row_ptr, int32_t* col_idx, float* val, hipStream_t s);
@@ -132,11 +137,11 @@ OccTemps carve_occ(Carver& c, int64_t rows, int64_t capacity, int64_t later = 0,
 }
 
 // The per-tensor thresholds, then how many elements of each row they clamp; the entries' temporaries are free until then, t.select is
-// cleared.
+// cleared (first_done: the first digit pass has run).
 int thresholds_and_counts(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t k, float* thresholds, const OccTemps& t,
-                          hipStream_t s) {
+                          hipStream_t s, bool first_done = false) {
   return fp4_launch_thresholds_and_counts(x, bf16, rows, cols, ld, k, thresholds, t.select, t.tmp_col, provisioned_entries(rows, cols),
-                                          t.row_cnt, t.row_sum, fp4_row_sum_shift(rows), s);
+                                          t.row_cnt, t.row_sum, fp4_row_sum_shift(rows), first_done, s);
 }
 
 // Clamp, codes and the ordered residual, after thresholds_and_counts.
@@ -381,6 +386,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
   int rc = FP4_OK;
   const uint8_t* qWt = w.qWt;
   void* const clear = occ && !token ? w.occ.select : nullptr;
+  bool first_done = false;
   if (wq || wgt_tensor) {
     const bool copy = wq && saved->gamma_W != wq->gamma_W;
     rc = fp4_launch_clear_select(clear, copy ? wq->gamma_W : nullptr, saved->gamma_W, copy ? N : 0, s);
@@ -393,7 +399,11 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
     if (!rc) rc = fp4_launch_quantize_cols_given_gamma(W, bf16, K, N, N, w.qWt, saved->gamma_W, s);
     if (rc) return rc;
   } else {
-    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, clear, fp4_select_clear_words());
+    // a small layer's first pass over A goes with the second over W
+    const SelFirst first = {A, M, K, K, reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(w.occ.select) + SEL_STATE_BYTES)};
+    first_done = clear && fp4_select_first_beside(first, K, N) && fp4_select_begins_with_digits(bf16, M, K, K, provisioned_entries(M, K));
+    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, clear, fp4_select_clear_words(),
+                                  first_done ? &first : nullptr);
     if (rc) return rc;
   }
   const float* addend = nullptr;
@@ -403,7 +413,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
       rc = occ_token_chain(A, bf16, M, K, K, k_row, saved->thresholds, w.qA, w.gA, nullptr, saved->row_ptr,
                            saved->col_idx, saved->val, cap, saved->nnz, w.occ, s);
     } else {
-      rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s);
+      rc = thresholds_and_counts(A, bf16, M, K, K, k, saved->thresholds, w.occ, s, first_done);
       if (rc) return rc;
       const float* g_all = nullptr;   // tensor-wise activations: one scale, from the clamped tensor's absmax
       if (act_tensor) {
@@ -498,7 +508,7 @@ extern "C" int fp4_linear_fwd_mixed(const void* A, const void* W, fp4_dtype dt, 
     rc = occ ? fp4_launch_clear_select(w.occ.select, nullptr, nullptr, 0, s) : FP4_OK;
     if (!rc) rc = fp8_launch_quantize_cols(W, bf16, K, N, N, w.qWt, saved->gamma_W, w.amax, s);
   } else {
-    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, nullptr, 0);
+    rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, nullptr, 0, nullptr);
   }
   if (rc) return rc;
   const float* addend = nullptr;
@@ -548,7 +558,7 @@ extern "C" int fp4_prepare_weights(const void* W, fp4_dtype dt, int64_t K, int64
   hipStream_t s = (hipStream_t)stream;
   const int bf16 = dt == FP4_BF16;
   uint32_t* amax = reinterpret_cast<uint32_t*>(align_up((size_t)(uintptr_t)workspace, 256));
-  int rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, wq->qWt, wq->gamma_W, amax, s, nullptr, 0);   // forward's operand
+  int rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, wq->qWt, wq->gamma_W, amax, s, nullptr, 0, nullptr);   // forward's operand
   if (rc) return rc;
   return fp4_launch_quantize_rows(W, bf16, K, N, N, wq->qWk, wq->gamma_Wk, s);                   // dgrad's operand
 }
@@ -575,6 +585,17 @@ extern "C" int fp4_linear_bwd_dgrad_cached(const void* dY, const fp4_weight_cach
   return dgrad_impl(dY, nullptr, wq, dt, M, K, N, dA, workspace, workspace_bytes, stream);
 }
 
+namespace {
+// The saved residual's transpose, but for what goes with other launches: m's passes that they have taken (m.counted, m.scanned), and its
+// last pass (beside).
+int transpose_residual(const fp4_fwd_ctx* saved, int64_t M, int64_t K, int64_t cap, const WgradWs& w, const MbArgs& m, bool beside,
+                       hipStream_t s) {
+  if (m.nblocks > 0) return fp4_launch_csr_mask(m, !beside, s);
+  return fp4_launch_csr_transpose(saved->row_ptr, saved->col_idx, saved->val, saved->nnz, M, K, cap, w.t_ptr, w.t_idx, w.t_val, w.u_idx,
+                                  w.u_val, w.t_scratch, s);
+}
+}  // namespace
+
 extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W, fp4_dtype dt, int64_t M,
                                     int64_t K, int64_t N, const fp4_fwd_ctx* saved, float dge_k,
                                     float dge_cap, float* dW, void* workspace, size_t workspace_bytes,
@@ -597,12 +618,13 @@ extern "C" int fp4_linear_bwd_wgrad(const void* A, const void* dY, const void* W
   // as the forward pass: entries beyond what the workspaces provide for cannot exist
   const int64_t cap = occ ? std::min(saved->capacity, provisioned_entries(M, K)) : 0;
   int rc = FP4_OK;
-  if (occ)
-    rc = fp4_launch_csr_transpose(saved->row_ptr, saved->col_idx, saved->val, saved->nnz, M, K, cap,
-                                  w.t_ptr, w.t_idx, w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
+  MbArgs m = {};
+  if (occ) m = mb_args(saved->row_ptr, saved->col_idx, saved->val, M, K, cap, w.t_ptr, w.t_idx, w.t_val, w.t_scratch);
+  const bool beside = fp4_csr_fill_beside(m, N);
+  if (occ) rc = transpose_residual(saved, M, K, cap, w, m, beside, s);
   // A_c per input channel (codes [K x M/2]); dY per output channel (codes [N x M/2])
   if (!rc) rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, occ ? saved->thresholds : nullptr, token, w.qAt, w.gAk, dY, N, nullptr, w.qdYt,
-                                              w.gdYn, w.amax, false, s);
+                                              w.gdYn, w.amax, false, beside ? &m : nullptr, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {
@@ -639,8 +661,11 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   // maxima (for the weight gradient) beside it
   bool dual, known;
   const float* const thr = occ ? saved->thresholds : nullptr;
+  const int64_t cap = occ ? std::min(saved->capacity, provisioned_entries(M, K)) : 0;
+  MbArgs m = {};
+  if (occ) m = mb_args(saved->row_ptr, saved->col_idx, saved->val, M, K, cap, w.t_ptr, w.t_idx, w.t_val, w.t_scratch);
   int rc = fp4_launch_quantize_rows_absmax(dY, bf16, M, N, d.qdY, d.gdY, part, wq ? nullptr : W, K, d.qW, d.gWk, A, K, thr, token, w.amax,
-                                           &dual, &known, s);
+                                           &dual, &known, &m, s);
   if (rc) return rc;
   // activation gradient
   const uint8_t* const qW = wq ? wq->qWk : d.qW;
@@ -648,13 +673,13 @@ extern "C" int fp4_linear_bwd(const void* dY, const void* A, const void* W, cons
   rc = fp4_launch_gemm(d.qdY, d.gdY, qW, gWk, M, K, N, nullptr, dA, bf16, K, nullptr, 0, 0, nullptr, 0.0f, 0.0f, s);
   if (rc) return rc;
   // weight gradient
-  const int64_t cap = occ ? std::min(saved->capacity, provisioned_entries(M, K)) : 0;
+  const bool beside = fp4_csr_fill_beside(m, N);
   if (occ) {
-    rc = fp4_launch_csr_transpose(saved->row_ptr, saved->col_idx, saved->val, saved->nnz, M, K, cap, w.t_ptr, w.t_idx,
-                                  w.t_val, w.u_idx, w.u_val, w.t_scratch, s);
+    rc = transpose_residual(saved, M, K, cap, w, m, beside, s);
     if (rc) return rc;
   }
-  rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, thr, token, w.qAt, w.gAk, dY, N, dual ? part : nullptr, w.qdYt, w.gdYn, w.amax, known, s);
+  rc = fp4_launch_quantize_cols_pair(A, bf16, M, K, thr, token, w.qAt, w.gAk, dY, N, dual ? part : nullptr, w.qdYt, w.gdYn, w.amax, known,
+                                     beside ? &m : nullptr, s);
   if (rc) return rc;
   const float* addend = nullptr;
   if (occ) {

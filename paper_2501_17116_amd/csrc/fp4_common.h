@@ -13,6 +13,10 @@
 #define FP4_D inline
 #endif
 
+// Master types as kernel template arguments.
+struct BF16 {};
+struct F32 {};
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));

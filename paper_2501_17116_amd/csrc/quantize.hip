@@ -6,9 +6,13 @@
 // 4-byte store of codes, so a wave reads 1 KiB (bf16) contiguous and writes 256 B contiguous.
 #include "fp4_common.h"
 #include "fp4_measure.h"
+#include "csr_mask.h"
+#include "select.h"
 
 #include <mutex>
 #include <type_traits>
+
+int fp4_compute_units_of_current_device();
 
 namespace {
 
@@ -18,8 +22,6 @@ FP4_D void static_for4(F&& f) {
   f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
-struct BF16 {};
-struct F32 {};
 
 template <class DT>
 FP4_D void load8(const void* base, int64_t off, int valid, float (&v)[8]) {
@@ -897,11 +899,32 @@ struct AbsmaxTail {
   unsigned strips_a, strips;   // of a, of both
 };
 template <class DT, bool CLAMP>
-FP4_D void absmax_tail(const AbsmaxTail& t, unsigned i) {
-  __shared__ float s_m[4][64][8];
+FP4_D void absmax_tail(const AbsmaxTail& t, unsigned i, float (&s_m)[4][64][8]) {
   const unsigned strip = i % t.strips, row_block = i / t.strips;
   if (strip < t.strips_a) col_absmax_strip<DT, CLAMP>(t.a, strip, row_block, s_m);
   else col_absmax_strip<DT, false>(t.b, strip - t.strips_a, row_block, s_m);
+}
+
+// What the launch that begins a backward pass does beside its rows: that absmax pass, then (COUNT) pass 1 of the residual's transposition.
+struct RowsBeside {
+  AbsmaxTail absmax;
+  unsigned first, count_first;   // of their workgroups
+  MbArgs m;
+};
+constexpr int COUNT_MAXQ = 4096;
+template <bool COUNT>
+union BesideShared {
+  float m[4][64][8];
+  MbCountShared<COUNT ? COUNT_MAXQ : 1> count;
+};
+template <class DT, bool CLAMP, bool COUNT>
+FP4_D void rows_beside(const RowsBeside& t, unsigned i, BesideShared<COUNT>& sh) {
+  if constexpr (COUNT)
+    if (i >= t.count_first) {
+      mb_count<COUNT_MAXQ, 256>(t.m, i - t.count_first, sh.count);
+      return;
+    }
+  absmax_tail<DT, CLAMP>(t.absmax, i - t.first, sh.m);
 }
 
 // gamma[c] from the g partial rows of column maxima (bit patterns of non-negative floats order
@@ -940,8 +963,8 @@ FP4_D uint32_t pk_max_u16(uint32_t a, uint32_t b) {
 
 // The scales of a tile's columns from their partial maxima, 16 bytes a lane: every tile of a column does this again, beside its own
 // loads, where a launch in between took 3 to 5 us.  The tiles of the first row block leave the scales in memory.
-FP4_D void cols_fold(const ColArgs& a, int64_t c0, bool leave, ColShared& sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+FP4_D void cols_fold(const ColArgs& a, int64_t c0, bool leave, int tid, ColShared& sh) {
+  const int lane = tid & 63, wave = tid >> 6;
   u32x4 m = {0u, 0u, 0u, 0u};
   if (a.part16) {   // 8 lanes a row, 32 rows of partial maxima at a time
     const int l = tid & 7;
@@ -992,13 +1015,13 @@ FP4_D void cols_fold(const ColArgs& a, int64_t c0, bool leave, ColShared& sh) {
   __syncthreads();
 }
 
+// By 256 threads (tid: of them).  All tiles of a tensor meet the same barriers, also those past its last column.
 template <class DT, bool CLAMP>
-FP4_D void quantize_cols_tile(const ColArgs& a, unsigned strip, ColShared& sh) {
-  const int tid = threadIdx.x;
+FP4_D void quantize_cols_tile(const ColArgs& a, unsigned strip, unsigned row_block, int tid, ColShared& sh) {
   const int chunk = tid & 7;      // 8 columns
   const int rg = tid >> 3;        // row group 0..31 (8 rows each)
   const int64_t c0 = (int64_t)strip * CT_COLS;
-  const int64_t r0 = (int64_t)blockIdx.y * CT_ROWS;
+  const int64_t r0 = (int64_t)row_block * CT_ROWS;
   const int64_t col = c0 + chunk * 8;
   const int valid = col < a.cols ? (int)min((int64_t)8, a.cols - col) : 0;
   float lo = 0, hi = 0;
@@ -1012,7 +1035,7 @@ FP4_D void quantize_cols_tile(const ColArgs& a, unsigned strip, ColShared& sh) {
   }
   float g[8];
   if (a.parts) {
-    cols_fold(a, c0, blockIdx.y == 0, sh);
+    cols_fold(a, c0, row_block == 0, tid, sh);
 #pragma unroll
     for (int e = 0; e < 8; ++e) g[e] = sh.g[chunk * 8 + e];
   } else {
@@ -1076,8 +1099,49 @@ FP4_D void quantize_cols_tile(const ColArgs& a, unsigned strip, ColShared& sh) {
 template <class DT, bool CLAMP>
 __global__ __launch_bounds__(256) void quantize_cols_kernel(ColArgs a, ColArgs b, unsigned strips_a) {
   __shared__ ColShared sh;
-  if (blockIdx.x < strips_a) quantize_cols_tile<DT, CLAMP>(a, blockIdx.x, sh);
-  else quantize_cols_tile<DT, false>(b, blockIdx.x - strips_a, sh);
+  if (blockIdx.x < strips_a) quantize_cols_tile<DT, CLAMP>(a, blockIdx.x, blockIdx.y, threadIdx.x, sh);
+  else quantize_cols_tile<DT, false>(b, blockIdx.x - strips_a, blockIdx.y, threadIdx.x, sh);
+}
+
+// The same in workgroups of 1024 threads beside other work whose workgroups come first: `per` tiles a workgroup (1, 2 or 4; the other threads
+// leave), strips of one tensor side by side.
+struct ColsBeside {
+  ColArgs a, b;
+  unsigned groups_a, groups, per, first;
+};
+template <class DT, bool CLAMP>
+FP4_D void quantize_cols_beside(const ColsBeside& c, ColShared (&sh)[4]) {
+  const unsigned id = blockIdx.x - c.first, group = id % c.groups, row_block = id / c.groups;
+  const unsigned sub = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
+  if (sub >= c.per) return;   // whole waves: the barriers wait for those that are left
+  if (group < c.groups_a) quantize_cols_tile<DT, CLAMP>(c.a, group * c.per + sub, row_block, threadIdx.x & 255, sh[sub]);
+  else quantize_cols_tile<DT, false>(c.b, (group - c.groups_a) * c.per + sub, row_block, threadIdx.x & 255, sh[sub]);
+}
+
+// Beside pass 3 of the residual's transposition (csr_mask.h).
+template <class DT, int QMAX, MbFrom FROM>
+__global__ __launch_bounds__(MB_THREADS) void quantize_cols_fill_kernel(ColsBeside c, MbArgs m) {
+  union Shared {
+    ColShared cols[4];
+    MbFillShared<QMAX, FROM> fill;
+  };
+  static_assert(MB_THREADS == 1024, "four tiles");
+  __shared__ Shared sh;
+  if (blockIdx.x < c.first) mb_fill<QMAX, FROM>(m, blockIdx.x, sh.fill);
+  else quantize_cols_beside<DT, true>(c, sh.cols);
+}
+
+// Beside the first digit pass over another tensor (select.h).
+template <class DT>
+__global__ __launch_bounds__(SEL_THREADS) void quantize_cols_select_kernel(ColsBeside c, SelFirst f) {
+  union Shared {
+    ColShared cols[4];
+    SelTable<DT, 0> table;
+  };
+  static_assert(SEL_THREADS == 1024, "four tiles");
+  __shared__ Shared sh;
+  if (blockIdx.x < c.first) sel_hist<DT, 0, false>(f.x, f.rows, f.cols, f.ld, Ranks{}, nullptr, f.hist, nullptr, blockIdx.x, c.first, sh.table);
+  else quantize_cols_beside<DT, false>(c, sh.cols);
 }
 
 // The tiles fold the partial maxima themselves while all of them together read no more than 128 MiB for it, from L2.  Pass in us with
@@ -1098,6 +1162,22 @@ inline bool fold_in_tiles(int64_t rows, int64_t cols, int64_t parts, int bytes, 
 
 inline unsigned ca_strips(int64_t cols) { return (unsigned)(((cols + 7) / 8 + 63) / 64); }
 inline unsigned ct_strips(int64_t cols) { return (unsigned)((cols + CT_COLS - 1) / CT_COLS); }
+
+// How many tiles a workgroup has beside `first` others, as few as leave all workgroups on the chip at once, two a CU; 0: there are more
+// with four.  The fewer, the more CUs have a share of the reads.
+unsigned cols_beside_per(int64_t rows, int64_t cols_a, int64_t cols_b, unsigned first) {
+  for (unsigned per = 1; per <= 4; per *= 2) {
+    const int64_t groups = (ct_strips(cols_a) + per - 1) / per + (ct_strips(cols_b) + per - 1) / per;
+    if (first + groups * ((rows + CT_ROWS - 1) / CT_ROWS) <= 2 * fp4_compute_units_of_current_device()) return per;
+  }
+  return 0;
+}
+ColsBeside cols_beside(const ColArgs& a, const ColArgs& b, unsigned first) {
+  ColsBeside c = {a, b, 0, 0, cols_beside_per(a.rows, a.cols, b.x ? b.cols : 0, first), first};
+  c.groups_a = (ct_strips(a.cols) + c.per - 1) / c.per;
+  c.groups = c.groups_a + (b.x ? (ct_strips(b.cols) + c.per - 1) / c.per : 0);
+  return c;
+}
 
 // The scales, where the tiles don't form them themselves.
 void launch_amax_to_gamma(ColArgs& a, int parts, bool alone, hipStream_t s) {
@@ -1138,15 +1218,15 @@ FP4_D uint32_t max_without_nan(uint32_t m, uint32_t pair) {
   return pk_max_u16(m, (lo > 0x7f80u ? 0u : lo) | (hi > 0x7f800000u ? 0u : hi));
 }
 
-template <int NV, bool CLAMP>
+template <int NV, bool CLAMP, bool COUNT>
 __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                    int64_t cols, int64_t ld, uint8_t* __restrict__ codes,
                                                                    float* __restrict__ gamma, uint16_t* __restrict__ part, int per, unsigned blocks,
                                                                    const uint16_t* __restrict__ y, int64_t rows_y, uint8_t* __restrict__ codes_y,
-                                                                   float* __restrict__ gamma_y, int per_y, unsigned blocks_rows,
-                                                                   AbsmaxTail tail) {
-  if (blockIdx.x >= blocks_rows) {
-    absmax_tail<BF16, CLAMP>(tail, blockIdx.x - blocks_rows);
+                                                                   float* __restrict__ gamma_y, int per_y, RowsBeside beside) {
+  __shared__ BesideShared<COUNT> sh;
+  if (blockIdx.x >= beside.first) {
+    rows_beside<BF16, CLAMP, COUNT>(beside, blockIdx.x, sh);
     return;
   }
   __shared__ float s_max[2][4];
@@ -1294,9 +1374,10 @@ unsigned absmax_layout(ColArgs& a, ColArgs& b, uint32_t* amax) {
   return (unsigned)((a.rows + a.row_block - 1) / a.row_block);
 }
 
-// b.x null: a alone.  b.part16 set: b's maxima are known (b.parts rows of them).  known: the absmax pass is done.
+// b.x null: a alone.  b.part16 set: b's maxima are known (b.parts rows of them).  known: the absmax pass is done.  m: a transposition
+// whose pass 3 goes with the last launch (b.x and a.thr set), or null.  f: likewise a selection's first pass (a alone, no clamp).
 template <class DT, bool CLAMP>
-int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, hipStream_t s) {
+int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, const MbArgs* m, const SelFirst* f, hipStream_t s) {
   const bool b_max = b.x && !b.part16;
   const int rblocks = (int)absmax_layout(a, b, amax);
   if (!known)
@@ -1305,27 +1386,62 @@ int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, hipStream_t s)
   launch_amax_to_gamma(a, rblocks, !b.x, s);
   if (b_max) launch_amax_to_gamma(b, rblocks, false, s);
   else if (b.x) launch_amax16_to_gamma(b, s);
-  hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>),
-                     dim3(ct_strips(a.cols) + (b.x ? ct_strips(b.cols) : 0), (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS)), dim3(256), 0, s, a, b,
+  const unsigned row_blocks = (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS);
+  if constexpr (CLAMP) {
+    if (m) {
+      const ColsBeside c = cols_beside(a, b, mb_fill_blocks(m->nblocks));
+      auto go = [&](auto qmax, auto from) {
+        hipLaunchKernelGGL((quantize_cols_fill_kernel<DT, decltype(qmax)::value, decltype(from)::value>), dim3(c.first + c.groups * row_blocks),
+                           dim3(MB_THREADS), 0, s, c, *m);
+      };
+      auto width = [&](auto from) {
+        if (m->Q <= 4096) go(std::integral_constant<int, 4096>{}, from);
+        else go(std::integral_constant<int, 8192>{}, from);
+      };
+      if (m->from == MbFrom::FEW) width(std::integral_constant<MbFrom, MbFrom::FEW>{});
+      else width(std::integral_constant<MbFrom, MbFrom::SCAN>{});
+      FP4_CHECK_LAUNCH();
+      return FP4_OK;
+    }
+  } else if (f) {
+    const ColsBeside c = cols_beside(a, b, sel_blocks(f->rows * f->cols));
+    hipLaunchKernelGGL((quantize_cols_select_kernel<DT>), dim3(c.first + c.groups * row_blocks), dim3(SEL_THREADS), 0, s, c, *f);
+    FP4_CHECK_LAUNCH();
+    return FP4_OK;
+  }
+  hipLaunchKernelGGL((quantize_cols_kernel<DT, CLAMP>), dim3(ct_strips(a.cols) + (b.x ? ct_strips(b.cols) : 0), row_blocks), dim3(256), 0, s, a, b,
                      ct_strips(a.cols));
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
 
 // Rows by themselves, two tensors of them, and the absmax pass of tensors that are quantized by columns later.
-template <class DT, int TPR, int NV, bool CLAMP>
-__global__ __launch_bounds__(256) void quantize_rows_absmax_kernel(RowArgs a, unsigned blocks_rows, AbsmaxTail tail) {
-  if (blockIdx.x < blocks_rows) quantize_rows_block<DT, false, TPR, NV>(a);
-  else absmax_tail<DT, CLAMP>(tail, blockIdx.x - blocks_rows);
+template <class DT, int TPR, int NV, bool CLAMP, bool COUNT>
+__global__ __launch_bounds__(256) void quantize_rows_absmax_kernel(RowArgs a, RowsBeside beside) {
+  __shared__ BesideShared<COUNT> sh;
+  if (blockIdx.x < beside.first) quantize_rows_block<DT, false, TPR, NV>(a);
+  else rows_beside<DT, CLAMP, COUNT>(beside, blockIdx.x, sh);
+}
+
+// The workgroups that a launch of `blocks` for its rows has in all, and whether pass 1 of the transposition goes along: where all of
+// them find room on the chip at once, four a CU with the masks' 33 KiB of LDS.
+unsigned beside_blocks(RowsBeside& t, unsigned blocks, unsigned blocks_tail, MbArgs* m) {
+  t.first = blocks;
+  t.count_first = blocks + blocks_tail;
+  if (!m || m->nblocks == 0 || m->Q > COUNT_MAXQ || (int64_t)t.count_first + m->nblocks > 4 * fp4_compute_units_of_current_device()) return t.count_first;
+  t.m = *m;
+  m->counted = true;
+  return t.count_first + (unsigned)m->nblocks;
 }
 
 template <class DT>
-int launch_rows_absmax(const RowArgs& a, const AbsmaxTail& t, unsigned blocks_tail, hipStream_t s) {
+int launch_rows_absmax(const RowArgs& a, RowsBeside& t, unsigned blocks_tail, MbArgs* m, hipStream_t s) {
   rows_shape(a.cols, [&](auto tpr, auto nv) {
     constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
-    const unsigned blocks = (unsigned)((a.rows + a.rows2 + 256 / TPR - 1) / (256 / TPR));
-    if (t.a.thr) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true>), dim3(blocks + blocks_tail), dim3(256), 0, s, a, blocks, t);
-    else hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, false>), dim3(blocks + blocks_tail), dim3(256), 0, s, a, blocks, t);
+    const unsigned blocks = beside_blocks(t, (unsigned)((a.rows + a.rows2 + 256 / TPR - 1) / (256 / TPR)), blocks_tail, m);
+    if (m && m->counted) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, true>), dim3(blocks), dim3(256), 0, s, a, t);
+    else if (t.absmax.a.thr) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, false>), dim3(blocks), dim3(256), 0, s, a, t);
+    else hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, false, false>), dim3(blocks), dim3(256), 0, s, a, t);
   });
   FP4_CHECK_LAUNCH();
   return FP4_OK;
@@ -1642,13 +1758,14 @@ int64_t fp4_dual_axis_part_elems(int64_t rows, int64_t cols) {
 // What the backward pass of a layer begins with, in one launch: dY [rows x cols] by rows (codes, gamma), W (y; null: none) [rows_y x cols]
 // by rows, and the column maxima that fp4_launch_quantize_cols_pair(known) goes on with: dY's as rows of part16 where the dual-axis
 // pass covers it (bf16, cols at most 16384: *dual), otherwise in amax_scratch, beside those of A (z) [rows x cols_z], clamped at clamp_thr; *known
-// tells whether they are there.
+// tells whether they are there.  m: a transposition whose pass 1 goes along where there is room (m->counted tells), or null.
 int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64_t cols, uint8_t* codes, float* gamma, uint16_t* part16,
                                     const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, const void* z, int64_t cols_z,
-                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, hipStream_t s) {
+                                    const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, MbArgs* m, hipStream_t s) {
   if (rows == 0 || cols == 0 || cols_z == 0 || cols % 8 != 0) return FP4_ERR_SHAPE;
   *dual = bf16 && cols <= 256 * 8 * 8;
-  AbsmaxTail t = {};
+  RowsBeside beside = {};
+  AbsmaxTail& t = beside.absmax;
   t.a.x = z; t.a.thr = clamp_thr; t.a.thr_stride = per_row_thr ? 2 : 0;
   t.a.rows = rows; t.a.cols = cols_z; t.a.ld = cols_z;
   t.b.x = x; t.b.part16 = *dual ? part16 : nullptr;
@@ -1665,23 +1782,27 @@ int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64
     const int64_t nunits = cols / 8;
     const int per = da_rows(rows, cols), per_y = 4;   // nothing is folded over y's rows, so few are as good
     const unsigned blocks = (unsigned)((rows + per - 1) / per), blocks_y = y ? (unsigned)((rows_y + per_y - 1) / per_y) : 0;
-    auto go = [&](auto nv, auto clamp) {
-      hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value, decltype(clamp)::value>), dim3(blocks + blocks_y + blocks_tail), dim3(256),
+    const unsigned grid = beside_blocks(beside, blocks + blocks_y, blocks_tail, clamp_thr ? m : nullptr);
+    auto go = [&](auto nv, auto clamp, auto count) {
+      hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value, decltype(clamp)::value, decltype(count)::value>), dim3(grid), dim3(256),
                          0, s, reinterpret_cast<const uint16_t*>(x), rows, cols, cols, codes, gamma, part16, per, blocks,
-                         reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y, blocks + blocks_y, t);
+                         reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y, beside);
     };
-    auto width = [&](auto clamp) {
-      if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{}, clamp);
-      else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{}, clamp);
-      else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{}, clamp);
-      else go(std::integral_constant<int, 8>{}, clamp);
+    auto width = [&](auto clamp, auto count) {
+      if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{}, clamp, count);
+      else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{}, clamp, count);
+      else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{}, clamp, count);
+      else go(std::integral_constant<int, 8>{}, clamp, count);
     };
-    if (clamp_thr) width(std::true_type{}); else width(std::false_type{});
+    if (m && m->counted) width(std::true_type{}, std::true_type{});
+    else if (clamp_thr) width(std::true_type{}, std::false_type{});
+    else width(std::false_type{}, std::false_type{});
   } else {
     RowArgs a = {};
     a.x = x; a.codes = codes; a.gamma = gamma; a.rows = rows; a.cols = cols; a.ld = cols;
     if (y) { a.x2 = y; a.codes2 = codes_y; a.gamma2 = gamma_y; a.rows2 = rows_y; }
-    const int rc = bf16 ? launch_rows_absmax<BF16>(a, t, blocks_tail, s) : launch_rows_absmax<F32>(a, t, blocks_tail, s);
+    const int rc = bf16 ? launch_rows_absmax<BF16>(a, beside, blocks_tail, clamp_thr ? m : nullptr, s)
+                        : launch_rows_absmax<F32>(a, beside, blocks_tail, clamp_thr ? m : nullptr, s);
     if (rc) return rc;
   }
   FP4_CHECK_LAUNCH();
@@ -1736,25 +1857,39 @@ int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const 
   return FP4_OK;
 }
 
+// Whether a selection's first digit pass goes with the column-wise quantization of a tensor, by the same line.
+bool fp4_select_first_beside(const SelFirst& f, int64_t rows, int64_t cols) { return cols_beside_per(rows, cols, 0, sel_blocks(f.rows * f.cols)) > 0; }
+
+// first: a selection's first digit pass that goes with the last launch (fp4_select_first_beside; no clamp), or null.
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
-                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words) {
+                             uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words, const SelFirst* first) {
   if (rows == 0 || cols == 0) return FP4_OK;
+  if (first && (clamp_thr || !fp4_select_first_beside(*first, rows, cols))) return FP4_ERR_ARG;
   ColArgs a = {};
   a.clear = reinterpret_cast<unsigned long long*>(clear); a.clear_words = clear_words;
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
   a.thr_stride = per_row_thr ? 2 : 0;
   a.rows = rows; a.cols = cols; a.ld = ld;
-  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, {}, amax_scratch, false, s) : launch_cols<F32, true>(a, {}, amax_scratch, false, s);
-  return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, false, s) : launch_cols<F32, false>(a, {}, amax_scratch, false, s);
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, {}, amax_scratch, false, nullptr, nullptr, s) : launch_cols<F32, true>(a, {}, amax_scratch, false, nullptr, nullptr, s);
+  return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, false, nullptr, first, s) : launch_cols<F32, false>(a, {}, amax_scratch, false, nullptr, first, s);
+}
+
+// Whether pass 3 of a transposition goes with the column-wise quantization of a weight gradient's operands (m.rows rows, m.Q and cols_y
+// columns): where all workgroups find room on the chip at once, two a CU.  Either has so little to do there that it waits for memory most of
+// the time (fill and quantization by themselves / beside each other, us: 1056 x (1376 + 2080) 15.2 + 8.6 / 15.1, fp32 2048 x (2048 + 2048) 9.9 + 10.8 /
+// 13.6); with more of them the tiles, four a workgroup, take as long as the two launches (8192 x (2048 + 2048) 10.0 + 26.8 / 37.5) or
+// longer (8192 x (2048 + 5504) 10.6 + 38.2 / 58.1, 16384 x (4096 + 12288) 24.8 + 148.5 / 195).
+bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y) {
+  return m.nblocks > 0 && m.Q <= 8192 && m.from != MbFrom::TABLE && cols_beside_per(m.rows, m.Q, cols_y, mb_fill_blocks(m.nblocks)) > 0;
 }
 
 // The weight gradient's operands, x [rows x cols] (clamped) and y [rows x cols_y], in as many launches as one of them takes.  part_y:
 // y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.  known:
-// fp4_launch_quantize_rows_absmax has left the maxima in it.
+// fp4_launch_quantize_rows_absmax has left the maxima in it.  m: a transposition whose pass 3 goes along (fp4_csr_fill_beside, a clamp), or null.
 int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t cols, const float* clamp_thr, int per_row_thr,
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
-                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, hipStream_t s) {
+                                  uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, const MbArgs* m, hipStream_t s) {
   if (rows == 0 || cols == 0 || cols_y == 0) return FP4_ERR_SHAPE;
   ColArgs a = {}, b = {};
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
@@ -1763,8 +1898,9 @@ int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t
   b.x = y; b.codes_t = codes_y; b.gamma = gamma_y; b.part16 = part_y;
   b.rows = rows; b.cols = cols_y; b.ld = cols_y;
   if (part_y) b.parts = (int)((rows + da_rows(rows, cols_y) - 1) / da_rows(rows, cols_y));
-  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, b, amax_scratch, known, s) : launch_cols<F32, true>(a, b, amax_scratch, known, s);
-  return bf16 ? launch_cols<BF16, false>(a, b, amax_scratch, known, s) : launch_cols<F32, false>(a, b, amax_scratch, known, s);
+  if (m && !(clamp_thr && fp4_csr_fill_beside(*m, cols_y))) return FP4_ERR_ARG;
+  if (clamp_thr) return bf16 ? launch_cols<BF16, true>(a, b, amax_scratch, known, m, nullptr, s) : launch_cols<F32, true>(a, b, amax_scratch, known, m, nullptr, s);
+  return bf16 ? launch_cols<BF16, false>(a, b, amax_scratch, known, nullptr, nullptr, s) : launch_cols<F32, false>(a, b, amax_scratch, known, nullptr, nullptr, s);
 }
 
 int fp8_launch_quantize_rows(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, uint8_t* codes,
@@ -1828,7 +1964,7 @@ extern "C" int fp4_quantize(const void* x, fp4_dtype dt, int64_t rows, int64_t c
     return fp4_launch_quantize_rows_fixed(x, dt == FP4_BF16, rows, cols, ld, gamma, codes, nullptr, (hipStream_t)stream);
   }
   return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma,
-                                  reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream, nullptr, 0);
+                                  reinterpret_cast<uint32_t*>(workspace), (hipStream_t)stream, nullptr, 0, nullptr);
 }
 
 // ---- the entry point that allocates nothing -----------------------------------------------------
@@ -1873,7 +2009,7 @@ extern "C" int fp4_quantize_noalloc(const void* x, fp4_dtype dt, int64_t rows, i
   if (rc) return rc;
   // every word the scale kernel reads is written by the maxima kernel of the same call first, so
   // what an earlier call left behind is never seen and nothing has to be cleared
-  return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma, sp, (hipStream_t)stream, nullptr, 0);
+  return fp4_launch_quantize_cols(x, dt == FP4_BF16, rows, cols, ld, nullptr, 0, codes, gamma, sp, (hipStream_t)stream, nullptr, 0, nullptr);
 }
 
 extern "C" int fp4_dge_apply(const float* G, const void* W, fp4_dtype dt, const float* gamma_W,

@@ -20,6 +20,7 @@
 // stall their workgroup; they are left out of the tiled kernel and multiplied eight at a time as a dense matrix.
 #include "fp4_common.h"
 #include "fp4_measure.h"
+#include "csr_mask.h"
 #include "spmm_long.h"
 
 #include <algorithm>
@@ -27,8 +28,6 @@
 
 namespace {
 
-struct BF16 {};
-struct F32 {};
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SP_ROWS = 1024;   // output rows per workgroup = threads, where there are rows enough
@@ -762,231 +761,22 @@ __global__ __launch_bounds__(256) void csr_transpose_fill_kernel(const int64_t* 
   }
 }
 
-// ---- transpose as a stable counting sort on the column (column range fits the LDS masks) ---------
-// The rows are cut into blocks of 64 (32, mb_rows).  Inside a block, column c's entries are described by a 64-bit
-// mask of the rows that hold one (built with LDS atomic ORs: the result does not depend on their
-// order).  Pass 1 writes the population count of every mask, cnt8[block][c].  Pass 2 scans those
-// counts over the blocks of each column (exclusive, ex[block][c]) and leaves the column totals.
-// After the scan of the totals into t_ptr, pass 3 rebuilds the masks and places entry (r, c) at
-//   t_ptr[c] + ex[block][c] + popcount(mask[c] below bit r - r0),
-// i.e. behind every entry of the column from an earlier row: the transposed matrix comes out with
-// ascending indices inside every segment, without global atomics and without an ordering pass.
-// Rows per block = bits per mask: 64, above 8192 columns 32, whose masks leave the LDS room for the columns' positions.
-constexpr int mb_rows(int64_t Q) { return Q > 8192 ? 32 : 64; }
-constexpr int MB_THREADS = 1024;   // per workgroup in the two passes that walk entries: they are latency-bound
-constexpr int MB_MAXQ = 16384;       // columns whose masks and positions (4 bytes each) fit 128 KiB of LDS
-
-// first (entry offset, row) bookkeeping shared by pass 1 and pass 3: s_rp[0..MB_ROWS] = clipped row starts
-template <int MB_ROWS>
-FP4_D void mb_load_rows(const int64_t* row_ptr, int64_t rows, int64_t capacity, int64_t r0, long long* s_rp) {
-  if (threadIdx.x <= MB_ROWS) {
-    const int64_t r = min(r0 + (int64_t)threadIdx.x, rows);
-    s_rp[threadIdx.x] = min(row_ptr[r], capacity);
-  }
-}
-// row of entry e of the block: the last i with s_rp[i] <= e
-template <int MB_ROWS>
-FP4_D int mb_row_of(const long long* s_rp, long long e) {
-  int lo = 0, hi = MB_ROWS;   // invariant: s_rp[lo] <= e < s_rp[hi]
-#pragma unroll
-  for (int it = 0; (1 << it) < MB_ROWS; ++it) {
-    const int mid = (lo + hi) >> 1;
-    if (s_rp[mid] <= e) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// sets, for every entry e of the block's range [b, e_end), bit (row of e) of its column's mask; four
-// column loads a thread in flight
-template <int MB_ROWS>
-FP4_D void mb_build_masks(const int32_t* col_idx, const long long* s_rp, long long b, long long e_end, uint32_t* mb_mask) {
-  for (long long i0 = b + threadIdx.x; i0 < e_end; i0 += 4 * MB_THREADS) {
-    int32_t c[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const long long i = i0 + (long long)u * MB_THREADS;
-      c[u] = i < e_end ? col_idx[i] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (c[u] < 0) continue;
-      const int r = mb_row_of<MB_ROWS>(s_rp, i0 + (long long)u * MB_THREADS);
-      atomicOr(&mb_mask[MB_ROWS / 32 * c[u] + (r >> 5)], 1u << (r & 31));
-    }
-  }
-}
-
+// ---- transpose as a stable counting sort on the column (csr_mask.h), its three passes by themselves -------------------------
 template <int QMAX>   // columns the LDS masks are laid out for (the launcher picks the smallest that fits)
-__global__ __launch_bounds__(MB_THREADS) void csr_mask_count_kernel(const int64_t* row_ptr, const int32_t* col_idx,
-                                                             int64_t rows, int64_t Q, int64_t capacity,
-                                                             uint8_t* cnt8) {
-  constexpr int MB_ROWS = mb_rows(QMAX), MW = MB_ROWS / 32;
-  __shared__ uint32_t mb_mask[MW * QMAX];   // rows 0..31 of the block in the first of a column's words
-  __shared__ long long s_rp[MB_ROWS + 1];
-  const int64_t r0 = (int64_t)blockIdx.x * MB_ROWS;
-  for (int i = threadIdx.x; i < MW * Q; i += MB_THREADS) mb_mask[i] = 0;
-  mb_load_rows<MB_ROWS>(row_ptr, rows, capacity, r0, s_rp);
-  __syncthreads();
-  const long long b = s_rp[0], e = s_rp[MB_ROWS];
-  mb_build_masks<MB_ROWS>(col_idx, s_rp, b, e, mb_mask);
-  __syncthreads();
-  uint8_t* out = cnt8 + (int64_t)blockIdx.x * Q;
-  for (int c = threadIdx.x; c < Q; c += MB_THREADS) out[c] = (uint8_t)(__popc(mb_mask[MW * c]) + (MW > 1 ? __popc(mb_mask[MW * c + MW - 1]) : 0));
+__global__ __launch_bounds__(MB_THREADS) void csr_mask_count_kernel(MbArgs m) {
+  __shared__ MbCountShared<QMAX> sh;
+  mb_count<QMAX, MB_THREADS>(m, blockIdx.x, sh);
 }
 
-// 64 columns per workgroup; the four waves split the blocks into quarters: sum, exchange, rescan.
-__global__ __launch_bounds__(256) void csr_mask_scan_kernel(const uint8_t* cnt8, int nblocks, int64_t Q,
-                                                            uint32_t* ex, int32_t* cnt) {
-  __shared__ uint32_t s_q[4][64];
-  const int lane = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
-  const int per = (nblocks + 3) / 4;
-  const int b0 = quarter * per, b1 = min(nblocks, b0 + per);
-  uint32_t sum = 0;
-  if (c < Q) {
-    int bi = b0;
-    for (; bi + 15 < b1; bi += 16) {   // sixteen independent loads at a time
-      uint32_t v[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = cnt8[(int64_t)(bi + j) * Q + c];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sum += v[j];
-    }
-    for (; bi < b1; ++bi) sum += cnt8[(int64_t)bi * Q + c];
-  }
-  s_q[quarter][lane] = sum;
-  __syncthreads();
-  if (c >= Q) return;
-  uint32_t run = 0;
-  for (int q = 0; q < quarter; ++q) run += s_q[q][lane];
-  if (quarter == 3) cnt[c] = (int32_t)(run + sum);
-  int bi = b0;
-  for (; bi + 15 < b1; bi += 16) {
-    uint32_t v[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = cnt8[(int64_t)(bi + j) * Q + c];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) { ex[(int64_t)(bi + j) * Q + c] = run; run += v[j]; }
-  }
-  for (; bi < b1; ++bi) { ex[(int64_t)bi * Q + c] = run; run += cnt8[(int64_t)bi * Q + c]; }
+__global__ __launch_bounds__(256) void csr_mask_scan_kernel(MbArgs m) {
+  __shared__ MbScanShared sh;
+  mb_scan(m, blockIdx.x, threadIdx.x, sh);
 }
-
-// Where pass 3 takes the positions from.  FEW: from the counts of all row blocks, at most MB_FEW_BYTES of them in MB_FEW_BLOCKS, which
-// every workgroup adds up for itself, sixteen blocks at a time: as many rows of counts take as many round trips however few the
-// columns are (fill alone, FEW / as SCAN with its launch before it, us: 16384 x 128 15 / 10, 65536 x 64 123 / 22, 131072 x 32 477 / 38; whole
-// weight gradients with 64 blocks 53.6 / 53.9, with 128 51.5 / 50.5).  SCAN: from pass 2's ex and totals, which every workgroup scans over the columns.  Either way
-// a column's position waits in LDS beside its mask, and the workgroup of the first row block writes t_ptr.  TABLE: with 2^32
-// elements or more positions have no room in 32 bits; t_ptr comes from a scan of its own.  Bound by round trips to memory, so by the
-// launches and by what a workgroup asks for one after another.
-// Whole transposition at 2 % (count, scan over blocks, scan over columns and fill as four launches / now): 256 x 512 12.3 / 8.2 us,
-// 1056 x 1376 at 6 % 28.7 / 19.3, 2048 x 2048 22.2 / 14.9, 8192 x 2048 25.0 / 19.3, 16384 x 4096 46.3 / 38.1,
-// 16384 x 11008 the fill alone (blocks of 64 rows, from a table / of 32) 156 / 98.
-enum class MbFrom { FEW = 1, SCAN, TABLE };
-constexpr int64_t MB_FEW_BYTES = 64 * 1024, MB_FEW_BLOCKS = 64;
 
 template <int QMAX, MbFrom FROM>
-__global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(const int64_t* row_ptr, const int32_t* col_idx,
-                                                            const float* val, int64_t rows, int64_t Q,
-                                                            int64_t capacity, int64_t* t_ptr, const uint32_t* ex, const int32_t* cnt,
-                                                            const uint8_t* cnt8, int32_t* t_idx, float* t_val) {
-  constexpr bool TABLE = FROM == MbFrom::TABLE;
-  constexpr int MB_ROWS = mb_rows(QMAX), MW = MB_ROWS / 32;
-  constexpr int PER = QMAX / MB_THREADS;   // consecutive columns a thread forms positions of: a multiple of 4
-  __shared__ uint32_t mb_mask[MW * QMAX];
-  __shared__ long long s_rp[MB_ROWS + 1];
-  __shared__ uint32_t s_pos[TABLE ? 1 : QMAX];   // fewer than 2^32 entries (the launcher's rule)
-  __shared__ uint32_t s_w[MB_THREADS / 64];
-  // Each XCD takes a contiguous run of row blocks.  A block has one or two entries of a column, and its neighbours' lie beside
-  // them: written from eight L2s they were partial lines of every one, from one L2 they are whole (16384 x 4096 at 2 %: 48.9
-  // -> 29.3 us).
-  const int nblocks = (int)((rows + MB_ROWS - 1) / MB_ROWS), per_xcd = (nblocks + 7) / 8;
-  const int block = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if ((int)(blockIdx.x / 8) >= per_xcd || block >= nblocks) return;
-  const int64_t r0 = (int64_t)block * MB_ROWS;
-  const int c0 = (int)threadIdx.x * PER;
-  uint32_t before[PER] = {}, total[PER] = {}, sum = 0, incl = 0;   // a column's entries in earlier blocks, and all of them
-  mb_load_rows<MB_ROWS>(row_ptr, rows, capacity, r0, s_rp);
-  for (int i = threadIdx.x; i < MW * Q; i += MB_THREADS) mb_mask[i] = 0;
-  if constexpr (!TABLE) {
-#pragma unroll
-    for (int j = 0; j < PER; j += 4) {   // Q is a multiple of 4
-      if (c0 + j >= Q) break;
-      if constexpr (FROM == MbFrom::FEW) {
-#pragma unroll 16
-        for (int b = 0; b < nblocks; ++b) {
-          const uint32_t four = *reinterpret_cast<const uint32_t*>(cnt8 + (int64_t)b * Q + c0 + j);
-          const uint32_t early = b < block ? four : 0;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            before[j + q] += (early >> (8 * q)) & 0xffu;
-            total[j + q] += (four >> (8 * q)) & 0xffu;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          before[j + q] = ex[(int64_t)block * Q + c0 + j + q];
-          total[j + q] = (uint32_t)cnt[c0 + j + q];
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) sum += total[j];
-    incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t up = __shfl_up(incl, o, 64);
-      if ((int)(threadIdx.x & 63) >= o) incl += up;
-    }
-    if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = incl;
-  }
-  __syncthreads();
-  if constexpr (!TABLE) {
-    uint32_t at = incl - sum;
-    for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) at += s_w[w];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      if (c0 + j >= Q) break;
-      s_pos[c0 + j] = at + before[j];
-      at += total[j];
-      if (block == 0) t_ptr[c0 + j + 1] = at;
-    }
-    if (block == 0 && threadIdx.x == 0) t_ptr[0] = 0;
-  }
-  const long long b = s_rp[0], e = s_rp[MB_ROWS];
-  mb_build_masks<MB_ROWS>(col_idx, s_rp, b, e, mb_mask);
-  __syncthreads();
-  // Placement, four entries a thread at a time: the steps of the chain column -> position -> store that go to memory are round
-  // trips, so the four chains run side by side.
-  const uint32_t* exb = ex + (int64_t)block * Q;
-  for (long long i0 = b + threadIdx.x; i0 < e; i0 += 4 * MB_THREADS) {
-    int32_t c[4];
-    float v[4];
-    int64_t pos[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const long long i = i0 + (long long)u * MB_THREADS;
-      c[u] = i < e ? col_idx[i] : -1;
-      v[u] = i < e ? val[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if constexpr (TABLE) pos[u] = c[u] >= 0 ? t_ptr[c[u]] + exb[c[u]] : capacity;
-      else pos[u] = c[u] >= 0 ? (int64_t)s_pos[c[u]] : capacity;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (c[u] < 0) continue;
-      const int r = mb_row_of<MB_ROWS>(s_rp, i0 + (long long)u * MB_THREADS);
-      const uint32_t lo = mb_mask[MW * c[u]], hi = mb_mask[MW * c[u] + MW - 1];
-      const uint32_t below = r < 32 ? __popc(lo & ((1u << r) - 1u)) : __popc(lo) + __popc(hi & ((1u << (r - 32)) - 1u));
-      const int64_t p = pos[u] + below;
-      if (p < capacity) {
-        t_idx[p] = (int32_t)(r0 + r);
-        t_val[p] = v[u];
-      }
-    }
-  }
+__global__ __launch_bounds__(MB_THREADS) void csr_mask_fill_kernel(MbArgs m) {
+  __shared__ MbFillShared<QMAX, FROM> sh;
+  mb_fill<QMAX, FROM>(m, blockIdx.x, sh);
 }
 
 // Order every segment by index (the indices inside a segment are distinct): an entry's final
@@ -1167,9 +957,8 @@ int fp4_launch_spmm(const int64_t* row_ptr, const int32_t* col_idx, const float*
 
 int fp4_launch_scan_rows(const int32_t* row_cnt, int64_t rows, int64_t* row_ptr, int64_t* nnz, hipStream_t s);
 
-// int32 words of scratch the transpose of a P x Q matrix needs.  Mask path (Q <= MB_MAXQ):
-// cnt[Q], ex[blocks][Q] (uint32), cnt8[blocks][Q] (bytes).  Otherwise: cnt[Q], cursor[Q].
-// A matrix too wide for the masks counts as the widest that is not, or a wider one would need less.
+// int32 words of scratch the transpose of a P x Q matrix needs.  Mask path (Q <= MB_MAXQ): cnt[Q], ex[blocks][Q] (uint32), cnt8[blocks][Q]
+// (bytes).  Otherwise: cnt[Q], cursor[Q].  A matrix too wide for the masks counts as the widest that is not, or a wider one would need less.
 int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
   const int64_t columns = 2 * Q;
   Q = std::min<int64_t>(Q, MB_MAXQ);
@@ -1177,58 +966,51 @@ int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
   return std::max(columns, Q + 64 + blocks * Q + (blocks * Q + 3) / 4 + 64);
 }
 
+int fp4_csr_transpose_from(int64_t P, int64_t Q) { return (int)mb_from(P, Q); }
+
+// The passes that other launches have not taken along (m.counted, m.scanned; m.nblocks > 0).
+int fp4_launch_csr_mask(const MbArgs& m, bool fill_too, hipStream_t s) {
+  using Q4 = std::integral_constant<int, 4096>;
+  using Q8 = std::integral_constant<int, 8192>;
+  using Q16 = std::integral_constant<int, MB_MAXQ>;
+  auto width = [&](auto go) {
+    if (m.Q <= 4096) go(Q4{}); else if (m.Q <= 8192) go(Q8{}); else go(Q16{});
+  };
+  if (!m.counted)
+    width([&](auto q) { hipLaunchKernelGGL((csr_mask_count_kernel<decltype(q)::value>), dim3(m.nblocks), dim3(MB_THREADS), 0, s, m); });
+  if (m.from != MbFrom::FEW && !m.scanned)
+    hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((m.Q + 63) / 64)), dim3(256), 0, s, m);
+  FP4_CHECK_LAUNCH();
+  if (!fill_too) return FP4_OK;
+  if (m.from == MbFrom::TABLE) {
+    const int rc = fp4_launch_scan_rows(m.cnt, m.Q, m.t_ptr, nullptr, s);
+    if (rc) return rc;
+  }
+  auto fill = [&](auto from) {
+    width([&](auto q) {
+      hipLaunchKernelGGL((csr_mask_fill_kernel<decltype(q)::value, decltype(from)::value>), dim3(mb_fill_blocks(m.nblocks)), dim3(MB_THREADS), 0, s,
+                         m);
+    });
+  };
+  if (m.from == MbFrom::FEW) fill(std::integral_constant<MbFrom, MbFrom::FEW>{});
+  else if (m.from == MbFrom::SCAN) fill(std::integral_constant<MbFrom, MbFrom::SCAN>{});
+  else fill(std::integral_constant<MbFrom, MbFrom::TABLE>{});
+  FP4_CHECK_LAUNCH();
+  return FP4_OK;
+}
+
 // u_idx/u_val: unordered staging, capacity entries each (only the path for very wide matrices uses it)
 // from: a MbFrom, or 0 for that of the sizes
-static int64_t mb_blocks(int64_t P, int64_t Q) { return std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q)); }
-static bool mb_positions(int64_t P, int64_t Q) { return Q % 4 == 0 && P * Q < ((int64_t)1 << 32); }
-int fp4_csr_transpose_from(int64_t P, int64_t Q) {
-  if (Q > MB_MAXQ) return 0;   // no masks
-  if (!mb_positions(P, Q)) return (int)MbFrom::TABLE;
-  const int64_t blocks = mb_blocks(P, Q);
-  return (int)(blocks <= MB_FEW_BLOCKS && blocks * Q <= MB_FEW_BYTES ? MbFrom::FEW : MbFrom::SCAN);
-}
 int fp4_launch_csr_transpose(const int64_t* row_ptr, const int32_t* col_idx, const float* val,
                              const int64_t* nnz, int64_t P, int64_t Q, int64_t capacity, int64_t* t_ptr,
                              int32_t* t_idx, float* t_val, int32_t* u_idx, float* u_val, int32_t* scratch,
                              hipStream_t s, int from) {
   int32_t* cnt = scratch;
   if (Q <= MB_MAXQ) {
-    const MbFrom source = (MbFrom)(from ? from : fp4_csr_transpose_from(P, Q));
-    if (source != MbFrom::TABLE && !mb_positions(P, Q)) return FP4_ERR_ARG;
-    const int nblocks = (int)mb_blocks(P, Q);
-    uint32_t* ex = reinterpret_cast<uint32_t*>(scratch + Q + 64);
-    uint8_t* cnt8 = reinterpret_cast<uint8_t*>(ex + (int64_t)nblocks * Q);
-    auto count = [&](auto qmax) {
-      hipLaunchKernelGGL((csr_mask_count_kernel<decltype(qmax)::value>), dim3(nblocks), dim3(MB_THREADS), 0, s, row_ptr, col_idx,
-                         P, Q, capacity, cnt8);
-    };
-    using Q4 = std::integral_constant<int, 4096>;
-    using Q8 = std::integral_constant<int, 8192>;
-    using Q16 = std::integral_constant<int, MB_MAXQ>;
-    auto fill = [&](auto qmax, auto from) {
-      hipLaunchKernelGGL((csr_mask_fill_kernel<decltype(qmax)::value, decltype(from)::value>), dim3((nblocks + 7) / 8 * 8), dim3(MB_THREADS), 0,
-                         s, row_ptr, col_idx, val, P, Q, capacity, t_ptr, ex, cnt, cnt8, t_idx, t_val);
-    };
-    using Few = std::integral_constant<MbFrom, MbFrom::FEW>;
-    using Scan = std::integral_constant<MbFrom, MbFrom::SCAN>;
-    using Table = std::integral_constant<MbFrom, MbFrom::TABLE>;
-    if (Q <= 4096) count(Q4{}); else if (Q <= 8192) count(Q8{}); else count(Q16{});
-    if (source == MbFrom::FEW) {
-      if (Q <= 4096) fill(Q4{}, Few{}); else if (Q <= 8192) fill(Q8{}, Few{}); else fill(Q16{}, Few{});
-      FP4_CHECK_LAUNCH();
-      return FP4_OK;
-    }
-    hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0, s, cnt8, nblocks, Q, ex, cnt);
-    FP4_CHECK_LAUNCH();
-    if (source == MbFrom::SCAN) {
-      if (Q <= 4096) fill(Q4{}, Scan{}); else if (Q <= 8192) fill(Q8{}, Scan{}); else fill(Q16{}, Scan{});
-    } else {
-      const int rc = fp4_launch_scan_rows(cnt, Q, t_ptr, nullptr, s);
-      if (rc) return rc;
-      if (Q <= 4096) fill(Q4{}, Table{}); else if (Q <= 8192) fill(Q8{}, Table{}); else fill(Q16{}, Table{});
-    }
-    FP4_CHECK_LAUNCH();
-    return FP4_OK;
+    if (from && from != (int)MbFrom::TABLE && !mb_positions(P, Q)) return FP4_ERR_ARG;
+    MbArgs m = mb_args(row_ptr, col_idx, val, P, Q, capacity, t_ptr, t_idx, t_val, scratch);
+    if (from) m.from = (MbFrom)from;
+    return fp4_launch_csr_mask(m, true, s);
   }
   int32_t* cursor = scratch + Q;
   hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((2 * Q + 255) / 256)), dim3(256), 0, s, scratch, 2 * Q, 0);

@@ -12,8 +12,6 @@
 
 namespace {
 
-struct BF16 {};
-struct F32 {};
 
 constexpr int GA_AHEAD = 8;
 constexpr int GA_LONG = 256;         // entries up to which no row is long
