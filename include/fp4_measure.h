@@ -38,6 +38,9 @@ int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
+/* Whether that GEMM takes 32 x 32 tiles, whose waves share a contraction, in the place of those (1) or not (0) (host arithmetic, no GPU). */
+int fp4_gemm_splits(int64_t P, int64_t Q, int64_t Kc, int factor, int compute_units);
+
 /* Whether the tiles of one tensor's column-wise quantization form their scales themselves (1) or a launch before them does (0)
  * (host arithmetic, no GPU). */
 int fp4_quantize_cols_folds(int64_t rows, int64_t cols);

@@ -112,6 +112,8 @@ def lib() -> C.CDLL:
         L.fp4_probe_copy.restype = i32
         L.fp4_gemm_tiling.argtypes = [i64, i64, i64, i32, i32, i32, i32, i32, vp, vp]
         L.fp4_gemm_tiling.restype = i32
+        L.fp4_gemm_splits.argtypes = [i64, i64, i64, i32, i32]
+        L.fp4_gemm_splits.restype = i32
         L.fp4_trace_begin.argtypes = [i32]
         L.fp4_trace_begin.restype = i32
         L.fp4_trace_end.argtypes = [vp, vp, i32]
@@ -626,6 +628,11 @@ def fp4_gemm_tiling(P: int, Q: int, Kc: int, factor: bool = False, w_bf16: bool 
     if tile < 0:
         _check(tile, "fp4_gemm_tiling")
     return tile, last_round.value, stagger.value
+
+
+def fp4_gemm_splits(P: int, Q: int, Kc: int, factor: bool = False, compute_units: int = 256) -> bool:
+    """Whether an FP4 GEMM takes 32 x 32 tiles in the place of those of fp4_gemm_tiling (host arithmetic, no GPU)."""
+    return lib().fp4_gemm_splits(P, Q, Kc, int(factor), compute_units) == 1
 
 
 def fp4_trace_begin(max_launches: int) -> None:

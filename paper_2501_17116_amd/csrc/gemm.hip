@@ -599,13 +599,13 @@ FP4_D void column_scales(int64_t Q0, const float* gr, const float* gamma_w, cons
   }
 }
 // What is left of a T x T tile of sums that lie in LDS scaled by 1/gamma_l: 1/gamma_r, addend, factor, conversion, stores
-// along rows.  The same operations in the same order as in fp4_gemm_nt_kernel.  256 threads.
+// along rows.  The same operations in the same order as in fp4_gemm_nt_kernel.  256 threads, the first 128 of them where T is 32.
 template <int T, bool OUT_BF16, bool DGE, bool W_BF16>
 FP4_D void finish_tile(const float* tile, int64_t P0, int64_t Q0, const float (&ir)[8], const float (&gw)[8], const float* addend,
                        void* outp, const void* Wp, const GemmShape& g) {
   constexpr int LD = T + 4;
   const int tid = threadIdx.x;
-  constexpr int UPR = T / 8, RPT = 256 / UPR;   // 8-column units a row, rows a pass
+  constexpr int UPR = T / 8, RPT = (T == 32 ? 128 : 256) / UPR;   // 8-column units a row, rows a pass
   const int ql = (tid % UPR) * 8;
   const int64_t q0 = Q0 + ql;
   if (q0 >= g.Q) return;
@@ -939,6 +939,116 @@ __global__ __launch_bounds__(256) void fp4_gemm_mid_kernel(
   finish_tile<T, OUT_BF16, DGE, W_BF16>(tile, P0, Q0, ir, gw, addend, outp, Wp, g);
 }
 
+// The same for the smallest outputs (a few tokens): 32 x 32 a workgroup, of which each of the four waves takes every fourth K step.  Such a
+// call is one round trip to memory after another, so there are as many workgroups as can be and a wave has SP_RING steps of its own
+// under way, which it stages, waits for and multiplies without any other; whole lines at a time (a lane of the 64 x 64 tiles reads 16 bytes
+// of its row: 32 lines an instruction).  The waves' sums are multiples of 1/4 below 2^22, so added up they are the same bits
+// as in one chain, and the rest is as above.
+constexpr int SP_T = 32, SP_OP = SP_T * BKB, SP_STEP = 2 * SP_OP, SP_LD = SP_T / 8;   // SP_LD: 1 KiB requests an operand and step
+template <bool OUT_BF16, bool DGE, bool W_BF16, int RING>
+__global__ __launch_bounds__(256) void fp4_gemm_split_kernel(
+    const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,
+    const float* __restrict__ gr, const float* addend, void* outp, const void* __restrict__ Wp,
+    const float* __restrict__ gamma_w, GemmShape g) {
+  constexpr int T = SP_T, LD = T + 4, WAVES = 4;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[WAVES * RING * SP_STEP];
+  static_assert(RING * SP_STEP >= T * LD * 4, "a wave's sums lie over its ring");
+  auto part = [&](int w) { return reinterpret_cast<float*>(smem + w * (RING * SP_STEP)); };
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  // each XCD a contiguous run of tiles, column by column: the rows of Rt are read by one of them
+  const int total = g.count, per_xcd = (total + 7) / 8;
+  const int id = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
+  const int64_t P0 = (int64_t)(id % g.tiles_p) * T, Q0 = (int64_t)(id / g.tiles_p) * T;
+  const __amdgpu_buffer_rsrc_t rsrcL = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(Lp) + P0 * g.Kb, 0, (int)(uint32_t)(min(g.P - P0, (int64_t)T) * g.Kb), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrcR = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(Rp) + Q0 * g.Kb, 0, (int)(uint32_t)(min(g.Q - Q0, (int64_t)T) * g.Kb), 0x00020000);
+  const uint32_t Kb = (uint32_t)g.Kb;
+  uint32_t offL[SP_LD], offR[SP_LD], at[SP_LD];
+#pragma unroll
+  for (int j = 0; j < SP_LD; ++j) {
+    const int row = 8 * j + (lane >> 3);
+    at[j] = (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    offL[j] = (uint32_t)min((int64_t)row, g.P - 1 - P0) * Kb + at[j];   // rows past the edge re-read the last row
+    offR[j] = (uint32_t)min((int64_t)row, g.Q - 1 - Q0) * Kb + at[j];
+  }
+  uint8_t* const mine = smem + wave * (RING * SP_STEP);
+  const int KT = (int)((g.Kb + BKB - 1) / BKB), steps = (KT - wave + WAVES - 1) / WAVES;   // of this wave
+  auto request = [&](int i) {   // what lies past the row, and steps past the last, arrive as zeros
+    uint8_t* const st = mine + (i % RING) * SP_STEP;
+    const uint32_t k = (uint32_t)((wave + WAVES * i) * BKB);
+#pragma unroll
+    for (int j = 0; j < SP_LD; ++j) {
+      const bool in = i < steps && k + at[j] < Kb;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcL, (__attribute__((address_space(3))) void*)(st + j * 1024), 16,
+                                               in ? offL[j] + k : OUT_OF_RANGE, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcR, (__attribute__((address_space(3))) void*)(st + SP_OP + j * 1024), 16,
+                                               in ? offR[j] + k : OUT_OF_RANGE, 0, 0, 0);
+    }
+  };
+  const int key = (l32 >> 1) & 7;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  const int one = 0x7f7f7f7f;
+#pragma unroll
+  for (int i = 0; i < RING; ++i) request(i);
+  float ir[8], gw[8], il = 1.0f;
+  column_scales<T, DGE>(Q0, gr, gamma_w, g, ir, gw);
+  if (gl != nullptr) il = gl[min(P0 + (tid >> 3), g.P - 1)];
+  for (int i = 0; i < steps; ++i) {
+    asm volatile("" ::: "memory");
+    constexpr int left = (RING - 1) * 2 * SP_LD;   // the steps behind this one
+    __builtin_amdgcn_s_waitcnt(0x0070 | (left & 15) | ((left >> 4) << 14));
+    asm volatile("" ::: "memory");
+    const uint8_t* const sL = mine + (i % RING) * SP_STEP + l32 * BKB;
+    u32x4 fl[4], fr[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int slot = ((2 * ks + lhi) ^ key) * 16;
+      fr[ks] = *reinterpret_cast<const u32x4*>(sL + SP_OP + slot);
+      fl[ks] = *reinterpret_cast<const u32x4*>(sL + slot);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read: the slot may be filled again
+    request(i + RING);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const i32x8 a = {(int)fr[ks].x, (int)fr[ks].y, (int)fr[ks].z, (int)fr[ks].w, 0, 0, 0, 0};
+      const i32x8 b = {(int)fl[ks].x, (int)fl[ks].y, (int)fl[ks].z, (int)fl[ks].w, 0, 0, 0, 0};
+      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 4, 0, one, 0, one);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);   // no load may land over the sums
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4)
+    *reinterpret_cast<f32x4*>(&part(wave)[l32 * LD + g4 * 8 + lhi * 4]) = f32x4{acc[g4 * 4], acc[g4 * 4 + 1], acc[g4 * 4 + 2], acc[g4 * 4 + 3]};
+  __syncthreads();
+  {   // four columns of a row a thread
+    const int o = (tid >> 3) * LD + (tid & 7) * 4;
+    f32x4 sum = *reinterpret_cast<const f32x4*>(&part(0)[o]);
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&part(w)[o]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] += v[e];
+    }
+    const float i1 = __builtin_amdgcn_rcpf(il);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum[e] = __fmul_rn(sum[e], i1);
+    *reinterpret_cast<f32x4*>(&part(0)[o]) = sum;
+  }
+  __syncthreads();
+  if (tid >= 128) return;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ir[e] = __builtin_amdgcn_rcpf(ir[e]);
+  finish_tile<T, OUT_BF16, DGE, W_BF16>(part(0), P0, Q0, ir, gw, addend, outp, Wp, g);
+}
+
 __global__ void fp4_unpack_kernel(const uint8_t* codes, int64_t nbytes, uint8_t* out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nbytes) {
@@ -983,6 +1093,10 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   const GemmTiling t = gemm_tiling(P, Q, Kc, dge, w_bf16 != 0, addend != nullptr, out_bf16 != 0, n_cu);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
   const bool ragged = (g.Kb % BKB) != 0, small = t.tile == 64, mid = t.tile == 128;
+  GemmShape gt = g;
+  gt.tiles_p = (int)((P + SP_T - 1) / SP_T);
+  gt.tiles_q = (int)((Q + SP_T - 1) / SP_T);
+  gt.count = gt.tiles_p * gt.tiles_q;
   const int total = g.tiles_p * g.tiles_q - t.rest;
   g.first = 0;
   g.count = total;
@@ -1000,6 +1114,15 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   }
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
+    if (t.split) {                                                                                        \
+      if (gt.count <= n_cu)                                                                               \
+        hipLaunchKernelGGL((fp4_gemm_split_kernel<OB, DG, WB, 4>), dim3((unsigned)((gt.count + 7) / 8 * 8)), dim3(256), 0, stream, L, Rt, \
+                           gl, gr, addend, out, W, gamma_w, gt);                                          \
+      else                                                                                                \
+        hipLaunchKernelGGL((fp4_gemm_split_kernel<OB, DG, WB, 2>), dim3((unsigned)((gt.count + 7) / 8 * 8)), dim3(256), 0, stream, L, Rt, \
+                         gl, gr, addend, out, W, gamma_w, gt);                                            \
+      break;                                                                                              \
+    }                                                                                                     \
     if (small)                                                                                            \
       hipLaunchKernelGGL((fp4_gemm_small_kernel<OB, DG, WB>), dim3((unsigned)(((P + 63) / 64) * ((Q + 63) / 64))), dim3(256), 0, stream, L, Rt, gl, gr, \
                          addend, out, W, gamma_w, gs);                                                    \
@@ -1053,6 +1176,11 @@ extern "C" int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int
   if (last_round) *last_round = t.rest;
   if (stagger) *stagger = t.stagger;
   return t.tile;
+}
+
+extern "C" int fp4_gemm_splits(int64_t P, int64_t Q, int64_t Kc, int factor, int compute_units) {
+  if (P <= 0 || Q <= 0 || Kc < 0 || (Kc % 32) != 0 || compute_units < 8) return FP4_ERR_SHAPE;
+  return gemm_tiling(P, Q, Kc, factor != 0, false, false, false, compute_units).split ? 1 : 0;
 }
 
 extern "C" int fp4_unpack(const uint8_t* codes, int64_t rows, int64_t cols, uint8_t* one_per_byte,

@@ -8,6 +8,7 @@ struct GemmTiling {
   int tile;      // 64, 128 or 256: rows and columns of an output tile
   int rest;      // 256: tiles of the last round that are cut into 128 x 128 ones
   int stagger;   // 256: how much later than the one before each quarter of the workgroups begins, in 512 cycles
+  bool split;    // 32 x 32 tiles instead, whose waves share a contraction
 };
 
 // Offset past the end of any tile's buffer descriptor while the tile's rows take no more bytes than this.
@@ -50,8 +51,23 @@ inline bool gemm_small_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, 
   return rows * Kb <= (!factor ? 15 << 18 : r == 0 ? 18 << 18 : 10 << 18);
 }
 
+// Whether 32 x 32 tiles, whose four waves share the contraction, beat both: what they save are round trips, up to two workgroups a CU (one with
+// rings of four steps, two with rings of two), so they win from two steps of whole lines on, and where rows are no whole lines, so
+// that a step's lines are half another's, from four on.  With the factor from one, because they have more threads for it.  In us,
+// 64 or 128 tiles / these, bf16 with fp32 addend: 64 x 2048, 256 codes 4.4 / 4.7, 512 5.4 / 4.4, 1024 7.0 / 4.6, 2048 9.7 / 5.0, 8192 20.9 / 6.8, 544
+// 4.6 / 4.5, 1376 5.8 / 4.9; two a CU, 64 x 8192, 512 5.5 / 5.1, 2048 9.6 / 6.0, 8192 22 / 10.8, 544 4.6 / 5.4, 1376 6.0 / 5.7; factor, 512 x 512,
+// 128 5.5 / 5.3, 256 5.9 / 5.2, 512 x 1024, 128 5.6 / 6.2, 256 6.2 / 6.0.  Another half round: 96 x 8192, 1024 7.4 / 7.2, 2048 10.2 / 8.1, 8192 23 /
+// 13.8, 2080 7.5 / 8.4, 3168 12.9 / 9.5.  Beyond, the operands' second and third reading counts: 1024 tiles, 4096 codes 13.5 / 11.3 to 13.4 / 13.0, 2048
+// tiles 13.8 / 18.8.
+inline bool gemm_split_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, int n_cu) {
+  const int64_t tiles = ((P + 31) / 32) * ((Q + 31) / 32);
+  const bool whole = Kc / 2 % GEMM_K_STEP == 0;
+  if (tiles <= 2 * (int64_t)n_cu) return Kc >= (factor ? 256 : whole ? 512 : 1120);
+  return tiles <= 3 * (int64_t)n_cu && !factor && Kc >= (whole ? 1024 : 3072);
+}
+
 inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, bool w_bf16, bool addend, bool out_bf16, int n_cu) {
-  GemmTiling t = {256, 0, 0};
+  GemmTiling t = {256, 0, 0, false};
   const int64_t Kb = Kc / 2;
   const bool few = gemm_small_tiles_win(P, Q, Kc, factor, w_bf16, n_cu);
   // 128 x 128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend, as 64 / 128 / 256 tiles in us: 40 / 22.6 / 24.8 and
@@ -63,6 +79,7 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
   // The larger tiles address their rows by 32-bit offsets into a descriptor; rows too long for that go to the next smaller
   // one, and the 64 x 64 ones have 64-bit addresses.
   const bool fits_big = Kb * 256 <= (int64_t)GEMM_OUT_OF_RANGE, fits_mid = Kb * 128 <= (int64_t)GEMM_OUT_OF_RANGE;
+  t.split = gemm_split_tiles_win(P, Q, Kc, factor, n_cu) && Kb * 32 <= (int64_t)GEMM_OUT_OF_RANGE;
   // An empty contraction has no K step to request, which the staged tilings do ahead: the operands may be null.
   if (few || !fits_mid || Kb == 0) {
     t.tile = 64;
