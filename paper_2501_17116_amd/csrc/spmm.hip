@@ -681,7 +681,7 @@ __global__ __launch_bounds__(SP_ROWS) void spmm_rest_kernel(const int64_t* __res
   bool mine = false;
   if (block * SP_ROWS + threadIdx.x < P) {
     const uint32_t group = (uint32_t)((block * SP_ROWS + threadIdx.x) >> 4);   // P < 2^31: the list's rows have 32 bits
-    const uint32_t bundle = rest.groups == 3 ? group / 3u : group;
+    const uint32_t bundle = rest.groups == 3 ? group / 3u : group >> (rest.groups - 1);
     mine = rest.steps[bundle] < 0 || rest.redo[bundle] != 0;
   }
   s_mine[threadIdx.x] = mine;

@@ -9,7 +9,7 @@
 struct SpmmRest {
   const int32_t* steps;
   const int32_t* redo;
-  int groups;   // 1 or 3
+  int groups;   // 1 to 3
 };
 
 #if defined(__HIPCC__)

@@ -30,7 +30,7 @@
 #include "spmm_long.h"
 
 #include <algorithm>
-#include <type_traits>
+#include <tuple>
 
 namespace {
 
@@ -38,7 +38,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 
-constexpr int SM_STEPS_PAD = 12;   // step counts read past the last bundle (11 waves)
+constexpr int SM_STEPS_PAD = 12;   // step counts read past the last bundle (up to 12 waves)
 constexpr int SM_KC = 128;       // rows of D per chunk
 constexpr int SM_RING = 5;       // chunks in LDS (all 160 KiB): to multiply from, and on their way
 // Chunks on their way.  With one group a wave a phase has so little to multiply that it lasts as long as a chunk takes to come, so three
@@ -533,6 +533,11 @@ __global__ __launch_bounds__((WV + sm_stagers(G)) * 64) void spmm_mfma_kernel(co
   }
 }
 
+template <int G, int WV>
+struct Shape {   // of a workgroup: groups a wave, waves that multiply
+  static constexpr int groups = G, waves = WV;
+};
+
 }  // namespace
 
 int fp4_compute_units_of_current_device();
@@ -555,8 +560,8 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
   const int col_blocks = (int)((N + SM_NT - 1) / SM_NT);
   const bool small_grid = (P + 1023) / 1024 * ((N + 63) / 64) < 256;   // workgroups of the tiled kernel
   auto blocks = [&](int g, int wv) { return (P + 16 * g * wv - 1) / (16 * g * wv); };
-  auto launch = [&](auto g_c, auto wv_c) {
-    constexpr int G = decltype(g_c)::value, WV = decltype(wv_c)::value;
+  auto launch = [&](auto shape) {
+    constexpr int G = decltype(shape)::groups, WV = decltype(shape)::waves;
     const int64_t bundles = (P + 16 * G - 1) / (16 * G);
     uint8_t* const a_buf = reinterpret_cast<uint8_t*>(scratch);
     uint8_t* const o_buf = a_buf + bundles * G * (int64_t)(cap + 1) * 1024;
@@ -573,23 +578,21 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
                        steps, redo, cap, phases, row_blocks, col_blocks, P, Q, reinterpret_cast<const uint16_t*>(D),
                        N, R);
     rest = SpmmRest{steps, redo, G};
-    static_assert(G == 1 || G == 3, "the rest's bundles");
+    static_assert(G <= 3, "the rest's bundles");
   };
-  // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier);
-  // 256 workgroups run at a time.  So: the shape with the fewest rounds x (300 + rows).  Measured at 2 %: 528 rows
-  // 2.3 us a phase, 176 rows 0.9 (1.05 with two chunks on their way and one step requested ahead); products, their packing and long rows
-  // included, 528 / 176 / 112 rows: 2048 x 8192 -> 2048 218 / 116 / 169 us, 3072 x 8192 -> 2048 223 / 194 / 172, 4096^3 133 / 157 / 210,
-  // 512 x 8192 -> 8192 214 / 110 / 158.  Two rounds of 176 rows against one of 528, between which this leaves the latter: at 2 % they are
-  // faster (4096 x 8192 -> 2048 200 / 227), at 0.2 % slower (110 / 96), and how full the matrix is is not known here.
-  auto cost = [&](int g, int wv) { return (blocks(g, wv) * col_blocks + 255) / 256 * (300 + 16 * g * wv); };
-  const int64_t big = cost(3, 11), mid = cost(1, 11), small = cost(1, 7);
-  using I1 = std::integral_constant<int, 1>;
-  using I3 = std::integral_constant<int, 3>;
-  using I7 = std::integral_constant<int, 7>;
-  using I11 = std::integral_constant<int, 11>;
-  if (big <= mid && big <= small) launch(I3{}, I11{});
-  else if (mid <= small) launch(I1{}, I11{});
-  else launch(I1{}, I7{});
+  // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier), and 256 workgroups run at
+  // a time.  So: the shape with the fewest rounds x (300 + rows), the larger one of equals.  Multiplying waves are whole numbers a SIMD
+  // beside the staging ones (8: two, 12: three, 11 + 1: three), and rows come in the halves and quarters of which row counts are made.
+  // Products, their packing and long rows included, 528 / 384 / 256 / 192 / 128 rows, us, the one taken in brackets; at 2 %
+  // 2048 x 8192 -> 2048 123 / 110 / 95 / 83 / (76), 3072 x 8192 -> 2048 124 / 110 / 97 / (87) / 122, 4096 x 8192 -> 2048 126 / 112 / (100) / 140 /
+  // 126, 5504 x 2048 -> 4096 92 / (84) / 93 / 103 / 120, 4096^3 (82) / 110 / 96 / 113 / 128, 4096 x 4096 -> 11008 (192) / 203 / 235 / 267 / 308,
+  // 2048 x 8192 -> 5504 (147) / 208 / 180 / 160 / 190; at 0.2 % 4096 x 8192 -> 2048 81 / 81 / (74) / 107 / 100.
+  const std::tuple<Shape<3, 11>, Shape<2, 12>, Shape<2, 8>, Shape<1, 12>, Shape<1, 8>> shapes;
+  std::apply([&](auto... shape) {
+    auto cost = [&](int g, int wv) { return (blocks(g, wv) * col_blocks + 255) / 256 * (300 + 16 * g * wv); };
+    const int64_t least = std::min({cost(shape.groups, shape.waves)...});
+    (void)((cost(shape.groups, shape.waves) == least && (launch(shape), true)) || ...);
+  }, shapes);
   FP4_CHECK_LAUNCH();
   return FP4_OK;
 }
