@@ -83,6 +83,18 @@ FP4_D void load_raw8(const void* base, int64_t off, int valid, Raw8<DT>& w) {
   }
 }
 
+// The same for a whole unit, without a branch.  A load under a branch that leaves zeros otherwise is moved into the registers of those zeros
+// at the branch's end, which waits for it: several units read so came one after another.
+template <class DT>
+FP4_D void load_whole8(const void* base, int64_t off, Raw8<DT>& w) {
+  if constexpr (__is_same(DT, BF16)) {
+    w.r = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(base) + off);
+  } else {
+    const f32x4* p = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(base) + off);
+    w.a = p[0]; w.b = p[1];
+  }
+}
+
 template <class DT>
 FP4_D void widen8(const Raw8<DT>& w, float (&v)[8]) {
   if constexpr (__is_same(DT, BF16)) {
@@ -444,11 +456,17 @@ FP4_D void quantize_rows_block(RowArgs a) {
 
   // ---- pass 1: absmax of the (clamped) row, outlier count
   if constexpr (CACHED) {
+    if (row_ok && nunits > 0 && (FULL || a.cols % 8 == 0)) {
+      // all of a thread's units requested at once; one past the row's end is the last unit again, which changes no maximum and is
+      // neither counted nor emitted
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int64_t unit = (int64_t)u * TPR + t;
-      const int valid = valid_of(unit);
-      load_raw8<DT>(a.x, xoff + unit * 8, valid, cache[u]);   // valid <= 0 reads nothing and yields zeros
+      for (int u = 0; u < NV; ++u) load_whole8<DT>(a.x, xoff + (int64_t)min(u * TPR + t, (int)nunits - 1) * 8, cache[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        const int64_t unit = (int64_t)u * TPR + t;
+        load_raw8<DT>(a.x, xoff + unit * 8, valid_of(unit), cache[u]);   // valid <= 0 reads nothing and yields zeros
+      }
     }
     if constexpr (TOKEN) {
       select_row_thresholds<DT, TPR, NV>(cache, row_ok, t, a.cols, nunits, a.tail_k,
@@ -833,27 +851,39 @@ FP4_D void col_absmax_strip(const ColArgs& a, unsigned strip, unsigned row_block
 #pragma unroll
   for (int e = 0; e < 8; ++e) m[e] = 0.0f;
   const int valid = unit < nunits ? (int)min((int64_t)8, a.cols - unit * 8) : 0;
-  if (valid > 0) {
-    // four rows a wave at a time, their loads (and, with per-row thresholds, those) issued together
-    constexpr int UN = 4;
-    int64_t r = r0 + wave;
+  int64_t r = r0 + wave;
+  if (valid == 8) {
+    // Two or four rows a wave at a time, their loads (and, with per-row thresholds, those) requested together, which takes loads without a
+    // branch.  In us, one after another / two / four / eight: 4096 x 12288 26.6 / 20.1 / 20.0 / 20.2, 11008 x 4096 30.4 / 22.1 / 22.3 / 23.2, 5120 x
+    // 13824 33 / 31.7 / 34 / 32, 16384 x 4096 beside as many rows 69 / 71 / 75 / 76; clamped, which has more to do for a row: 8192 x 7552
+    // 28.7 / - / 23.0 / 24.6, beside 8192 x 2048 rows 24.5 / - / 20.0 / 23.6.
+    constexpr int UN = CLAMP ? 4 : 2;
     for (; r + 4 * (UN - 1) < r1; r += 4 * UN) {
-      float v[UN][8], l4[UN], h4[UN];
+      Raw8<DT> raw[UN];
+      float l4[UN], h4[UN];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        load8<DT>(a.x, (r + 4 * u) * a.ld + unit * 8, valid, v[u]);
-        l4[u] = lo; h4[u] = hi;
-        if (CLAMP && a.thr_stride) { l4[u] = a.thr[(r + 4 * u) * a.thr_stride]; h4[u] = a.thr[(r + 4 * u) * a.thr_stride + 1]; }
+      for (int u = 0; u < UN; ++u) load_whole8<DT>(a.x, (r + 4 * u) * a.ld + unit * 8, raw[u]);
+      if (CLAMP && a.thr_stride) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) { l4[u] = a.thr[(r + 4 * u) * a.thr_stride]; h4[u] = a.thr[(r + 4 * u) * a.thr_stride + 1]; }
+      } else {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) { l4[u] = lo; h4[u] = hi; }
       }
 #pragma unroll
-      for (int u = 0; u < UN; ++u)
+      for (int u = 0; u < UN; ++u) {
+        float v[8];
+        widen8<DT>(raw[u], v);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          float x = v[u][e];
+          float x = v[e];
           if (CLAMP) x = clamp3(x, l4[u], h4[u]);
           m[e] = fmaxf(m[e], fabsf(x));
         }
+      }
     }
+  }
+  if (valid > 0) {
     for (; r < r1; r += 4) {
       float v[8];
       load8<DT>(a.x, r * a.ld + unit * 8, valid, v);
@@ -1247,11 +1277,8 @@ __global__ __launch_bounds__(256) void quantize_rows_colmax_kernel(const uint16_
   u32x4 buf[2][NV];
   auto fetch = [&](int r, u32x4 (&dst)[NV]) {
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int64_t unit = (int64_t)u * 256 + tid;
-      dst[u] = u32x4{0u, 0u, 0u, 0u};
-      if (r < nrows && unit < nunits) dst[u] = *reinterpret_cast<const u32x4*>(x + (r0 + r) * ld + unit * 8);
-    }
+    for (int u = 0; u < NV; ++u)   // without a branch, or each load is waited for; the last unit or row again changes no maximum
+      dst[u] = *reinterpret_cast<const u32x4*>(x + (r0 + min(r, nrows - 1)) * ld + min(u * 256 + tid, (int)nunits - 1) * 8);
   };
   bool any_nan = false;
   auto process = [&](int r, const u32x4 (&cur)[NV]) {
