@@ -79,22 +79,19 @@ FP4_D int sm_a_at(int p, int r) {
   return (quarter * 16 + r) * 16 + i * 2;
 }
 
+FP4_D uint32_t bf16_nearest(float v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }   // v_cvt_pk_bf16_f32
+
 // v as the exact sum of up to three bf16 numbers (nearest first); returns how many, 4 if three are not enough: below
 // 2^-110 the last of fp32's 24 bits can lie under the smallest bf16 number, 2^-133.
 FP4_D int bf16_terms(float v, uint32_t (&t)[3]) {
-  int n = 0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const uint32_t u = f2u(v);
-    uint32_t h = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-    if ((h & 0x7f80u) == 0x7f80u) h = u >> 16;   // no rounding up to infinity
-    if ((u & 0x7f800000u) == 0x7f800000u) h = (u >> 16) | ((u & 0x7fffffu) != 0u ? 1u : 0u);
-    t[i] = i == 0 || (v != 0.0f) ? h : 0u;
-    if (i == 0 || v != 0.0f) n = i + 1;
-    const float r = v - u2f(h << 16);
-    v = (u & 0x7f800000u) == 0x7f800000u ? 0.0f : r;
-  }
-  return v != 0.0f ? 4 : n;
+  const uint32_t u = f2u(v);
+  t[0] = bf16_nearest(v);
+  if ((t[0] & 0x7f80u) == 0x7f80u) t[0] = (u >> 16) | ((u & 0x7fffffffu) > 0x7f800000u ? 1u : 0u);   // no rounding up to infinity
+  const float r = (u & 0x7f800000u) == 0x7f800000u ? 0.0f : v - u2f(t[0] << 16);
+  t[1] = bf16_nearest(r);
+  const float r2 = r - u2f(t[1] << 16);
+  t[2] = bf16_nearest(r2);
+  return r2 != u2f(t[2] << 16) ? 4 : r2 != 0.0f ? 3 : r != 0.0f ? 2 : 1;
 }
 
 // Whether a matrix is worth packing, from 64 rows spread over it (every workgroup looks at the same ones and comes to the
@@ -129,11 +126,11 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
                                                                int32_t* __restrict__ steps, int32_t* __restrict__ redo, int32_t* list,
                                                                int32_t* count) {
   constexpr int ROWS = 16 * G, PK_TPR = pk_tpr(G), THREADS = ROWS * PK_TPR, SM_SLACK = sm_slack(G);
-  extern __shared__ uint32_t pk_lds[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t pk_lds[];
   const int words = phases * (SM_KC / 8);
   uint32_t* const nib = pk_lds;                                                // [G][words] a nibble per column: as many bits as slots
-  int32_t* const start = reinterpret_cast<int32_t*>(nib + G * words);       // [G][phases] slot count, then first slot
-  uint16_t* const pre = reinterpret_cast<uint16_t*>(start + G * phases);   // [G][words] slots of the chunk before this word
+  uint16_t* const pre = reinterpret_cast<uint16_t*>(nib + G * words);      // [G][words] slots of the chunk before this word
+  int32_t* const start = reinterpret_cast<int32_t*>(pre + G * words);       // [G][phases] slot count, then first slot
   __shared__ int64_t s_b[ROWS];
   __shared__ int s_n[ROWS];
   __shared__ int s_bad, s_total[G], s_steps, s_sample[4];
@@ -214,9 +211,18 @@ __global__ __launch_bounds__(16 * G * pk_tpr(G)) void spmm_pack_kernel(const int
   for (int i = tid; i < G * phases; i += THREADS) {
     int sum = 0;
 #pragma unroll
-    for (int w = 0; w < SM_KC / 8; ++w) {
-      pre[i * (SM_KC / 8) + w] = (uint16_t)sum;
-      sum += __popc(nib[i * (SM_KC / 8) + w]);
+    for (int w = 0; w < SM_KC / 8; w += 8) {
+      const u32x4* const m = reinterpret_cast<const u32x4*>(nib + i * (SM_KC / 8) + w);
+      const u32x4 m0 = m[0], m1 = m[1];
+      u32x4 before;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        before[h] = (uint32_t)sum;
+        sum += __popc(h < 2 ? m0[2 * h] : m1[2 * h - 4]);
+        before[h] |= (uint32_t)sum << 16;
+        sum += __popc(h < 2 ? m0[2 * h + 1] : m1[2 * h - 3]);
+      }
+      *reinterpret_cast<u32x4*>(pre + i * (SM_KC / 8) + w) = before;
     }
     start[i] = sum;
     atomicAdd(&s_total[i / phases], sum);
