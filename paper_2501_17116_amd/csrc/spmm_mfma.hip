@@ -25,7 +25,7 @@
 // Bound: a SIMD's vector instructions (34 a step beside the matrix core's 8, which have 16 cycles each) and the return of its LDS reads, which
 // do not overlap: reads alone 62 ns a step, with the matrix core 84, with the moves 122; nine wave-steps of the fullest SIMD where there
 // are 8.25 on average; of 16384 x 4096 -> 12288's 813 us about 190 are what the sums' way to memory costs, mostly by making the loads wait.
-// The same with plain fp32 FMAs fed from LDS (spmm.hip): 1423 us; 6 %: 1400 against 2961 us; 0.2 %: 500 against 609 us.
+// The same with plain fp32 FMAs fed from LDS (spmm.hip): 1423 us; 6 %: 1347 against 2961 us; 0.2 %: 515 against 609 us.
 #include "fp4_common.h"
 #include "spmm_long.h"
 
