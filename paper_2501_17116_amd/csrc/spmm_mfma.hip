@@ -495,6 +495,11 @@ __global__ __launch_bounds__((WV + sm_stagers(G)) * 64) void spmm_mfma_kernel(co
 #pragma unroll
       for (int i = 0; i + 1 < SM_PLANS; ++i) plan[i] = plan[i + 1];
     const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane(plan[0], p & 63);
+    // A single group's operands, on their way since the phase before, are waited for once a phase.  Where a step begins at any of three sets,
+    // the compiler does not know how many requests came after the set's own and waits for all of them, at every step, a round trip to L2 each.
+    // Without / with, us: 1536 x 8192 -> 2048 at 2 % 76.5 / 71.0, at 6 % 122.2 / 107.5; 2048 x 11008 -> 2048 98.8 / 91.8 and 161.2 / 143.0, at 0.2 %,
+    // a step a phase at most, 75.4 / 75.2; 9312 x 11008 -> 512 147.0 / 140.4 and 246.4 / 232.2.
+    if constexpr (G == 1) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     rounds(upto);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the chunk that goes next are done
     __builtin_amdgcn_s_barrier();
