@@ -99,6 +99,10 @@ def lib() -> C.CDLL:
         L.fp4_quantize_cols_folds.restype = i32
         L.fp4_select_route.argtypes = [i64, i64, i64, i32]
         L.fp4_select_route.restype = i32
+        L.fp4_select_beside.argtypes = [i64, i64, i64, i32, i32]
+        L.fp4_select_beside.restype = i32
+        L.fp4_transpose_beside.argtypes = [i64, i64, i64, i32]
+        L.fp4_transpose_beside.restype = i32
         L.fp4_residual_transpose_positions.argtypes = [i64, i64]
         L.fp4_residual_transpose_positions.restype = i32
         L.fp4_residual_transpose.argtypes = [vp, vp, vp, vp, i64, i64, i64, i32, vp, vp, vp, vp, sz, vp]
@@ -567,6 +571,16 @@ FP4_SELECT_WINDOWS, FP4_SELECT_SAMPLE, FP4_SELECT_FOUND, FP4_SELECT_APART = 1, 2
 def fp4_select_route(rows: int, cols: int, dt: int, ld: Optional[int] = None) -> int:
     """Which passes find a tensor's thresholds (host arithmetic, no GPU)."""
     return int(lib().fp4_select_route(rows, cols, cols if ld is None else ld, dt))
+
+
+def fp4_select_beside(M: int, K: int, N: int, dt: int, compute_units: int = 256) -> int:
+    """Tiles a workgroup of W's column-wise codes beside the first digit pass over A, or 0 (host arithmetic, no GPU)."""
+    return int(lib().fp4_select_beside(M, K, N, dt, compute_units))
+
+
+def fp4_transpose_beside(M: int, K: int, N: int, compute_units: int = 256) -> int:
+    """Tiles a workgroup of a weight gradient's codes beside the transposition's last pass, or 0 (host arithmetic, no GPU)."""
+    return int(lib().fp4_transpose_beside(M, K, N, compute_units))
 
 
 def fp4_residual_transpose_positions(P: int, Q: int) -> int:

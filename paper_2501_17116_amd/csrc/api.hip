@@ -34,7 +34,8 @@ int fp4_launch_quantize_cols_given_gamma(const void* x, int bf16, int64_t rows, 
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
                              uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words, const SelFirst* first);
-bool fp4_select_first_beside(const SelFirst& f, int64_t rows, int64_t cols);
+bool fp4_select_first_beside(const SelFirst& f, int bf16, int64_t rows, int64_t cols);
+int fp4_select_beside_tiles(int64_t n, int bf16, int64_t rows, int64_t cols, int n_cu);
 bool fp4_select_begins_with_digits(int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t rows_scratch_words);
 int fp4_launch_occ_rows_token(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld, int64_t tail_k,
                               float* thr_out, uint8_t* codes, float* gamma, void* x_clamped, int32_t* tmp_col,
@@ -49,6 +50,7 @@ int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t
                                   uint8_t* codes_t, float* gamma, const void* y, int64_t cols_y, const uint16_t* part_y,
                                   uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, const MbArgs* m, hipStream_t s);
 bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y);
+int fp4_csr_fill_beside_tiles(int64_t rows, int64_t Q, int64_t cols_y, int n_cu);
 int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const int32_t* row_cnt, int64_t stride,
                             const int64_t* row_ptr, int64_t rows, int64_t capacity, int32_t* col_idx, float* val,
                             hipStream_t s);
@@ -401,7 +403,7 @@ int fwd_impl(const void* A, const void* W, const fp4_weight_cache* wq, fp4_dtype
   } else {
     // a small layer's first pass over A goes with the second over W
     const SelFirst first = {A, M, K, K, reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(w.occ.select) + SEL_STATE_BYTES)};
-    first_done = clear && fp4_select_first_beside(first, K, N) && fp4_select_begins_with_digits(bf16, M, K, K, provisioned_entries(M, K));
+    first_done = clear && fp4_select_first_beside(first, bf16, K, N) && fp4_select_begins_with_digits(bf16, M, K, K, provisioned_entries(M, K));
     rc = fp4_launch_quantize_cols(W, bf16, K, N, N, nullptr, 0, w.qWt, saved->gamma_W, w.amax, s, clear, fp4_select_clear_words(),
                                   first_done ? &first : nullptr);
     if (rc) return rc;
@@ -727,6 +729,17 @@ extern "C" int fp4_residual_spmm_general(const int64_t* row_ptr, const int32_t* 
 
 extern "C" int fp4_select_route(int64_t rows, int64_t cols, int64_t ld, fp4_dtype dt) {
   return fp4_select_passes(dt == FP4_BF16, rows, cols, ld, provisioned_entries(rows, cols));
+}
+
+extern "C" int fp4_select_beside(int64_t M, int64_t K, int64_t N, fp4_dtype dt, int compute_units) {
+  if (M <= 0 || K <= 0 || N <= 0 || compute_units < 1 || !dtype_ok(dt)) return FP4_ERR_SHAPE;
+  const int bf16 = dt == FP4_BF16;
+  return fp4_select_begins_with_digits(bf16, M, K, K, provisioned_entries(M, K)) ? fp4_select_beside_tiles(M * K, bf16, K, N, compute_units) : 0;
+}
+
+extern "C" int fp4_transpose_beside(int64_t M, int64_t K, int64_t N, int compute_units) {
+  if (M <= 0 || K <= 0 || N <= 0 || compute_units < 1) return FP4_ERR_SHAPE;
+  return fp4_csr_fill_beside_tiles(M, K, N, compute_units);
 }
 
 extern "C" int fp4_residual_transpose_positions(int64_t P, int64_t Q) { return fp4_csr_transpose_from(P, Q); }

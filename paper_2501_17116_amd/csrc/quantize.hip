@@ -1193,20 +1193,52 @@ inline bool fold_in_tiles(int64_t rows, int64_t cols, int64_t parts, int bytes, 
 inline unsigned ca_strips(int64_t cols) { return (unsigned)(((cols + 7) / 8 + 63) / 64); }
 inline unsigned ct_strips(int64_t cols) { return (unsigned)((cols + CT_COLS - 1) / CT_COLS); }
 
-// How many tiles a workgroup has beside `first` others, as few as leave all workgroups on the chip at once, two a CU; 0: there are more
+// Column tiles in workgroups of `per` of them beside `first` other workgroups.  As few as keep all workgroups within `most`; 0: there are more
 // with four.  The fewer, the more CUs have a share of the reads.
-unsigned cols_beside_per(int64_t rows, int64_t cols_a, int64_t cols_b, unsigned first) {
-  for (unsigned per = 1; per <= 4; per *= 2) {
-    const int64_t groups = (ct_strips(cols_a) + per - 1) / per + (ct_strips(cols_b) + per - 1) / per;
-    if (first + groups * ((rows + CT_ROWS - 1) / CT_ROWS) <= 2 * fp4_compute_units_of_current_device()) return per;
-  }
+int64_t cols_beside_groups(int64_t rows, int64_t cols_a, int64_t cols_b, int per) {
+  return ((ct_strips(cols_a) + per - 1) / per + (ct_strips(cols_b) + per - 1) / per) * ((rows + CT_ROWS - 1) / CT_ROWS);
+}
+int cols_beside_per(int64_t rows, int64_t cols_a, int64_t cols_b, int64_t first, int64_t most) {
+  for (int per = 1; per <= 4; per *= 2)
+    if (first + cols_beside_groups(rows, cols_a, cols_b, per) <= most) return per;
   return 0;
 }
-ColsBeside cols_beside(const ColArgs& a, const ColArgs& b, unsigned first) {
-  ColsBeside c = {a, b, 0, 0, cols_beside_per(a.rows, a.cols, b.x ? b.cols : 0, first), first};
+ColsBeside cols_beside(const ColArgs& a, const ColArgs& b, int per, unsigned first) {
+  ColsBeside c = {a, b, 0, 0, (unsigned)per, first};
   c.groups_a = (ct_strips(a.cols) + c.per - 1) / c.per;
   c.groups = c.groups_a + (b.x ? (ct_strips(b.cols) + c.per - 1) / c.per : 0);
   return c;
+}
+
+// Pass 3 of a transposition beside the column-wise quantization of a weight gradient's operands (rows rows, Q and cols_y columns): tiles a
+// workgroup, or 0, in launches of their own.  One workgroup is on a CU at a time (its 106 registers, fp32 120, leave no room for a second;
+// above 4096 columns 97 KiB of LDS do), and up to two rounds of them gain, because either has so little to do that it waits for memory
+// most of the time and a launch takes 4 to 5 us.  Count, fill and quantization apart / beside, with the workgroups, us, bf16 at 6 %: 256 x (512 + 512),
+// 24, 18.2 / 12.8; 1056 x (1376 + 2080), 299, 29.3 / 23.4; 4096 x (2048 + 2048), 320, 49.2 / 40.3; 1024 x (8192 + 2048), 336, 106.4 / 98.4; 2048 x (5504 +
+// 2048), 504, 86.6 / 76.9; fp32 4096 x (2048 + 2048) 62.6 / 52.5, 2048 x (4096 + 4096), 288, 78.0 / 67.3.  At the line, 512, with four tiles each,
+// at 0.2 / 2 / 6 %: 8192 x (1024 + 2048) 40.0 / 41.2, 42.5 / 41.6, 49.0 / 45.7; 16384 x (512 + 512), where pass 3 alone has one for every
+// CU, 33.9 / 34.3, 35.7 / 36.4, 40.8 / 41.7.  Beyond it (fill and quantization alone) as long, 8192 x (2048 + 2048) 10.0 + 26.8 / 37.5, or longer, 8192 x
+// (2048 + 5504) 10.6 + 38.2 / 58.1, 16384 x (4096 + 12288) 24.8 + 148.5 / 195.
+int fill_beside_per(int64_t rows, int64_t Q, int64_t cols_y, int n_cu) {
+  if (Q > 8192 || !mb_positions(rows, Q)) return 0;
+  return cols_beside_per(rows, Q, cols_y, mb_fill_blocks((int)mb_blocks(rows, Q)), 2 * n_cu);
+}
+
+// A selection's first digit pass over n elements beside the column-wise quantization of a tensor: tiles a workgroup, or 0.  bf16: workgroups of one
+// tile, three quarters of whose registers come back at once (88 a thread, so the next begins beside what is left, which after two tiles it
+// could not), up to 1024 of them.  fp32 (120 registers, one workgroup a CU): one or two tiles while there are two rounds of workgroups; four
+// only where the digit pass leaves a quarter of the CUs, or the tiles' workgroups are a round of their own, or CUs stand idle in theirs.  Forward
+// pass up to the rows' counts, apart / beside, us.  bf16, one tile: 256 x 512 -> 512 19.7 / 16.6, 32 x 2048 -> 5504 31.1 / 28.9 (two tiles 32.2), 2048 x
+// 4096 -> 2048 39.5 / 36.8, 2048 x 2048 -> 5504 39.6 / 38.2 (four 39.6), 4096^3 54.0 / 52.6; with 2048 tiles 256 x 4096 -> 8192 54.0 / 53.1, 1024 x 4096 -> 8192
+// 58.1 / 58.7, with 2752 1024 x 4096 -> 11008 61.4 / 63.2.  fp32, one or two tiles: 256 x 512 -> 512 26.4 / 23.3, 2048^3 48.1 / 45.8, 512 x 2048 -> 4096
+// 42.3 / 39.4, 4096 x 2048 -> 4096 63.3 / 62.9, beyond the line 1024 x 4096 -> 4096 64.0 / 64.5, 512 x 8192 -> 2048 63.2 / 65.0; four: 256 x 2048 -> 8192 (64
+// workgroups of digits) 49.9 / 46.8, 4096^3 (256 and 256) 96.3 / 93.2, but 256 and 192 or fewer 2048 x 4096 -> 3072 65.5 / 67.4, 1024 x 4096 -> 2560 55.0 /
+// 56.3, 2048 x 2048 -> 5504 57.5 / 58.7.
+int select_beside_per(int64_t n, int bf16, int64_t rows, int64_t cols, int n_cu) {
+  const int64_t first = sel_blocks(n);
+  if (bf16) return cols_beside_groups(rows, cols, 0, 1) <= 4 * n_cu ? 1 : 0;
+  const int per = cols_beside_per(rows, cols, 0, first, 2 * n_cu);
+  return per < 4 || first <= 3 * n_cu / 4 || cols_beside_groups(rows, cols, 0, 4) >= 15 * n_cu / 16 ? per : 0;
 }
 
 // The scales, where the tiles don't form them themselves.
@@ -1416,7 +1448,7 @@ int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, const MbArgs* 
   const unsigned row_blocks = (unsigned)((a.rows + CT_ROWS - 1) / CT_ROWS);
   if constexpr (CLAMP) {
     if (m) {
-      const ColsBeside c = cols_beside(a, b, mb_fill_blocks(m->nblocks));
+      const ColsBeside c = cols_beside(a, b, fill_beside_per(a.rows, m->Q, b.cols, fp4_compute_units_of_current_device()), mb_fill_blocks(m->nblocks));
       auto go = [&](auto qmax, auto from) {
         hipLaunchKernelGGL((quantize_cols_fill_kernel<DT, decltype(qmax)::value, decltype(from)::value>), dim3(c.first + c.groups * row_blocks),
                            dim3(MB_THREADS), 0, s, c, *m);
@@ -1431,7 +1463,8 @@ int launch_cols(ColArgs a, ColArgs b, uint32_t* amax, bool known, const MbArgs* 
       return FP4_OK;
     }
   } else if (f) {
-    const ColsBeside c = cols_beside(a, b, sel_blocks(f->rows * f->cols));
+    const int64_t n = f->rows * f->cols;
+    const ColsBeside c = cols_beside(a, b, select_beside_per(n, __is_same(DT, BF16), a.rows, a.cols, fp4_compute_units_of_current_device()), sel_blocks(n));
     hipLaunchKernelGGL((quantize_cols_select_kernel<DT>), dim3(c.first + c.groups * row_blocks), dim3(SEL_THREADS), 0, s, c, *f);
     FP4_CHECK_LAUNCH();
     return FP4_OK;
@@ -1884,15 +1917,18 @@ int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const 
   return FP4_OK;
 }
 
-// Whether a selection's first digit pass goes with the column-wise quantization of a tensor, by the same line.
-bool fp4_select_first_beside(const SelFirst& f, int64_t rows, int64_t cols) { return cols_beside_per(rows, cols, 0, sel_blocks(f.rows * f.cols)) > 0; }
+int fp4_select_beside_tiles(int64_t n, int bf16, int64_t rows, int64_t cols, int n_cu) { return select_beside_per(n, bf16, rows, cols, n_cu); }
+// Whether a selection's first digit pass goes with the column-wise quantization of a tensor.
+bool fp4_select_first_beside(const SelFirst& f, int bf16, int64_t rows, int64_t cols) {
+  return select_beside_per(f.rows * f.cols, bf16, rows, cols, fp4_compute_units_of_current_device()) > 0;
+}
 
 // first: a selection's first digit pass that goes with the last launch (fp4_select_first_beside; no clamp), or null.
 int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols, int64_t ld,
                              const float* clamp_thr, int per_row_thr, uint8_t* codes_t, float* gamma,
                              uint32_t* amax_scratch, hipStream_t s, void* clear, int64_t clear_words, const SelFirst* first) {
   if (rows == 0 || cols == 0) return FP4_OK;
-  if (first && (clamp_thr || !fp4_select_first_beside(*first, rows, cols))) return FP4_ERR_ARG;
+  if (first && (clamp_thr || !fp4_select_first_beside(*first, bf16, rows, cols))) return FP4_ERR_ARG;
   ColArgs a = {};
   a.clear = reinterpret_cast<unsigned long long*>(clear); a.clear_words = clear_words;
   a.x = x; a.codes_t = codes_t; a.gamma = gamma; a.thr = clamp_thr;
@@ -1902,14 +1938,11 @@ int fp4_launch_quantize_cols(const void* x, int bf16, int64_t rows, int64_t cols
   return bf16 ? launch_cols<BF16, false>(a, {}, amax_scratch, false, nullptr, first, s) : launch_cols<F32, false>(a, {}, amax_scratch, false, nullptr, first, s);
 }
 
-// Whether pass 3 of a transposition goes with the column-wise quantization of a weight gradient's operands (m.rows rows, m.Q and cols_y
-// columns): where all workgroups find room on the chip at once, two a CU.  Either has so little to do there that it waits for memory most of
-// the time (fill and quantization by themselves / beside each other, us: 1056 x (1376 + 2080) 15.2 + 8.6 / 15.1, fp32 2048 x (2048 + 2048) 9.9 + 10.8 /
-// 13.6); with more of them the tiles, four a workgroup, take as long as the two launches (8192 x (2048 + 2048) 10.0 + 26.8 / 37.5) or
-// longer (8192 x (2048 + 5504) 10.6 + 38.2 / 58.1, 16384 x (4096 + 12288) 24.8 + 148.5 / 195).
+// Whether pass 3 of a transposition goes with the column-wise quantization of a weight gradient's operands (m.rows rows, m.Q and cols_y columns).
 bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y) {
-  return m.nblocks > 0 && m.Q <= 8192 && m.from != MbFrom::TABLE && cols_beside_per(m.rows, m.Q, cols_y, mb_fill_blocks(m.nblocks)) > 0;
+  return m.nblocks > 0 && fill_beside_per(m.rows, m.Q, cols_y, fp4_compute_units_of_current_device()) > 0;
 }
+int fp4_csr_fill_beside_tiles(int64_t rows, int64_t Q, int64_t cols_y, int n_cu) { return fill_beside_per(rows, Q, cols_y, n_cu); }
 
 // The weight gradient's operands, x [rows x cols] (clamped) and y [rows x cols_y], in as many launches as one of them takes.  part_y:
 // y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.  known:
