@@ -55,9 +55,11 @@ int fp4_select_route(int64_t rows, int64_t cols, int64_t ld, fp4_dtype dt);
 /* What a layer's launches on a device with that many compute units do beside their own work (host arithmetic, no GPU).
  * fp4_select_beside: the first digit pass over A goes with the column-wise codes of W (forward pass, per-tensor thresholds, W not cached);
  * fp4_transpose_beside: the last pass of the residual's transposition with the codes of the weight gradient's operands; both tell how many
- * tiles of 64 columns a workgroup then has (1, 2 or 4), or 0: in launches of their own. */
+ * tiles of 64 columns a workgroup then has (1, 2 or 4), or 0: in launches of their own.  fp4_count_beside: the transposition's first pass, of
+ * a residual of at most capacity entries, goes with the launch that begins fp4_linear_bwd (1) or is one of its own (0). */
 int fp4_select_beside(int64_t M, int64_t K, int64_t N, fp4_dtype dt, int compute_units);
 int fp4_transpose_beside(int64_t M, int64_t K, int64_t N, int compute_units);
+int fp4_count_beside(int64_t M, int64_t K, int64_t N, fp4_dtype dt, int cached, int64_t capacity, int compute_units);
 
 /* The transpose that a weight gradient takes of its residual [P x Q]: CSR of [Q x P], indices ascending in every row.  positions: where
  * the entries' places come from, 1: counts of all row blocks, added up where they are needed, 2: a scan of them over the blocks,

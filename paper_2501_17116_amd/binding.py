@@ -103,6 +103,8 @@ def lib() -> C.CDLL:
         L.fp4_select_beside.restype = i32
         L.fp4_transpose_beside.argtypes = [i64, i64, i64, i32]
         L.fp4_transpose_beside.restype = i32
+        L.fp4_count_beside.argtypes = [i64, i64, i64, i32, i32, i64, i32]
+        L.fp4_count_beside.restype = i32
         L.fp4_residual_transpose_positions.argtypes = [i64, i64]
         L.fp4_residual_transpose_positions.restype = i32
         L.fp4_residual_transpose.argtypes = [vp, vp, vp, vp, i64, i64, i64, i32, vp, vp, vp, vp, sz, vp]
@@ -581,6 +583,11 @@ def fp4_select_beside(M: int, K: int, N: int, dt: int, compute_units: int = 256)
 def fp4_transpose_beside(M: int, K: int, N: int, compute_units: int = 256) -> int:
     """Tiles a workgroup of a weight gradient's codes beside the transposition's last pass, or 0 (host arithmetic, no GPU)."""
     return int(lib().fp4_transpose_beside(M, K, N, compute_units))
+
+
+def fp4_count_beside(M: int, K: int, N: int, dt: int, capacity: int, cached: bool = False, compute_units: int = 256) -> bool:
+    """Whether the transposition's first pass goes with the launch that begins a backward pass (host arithmetic, no GPU)."""
+    return lib().fp4_count_beside(M, K, N, dt, int(cached), capacity, compute_units) == 1
 
 
 def fp4_residual_transpose_positions(P: int, Q: int) -> int:

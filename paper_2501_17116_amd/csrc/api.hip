@@ -51,6 +51,7 @@ int fp4_launch_quantize_cols_pair(const void* x, int bf16, int64_t rows, int64_t
                                   uint8_t* codes_y, float* gamma_y, uint32_t* amax_scratch, bool known, const MbArgs* m, hipStream_t s);
 bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y);
 int fp4_csr_fill_beside_tiles(int64_t rows, int64_t Q, int64_t cols_y, int n_cu);
+bool fp4_csr_count_beside(int bf16, int64_t rows, int64_t Q, int64_t cols, int64_t rows_y, int64_t capacity, int n_cu);
 int fp4_launch_compact_rows(const int32_t* tmp_col, const float* tmp_val, const int32_t* row_cnt, int64_t stride,
                             const int64_t* row_ptr, int64_t rows, int64_t capacity, int32_t* col_idx, float* val,
                             hipStream_t s);
@@ -740,6 +741,11 @@ extern "C" int fp4_select_beside(int64_t M, int64_t K, int64_t N, fp4_dtype dt, 
 extern "C" int fp4_transpose_beside(int64_t M, int64_t K, int64_t N, int compute_units) {
   if (M <= 0 || K <= 0 || N <= 0 || compute_units < 1) return FP4_ERR_SHAPE;
   return fp4_csr_fill_beside_tiles(M, K, N, compute_units);
+}
+
+extern "C" int fp4_count_beside(int64_t M, int64_t K, int64_t N, fp4_dtype dt, int cached, int64_t capacity, int compute_units) {
+  if (M <= 0 || K <= 0 || N <= 0 || capacity < 0 || compute_units < 1 || !dtype_ok(dt)) return FP4_ERR_SHAPE;
+  return fp4_csr_count_beside(dt == FP4_BF16, M, K, N, cached ? 0 : K, std::min(capacity, provisioned_entries(M, K)), compute_units);
 }
 
 extern "C" int fp4_residual_transpose_positions(int64_t P, int64_t Q) { return fp4_csr_transpose_from(P, Q); }

@@ -1270,7 +1270,8 @@ inline int da_rows(int64_t rows, int64_t cols) {
 // A second tensor with as many columns (y; the weights, whose codes the activation gradient needs) goes through the same launch by
 // rows only: the workgroups from `blocks` on have per_y rows of it each.  Apart / together in us: 1056 x 2080 and 1376 rows more 7.8 + 6.8 /
 // 9.9, 8192 x 2048 and 2048 14.9 + 5.5 / 15.0, 4096 x 11008 and 4096 34.7 + 34.1 / 57.7, 4096 x 13824 and 5120 40.9 + 46.1 / 75.5.
-// The workgroups from `blocks_rows` on do the absmax pass of a tensor that is quantized by columns later (the weight gradient's A).
+// Those from beside.first on do the absmax pass of a tensor that is quantized by columns later (the weight gradient's A) and, with
+// COUNT, pass 1 of the residual's transposition.
 // A NaN is no maximum, of a row or of a column, as elsewhere.  Among the magnitudes' patterns it is the largest, so it shows in its row's maximum;
 // the workgroup then takes that once more without it, and at its end the columns' from memory.  All threads branch alike, on one comparison a
 // row: a branch of the thread that has the NaN took 2.5 % of an 8192 x 2048 x 2048 backward pass, NaNs ordered below zero by a packed addition
@@ -1483,25 +1484,68 @@ __global__ __launch_bounds__(256) void quantize_rows_absmax_kernel(RowArgs a, Ro
   else rows_beside<DT, CLAMP, COUNT>(beside, blockIdx.x, sh);
 }
 
-// The workgroups that a launch of `blocks` for its rows has in all, and whether pass 1 of the transposition goes along: where all of
-// them find room on the chip at once, four a CU with the masks' 33 KiB of LDS.
-unsigned beside_blocks(RowsBeside& t, unsigned blocks, unsigned blocks_tail, MbArgs* m) {
-  t.first = blocks;
-  t.count_first = blocks + blocks_tail;
-  if (!m || m->nblocks == 0 || m->Q > COUNT_MAXQ || (int64_t)t.count_first + m->nblocks > 4 * fp4_compute_units_of_current_device()) return t.count_first;
+// Whether pass 1 of the residual's transposition (rows x Q, capacity entries) goes along with `workgroups` others of the launch that begins a
+// backward pass: up to four workgroups a CU, what the masks' 33 KiB of LDS leave (as many are there at once while dY's rows have up to
+// 8192 columns; wider ones' registers allow three or two, which gains as much), and while a row block has little to count.  A workgroup has 256
+// threads for it here, 1024 in a launch of its own, so the entries of a row block, and a part for the masks to clear and read, take it
+// longer, past what the launch saves (2 us) unless its neighbours, the rows of a wide dY, take as long (dual: the kernel for bf16, which has them).  Backward pass
+// without its products, apart / beside, us.  bf16, dY up to 4096 columns wide: 512 x 512 -> 2048, 655 entries a row block, 14.0 / 11.7, 512 x 1376 ->
+// 2080, 4600, 22.6 / 22.9, 5400 24.6 / 25.3, 64 x 2048 -> 2048, 4600, 18.8 / 19.0, 7600 24.2 / 26.2, 512 x 4096 -> 2048, 524, 19.8 / 18.4, 5242 29.7 /
+// 31.8, 52428 145 / 185; wider: 64 x 4096 -> 5504, 5400, 32.7 / 31.4, 6400 34.0 / 33.6, 7600 37.0 / 37.2, 64 x 2048 -> 11008, 7600, 37.9 / 33.9.  fp32: 512 x
+// 1024 -> 2048, 1310, 14.5 / 12.9, 3932 19.4 / 19.2, 64 x 1024 -> 512, 3932, 14.8 / 15.2, 512 x 2048 -> 2048, 2621, 20.9 / 19.9, 7864 33.0 / 36.0.
+bool count_beside(int64_t workgroups, int64_t rows, int64_t Q, int64_t cols, int64_t capacity, bool dual, int n_cu) {
+  const int64_t entries = rows <= 64 ? capacity : capacity / rows * 64 + capacity % rows * 64 / rows;   // of a row block
+  return Q <= COUNT_MAXQ && workgroups + mb_blocks(rows, Q) <= 4 * n_cu && entries + Q / 2 <= (!dual ? 4096 : cols <= 4096 ? 4864 : 7680);
+}
+
+// The launch that begins a backward pass: dY [rows x cols] and rows_y rows of W, the column maxima of A [rows x cols_z] (and, unless dual, of dY).
+struct RowsLayout {
+  bool dual, known;   // dY goes through the dual-axis pass; the maxima are taken along
+  int per;            // dual: rows of dY a workgroup, 4 of W
+  unsigned blocks, blocks_all, blocks_max;   // workgroups for dY, for both, for maxima
+};
+constexpr int ROWS_Y = 4;   // nothing is folded over W's rows, so few are as good
+RowsLayout rows_layout(int bf16, int64_t rows, int64_t cols, int64_t rows_y, int64_t cols_z) {
+  RowsLayout l = {};
+  l.dual = bf16 && cols <= 256 * 8 * 8;
+  // A second read of what the memory-side cache still holds is cheaper than one from memory: where A and dY are more than that, A's
+  // maxima are taken right before its codes.  In us, apart / together: 8192 x 2048 x 2048 step 424 / 416, 4096 x 4096 x 11008 1100 / 1093,
+  // 8192 x 4096 x 11008 backward (247 MB) 1069 / 1061, 16384 x 4096 x 4096 (268 MB) 644 / 642, 16384 x 4096 x 12288 (537 MB) 3604 / 3620.
+  l.known = rows * (cols + cols_z) * (bf16 ? 2 : 4) <= (int64_t)288 << 20;
+  const int64_t width = cols_z + (l.dual ? 0 : cols), in_block = ca_rows(rows, width);
+  l.blocks_max = l.known ? (unsigned)((rows + in_block - 1) / in_block) * (ca_strips(cols_z) + (l.dual ? 0 : ca_strips(cols))) : 0;
+  if (l.dual) {
+    l.per = da_rows(rows, cols);
+    l.blocks = (unsigned)((rows + l.per - 1) / l.per);
+    l.blocks_all = l.blocks + (unsigned)((rows_y + ROWS_Y - 1) / ROWS_Y);
+  } else {
+    rows_shape(cols, [&](auto tpr, auto) {
+      constexpr int RPB = 256 / decltype(tpr)::value;
+      l.blocks_all = (unsigned)((rows + rows_y + RPB - 1) / RPB);
+    });
+  }
+  return l;
+}
+
+// The workgroups of that launch, pass 1 of the transposition m (null: none) among them where it goes along (m->counted).
+unsigned beside_blocks(RowsBeside& t, const RowsLayout& l, int64_t cols, MbArgs* m) {
+  t.first = l.blocks_all;
+  t.count_first = l.blocks_all + l.blocks_max;
+  if (!m || m->nblocks == 0 ||
+      !count_beside(t.count_first, m->rows, m->Q, cols, m->capacity, l.dual, fp4_compute_units_of_current_device()))
+    return t.count_first;
   t.m = *m;
   m->counted = true;
   return t.count_first + (unsigned)m->nblocks;
 }
 
 template <class DT>
-int launch_rows_absmax(const RowArgs& a, RowsBeside& t, unsigned blocks_tail, MbArgs* m, hipStream_t s) {
+int launch_rows_absmax(const RowArgs& a, const RowsBeside& t, unsigned grid, bool count, hipStream_t s) {
   rows_shape(a.cols, [&](auto tpr, auto nv) {
     constexpr int TPR = decltype(tpr)::value, NV = decltype(nv)::value;
-    const unsigned blocks = beside_blocks(t, (unsigned)((a.rows + a.rows2 + 256 / TPR - 1) / (256 / TPR)), blocks_tail, m);
-    if (m && m->counted) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, true>), dim3(blocks), dim3(256), 0, s, a, t);
-    else if (t.absmax.a.thr) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, false>), dim3(blocks), dim3(256), 0, s, a, t);
-    else hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, false, false>), dim3(blocks), dim3(256), 0, s, a, t);
+    if (count) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, true>), dim3(grid), dim3(256), 0, s, a, t);
+    else if (t.absmax.a.thr) hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, true, false>), dim3(grid), dim3(256), 0, s, a, t);
+    else hipLaunchKernelGGL((quantize_rows_absmax_kernel<DT, TPR, NV, false, false>), dim3(grid), dim3(256), 0, s, a, t);
   });
   FP4_CHECK_LAUNCH();
   return FP4_OK;
@@ -1823,46 +1867,41 @@ int fp4_launch_quantize_rows_absmax(const void* x, int bf16, int64_t rows, int64
                                     const void* y, int64_t rows_y, uint8_t* codes_y, float* gamma_y, const void* z, int64_t cols_z,
                                     const float* clamp_thr, int per_row_thr, uint32_t* amax_scratch, bool* dual, bool* known, MbArgs* m, hipStream_t s) {
   if (rows == 0 || cols == 0 || cols_z == 0 || cols % 8 != 0) return FP4_ERR_SHAPE;
-  *dual = bf16 && cols <= 256 * 8 * 8;
+  const RowsLayout l = rows_layout(bf16, rows, cols, y ? rows_y : 0, cols_z);
+  *dual = l.dual;
+  *known = l.known;
   RowsBeside beside = {};
   AbsmaxTail& t = beside.absmax;
   t.a.x = z; t.a.thr = clamp_thr; t.a.thr_stride = per_row_thr ? 2 : 0;
   t.a.rows = rows; t.a.cols = cols_z; t.a.ld = cols_z;
   t.b.x = x; t.b.part16 = *dual ? part16 : nullptr;
   t.b.rows = rows; t.b.cols = cols; t.b.ld = cols;
-  const unsigned row_blocks = absmax_layout(t.a, t.b, amax_scratch);
+  absmax_layout(t.a, t.b, amax_scratch);
   t.strips_a = ca_strips(cols_z);
   t.strips = t.strips_a + (*dual ? 0 : ca_strips(cols));
-  // A second read of what the memory-side cache still holds is cheaper than one from memory: where A and dY are more than that, A's
-  // maxima are taken right before its codes.  In us, apart / together: 8192 x 2048 x 2048 step 424 / 416, 4096 x 4096 x 11008 1100 / 1093,
-  // 8192 x 4096 x 11008 backward (247 MB) 1069 / 1061, 16384 x 4096 x 4096 (268 MB) 644 / 642, 16384 x 4096 x 12288 (537 MB) 3604 / 3620.
-  *known = rows * (cols + cols_z) * (bf16 ? 2 : 4) <= (int64_t)288 << 20;
-  const unsigned blocks_tail = *known ? t.strips * row_blocks : 0;
+  const unsigned grid = beside_blocks(beside, l, cols, clamp_thr ? m : nullptr);
+  const bool count = clamp_thr && m && m->counted;
   if (*dual) {
     const int64_t nunits = cols / 8;
-    const int per = da_rows(rows, cols), per_y = 4;   // nothing is folded over y's rows, so few are as good
-    const unsigned blocks = (unsigned)((rows + per - 1) / per), blocks_y = y ? (unsigned)((rows_y + per_y - 1) / per_y) : 0;
-    const unsigned grid = beside_blocks(beside, blocks + blocks_y, blocks_tail, clamp_thr ? m : nullptr);
-    auto go = [&](auto nv, auto clamp, auto count) {
-      hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value, decltype(clamp)::value, decltype(count)::value>), dim3(grid), dim3(256),
-                         0, s, reinterpret_cast<const uint16_t*>(x), rows, cols, cols, codes, gamma, part16, per, blocks,
-                         reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, per_y, beside);
+    auto go = [&](auto nv, auto clamp, auto with_count) {
+      hipLaunchKernelGGL((quantize_rows_colmax_kernel<decltype(nv)::value, decltype(clamp)::value, decltype(with_count)::value>), dim3(grid), dim3(256),
+                         0, s, reinterpret_cast<const uint16_t*>(x), rows, cols, cols, codes, gamma, part16, l.per, l.blocks,
+                         reinterpret_cast<const uint16_t*>(y), rows_y, codes_y, gamma_y, ROWS_Y, beside);
     };
-    auto width = [&](auto clamp, auto count) {
-      if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{}, clamp, count);
-      else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{}, clamp, count);
-      else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{}, clamp, count);
-      else go(std::integral_constant<int, 8>{}, clamp, count);
+    auto width = [&](auto clamp, auto with_count) {
+      if (nunits <= 256 * 2) go(std::integral_constant<int, 2>{}, clamp, with_count);
+      else if (nunits <= 256 * 4) go(std::integral_constant<int, 4>{}, clamp, with_count);
+      else if (nunits <= 256 * 6) go(std::integral_constant<int, 6>{}, clamp, with_count);
+      else go(std::integral_constant<int, 8>{}, clamp, with_count);
     };
-    if (m && m->counted) width(std::true_type{}, std::true_type{});
+    if (count) width(std::true_type{}, std::true_type{});
     else if (clamp_thr) width(std::true_type{}, std::false_type{});
     else width(std::false_type{}, std::false_type{});
   } else {
     RowArgs a = {};
     a.x = x; a.codes = codes; a.gamma = gamma; a.rows = rows; a.cols = cols; a.ld = cols;
     if (y) { a.x2 = y; a.codes2 = codes_y; a.gamma2 = gamma_y; a.rows2 = rows_y; }
-    const int rc = bf16 ? launch_rows_absmax<BF16>(a, beside, blocks_tail, clamp_thr ? m : nullptr, s)
-                        : launch_rows_absmax<F32>(a, beside, blocks_tail, clamp_thr ? m : nullptr, s);
+    const int rc = bf16 ? launch_rows_absmax<BF16>(a, beside, grid, count, s) : launch_rows_absmax<F32>(a, beside, grid, count, s);
     if (rc) return rc;
   }
   FP4_CHECK_LAUNCH();
@@ -1943,6 +1982,10 @@ bool fp4_csr_fill_beside(const MbArgs& m, int64_t cols_y) {
   return m.nblocks > 0 && fill_beside_per(m.rows, m.Q, cols_y, fp4_compute_units_of_current_device()) > 0;
 }
 int fp4_csr_fill_beside_tiles(int64_t rows, int64_t Q, int64_t cols_y, int n_cu) { return fill_beside_per(rows, Q, cols_y, n_cu); }
+bool fp4_csr_count_beside(int bf16, int64_t rows, int64_t Q, int64_t cols, int64_t rows_y, int64_t capacity, int n_cu) {
+  const RowsLayout l = rows_layout(bf16, rows, cols, rows_y, Q);
+  return count_beside((int64_t)l.blocks_all + l.blocks_max, rows, Q, cols, capacity, l.dual, n_cu);
+}
 
 // The weight gradient's operands, x [rows x cols] (clamped) and y [rows x cols_y], in as many launches as one of them takes.  part_y:
 // y's column maxima as the dual-axis pass left them, or null.  Scratch for a tensor of cols + cols_y columns.  known:

@@ -25,3 +25,22 @@ def test_digit_pass_beside_the_weights(M, K, N, dt, want):
 ])
 def test_transposition_beside_the_codes(M, K, N, want):
     assert b.fp4_transpose_beside(M, K, N) == want
+
+
+@pytest.mark.parametrize("M,K,N,alpha,bf16,f32", [
+    (256, 512, 512, 0.99, 1, 1), (512, 2048, 512, 0.99, 1, 1), (64, 3072, 2048, 0.999, 1, 1), (1024, 1024, 1024, 0.97, 1, 0),
+    # more entries in 64 rows than 256 threads count while the others run: later beside wide rows of bf16
+    (512, 1376, 2048, 0.97, 0, 0), (64, 2048, 2048, 0.97, 0, 0), (512, 4096, 512, 0.99, 0, 0), (64, 3072, 5504, 0.985, 1, 0), (64, 3072, 5504, 0.97, 0, 0),
+    (32, 1376, 11008, 0.9, 0, 0), (48, 96, 96, 0.9, 1, 1),
+    # more than four workgroups a CU; columns beyond the masks
+    (8192, 512, 512, 0.99, 0, 0), (64, 4128, 64, 0.999, 0, 0),
+])
+def test_count_beside_the_rows(M, K, N, alpha, bf16, f32):
+    cap = b.occ_capacity(M, K, alpha)
+    assert b.fp4_count_beside(M, K, N, BF16, cap) == bool(bf16) and b.fp4_count_beside(M, K, N, F32, cap) == bool(f32)
+
+
+def test_count_beside_with_cached_weights_and_any_capacity():
+    assert not b.fp4_count_beside(64, 4096, 64, BF16, 64)          # 1024 workgroups have W's rows
+    assert b.fp4_count_beside(64, 4096, 64, BF16, 64, cached=True)
+    assert not b.fp4_count_beside(64, 1024, 64, BF16, 2 ** 62)     # as many as are provided for

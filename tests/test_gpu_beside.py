@@ -54,3 +54,15 @@ def test_same_as_by_themselves(M, K, N, fill, bf16, f32, scope, dtype):
     parts = b.fp4_gemm(qA, gA, qY, gY, addend=R)
     assert torch.equal(b.fp4_linear_bwd(dY, A, W, ctx, 0.0, 0.0)[1], parts)
     assert torch.equal(b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 0.0, 0.0), parts)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,K,N,alpha", [(32, 32, 32, 0.9), (96, 3072, 96, 0.999), (512, 1376, 2080, 0.99), (512, 1376, 2080, 0.97), (96, 1376, 8224, 0.97),
+                                         (96, 256, 16416, 0.97), (96, 2048, 11040, 0.99)])
+def test_count_beside_the_rows(M, K, N, alpha, dtype):
+    """The transposition's first pass beside the rows of narrow and wide dY (one with a row's units in each of the kernel's forms) and W."""
+    A, W, dY = _inputs(M, K, N, dtype)
+    ctx = b.fp4_linear_fwd(A, W, alpha)[1]
+    want = b.fp4_linear_bwd_wgrad(A, dY, W, ctx, 5.0, 3.0)   # counts in a launch of its own
+    assert torch.equal(b.fp4_linear_bwd(dY, A, W, ctx, 5.0, 3.0)[1], want)
+    assert torch.equal(b.fp4_linear_bwd(dY, A, W, ctx, 5.0, 3.0, wq=b.fp4_prepare_weights(W))[1], want)
