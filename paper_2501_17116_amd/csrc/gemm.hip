@@ -942,9 +942,10 @@ __global__ __launch_bounds__(256) void fp4_gemm_mid_kernel(
 // The same for the smallest outputs (a few tokens): 32 x 32 a workgroup, of which each of the four waves takes every fourth K step.  Such a
 // call is one round trip to memory after another, so there are as many workgroups as can be and a wave has SP_RING steps of its own
 // under way, which it stages, waits for and multiplies without any other; whole lines at a time (a lane of the 64 x 64 tiles reads 16 bytes
-// of its row: 32 lines an instruction).  The waves' sums are multiples of 1/4 below 2^22, so added up they are the same bits
-// as in one chain, and the rest is as above.
+// of its row: 32 lines an instruction).  The waves' sums are multiples of 1/4 below 2^22 (the rule that takes these tiles sees to it), so added
+// up they are the same bits as in one chain, and the rest is as above.
 constexpr int SP_T = 32, SP_OP = SP_T * BKB, SP_STEP = 2 * SP_OP, SP_LD = SP_T / 8;   // SP_LD: 1 KiB requests an operand and step
+static_assert(GEMM_EXACT_CODES / 2 * SP_T <= GEMM_OUT_OF_RANGE, "a tile's rows are within 32-bit offsets");
 template <bool OUT_BF16, bool DGE, bool W_BF16, int RING>
 __global__ __launch_bounds__(256) void fp4_gemm_split_kernel(
     const uint8_t* __restrict__ Lp, const uint8_t* __restrict__ Rp, const float* __restrict__ gl,

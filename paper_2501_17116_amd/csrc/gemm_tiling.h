@@ -11,6 +11,8 @@ struct GemmTiling {
   bool split;    // 32 x 32 tiles instead, whose waves share a contraction
 };
 
+// Codes up to which every sum of products is a multiple of 1/4 below 2^22 (a product is 36 at most), so exact in fp32 in any order.
+constexpr int64_t GEMM_EXACT_CODES = (1 << 22) / 36;
 // Offset past the end of any tile's buffer descriptor while the tile's rows take no more bytes than this.
 constexpr uint32_t GEMM_OUT_OF_RANGE = 0xf0000000u;
 constexpr int GEMM_K_STEP = 128;   // bytes of a row that one stage of the staged tilings holds
@@ -58,10 +60,11 @@ inline bool gemm_small_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, 
 // 4.6 / 4.5, 1376 5.8 / 4.9; two a CU, 64 x 8192, 512 5.5 / 5.1, 2048 9.6 / 6.0, 8192 22 / 10.8, 544 4.6 / 5.4, 1376 6.0 / 5.7; factor, 512 x 512,
 // 128 5.5 / 5.3, 256 5.9 / 5.2, 512 x 1024, 128 5.6 / 6.2, 256 6.2 / 6.0.  Another half round: 96 x 8192, 1024 7.4 / 7.2, 2048 10.2 / 8.1, 8192 23 /
 // 13.8, 2080 7.5 / 8.4, 3168 12.9 / 9.5.  Beyond, the operands' second and third reading counts: 1024 tiles, 4096 codes 13.5 / 11.3 to 13.4 / 13.0, 2048
-// tiles 13.8 / 18.8.
+// tiles 13.8 / 18.8.  Only while sums are exact, or the waves' four would not add up to the bits of the others' one chain.
 inline bool gemm_split_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, int n_cu) {
   const int64_t tiles = ((P + 31) / 32) * ((Q + 31) / 32);
   const bool whole = Kc / 2 % GEMM_K_STEP == 0;
+  if (Kc > GEMM_EXACT_CODES) return false;
   if (tiles <= 2 * (int64_t)n_cu) return Kc >= (factor ? 256 : whole ? 512 : 1120);
   return tiles <= 3 * (int64_t)n_cu && !factor && Kc >= (whole ? 1024 : 3072);
 }
@@ -79,7 +82,7 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
   // The larger tiles address their rows by 32-bit offsets into a descriptor; rows too long for that go to the next smaller
   // one, and the 64 x 64 ones have 64-bit addresses.
   const bool fits_big = Kb * 256 <= (int64_t)GEMM_OUT_OF_RANGE, fits_mid = Kb * 128 <= (int64_t)GEMM_OUT_OF_RANGE;
-  t.split = gemm_split_tiles_win(P, Q, Kc, factor, n_cu) && Kb * 32 <= (int64_t)GEMM_OUT_OF_RANGE;
+  t.split = gemm_split_tiles_win(P, Q, Kc, factor, n_cu);
   // An empty contraction has no K step to request, which the staged tilings do ahead: the operands may be null.
   if (few || !fits_mid || Kb == 0) {
     t.tile = 64;

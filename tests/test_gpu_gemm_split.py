@@ -37,6 +37,24 @@ def test_against_the_exact_product(P, Q, K):
             assert torch.equal(one, big[:P, :Q])
 
 
+@pytest.mark.parametrize("K", [116480, 116512])
+def test_the_longest_exact_sums(K):
+    """Rows of sixes, whose sums are the largest there are: 2^22 is not reached up to 116508 codes, and the next length goes to another tiling."""
+    from paper_2501_17116_amd import binding as b
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or b.fp4_gemm_splits(33, 40, K) == (K == 116480)
+    g = torch.Generator().manual_seed(K)
+    L, R = (torch.randint(0, 256, (n, K // 2), generator=g, dtype=torch.uint8) for n in (33, 40))
+    L[5], R[7], R[8] = 0x77, 0x77, 0xff
+    exact = _values(L).double() @ _values(R).double().t()
+    got = b.fp4_gemm(L.cuda(), None, R.cuda(), None).cpu().double()
+    if K == 116480:
+        assert exact[5, 7] == 36 * K and exact[5, 8] == -36 * K
+        assert torch.equal(got, exact)
+    else:   # half an ulp beyond 2^22 for each 64 codes that are added at a time
+        assert torch.all((got - exact).abs() <= K / 64 * 0.25)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("M,K,N", [(256, 32, 32), (288, 72, 136), (512, 512, 1024), (1056, 1032, 488), (4096, 264, 520)])
 def test_factor(M, K, N, dtype):
