@@ -337,7 +337,7 @@ def gemm_kernels(cfg, layers, torch):
         for P, Q, Kc, factor, addend, out_bf16 in ((l.M, l.N, l.K, False, clamp, bf16), (l.M, l.K, l.N, False, False, bf16),
                                                    (l.K, l.N, l.M, cfg.dge_k > 0, clamp, False)):
             tile, last_round, _ = b.fp4_gemm_tiling(P, Q, Kc, factor, bf16, addend, out_bf16, cus)
-            names.add({64: "fp4_gemm_small_kernel", 128: "fp4_gemm_mid_kernel", 256: "fp4_gemm_nt_kernel"}[tile])
+            names.add({32: "fp4_gemm_split_kernel", 64: "fp4_gemm_small_kernel", 128: "fp4_gemm_mid_kernel", 256: "fp4_gemm_nt_kernel"}[tile])
             if last_round:
                 names.add("fp4_gemm_mid_kernel")
     return " + ".join(sorted(names))

@@ -31,14 +31,14 @@ int fp4_device_round_codes(const float* x, int64_t n, uint8_t* codes, void* stre
 int fp4_device_round_sweep(unsigned long long* mismatches, void* stream);
 
 /* Output tiles the FP4 GEMM [P x Q], contraction Kc, is cut into on a device with that many compute units, by the rule its launches
- * follow (host arithmetic, no GPU): 64, 128 or 256 rows and columns.  With 256, *last_round is the number of tiles of the
+ * follow (host arithmetic, no GPU): 32 (whose waves share a contraction), 64, 128 or 256 rows and columns.  With 256, *last_round is the number of tiles of the
  * last round that are cut into 128 x 128 ones and *stagger how much later than the one before each quarter of the workgroups
  * begins, in 512 cycles; otherwise 0 (either may be NULL).  factor: the weight gradient's derivative factor
  * with weights in bf16 (w_bf16) or fp32; addend: whether there is one; out_bf16: the output's type. */
 int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int w_bf16, int addend, int out_bf16, int compute_units,
                     int* last_round, int* stagger);
 
-/* Whether that GEMM takes 32 x 32 tiles, whose waves share a contraction, in the place of those (1) or not (0) (host arithmetic, no GPU). */
+/* Whether those are 32 (1) or not (0): neither types nor an addend matter for it (host arithmetic, no GPU). */
 int fp4_gemm_splits(int64_t P, int64_t Q, int64_t Kc, int factor, int compute_units);
 
 /* Whether the tiles of one tensor's column-wise quantization form their scales themselves (1) or a launch before them does (0)

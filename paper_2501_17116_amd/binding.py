@@ -652,7 +652,7 @@ def fp4_gemm_tiling(P: int, Q: int, Kc: int, factor: bool = False, w_bf16: bool 
 
 
 def fp4_gemm_splits(P: int, Q: int, Kc: int, factor: bool = False, compute_units: int = 256) -> bool:
-    """Whether an FP4 GEMM takes 32 x 32 tiles in the place of those of fp4_gemm_tiling (host arithmetic, no GPU)."""
+    """Whether fp4_gemm_tiling's tiles are 32 x 32, whatever the types (host arithmetic, no GPU)."""
     return lib().fp4_gemm_splits(P, Q, Kc, int(factor), compute_units) == 1
 
 

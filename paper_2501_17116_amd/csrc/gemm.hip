@@ -1093,7 +1093,7 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   const int n_cu = fp4_compute_units_of_current_device();
   const GemmTiling t = gemm_tiling(P, Q, Kc, dge, w_bf16 != 0, addend != nullptr, out_bf16 != 0, n_cu);
   const int trace_slot = fp4_trace_open(FP4_TRACE_GEMM, stream);
-  const bool ragged = (g.Kb % BKB) != 0, small = t.tile == 64, mid = t.tile == 128;
+  const bool ragged = (g.Kb % BKB) != 0, split = t.tile == 32, small = t.tile == 64, mid = t.tile == 128;
   GemmShape gt = g;
   gt.tiles_p = (int)((P + SP_T - 1) / SP_T);
   gt.tiles_q = (int)((Q + SP_T - 1) / SP_T);
@@ -1115,7 +1115,7 @@ int fp4_launch_gemm(const uint8_t* L, const float* gl, const uint8_t* Rt, const 
   }
 #define FP4_GEMM_LAUNCH(OB, DG, WB)                                                                       \
   do {                                                                                                    \
-    if (t.split) {                                                                                        \
+    if (split) {                                                                                          \
       if (gt.count <= n_cu)                                                                               \
         hipLaunchKernelGGL((fp4_gemm_split_kernel<OB, DG, WB, 4>), dim3((unsigned)((gt.count + 7) / 8 * 8)), dim3(256), 0, stream, L, Rt, \
                            gl, gr, addend, out, W, gamma_w, gt);                                          \
@@ -1181,7 +1181,7 @@ extern "C" int fp4_gemm_tiling(int64_t P, int64_t Q, int64_t Kc, int factor, int
 
 extern "C" int fp4_gemm_splits(int64_t P, int64_t Q, int64_t Kc, int factor, int compute_units) {
   if (P <= 0 || Q <= 0 || Kc < 0 || (Kc % 32) != 0 || compute_units < 8) return FP4_ERR_SHAPE;
-  return gemm_tiling(P, Q, Kc, factor != 0, false, false, false, compute_units).split ? 1 : 0;
+  return gemm_tiling(P, Q, Kc, factor != 0, false, false, false, compute_units).tile == 32;
 }
 
 extern "C" int fp4_unpack(const uint8_t* codes, int64_t rows, int64_t cols, uint8_t* one_per_byte,

@@ -5,10 +5,9 @@
 #include <algorithm>
 
 struct GemmTiling {
-  int tile;      // 64, 128 or 256: rows and columns of an output tile
+  int tile;      // 32 (whose waves share a contraction), 64, 128 or 256: rows and columns of an output tile
   int rest;      // 256: tiles of the last round that are cut into 128 x 128 ones
   int stagger;   // 256: how much later than the one before each quarter of the workgroups begins, in 512 cycles
-  bool split;    // 32 x 32 tiles instead, whose waves share a contraction
 };
 
 // Codes up to which every sum of products is a multiple of 1/4 below 2^22 (a product is 36 at most), so exact in fp32 in any order.
@@ -39,9 +38,7 @@ inline bool gemm_small_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, 
     return Kc <= (factor ? with_factor : plain)[r];
   }
   static constexpr int plain[4] = {6144, 1088, 448, 0}, with_factor[4] = {8448, 2336, 1184, 0}, with_f32_factor[4] = {8448, 2336, 1376, 640};
-  int limit = (factor ? (w_bf16 ? with_factor : with_f32_factor) : plain)[r];
-  if (P <= 32 && !factor && r == 0) limit *= 2;   // half of a 64-row tile re-reads its last row (32 x 2976, 6368 codes 14.6 / 16.9)
-  if (Kc > limit) return false;
+  if (Kc > (factor ? (w_bf16 ? with_factor : with_f32_factor) : plain)[r]) return false;
   if (Kc <= 1024 || tp == 1 || tq == 1) return true;
   // An operand row is read once for every tile that needs it, so the rows that an XCD's tiles need (they are dealt round, column by
   // column) have to stay in its 4 MiB of L2: 320 x 3200, 2592 / 3616 codes, 3.0 / 4.3 MB: 0.92 / 1.13; 512 x 2048, 3104 / 4640, 3.3 / 4.9
@@ -70,8 +67,12 @@ inline bool gemm_split_tiles_win(int64_t P, int64_t Q, int64_t Kc, bool factor, 
 }
 
 inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, bool w_bf16, bool addend, bool out_bf16, int n_cu) {
-  GemmTiling t = {256, 0, 0, false};
+  GemmTiling t = {256, 0, 0};
   const int64_t Kb = Kc / 2;
+  if (gemm_split_tiles_win(P, Q, Kc, factor, n_cu)) {
+    t.tile = 32;
+    return t;
+  }
   const bool few = gemm_small_tiles_win(P, Q, Kc, factor, w_bf16, n_cu);
   // 128 x 128, up to two per CU: 4096 x 2048, 1024 / 8192 codes, fp32 with addend, as 64 / 128 / 256 tiles in us: 40 / 22.6 / 24.8 and
   // 237 / 54 / 58; past it 2816 x 3072, 4096 140 / 48 / 38.  With the factor one (2048 x 4096 x 4096 bf16 172 / 87 / 86).  With fp32
@@ -82,7 +83,6 @@ inline GemmTiling gemm_tiling(int64_t P, int64_t Q, int64_t Kc, bool factor, boo
   // The larger tiles address their rows by 32-bit offsets into a descriptor; rows too long for that go to the next smaller
   // one, and the 64 x 64 ones have 64-bit addresses.
   const bool fits_big = Kb * 256 <= (int64_t)GEMM_OUT_OF_RANGE, fits_mid = Kb * 128 <= (int64_t)GEMM_OUT_OF_RANGE;
-  t.split = gemm_split_tiles_win(P, Q, Kc, factor, n_cu);
   // An empty contraction has no K step to request, which the staged tilings do ahead: the operands may be null.
   if (few || !fits_mid || Kb == 0) {
     t.tile = 64;

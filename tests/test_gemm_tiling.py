@@ -26,15 +26,17 @@ def test_an_empty_contraction_runs_where_nothing_is_requested_ahead(P, Q):
 
 # (P, Q, Kc, factor, w_bf16, addend, tile): either side of the lines, and shapes that were measured far from them
 LINES = [
+    # the smallest outputs: 32 x 32, up to two a CU, three without the factor (test_gemm_split_route.py)
+    (64, 2048, 2048, 0, 0, 1, 32), (512, 512, 256, 1, 0, 0, 32), (512, 1536, 4096, 0, 0, 0, 32), (512, 1568, 4096, 0, 0, 0, 128),
     # rows of whole 128-byte lines: one round of 64 x 64 tiles, two, three
     (512, 2048, 1280, 0, 0, 0, 64), (512, 2048, 1536, 0, 0, 0, 128), (520, 2048, 256, 0, 0, 0, 64), (520, 2048, 512, 0, 0, 0, 128),
     (1032, 2048, 256, 0, 0, 0, 128), (512, 2048, 3072, 1, 1, 0, 64), (512, 2048, 3328, 1, 1, 0, 128), (520, 2048, 768, 1, 1, 1, 64),
     (520, 2048, 1024, 1, 1, 1, 128), (1032, 2048, 256, 1, 0, 1, 64), (1032, 2048, 512, 1, 0, 1, 128),
     # others
-    (192, 1216, 1216, 0, 0, 0, 64), (32, 704, 1056, 0, 0, 0, 64), (224, 1408, 1312, 0, 0, 1, 64), (512, 512, 6144 - 32, 0, 0, 0, 64),
-    (512, 512, 6176, 0, 0, 0, 128), (32, 512, 6176, 0, 0, 0, 64), (520, 2048, 1056, 0, 0, 0, 64), (520, 2048, 1120, 0, 0, 0, 128),
-    (1032, 2048, 416, 0, 0, 0, 64), (1032, 2048, 480, 0, 0, 0, 128), (1024, 832, 6016, 1, 1, 0, 64), (512, 512, 8416, 1, 1, 0, 64),
-    (512, 512, 8480, 1, 1, 0, 128), (520, 2048, 1312, 1, 1, 0, 64), (1280, 1280, 2400, 1, 1, 0, 128), (1032, 2048, 1184, 1, 1, 0, 64), (1032, 2048, 1248, 1, 1, 0, 128),
+    (192, 4128, 1216, 0, 0, 0, 64), (32, 704, 1056, 0, 0, 0, 64), (224, 3520, 1312, 0, 0, 1, 64), (64, 16384, 6144 - 32, 0, 0, 0, 64),
+    (64, 16384, 6176, 0, 0, 0, 128), (520, 2048, 1056, 0, 0, 0, 64), (520, 2048, 1120, 0, 0, 0, 128),
+    (1032, 2048, 416, 0, 0, 0, 64), (1032, 2048, 480, 0, 0, 0, 128), (1024, 832, 6016, 1, 1, 0, 64), (64, 16384, 8416, 1, 1, 0, 64),
+    (64, 16384, 8480, 1, 1, 0, 128), (520, 2048, 1312, 1, 1, 0, 64), (1280, 1280, 2400, 1, 1, 0, 128), (1032, 2048, 1184, 1, 1, 0, 64), (1032, 2048, 1248, 1, 1, 0, 128),
     (1032, 2048, 1376, 1, 0, 0, 64), (672, 5496, 384, 1, 0, 0, 64), (672, 5496, 672, 1, 0, 0, 128),
     # what an XCD's tiles need of the operands beyond its L2
     (320, 3200, 2592, 0, 0, 0, 64), (320, 3200, 3616, 0, 0, 0, 128), (512, 2048, 3104, 0, 0, 0, 64), (512, 2048, 4640, 0, 0, 0, 128),

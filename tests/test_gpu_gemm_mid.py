@@ -13,7 +13,7 @@ def _values(codes):
     return GRID[torch.stack([codes & 15, codes >> 4], -1).reshape(codes.shape[0], -1).long()]
 
 
-@pytest.mark.parametrize("P,Q,K", [(1, 8, 1056), (127, 136, 1280), (128, 128, 1312), (129, 1000, 2048), (2048, 2048, 32),
+@pytest.mark.parametrize("P,Q,K", [(1, 8, 1056), (127, 136, 1280), (128, 128, 1312), (129, 1000, 2048), (2048, 2048, 32),   # 64 x 64 and 32 x 32
                                    (2049, 2056, 288), (2176, 3840, 1024), (4096, 2048, 544),      # 128 x 128; 512 of them
                                    (4096, 2056, 544), (2816, 3080, 32), (2816, 3072, 288), (4352, 4096, 992),   # 256 x 256
                                    (4104, 4104, 32), (4224, 4232, 544), (4352, 4352, 1024), (5120, 4096, 160)])   # and a last round in quarters
@@ -33,9 +33,9 @@ def test_products(P, Q, K):
     assert torch.equal(b.fp4_gemm(L, gl, R, gr, addend=addend), scaled + addend)
 
 
-@pytest.mark.parametrize("P,Q,K", [(33, 8, 1536), (127, 136, 1792), (128, 128, 6176), (129, 264, 6208), (127, 392, 6304), (1, 8, 12320)])
+@pytest.mark.parametrize("P,Q,K", [(33, 12296, 1536), (127, 6152, 1792), (128, 6272, 6176), (129, 5000, 6208), (127, 6280, 6304), (1, 24584, 1536)])
 def test_edges_of_a_tile(P, Q, K):
-    """Contractions long enough for 128 x 128 tiles however few there are."""
+    """Contractions long enough for 128 x 128 tiles, at the fewest rows and outputs just past what 32 x 32 tiles take."""
     from paper_2501_17116_amd import binding as b
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert b.fp4_gemm_tiling(P, Q, K)[0] == 128

@@ -62,7 +62,7 @@ def test_an_empty_contraction(P, Q):
 
 @pytest.mark.parametrize("P,Q,K,tile", [(512, 2048, 1280, 64), (512, 2048, 1536, 128), (520, 2048, 256, 64), (520, 2048, 512, 128),
                                         (520, 2056, 1056, 64), (520, 2056, 1120, 128), (1032, 2056, 416, 64), (1032, 2056, 480, 128),
-                                        (512, 512, 6112, 64), (32, 520, 6176, 64), (40, 520, 6176, 128)])
+                                        (192, 4136, 4384, 64), (192, 4136, 4416, 128), (776, 1032, 1120, 64), (776, 1032, 1536, 128)])
 def test_either_side_of_the_lines_between_the_tilings(P, Q, K, tile):
     """Under scales of any value: the rows of a problem that the 256 x 256 tiles take, to the last bit."""
     from paper_2501_17116_amd import binding as b
@@ -82,12 +82,15 @@ def test_either_side_of_the_lines_between_the_tilings(P, Q, K, tile):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("M,K,N", [(3072, 512, 2048), (3328, 512, 2048), (768, 520, 2048), (1024, 520, 2048), (256, 1032, 2048), (512, 1032, 2048),
-                                   (6016, 1024, 832), (8480, 512, 512), (8480, 264, 136), (3328, 136, 264), (1312, 520, 2048), (2400, 1280, 1280), (1184, 1032, 2048),
+                                   (6016, 1024, 832), (8480, 512, 512), (8480, 264, 136), (3328, 136, 264),   # 32 x 32, three of them
+                                   (8160, 1024, 1024), (8224, 1024, 1024), (8224, 904, 1032), (3328, 904, 1032), (1312, 520, 2048), (2400, 1280, 1280), (1184, 1032, 2048),
                                    (1376, 1032, 2048), (1408, 1032, 2048), (640, 672, 5496), (672, 672, 5496)])
 def test_factor_on_either_side_of_the_lines(M, K, N, dtype):
     """The weight gradient against its parts called one by one: the product is the same to the last bit, the factor one
     rounding of fp32 in either."""
     from paper_2501_17116_amd import binding as b
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (b.fp4_gemm_tiling(K, N, M, True, dtype == torch.bfloat16)[0] == 32) == (K * N <= 512 * 1024 and M >= 256)
     torch.manual_seed(M + N)
     A, W, dY = (t.to(dtype) for t in (torch.randn(M, K, device="cuda"), torch.randn(K, N, device="cuda") * 0.02, torch.randn(M, N, device="cuda")))
     _, ctx = b.fp4_linear_fwd(A[:, :K // 32 * 32].contiguous(), W[:K // 32 * 32].contiguous(), 1.0)
