@@ -589,8 +589,7 @@ extern "C" int fp4_linear_bwd_dgrad_cached(const void* dY, const fp4_weight_cach
 }
 
 namespace {
-// The saved residual's transpose, but for what goes with other launches: m's passes that they have taken (m.counted, m.scanned), and its
-// last pass (beside).
+// The saved residual's transpose, but for what goes with other launches: m's first pass (m.counted) and its last (beside).
 int transpose_residual(const fp4_fwd_ctx* saved, int64_t M, int64_t K, int64_t cap, const WgradWs& w, const MbArgs& m, bool beside,
                        hipStream_t s) {
   if (m.nblocks > 0) return fp4_launch_csr_mask(m, !beside, s);

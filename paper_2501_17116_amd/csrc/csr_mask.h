@@ -1,5 +1,5 @@
-// Transpose of a CSR matrix as a stable counting sort on the column, for column ranges that fit the LDS masks: its passes, which run
-// by themselves (spmm.hip) or beside the quantization passes of the backward pass (quantize.hip).
+// Transpose of a CSR matrix as a stable counting sort on the column, for column ranges that fit the LDS masks: passes 1 and 3, which run
+// by themselves (spmm.hip, as pass 2 does) or beside the quantization passes of the backward pass (quantize.hip).
 //
 // The rows are cut into blocks of 64 (32, mb_rows).  Inside a block, column c's entries are described by a 64-bit
 // mask of the rows that hold one (built with LDS atomic ORs: the result does not depend on their
@@ -45,7 +45,7 @@ struct MbArgs {
   uint8_t* cnt8;   // [blocks][Q]
   int nblocks;
   MbFrom from;
-  bool counted, scanned;   // passes that have been launched elsewhere
+  bool counted;   // pass 1 has been launched elsewhere
 };
 
 inline int64_t mb_blocks(int64_t P, int64_t Q) { return std::max<int64_t>(1, (P + mb_rows(Q) - 1) / mb_rows(Q)); }
@@ -135,43 +135,6 @@ FP4_D void mb_count(const MbArgs& m, unsigned block, MbCountShared<QMAX>& sh) {
   uint8_t* out = m.cnt8 + (int64_t)block * m.Q;
   for (int c = threadIdx.x; c < m.Q; c += THREADS)
     out[c] = (uint8_t)(__popc(sh.mask[MW * c]) + (MW > 1 ? __popc(sh.mask[MW * c + MW - 1]) : 0));
-}
-
-struct MbScanShared { uint32_t q[4][64]; };
-
-// 64 columns per 256 threads (tid: of them); the four waves split the blocks into quarters: sum, exchange, rescan.
-FP4_D void mb_scan(const MbArgs& m, unsigned strip, int tid, MbScanShared& sh) {
-  const int lane = tid & 63, quarter = tid >> 6;
-  const int64_t Q = m.Q, c = (int64_t)strip * 64 + lane;
-  const int per = (m.nblocks + 3) / 4;
-  const int b0 = quarter * per, b1 = min(m.nblocks, b0 + per);
-  uint32_t sum = 0;
-  if (c < Q) {
-    int bi = b0;
-    for (; bi + 15 < b1; bi += 16) {   // sixteen independent loads at a time
-      uint32_t v[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) v[j] = m.cnt8[(int64_t)(bi + j) * Q + c];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sum += v[j];
-    }
-    for (; bi < b1; ++bi) sum += m.cnt8[(int64_t)bi * Q + c];
-  }
-  sh.q[quarter][lane] = sum;
-  __syncthreads();
-  if (c >= Q) return;
-  uint32_t run = 0;
-  for (int q = 0; q < quarter; ++q) run += sh.q[q][lane];
-  if (quarter == 3) m.cnt[c] = (int32_t)(run + sum);
-  int bi = b0;
-  for (; bi + 15 < b1; bi += 16) {
-    uint32_t v[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = m.cnt8[(int64_t)(bi + j) * Q + c];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) { m.ex[(int64_t)(bi + j) * Q + c] = run; run += v[j]; }
-  }
-  for (; bi < b1; ++bi) { m.ex[(int64_t)bi * Q + c] = run; run += m.cnt8[(int64_t)bi * Q + c]; }
 }
 
 template <int QMAX, MbFrom FROM>

@@ -22,7 +22,6 @@ FP4_D void static_for4(F&& f) {
   f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
-
 template <class DT>
 FP4_D void load8(const void* base, int64_t off, int valid, float (&v)[8]) {
   if (valid >= 8) {

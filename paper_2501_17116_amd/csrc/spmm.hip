@@ -768,9 +768,40 @@ __global__ __launch_bounds__(MB_THREADS) void csr_mask_count_kernel(MbArgs m) {
   mb_count<QMAX, MB_THREADS>(m, blockIdx.x, sh);
 }
 
+// 64 columns a workgroup; its four waves split the blocks into quarters: sum, exchange, rescan.
 __global__ __launch_bounds__(256) void csr_mask_scan_kernel(MbArgs m) {
-  __shared__ MbScanShared sh;
-  mb_scan(m, blockIdx.x, threadIdx.x, sh);
+  const int lane = threadIdx.x & 63, quarter = threadIdx.x >> 6;
+  const int64_t Q = m.Q, c = (int64_t)blockIdx.x * 64 + lane;
+  const int per = (m.nblocks + 3) / 4;
+  const int b0 = quarter * per, b1 = min(m.nblocks, b0 + per);
+  __shared__ uint32_t s_q[4][64];
+  uint32_t sum = 0;
+  if (c < Q) {
+    int bi = b0;
+    for (; bi + 15 < b1; bi += 16) {   // sixteen independent loads at a time
+      uint32_t v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v[j] = m.cnt8[(int64_t)(bi + j) * Q + c];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) sum += v[j];
+    }
+    for (; bi < b1; ++bi) sum += m.cnt8[(int64_t)bi * Q + c];
+  }
+  s_q[quarter][lane] = sum;
+  __syncthreads();
+  if (c >= Q) return;
+  uint32_t run = 0;
+  for (int q = 0; q < quarter; ++q) run += s_q[q][lane];
+  if (quarter == 3) m.cnt[c] = (int32_t)(run + sum);
+  int bi = b0;
+  for (; bi + 15 < b1; bi += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = m.cnt8[(int64_t)(bi + j) * Q + c];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) { m.ex[(int64_t)(bi + j) * Q + c] = run; run += v[j]; }
+  }
+  for (; bi < b1; ++bi) { m.ex[(int64_t)bi * Q + c] = run; run += m.cnt8[(int64_t)bi * Q + c]; }
 }
 
 template <int QMAX, MbFrom FROM>
@@ -968,7 +999,7 @@ int64_t fp4_csr_transpose_scratch_words(int64_t P, int64_t Q) {
 
 int fp4_csr_transpose_from(int64_t P, int64_t Q) { return (int)mb_from(P, Q); }
 
-// The passes that other launches have not taken along (m.counted, m.scanned; m.nblocks > 0).
+// The passes that other launches have not taken along (m.counted, and the last unless fill_too; m.nblocks > 0).
 int fp4_launch_csr_mask(const MbArgs& m, bool fill_too, hipStream_t s) {
   using Q4 = std::integral_constant<int, 4096>;
   using Q8 = std::integral_constant<int, 8192>;
@@ -978,7 +1009,7 @@ int fp4_launch_csr_mask(const MbArgs& m, bool fill_too, hipStream_t s) {
   };
   if (!m.counted)
     width([&](auto q) { hipLaunchKernelGGL((csr_mask_count_kernel<decltype(q)::value>), dim3(m.nblocks), dim3(MB_THREADS), 0, s, m); });
-  if (m.from != MbFrom::FEW && !m.scanned)
+  if (m.from != MbFrom::FEW)
     hipLaunchKernelGGL(csr_mask_scan_kernel, dim3((unsigned)((m.Q + 63) / 64)), dim3(256), 0, s, m);
   FP4_CHECK_LAUNCH();
   if (!fill_too) return FP4_OK;

@@ -12,7 +12,6 @@
 
 namespace {
 
-
 constexpr int GA_AHEAD = 8;
 constexpr int GA_LONG = 256;         // entries up to which no row is long
 constexpr int GA_LONG_COLS = 4096;   // columns up to which long rows are as others
