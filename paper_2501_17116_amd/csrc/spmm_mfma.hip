@@ -12,7 +12,7 @@
 // matrix instruction wants two rows of one column: v_perm_b32 turned eight rows x eight columns around, 32 a step.  The 2:4 sparse
 // instruction (v_smfmac_f32_16x16x64_bf16) takes them as they came: of every four adjacent k values, here two columns of two rows, it
 // multiplies two, the first column's or the second's as its index says, so that the same registers serve for both columns, and the
-// eight registers of eight rows have only to be put side by side (26 v_mov_b32 a step; 12 v_swap_b32, or v_pk_mov_b32, take as long).
+// eight registers of eight rows have only to be put side by side (30 v_mov_b32 a step; 12 v_swap_b32, or v_pk_mov_b32, take as long).
 // A step of a SIMD alone, three waves of three groups: 155 -> 122 ns.  The product with its packing, at 2 %, us: 16384 x 4096 -> 12288
 // 826 -> 813, 4096 x 16384 -> 12288 787 -> 764, 16384 x 11008 -> 4096 669 -> 652, 8192 x 4096 -> 11008 377 -> 360, 4096 x 8192 ->
 // 11008 397 -> 377 (1 to 2 % of it from not waiting for operands at each phase, at `plan`).
@@ -22,10 +22,10 @@
 // how many steps a group runs in each phase (a prefix of its slots, S[phase]): the steps stay full and the
 // waves of a workgroup in step with each other although the entries of a chunk are few and random.
 //
-// Bound: a SIMD's vector instructions (34 a step beside the matrix core's 8, which have 16 cycles each) and the return of its LDS reads, which
-// do not overlap: reads alone 62 ns a step, with the matrix core 84, with the moves 122; nine wave-steps of the fullest SIMD where there
-// are 8.25 on average; of 16384 x 4096 -> 12288's 813 us about 190 are what the sums' way to memory costs, mostly by making the loads wait.
-// The same with plain fp32 FMAs fed from LDS (spmm.hip): 1423 us; 6 %: 1347 against 2961 us; 0.2 %: 515 against 609 us.
+// Bound: a SIMD's vector instructions (38 a step beside the matrix core's 8, which have 16 cycles each) and the return of its LDS reads, which
+// do not overlap: reads alone 62 ns a step, with the matrix core 84, with the moves 122.  Another 6 to 11 vector instructions a step
+// are the sums' way to memory, the staging wave's and the phases'.  16384 x 4096 -> 12288 with its packing: 805 us at 2 % (650 without the stores of
+// the sums, which mostly make the loads wait), 1364 at 6 % (1260), 514 at 0.2 % (384).  With plain fp32 FMAs fed from LDS (spmm.hip) 1423, 2961 and 609.
 #include "fp4_common.h"
 #include "spmm_long.h"
 
@@ -592,9 +592,13 @@ int fp4_launch_spmm_mfma(const int64_t* row_ptr, const int32_t* col_idx, const f
     static_assert(G <= 3, "the rest's bundles");
   };
   // A phase takes a workgroup about as long as 300 of its rows do, whatever their number (staging, the barrier), and 256 workgroups run at
-  // a time.  So: the shape with the fewest rounds x (300 + rows), but a smaller one only where it saves a tenth on the larger: in many
-  // rounds workgroups drift apart and the last round's size matters less, in sparse matrices the rows do (0.1 %, 5120 x 4096 -> 13824, five rounds
-  // of 528 or six of 384, 1 % less by this count: 207 / 227 us).  Multiplying waves are whole numbers a SIMD beside the staging ones (8: two, 12: three, 11 + 1: three), and rows come in the halves and quarters of which row counts are made.
+  // a time.  So: the shape with the fewest rounds x (300 + rows), but a smaller one only where it saves a tenth on the larger.  That tenth
+  // decides between 528 and 384 rows alone, in grids of several rounds, where 384 save up to 4 % by this count: about as fast at 2 % of entries, slower
+  // where they are few, which the sizes don't tell, faster where they are many.  528 / 384, us, at 0.2, 2 and 6 %: 5120 x 4096 -> 13824 208 / 226,
+  // 308 / 307, 531 / 501; 12288 x 4096 -> 5504 192 / 214, 298 / 302, 541 / 506; 6144 x 5120 -> 13824 306 / 318, 442 / 428, 763 / 713; 5856 x 2048 ->
+  // 13824 148 / 160, 202 / 206, 325 / 313.  Multiplying waves are whole numbers a SIMD beside the staging ones (8: two, 12: three, 11 + 1:
+  // three), and rows come in the halves and quarters of which row counts are made; the sixteen rows that 128 and 192 have more than 112 and 176
+  // cost nothing (within one round of either, 3584 x 8192 -> 1024 at 0.2, 2 and 6 % 61 / 61, 74 / 73, 117 / 114, 1408 x 8192 -> 4096 64 / 64, 80 / 78, 122 / 118).
   // Products, their packing and long rows included, 528 / 384 / 256 / 192 / 128 rows, us, the one taken in brackets; at 2 %
   // 2048 x 8192 -> 2048 123 / 110 / 95 / 83 / (76), 3072 x 8192 -> 2048 124 / 110 / 97 / (87) / 122, 4096 x 8192 -> 2048 126 / 112 / (100) / 140 /
   // 126, 5504 x 2048 -> 4096 92 / (84) / 93 / 103 / 120, 4096^3 (82) / 110 / 96 / 113 / 128, 4096 x 4096 -> 11008 (192) / 203 / 235 / 267 / 308,
